@@ -20,9 +20,6 @@
 #include "coop_internal.h"
 #include "device_utils.h"
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
 namespace coop {
 
 constexpr int kSelBits = 8;  // most bits per radix-select pass: 256 counters, so that merging the blocks' counts into the
@@ -82,105 +79,92 @@ __global__ __launch_bounds__(kBlock) void k_cache_split(const uint64_t* __restri
 }
 
 // ---- row movers -----------------------------------------------------------------------------------------------
-// Rows are moved by lpr = 2^lpr_log2 adjacent lanes, V-sized vectors, kRowUnroll rows per thread in flight.
-template <typename V>
-__global__ __launch_bounds__(kBlock) void k_cache_hits(const V* __restrict__ rows, int32_t vecs, int lpr_log2,
-                                                       const OrderEntry* __restrict__ order,
-                                                       const CacheCtl* __restrict__ ctl, V* __restrict__ out,
+// Rows are moved as the plain gather moves them: their items (device_utils.h) dealt to the threads in order, kRowUnroll
+// per thread in flight.  The thread with a row's first item also keeps that row's books.
+template <int VB>
+__global__ __launch_bounds__(kBlock) void k_cache_hits(const char* __restrict__ rows, RowShape sh, const OrderEntry* __restrict__ order,
+                                                       const CacheCtl* __restrict__ ctl, char* __restrict__ out,
                                                        uint64_t* __restrict__ stamp, uint64_t clock) {
   const int64_t n_hit = ctl->n_hit;  // known on the device before the host has read it
-  const int lpr = 1 << lpr_log2;
-  const int rows_per_block = kBlock >> lpr_log2;
-  const int sub = threadIdx.x & (lpr - 1);
-  const int64_t row0 = ((int64_t)blockIdx.x * kRowUnroll) * rows_per_block + (threadIdx.x >> lpr_log2);
-  if ((int64_t)blockIdx.x * kRowUnroll * rows_per_block >= n_hit) return;
-  int64_t src[kRowUnroll], dst[kRowUnroll];
+  const BlockItems items((int64_t)blockIdx.x * (kBlock * kRowUnroll), sh.vecs);
+  if (items.row0 >= n_hit) return;
+  int64_t src[kRowUnroll], dst[kRowUnroll], hit[kRowUnroll];
+  int32_t slot[kRowUnroll];  // the cache slot, in the thread with the row's first item; else -1
 #pragma unroll
   for (int u = 0; u < kRowUnroll; ++u) {
-    const int64_t r = row0 + (int64_t)u * rows_per_block;  // r-th hit
-    src[u] = -1;
-    dst[u] = 0;
-    if (r < n_hit) {
-      const OrderEntry e = order[r];
-      src[u] = e.from;
-      dst[u] = e.i;
-    }
+    uint32_t item;
+    hit[u] = items.row_of((uint32_t)(u * kBlock) + threadIdx.x, sh, &item);  // r-th hit
+    const bool is = hit[u] < n_hit;
+    const OrderEntry e = order[is ? hit[u] : n_hit - 1];
+    const int64_t at = BlockItems::byte_of<VB>(item, sh);
+    src[u] = (int64_t)e.from * sh.row_bytes + at;
+    dst[u] = is ? (int64_t)e.i * sh.row_bytes + at : -1;
+    slot[u] = is && item == 0 ? e.from : -1;
   }
-  for (int32_t v = sub; v < vecs; v += lpr) {
-    V x[kRowUnroll];
+  typename RowVec<VB>::T x[kRowUnroll];
 #pragma unroll
-    for (int u = 0; u < kRowUnroll; ++u)
-      if (src[u] >= 0) x[u] = __builtin_nontemporal_load(rows + src[u] * vecs + v);  // (a cached row is read at most once per call)
+  for (int u = 0; u < kRowUnroll; ++u)
+    x[u] = row_load_nt<VB>(rows + src[u]);  // (a cached row is read at most once per call)
 #pragma unroll
-    for (int u = 0; u < kRowUnroll; ++u)
-      if (src[u] >= 0) __builtin_nontemporal_store(x[u], out + dst[u] * vecs + v);
-  }
+  for (int u = 0; u < kRowUnroll; ++u)
+    if (dst[u] >= 0) row_store_nt<VB>(out + dst[u], x[u]);
   // the new stamps go out behind the rows: memory operations complete in the order in which they were sent, and the row
   // loads must not wait for these scattered stores
-  if (sub == 0) {
 #pragma unroll
-    for (int u = 0; u < kRowUnroll; ++u)
-      if (src[u] >= 0) stamp[src[u]] = clock + (uint64_t)(row0 + (int64_t)u * rows_per_block);
-  }
+  for (int u = 0; u < kRowUnroll; ++u)
+    if (slot[u] >= 0) stamp[slot[u]] = clock + (uint64_t)hit[u];
 }
 
-template <typename V>
-__global__ __launch_bounds__(kBlock) void k_cache_misses(const V* __restrict__ table, int32_t vecs, int lpr_log2,
-                                                         const OrderEntry* __restrict__ order,
-                                                         int64_t n_ids, V* __restrict__ out, V* __restrict__ rows,
+template <int VB>
+__global__ __launch_bounds__(kBlock) void k_cache_misses(const char* __restrict__ table, RowShape sh, const OrderEntry* __restrict__ order,
+                                                         int64_t n_ids, char* __restrict__ out, char* __restrict__ rows,
                                                          int32_t* __restrict__ slot_of, int32_t* __restrict__ vertex_of,
                                                          uint64_t* __restrict__ stamp, const int32_t* __restrict__ free_list,
                                                          int64_t n_free, int64_t n_miss, int64_t n_ins, uint64_t clock_miss,
                                                          int64_t table_rows) {
-  const int lpr = 1 << lpr_log2;
-  const int rows_per_block = kBlock >> lpr_log2;
-  const int sub = threadIdx.x & (lpr - 1);
-  const int64_t row0 = ((int64_t)blockIdx.x * kRowUnroll) * rows_per_block + (threadIdx.x >> lpr_log2);
-  int64_t src[kRowUnroll], dst[kRowUnroll], dst_slot[kRowUnroll];
-  int32_t src_id[kRowUnroll];  // the vertex itself (src is its row in the table, which may be aliased)
+  const BlockItems items((int64_t)blockIdx.x * (kBlock * kRowUnroll), sh.vecs);
+  int64_t src[kRowUnroll], dst[kRowUnroll], keep[kRowUnroll], miss[kRowUnroll];
+  int32_t slot[kRowUnroll];    // the slot that the row enters; -1: it does not, or another thread keeps its books
+  int32_t vertex[kRowUnroll];
 #pragma unroll
   for (int u = 0; u < kRowUnroll; ++u) {
-    const int64_t rank_m = row0 + (int64_t)u * rows_per_block;  // rank_m-th miss
-    src[u] = -1;
-    dst[u] = 0;
-    dst_slot[u] = -1;
-    src_id[u] = 0;
-    if (rank_m < n_miss) {
-      const OrderEntry e = order[n_ids - 1 - rank_m];
-      const int32_t i = e.i, id = e.from;
-      if (id >= 0) {  // ids out of range were reported by the lookup; negative ones are skipped here
-        src[u] = id < table_rows ? id : id % table_rows;
-        src_id[u] = id;
-        dst[u] = i;
-        const int64_t q = rank_m - (n_miss - n_ins);  // the last n_ins misses enter the cache
-        if (q >= 0) dst_slot[u] = free_list[n_free - 1 - q];
-      }
-    }
+    uint32_t item;
+    miss[u] = items.row_of((uint32_t)(u * kBlock) + threadIdx.x, sh, &item);  // r-th miss
+    const bool is = miss[u] < n_miss;
+    const OrderEntry e = order[n_ids - 1 - (is ? miss[u] : n_miss - 1)];
+    const int64_t q = miss[u] - (n_miss - n_ins);  // the last n_ins misses enter the cache
+    int32_t to = -1;
+    if (is && q >= 0) to = free_list[n_free - 1 - q];
+    const int64_t at = BlockItems::byte_of<VB>(item, sh);
+    const int32_t id = e.from;  // ids out of range were reported by the lookup; negative ones are skipped here
+    int64_t row = id < 0 ? 0 : id;
+    if (row >= table_rows) row %= table_rows;  // (the table may be aliased)
+    src[u] = row * sh.row_bytes + at;
+    dst[u] = is && id >= 0 ? (int64_t)e.i * sh.row_bytes + at : -1;
+    keep[u] = to >= 0 ? (int64_t)to * sh.row_bytes + at : -1;
+    slot[u] = id >= 0 && item == 0 ? to : -1;
+    vertex[u] = id;
   }
-  for (int32_t v = sub; v < vecs; v += lpr) {
-    V x[kRowUnroll];
+  typename RowVec<VB>::T x[kRowUnroll];
 #pragma unroll
-    for (int u = 0; u < kRowUnroll; ++u)
-      if (src[u] >= 0) x[u] = __builtin_nontemporal_load(table + src[u] * vecs + v);
+  for (int u = 0; u < kRowUnroll; ++u)
+    x[u] = row_load_nt<VB>(table + src[u]);
 #pragma unroll
-    for (int u = 0; u < kRowUnroll; ++u) {
-      if (src[u] >= 0) {
-        __builtin_nontemporal_store(x[u], out + dst[u] * vecs + v);
-        if (dst_slot[u] >= 0) __builtin_nontemporal_store(x[u], rows + dst_slot[u] * vecs + v);  // (not read again before a later call)
-      }
+  for (int u = 0; u < kRowUnroll; ++u) {
+    if (dst[u] >= 0) {
+      row_store_nt<VB>(out + dst[u], x[u]);
+      if (keep[u] >= 0) row_store_nt<VB>(rows + keep[u], x[u]);  // (not read again before a later call)
     }
   }
   // the books of the rows that entered the cache, behind the row traffic as well (a kernel of its own for these three
   // stores costs more than it takes off this one)
-  if (sub == 0) {
 #pragma unroll
-    for (int u = 0; u < kRowUnroll; ++u)
-      if (dst_slot[u] >= 0) {
-        slot_of[src_id[u]] = (int32_t)dst_slot[u];
-        vertex_of[dst_slot[u]] = src_id[u];
-        stamp[dst_slot[u]] = clock_miss + (uint64_t)(row0 + (int64_t)u * rows_per_block);
-      }
-  }
+  for (int u = 0; u < kRowUnroll; ++u)
+    if (slot[u] >= 0) {
+      slot_of[vertex[u]] = slot[u];
+      vertex_of[slot[u]] = vertex[u];
+      stamp[slot[u]] = clock_miss + (uint64_t)miss[u];
+    }
 }
 
 // ---- eviction: radix select of the E-th smallest stamp, then sweep -----------------------------------------------
@@ -346,7 +330,6 @@ using namespace coop;
 
 struct coop_cache {
   int64_t capacity, n_vertices, max_ids, row_bytes;
-  int vec_bytes;          // 16 / 8 / 4 / 2: widest vector that divides the row and the buffers' alignment
   int32_t* slot_of;
   int32_t* vertex_of;
   uint64_t* stamp;
@@ -466,28 +449,28 @@ __global__ __launch_bounds__(kBlock) void k_cache_export(const int32_t* __restri
 }
 
 // entry i of the exported lists goes to slot i; its row is read again from the backing table
-template <typename V>
-__global__ __launch_bounds__(kBlock) void k_cache_import(const V* __restrict__ table, int64_t table_rows, int32_t vecs, int lpr_log2,
+template <int VB>
+__global__ __launch_bounds__(kBlock) void k_cache_import(const char* __restrict__ table, int64_t table_rows, RowShape sh,
                                                          const int32_t* __restrict__ vertices, const uint64_t* __restrict__ stamps,
-                                                         int64_t n, int64_t n_vertices, V* __restrict__ rows,
+                                                         int64_t n, int64_t n_vertices, char* __restrict__ rows,
                                                          int32_t* __restrict__ slot_of, int32_t* __restrict__ vertex_of,
                                                          uint64_t* __restrict__ stamp, CacheCtl* ctl) {
-  const int lpr = 1 << lpr_log2;
-  const int sub = threadIdx.x & (lpr - 1);
-  const int64_t i = (int64_t)blockIdx.x * (kBlock >> lpr_log2) + (threadIdx.x >> lpr_log2);
+  const BlockItems items((int64_t)blockIdx.x * kBlock, sh.vecs);
+  uint32_t item;
+  const int64_t i = items.row_of(threadIdx.x, sh, &item);
   if (i >= n) return;
   const int32_t v = vertices[i];
   if ((uint64_t)(uint32_t)v >= (uint64_t)n_vertices || stamps[i] == 0) {
-    if (sub == 0) atomicOr(&ctl->err_range, 1);
+    if (item == 0) atomicOr(&ctl->err_range, 1);
     return;
   }
-  if (sub == 0) {
+  if (item == 0) {
     slot_of[v] = (int32_t)i;
     vertex_of[i] = v;
     stamp[i] = stamps[i];
   }
-  const int64_t src = v < table_rows ? v : v % table_rows;
-  for (int32_t c = sub; c < vecs; c += lpr) rows[i * vecs + c] = table[src * vecs + c];
+  const int64_t src = v < table_rows ? v : v % table_rows, at = BlockItems::byte_of<VB>(item, sh);
+  row_store_nt<VB>(rows + i * sh.row_bytes + at, row_load_nt<VB>(table + src * sh.row_bytes + at));
 }
 
 // every listed vertex must own its slot: a vertex listed twice owns only one of the two
@@ -539,19 +522,17 @@ extern "C" int coop_cache_import(coop_cache* c, const void* table, int64_t table
   };
   reset(state->size);
   if (state->size > 0) {
-    const uintptr_t align = (uintptr_t)table | (uintptr_t)c->rows | (uintptr_t)c->row_bytes;
-    const int vb = align % 16 == 0 ? 16 : align % 8 == 0 ? 8 : align % 4 == 0 ? 4 : 2;
-    const int32_t vecs = (int32_t)(c->row_bytes / vb);
-    int lpr_log2 = 0;
-    while ((1 << lpr_log2) < vecs && lpr_log2 < 8) ++lpr_log2;
-    const unsigned grid = (unsigned)((state->size + (kBlock >> lpr_log2) - 1) / (kBlock >> lpr_log2));
-#define COOP_IMPORT(V) COOP_LAUNCH(K_CACHE_UPDATE, k_cache_import<V>, dim3(grid), dim3(kBlock), 0, s, (const V*)table, table_rows, vecs, \
-                                   lpr_log2, vertices, stamps, state->size, c->n_vertices, (V*)c->rows, c->slot_of, c->vertex_of,     \
-                                   c->stamp, c->d_ctl)
-    if (vb == 16) COOP_IMPORT(u32x4);
-    else if (vb == 8) COOP_IMPORT(u32x2);
-    else if (vb == 4) COOP_IMPORT(uint32_t);
-    else COOP_IMPORT(uint16_t);
+    const RowShape sh = row_shape(c->row_bytes);
+    const unsigned grid = (unsigned)((state->size * (int64_t)sh.vecs + kBlock - 1) / kBlock);
+#define COOP_IMPORT(VB) COOP_LAUNCH(K_CACHE_UPDATE, k_cache_import<VB>, dim3(grid), dim3(kBlock), 0, s, (const char*)table, table_rows, sh,  \
+                                    vertices, stamps, state->size, c->n_vertices, (char*)c->rows, c->slot_of, c->vertex_of, c->stamp, \
+                                    c->d_ctl)
+    switch (sh.vec_bytes) {
+      case 16: COOP_IMPORT(16); break;
+      case 8: COOP_IMPORT(8); break;
+      case 4: COOP_IMPORT(4); break;
+      default: COOP_IMPORT(2); break;
+    }
 #undef COOP_IMPORT
     COOP_LAUNCH(K_CACHE_LOOKUP, k_cache_import_check, dim3(grid_for(state->size)), dim3(kBlock), 0, s, c->slot_of, c->vertex_of, state->size,
                 c->d_ctl);
@@ -589,32 +570,30 @@ extern "C" int coop_cache_vertices(const coop_cache* c, const int32_t** vertex_o
 }
 
 namespace {
-template <typename V>
-void launch_rows(coop_cache* c, const void* table, int64_t table_rows, const int32_t* ids, int64_t n_ids, void* out, int64_t n_free,
+template <int VB>
+void launch_rows(coop_cache* c, const RowShape& sh, const void* table, int64_t table_rows, int64_t n_ids, void* out, int64_t n_free,
                  int64_t n_miss, int64_t n_ins, int64_t n_hit, bool hits, hipStream_t s) {
-  const int32_t vecs = (int32_t)(c->row_bytes / (int64_t)sizeof(V));
-  int lpr_log2 = 0;
-  while ((1 << lpr_log2) < vecs && lpr_log2 < 8) ++lpr_log2;
-  const int64_t rows_per_launch_block = (int64_t)(kBlock >> lpr_log2) * kRowUnroll;
-  const unsigned grid = (unsigned)((n_ids + rows_per_launch_block - 1) / rows_per_launch_block);
+  constexpr int64_t per_block = kBlock * kRowUnroll;
+  const int64_t n_items = (hits ? n_ids : n_miss) * (int64_t)sh.vecs;
+  const unsigned grid = (unsigned)((n_items + per_block - 1) / per_block);
   if (hits) {
-    COOP_LAUNCH(K_CACHE_GATHER, k_cache_hits<V>, dim3(grid), dim3(kBlock), 0, s, (const V*)c->rows, vecs, lpr_log2, (const OrderEntry*)c->order,
-                c->d_ctl, (V*)out, c->stamp, c->clock);
+    COOP_LAUNCH(K_CACHE_GATHER, k_cache_hits<VB>, dim3(grid), dim3(kBlock), 0, s, (const char*)c->rows, sh, (const OrderEntry*)c->order,
+                c->d_ctl, (char*)out, c->stamp, c->clock);
   } else {
-    const unsigned grid_m = (unsigned)((n_miss + rows_per_launch_block - 1) / rows_per_launch_block);
-    COOP_LAUNCH(K_CACHE_UPDATE, k_cache_misses<V>, dim3(grid_m), dim3(kBlock), 0, s, (const V*)table, vecs, lpr_log2, (const OrderEntry*)c->order, n_ids,
-                (V*)out, (V*)c->rows, c->slot_of, c->vertex_of, c->stamp, c->free_list, n_free, n_miss, n_ins,
+    COOP_LAUNCH(K_CACHE_UPDATE, k_cache_misses<VB>, dim3(grid), dim3(kBlock), 0, s, (const char*)table, sh, (const OrderEntry*)c->order, n_ids,
+                (char*)out, (char*)c->rows, c->slot_of, c->vertex_of, c->stamp, c->free_list, n_free, n_miss, n_ins,
                 c->clock + (uint64_t)n_hit, table_rows);
   }
 }
 
-void dispatch_rows(coop_cache* c, int vec_bytes, const void* table, int64_t table_rows, const int32_t* ids, int64_t n_ids, void* out,
-                   int64_t n_free, int64_t n_miss, int64_t n_ins, int64_t n_hit, bool hits, hipStream_t s) {
-  switch (vec_bytes) {
-    case 16: launch_rows<u32x4>(c, table, table_rows, ids, n_ids, out, n_free, n_miss, n_ins, n_hit, hits, s); break;
-    case 8: launch_rows<u32x2>(c, table, table_rows, ids, n_ids, out, n_free, n_miss, n_ins, n_hit, hits, s); break;
-    case 4: launch_rows<uint32_t>(c, table, table_rows, ids, n_ids, out, n_free, n_miss, n_ins, n_hit, hits, s); break;
-    default: launch_rows<uint16_t>(c, table, table_rows, ids, n_ids, out, n_free, n_miss, n_ins, n_hit, hits, s); break;
+void dispatch_rows(coop_cache* c, const void* table, int64_t table_rows, int64_t n_ids, void* out, int64_t n_free, int64_t n_miss,
+                   int64_t n_ins, int64_t n_hit, bool hits, hipStream_t s) {
+  const RowShape sh = row_shape(c->row_bytes);
+  switch (sh.vec_bytes) {
+    case 16: launch_rows<16>(c, sh, table, table_rows, n_ids, out, n_free, n_miss, n_ins, n_hit, hits, s); break;
+    case 8: launch_rows<8>(c, sh, table, table_rows, n_ids, out, n_free, n_miss, n_ins, n_hit, hits, s); break;
+    case 4: launch_rows<4>(c, sh, table, table_rows, n_ids, out, n_free, n_miss, n_ins, n_hit, hits, s); break;
+    default: launch_rows<2>(c, sh, table, table_rows, n_ids, out, n_free, n_miss, n_ins, n_hit, hits, s); break;
   }
 }
 }  // namespace
@@ -628,9 +607,7 @@ extern "C" int coop_cache_gather(coop_cache* c, const void* table, int64_t table
   if (n_ids == 0) return COOP_OK;
   if (!table || !ids || !out) return COOP_E_NULL;
   hipStream_t s = (hipStream_t)stream;
-  const uintptr_t align = (uintptr_t)table | (uintptr_t)out | (uintptr_t)c->rows | (uintptr_t)c->row_bytes;
-  const int vec_bytes = align % 16 == 0 ? 16 : align % 8 == 0 ? 8 : align % 4 == 0 ? 4 : 2;
-  if (align % 2 != 0) return COOP_E_ARG;
+  if ((((uintptr_t)table | (uintptr_t)out | (uintptr_t)c->rows) & 1) != 0) return COOP_E_ARG;
 
   // (a call on another stream than the last one's: the threshold of that one is still to be copied out of the control block)
   if (c->base_pending) COOP_HIP_TRY(hipStreamWaitEvent(s, c->ev_threshold, 0));
@@ -644,7 +621,7 @@ extern "C" int coop_cache_gather(coop_cache* c, const void* table, int64_t table
   COOP_LAUNCH(K_CACHE_LOOKUP, k_cache_split, dim3((unsigned)((n_ids + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, (const uint64_t*)c->hit_bits,
               (const uint32_t*)c->rank_h, ids, (const int32_t*)c->slot_i, n_ids, c->order);
   // 2. hits: rows out of the cache, new stamps (runs while the host waits for the counts and queues the rest)
-  dispatch_rows(c, vec_bytes, table, table_rows, ids, n_ids, out, 0, 0, 0, 0, true, s);
+  dispatch_rows(c, table, table_rows, n_ids, out, 0, 0, 0, 0, true, s);
   {  // the wait is bounded: after a while, or once the stream has run dry, the host synchronises instead
     bool seen = false;
     for (int64_t spin = 0; spin < ((int64_t)1 << 26); ++spin) {
@@ -714,7 +691,7 @@ extern "C" int coop_cache_gather(coop_cache* c, const void* table, int64_t table
   }
 
   // 4. misses: rows from the backing table to `out`, the last n_ins of them also into free slots
-  if (n_miss > 0) dispatch_rows(c, vec_bytes, table, table_rows, ids, n_ids, out, n_free, n_miss, n_ins, n_hit, false, s);
+  if (n_miss > 0) dispatch_rows(c, table, table_rows, n_ids, out, n_free, n_miss, n_ins, n_hit, false, s);
   c->size += n_ins;
   c->clock = clock_after;
 

@@ -37,4 +37,61 @@ __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
   return v;
 }
 
+// ---- rows moved as items of up to 16 bytes --------------------------------------------------------------------------
+// Feature rows have any even number of bytes (an odd number of fp16 columns, 602 fp32 columns, ...), and the tables any
+// 2-byte aligned base.  A row is cut into vecs = ceil(row_bytes / VB) items of VB bytes, VB the largest power of two up to
+// 16 that the row is long enough for; the last item is anchored at the row's end, so it may overlap the one before it
+// (both copies of the shared bytes are the same).  Items are read and written at the alignment they have: global memory
+// instructions take any.  The (row, item) pairs are dealt to the threads without gaps, so a row of 10 or 151 items leaves
+// no lane idle.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+template <int VB> struct RowVec;
+template <> struct RowVec<16> { typedef u32x4 T; typedef u32x4 U __attribute__((aligned(2))); };
+template <> struct RowVec<8> { typedef u32x2 T; typedef u32x2 U __attribute__((aligned(2))); };
+template <> struct RowVec<4> { typedef uint32_t T; typedef uint32_t U __attribute__((aligned(2))); };
+template <> struct RowVec<2> { typedef uint16_t T; typedef uint16_t U; };
+
+template <int VB>
+__device__ __forceinline__ typename RowVec<VB>::T row_load_nt(const char* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const typename RowVec<VB>::U*>(p));
+}
+template <int VB>
+__device__ __forceinline__ void row_store_nt(char* p, typename RowVec<VB>::T x) {
+  __builtin_nontemporal_store(x, reinterpret_cast<typename RowVec<VB>::U*>(p));
+}
+
+struct RowShape {
+  int64_t row_bytes;
+  uint32_t vecs;   // items per row
+  uint32_t magic;  // ceil(2^32 / vecs)
+  int vec_bytes;
+};
+inline RowShape row_shape(int64_t row_bytes) {
+  const int vb = row_bytes >= 16 ? 16 : row_bytes >= 8 ? 8 : row_bytes >= 4 ? 4 : 2;
+  const uint32_t vecs = (uint32_t)((row_bytes + vb - 1) / vb);
+  return RowShape{row_bytes, vecs, (uint32_t)((((uint64_t)1 << 32) + vecs - 1) / vecs), vb};
+}
+
+// The items [first, first + count) of a block, count <= 1024: thread items are given as offsets below count.
+struct BlockItems {
+  int64_t row0;  // row of the block's first item
+  uint32_t rem;  // ... and that item's number in the row
+  __device__ __forceinline__ BlockItems(int64_t first, uint32_t vecs) : row0(first / vecs), rem((uint32_t)(first - row0 * vecs)) {}
+  // (the multiplication is exact for vecs < 1024: the dividend stays below 2048 and the excess of magic * vecs over 2^32
+  // below vecs)
+  __device__ __forceinline__ int64_t row_of(uint32_t at, const RowShape& sh, uint32_t* item) const {
+    const uint32_t i = rem + at;
+    const uint32_t q = sh.vecs >= 1024u ? (i >= sh.vecs ? 1u : 0u) : sh.vecs == 1u ? i : __umulhi(i, sh.magic);
+    *item = i - q * sh.vecs;
+    return row0 + q;
+  }
+  template <int VB>
+  static __device__ __forceinline__ int64_t byte_of(uint32_t item, const RowShape& sh) {
+    const int64_t o = (int64_t)item * VB, last = sh.row_bytes - VB;
+    return o < last ? o : last;
+  }
+};
+
 }  // namespace coop

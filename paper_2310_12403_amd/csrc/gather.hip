@@ -1,9 +1,11 @@
 // Feature loading step of Algorithm 1: out[i, :] = feat[ids[i], :], an exact copy of bits.
 //
-// HBM-bound row gather.  A row of `vecs` vectors (16, 8, 4, 2 or 1 bytes each, the widest that the row size and
-// the base addresses allow) is moved by `lpr` adjacent lanes (a power of two), so one wave64 load instruction
-// covers 64 / lpr rows and each row is read with full-width, coalesced accesses.  Every thread keeps kUnroll rows
-// in flight to cover the latency of the random row reads.  Loads and stores are non-temporal: a row is used once.
+// HBM-bound row gather.  The rows' items (device_utils.h: up to 16 bytes each, at whatever alignment the row has) are
+// dealt to the threads of the grid in order, kGatherUnroll per thread in flight to cover the latency of the random row
+// reads.  Loads and stores are non-temporal: a row is used once.  Against a power of two of lanes per row and the widest
+// vectors that divide row and bases: rows of 75 fp16 columns (2-byte vectors before) 64 -> 24 us for 284 thousand rows, rows
+// of 602 fp32 columns (8-byte vectors) 243 -> 229 us for 233 thousand (4.9 TB/s; a plain copy of 2 GiB reaches 4.9), rows
+// of 100 fp32 columns (25 items on 32 lanes) 178 -> 170 us, rows of 128 fp16 columns unchanged.
 #include <hip/hip_fp16.h>
 
 #include <mutex>
@@ -15,41 +17,33 @@ namespace coop {
 
 constexpr int kGatherUnroll = 4;
 
-template <typename V>
-__global__ __launch_bounds__(kBlock) void k_gather(const V* __restrict__ feat, int64_t n_rows, int32_t vecs, int lpr_log2,
-                                                   const int32_t* __restrict__ ids, int64_t n_ids, V* __restrict__ out,
-                                                   int32_t* __restrict__ bad) {
-  const int lpr = 1 << lpr_log2;
-  const int rows_per_block = kBlock >> lpr_log2;
-  const int sub = threadIdx.x & (lpr - 1);
-  const int64_t row0 = ((int64_t)blockIdx.x * kGatherUnroll) * rows_per_block + (threadIdx.x >> lpr_log2);
-
-  int64_t src_row[kGatherUnroll];
+template <int VB>
+__global__ __launch_bounds__(kBlock) void k_gather(const char* __restrict__ feat, int64_t n_rows, RowShape sh, const int32_t* __restrict__ ids,
+                                                   int64_t n_ids, char* __restrict__ out, int32_t* __restrict__ bad) {
+  const BlockItems items((int64_t)blockIdx.x * (kBlock * kGatherUnroll), sh.vecs);
+  int64_t row[kGatherUnroll];
+  int32_t id[kGatherUnroll];
+  uint32_t item[kGatherUnroll];
 #pragma unroll
   for (int u = 0; u < kGatherUnroll; ++u) {
-    const int64_t r = row0 + (int64_t)u * rows_per_block;
-    int64_t id = -1;
-    if (r < n_ids) {
-      id = ids[r];
-      if ((uint64_t)id >= (uint64_t)n_rows) {
-        if (sub == 0) atomicOr(bad, 1);
-        id = -2;
-      }
-    }
-    src_row[u] = id;
+    row[u] = items.row_of((uint32_t)(u * kBlock) + threadIdx.x, sh, &item[u]);
+    id[u] = ids[row[u] < n_ids ? row[u] : n_ids - 1];  // (all of them requested before the first one is looked at)
   }
-  for (int32_t v = sub; v < vecs; v += lpr) {
-    V x[kGatherUnroll];
+  typename RowVec<VB>::T x[kGatherUnroll];
+  char* to[kGatherUnroll];
 #pragma unroll
-    for (int u = 0; u < kGatherUnroll; ++u) {
-      if (src_row[u] >= 0) x[u] = __builtin_nontemporal_load(feat + src_row[u] * vecs + v);
-      else x[u] = V{};
-    }
+  for (int u = 0; u < kGatherUnroll; ++u) {
+    const int64_t at = BlockItems::byte_of<VB>(item[u], sh);
+    to[u] = out + (row[u] < n_ids ? row[u] : n_ids - 1) * sh.row_bytes + at;
+    // every load is issued, without a branch: that of an id out of range reads the place it would be written to
+    x[u] = row_load_nt<VB>((uint64_t)(int64_t)id[u] < (uint64_t)n_rows ? feat + id[u] * sh.row_bytes + at : to[u]);
+  }
 #pragma unroll
-    for (int u = 0; u < kGatherUnroll; ++u) {
-      const int64_t r = row0 + (int64_t)u * rows_per_block;
-      if (src_row[u] != -1) __builtin_nontemporal_store(x[u], out + r * vecs + v);
-    }
+  for (int u = 0; u < kGatherUnroll; ++u) {
+    if (row[u] >= n_ids) continue;
+    const bool ok = (uint64_t)(int64_t)id[u] < (uint64_t)n_rows;
+    row_store_nt<VB>(to[u], ok ? x[u] : typename RowVec<VB>::T{});
+    if (!ok && item[u] == 0) atomicOr(bad, 1);
   }
 }
 
@@ -94,39 +88,38 @@ struct MeanAcc {
   }
 };
 
-template <typename V, bool F16>
-__global__ __launch_bounds__(kBlock) void k_gather_mean(const V* __restrict__ feat, int64_t n_rows, int32_t vecs, int lpr_log2,
+template <int VB, bool F16>
+__global__ __launch_bounds__(kBlock) void k_gather_mean(const char* __restrict__ feat, int64_t n_rows, RowShape sh,
                                                         const int64_t* __restrict__ indptr, const int32_t* __restrict__ col,
-                                                        int64_t n_dst, V* __restrict__ out, int32_t* __restrict__ bad) {
-  const int lpr = 1 << lpr_log2;
-  const int rows_per_block = kBlock >> lpr_log2;
-  const int sub = threadIdx.x & (lpr - 1);
-  const int64_t i = (int64_t)blockIdx.x * rows_per_block + (threadIdx.x >> lpr_log2);
+                                                        int64_t n_dst, char* __restrict__ out, int32_t* __restrict__ bad) {
+  typedef typename RowVec<VB>::T V;
+  const BlockItems items((int64_t)blockIdx.x * kBlock, sh.vecs);
+  uint32_t item;
+  const int64_t i = items.row_of(threadIdx.x, sh, &item);
   if (i >= n_dst) return;
+  const int64_t at = BlockItems::byte_of<VB>(item, sh);
   const int64_t beg = indptr[i], end = indptr[i + 1];
-  for (int32_t v = sub; v < vecs; v += lpr) {
-    MeanAcc<V, F16> acc;
-    acc.clear();
-    for (int64_t e = beg; e < end; e += kMeanUnroll) {
-      V x[kMeanUnroll];
-      bool ok[kMeanUnroll];
+  MeanAcc<V, F16> acc;
+  acc.clear();
+  for (int64_t e = beg; e < end; e += kMeanUnroll) {
+    V x[kMeanUnroll];
+    bool ok[kMeanUnroll];
 #pragma unroll
-      for (int u = 0; u < kMeanUnroll; ++u) {
-        ok[u] = false;
-        if (e + u < end) {
-          const int64_t id = col[e + u];
-          ok[u] = (uint64_t)id < (uint64_t)n_rows;
-          if (ok[u]) x[u] = feat[id * vecs + v];
-          else if (sub == 0 && v == sub) atomicOr(bad, 1);
-        }
+    for (int u = 0; u < kMeanUnroll; ++u) {
+      ok[u] = false;
+      if (e + u < end) {
+        const int64_t id = col[e + u];
+        ok[u] = (uint64_t)id < (uint64_t)n_rows;
+        if (ok[u]) x[u] = *reinterpret_cast<const typename RowVec<VB>::U*>(feat + id * sh.row_bytes + at);
+        else if (item == 0) atomicOr(bad, 1);
       }
-#pragma unroll
-      for (int u = 0; u < kMeanUnroll; ++u)
-        if (ok[u]) acc.add(x[u]);
     }
-    const int64_t cnt = end - beg;
-    __builtin_nontemporal_store(cnt > 0 ? acc.mean((float)cnt) : V{}, out + i * vecs + v);
+#pragma unroll
+    for (int u = 0; u < kMeanUnroll; ++u)
+      if (ok[u]) acc.add(x[u]);
   }
+  const int64_t cnt = end - beg;
+  row_store_nt<VB>(out + i * sh.row_bytes + at, cnt > 0 ? acc.mean((float)cnt) : V{});
 }
 
 namespace {
@@ -158,20 +151,12 @@ int32_t* bad_flag() {
 
 namespace {
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-template <typename V>
-void launch_gather(const void* feat, int64_t n_rows, int64_t row_bytes, const int32_t* ids, int64_t n_ids, void* out,
-                   int32_t* bad, hipStream_t s) {
-  const int32_t vecs = (int32_t)(row_bytes / (int64_t)sizeof(V));
-  int lpr_log2 = 0;
-  while ((1 << lpr_log2) < vecs && lpr_log2 < 8) ++lpr_log2;
-  const int rows_per_block = kBlock >> lpr_log2;
-  const int64_t rows_per_launch_block = (int64_t)rows_per_block * kGatherUnroll;
-  const unsigned grid = (unsigned)((n_ids + rows_per_launch_block - 1) / rows_per_launch_block);
-  COOP_LAUNCH(K_GATHER, k_gather<V>, dim3(grid), dim3(kBlock), 0, s, (const V*)feat, n_rows, vecs, lpr_log2, ids, n_ids, (V*)out,
-              bad);
+template <int VB>
+void launch_gather(const void* feat, int64_t n_rows, const RowShape& sh, const int32_t* ids, int64_t n_ids, void* out, int32_t* bad,
+                   hipStream_t s) {
+  constexpr int64_t per_block = kBlock * kGatherUnroll;
+  const unsigned grid = (unsigned)((n_ids * (int64_t)sh.vecs + per_block - 1) / per_block);
+  COOP_LAUNCH(K_GATHER, k_gather<VB>, dim3(grid), dim3(kBlock), 0, s, (const char*)feat, n_rows, sh, ids, n_ids, (char*)out, bad);
 }
 }  // namespace
 
@@ -185,32 +170,29 @@ extern "C" int coop_gather(const void* feat, int64_t n_rows, int32_t dim, int dt
   if (dim < 1 || n_rows < 0 || n_ids < 0) return COOP_E_ARG;
   if (n_ids == 0) return COOP_OK;
   if (!feat || !ids || !out) return COOP_E_NULL;
-  const int64_t row_bytes = (int64_t)dim * (dtype == COOP_F32 ? 4 : 2);
-  if ((n_ids + 255) / 256 > 0x7FFFFFFF) return COOP_E_ARG;
+  const RowShape sh = row_shape((int64_t)dim * (dtype == COOP_F32 ? 4 : 2));
+  if ((n_ids + 255) / 256 > 0x7FFFFFFF || n_ids > ((int64_t)0x7FFFFFFF * kBlock) / (int64_t)sh.vecs) return COOP_E_ARG;
   int32_t* bad = bad_flag();
   if (!bad) return COOP_E_HIP;
   hipStream_t s = (hipStream_t)stream;
-  const uintptr_t align = (uintptr_t)feat | (uintptr_t)out | (uintptr_t)row_bytes;
-  if (align % 16 == 0) launch_gather<u32x4>(feat, n_rows, row_bytes, ids, n_ids, out, bad, s);
-  else if (align % 8 == 0) launch_gather<u32x2>(feat, n_rows, row_bytes, ids, n_ids, out, bad, s);
-  else if (align % 4 == 0) launch_gather<uint32_t>(feat, n_rows, row_bytes, ids, n_ids, out, bad, s);
-  else if (align % 2 == 0) launch_gather<uint16_t>(feat, n_rows, row_bytes, ids, n_ids, out, bad, s);
-  else return COOP_E_ARG;  // fp16 / fp32 tables are at least 2-byte aligned
+  if ((((uintptr_t)feat | (uintptr_t)out) & 1) != 0) return COOP_E_ARG;  // fp16 / fp32 tables are at least 2-byte aligned
+  switch (sh.vec_bytes) {
+    case 16: launch_gather<16>(feat, n_rows, sh, ids, n_ids, out, bad, s); break;
+    case 8: launch_gather<8>(feat, n_rows, sh, ids, n_ids, out, bad, s); break;
+    case 4: launch_gather<4>(feat, n_rows, sh, ids, n_ids, out, bad, s); break;
+    default: launch_gather<2>(feat, n_rows, sh, ids, n_ids, out, bad, s); break;
+  }
   if (hipGetLastError() != hipSuccess) return COOP_E_HIP;
   return COOP_OK;
 }
 
 namespace {
-template <typename V, bool F16>
-void launch_mean(const void* feat, int64_t n_rows, int64_t row_bytes, const int64_t* indptr, const int32_t* col, int64_t n_dst,
+template <int VB, bool F16>
+void launch_mean(const void* feat, int64_t n_rows, const RowShape& sh, const int64_t* indptr, const int32_t* col, int64_t n_dst,
                  void* out, int32_t* bad, hipStream_t s) {
-  const int32_t vecs = (int32_t)(row_bytes / (int64_t)sizeof(V));
-  int lpr_log2 = 0;
-  while ((1 << lpr_log2) < vecs && lpr_log2 < 8) ++lpr_log2;
-  const int rows_per_block = kBlock >> lpr_log2;
-  const unsigned grid = (unsigned)((n_dst + rows_per_block - 1) / rows_per_block);
-  COOP_LAUNCH(K_GATHER_MEAN, (k_gather_mean<V, F16>), dim3(grid), dim3(kBlock), 0, s, (const V*)feat, n_rows, vecs, lpr_log2, indptr, col,
-              n_dst, (V*)out, bad);
+  const unsigned grid = (unsigned)((n_dst * (int64_t)sh.vecs + kBlock - 1) / kBlock);
+  COOP_LAUNCH(K_GATHER_MEAN, (k_gather_mean<VB, F16>), dim3(grid), dim3(kBlock), 0, s, (const char*)feat, n_rows, sh, indptr, col, n_dst,
+              (char*)out, bad);
 }
 }  // namespace
 
@@ -220,23 +202,25 @@ extern "C" int coop_gather_mean(const void* feat, int64_t n_rows, int32_t dim, i
   if (dim < 1 || n_rows < 0 || n_dst < 0) return COOP_E_ARG;
   if (n_dst == 0) return COOP_OK;
   if (!feat || !indptr || !out) return COOP_E_NULL;  // col_global may be NULL only if there are no edges; not checkable here
-  if ((n_dst + 255) / 256 > 0x7FFFFFFF) return COOP_E_ARG;
-  const int64_t row_bytes = (int64_t)dim * (dtype == COOP_F32 ? 4 : 2);
+  const RowShape sh = row_shape((int64_t)dim * (dtype == COOP_F32 ? 4 : 2));
+  if ((n_dst + 255) / 256 > 0x7FFFFFFF || n_dst > ((int64_t)0x7FFFFFFF * kBlock) / (int64_t)sh.vecs) return COOP_E_ARG;
   int32_t* bad = bad_flag();
   if (!bad) return COOP_E_HIP;
   hipStream_t s = (hipStream_t)stream;
-  const uintptr_t align = (uintptr_t)feat | (uintptr_t)out | (uintptr_t)row_bytes;
+  if ((((uintptr_t)feat | (uintptr_t)out) & (dtype == COOP_F16 ? 1 : 3)) != 0) return COOP_E_ARG;
   if (dtype == COOP_F16) {
-    if (align % 16 == 0) launch_mean<u32x4, true>(feat, n_rows, row_bytes, indptr, col_global, n_dst, out, bad, s);
-    else if (align % 8 == 0) launch_mean<u32x2, true>(feat, n_rows, row_bytes, indptr, col_global, n_dst, out, bad, s);
-    else if (align % 4 == 0) launch_mean<uint32_t, true>(feat, n_rows, row_bytes, indptr, col_global, n_dst, out, bad, s);
-    else if (align % 2 == 0) launch_mean<uint16_t, true>(feat, n_rows, row_bytes, indptr, col_global, n_dst, out, bad, s);
-    else return COOP_E_ARG;
+    switch (sh.vec_bytes) {
+      case 16: launch_mean<16, true>(feat, n_rows, sh, indptr, col_global, n_dst, out, bad, s); break;
+      case 8: launch_mean<8, true>(feat, n_rows, sh, indptr, col_global, n_dst, out, bad, s); break;
+      case 4: launch_mean<4, true>(feat, n_rows, sh, indptr, col_global, n_dst, out, bad, s); break;
+      default: launch_mean<2, true>(feat, n_rows, sh, indptr, col_global, n_dst, out, bad, s); break;
+    }
   } else {
-    if (align % 16 == 0) launch_mean<u32x4, false>(feat, n_rows, row_bytes, indptr, col_global, n_dst, out, bad, s);
-    else if (align % 8 == 0) launch_mean<u32x2, false>(feat, n_rows, row_bytes, indptr, col_global, n_dst, out, bad, s);
-    else if (align % 4 == 0) launch_mean<uint32_t, false>(feat, n_rows, row_bytes, indptr, col_global, n_dst, out, bad, s);
-    else return COOP_E_ARG;
+    switch (sh.vec_bytes) {
+      case 16: launch_mean<16, false>(feat, n_rows, sh, indptr, col_global, n_dst, out, bad, s); break;
+      case 8: launch_mean<8, false>(feat, n_rows, sh, indptr, col_global, n_dst, out, bad, s); break;
+      default: launch_mean<4, false>(feat, n_rows, sh, indptr, col_global, n_dst, out, bad, s); break;
+    }
   }
   if (hipGetLastError() != hipSuccess) return COOP_E_HIP;
   return COOP_OK;

@@ -166,6 +166,37 @@ def test_gather_unaligned_views_and_range(P):
     P.coop_gather_status()                              # the condition was cleared
 
 
+@pytest.mark.parametrize("dtype,dims", [(torch.float16, (1, 2, 3, 4, 5, 7, 8, 9, 15, 17, 75, 8183, 8184, 8193)),
+                                        (torch.float32, (1, 2, 3, 4, 5, 7, 151, 4093, 4097))])
+@pytest.mark.parametrize("where", ["device", "pinned"])
+def test_rows_of_any_size(P, dtype, dims, where):
+    """Rows one item short of, at and past the item sizes (2, 4, 8, 16 bytes) and the 1,023 / 1,024 items at which the row
+    of an item is found in another way, from bases that are only as aligned as an element; the rows around the output stay
+    untouched.  Copies are compared bit for bit; a mean over one row is that row."""
+    n, rows_out = 37, 41
+    for dim in dims:
+        feat = synth.features(n, dim, dtype, seed=dim, device="cpu")
+        host = torch.zeros(n * dim + 1, dtype=dtype, pin_memory=where == "pinned")
+        host[1:] = feat.reshape(-1)
+        table = (host.cuda() if where == "device" else host)[1:].view(n, dim)
+        ids = (synth.hash_u53(torch.arange(rows_out), 7) % n).to(torch.int32)
+        want = R.gather(feat.numpy(), ids.numpy())
+        if where == "device":
+            out = torch.full(((rows_out + 2) * dim + 1,), 7.0, dtype=dtype, device="cuda")
+            P.coop_gather(table, ids.cuda(), out=out[1 + dim:1 + (rows_out + 1) * dim].view(rows_out, dim))
+            out = out.cpu()
+            assert out[1 + dim:1 + (rows_out + 1) * dim].numpy().tobytes() == want.tobytes(), dim
+            assert (out[:1 + dim] == 7.0).all() and (out[1 + (rows_out + 1) * dim:] == 7.0).all(), dim
+            mean = P.coop_gather_mean(table, torch.arange(rows_out + 1).cuda(), ids.cuda())
+            assert mean.cpu().numpy().tobytes() == want.tobytes(), dim
+        cache = P.Cache(9, n, dim, dtype, n)
+        for batch in (ids.unique()[:11], ids.unique()[5:], ids.unique()[5:9]):
+            got, _ = cache.gather(table, batch.cuda())
+            assert got.cpu().numpy().tobytes() == R.gather(feat.numpy(), batch.numpy()).tobytes(), dim
+        cache.close()
+    P.coop_gather_status()
+
+
 def test_sample_then_gather_end_to_end(P, tiny):
     feat = synth.features(tiny.n, 64, torch.float32, seed=0, device="cpu")
     seeds = synth.seed_batches(tiny.n, 1024, seed=0)(0).numpy()
