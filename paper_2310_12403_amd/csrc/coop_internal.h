@@ -26,6 +26,8 @@ enum KernelId {
   K_SCAN_OFFSET,     // scan: add the sum of the preceding tiles
   K_UNIQ_INSERT,     // hash table insert (atomic CAS / min)
   K_UNIQ_FLAG,       // first-occurrence lookup
+  K_UNIQ_FILTER,     // short lists: first positions through tables in LDS, every block picking its bucket from the whole list
+  K_UNIQ_COLLECT,    // new-vertex bits and their ranks, in edge order
   K_UNIQ_RELABEL,    // new-id compaction + col_local
   K_PART_COUNT,      // dedup by partition: bucket sizes per block
   K_PART_SCATTER,    // dedup by partition: (key, position) pairs to their buckets
@@ -75,6 +77,20 @@ struct Ctl {
   int32_t pad[1];
 };
 
+// "Who is the last block?"  Returning atomics on one address are taken one after the other, some 20 ns each, so a kernel of
+// a thousand blocks that all count themselves in one word takes 20 us for that alone.  Blocks therefore count themselves
+// in one of kTallyLines words, each in a cache line of its own, and the one that completes a line counts the line.  A
+// count carries a sum along in its lower half: the last block knows the sum of all without reading what others stored.
+// All words are zero at the start of a sampling call and again when the last block has counted itself.
+constexpr int kTallyLines = 32;
+struct Tally { unsigned long long word[(kTallyLines + 1) * 16]; };
+
+// The control data of a call in device memory: Ctl (its address stands for the whole) and what the host does not see.
+struct DeviceCtl {
+  Ctl ctl;       // must stay the first member
+  Tally tally;
+};
+
 // Landing pad of the control block in mapped pinned host memory (see read_ctl).
 struct HostCtl {
   Ctl ctl;               // must stay the first member
@@ -105,9 +121,7 @@ void scan_chunks_to_i64(const ChunkedI32& in, int64_t n, int64_t* out, int64_t* 
                         const Publish* pub = nullptr);
 // exclusive scan of n uint32 (sum below 2^32); out has n + 1 entries, the last one the total
 void scan_u32_to_u32(const uint32_t* in, int64_t n, uint32_t* out, void* tmp, hipStream_t s);
-// (n_bits_dev, device, optional: only bits [0, *n_bits_dev) count; n_words is then an upper bound known to the host)
-void scan_popc_to_u32(const uint64_t* bits, int64_t n_words, uint32_t* out, int64_t* total_out, void* tmp, hipStream_t s,
-                      const Publish* pub = nullptr, const int64_t* n_bits_dev = nullptr);
+void scan_popc_to_u32(const uint64_t* bits, int64_t n_words, uint32_t* out, int64_t* total_out, void* tmp, hipStream_t s);
 
 // One-kernel exclusive scans for the library's own consumers.  Every block scans its tile and leaves the tile's sum; the
 // block that finishes last (a counter in the call's control block tells it) scans the tile sums.  The result stays in two
@@ -128,8 +142,6 @@ struct TiledScan {
 };
 // (`done` points at a zeroed uint32 that no other scan in flight uses; it is zero again when the scan has run.)
 TiledScan<uint32_t> scan_u32_tiled(const uint32_t* in, int64_t n, uint32_t* out, void* tmp, uint32_t* done, hipStream_t s);
-TiledScan<uint32_t> scan_popc_tiled(const uint64_t* bits, int64_t n_words, uint32_t* out, int64_t* total_out, void* tmp, uint32_t* done,
-                                    hipStream_t s, const Publish* pub = nullptr, const int64_t* n_bits_dev = nullptr);
 
 void fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
 
@@ -166,24 +178,26 @@ int read_ctl(Ctl* d_ctl, Ctl* h_ctl, hipStream_t s);
 //          serves the sampler and the dedup).
 //   back:  writes src_ids and col_local.
 extern int g_unique_mode;  // COOP_TUNE_UNIQUE
+// 64 positions of [dst ; col_global]: which are the first occurrence of a new vertex, and how many of those the words in
+// front have, inside the word's stretch
+struct __attribute__((aligned(16))) RankWord { uint64_t bits; uint32_t before, pad; };
 struct UniqueWork {
-  uint32_t* first = nullptr;
-  uint64_t* bits = nullptr;
-  uint32_t* word_rank = nullptr;
-  TiledScan<uint32_t> rank{nullptr, nullptr, 0};  // scanned bit counts of the words of `bits` (over word_rank)
-  void* scan_tmp = nullptr;
+  RankWord* words = nullptr;
+  uint32_t* block_prefix = nullptr;  // ... and in the stretches in front
   int64_t n_buckets = 0;
-  bool by_partition = false;
+  uint32_t part_blocks = 0;          // blocks of the partition whose stretches those are (0: stretches of fixed length)
+  int path = 0;
   Publish pub{};
   int64_t n_new = 0;
 };
-// launch: every kernel of the front half, ending with the scan that sends the sizes to the host; does not wait.
-int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, UniqueWork* w,
-                        Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s);
+// launch: every kernel of the front half; one of them sends the sizes to the host; does not wait.  col_local (m entries)
+// holds intermediate results until `back` has run.
+int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
+                        UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s);
 // finish: waits for the sizes (h_ctl then holds total_edges, total_new and the flags; w->n_new is set).  If the dedup
 // had to be run again (*redone), a relabelling launched in between has to be launched again.
-int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, UniqueWork* w,
-                        Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s, bool* redone);
+int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
+                        UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s, bool* redone);
 // back: writes src_ids (S^l, then the new vertices) and col_local[m]; src must have room for n_dst + (number of new
 // vertices) entries.  May be launched between launch and finish with room for n_dst + m entries.
 int unique_back(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, const UniqueWork& w,

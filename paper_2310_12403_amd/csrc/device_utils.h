@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "coop_internal.h"
+
 namespace coop {
 
 constexpr int kWave = 64;
@@ -35,6 +37,28 @@ __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
   return v;
+}
+
+// One thread per block: counts the block, with `add`, in the tally; true in the block that is the last of gridDim.x, where
+// *total is the sum of all blocks' `add` (below 2^32).  Each atomic is performed before the next one that depends on it is
+// sent.  The words are zero again afterwards.
+__device__ __forceinline__ bool tally_last(Ctl* ctl, uint32_t add, uint32_t* total) {
+  unsigned long long* word = reinterpret_cast<DeviceCtl*>(ctl)->tally.word;
+  const uint32_t line = blockIdx.x % kTallyLines;
+  const uint32_t in_line = (gridDim.x - line + kTallyLines - 1) / kTallyLines;  // blocks line, line + kTallyLines, ...
+  uint32_t sum = add, counts = gridDim.x;
+  if (gridDim.x > (uint32_t)kTallyLines) {  // (fewer blocks count themselves in the one word)
+    const unsigned long long a = atomicAdd(&word[(line + 1) * 16], ((unsigned long long)1 << 32) | add);
+    if ((uint32_t)(a >> 32) != in_line - 1) return false;
+    __hip_atomic_store(&word[(line + 1) * 16], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sum = (uint32_t)a + add;
+    counts = kTallyLines;
+  }
+  const unsigned long long b = atomicAdd(&word[0], ((unsigned long long)1 << 32) | sum);
+  if ((uint32_t)(b >> 32) != counts - 1) return false;
+  __hip_atomic_store(&word[0], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  *total = (uint32_t)b + sum;
+  return true;
 }
 
 // ---- rows moved as items of up to 16 bytes --------------------------------------------------------------------------

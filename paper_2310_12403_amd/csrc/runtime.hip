@@ -24,7 +24,7 @@ struct Prof {
 
 const char* const kKernelNames[K_COUNT_] = {
     "fill", "labor_scan", "labor_fill", "labor_fill_overflow", "labor_exact", "segments", "enum_list", "enum_walk", "ns_count", "ns_fill", "ns_select", "rw_walk", "rw_fill", "scan_local", "scan_offset",
-    "unique_insert", "unique_flag", "unique_relabel", "unique_part_count", "unique_part_scatter", "unique_part_first", "copy_ids", "gather", "gather_mean", "owner_count", "owner_scatter", "validate_csr",
+    "unique_insert", "unique_flag", "unique_filter", "unique_collect", "unique_relabel", "unique_part_count", "unique_part_scatter", "unique_part_first", "copy_ids", "gather", "gather_mean", "owner_count", "owner_scatter", "validate_csr",
     "cache_lookup", "cache_select", "cache_evict", "cache_miss_rows", "cache_hit_rows"};
 
 hipEvent_t take_event() {
@@ -150,11 +150,7 @@ struct LoadU32 {
 };
 struct LoadPopc {  // element i = number of set bits of word i
   const uint64_t* bits;
-  const int64_t* n_bits;  // when not null: only the words that hold bits [0, *n_bits) count (a size that the host does not know yet)
-  __device__ __forceinline__ int64_t operator()(int64_t i) const {
-    if (n_bits != nullptr && i >= ((*n_bits + 63) >> 6)) return 0;
-    return __popcll(bits[i]);
-  }
+  __device__ __forceinline__ int64_t operator()(int64_t i) const { return __popcll(bits[i]); }
 };
 
 template <typename Load, typename Out>
@@ -365,14 +361,8 @@ TiledScan<uint32_t> scan_u32_tiled(const uint32_t* in, int64_t n, uint32_t* out,
   return scan_tiled_impl<LoadU32>(LoadU32{in}, n, out, nullptr, tmp, done, s, nullptr);
 }
 
-TiledScan<uint32_t> scan_popc_tiled(const uint64_t* bits, int64_t n_words, uint32_t* out, int64_t* total_out, void* tmp, uint32_t* done,
-                                    hipStream_t s, const Publish* pub, const int64_t* n_bits_dev) {
-  return scan_tiled_impl<LoadPopc>(LoadPopc{bits, n_bits_dev}, n_words, out, total_out, tmp, done, s, pub);
-}
-
-void scan_popc_to_u32(const uint64_t* bits, int64_t n_words, uint32_t* out, int64_t* total_out, void* tmp, hipStream_t s,
-                      const Publish* pub, const int64_t* n_bits_dev) {
-  scan_impl<LoadPopc, uint32_t>(LoadPopc{bits, n_bits_dev}, n_words, out, (uint32_t*)nullptr, total_out, tmp, s, pub);
+void scan_popc_to_u32(const uint64_t* bits, int64_t n_words, uint32_t* out, int64_t* total_out, void* tmp, hipStream_t s) {
+  scan_impl<LoadPopc, uint32_t>(LoadPopc{bits}, n_words, out, (uint32_t*)nullptr, total_out, tmp, s, nullptr);
 }
 
 // ---- CSR validation -------------------------------------------------------------------------------------------

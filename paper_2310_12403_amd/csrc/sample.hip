@@ -17,6 +17,7 @@ __global__ __launch_bounds__(kBlock) void k_begin_call(const int32_t* __restrict
                                                        Ctl* ctl, uint32_t* piece_count, int L) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < n_seeds) seed_copy[i] = seeds[i];
+  if (i < (kTallyLines + 1) * 16) reinterpret_cast<DeviceCtl*>(ctl)->tally.word[i] = 0;
   if (i == 0) {
     *ctl = Ctl{};
     for (int l = 0; l < L; ++l) piece_count[l] = 0;
@@ -169,11 +170,12 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
   }
   Ctl* h_ctl = &h_pad->ctl;
   cx.h_ctl = h_ctl;
-  cx.d_ctl = alloc.get<Ctl>(1, COOP_TAG_SCRATCH);
+  cx.d_ctl = (Ctl*)alloc.get<DeviceCtl>(1, COOP_TAG_SCRATCH);
   cx.d_piece_count = alloc.get<uint32_t>(L, COOP_TAG_SCRATCH);
   int32_t* seed_copy = alloc.get<int32_t>(n_seeds, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
-  COOP_LAUNCH(K_COPY_IDS, k_begin_call, dim3(n_seeds > 0 ? blocks_for(n_seeds, kBlock) : 1u), dim3(kBlock), 0, s, seeds, seed_copy, n_seeds,
+  const int64_t n_begin = n_seeds > (kTallyLines + 1) * 16 ? n_seeds : (kTallyLines + 1) * 16;
+  COOP_LAUNCH(K_COPY_IDS, k_begin_call, dim3(blocks_for(n_begin, kBlock)), dim3(kBlock), 0, s, seeds, seed_copy, n_seeds,
               cx.d_ctl, cx.d_piece_count, L);
 
   LaborState labor;
@@ -214,7 +216,7 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
       rc = sample_layer(edge_cap);
       if (rc != COOP_OK) break;
       const int64_t* m_dev = &cx.d_ctl->total_edges;
-      rc = unique_front_launch(dst, n_dst, blk.col_global, edge_cap, m_dev, &uw, alloc, cx.d_ctl, h_ctl, s);
+      rc = unique_front_launch(dst, n_dst, blk.col_global, edge_cap, m_dev, blk.col_local, &uw, alloc, cx.d_ctl, h_ctl, s);
       if (rc != COOP_OK) break;
       // S^{l+1} and local ids (Eq. 2) are queued before the sizes are back, with room for the bound, so that the device
       // is at work while the host waits for the sizes and sets up the next layer
@@ -222,7 +224,7 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
       if (alloc.failed) { rc = COOP_E_NOMEM; break; }
       rc = unique_back(dst, n_dst, blk.col_global, edge_cap, m_dev, uw, blk.col_local, src, s);
       if (rc != COOP_OK) break;
-      rc = unique_front_finish(dst, n_dst, blk.col_global, edge_cap, m_dev, &uw, alloc, cx.d_ctl, h_ctl, s, &redone);
+      rc = unique_front_finish(dst, n_dst, blk.col_global, edge_cap, m_dev, blk.col_local, &uw, alloc, cx.d_ctl, h_ctl, s, &redone);
       if (rc != COOP_OK) break;
       if (h_ctl->n_overflow > 0) defer_ok = false;  // the counter is never reset: the overflow pass runs from here on
       if (h_ctl->total_edges <= edge_cap && h_ctl->n_overflow == 0 && h_ctl->cand_overflow == 0) {
@@ -242,9 +244,9 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
       rc = sample_layer(0);
       if (rc != COOP_OK) break;
       if (n_dst + blk.n_edges >= ((int64_t)1 << 32) - 1) { rc = COOP_E_CAPACITY; break; }
-      rc = unique_front_launch(dst, n_dst, blk.col_global, blk.n_edges, nullptr, &uw, alloc, cx.d_ctl, h_ctl, s);
+      rc = unique_front_launch(dst, n_dst, blk.col_global, blk.n_edges, nullptr, blk.col_local, &uw, alloc, cx.d_ctl, h_ctl, s);
       if (rc != COOP_OK) break;
-      rc = unique_front_finish(dst, n_dst, blk.col_global, blk.n_edges, nullptr, &uw, alloc, cx.d_ctl, h_ctl, s, &redone);
+      rc = unique_front_finish(dst, n_dst, blk.col_global, blk.n_edges, nullptr, blk.col_local, &uw, alloc, cx.d_ctl, h_ctl, s, &redone);
       if (rc != COOP_OK) break;
       src = alloc.get<int32_t>(n_dst + uw.n_new, COOP_TAG_OUTPUT);
       if (alloc.failed) { rc = COOP_E_NOMEM; break; }

@@ -1,14 +1,15 @@
-// Frontier dedup and relabelling (Eq. 2: S^{l+1} = S^l ∪ sampled sources): every edge's source vertex gets the FIRST
-// position of that vertex in the list [S^l ; col_global], through hash tables in LDS after a partition of the list into
-// buckets (long lists, further down) or through one open-addressing hash table in HBM (short lists, and the fallback).
+// Frontier dedup and relabelling (Eq. 2: S^{l+1} = S^l ∪ sampled sources).  Every edge's source vertex gets the FIRST
+// position of that vertex in the list [S^l ; col_global]; a vertex is "new" exactly at the edge whose position equals that
+// first position (and is not a seed position).  The new-flags are kept as a bit per edge; bit counts per 64-edge word, their
+// scan inside a block's stretch and the scan of the stretches' totals give each new vertex its rank, hence its place
+// n_dst + rank in S^{l+1}: the order is "S^l, then first appearance in col_global", independent of scheduling.
 //
-// The table in HBM: the list is inserted into a table of 8-byte slots (key << 32 | position in that list).  A slot is
-// claimed with atomicCAS; every further occurrence of the key lowers the slot's position with atomicMin, so after
-// the insert kernel each slot holds the FIRST position of its key, whichever thread won the race.  A vertex is
-// "new" exactly at the edge whose position equals that first position (and is not a seed position).  The new-flags
-// are kept as a bit per edge; a device-wide scan over the words' bit counts plus a bit count inside the word gives each
-// new vertex its rank, hence its place n_dst + rank in S^{l+1}: the order is "S^l, then first appearance in
-// col_global", independent of scheduling.
+// First positions come from hash tables in LDS: a block owns the keys of one bucket of hash values, and all occurrences of
+// a key share a bucket, so the minimum position found there is the global one.  Short lists: every block reads the whole
+// list and picks its keys (k_uniq_filter).  Long lists: a partition brings each bucket's pairs together first.  A bucket
+// with more distinct keys than its table serves sends the call to one open-addressing table in HBM (k_uniq_insert).
+// The distinct keys are known once the first positions are, so the block that finishes last there sends the sizes to the
+// host, and the host's wait and the setup of the next layer run beside the collecting and relabelling kernels.
 #include "coop_internal.h"
 #include "device_utils.h"
 
@@ -61,47 +62,202 @@ __device__ __forceinline__ uint32_t first_position(const unsigned long long* __r
   }
 }
 
-// first[e] = first position of col[e] in [S^l ; col]; bit e of `bits` = that position is this very edge
-__global__ __launch_bounds__(kBlock) void k_uniq_flag(const int32_t* __restrict__ col, int64_t m, const int64_t* __restrict__ m_dev,
-                                                      int64_t n_dst, const unsigned long long* __restrict__ table, uint64_t cap,
-                                                      uint32_t* __restrict__ first, uint64_t* __restrict__ bits) {
+// first[e] = first position of col[e] in [S^l ; col]
+__global__ __launch_bounds__(kBlock) void k_uniq_lookup(const int32_t* __restrict__ col, int64_t m, const int64_t* __restrict__ m_dev,
+                                                        const unsigned long long* __restrict__ table, uint64_t cap,
+                                                        uint32_t* __restrict__ first) {
   const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (m_dev != nullptr && *m_dev < m) m = *m_dev;
-  bool is_new = false;
-  if (e < m) {
-    const uint32_t f = first_position(table, cap, (uint32_t)col[e]);
-    first[e] = f;
-    is_new = (int64_t)f == n_dst + e;
-  }
-  const uint64_t b = ballot64(is_new);
-  if (lane_id() == 0 && (e & ~(int64_t)63) < m) bits[e >> 6] = b;
+  if (e < m) first[e] = first_position(table, cap, (uint32_t)col[e]);
 }
 
-// col_local and the tail of src_ids; the threads of the first n_dst positions also copy S^l to the front of src_ids
-// (m_dev, optional: the exact number of edges, on the device; m is then the capacity of col.  The kernel may be
-// launched before the host has seen the dedup's error and overflow flags, on a `first` that a failed dedup left
-// partly unwritten: positions outside [0, n_dst + m) are skipped, so that every access stays inside the arrays whatever
-// `first` holds; the caller discards the result in that case.)
-__global__ __launch_bounds__(kBlock) void k_uniq_relabel(const int32_t* __restrict__ dst, const int32_t* __restrict__ col, int64_t m,
-                                                         const int64_t* __restrict__ m_dev, int64_t n_dst,
-                                                         const uint32_t* __restrict__ first, const uint64_t* __restrict__ bits,
-                                                         TiledScan<uint32_t> word_rank, int32_t* __restrict__ src,
-                                                         int32_t* __restrict__ col_local) {
-  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
-  if (e < n_dst) src[e] = dst[e];
-  if (e >= m) return;
-  const int64_t f = first[e];
-  if (f >= n_dst + m) return;
-  int64_t local = f;
-  if (f >= n_dst) {
-    const int64_t at = f - n_dst;  // the edge at which this vertex first appears
-    const uint64_t below = bits[at >> 6] & ((1ull << (at & 63)) - 1ull);
-    local = n_dst + word_rank.at(at >> 6) + __popcll(below);
-    if (at == e) src[local] = col[e];
+// ---- a bucket's table in LDS -------------------------------------------------------------------------------------
+// Slots of 8 bytes (key << 32 | position), as in the table in HBM.  The table gives up at `most` distinct keys, with room
+// left for one claim per thread under way, so that a probe always reaches an empty slot.  (The reads are relaxed atomics:
+// volatile ones would become flat loads.  Keys and positions in separate 32-bit arrays, and two or four insertions side
+// by side per thread, were slower: 45 us for the 1,536 buckets of 5.8 M entries in the place of 36.)
+struct BucketState { uint32_t claimed, full, dup; };
+__device__ __forceinline__ uint32_t lds_read(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+__device__ __forceinline__ uint32_t bucket_insert(unsigned long long* table, uint32_t slots, uint32_t most, uint32_t h, unsigned long long mine,
+                                                  uint32_t nd, BucketState* st) {
+  const uint32_t key = (uint32_t)(mine >> 32);
+  const bool seed_pos = (uint32_t)mine < nd;
+  for (;;) {
+    unsigned long long cur = __hip_atomic_load(&table[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (cur == kEmptySlot) {
+      cur = atomicCAS(&table[h], (unsigned long long)kEmptySlot, mine);
+      if (cur == kEmptySlot) {
+        if (atomicAdd(&st->claimed, 1u) >= most) st->full = 1;
+        return h;
+      }
+    }
+    if ((uint32_t)(cur >> 32) == key) {
+      if (!seed_pos && cur < mine) return h;  // (a hub that many lists keep lowers its position a few times, not every time)
+      const unsigned long long old = atomicMin(&table[h], mine);
+      if (seed_pos && (uint32_t)old < nd) st->dup = 1;  // S^l holds a vertex twice
+      return h;
+    }
+    h = (h + 1) & (slots - 1);
   }
-  col_local[e] = (int32_t)local;
 }
+__device__ __forceinline__ uint32_t bucket_find(const unsigned long long* table, uint32_t slots, uint32_t h, uint32_t key) {
+  for (;;) {  // (every key looked up was inserted; an empty slot ends the search regardless)
+    const unsigned long long cur = table[h];
+    if ((uint32_t)(cur >> 32) == key || cur == kEmptySlot) return (uint32_t)cur;
+    h = (h + 1) & (slots - 1);
+  }
+}
+
+// One thread per block, when the block's part of the first positions is done: adds the distinct keys and counts the block;
+// the last one stores the number of new vertices and sends the control block to the host.
+__device__ __forceinline__ void bucket_done(Ctl* ctl, const BucketState& st, int64_t n_dst, const Publish& pub) {
+  if (st.dup | st.full) {  // (rare: the fence orders the flag before the count)
+    if (st.dup) atomicOr(&ctl->err_dup, 1);
+    if (st.full) atomicOr(&ctl->uniq_overflow, 1);
+    __threadfence();
+  }
+  uint32_t distinct;
+  if (!tally_last(ctl, st.claimed, &distinct)) return;
+  const int64_t n_new = (int64_t)distinct - n_dst;
+  ctl->total_new = n_new;
+  if (pub.h == nullptr) return;
+  pub.h->ctl = *ctl;  // (the fields of earlier kernels; those of this one follow)
+  pub.h->ctl.total_new = n_new;
+  pub.h->ctl.err_dup = __hip_atomic_load(&ctl->err_dup, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  pub.h->ctl.uniq_overflow = __hip_atomic_load(&ctl->uniq_overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __threadfence_system();
+  __hip_atomic_store(&pub.h->ticket, pub.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// ---- first positions of a short list -----------------------------------------------------------------------------
+// Block b reads the whole list and notes, wave by wave, the positions whose key hashes to bucket b; those keys go into the
+// block's table, and the edges among them get what the table then says.  One launch in the place of clearing a table,
+// inserting and looking up in HBM, and no atomic leaves the block.  Reading everything in every block is what it pays for
+// that, three vector instructions per key, which is why it ends at kFilterMax entries.  188 thousand entries 17 us (clear,
+// insert and look up in HBM: 25), 11 to 58 thousand 10 to 12 us (10 to 16).
+constexpr int kFilterBlock = 1024;
+constexpr uint32_t kFilterSlots = 4096;
+constexpr uint32_t kFilterFull = kFilterSlots / 4 * 3 - kFilterBlock;  // distinct keys at which a bucket gives up
+constexpr uint32_t kFilterList = 256;                   // positions that a wave can note
+constexpr int64_t kFilterPairs = 1024;                  // mean entries of a bucket (64 per wave)
+constexpr int64_t kFilterMax = 262144;                  // 256 buckets at most: one per CU
+__device__ __forceinline__ uint32_t filter_hash(uint32_t key) { return key * 0x9E3779B9u; }
+
+__global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
+                                                              int64_t m, const int64_t* __restrict__ m_dev, int log2_buckets,
+                                                              uint32_t* __restrict__ first, Ctl* ctl, Publish pub) {
+  __shared__ unsigned long long table[kFilterSlots];
+  __shared__ uint32_t noted[kFilterBlock / kWave][kFilterList];
+  __shared__ BucketState st;
+  __shared__ uint32_t s_overflow;
+  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  const uint32_t n = (uint32_t)(n_dst + m);  // (below kFilterMax)
+  const uint32_t nd = (uint32_t)n_dst;
+  for (uint32_t i = threadIdx.x; i < kFilterSlots; i += kFilterBlock) table[i] = kEmptySlot;
+  if (threadIdx.x == 0) { st = BucketState{0u, 0u, 0u}; s_overflow = 0; }
+  __syncthreads();
+  auto key_at = [&](uint32_t i) { return (uint32_t)(i < nd ? dst[i] : col[i - nd]); };
+  const uint32_t width = 1u << (32 - log2_buckets), low = blockIdx.x * width;  // the bucket's hashes: low .. low + width - 1 (log2_buckets >= 1)
+  auto slot = [&](uint32_t h) { return (h << log2_buckets) >> 20; };           // the hash bits behind those of the bucket
+  static_assert(kFilterSlots == 1u << 12, "slot() takes 12 bits");
+  uint32_t* list = noted[uniform_wave_in_block()];
+  uint32_t count = 0;  // (the same in every lane)
+  // Each part of the list ([S^l], [col]; 256-byte aligned and padded to that) is read as groups of four keys, U groups per
+  // thread and step, the next step's groups requested before this step's keys are looked at.
+  constexpr uint32_t U = 4;
+  auto part = [&](const int32_t* __restrict__ p, uint32_t len, uint32_t at0) {
+    const uint32_t groups = (len + 3) / 4;
+    u32x4 next[U];
+    auto fetch = [&](uint32_t g0) {
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t g = g0 + u * kFilterBlock + threadIdx.x;
+        next[u] = reinterpret_cast<const u32x4*>(p)[g < groups ? g : groups - 1];
+      }
+    };
+    if (groups > 0) fetch(0);
+    for (uint32_t g0 = 0; g0 < groups; g0 += U * kFilterBlock) {
+      uint32_t off[U][4];  // hash minus the bucket's lowest: one of the bucket's if below width
+      uint32_t least = 0xFFFFFFFFu;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u)
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e) {
+          off[u][e] = filter_hash(next[u][e]) - low;
+          least = off[u][e] < least ? off[u][e] : least;
+        }
+      if (g0 + U * kFilterBlock < groups) fetch(g0 + U * kFilterBlock);
+      if (ballot64(least < width) == 0) continue;
+      uint32_t flags = 0;  // bit 4 u + e
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u)
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e) flags |= off[u][e] < width ? 1u << (4 * u + e) : 0u;
+      const uint32_t i0 = (g0 + threadIdx.x) * 4;  // entry of this thread's first key in this part
+      for (;;) {  // a few of the wave's 1024 keys: every round notes one of each lane's
+        const uint64_t some = ballot64(flags != 0);
+        if (some == 0) break;
+        const uint32_t bit = flags != 0 ? (uint32_t)__builtin_ctz(flags) : 0u;
+        const uint32_t i = i0 + (bit >> 2) * (4 * kFilterBlock) + (bit & 3u);
+        const bool in = flags != 0 && i < len;
+        const uint64_t mask = ballot64(in);
+        const uint32_t to = count + lanes_below(mask);
+        if (in && to < kFilterList) list[to] = at0 + i;
+        count += (uint32_t)__popcll(mask);
+        flags &= flags - 1;
+      }
+    }
+  };
+  part(dst, nd, 0u);
+  part(col, n - nd, nd);
+  if (count > kFilterList && lane_id() == 0) s_overflow = 1;
+  __syncthreads();
+  if (s_overflow == 0) {  // every wave goes on with its own list
+    constexpr int V = kFilterList / kWave;
+    unsigned long long pair[V];
+    uint32_t h[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const uint32_t q = (uint32_t)(v * kWave + lane_id());
+      const bool in = q < count;
+      const uint32_t i = in ? list[q] : 0u;
+      const uint32_t key = in ? key_at(i) : 0u;
+      h[v] = slot(filter_hash(key));
+      pair[v] = in ? ((unsigned long long)key << 32) | i : kEmptySlot;
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if (pair[v] != kEmptySlot && lds_read(&st.full) == 0) h[v] = bucket_insert(table, kFilterSlots, kFilterFull, h[v], pair[v], nd, &st);
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if (pair[v] != kEmptySlot && (uint32_t)pair[v] >= nd) first[(uint32_t)pair[v] - nd] = (uint32_t)table[h[v]];
+  } else {  // (a vertex that very many lists keep): the whole list is read again, twice
+    for (uint32_t i = threadIdx.x; i < n; i += kFilterBlock) {
+      const uint32_t key = key_at(i), hash = filter_hash(key);
+      if (hash - low < width && lds_read(&st.full) == 0)
+        bucket_insert(table, kFilterSlots, kFilterFull, slot(hash), ((unsigned long long)key << 32) | i, nd, &st);
+    }
+    __syncthreads();
+    for (uint32_t i = nd + threadIdx.x; i < n && st.full == 0; i += kFilterBlock) {
+      const uint32_t key = key_at(i), hash = filter_hash(key);
+      if (hash - low < width) first[i - nd] = bucket_find(table, kFilterSlots, slot(hash), key);
+    }
+  }
+  if (threadIdx.x == 0) bucket_done(ctl, st, n_dst, pub);
+}
+
+// ---- ranks and local ids -----------------------------------------------------------------------------------------
+// The new-flags are a bit per position of [S^l ; col]: bit i is set when edge i - n_dst is the first occurrence of its
+// vertex.  The rank of such a position among them is kept in three parts: the bits below it in its word, the bits of the
+// words in front of it in its block's stretch of positions (one record with the word: looking ranks up is bound by the number
+// of scattered requests), and those of the stretches in front (block_prefix).
+struct RankView {
+  const RankWord* word;
+  const uint32_t* block_prefix;
+  uint32_t n_blocks;  // when not 0: the stretches are those of the partition's blocks (part_stretch_len of the whole list)
+};
+constexpr int64_t kCollectStretch = 8192;
 
 // ---- first positions by partition ------------------------------------------------------------------------------
 // For long lists the table in HBM costs two dependent random accesses per entry (insert, then look-up), each an
@@ -109,8 +265,13 @@ __global__ __launch_bounds__(kBlock) void k_uniq_relabel(const int32_t* __restri
 // distributed over buckets by the high bits of the key's hash (count, scan, scatter: the classic three-step
 // partition, with a counter matrix [bucket][block] so that no atomic leaves a block and every pair has its place
 // before it is moved), and a bucket, about kPartPairs pairs, is deduplicated by one block in a table in LDS.
-// All occurrences of a key share a bucket, so the minimum position found there is the global first position.  The
-// results are the same `first` and `bits` arrays that the table in HBM produces.
+// The scatter orders a tile of the list by bucket and notes, in that order, where every entry went and which entry of the
+// tile it is; the first positions are left in the buckets' order, written in streams, and the collecting kernel reads
+// them back run by run and puts the tile into list order in LDS.  4-byte stores from the buckets to the places in the list
+// cost a partial line each (5.8 M of them 72 us, however they are spread over the XCDs).  For the 5.8 M entries of a last
+// papers100M-shaped layer: scatter 37 us (2.8 TB/s; as before, with 6 bytes per entry more to write), first positions 36
+// (84 with the stores to random places), collecting with the ranks 26 (20 for two kernels that only made flags and ranks),
+// relabelling 21 (24; 75 MB, 3.6 TB/s).
 constexpr int kPartBlock = 1024;        // threads of a counting / scattering block
 constexpr int kPartMaxBlocks = 512;     // blocks of those two kernels (two per compute unit)
 constexpr int kPartPairs = 4096;        // mean pairs of a bucket
@@ -132,9 +293,12 @@ __device__ __forceinline__ uint32_t table_slot_of_hash(uint32_t h) {
 }
 
 // The stretch of [S^l ; col] that block `block` of `n_blocks` counts and scatters.
+__device__ __forceinline__ int64_t part_stretch_len(int64_t n_all, uint32_t n_blocks) {
+  const int64_t stretch = (n_all + n_blocks - 1) / n_blocks;
+  return (stretch + kPartBlock - 1) / kPartBlock * kPartBlock;
+}
 __device__ __forceinline__ void part_stretch(int64_t n_all, uint32_t n_blocks, uint32_t block, int64_t* lo, int64_t* hi) {
-  int64_t stretch = (n_all + n_blocks - 1) / n_blocks;
-  stretch = (stretch + kPartBlock - 1) / kPartBlock * kPartBlock;
+  const int64_t stretch = part_stretch_len(n_all, n_blocks);
   *lo = (int64_t)block * stretch;
   *hi = *lo + stretch < n_all ? *lo + stretch : n_all;
   if (*lo > n_all) *lo = n_all;
@@ -172,29 +336,37 @@ __global__ __launch_bounds__(kPartBlock) void k_part_count(const int32_t* __rest
 }
 
 // The same stretch again: its pairs go to pairs[], bucket b's from place[b * gridDim.x + column] on (place = exclusive
-// scan of counts).  A round of kTilePairs pairs is first ordered by bucket in LDS, so that the pairs of a round that
-// share a bucket leave as one contiguous run written by neighbouring lanes, not as single 8-byte stores.
+// scan of counts).  A tile of kTilePairs pairs is first ordered by bucket in LDS, so that the pairs of a tile that share a
+// bucket leave as one contiguous run written by neighbouring lanes, not as single 8-byte stores.  In the tile's new order,
+// went[] gets every pair's index in pairs[] and which[] its number in the tile, for k_uniq_collect.
 constexpr int kTilePairs = 8 * kPartBlock;
-__global__ __launch_bounds__(kPartBlock) void k_part_scatter(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
+// PER: buckets that a thread looks after.  (64 registers, so that two blocks fit a CU.)
+template <int PER>
+__global__ __launch_bounds__(kPartBlock, PER <= 2 ? 8 : 4) void k_part_scatter(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
                                                              int64_t m, const int64_t* __restrict__ m_dev, uint32_t n_buckets,
-                                                             TiledScan<uint32_t> place, unsigned long long* __restrict__ pairs) {
-  __shared__ unsigned long long staged[kTilePairs];  // the round's pairs, by bucket
-  extern __shared__ uint32_t cursor[];               // [n_buckets] next free place of the bucket's column
-  uint32_t* off = cursor + n_buckets;                // [n_buckets] the round's tallies, then run starts
+                                                             TiledScan<uint32_t> place, unsigned long long* __restrict__ pairs,
+                                                             uint32_t* __restrict__ went, uint16_t* __restrict__ which) {
+  __shared__ unsigned long long staged[kTilePairs];  // the tile's pairs, by bucket
+  extern __shared__ uint32_t off[];                  // [n_buckets] the tile's tallies, then run starts in the tile
+  uint32_t* delta = off + n_buckets;                 // [n_buckets] run start in pairs[] minus run start in the tile
   __shared__ uint32_t wave_total[kPartBlock / kWave];
   if (m_dev != nullptr && *m_dev < m) m = *m_dev;
   int64_t lo, hi;
   part_stretch(n_dst + m, gridDim.x, blockIdx.x, &lo, &hi);
   const uint32_t column = part_column();
-  for (uint32_t b = threadIdx.x; b < n_buckets; b += kPartBlock) cursor[b] = place.at((int64_t)b * gridDim.x + column);
-  const uint32_t per = (n_buckets + kPartBlock - 1) / kPartBlock;  // tallies that a thread scans (at most 8)
   const int lane = lane_id(), wave = wave_in_block();
+  constexpr int U = kTilePairs / kPartBlock;
+  uint32_t cursor[PER];  // next free place of this thread's buckets in this column
+#pragma unroll
+  for (uint32_t q = 0; q < PER; ++q) {
+    const uint32_t b = threadIdx.x * PER + q;
+    cursor[q] = b < n_buckets ? place.at((int64_t)b * gridDim.x + column) : 0u;
+    if (b < n_buckets) off[b] = 0u;
+  }
+  __syncthreads();
   for (int64_t tile = lo; tile < hi; tile += kTilePairs) {
     const uint32_t tile_n = (uint32_t)(hi - tile < kTilePairs ? hi - tile : kTilePairs);
-    for (uint32_t b = threadIdx.x; b < n_buckets; b += kPartBlock) off[b] = 0u;
-    __syncthreads();
-    constexpr int U = kTilePairs / kPartBlock;
-    uint32_t key[U], bucket[U], rank[U];
+    uint32_t key[U], place_in[U];  // place_in: bucket << 16 | rank in the tile's bucket
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t i = tile + u * kPartBlock + threadIdx.x;
@@ -202,143 +374,276 @@ __global__ __launch_bounds__(kPartBlock) void k_part_scatter(const int32_t* __re
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (tile + u * kPartBlock + threadIdx.x >= hi) continue;
-      bucket[u] = bucket_of_hash(hash_of_key(key[u]), n_buckets);
-      rank[u] = atomicAdd(&off[bucket[u]], 1u);
+      const uint32_t bucket = bucket_of_hash(hash_of_key(key[u]), n_buckets);
+      place_in[u] = bucket << 16;
+      if ((uint32_t)(u * kPartBlock) + threadIdx.x < tile_n) place_in[u] |= atomicAdd(&off[bucket], 1u);
     }
     __syncthreads();
     {  // tallies -> run starts (exclusive scan over the buckets)
-      uint32_t c[8], sum = 0;
+      uint32_t c[PER], sum = 0;
 #pragma unroll
-      for (uint32_t q = 0; q < 8; ++q) {
-        const uint32_t b = threadIdx.x * per + q;
-        c[q] = q < per && b < n_buckets ? off[b] : 0u;
+      for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t b = threadIdx.x * PER + q;
+        c[q] = b < n_buckets ? off[b] : 0u;
         sum += c[q];
       }
-      uint32_t incl = sum;
-#pragma unroll
-      for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t o = __shfl_up(incl, d, kWave);
-        if (lane >= d) incl += o;
-      }
+      const uint32_t incl = wave_incl_scan(sum);
       if (lane == kWave - 1) wave_total[wave] = incl;
       __syncthreads();
       uint32_t run = incl - sum;
       for (int w = 0; w < wave; ++w) run += wave_total[w];
 #pragma unroll
-      for (uint32_t q = 0; q < 8; ++q) {
-        const uint32_t b = threadIdx.x * per + q;
-        if (q < per && b < n_buckets) off[b] = run;
+      for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t b = threadIdx.x * PER + q;
+        if (b < n_buckets) {
+          off[b] = run;
+          delta[b] = cursor[q] - run;
+          cursor[q] += c[q];
+        }
         run += c[q];
       }
     }
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t i = tile + u * kPartBlock + threadIdx.x;
-      if (i < hi) staged[off[bucket[u]] + rank[u]] = ((unsigned long long)key[u] << 32) | (uint32_t)i;
+      const uint32_t j = (uint32_t)(u * kPartBlock) + threadIdx.x;
+      if (j < tile_n) staged[off[place_in[u] >> 16] + (place_in[u] & 0xFFFFu)] = ((unsigned long long)key[u] << 32) | j;
     }
     __syncthreads();
-    for (uint32_t j = threadIdx.x; j < tile_n; j += kPartBlock) {
-      const unsigned long long pr = staged[j];
-      const uint32_t b = bucket_of_hash(hash_of_key((uint32_t)(pr >> 32)), n_buckets);
-      pairs[cursor[b] + (j - off[b])] = pr;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t j = (uint32_t)(u * kPartBlock) + threadIdx.x;
+      if (j < tile_n) {
+        const unsigned long long pr = staged[j];
+        const uint32_t to = delta[bucket_of_hash(hash_of_key((uint32_t)(pr >> 32)), n_buckets)] + j;
+        pairs[to] = pr + (uint32_t)tile;  // (positions stay below 2^32)
+        went[tile + j] = to;
+        which[tile + j] = (uint16_t)pr;
+      }
     }
-    __syncthreads();
-    for (uint32_t b = threadIdx.x; b < n_buckets; b += kPartBlock) cursor[b] += (b + 1 < n_buckets ? off[b + 1] : tile_n) - off[b];
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+      const uint32_t b = threadIdx.x * PER + q;
+      if (b < n_buckets) off[b] = 0u;
+    }
     __syncthreads();
   }
 }
 
-// One bucket per block: first positions of the bucket's keys through a table in LDS, then first[] of the bucket's edges.
-__global__ __launch_bounds__(kFirstBlock) void k_part_first(const unsigned long long* __restrict__ pairs, TiledScan<uint32_t> place,
-                                                            uint32_t G, int64_t n_dst, int64_t n_all, uint32_t* __restrict__ first,
-                                                            Ctl* ctl) {
+// One bucket per block: first positions of the bucket's keys through a table in LDS; by_place[p] = that of pair p.
+// (64 registers and 64 KB of LDS: two blocks per CU.)
+__global__ __launch_bounds__(kFirstBlock, 8) void k_part_first(const unsigned long long* __restrict__ pairs, TiledScan<uint32_t> place,
+                                                               uint32_t G, int64_t n_dst, int64_t n_all, uint32_t* __restrict__ by_place,
+                                                               Ctl* ctl, Publish pub) {
   __shared__ unsigned long long table[kPartSlots];
-  __shared__ uint32_t n_claimed, full;
+  __shared__ BucketState st;
   uint32_t lo = place.at((int64_t)blockIdx.x * G), hi = place.at((int64_t)(blockIdx.x + 1) * G);
   if ((int64_t)hi > n_all) hi = (uint32_t)n_all;  // (holds by construction; keeps every access inside the arrays regardless)
   if (lo > hi) lo = hi;
-  for (uint32_t i = threadIdx.x; i < kPartSlots; i += kFirstBlock) table[i] = kEmptySlot;
-  if (threadIdx.x == 0) { n_claimed = 0; full = 0; }
-  __syncthreads();
+  const uint32_t nd = (uint32_t)n_dst;
   constexpr int U = 4;  // pairs per thread and round, loaded together
-  unsigned long long first_round[U];  // the pairs of the first round, kept for the look-up phase
-#pragma unroll
-  for (int u = 0; u < U; ++u) first_round[u] = kEmptySlot;
-  for (uint32_t base = lo; base < hi; base += U * kFirstBlock) {
-    if (*(volatile uint32_t*)&full) break;
-    unsigned long long mine[U];
+  unsigned long long mine[U];
+  auto fetch = [&](uint32_t base) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t i = base + u * kFirstBlock + threadIdx.x;
       mine[u] = i < hi ? pairs[i] : kEmptySlot;
-      if (base == lo) first_round[u] = mine[u];
     }
+  };
+  fetch(lo);  // under way while the table is cleared
+  for (uint32_t i = threadIdx.x; i < kPartSlots; i += kFirstBlock) table[i] = kEmptySlot;
+  if (threadIdx.x == 0) st = BucketState{0u, 0u, 0u};
+  __syncthreads();
+  uint32_t h[U];
+  for (uint32_t base = lo; base < hi; base += U * kFirstBlock) {
+    if (base != lo) fetch(base);
+    if (lds_read(&st.full) != 0) break;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (mine[u] == kEmptySlot || *(volatile uint32_t*)&full) continue;
-      const uint32_t key = (uint32_t)(mine[u] >> 32);
-      const bool seed_pos = (int64_t)(uint32_t)mine[u] < n_dst;
-      uint32_t h = table_slot_of_hash(hash_of_key(key));
-      for (;;) {  // ends: at most kPartFull + 1 + kFirstBlock < kPartSlots slots are ever claimed
-        unsigned long long cur = *(volatile unsigned long long*)&table[h];
-        if (cur == kEmptySlot) {
-          cur = atomicCAS(&table[h], (unsigned long long)kEmptySlot, mine[u]);
-          if (cur == kEmptySlot) {
-            if (atomicAdd(&n_claimed, 1u) >= kPartFull) full = 1;
-            break;
-          }
-        }
-        if ((uint32_t)(cur >> 32) == key) {
-          if (!seed_pos && cur < mine[u]) break;
-          const unsigned long long old = atomicMin(&table[h], mine[u]);
-          if (seed_pos && (int64_t)(uint32_t)old < n_dst) atomicOr(&ctl->err_dup, 1);  // S^l holds a vertex twice
-          break;
-        }
-        h = (h + 1) & (kPartSlots - 1);
-      }
+      h[u] = 0;
+      if (mine[u] == kEmptySlot || lds_read(&st.full) != 0) continue;
+      h[u] = bucket_insert(table, kPartSlots, kPartFull, table_slot_of_hash(hash_of_key((uint32_t)(mine[u] >> 32))), mine[u], nd, &st);
     }
   }
   __syncthreads();
-  if (full) {  // more distinct keys than the table serves: the caller falls back to the table in HBM
-    if (threadIdx.x == 0) atomicOr(&ctl->uniq_overflow, 1);
-    return;
+  if (hi - lo <= (uint32_t)(U * kFirstBlock)) {  // the usual bucket: one round, whose slots are at hand
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t i = lo + u * kFirstBlock + threadIdx.x;
+      if (i < hi) by_place[i] = (uint32_t)table[h[u]];
+    }
+  } else if (st.full == 0) {
+    for (uint32_t i = lo + threadIdx.x; i < hi; i += kFirstBlock) {
+      const uint32_t key = (uint32_t)(pairs[i] >> 32);
+      by_place[i] = bucket_find(table, kPartSlots, table_slot_of_hash(hash_of_key(key)), key);
+    }
   }
-  const bool one_round = hi - lo <= (uint32_t)(U * kFirstBlock);  // (the usual bucket: its pairs are still in the registers)
-  for (uint32_t base = lo; base < hi; base += U * kFirstBlock) {
-    unsigned long long mine[U];
+  if (threadIdx.x == 0) bucket_done(ctl, st, n_dst, pub);
+}
+
+// List order again, the new-flags and their ranks (see RankView).  GATHER: the first positions lie in by_place and go to
+// first[e] (edge order), tile by tile: neighbouring lanes read the runs that the scatter wrote, LDS turns the tile into
+// list order.  Else first[e] is there already.  A block takes the stretch that the block of the same number scattered
+// (the same XCD, as blocks are dealt to the XCDs in order, and so the columns of by_place that its L2 has seen).
+template <bool GATHER>
+__global__ __launch_bounds__(kPartBlock, 8) void k_uniq_collect(uint32_t* __restrict__ first, const uint32_t* __restrict__ by_place,
+                                                             const uint32_t* __restrict__ went, const uint16_t* __restrict__ which, int64_t m,
+                                                             const int64_t* __restrict__ m_dev, int64_t n_dst, RankWord* __restrict__ words,
+                                                             uint32_t* __restrict__ block_total,
+                                                             uint32_t* __restrict__ block_prefix, Ctl* ctl, Publish pub) {
+  constexpr int U = kTilePairs / kPartBlock, kWaves = kPartBlock / kWave, kWords = kTilePairs / 64;
+  static_assert(kWords == 2 * kWave, "two words per lane of the scanning wave");
+  static_assert(kCollectStretch == kTilePairs, "one tile per block when the stretches are not the partition's");
+  __shared__ uint32_t in_order[GATHER ? kTilePairs : 1];
+  __shared__ uint32_t count[2][kWords];
+  __shared__ uint32_t s_last;
+  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  const int64_t n_all = n_dst + m;
+  int64_t lo, hi;
+  if constexpr (GATHER) {
+    part_stretch(n_all, gridDim.x, blockIdx.x, &lo, &hi);
+  } else {
+    lo = (int64_t)blockIdx.x * kCollectStretch;
+    hi = lo + kCollectStretch < n_all ? lo + kCollectStretch : n_all;
+  }
+  const int lane = lane_id(), wave = wave_in_block();
+  uint32_t run = 0;  // (kept by the first wave)
+  int flip = 0;
+  for (int64_t tile = lo; tile < hi; tile += kTilePairs, flip ^= 1) {
+    const uint32_t tile_n = (uint32_t)(hi - tile < kTilePairs ? hi - tile : kTilePairs);
+    uint32_t f[U];
+    if constexpr (GATHER) {
+      uint32_t at[U], to[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t i = base + u * kFirstBlock + threadIdx.x;
-      mine[u] = one_round ? first_round[u] : (i < hi ? pairs[i] : kEmptySlot);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t pos = (uint32_t)mine[u];
-      if (mine[u] == kEmptySlot || pos < n_dst || pos >= n_all) continue;
-      const uint32_t key = (uint32_t)(mine[u] >> 32);
-      uint32_t h = table_slot_of_hash(hash_of_key(key));
-      unsigned long long cur;
-      for (;;) {  // (every key of the bucket was inserted above; an empty slot ends the search regardless)
-        cur = table[h];
-        if ((uint32_t)(cur >> 32) == key || cur == kEmptySlot) break;
-        h = (h + 1) & (kPartSlots - 1);
+      for (int u = 0; u < U; ++u) {
+        const uint32_t j = (uint32_t)(u * kPartBlock) + threadIdx.x;
+        at[u] = went[tile + (j < tile_n ? j : 0u)];
+        to[u] = which[tile + (j < tile_n ? j : 0u)];
       }
-      const int64_t e = pos - n_dst;
-      first[e] = (uint32_t)cur;
+#pragma unroll
+      for (int u = 0; u < U; ++u) f[u] = by_place[at[u]];
+#pragma unroll
+      for (int u = 0; u < U; ++u) in_order[to[u]] = f[u];  // (a thread behind the tile's end repeats entry 0)
+      __syncthreads();
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t j = (uint32_t)(u * kPartBlock) + threadIdx.x;
+      const int64_t i = tile + j;
+      const bool edge = j < tile_n && i >= n_dst;
+      if constexpr (GATHER) {
+        f[u] = in_order[j];
+        if (edge) first[i - n_dst] = f[u];
+      } else {
+        f[u] = 0;
+        if (edge) f[u] = first[i - n_dst];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t j = (uint32_t)(u * kPartBlock) + threadIdx.x;
+      const int64_t i = tile + j;
+      const uint64_t b = ballot64(j < tile_n && i >= n_dst && (int64_t)f[u] == i);
+      if (lane == 0) {
+        if (j < tile_n) words[i >> 6].bits = b;
+        count[flip][u * kWaves + wave] = (uint32_t)__popcll(b);
+      }
+    }
+    __syncthreads();  // (two buffers of counts: the next tile's go to the other one while the first wave scans these)
+    if (wave == 0) {
+      const uint32_t a = count[flip][2 * lane], b = count[flip][2 * lane + 1];
+      const uint32_t incl = wave_incl_scan(a + b);
+      const uint32_t j = (uint32_t)lane * 128;
+      if (j < tile_n) words[(tile + j) >> 6].before = run + incl - a - b;
+      if (j + 64 < tile_n) words[((tile + j) >> 6) + 1].before = run + incl - b;
+      run += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+    }
+  }
+  if (threadIdx.x == 0) {
+    // the exchange has been performed when its result is here; the block counts itself behind it
+    const uint32_t old = atomicExch(&block_total[blockIdx.x], run);
+    asm volatile("" : : "v"(old) : "memory");
+    uint32_t unused;
+    s_last = tally_last(ctl, 0u, &unused) ? 1u : 0u;
+  }
+  __syncthreads();
+  if (s_last == 0) return;
+  __shared__ uint32_t wave_total[kWaves];
+  uint32_t carry = 0;
+  for (uint32_t base = 0; base < gridDim.x; base += kPartBlock) {
+    const uint32_t b = base + threadIdx.x;
+    const uint32_t v = b < gridDim.x ? __hip_atomic_load(&block_total[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    uint32_t incl = wave_incl_scan(v);
+    if (lane == kWave - 1) wave_total[wave] = incl;
+    __syncthreads();
+    uint32_t all = 0;
+    for (int w = 0; w < kWaves; ++w) {
+      if (w < wave) incl += wave_total[w];
+      all += wave_total[w];
+    }
+    if (b < gridDim.x) block_prefix[b] = carry + incl - v;
+    carry += all;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0 && pub.h != nullptr) {
+    ctl->total_new = carry;
+    pub.h->ctl = *ctl;
+    pub.h->ctl.total_new = carry;
+    __threadfence_system();
+    __hip_atomic_store(&pub.h->ticket, pub.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
-// bit e of `bits` = edge e is the first occurrence of its vertex (its first position is its own)
-__global__ __launch_bounds__(kBlock) void k_flag_from_first(const uint32_t* __restrict__ first, int64_t m, const int64_t* __restrict__ m_dev,
-                                                            int64_t n_dst, uint64_t* __restrict__ bits) {
-  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+// col_local and the tail of src_ids; the threads of the first n_dst positions also copy S^l to the front of src_ids.
+// col_local holds the first positions and gets the local ids in their place.
+// (m_dev, optional: the exact number of edges, on the device; m is then the capacity of col.  The kernel may be
+// launched before the host has seen the dedup's error and overflow flags, on first positions that a failed dedup left
+// partly unwritten: positions outside [0, n_dst + m) are skipped, so that every access stays inside the arrays whatever
+// they are; the caller discards the result in that case.)
+constexpr int kRelabelUnroll = 4;  // edges per thread in flight
+__global__ __launch_bounds__(kBlock) void k_uniq_relabel(const int32_t* __restrict__ dst, const int32_t* __restrict__ col, int64_t m,
+                                                         const int64_t* __restrict__ m_dev, int64_t n_dst, RankView rank,
+                                                         int32_t* __restrict__ src, int32_t* __restrict__ col_local) {
   if (m_dev != nullptr && *m_dev < m) m = *m_dev;
-  const bool is_new = e < m && (int64_t)first[e] == n_dst + e;
-  const uint64_t b = ballot64(is_new);
-  if (lane_id() == 0 && (e & ~(int64_t)63) < m) bits[e >> 6] = b;
+  // the stretch of a word by multiplication: exact while (positions / 1024) * (stretch / 1024) stays below 2^32
+  const int64_t stretch = rank.n_blocks ? part_stretch_len(n_dst + m, rank.n_blocks) : kCollectStretch;
+  const uint32_t d = (uint32_t)(stretch >> 10), magic = d <= 1 ? 0u : 0xFFFFFFFFu / d + 1u;
+  __shared__ uint32_t prefix[kPartMaxBlocks];
+  if (rank.n_blocks) {
+    for (uint32_t b = threadIdx.x; b < rank.n_blocks; b += kBlock) prefix[b] = rank.block_prefix[b];
+    __syncthreads();
+  }
+  const int64_t e0 = (int64_t)blockIdx.x * (kBlock * kRelabelUnroll) + threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < kRelabelUnroll; ++u) {
+    const int64_t e = e0 + u * kBlock;
+    if (e < n_dst) src[e] = dst[e];
+  }
+  uint32_t f[kRelabelUnroll];
+#pragma unroll
+  for (int u = 0; u < kRelabelUnroll; ++u) {
+    const int64_t e = e0 + u * kBlock;
+    f[u] = e < m ? (uint32_t)col_local[e] : 0xFFFFFFFFu;
+  }
+  RankWord w[kRelabelUnroll];
+#pragma unroll
+  for (int u = 0; u < kRelabelUnroll; ++u) {
+    w[u] = RankWord{0, 0, 0};
+    if ((int64_t)f[u] >= n_dst && (int64_t)f[u] < n_dst + m) w[u] = rank.word[f[u] >> 6];
+  }
+#pragma unroll
+  for (int u = 0; u < kRelabelUnroll; ++u) {
+    const int64_t e = e0 + u * kBlock;
+    if ((int64_t)f[u] >= n_dst + m) continue;
+    int64_t local = f[u];
+    if (local >= n_dst) {
+      const uint32_t q = f[u] >> 10, block = d <= 1 ? q : __umulhi(q, magic);
+      const uint32_t in_front = rank.n_blocks ? prefix[block] : rank.block_prefix[block];
+      local = n_dst + in_front + w[u].before + __popcll(w[u].bits & ((1ull << (f[u] & 63)) - 1ull));
+      if ((int64_t)f[u] == n_dst + e) src[local] = col[e];
+    }
+    col_local[e] = (int32_t)local;
+  }
 }
 
 __global__ void k_clear_uniq_overflow(Ctl* ctl) { ctl->uniq_overflow = 0; }
@@ -347,12 +652,25 @@ static inline unsigned nblocks(int64_t n) { return (unsigned)((n + kBlock - 1) /
 
 int g_unique_mode = 0;  // COOP_TUNE_UNIQUE: 0 automatic, 1 table in HBM, 2 partition whenever it applies, 3 as 2 with buckets 16 times too large
 
-// launches the dedup's kernels up to the scan that ranks the new vertices and sends the control block to the host
-static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, UniqueWork* w,
-                         bool by_partition, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
+// launches the dedup's kernels up to the one that ranks the new vertices; the sizes are on their way to the host from the
+// kernel that finds the first positions on.  col_local serves as the array of first positions (edge order).
+enum UniqPath { kByFilter, kByPartition, kByTable };
+static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
+                         UniqueWork* w, UniqPath path, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
   const int64_t n_all = n_dst + m;
-  const int64_t n_words = (m + 63) / 64;
-  if (by_partition) {
+  uint32_t* first = (uint32_t*)col_local;
+  w->pub = begin_publish(d_ctl, h_ctl);
+  w->path = path;
+  uint32_t collect_blocks = (uint32_t)((n_all + kCollectStretch - 1) / kCollectStretch);
+  const uint32_t *by_place = nullptr, *went_c = nullptr;
+  const uint16_t* which_c = nullptr;
+  w->part_blocks = 0;
+  if (path == kByFilter) {
+    int log2_buckets = 1;
+    while (((int64_t)kFilterPairs << log2_buckets) < n_all) ++log2_buckets;
+    COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_filter, dim3(1u << log2_buckets), dim3(kFilterBlock), 0, s, dst, n_dst, col_global, m, m_dev, log2_buckets,
+                first, d_ctl, w->pub);
+  } else if (path == kByPartition) {
     const int64_t n_buckets = w->n_buckets;
     const int64_t by_size = (n_all + 4 * kPartBlock - 1) / (4 * kPartBlock);
     const uint32_t G = (uint32_t)(by_size < kPartMaxBlocks ? (by_size + 7) / 8 * 8 : kPartMaxBlocks);  // a multiple of 8
@@ -360,16 +678,27 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     uint32_t* counts = alloc.get<uint32_t>(n_counts, COOP_TAG_SCRATCH);
     uint32_t* place = alloc.get<uint32_t>(n_counts + 1, COOP_TAG_SCRATCH);
     unsigned long long* pairs = alloc.get<unsigned long long>(n_all, COOP_TAG_SCRATCH);
+    uint32_t* firsts = alloc.get<uint32_t>(n_all, COOP_TAG_SCRATCH);
+    uint32_t* went = alloc.get<uint32_t>(n_all, COOP_TAG_SCRATCH);
+    uint16_t* which = alloc.get<uint16_t>(n_all, COOP_TAG_SCRATCH);
     void* tmp = alloc.get<char>((int64_t)scan_tmp_bytes(n_counts), COOP_TAG_SCRATCH);
     if (alloc.failed) return COOP_E_NOMEM;
     const size_t lds = (size_t)n_buckets * sizeof(uint32_t);
     COOP_LAUNCH(K_PART_COUNT, k_part_count, dim3(G), dim3(kPartBlock), lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets, counts);
     const TiledScan<uint32_t> places = scan_u32_tiled(counts, n_counts, place, tmp, &d_ctl->scan_done, s);
-    COOP_LAUNCH(K_PART_SCATTER, k_part_scatter, dim3(G), dim3(kPartBlock), 2 * lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets,
-                places, pairs);
-    COOP_LAUNCH(K_PART_FIRST, k_part_first, dim3((unsigned)n_buckets), dim3(kFirstBlock), 0, s, pairs, places, G, n_dst, n_all, w->first, d_ctl);
-    if (hipGetLastError() != hipSuccess) return COOP_E_HIP;  // (a launch that did not happen would leave `first` unwritten)
-    COOP_LAUNCH(K_UNIQ_FLAG, k_flag_from_first, dim3(nblocks(m)), dim3(kBlock), 0, s, w->first, m, m_dev, n_dst, w->bits);
+    static_assert(kPartMaxBuckets <= 8 * kPartBlock, "a thread of the scatter looks after eight buckets at most");
+    if (n_buckets <= 2 * kPartBlock)
+      COOP_LAUNCH(K_PART_SCATTER, k_part_scatter<2>, dim3(G), dim3(kPartBlock), 2 * lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets,
+                  places, pairs, went, which);
+    else
+      COOP_LAUNCH(K_PART_SCATTER, k_part_scatter<8>, dim3(G), dim3(kPartBlock), 2 * lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets,
+                  places, pairs, went, which);
+    COOP_LAUNCH(K_PART_FIRST, k_part_first, dim3((unsigned)n_buckets), dim3(kFirstBlock), 0, s, pairs, places, G, n_dst, n_all, firsts, d_ctl, w->pub);
+    if (hipGetLastError() != hipSuccess) return COOP_E_HIP;  // (a launch that did not happen would leave places or firsts unwritten)
+    by_place = firsts;
+    went_c = went;
+    which_c = which;
+    collect_blocks = w->part_blocks = G;
   } else {
     // at most half full; an even number of slots (the clear uses 16-byte stores)
     const int64_t cap = 2 * n_all + 1024;
@@ -381,42 +710,52 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
                   d_ctl);
     }
     if (m > 0)
-      COOP_LAUNCH(K_UNIQ_FLAG, k_uniq_flag, dim3(nblocks(m)), dim3(kBlock), 0, s, col_global, m, m_dev, n_dst, table, (uint64_t)cap, w->first,
-                  w->bits);
+      COOP_LAUNCH(K_UNIQ_FLAG, k_uniq_lookup, dim3(nblocks(m)), dim3(kBlock), 0, s, col_global, m, m_dev, table, (uint64_t)cap, first);
   }
-  // sizes (and the duplicate / range flags) back to the host, sent by the scan's last thread when there is a scan
-  w->pub = begin_publish(d_ctl, h_ctl);
-  if (m > 0) w->rank = scan_popc_tiled(w->bits, n_words, w->word_rank, &d_ctl->total_new, w->scan_tmp, &d_ctl->scan_done, s, &w->pub, m_dev);
-  else if (launch_publish(w->pub, s) != COOP_OK) return COOP_E_HIP;
-  w->by_partition = by_partition;
+  if (m > 0) {
+    uint32_t* totals = alloc.get<uint32_t>(2 * (int64_t)collect_blocks, COOP_TAG_SCRATCH);
+    if (alloc.failed) return COOP_E_NOMEM;
+    w->block_prefix = totals + collect_blocks;
+    // (the table in HBM does not count its keys: there the ranks bring the number of new vertices, and the sizes leave with them)
+    const Publish pub = path == kByTable ? w->pub : Publish{};
+    if (by_place)
+      COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<true>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, went_c, which_c, m, m_dev, n_dst,
+                  w->words, totals, w->block_prefix, d_ctl, pub);
+    else
+      COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<false>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, went_c, which_c, m, m_dev, n_dst,
+                  w->words, totals, w->block_prefix, d_ctl, pub);
+  } else if (path == kByTable && launch_publish(w->pub, s) != COOP_OK) {
+    return COOP_E_HIP;
+  }
   return COOP_OK;
 }
 
-int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, UniqueWork* w,
-                        Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
+int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
+                        UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
   const int64_t n_all = n_dst + m;
-  w->first = alloc.get<uint32_t>(m, COOP_TAG_SCRATCH);
-  const int64_t n_words = (m + 63) / 64;
-  w->word_rank = alloc.get<uint32_t>(n_words + 1, COOP_TAG_SCRATCH);
-  w->bits = alloc.get<uint64_t>(n_words, COOP_TAG_SCRATCH);
-  w->scan_tmp = alloc.get<char>((int64_t)scan_tmp_bytes(n_words), COOP_TAG_SCRATCH);
+  const int64_t n_words = (n_all + 63) / 64;
+  w->words = alloc.get<RankWord>(n_words, COOP_TAG_SCRATCH);
   if (alloc.failed) return COOP_E_NOMEM;
-  // by partition from a few hundred thousand entries on (below that its five launches cost more than the table's
-  // three), as long as a block's counters fit LDS
+  // by partition from kFilterMax entries on, as long as a block's counters fit LDS
   const int64_t pairs_per_bucket = g_unique_mode == 3 ? 16 * kPartPairs : kPartPairs;
   w->n_buckets = (n_all + pairs_per_bucket - 1) / pairs_per_bucket;
-  const bool by_partition = m > 0 && w->n_buckets <= kPartMaxBuckets && g_unique_mode != 1 && (g_unique_mode >= 2 || n_all >= 262144);
-  return unique_launch(dst, n_dst, col_global, m, m_dev, w, by_partition, alloc, d_ctl, h_ctl, s);
+  // two bucket blocks fit a CU: a last round of a few blocks is spread over the others, which grow by an eighth at most
+  const int64_t whole_rounds = w->n_buckets / 512 * 512;
+  if (whole_rounds > 0 && n_all <= whole_rounds * (pairs_per_bucket + pairs_per_bucket / 8)) w->n_buckets = whole_rounds;
+  const bool by_partition = m > 0 && w->n_buckets <= kPartMaxBuckets && g_unique_mode != 1 && (g_unique_mode >= 2 || n_all >= kFilterMax);
+  const bool by_filter = !by_partition && g_unique_mode != 1 && n_all > 0 && n_all < kFilterMax;
+  return unique_launch(dst, n_dst, col_global, m, m_dev, col_local, w, by_partition ? kByPartition : by_filter ? kByFilter : kByTable, alloc,
+                       d_ctl, h_ctl, s);
 }
 
-int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, UniqueWork* w,
-                        Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s, bool* redone) {
+int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
+                        UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s, bool* redone) {
   *redone = false;
   int rc = wait_ctl(w->pub, h_ctl, s);
   if (rc != COOP_OK) return rc;
-  if (w->by_partition && h_ctl->uniq_overflow != 0) {  // a bucket's table overflowed: once more through the table in HBM
+  if (w->path != kByTable && h_ctl->uniq_overflow != 0) {  // a bucket's table overflowed: once more through the table in HBM
     hipLaunchKernelGGL(k_clear_uniq_overflow, dim3(1), dim3(1), 0, s, d_ctl);
-    rc = unique_launch(dst, n_dst, col_global, m, m_dev, w, false, alloc, d_ctl, h_ctl, s);
+    rc = unique_launch(dst, n_dst, col_global, m, m_dev, col_local, w, kByTable, alloc, d_ctl, h_ctl, s);
     if (rc != COOP_OK) return rc;
     rc = wait_ctl(w->pub, h_ctl, s);
     if (rc != COOP_OK) return rc;
@@ -429,9 +768,9 @@ int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_gl
 int unique_back(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, const UniqueWork& w,
                 int32_t* col_local, int32_t* src, hipStream_t s) {
   const int64_t n_threads = m > n_dst ? m : n_dst;
+  const RankView rank{w.words, w.block_prefix, w.part_blocks};
   if (n_threads > 0)
-    COOP_LAUNCH(K_UNIQ_RELABEL, k_uniq_relabel, dim3(nblocks(n_threads)), dim3(kBlock), 0, s, dst, col_global, m, m_dev, n_dst, w.first, w.bits,
-                w.rank, src, col_local);
+    COOP_LAUNCH(K_UNIQ_RELABEL, k_uniq_relabel, dim3(nblocks((n_threads + kRelabelUnroll - 1) / kRelabelUnroll)), dim3(kBlock), 0, s, dst, col_global, m, m_dev, n_dst, rank, src, col_local);
   return COOP_OK;
 }
 

@@ -731,6 +731,36 @@ def test_frontier_dedup_modes(P, tiny, medium, mode):
         P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
 
 
+@pytest.mark.parametrize("shape", ["ring", "star", "one_bucket"])
+def test_frontier_dedup_of_short_lists(P, shape):
+    """The dedup that lets every block pick its keys from the whole list: lists of one entry to both sides of a tile (8,192
+    entries) and of the length at which the partition takes over (262,144); a vertex that every list keeps, more often than
+    a wave can note; and seeds whose hashes all share a bucket, so that its table overflows and the call falls back."""
+    n = 300000
+    if shape == "star":      # every list is [7]
+        indices = torch.full((n,), 7, dtype=torch.int32)
+    else:                    # every list is [the next vertex but 6]
+        indices = ((torch.arange(n) + 7) % n).to(torch.int32)
+    g = G(P, torch.arange(n + 1, dtype=torch.int64), indices)
+    perm = np.random.default_rng(11).permutation(n).astype(np.int32)
+    if shape == "one_bucket":
+        hashes = (perm.astype(np.uint64) * np.uint64(0x9E3779B9)) & np.uint64(0xFFFFFFFF)
+        perm = perm[(hashes >> np.uint64(29)) == 5]
+        sizes = (1500, 4000)          # n_all = 8,000: eight buckets, and one of them gets all the seeds
+    else:
+        sizes = (1, 2, 3, 2047, 4095, 4096, 4097, 12000) + ((131071, 131072, 131073) if shape == "ring" else ())
+    for size in sizes:
+        seeds = perm[:size]
+        P.profile_reset()
+        P.profile_enable(True)
+        compare(P, g, seeds, (1, 1), R.NS, seed=size)
+        compare(P, g, seeds, (2,), R.LABOR0, it=1, seed=size)
+        P.profile_enable(False)
+        ran = P.profile_read_all()
+        assert ("unique_insert" in ran) == (shape == "one_bucket" and size == 4000), (size, ran.keys())
+        assert "unique_filter" in ran or size > 100000, (size, ran.keys())
+
+
 def test_repeated_neighbours_and_unsorted_lists(P):
     """A multigraph with unsorted lists (legal without COOP_SYMMETRIC): a neighbour that occurs several times in a list
     has the same variate each time, so NS must break the tie by list position (in the candidate ranking, in the
