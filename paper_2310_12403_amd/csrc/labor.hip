@@ -556,10 +556,12 @@ __device__ __forceinline__ void labor_scan_fast(const int32_t* __restrict__ g_in
       bool f[NF][4];
       bool any = false;
 #pragma unroll
-      for (int l = 0; l < NF; ++l) {
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t folded = fold16((uint32_t)buf[gq][e]);  // (shared by the layers)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          f[l][e] = ok[gq] & (variate<false, BLEND>(keys.K[l], keys.cw, keys.sw, (uint32_t)buf[gq][e], 0u, 0u) <= thr[l]);
+        for (int l = 0; l < NF; ++l) {
+          if constexpr (BLEND) f[l][e] = ok[gq] & (variate<false, true>(keys.K[l], keys.cw, keys.sw, (uint32_t)buf[gq][e], 0u, 0u) <= thr[l]);
+          else f[l][e] = ok[gq] & (keyed_from_head<false>(keys.K[l].Ka, folded, 0u) <= thr[l]);
           any |= f[l][e];
         }
       }
@@ -655,8 +657,8 @@ __device__ __forceinline__ void blend_second(BlendState& st, int l, uint32_t fir
   const float keep2 = __shfl(lb.keep2[l], (int)slot, kWave);
   bool keep = false, maybe = false;
   if (lane < n) {
-    const uint32_t u1 = keyed_uniform<false>(keys.K[l].Ka, (uint32_t)e.t, 0u);
-    const uint32_t u2 = keyed_uniform<false>(keys.K[l].Kb, (uint32_t)e.t, 0u);
+    const uint32_t folded = fold16((uint32_t)e.t);
+    const uint32_t u1 = keyed_from_head<false>(keys.K[l].Ka, folded, 0u), u2 = keyed_from_head<false>(keys.K[l].Kb, folded, 0u);
     e.list = lb.first + slot;
     e.layer = (uint32_t)l;
     const float est = __builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2));
@@ -738,6 +740,11 @@ __device__ __forceinline__ void labor_scan_blend(const int32_t* __restrict__ g_i
   const int32_t* __restrict__ p = g_indices + abeg;
   const uint32_t lane = (uint32_t)lane_id();
   const float cwf = (float)keys.cw, swf = (float)keys.sw;
+  // stage 1 looks at the uniforms without their last fold: the bounds are rounded up to whole upper halves, so that nothing is
+  // lost, and stage 2 evaluates the passers anew
+  uint32_t a1[NF], a2[NF], b2[NF];
+#pragma unroll
+  for (int l = 0; l < NF; ++l) { a1[l] = pthr[l].a1 | 0xFFFFu; a2[l] = pthr[l].a2 | 0xFFFFu; b2[l] = pthr[l].b2 | 0xFFFFu; }
   // the ragged ends (lanes 0..2: the entries in front of the first whole group; lanes 3..5: those behind the last one) are
   // requested now, so that a short list waits for memory once
   const uint32_t end_pos = lane < 3 ? head + lane : vec_end + (lane - 3);
@@ -762,13 +769,13 @@ __device__ __forceinline__ void labor_scan_blend(const int32_t* __restrict__ g_i
       bool pre[NF][4];
       bool any = false;
 #pragma unroll
-      for (int l = 0; l < NF; ++l) {
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t folded = fold16((uint32_t)buf[gq][e]);  // (shared by the layers and the two uniforms)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t u1 = keyed_uniform<false>(keys.K[l].Ka, (uint32_t)buf[gq][e], 0u);
-          const uint32_t u2 = keyed_uniform<false>(keys.K[l].Kb, (uint32_t)buf[gq][e], 0u);
+        for (int l = 0; l < NF; ++l) {
+          const uint32_t u1 = keyed_rough<false>(keys.K[l].Ka, folded, 0u), u2 = keyed_rough<false>(keys.K[l].Kb, folded, 0u);
           const uint32_t lo = u1 < u2 ? u1 : u2, hi = u1 < u2 ? u2 : u1;
-          pre[l][e] = ok[gq] & ((lo <= pthr[l].a1) | ((lo <= pthr[l].a2) & (hi <= pthr[l].b2)));
+          pre[l][e] = ok[gq] & ((lo <= a1[l]) | ((lo <= a2[l]) & (hi <= b2[l])));
           any |= pre[l][e];
         }
       }
@@ -783,10 +790,10 @@ __device__ __forceinline__ void labor_scan_blend(const int32_t* __restrict__ g_i
   }
 #pragma unroll
   for (int l = 0; l < NF; ++l) {  // the ragged ends
-    const uint32_t a = keyed_uniform<false>(keys.K[l].Ka, (uint32_t)end_t, 0u);
-    const uint32_t b = keyed_uniform<false>(keys.K[l].Kb, (uint32_t)end_t, 0u);
+    const uint32_t folded = fold16((uint32_t)end_t);
+    const uint32_t a = keyed_rough<false>(keys.K[l].Ka, folded, 0u), b = keyed_rough<false>(keys.K[l].Kb, folded, 0u);
     const uint32_t lo = a < b ? a : b, hi = a < b ? b : a;
-    blend_first<NF>(st, l, end_valid && (lo <= pthr[l].a1 || (lo <= pthr[l].a2 && hi <= pthr[l].b2)), end_t, end_pos - head + j0, slot, lb, keys,
+    blend_first<NF>(st, l, end_valid && (lo <= a1[l] || (lo <= a2[l] && hi <= b2[l])), end_t, end_pos - head + j0, slot, lb, keys,
                     cwf, swf, stage_cap, out, ctl);
   }
 }

@@ -90,7 +90,7 @@ constexpr int kNsQueueCap = 2 * kWave;
 struct NsQueue {
   int32_t t[kNsQueueCap];
   uint32_t j[kNsQueueCap];
-  uint32_t u1[kNsQueueCap];
+  uint32_t u1[kNsQueueCap];  // (keyed_rough)
   uint32_t u2[kNsQueueCap];
 };
 
@@ -132,7 +132,7 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
     if (lane < n) {
       t = q->t[lane];
       j = q->j[lane];
-      const uint32_t u1 = q->u1[lane], u2 = q->u2[lane];
+      const uint32_t u1 = keyed_exact<true>(vp.K.Ka, q->u1[lane]), u2 = keyed_exact<true>(vp.K.Kb, q->u2[lane]);
       if (__builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2)) <= bt.lim2) {
         if constexpr (STAGED) {
           in = true;
@@ -165,15 +165,18 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
       __builtin_amdgcn_wave_barrier();
     }
   };
-  // first look at one entry: its variate (c = 0) or the integer bounds on its two uniforms (c > 0)
+  // first look at one entry: its variate (c = 0) or the integer bounds on its two uniforms (c > 0; without their last fold,
+  // and the bounds rounded up to whole upper halves, so that nothing is lost: keyed_exact finishes the passers')
   auto first_look = [&](bool valid, int32_t t, uint32_t& r, uint32_t& u2) -> bool {
-    r = keyed_uniform<true>(vp.K.Ka, (uint32_t)t, sigma_a);
+    const uint32_t folded = fold16((uint32_t)t);
     if constexpr (!BLEND) {
+      r = keyed_from_head<true>(vp.K.Ka, folded, sigma_a);
       return valid & (r <= bound);
     } else {
-      u2 = keyed_uniform<true>(vp.K.Kb, (uint32_t)t, sigma_b);
+      r = keyed_rough<true>(vp.K.Ka, folded, sigma_a);
+      u2 = keyed_rough<true>(vp.K.Kb, folded, sigma_b);
       const uint32_t lo = r < u2 ? r : u2, hi = r < u2 ? u2 : r;
-      return valid & ((lo <= bt.a1) | ((lo <= bt.a2) & (hi <= bt.b2)));
+      return valid & ((lo <= (bt.a1 | 0xFFFFu)) | ((lo <= (bt.a2 | 0xFFFFu)) & (hi <= (bt.b2 | 0xFFFFu))));
     }
   };
   auto take = [&](bool flag, int32_t t, uint32_t j, uint32_t r, uint32_t u2) {

@@ -24,7 +24,7 @@ struct RwParams {
 };
 
 __device__ __forceinline__ uint32_t rw_draw(const uint32_t (&K)[4], uint32_t sigma, uint32_t c) {
-  return mix32(mix32(c ^ K[0]) ^ K[1] ^ sigma) ^ K[3];  // sigma = mix32(s ^ K[2])
+  return keyed_uniform<true>(K, c, sigma);  // mix32(mix32(c ^ K0) ^ K1 ^ sigma) ^ K3, sigma = mix32(s ^ K2)
 }
 
 // E = table slots per lane (table of 64 E slots, at most 3/4 full)

@@ -37,6 +37,16 @@ __host__ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
   return x;
 }
 
+// The same in parts: mix32(x) = fold16(mix_body(fold16(x))).  fold16 is linear over xor, and twice fold16 is nothing, so a key
+// can be folded ahead of time and the fold at the end of one mixer cancels the one at the start of the next.
+__host__ __device__ __forceinline__ uint32_t fold16(uint32_t x) { return x ^ (x >> 16); }
+__host__ __device__ __forceinline__ uint32_t mix_body(uint32_t x) {
+  x *= 0x7FEB352Du;
+  x ^= x >> 15;
+  x *= 0x846CA68Bu;
+  return x;
+}
+
 // the mixer is a bijection of the 32-bit integers: its inverse (0x43021123, 0x1D69E2A5: the multipliers' inverses mod 2^32)
 __host__ __device__ __forceinline__ uint32_t unmix32(uint32_t x) {
   x ^= x >> 16;
@@ -270,11 +280,37 @@ __device__ __forceinline__ uint32_t kit_phi_to_u32(double x) {
 // sigma = mix(s ^ K2) of the destination, wave-uniform; NS only
 __device__ __forceinline__ uint32_t ns_sigma(const uint32_t K[4], uint32_t s) { return mix32(s ^ K[2]); }
 
+// U = mix32(t ^ K0) ^ K1, for NS mix32(that ^ sigma) ^ K3.  Evaluated from head = fold16(t), which the layers and the two
+// uniforms of a blend share; the folds between the two mixers of NS cancel.
+// keyed_rough leaves the last fold out: its upper 16 bits are those of U.
+// (The compiler must not see that the folded key is one: it would turn fold16(t) ^ fold16(K0) back into three instructions per
+// entry.  keyed_rough and keyed_from_head are for key words that are the same for every lane: the value lives in a scalar
+// register.)
+__device__ __forceinline__ uint32_t folded_key(uint32_t K0) {
+  uint32_t k = fold16(K0);
+  asm("" : "+s"(k));
+  return k;
+}
+template <bool NS>
+__device__ __forceinline__ uint32_t keyed_rough(const uint32_t K[4], uint32_t head, uint32_t sigma) {
+  const uint32_t m = mix_body(head ^ folded_key(K[0]));
+  if constexpr (!NS) return m ^ K[1];
+  else return mix_body(m ^ fold16(K[1] ^ sigma)) ^ K[3];
+}
+// U from keyed_rough's value
+template <bool NS>
+__device__ __forceinline__ uint32_t keyed_exact(const uint32_t K[4], uint32_t rough) { return rough ^ ((rough ^ (NS ? K[3] : K[1])) >> 16); }
+template <bool NS>
+__device__ __forceinline__ uint32_t keyed_from_head(const uint32_t K[4], uint32_t head, uint32_t sigma) {
+  const uint32_t m = mix_body(head ^ folded_key(K[0]));
+  if constexpr (!NS) return fold16(m) ^ K[1];
+  else return fold16(mix_body(m ^ fold16(K[1] ^ sigma))) ^ K[3];
+}
 template <bool NS>
 __device__ __forceinline__ uint32_t keyed_uniform(const uint32_t K[4], uint32_t t, uint32_t sigma) {
-  const uint32_t a = mix32(t ^ K[0]) ^ K[1];
-  if constexpr (!NS) return a;
-  else return mix32(a ^ sigma) ^ K[3];
+  const uint32_t m = mix_body(fold16(t ^ K[0]));
+  if constexpr (!NS) return fold16(m) ^ K[1];
+  else return fold16(mix_body(m ^ fold16(K[1] ^ sigma))) ^ K[3];
 }
 
 // R for source vertex t; for NS, sigma_a / sigma_b are ns_sigma(Ka, s) / ns_sigma(Kb, s) of the destination s
