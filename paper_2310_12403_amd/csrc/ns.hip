@@ -28,51 +28,84 @@ struct NsRecord {
 };
 
 // (long_min > 0: the destinations whose list is longer than long_min entries, and than k, are also queued in long_list,
-// in no particular order, *n_long counting them: the traversal kernels give those to their first waves, see there)
-__global__ __launch_bounds__(kBlock) void k_ns_count(const int64_t* __restrict__ g_indptr, int64_t n_vertices,
-                                                     const int32_t* __restrict__ dst, int64_t n_dst, uint32_t k, uint32_t target,
-                                                     int32_t* __restrict__ cnt, NsRecord* __restrict__ rec,
-                                                     NsBlendThr* __restrict__ bthr /* null when c = 0 */, double cw, double sw, Ctl* ctl,
-                                                     uint32_t long_min, uint32_t* __restrict__ long_list, uint32_t* __restrict__ n_long) {
-  __shared__ uint32_t wave_long[kWavesPerBlock];
+// in no particular order, *n_long counting them: the traversal kernels give those to their first waves, see there.  A
+// block reserves its places with one returning atomic, and those on one address are taken one after the other, some 20 ns
+// each: 675 thousand destinations took 40 us in blocks of 256 and take 28 in blocks of 1,024 threads with two each.  Below
+// kNsCountWideFrom destinations, and with c > 0, where every destination has its thresholds evaluated in fp64, the small
+// blocks are the quicker ones: 10 us against 12 for 110 thousand, 5 against 8 for 16 thousand, and half the time with c > 0.)
+constexpr int64_t kNsCountWideFrom = 262144;
+template <int kNsCountBlock, int kNsCountEach>
+__global__ __launch_bounds__(kNsCountBlock) void k_ns_count(const int64_t* __restrict__ g_indptr, int64_t n_vertices,
+                                                            const int32_t* __restrict__ dst, int64_t n_dst, uint32_t k, uint32_t target,
+                                                            int32_t* __restrict__ cnt, NsRecord* __restrict__ rec,
+                                                            NsBlendThr* __restrict__ bthr /* null when c = 0 */, double cw, double sw, Ctl* ctl,
+                                                            uint32_t long_min, uint32_t* __restrict__ long_list, uint32_t* __restrict__ n_long) {
+  __shared__ uint32_t wave_long[kNsCountBlock / kWave];
   __shared__ uint32_t block_base;
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  bool is_long = false;
-  if (i < n_dst) {
-    const int32_t s = dst[i];
-    if ((uint64_t)(uint32_t)s >= (uint64_t)n_vertices) {
+  const int64_t i0 = (int64_t)blockIdx.x * (kNsCountBlock * kNsCountEach) + threadIdx.x;
+  bool is_long[kNsCountEach];
+  int32_t s[kNsCountEach];
+  int64_t beg[kNsCountEach], end[kNsCountEach];
+#pragma unroll
+  for (int u = 0; u < kNsCountEach; ++u) {
+    const int64_t i = i0 + u * kNsCountBlock;
+    s[u] = i < n_dst ? dst[i] : -1;
+  }
+#pragma unroll
+  for (int u = 0; u < kNsCountEach; ++u) {
+    beg[u] = end[u] = 0;
+    if ((uint64_t)(uint32_t)s[u] < (uint64_t)n_vertices) {
+      beg[u] = g_indptr[s[u]];
+      end[u] = g_indptr[s[u] + 1];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kNsCountEach; ++u) {
+    const int64_t i = i0 + u * kNsCountBlock;
+    is_long[u] = false;
+    if (i >= n_dst) continue;
+    if ((uint64_t)(uint32_t)s[u] >= (uint64_t)n_vertices) {
       atomicOr(&ctl->err_range, 1);
       cnt[i] = 0;
       rec[i] = NsRecord{0, 0u, 0, 0u, 0u};
       if (bthr) bthr[i] = NsBlendThr{0u, 0u, 0u, 0.0f};
-    } else {
-      const int64_t beg = g_indptr[s];
-      const int64_t d = g_indptr[s + 1] - beg;
-      cnt[i] = (int32_t)(d < (int64_t)k ? d : (int64_t)k);
-      // bound such that E[#candidates] = target: R <= bound with probability (bound + 1) / 2^32 (one 64-bit division per
-      // list, here where every lane has a list of its own)
-      uint64_t bound = d > 0 ? ((uint64_t)target << 32) / (uint64_t)d : 0xFFFFFFFFull;
-      if (bound > 0xFFFFFFFFull) bound = 0xFFFFFFFFull;  // d <= target: every neighbour is a candidate
-      rec[i] = NsRecord{beg, (uint32_t)d, s, (uint32_t)bound, 0u};
-      if (bthr) bthr[i] = d > (int64_t)k ? ns_blend_thresholds((uint32_t)bound, cw, sw) : NsBlendThr{0u, 0u, 0u, 0.0f};
-      is_long = long_min != 0 && d > (int64_t)long_min && d > (int64_t)k;
+      continue;
     }
+    const int64_t d = end[u] - beg[u];
+    cnt[i] = (int32_t)(d < (int64_t)k ? d : (int64_t)k);
+    // bound such that E[#candidates] = target: R <= bound with probability (bound + 1) / 2^32 (one 64-bit division per
+    // list, here where every lane has a list of its own)
+    uint64_t bound = d > 0 ? ((uint64_t)target << 32) / (uint64_t)d : 0xFFFFFFFFull;
+    if (bound > 0xFFFFFFFFull) bound = 0xFFFFFFFFull;  // d <= target: every neighbour is a candidate
+    rec[i] = NsRecord{beg[u], (uint32_t)d, s[u], (uint32_t)bound, 0u};
+    if (bthr) bthr[i] = d > (int64_t)k ? ns_blend_thresholds((uint32_t)bound, cw, sw) : NsBlendThr{0u, 0u, 0u, 0.0f};
+    is_long[u] = long_min != 0 && d > (int64_t)long_min && d > (int64_t)k;
   }
   if (long_min == 0) return;  // (the same for every thread)
-  const uint64_t m = ballot64(is_long);
+  uint64_t mask[kNsCountEach];
+  uint32_t mine = 0;
+#pragma unroll
+  for (int u = 0; u < kNsCountEach; ++u) {
+    mask[u] = ballot64(is_long[u]);
+    mine += (uint32_t)__popcll(mask[u]);
+  }
   const int wib = wave_in_block();
-  if (lane_id() == 0) wave_long[wib] = (uint32_t)__popcll(m);
+  if (lane_id() == 0) wave_long[wib] = mine;
   __syncthreads();
   if (threadIdx.x == 0) {  // one reservation per block
     uint32_t total = 0;
-    for (int w = 0; w < kWavesPerBlock; ++w) total += wave_long[w];
+    for (int w = 0; w < kNsCountBlock / kWave; ++w) total += wave_long[w];
     block_base = total ? atomicAdd(n_long, total) : 0u;
   }
   __syncthreads();
-  if (is_long) {
-    uint32_t at = block_base + lanes_below(m);
-    for (int w = 0; w < wib; ++w) at += wave_long[w];
-    if ((int64_t)at < n_dst) long_list[at] = (uint32_t)i;  // (always: every destination is queued at most once; the queue has n_dst places)
+  if (mine == 0) return;  // (the same for the whole wave)
+  uint32_t at = block_base;
+  for (int w = 0; w < wib; ++w) at += wave_long[w];
+#pragma unroll
+  for (int u = 0; u < kNsCountEach; ++u) {
+    const uint32_t to = at + lanes_below(mask[u]);
+    if (is_long[u] && (int64_t)to < n_dst) long_list[to] = (uint32_t)(i0 + u * kNsCountBlock);  // (always: a destination is queued at most once)
+    at += (uint32_t)__popcll(mask[u]);
   }
 }
 
@@ -81,6 +114,17 @@ constexpr int64_t kNsQueueFrom = 32768;  // destinations from which the long lis
 constexpr int kNsLongDefault = 2048;
 int g_ns_long_min = kNsLongDefault;      // COOP_TUNE_NS_LONG_LIST: lists longer than this are queued (0 = none)
 constexpr uint32_t kNsRedo = 0xFFFFFFFFu;  // candidate count of a destination that the two-kernel path leaves to k_ns_fill
+// The two-kernel path's queue of such destinations (about one in 10^4; a kernel over all destinations that looked for them
+// took 14 us per layer).
+struct NsRedo {
+  uint32_t* list;
+  uint32_t* n;
+  __device__ __forceinline__ void add(int64_t w, uint32_t* __restrict__ n_cand) const {  // one lane
+    n_cand[w] = kNsRedo;
+    list[atomicAdd(n, 1u)] = (uint32_t)w;  // (a destination is queued once at most: by k_ns_collect, or else by k_ns_select)
+  }
+};
+constexpr int64_t kNsRedoWaves = 1024;
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 constexpr int kNsGroups = 4;  // 16-byte groups per lane and step of the fast traversal
@@ -315,6 +359,26 @@ __device__ __forceinline__ void ns_rank_write(uint32_t n_c, uint32_t k, const ui
   }
 }
 
+// The list of a traversal kernel's wave: the first long_blocks blocks take the queued long lists (the queue's length is read
+// from device memory), the others the destinations in order.  One list per wave and one wave per block: waves that stride
+// over many lists are not evened out by the dispatcher (fill 497 -> 531 us for 675 thousand lists).  -1: nothing to do.
+__device__ __forceinline__ int64_t ns_list_of(int64_t n_dst, int waves_per_block, int wib, const uint32_t* __restrict__ long_list,
+                                              const uint32_t* __restrict__ n_long, int long_blocks, bool* queued) {
+  *queued = (int)blockIdx.x < long_blocks;
+  int64_t w;
+  if (*queued) {  // the q-th queued long list
+    const int64_t q = (int64_t)blockIdx.x * waves_per_block + wib;
+    int64_t n_queued = (int64_t)*n_long;
+    if (n_queued > n_dst) n_queued = n_dst;  // (holds by construction; keeps every access inside the queue regardless)
+    if (q >= n_queued) return -1;
+    // (the same in every lane; said so, or everything derived from it would be kept per lane)
+    w = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)long_list[q]);
+  } else {
+    w = (int64_t)((int)blockIdx.x - long_blocks) * waves_per_block + wib;
+  }
+  return w < n_dst ? w : -1;
+}
+
 // Selection of the k smallest (R, j) among d > k neighbours, one wave per destination:
 //   1. one pass over the list collects, in LDS, the candidates with R <= bound, where bound is chosen so that about
 //      `target` of them are expected (target > k, target < cap);
@@ -391,7 +455,6 @@ __global__ __launch_bounds__(kBlock) void k_ns_fill(const int32_t* __restrict__ 
                                                     uint32_t cap, int waves_per_block, VariateParams vp,
                                                     const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
                                                     int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl,
-                                                    const uint32_t* __restrict__ only /* when not null: only lists marked kNsRedo */,
                                                     uint32_t long_min, const uint32_t* __restrict__ long_list,
                                                     const uint32_t* __restrict__ n_long, int long_blocks) {
   extern __shared__ __align__(16) uint32_t lds_words[];  // per wave: cap 64-bit keys, cap keep flags, cap vertex ids
@@ -399,22 +462,22 @@ __global__ __launch_bounds__(kBlock) void k_ns_fill(const int32_t* __restrict__ 
   const int wib = uniform_wave_in_block();
   if (wib >= waves_per_block) return;
   NsQueue* queue = &queues[BLEND ? wib : 0];
-  const bool queue_wave = (int)blockIdx.x < long_blocks;
-  int64_t w;
-  if (queue_wave) {  // the q-th queued long list
-    const int64_t q = (int64_t)blockIdx.x * waves_per_block + wib;
-    int64_t n_queued = (int64_t)*n_long;
-    if (n_queued > n_dst) n_queued = n_dst;  // (holds by construction; keeps every access inside the queue regardless)
-    if (q >= n_queued) return;
-    // (the same in every lane; said so, or everything derived from it would be kept per lane)
-    w = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)long_list[q]);
+  if constexpr (BLEND) {  // the destinations queued in long_list, by all waves of the grid
+    int64_t n = (int64_t)*n_long;
+    if (n > n_dst) n = n_dst;
+    for (int64_t q = (int64_t)blockIdx.x * waves_per_block + wib; q < n; q += (int64_t)gridDim.x * waves_per_block) {
+      const int64_t w = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)long_list[q]);
+      if (w < n_dst)
+        ns_fill_one<BLEND, VEC4>(w, wib, lds_words, queue, g_indices, rec, bthr, k, cap, vp, eptr, col_global, eid, edge_limit, ctl, 0xFFFFFFFFu);
+      __builtin_amdgcn_wave_barrier();
+    }
   } else {
-    w = (int64_t)((int)blockIdx.x - long_blocks) * waves_per_block + wib;
-    if (only != nullptr && w < n_dst && only[w] != kNsRedo) return;
+    bool queued;
+    const int64_t w = ns_list_of(n_dst, waves_per_block, wib, long_list, n_long, long_blocks, &queued);
+    if (w < 0) return;
+    ns_fill_one<BLEND, VEC4>(w, wib, lds_words, queue, g_indices, rec, bthr, k, cap, vp, eptr, col_global, eid, edge_limit, ctl,
+                             !queued && long_min != 0 ? long_min : 0xFFFFFFFFu);
   }
-  if (w >= n_dst) return;
-  ns_fill_one<BLEND, VEC4>(w, wib, lds_words, queue, g_indices, rec, bthr, k, cap, vp, eptr, col_global, eid, edge_limit, ctl,
-                           !queue_wave && long_min != 0 ? long_min : 0xFFFFFFFFu);
 }
 
 // ---- c > 0 in two kernels ----------------------------------------------------------------------------------------
@@ -431,28 +494,19 @@ __global__ __launch_bounds__(kBlock) void k_ns_collect(const int32_t* __restrict
                                                        const NsBlendThr* __restrict__ bthr, int64_t n_dst, uint32_t k, uint32_t cap,
                                                        int waves_per_block, VariateParams vp, const int64_t* __restrict__ eptr,
                                                        int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit,
-                                                       Ctl* ctl, NsCand* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand,
+                                                       NsCand* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand, NsRedo redo,
                                                        uint32_t long_min, const uint32_t* __restrict__ long_list,
                                                        const uint32_t* __restrict__ n_long, int long_blocks) {
   extern __shared__ __align__(16) uint32_t lds_words[];
   NsQueue* queues = reinterpret_cast<NsQueue*>(lds_words + (size_t)waves_per_block * cap * 4);  // (behind the candidates)
   const int wib = uniform_wave_in_block();
   if (wib >= waves_per_block) return;
-  const bool queue_wave = (int)blockIdx.x < long_blocks;  // the queued long lists first, as in k_ns_fill
-  int64_t w;
-  if (queue_wave) {
-    const int64_t q = (int64_t)blockIdx.x * waves_per_block + wib;
-    int64_t n_queued = (int64_t)*n_long;
-    if (n_queued > n_dst) n_queued = n_dst;
-    if (q >= n_queued) return;
-    w = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)long_list[q]);
-  } else {
-    w = (int64_t)((int)blockIdx.x - long_blocks) * waves_per_block + wib;
-  }
-  if (w >= n_dst) return;
   const uint32_t lane = (uint32_t)lane_id();
+  bool queued;
+  const int64_t w = ns_list_of(n_dst, waves_per_block, wib, long_list, n_long, long_blocks, &queued);
+  if (w < 0) return;
   const NsRecord g = rec[w];
-  if (!queue_wave && long_min != 0 && g.d > long_min && g.d > k) return;  // queued: one of the first waves takes it
+  if (!queued && long_min != 0 && g.d > long_min && g.d > k) return;  // queued: one of the first waves takes it
   if (lane == 0) n_cand[w] = 0;  // nothing left to do for this destination, unless said otherwise below
   const int64_t o = eptr[w];
   if (eptr[w + 1] > edge_limit) return;
@@ -473,7 +527,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_collect(const int32_t* __restrict
   __builtin_amdgcn_wave_barrier();
   __threadfence_block();
   if (n_c < k || n_c > row_cap || n_c > cap) {  // (too few even before the exact test, or no room)
-    if (lane == 0) n_cand[w] = kNsRedo;
+    if (lane == 0) redo.add(w, n_cand);
     return;
   }
   NsCand* row = rows + (size_t)w * row_cap;
@@ -485,15 +539,15 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
                                                       int waves_per_block, VariateParams vp, const int64_t* __restrict__ eptr,
                                                       int32_t* __restrict__ col_global, int64_t* __restrict__ eid,
                                                       const NsCand* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand,
-                                                      const NsBlendThr* __restrict__ bthr) {
+                                                      NsRedo redo, const NsBlendThr* __restrict__ bthr) {
   extern __shared__ __align__(16) uint32_t lds_words[];
   const int wib = uniform_wave_in_block();
   if (wib >= waves_per_block) return;
+  const uint32_t lane = (uint32_t)lane_id();
   const int64_t w = (int64_t)blockIdx.x * waves_per_block + wib;
   if (w >= n_dst) return;
   const uint32_t n = n_cand[w];
   if (n == 0 || n == kNsRedo) return;  // done by the collecting kernel, or left to k_ns_fill
-  const uint32_t lane = (uint32_t)lane_id();
   const NsRecord g = rec[w];
   uint64_t* cand_key = reinterpret_cast<uint64_t*>(lds_words + (size_t)wib * cap * 4);
   uint32_t* cand_k = lds_words + (size_t)wib * cap * 4 + 2 * cap;
@@ -528,7 +582,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
     // e_k must lie safely below what the traversal's filter let through, or a neighbour that it dropped could belong
     // to the k smallest
     if (!(e_k >= -5.0f && e_k <= 5.0f) || !(e_k + m <= bthr[w].lim2 - m)) {
-      if (lane == 0) n_cand[w] = kNsRedo;
+      if (lane == 0) redo.add(w, n_cand);
       return;
     }
     const bool in = has && est < e_k - m;
@@ -583,7 +637,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
     n_c += (uint32_t)__popcll(mask);
   }
   if (n_c < k) {
-    if (lane == 0) n_cand[w] = kNsRedo;
+    if (lane == 0) redo.add(w, n_cand);
     return;
   }
   ns_rank_write(n_c, k, cand_key, cand_k, cand_t, eptr[w], g.beg, col_global, eid);
@@ -692,9 +746,12 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
   uint32_t* long_list = queue_long ? alloc.get<uint32_t>(n_dst, COOP_TAG_SCRATCH) : nullptr;
   uint32_t* n_long = cx.d_piece_count + l;  // (zero at the start of the call and whenever the layer is redone)
   if (alloc.failed) return COOP_E_NOMEM;
-  if (n_dst > 0)
-    COOP_LAUNCH(K_NS_COUNT, k_ns_count, dim3(blocks_for(n_dst, kBlock)), dim3(kBlock), 0, s, cx.g->indptr, cx.g->n_vertices, dst, n_dst,
-                k, target, cnt, rec, bthr, cx.cw, cx.sw, cx.d_ctl, long_min, long_list, n_long);
+#define COOP_NS_COUNT(BLOCK, EACH)                                                                                                             \
+  COOP_LAUNCH(K_NS_COUNT, (k_ns_count<BLOCK, EACH>), dim3(blocks_for(n_dst, BLOCK * EACH)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices, \
+              dst, n_dst, k, target, cnt, rec, bthr, cx.cw, cx.sw, cx.d_ctl, long_min, long_list, n_long)
+  if (n_dst >= kNsCountWideFrom && !cx.blend) COOP_NS_COUNT(1024, 2);
+  else if (n_dst > 0) COOP_NS_COUNT(kBlock, 1);
+#undef COOP_NS_COUNT
   if (defer) {
     scan_i32_to_i64(cnt, n_dst, blk->indptr, &cx.d_ctl->total_edges, scan_tmp, s, nullptr);  // the count stays on the device
   } else {
@@ -716,7 +773,7 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
     const int wpb = 1;
     const size_t shmem = (size_t)wpb * cap * 16 + (cx.blend ? (size_t)wpb * sizeof(NsQueue) : 0);
     const dim3 grid(blocks_for(n_dst, wpb));
-#define COOP_NS_ARGS cx.g->indices, rec, bthr, n_dst, k, cap, wpb, vp, blk->indptr, blk->col_global, blk->eid, m, cx.d_ctl
+#define COOP_NS_ARGS cx.g->indices, rec, bthr, n_dst, k, cap, wpb, vp, blk->indptr, blk->col_global, blk->eid, m
     // the queue's waves, one per queued list: as many as there can be lists that long, by the degree census of the
     // registration and by the number of edges (the unused ones end at once)
     int64_t most_long = cx.g->n_edges / (int64_t)(long_min ? long_min : 1) + 1;
@@ -730,21 +787,23 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
       while (row_cap < 2 * target && row_cap < cap) row_cap <<= 1;
       NsCand* rows = alloc.get<NsCand>(n_dst * (int64_t)row_cap, COOP_TAG_SCRATCH);
       uint32_t* n_cand = alloc.get<uint32_t>(n_dst, COOP_TAG_SCRATCH);
+      // (the queue's counter: zero at the start of the call and whenever the layer is redone)
+      const NsRedo redo{alloc.get<uint32_t>(n_dst, COOP_TAG_SCRATCH), cx.d_piece_count + cx.L + l};
       if (alloc.failed) return COOP_E_NOMEM;
-      if (cx.vec4) COOP_LAUNCH(K_NS_FILL, k_ns_collect<true>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, rows, row_cap, n_cand, long_min,
-                               (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
-      else COOP_LAUNCH(K_NS_FILL, k_ns_collect<false>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, rows, row_cap, n_cand, long_min,
-                       (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
-      COOP_LAUNCH(K_NS_SELECT, k_ns_select, grid, dim3(wpb * kWave), shmem, s, rec, n_dst, k, cap, wpb, vp, blk->indptr, blk->col_global, blk->eid,
-                  (const NsCand*)rows, row_cap, n_cand, (const NsBlendThr*)bthr);
-      if (cx.vec4) COOP_LAUNCH(K_NS_FILL, (k_ns_fill<true, true>), grid, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, (const uint32_t*)n_cand, 0u,
-                               (const uint32_t*)nullptr, (const uint32_t*)nullptr, 0);
-      else COOP_LAUNCH(K_NS_FILL, (k_ns_fill<true, false>), grid, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, (const uint32_t*)n_cand, 0u,
-                       (const uint32_t*)nullptr, (const uint32_t*)nullptr, 0);
+      const dim3 grid_redo((unsigned)(n_dst < kNsRedoWaves ? n_dst : kNsRedoWaves));
+#define COOP_NS_BLEND(VEC4)                                                                                                                    \
+  COOP_LAUNCH(K_NS_FILL, k_ns_collect<VEC4>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, rows, row_cap, n_cand, redo, long_min,          \
+              (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);                                                               \
+  COOP_LAUNCH(K_NS_SELECT, k_ns_select, grid, dim3(wpb * kWave), shmem, s, rec, n_dst, k, cap, wpb, vp, blk->indptr, blk->col_global, blk->eid, \
+              (const NsCand*)rows, row_cap, n_cand, redo, (const NsBlendThr*)bthr);                                                            \
+  COOP_LAUNCH(K_NS_FILL, (k_ns_fill<true, VEC4>), grid_redo, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, 0u,                           \
+              (const uint32_t*)redo.list, (const uint32_t*)redo.n, (int)grid_redo.x)
+      if (cx.vec4) { COOP_NS_BLEND(true); } else { COOP_NS_BLEND(false); }
+#undef COOP_NS_BLEND
     } else {
-      if (cx.vec4) COOP_LAUNCH(K_NS_FILL, (k_ns_fill<false, true>), grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, (const uint32_t*)nullptr, long_min,
+      if (cx.vec4) COOP_LAUNCH(K_NS_FILL, (k_ns_fill<false, true>), grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
                                (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
-      else COOP_LAUNCH(K_NS_FILL, (k_ns_fill<false, false>), grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, (const uint32_t*)nullptr, long_min,
+      else COOP_LAUNCH(K_NS_FILL, (k_ns_fill<false, false>), grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
                        (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
     }
 #undef COOP_NS_ARGS

@@ -16,14 +16,14 @@ constexpr uint32_t kRwEmpty = 0xFFFFFFFFu;
 constexpr int kRwMaxSteps = 1024;  // largest walk_length * n_walks that the tally in LDS serves (beyond it: k_rw_walk_wide)
 
 struct RwParams {
-  uint32_t K[4];         // key words of (seed, sampler RW, layer, iteration)
+  uint32_t K[5];         // key words of (seed, sampler RW, layer, iteration)
   int32_t walk_length;   // o
   int32_t n_walks;       // a
   uint64_t restart_thr;  // restart iff draw < floor(p 2^32)
   uint32_t k_eff;        // min(fanout, o * a): slots of a staged row
 };
 
-__device__ __forceinline__ uint32_t rw_draw(const uint32_t (&K)[4], uint32_t sigma, uint32_t c) {
+__device__ __forceinline__ uint32_t rw_draw(const uint32_t (&K)[5], uint32_t sigma, uint32_t c) {
   return keyed_uniform<true>(K, c, sigma);  // mix32(mix32(c ^ K0) ^ K1 ^ sigma) ^ K3, sigma = mix32(s ^ K2)
 }
 

@@ -19,8 +19,8 @@
 namespace coop {
 
 struct LayerKeys {
-  uint32_t Ka[4];  // key words of group g
-  uint32_t Kb[4];  // key words of group g + 1 (blended path only)
+  uint32_t Ka[5];  // key words of group g, then the first one folded (fold16)
+  uint32_t Kb[5];  // those of group g + 1 (blended path only)
 };
 
 struct VariateParams {
@@ -75,10 +75,11 @@ inline void philox4x32_10(const uint32_t ctr[4], const uint32_t key[2], uint32_t
   out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
-inline void layer_keys(uint64_t seed, int sampler, int layer, uint64_t g, uint32_t K[4]) {
+inline void layer_keys(uint64_t seed, int sampler, int layer, uint64_t g, uint32_t K[5]) {
   const uint32_t ctr[4] = {(uint32_t)g, (uint32_t)(g >> 32), (uint32_t)layer | ((uint32_t)sampler << 8), 0x434F4F50u};
   const uint32_t key[2] = {(uint32_t)seed, (uint32_t)(seed >> 32)};
   philox4x32_10(ctr, key, K);
+  K[4] = fold16(K[0]);
 }
 
 // ---- reproducible binary64 kit ------------------------------------------------------------------------------
@@ -278,36 +279,30 @@ __device__ __forceinline__ uint32_t kit_phi_to_u32(double x) {
 }
 
 // sigma = mix(s ^ K2) of the destination, wave-uniform; NS only
-__device__ __forceinline__ uint32_t ns_sigma(const uint32_t K[4], uint32_t s) { return mix32(s ^ K[2]); }
+__device__ __forceinline__ uint32_t ns_sigma(const uint32_t K[5], uint32_t s) { return mix32(s ^ K[2]); }
 
 // U = mix32(t ^ K0) ^ K1, for NS mix32(that ^ sigma) ^ K3.  Evaluated from head = fold16(t), which the layers and the two
 // uniforms of a blend share; the folds between the two mixers of NS cancel.
 // keyed_rough leaves the last fold out: its upper 16 bits are those of U.
-// (The compiler must not see that the folded key is one: it would turn fold16(t) ^ fold16(K0) back into three instructions per
-// entry.  keyed_rough and keyed_from_head are for key words that are the same for every lane: the value lives in a scalar
-// register.)
-__device__ __forceinline__ uint32_t folded_key(uint32_t K0) {
-  uint32_t k = fold16(K0);
-  asm("" : "+s"(k));
-  return k;
-}
+// (The folded key K[4] comes from the host: if the compiler sees it made, it turns fold16(t) ^ fold16(K0) back into three
+// instructions per entry.)
 template <bool NS>
-__device__ __forceinline__ uint32_t keyed_rough(const uint32_t K[4], uint32_t head, uint32_t sigma) {
-  const uint32_t m = mix_body(head ^ folded_key(K[0]));
+__device__ __forceinline__ uint32_t keyed_rough(const uint32_t K[5], uint32_t head, uint32_t sigma) {
+  const uint32_t m = mix_body(head ^ K[4]);
   if constexpr (!NS) return m ^ K[1];
   else return mix_body(m ^ fold16(K[1] ^ sigma)) ^ K[3];
 }
 // U from keyed_rough's value
 template <bool NS>
-__device__ __forceinline__ uint32_t keyed_exact(const uint32_t K[4], uint32_t rough) { return rough ^ ((rough ^ (NS ? K[3] : K[1])) >> 16); }
+__device__ __forceinline__ uint32_t keyed_exact(const uint32_t K[5], uint32_t rough) { return rough ^ ((rough ^ (NS ? K[3] : K[1])) >> 16); }
 template <bool NS>
-__device__ __forceinline__ uint32_t keyed_from_head(const uint32_t K[4], uint32_t head, uint32_t sigma) {
-  const uint32_t m = mix_body(head ^ folded_key(K[0]));
+__device__ __forceinline__ uint32_t keyed_from_head(const uint32_t K[5], uint32_t head, uint32_t sigma) {
+  const uint32_t m = mix_body(head ^ K[4]);
   if constexpr (!NS) return fold16(m) ^ K[1];
   else return fold16(mix_body(m ^ fold16(K[1] ^ sigma))) ^ K[3];
 }
 template <bool NS>
-__device__ __forceinline__ uint32_t keyed_uniform(const uint32_t K[4], uint32_t t, uint32_t sigma) {
+__device__ __forceinline__ uint32_t keyed_uniform(const uint32_t K[5], uint32_t t, uint32_t sigma) {
   const uint32_t m = mix_body(fold16(t ^ K[0]));
   if constexpr (!NS) return fold16(m) ^ K[1];
   else return fold16(mix_body(m ^ fold16(K[1] ^ sigma))) ^ K[3];

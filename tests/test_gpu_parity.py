@@ -761,6 +761,39 @@ def test_frontier_dedup_of_short_lists(P, shape):
         assert "unique_filter" in ran or size > 100000, (size, ran.keys())
 
 
+def test_ns_lists_left_to_the_one_kernel_path(P):
+    """c > 0: lists in which one neighbour occurs 200 times tie with themselves beyond what a row of candidates holds, so all
+    3,000 of them go through the queue of the one-kernel path, several per wave; next to lists that do not."""
+    n, big = 6000, 3000
+    rng = np.random.default_rng(5)
+    lists = [np.concatenate([np.full(200, (7 * v) % n), rng.integers(0, n, 20)]) if v < big else rng.integers(0, n, 30) for v in range(n)]
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64))
+    g = G(P, indptr, torch.from_numpy(np.concatenate(lists).astype(np.int32)))
+    for defer in (1, 0):
+        P.coop_tune(P.COOP_TUNE_DEFER_SIZES, defer)
+        try:
+            compare(P, g, rng.permutation(n)[:5000], (10, 5), R.NS, it=5, kappa=16, seed=3)
+        finally:
+            P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
+
+
+def test_ns_count_in_wide_blocks(P):
+    """From 262,144 destinations on the counting blocks take 2,048 each: a number of destinations that is no multiple of that,
+    with long lists (queued from 64 entries on) at both ends of blocks and with lists without entries."""
+    n = 300000
+    v = np.arange(n)
+    deg = np.where(v % 2048 < 2, 90, np.where(v % 1024 == 1023, 70, v % 3))
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]).astype(np.int64))
+    indices = torch.from_numpy(((np.arange(deg.sum()) * 7919) % n).astype(np.int32))
+    g = G(P, indptr, indices)
+    P.coop_tune(P.COOP_TUNE_NS_LONG_LIST, 64)
+    try:
+        for size in (262143, 262145, n):
+            compare(P, g, v[:size], (5,), R.NS, seed=size)
+    finally:
+        P.coop_tune(P.COOP_TUNE_NS_LONG_LIST, 2048)
+
+
 def test_repeated_neighbours_and_unsorted_lists(P):
     """A multigraph with unsorted lists (legal without COOP_SYMMETRIC): a neighbour that occurs several times in a list
     has the same variate each time, so NS must break the tie by list position (in the candidate ranking, in the
