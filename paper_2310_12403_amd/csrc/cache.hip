@@ -26,6 +26,8 @@ constexpr int kSelBits = 8;  // most bits per radix-select pass: 256 counters, s
 constexpr int kSelBins = 1 << kSelBits;  // global ones takes at most 256 atomics per block
 constexpr int kSelBlock = 1024;    // threads of a select block
 constexpr int kSelMaxBlocks = 256; // one per compute unit
+constexpr int kSelCopies = 8;      // copies of the global counters: atomics on one address are taken one after the other, some 20 ns each
+constexpr int kEvictBlock = 1024;  // threads of an eviction block
 constexpr int kRowUnroll = 4;  // rows per thread in flight (as in the plain gather)
 
 struct CacheCtl {
@@ -34,8 +36,21 @@ struct CacheCtl {
   int64_t n_hit;
   int32_t n_push;      // slots pushed on the free list by the current eviction
   int32_t err_range;
-  uint32_t sel_done;   // radix select: blocks of the current pass that have merged their counts (back to 0 after each pass)
-  uint32_t pad;
+};
+// what the select's blocks share: the counters of the current pass, and the blocks that have merged theirs (zero between passes)
+struct SelShared {
+  uint32_t hist[kSelCopies][kSelBins];
+  Tally done;
+};
+static_assert(sizeof(SelShared) % 8 == 0, "cleared in 8-byte words");
+
+// Landing pad in mapped pinned host memory.  The counts of a call reach the host when the kernel behind their scan stores
+// the control block and then a ticket, which the host polls: quicker than an asynchronous copy and a wait for it.
+struct CachePad {
+  CacheCtl ctl;          // counts of the call under way; must stay the first member
+  uint64_t ticket;       // written by the device after ctl
+  uint64_t next_ticket;  // host side only
+  uint64_t threshold;    // prefix of the last eviction (stored by the eviction, read one call late)
 };
 
 // ---- lookup ---------------------------------------------------------------------------------------------------
@@ -45,6 +60,7 @@ __global__ __launch_bounds__(kBlock) void k_cache_lookup(const int32_t* __restri
   // (several ids per thread do not make this faster: the scattered reads of slot_of, a table of one word per vertex of
   // the graph, are what it waits for, not their latency)
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i == 0) ctl->n_push = 0;  // (for the eviction of this call)
   bool hit = false;
   if (i < n_ids) {
     const int32_t v = ids[i];
@@ -69,8 +85,14 @@ struct OrderEntry {
 };
 __global__ __launch_bounds__(kBlock) void k_cache_split(const uint64_t* __restrict__ hit_bits, const uint32_t* __restrict__ word_rank,
                                                         const int32_t* __restrict__ ids, const int32_t* __restrict__ slot_i,
-                                                        int64_t n_ids, OrderEntry* __restrict__ order) {
+                                                        int64_t n_ids, OrderEntry* __restrict__ order,
+                                                        const CacheCtl* __restrict__ ctl, CachePad* pad, uint64_t ticket) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i == 0) {  // the counts are known: on their way to the host while the ids are split
+    pad->ctl = *ctl;
+    __threadfence_system();
+    __hip_atomic_store(&pad->ticket, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
   if (i >= n_ids) return;
   const uint64_t word = hit_bits[i >> 6];
   const int64_t h = (int64_t)word_rank[i >> 6] + __popcll(word & ((1ull << (i & 63)) - 1ull));
@@ -170,16 +192,18 @@ __global__ __launch_bounds__(kBlock) void k_cache_misses(const char* __restrict_
 // ---- eviction: radix select of the E-th smallest stamp, then sweep -----------------------------------------------
 // One pass of the select: counts, per value of the next `bits` bits, the live entries whose leading digits equal the
 // prefix found so far; the block that merges its counts last (a counter in the control block; nobody waits) finds the
-// digit that holds the `remaining`-th entry, extends the prefix and clears the counters for the next pass.
+// digit that holds the `remaining`-th entry, extends the prefix and clears the counters for the next pass.  The blocks' adds
+// to one counter, and their counting themselves, are what a pass waits for: 2 M stamps (16 MB) 12 us with one copy of the
+// counters and one word, 7 us with kSelCopies copies and the tally's lines.
 __global__ __launch_bounds__(kSelBlock) void k_cache_sel_pass(const uint64_t* __restrict__ stamp, int64_t capacity, uint64_t base,
-                                                              int shift, int bits, int prev_shift, CacheCtl* ctl,
-                                                              uint32_t* __restrict__ hist) {
+                                                              int shift, int bits, int prev_shift, uint64_t rank, CacheCtl* ctl,
+                                                              SelShared* __restrict__ shared) {
   __shared__ uint32_t lh[kSelBins];
   __shared__ uint32_t wave_tot[kSelBins / kWave];
   __shared__ uint32_t s_last;
   if (threadIdx.x < kSelBins) lh[threadIdx.x] = 0;
   __syncthreads();
-  const uint64_t prefix = ctl->prefix;
+  const uint64_t prefix = prev_shift < 0 ? 0 : ctl->prefix;  // (the first pass: everything is still to be located)
   const uint32_t digit_mask = (1u << bits) - 1u;
   const int64_t stride = (int64_t)gridDim.x * kSelBlock;
   constexpr int U = 4;  // stamps per thread in flight
@@ -207,20 +231,25 @@ __global__ __launch_bounds__(kSelBlock) void k_cache_sel_pass(const uint64_t* __
     }
   }
   __syncthreads();
+  uint32_t* hist = shared->hist[blockIdx.x % kSelCopies];
+  uint32_t merged = 0;
   if (threadIdx.x < kSelBins) {
     const uint32_t c = lh[threadIdx.x];
-    if (c) atomicAdd(&hist[threadIdx.x], c);
+    if (c) merged = atomicAdd(&hist[threadIdx.x], c);
   }
-  __syncthreads();  // the block's adds have been performed (each wave waits for its own before the barrier)
+  asm volatile("" : : "v"(merged) : "memory");  // each wave's adds have been performed ...
+  __syncthreads();                              // ... before the block counts as done
   if (threadIdx.x == 0) {
-    __threadfence();  // ... and are ordered before the block counts as done
-    s_last = atomicAdd(&ctl->sel_done, 1u) == gridDim.x - 1 ? 1u : 0u;
-    __threadfence();  // every other block merged its counts before it counted itself
+    uint32_t unused;
+    s_last = tally_last(&shared->done, 0u, &unused) ? 1u : 0u;
   }
   __syncthreads();
   if (s_last == 0) return;
   const bool has = threadIdx.x < kSelBins;  // (the first kSelBins / 64 waves, whole)
-  const uint32_t v = has ? __hip_atomic_load(&hist[threadIdx.x % kSelBins], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+  uint32_t v = 0;
+#pragma unroll
+  for (int q = 0; q < kSelCopies; ++q)
+    v += has ? __hip_atomic_load(&shared->hist[q][threadIdx.x % kSelBins], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
   uint32_t incl = wave_incl_scan(v);
   if (has && lane_id() == kWave - 1) wave_tot[threadIdx.x / kWave] = incl;
   __syncthreads();
@@ -228,28 +257,30 @@ __global__ __launch_bounds__(kSelBlock) void k_cache_sel_pass(const uint64_t* __
   for (int w = 0; w < (int)threadIdx.x / kWave; ++w) incl += wave_tot[w];
   uint32_t total = 0;
   for (int w = 0; w < kSelBins / kWave; ++w) total += wave_tot[w];
-  const uint64_t remaining = ctl->remaining;
+  const uint64_t remaining = prev_shift < 0 ? rank : ctl->remaining;
   const uint64_t before = (uint64_t)(incl - v);
   // the digit that holds the remaining-th entry; if the counts fall short of it (they do not), the last digit
   const bool mine = remaining > (uint64_t)total ? threadIdx.x == digit_mask : (before < remaining && remaining <= (uint64_t)incl);
   if (mine) {
     ctl->prefix = (prefix << bits) | (uint64_t)threadIdx.x;
     ctl->remaining = remaining - before;
-    ctl->sel_done = 0;
   }
-  __hip_atomic_store(&hist[threadIdx.x], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (int q = 0; q < kSelCopies; ++q)
+    __hip_atomic_store(&shared->hist[q][threadIdx.x], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Evicts every entry with stamp - base <= threshold (or every entry, if evict_all) and pushes the freed slots on the
 // free list.  Each block owns a contiguous chunk of slots: it first counts its evictions, reserves that many free-list
 // places with ONE atomic, then sweeps the chunk again handing out the places by ballot and a running offset.
-__global__ __launch_bounds__(kBlock) void k_cache_evict(uint64_t* __restrict__ stamp, int32_t* __restrict__ vertex_of,
+__global__ __launch_bounds__(kEvictBlock) void k_cache_evict(uint64_t* __restrict__ stamp, int32_t* __restrict__ vertex_of,
                                                         int32_t* __restrict__ slot_of, int32_t* __restrict__ free_list,
                                                         int64_t capacity, int64_t chunk, uint64_t base, bool evict_all,
-                                                        int64_t n_free, CacheCtl* ctl) {
-  __shared__ int32_t wave_cnt[kWavesPerBlock];
+                                                        int64_t n_free, CacheCtl* ctl, CachePad* pad) {
+  __shared__ int32_t wave_cnt[kEvictBlock / kWave];
   __shared__ int32_t block_base;
   const uint64_t thr = ctl->prefix;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && !evict_all) pad->threshold = thr;  // (mapped host memory; read behind an event)
   const int64_t lo = (int64_t)blockIdx.x * chunk;
   const int64_t hi = lo + chunk < capacity ? lo + chunk : capacity;
   const int lane = lane_id(), wib = wave_in_block();
@@ -260,19 +291,19 @@ __global__ __launch_bounds__(kBlock) void k_cache_evict(uint64_t* __restrict__ s
   };
   // pass 1: how many
   int32_t mine = 0;
-  for (int64_t i = lo + threadIdx.x; i < hi; i += kBlock) mine += is_out(i);
+  for (int64_t i = lo + threadIdx.x; i < hi; i += kEvictBlock) mine += is_out(i);
   mine = (int32_t)wave_sum_i64(mine);
   if (lane == 0) wave_cnt[wib] = mine;
   __syncthreads();
   if (threadIdx.x == 0) {
     int32_t total = 0;
-    for (int w = 0; w < kWavesPerBlock; ++w) total += wave_cnt[w];
+    for (int w = 0; w < kEvictBlock / kWave; ++w) total += wave_cnt[w];
     block_base = total ? atomicAdd(&ctl->n_push, total) : 0;
   }
   __syncthreads();
   int64_t run = n_free + block_base;
   // pass 2: hand out the places (chunk is a multiple of the block size, so every thread runs every round)
-  for (int64_t r = lo; r < hi; r += kBlock) {
+  for (int64_t r = lo; r < hi; r += kEvictBlock) {
     const int64_t i = r + threadIdx.x;
     const bool out = is_out(i);
     const uint64_t mask = ballot64(out);
@@ -281,7 +312,7 @@ __global__ __launch_bounds__(kBlock) void k_cache_evict(uint64_t* __restrict__ s
     __syncthreads();
     int32_t before = 0, total = 0;
 #pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) {
+    for (int w = 0; w < kEvictBlock / kWave; ++w) {
       const int32_t cw = wave_cnt[w];
       if (w < wib) before += cw;
       total += cw;
@@ -299,24 +330,10 @@ __global__ __launch_bounds__(kBlock) void k_cache_evict(uint64_t* __restrict__ s
 }
 
 __global__ void k_cache_ctl_set(CacheCtl* ctl, uint64_t remaining) {
-  ctl->prefix = 0; ctl->remaining = remaining; ctl->n_push = 0; ctl->sel_done = 0;
+  ctl->prefix = 0; ctl->remaining = remaining; ctl->n_push = 0;
 }
 
 __global__ void k_cache_clear_err(CacheCtl* ctl) { ctl->err_range = 0; }
-
-// Landing pad in mapped pinned host memory.  The counts of a call reach the host by a one-thread kernel that stores the
-// control block and then a ticket, which the host polls: quicker than an asynchronous copy and a wait for it.
-struct CachePad {
-  CacheCtl ctl;          // counts of the call under way; must stay the first member
-  uint64_t ticket;       // written by the device after ctl
-  uint64_t next_ticket;  // host side only
-  CacheCtl threshold;    // control block after the last eviction (copied, read one call late)
-};
-__global__ void k_cache_publish(const CacheCtl* __restrict__ ctl, CachePad* pad, uint64_t ticket) {
-  pad->ctl = *ctl;
-  __threadfence_system();
-  __hip_atomic_store(&pad->ticket, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
 
 __global__ __launch_bounds__(kBlock) void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v, bool iota) {
   int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -341,7 +358,7 @@ struct coop_cache {
   uint32_t* rank_h;
   OrderEntry* order;      // hits from the front, misses from the back
   void* scan_tmp;
-  uint32_t* hist;
+  SelShared* sel;
   CacheCtl* d_ctl;
   CachePad* pad;          // mapped pinned
   hipEvent_t ev_threshold;  // threshold of the last eviction has landed in pad->threshold
@@ -362,7 +379,7 @@ static void release_host_side(coop_cache* c) {
 static int settle_base(coop_cache* c) {
   if (!c->base_pending) return COOP_OK;
   COOP_HIP_TRY(hipEventSynchronize(c->ev_threshold));
-  c->base += c->pad->threshold.prefix + 1;
+  c->base += c->pad->threshold + 1;
   c->base_pending = false;
   return COOP_OK;
 }
@@ -398,7 +415,7 @@ extern "C" int coop_cache_create(int64_t capacity_rows, int64_t n_vertices, int3
   c->rank_h = alloc.get<uint32_t>(max_ids, COOP_TAG_OUTPUT);
   c->order = alloc.get<OrderEntry>(max_ids, COOP_TAG_OUTPUT);
   c->scan_tmp = alloc.get<char>((int64_t)scan_tmp_bytes(max_ids), COOP_TAG_OUTPUT);
-  c->hist = alloc.get<uint32_t>(kSelBins, COOP_TAG_OUTPUT);
+  c->sel = alloc.get<SelShared>(1, COOP_TAG_OUTPUT);
   c->d_ctl = alloc.get<CacheCtl>(1, COOP_TAG_OUTPUT);
   if (alloc.failed) { delete c; return COOP_E_NOMEM; }
   if (hipHostMalloc((void**)&c->pad, sizeof(CachePad), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
@@ -415,7 +432,7 @@ extern "C" int coop_cache_create(int64_t capacity_rows, int64_t n_vertices, int3
     COOP_LAUNCH(K_FILL, k_fill_i32, dim3(grid_for(capacity_rows)), dim3(kBlock), 0, s, c->free_list, capacity_rows, 0, true);
     fill_u64(c->stamp, capacity_rows, 0, s);
   }
-  fill_u64((uint64_t*)c->hist, kSelBins / 2, 0, s);
+  fill_u64((uint64_t*)c->sel, sizeof(SelShared) / 8, 0, s);
   COOP_LAUNCH(K_FILL, k_cache_ctl_set, dim3(1), dim3(1), 0, s, c->d_ctl, (uint64_t)0);
   COOP_LAUNCH(K_FILL, k_cache_clear_err, dim3(1), dim3(1), 0, s, c->d_ctl);
   if (hipStreamSynchronize(s) != hipSuccess) { release_host_side(c); delete c; return COOP_E_HIP; }
@@ -612,14 +629,12 @@ extern "C" int coop_cache_gather(coop_cache* c, const void* table, int64_t table
   // (a call on another stream than the last one's: the threshold of that one is still to be copied out of the control block)
   if (c->base_pending) COOP_HIP_TRY(hipStreamWaitEvent(s, c->ev_threshold, 0));
   // 1. lookup, hit ranks
-  COOP_LAUNCH(K_FILL, k_cache_ctl_set, dim3(1), dim3(1), 0, s, c->d_ctl, (uint64_t)0);
   COOP_LAUNCH(K_CACHE_LOOKUP, k_cache_lookup, dim3((unsigned)((n_ids + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, ids, n_ids,
               c->n_vertices, c->slot_of, c->slot_i, c->hit_bits, c->d_ctl);
   scan_popc_to_u32(c->hit_bits, (n_ids + 63) / 64, c->rank_h, &c->d_ctl->n_hit, c->scan_tmp, s);
-  const uint64_t ticket = ++c->pad->next_ticket;  // the counts are known from here on: on their way while the split runs
-  COOP_LAUNCH(K_FILL, k_cache_publish, dim3(1), dim3(1), 0, s, (const CacheCtl*)c->d_ctl, c->pad, ticket);
+  const uint64_t ticket = ++c->pad->next_ticket;
   COOP_LAUNCH(K_CACHE_LOOKUP, k_cache_split, dim3((unsigned)((n_ids + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, (const uint64_t*)c->hit_bits,
-              (const uint32_t*)c->rank_h, ids, (const int32_t*)c->slot_i, n_ids, c->order);
+              (const uint32_t*)c->rank_h, ids, (const int32_t*)c->slot_i, n_ids, c->order, (const CacheCtl*)c->d_ctl, c->pad, ticket);
   // 2. hits: rows out of the cache, new stamps (runs while the host waits for the counts and queues the rest)
   dispatch_rows(c, table, table_rows, n_ids, out, 0, 0, 0, 0, true, s);
   {  // the wait is bounded: after a while, or once the stream has run dry, the host synchronises instead
@@ -659,7 +674,6 @@ extern "C" int coop_cache_gather(coop_cache* c, const void* table, int64_t table
       int nbits = 1;
       while (nbits < 64 && (range >> nbits) != 0) ++nbits;
       const int passes = (nbits + kSelBits - 1) / kSelBits;
-      COOP_LAUNCH(K_FILL, k_cache_ctl_set, dim3(1), dim3(1), 0, s, c->d_ctl, (uint64_t)n_evict);
       // the bits of the range are split evenly over the passes
       int prev_shift = -1, shift = nbits;
       for (int p = 0; p < passes; ++p) {
@@ -668,23 +682,22 @@ extern "C" int coop_cache_gather(coop_cache* c, const void* table, int64_t table
         int64_t blocks = (c->capacity + kSelBlock * 4 - 1) / (kSelBlock * 4);
         if (blocks > kSelMaxBlocks) blocks = kSelMaxBlocks;
         COOP_LAUNCH(K_CACHE_SELECT, k_cache_sel_pass, dim3((unsigned)(blocks > 0 ? blocks : 1)), dim3(kSelBlock), 0, s, c->stamp, c->capacity,
-                    c->base, shift, bits, prev_shift, c->d_ctl, c->hist);
+                    c->base, shift, bits, prev_shift, (uint64_t)n_evict, c->d_ctl, c->sel);
         prev_shift = shift;
       }
       threshold_known = true;
     }
     {
-      // at most 1,024 blocks: every block reserves its places with an atomic on one counter, which takes them one after
-      // the other (some 20 ns each), and the longer runs of neighbouring slots that a block hands out make the rows that
-      // the miss mover writes next lie closer together (with 2,048 blocks the sweep takes 0.086 instead of 0.077 ms and
-      // the mover 0.38 instead of 0.34 to 0.36; with 256 the sweep itself takes 0.117)
-      int64_t blocks = (c->capacity + kBlock - 1) / kBlock;
-      if (blocks > 1024) blocks = 1024;
+      // few and large blocks: every block reserves its places with an atomic on one counter, which takes them one after the
+      // other (some 20 ns each), and the longer runs of neighbouring slots that a block hands out make the rows that the miss
+      // mover writes next lie closer together (2 M slots: 34 us in 1,024 blocks of 256 threads, 28 in 256 of 1,024)
+      int64_t blocks = (c->capacity + kEvictBlock - 1) / kEvictBlock;
+      if (blocks > 256) blocks = 256;
       int64_t chunk = (c->capacity + blocks - 1) / blocks;
-      chunk = (chunk + kBlock - 1) / kBlock * kBlock;
+      chunk = (chunk + kEvictBlock - 1) / kEvictBlock * kEvictBlock;
       blocks = (c->capacity + chunk - 1) / chunk;
-      COOP_LAUNCH(K_CACHE_EVICT, k_cache_evict, dim3((unsigned)blocks), dim3(kBlock), 0, s, c->stamp, c->vertex_of, c->slot_of,
-                  c->free_list, c->capacity, chunk, c->base, evict_all, n_free, c->d_ctl);
+      COOP_LAUNCH(K_CACHE_EVICT, k_cache_evict, dim3((unsigned)blocks), dim3(kEvictBlock), 0, s, c->stamp, c->vertex_of, c->slot_of,
+                  c->free_list, c->capacity, chunk, c->base, evict_all, n_free, c->d_ctl, c->pad);
     }
     n_free += n_evict;
     c->size -= n_evict;
@@ -696,7 +709,6 @@ extern "C" int coop_cache_gather(coop_cache* c, const void* table, int64_t table
   c->clock = clock_after;
 
   if (threshold_known) {  // read when it is next needed: the call does not wait for its own row copies
-    COOP_HIP_TRY(hipMemcpyAsync(&c->pad->threshold, c->d_ctl, sizeof(CacheCtl), hipMemcpyDeviceToHost, s));
     COOP_HIP_TRY(hipEventRecord(c->ev_threshold, s));
     c->base_pending = true;
   }

@@ -42,8 +42,8 @@ __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
 // One thread per block: counts the block, with `add`, in the tally; true in the block that is the last of gridDim.x, where
 // *total is the sum of all blocks' `add` (below 2^32).  Each atomic is performed before the next one that depends on it is
 // sent.  The words are zero again afterwards.
-__device__ __forceinline__ bool tally_last(Ctl* ctl, uint32_t add, uint32_t* total) {
-  unsigned long long* word = reinterpret_cast<DeviceCtl*>(ctl)->tally.word;
+__device__ __forceinline__ bool tally_last(Tally* tally, uint32_t add, uint32_t* total) {
+  unsigned long long* word = tally->word;
   const uint32_t line = blockIdx.x % kTallyLines;
   const uint32_t in_line = (gridDim.x - line + kTallyLines - 1) / kTallyLines;  // blocks line, line + kTallyLines, ...
   uint32_t sum = add, counts = gridDim.x;
@@ -59,6 +59,10 @@ __device__ __forceinline__ bool tally_last(Ctl* ctl, uint32_t add, uint32_t* tot
   __hip_atomic_store(&word[0], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   *total = (uint32_t)b + sum;
   return true;
+}
+
+__device__ __forceinline__ bool tally_last(Ctl* ctl, uint32_t add, uint32_t* total) {
+  return tally_last(&reinterpret_cast<DeviceCtl*>(ctl)->tally, add, total);
 }
 
 // ---- rows moved as items of up to 16 bytes --------------------------------------------------------------------------

@@ -279,6 +279,16 @@ def test_cache_row_shapes(P, dtype, dim):
     run_cache_sequence(P, 400, n, dim, dtype, batches, "cuda" if dim % 2 else "pinned")
 
 
+@pytest.mark.parametrize("cap", [1, 1023, 1024, 1025, 262144, 262145, 300001])
+def test_cache_eviction_at_block_edges(P, cap):
+    """Capacities on both sides of one eviction block (1,024 slots), of a slot range of more than one round per block
+    (256 blocks), and a single slot; batches that evict a few entries, most of them and all of them."""
+    n = 400000
+    rng = np.random.default_rng(cap)
+    sizes = (cap, cap // 2 + 1, 3, cap // 3 + 1, min(n, cap + 7), cap // 2 + 1, 5)
+    run_cache_sequence(P, cap, n, 2, torch.float32, [rng.permutation(n)[:b].astype(np.int32) for b in sizes], "cuda")
+
+
 def test_cache_on_sampled_batches_with_kappa(P, medium):
     """Input sets of consecutive dependent LABOR-0 batches through the cache: misses equal the oracle's on every
     iteration, and a larger kappa lowers the miss count (temporal locality of Sec. 4.2)."""
