@@ -68,10 +68,11 @@ __device__ __forceinline__ uint32_t long_bit(uint32_t s) { return long_slot(s) >
 
 struct EnumItem { int64_t beg; uint32_t len, t, u, pad; };  // up to kEnumItem entries of listed vertex t's list; u = R_t
 constexpr uint32_t kEnumItem = 64;         // entries per item: 16 lanes walk it, 4 entries each, loaded together
-constexpr int kListBlock = 256;            // threads per block of k_enum_list
-constexpr uint32_t kEnumListSpan = 8192;   // variates per block of k_enum_list
-constexpr uint32_t kEnumListStep = 1024;   // variates per step of a block (4 per thread), between two barriers
-constexpr uint32_t kEnumListBuf = 2048;    // vertices a block collects before it writes their items out
+constexpr int kListBlock = 512;            // threads per block of k_enum_list
+constexpr uint32_t kEnumListSpan = 16384;  // variates per block of k_enum_list (few blocks: each reserves its items with a
+                                           // same-address atomic, and those are taken one after the other, some 20 ns each)
+constexpr uint32_t kEnumListStep = 1024;   // variates per step of a block (2 per thread), between two barriers
+constexpr uint32_t kEnumListBuf = 2048;    // vertices a block collects before it writes their items out (53 KB: three blocks per CU)
 
 struct EnumOut {
   EnumItem* item[kMaxFuse];    // [item_cap[f]] per covered layer
@@ -88,6 +89,7 @@ __global__ __launch_bounds__(kListBlock) void k_enum_list(FusedKeys keys, uint32
                                                       uint32_t todo /* bit f: layer f is to be listed (the others have their lists) */) {
   __shared__ uint2 buf[kEnumListBuf];     // (t, u)
   __shared__ uint32_t s_d[kEnumListBuf], s_at[kEnumListBuf];
+  __shared__ int64_t s_beg[kEnumListBuf];
   __shared__ uint16_t s_long[kEnumListBuf];  // the collected vertices that give more than one item
   __shared__ uint32_t n_buf, n_local, n_long, base;
   const int f = blockIdx.y;
@@ -107,6 +109,7 @@ __global__ __launch_bounds__(kListBlock) void k_enum_list(FusedKeys keys, uint32
       const int64_t beg = g_indptr[t];
       const uint32_t d = (uint32_t)(g_indptr[t + 1] - beg);  // (0: a vertex without neighbours is nobody's neighbour)
       s_d[i] = d;
+      s_beg[i] = beg;
       if (d != 0) s_at[i] = atomicAdd(&n_local, (d + kEnumItem - 1) / kEnumItem);
       if (d > kEnumItem) s_long[atomicAdd(&n_long, 1u)] = (uint16_t)i;
     }
@@ -118,15 +121,17 @@ __global__ __launch_bounds__(kListBlock) void k_enum_list(FusedKeys keys, uint32
     } else {
       for (uint32_t i = threadIdx.x; i < nb; i += kListBlock) {  // a thread per vertex with one item
         const uint32_t d = s_d[i];
-        if (d != 0 && d <= kEnumItem) item_f[base + s_at[i]] = EnumItem{g_indptr[buf[i].x], d, buf[i].x, buf[i].y, 0u};
+        if (d != 0 && d <= kEnumItem) item_f[base + s_at[i]] = EnumItem{s_beg[i], d, buf[i].x, buf[i].y, 0u};
       }
-      for (uint32_t v = 0; v < n_long; ++v) {                // the block together for each of the others
+      // a wave for each of the others (their bounds are at hand: read again, one list after the other, they were most of the
+      // kernel's 40 us)
+      for (uint32_t v = threadIdx.x / kWave; v < n_long; v += kListBlock / kWave) {
         const uint32_t i = s_long[v];
         const uint32_t d = s_d[i];
         const uint2 tu = buf[i];
-        const int64_t beg = g_indptr[tu.x];
+        const int64_t beg = s_beg[i];
         EnumItem* to = item_f + base + s_at[i];
-        for (uint32_t q = threadIdx.x; q * kEnumItem < d; q += kListBlock) {
+        for (uint32_t q = (uint32_t)lane_id(); (uint64_t)q * kEnumItem < d; q += kWave) {
           const uint32_t off = q * kEnumItem;
           to[q] = EnumItem{beg + off, d - off < kEnumItem ? d - off : kEnumItem, tu.x, tu.y, 0u};
         }
