@@ -323,7 +323,11 @@ __global__ __launch_bounds__(kWalkBlock, 6) void k_enum_walk(const int32_t* __re
 
 // list records of the destinations scanned in this pass, and their keep thresholds for the nf covered layers
 // (pthr, lim2: the blended path's first and second filter thresholds, null when c = 0)
-constexpr int kSegBlock = 1024;  // large blocks: one queue reservation (a same-address atomic) per 1024 destinations
+// Large blocks: one queue reservation (a same-address atomic) per 1,024 destinations.  Below kSegWideFrom destinations small
+// ones, which spread over more CUs what the thresholds of a blend cost in fp64 (1,024 destinations, three layers: 13 us in
+// one block, 10 in sixteen; 110 thousand with two layers 15 and 9).
+constexpr int64_t kSegWideFrom = 65536;
+template <int kSegBlock>
 __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restrict__ g_indptr, int64_t n_vertices,
                                                      const int32_t* __restrict__ dst, int64_t n, int nf,
                                                      uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3, Segment* __restrict__ seg,
@@ -1264,10 +1268,15 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
         if (alloc.failed) return COOP_E_NOMEM;
         fill_u64((uint64_t*)zeroed, (1 + kLongBits / 8 / sizeof(LongSlot) + (int64_t)slots) * (sizeof(LongSlot) / 8), 0, s);
       }
-      COOP_LAUNCH(K_SEGMENTS, k_segments, dim3(blocks_for(n_new, kSegBlock)), dim3(kSegBlock), 0, s, cx.g->indptr, cx.g->n_vertices,
-                  dst + ps.start, n_new, ps.nf, ks[0], ks[1], ks[2], ks[3], ps.seg, ps.thr, pthr, lim2, cx.cw, cx.sw,
-                  cx.blend && cx.vec4 ? 1 : 0, cx.d_ctl,
-                  piece_len, split_min, pieces, piece_cap, cx.d_piece_count + l, out, enum_degree, long_bits, long_tab, long_mask);
+#define COOP_SEGMENTS(BLOCK)                                                                                                          \
+  COOP_LAUNCH(K_SEGMENTS, k_segments<BLOCK>, dim3(blocks_for(n_new, BLOCK)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices,          \
+              dst + ps.start, n_new, ps.nf, ks[0], ks[1], ks[2], ks[3], ps.seg, ps.thr, pthr, lim2, cx.cw, cx.sw,                        \
+              cx.blend && cx.vec4 ? 1 : 0, cx.d_ctl, piece_len, split_min, pieces, piece_cap, cx.d_piece_count + l, out, enum_degree,    \
+              long_bits, long_tab, long_mask)
+      if (n_new >= kSegWideFrom) COOP_SEGMENTS(1024);
+      else if (n_new >= 16384 || !cx.blend) COOP_SEGMENTS(256);
+      else COOP_SEGMENTS(64);
+#undef COOP_SEGMENTS
       if (enum_degree != 0) {
         if (list_todo != 0) {
           const unsigned list_blocks = blocks_for((int64_t)um_most + 1, kEnumListSpan);

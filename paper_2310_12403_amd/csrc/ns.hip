@@ -32,7 +32,8 @@ struct NsRecord {
 // block reserves its places with one returning atomic, and those on one address are taken one after the other, some 20 ns
 // each: 675 thousand destinations took 40 us in blocks of 256 and take 28 in blocks of 1,024 threads with two each.  Below
 // kNsCountWideFrom destinations, and with c > 0, where every destination has its thresholds evaluated in fp64, the small
-// blocks are the quicker ones: 10 us against 12 for 110 thousand, 5 against 8 for 16 thousand, and half the time with c > 0.)
+// blocks are the quicker ones: 10 us against 12 for 110 thousand, 5 against 8 for 16 thousand, and half the time with c > 0;
+// with c > 0 below 16,384 blocks of one wave, which spread over more CUs.)
 constexpr int64_t kNsCountWideFrom = 262144;
 template <int kNsCountBlock, int kNsCountEach>
 __global__ __launch_bounds__(kNsCountBlock) void k_ns_count(const int64_t* __restrict__ g_indptr, int64_t n_vertices,
@@ -750,7 +751,8 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
   COOP_LAUNCH(K_NS_COUNT, (k_ns_count<BLOCK, EACH>), dim3(blocks_for(n_dst, BLOCK * EACH)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices, \
               dst, n_dst, k, target, cnt, rec, bthr, cx.cw, cx.sw, cx.d_ctl, long_min, long_list, n_long)
   if (n_dst >= kNsCountWideFrom && !cx.blend) COOP_NS_COUNT(1024, 2);
-  else if (n_dst > 0) COOP_NS_COUNT(kBlock, 1);
+  else if (n_dst >= 16384 || (n_dst > 0 && !cx.blend)) COOP_NS_COUNT(kBlock, 1);
+  else if (n_dst > 0) COOP_NS_COUNT(kWave, 1);
 #undef COOP_NS_COUNT
   if (defer) {
     scan_i32_to_i64(cnt, n_dst, blk->indptr, &cx.d_ctl->total_edges, scan_tmp, s, nullptr);  // the count stays on the device
