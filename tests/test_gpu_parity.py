@@ -771,6 +771,34 @@ def test_frontier_dedup_of_short_lists(P, shape):
         assert "unique_filter" in ran or size > 100000, (size, ran.keys())
 
 
+@pytest.mark.parametrize("chunks", [True, False])
+def test_scratch_cut_from_chunks(P, tiny, chunks):
+    """Small scratch buffers are cut from chunks; an allocator that does not hand out buffers of a chunk's size is asked for
+    each of them instead, and every output has a buffer of its own either way."""
+    import ctypes as C
+    from paper_2310_12403_amd import binding
+
+    class Limited(binding._TorchAllocator):
+        def __init__(self):
+            super().__init__(torch.device("cuda"))
+            inner = self.fn_obj
+            self.asked = []
+
+            def alloc(ctx, nbytes, tag):
+                self.asked.append((nbytes, tag))
+                return inner(ctx, nbytes, tag) if chunks or nbytes != 1020 << 10 else None
+
+            self.limited = binding.ALLOC_FN(alloc)
+            self.fn = C.cast(self.limited, C.c_void_p)
+
+    for sampler, kappa in ((R.LABOR0, 4), (R.NS, 1)):
+        al = Limited()
+        compare(P, tiny, np.arange(3, 60), (4, 3), sampler, it=5, kappa=kappa, seed=2, arena=al)
+        outputs = [n for n, tag in al.asked if tag == 0]
+        assert len(outputs) >= 1 + 2 * 5
+        assert (1020 << 10, 1) in al.asked and (len(al.asked) - len(outputs) < 8) == chunks
+
+
 def test_ns_lists_left_to_the_one_kernel_path(P):
     """c > 0: lists in which one neighbour occurs 200 times tie with themselves beyond what a row of candidates holds, so all
     3,000 of them go through the queue of the one-kernel path, several per wave; next to lists that do not."""
