@@ -321,7 +321,8 @@ const char* coop_strerror(int code);
                                       (exercises the fallback) */
 #define COOP_TUNE_UNIQUE 7         /* how the frontier is deduplicated.  0 (default): lists of 262,144 entries or more (S^l and
                                       the sampled edges together) by partition into buckets that are deduplicated in LDS,
-                                      shorter ones through a hash table in HBM; 1: always the table in HBM; 2: by partition
+                                      shorter ones in LDS as well, every block picking its bucket's keys from the whole list;
+                                      1: always a hash table in HBM; 2: by partition
                                       whatever the length; 3: as 2 with buckets 16 times too large, so that buckets overflow
                                       and the call falls back to the table (exercises the fallback) */
 #define COOP_TUNE_ENUM_DEGREE 8    /* LABOR-0 with independent variates on a graph registered with COOP_SYMMETRIC: lists
