@@ -250,6 +250,8 @@ __global__ __launch_bounds__(kSelBlock) void k_cache_sel_pass(const uint64_t* __
 #pragma unroll
   for (int q = 0; q < kSelCopies; ++q)
     v += has ? __hip_atomic_load(&shared->hist[q][threadIdx.x % kSelBins], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+  // (before the barrier: the thread that finds the digit overwrites it behind that)
+  const uint64_t remaining = prev_shift < 0 ? rank : __hip_atomic_load(&ctl->remaining, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   uint32_t incl = wave_incl_scan(v);
   if (has && lane_id() == kWave - 1) wave_tot[threadIdx.x / kWave] = incl;
   __syncthreads();
@@ -257,7 +259,6 @@ __global__ __launch_bounds__(kSelBlock) void k_cache_sel_pass(const uint64_t* __
   for (int w = 0; w < (int)threadIdx.x / kWave; ++w) incl += wave_tot[w];
   uint32_t total = 0;
   for (int w = 0; w < kSelBins / kWave; ++w) total += wave_tot[w];
-  const uint64_t remaining = prev_shift < 0 ? rank : ctl->remaining;
   const uint64_t before = (uint64_t)(incl - v);
   // the digit that holds the remaining-th entry; if the counts fall short of it (they do not), the last digit
   const bool mine = remaining > (uint64_t)total ? threadIdx.x == digit_mask : (before < remaining && remaining <= (uint64_t)incl);

@@ -289,6 +289,24 @@ def test_cache_eviction_at_block_edges(P, cap):
     run_cache_sequence(P, cap, n, 2, torch.float32, [rng.permutation(n)[:b].astype(np.int32) for b in sizes], "cuda")
 
 
+def test_cache_selects_among_more_stamps_than_one_round_reads(P):
+    """1,048,576 stamps are one round of loads of the select's blocks; a cache with half as many again, whose stamps take
+    three passes of eight bits, evicts few entries, many, and entries whose rank falls on the first and last of a digit."""
+    cap, n = 1572865, 2000000
+    perm = np.random.default_rng(31).permutation(n).astype(np.int32)
+    feat = synth.features(n, 1, torch.float32, seed=9, device="cpu")
+    table = feat.cuda()
+    cache, oracle = P.Cache(cap, n, 1, torch.float32, n), R.Cache(cap, n)
+    for it, ids in enumerate((perm[:cap], perm[cap:cap + 1], perm[cap + 1:cap + 256], perm[:65536], perm[400000:], perm[:300000])):
+        out, n_miss = cache.gather(table, torch.from_numpy(ids).cuda())
+        assert n_miss == oracle.access(ids)[0], it
+        assert torch.equal(out.cpu()[:, 0], feat[torch.from_numpy(ids).long(), 0]), it
+        held = cache.vertices().cpu().numpy()
+        assert len(held) == oracle.size(), it
+        assert all(oracle.contains(int(v)) for v in held[::97]), it
+    cache.close()
+
+
 def test_cache_on_sampled_batches_with_kappa(P, medium):
     """Input sets of consecutive dependent LABOR-0 batches through the cache: misses equal the oracle's on every
     iteration, and a larger kappa lowers the miss count (temporal locality of Sec. 4.2)."""
