@@ -385,7 +385,7 @@ static int settle_base(coop_cache* c) {
   return COOP_OK;
 }
 
-static unsigned grid_for(int64_t n) {
+static unsigned grid_for(int64_t n) {  // (for kernels that stride over what is left)
   int64_t b = (n + kBlock - 1) / kBlock;
   if (b > 256 * 32) b = 256 * 32;
   return (unsigned)(b > 0 ? b : 1);
@@ -534,7 +534,7 @@ extern "C" int coop_cache_import(coop_cache* c, const void* table, int64_t table
     if (c->capacity > 0) {
       COOP_LAUNCH(K_FILL, k_fill_i32, dim3(grid_for(c->capacity)), dim3(kBlock), 0, s, c->vertex_of, c->capacity, -1, false);
       fill_u64(c->stamp, c->capacity, 0, s);
-      COOP_LAUNCH(K_FILL, k_cache_free_tail, dim3(grid_for(c->capacity)), dim3(kBlock), 0, s, c->free_list, n_live, c->capacity);
+      COOP_LAUNCH(K_FILL, k_cache_free_tail, dim3((unsigned)((c->capacity + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, c->free_list, n_live, c->capacity);
     }
     COOP_LAUNCH(K_FILL, k_cache_clear_err, dim3(1), dim3(1), 0, s, c->d_ctl);
   };
@@ -552,8 +552,8 @@ extern "C" int coop_cache_import(coop_cache* c, const void* table, int64_t table
       default: COOP_IMPORT(2); break;
     }
 #undef COOP_IMPORT
-    COOP_LAUNCH(K_CACHE_LOOKUP, k_cache_import_check, dim3(grid_for(state->size)), dim3(kBlock), 0, s, c->slot_of, c->vertex_of, state->size,
-                c->d_ctl);
+    COOP_LAUNCH(K_CACHE_LOOKUP, k_cache_import_check, dim3((unsigned)((state->size + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+                (const int32_t*)c->slot_of, (const int32_t*)c->vertex_of, state->size, c->d_ctl);
   }
   COOP_HIP_TRY(hipMemcpyAsync(&c->pad->ctl, c->d_ctl, sizeof(CacheCtl), hipMemcpyDeviceToHost, s));
   COOP_HIP_TRY(hipStreamSynchronize(s));

@@ -540,6 +540,32 @@ def test_cache_export_import_resumes_exactly(P):
     assert n_miss == len(batches[0]) and torch.equal(out.cpu(), feat[torch.from_numpy(batches[0]).long()])
 
 
+def test_cache_import_into_a_large_cache(P):
+    """More slots than the 2,097,152 threads of a capped grid: after an import every free slot is listed once, whatever the
+    list held before, and a vertex listed twice is found anywhere in the list."""
+    cap, n, live = 2300000, 2600000, 100000
+    feat = synth.features(n, 1, torch.float32, seed=8, device="cpu")
+    table = feat.cuda()
+    perm = np.random.default_rng(23).permutation(n).astype(np.int32)
+    batches = [perm[:live], perm[live:cap], perm[:cap], perm[cap:], perm[500000:900000]]
+    oracle = R.Cache(cap, n)
+    a, b = (P.Cache(cap, n, 1, torch.float32, n) for _ in range(2))
+    for it, ids in enumerate(batches):
+        out, n_miss = (a if it == 0 else b).gather(table, torch.from_numpy(ids).cuda())
+        assert n_miss == oracle.access(ids)[0], it
+        assert torch.equal(out.cpu()[:, 0], feat[torch.from_numpy(ids).long(), 0]), it
+        if it == 0:
+            b.import_state(table, *a.export_state())
+    assert b.vertices().unique().numel() == oracle.size() == cap
+    vertices, stamps, state = b.export_state()
+    vertices[cap - 2] = vertices[cap - 1]
+    with pytest.raises(P.CoopError) as e:
+        a.import_state(table, vertices, stamps, state)
+    assert e.value.code == -2
+    a.close()
+    b.close()
+
+
 def compare_rw(P, g, seeds, fanouts, o, a, p, it=0, seed=0, arena=None):
     seeds_h = np.ascontiguousarray(seeds, dtype=np.int32)
     want = R.sample(g.indptr_h, g.indices_h, seeds_h, fanouts, R.RW, it=it, seed=seed, rw=(o, a, p))
