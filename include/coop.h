@@ -71,6 +71,20 @@ typedef struct {
 } coop_arena;
 void* coop_arena_alloc(void* arena /* coop_arena* */, size_t bytes, int tag);
 
+/* Small scratch buffers cut from larger ones of another allocator, usable as (coop_chunk_alloc, &chunks) for one call: a
+ * layer asks for a dozen of them, which is most of a small call's time where each request takes microseconds.  Scratch
+ * requests of up to a quarter of chunk_bytes come from chunks of that size (the request itself is passed on where `from`
+ * has no chunk to give); all others are passed on as they are.  For allocators with room to spare: the last chunk is seldom
+ * used up. */
+typedef struct {
+  coop_alloc_fn from;  /* the allocator behind */
+  void* ctx;
+  size_t chunk_bytes;
+  void* at;            /* what is left of the last chunk; at first NULL, 0 */
+  size_t left;
+} coop_chunks;
+void* coop_chunk_alloc(void* chunks /* coop_chunks* */, size_t bytes, int tag);
+
 typedef struct coop_graph coop_graph; /* opaque */
 typedef struct coop_cache coop_cache; /* opaque */
 

@@ -148,33 +148,15 @@ void fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
 // The current device's sticky "an id was out of range" word (device memory; read and cleared by coop_gather_status).
 int32_t* bad_flag();
 
-// Per-call allocator wrapper: 256-byte rounding, NULL check.  A layer asks for a dozen small scratch buffers, and a caller's
-// allocator may take microseconds for each (a torch tensor through a Python callback: 3 to 4, most of a small call's time),
-// so scratch requests of up to a quarter of kScratchChunk are cut from chunks of that size; where a chunk is not to be had the
-// request itself is made.  The arena, which only moves a pointer, is asked for each: it pays nothing for that and wastes nothing.
+// Per-call allocator wrapper: 256-byte rounding, NULL check.
 struct Alloc {
   coop_alloc_fn fn;
   void* ctx;
   bool failed = false;
-  static constexpr size_t kScratchChunk = 1020 << 10;
-  char* chunk = nullptr;
-  size_t left = 0;
   template <typename T>
   T* get(int64_t count, int tag) {
     size_t bytes = (size_t)(count > 0 ? count : 1) * sizeof(T);
     bytes = (bytes + 255) & ~(size_t)255;
-    if (tag == COOP_TAG_SCRATCH && bytes <= kScratchChunk / 4 && fn != coop_arena_alloc) {
-      if (bytes > left) {
-        char* p = (char*)fn(ctx, kScratchChunk, tag);
-        if (p) { chunk = p; left = kScratchChunk; }
-      }
-      if (bytes <= left) {
-        T* p = (T*)chunk;
-        chunk += bytes;
-        left -= bytes;
-        return p;
-      }
-    }
     void* p = fn(ctx, bytes, tag);
     if (!p) failed = true;
     return (T*)p;

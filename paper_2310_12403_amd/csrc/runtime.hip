@@ -458,6 +458,23 @@ void* coop_arena_alloc(void* arena, size_t bytes, int tag) {
   return p;
 }
 
+void* coop_chunk_alloc(void* chunks, size_t bytes, int tag) {
+  coop_chunks* c = (coop_chunks*)chunks;
+  if (!c || !c->from) return nullptr;
+  const size_t need = (bytes + 255) & ~(size_t)255;
+  if (tag != COOP_TAG_SCRATCH || need < bytes || need > c->chunk_bytes / 4) return c->from(c->ctx, bytes, tag);
+  if (need > c->left) {
+    void* p = c->from(c->ctx, c->chunk_bytes, tag);
+    if (!p) return c->from(c->ctx, bytes, tag);
+    c->at = p;
+    c->left = c->chunk_bytes;
+  }
+  void* p = c->at;
+  c->at = (char*)p + need;
+  c->left -= need;
+  return p;
+}
+
 int coop_graph_load_with(const int64_t* indptr, const int32_t* indices, int64_t n_vertices, int64_t n_edges, int flags,
                          coop_alloc_fn alloc, void* alloc_ctx, void* stream, coop_graph** out) {
   if (!out) return COOP_E_NULL;

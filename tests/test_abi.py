@@ -76,6 +76,29 @@ def test_arena_bump_allocator():
     assert L.coop_arena_alloc(None, 8, 0) is None
 
 
+def test_chunk_allocator():
+    """Small scratch requests share a chunk; large ones, outputs and, where there is no chunk, small ones are passed on."""
+    L = P.lib()
+    asked = []
+
+    def alloc(ctx, nbytes, tag):
+        asked.append((nbytes, tag))
+        return 0x100000 * len(asked) if nbytes <= limit else None
+
+    fn = binding.ALLOC_FN(alloc)
+    c = binding._CChunks(C.cast(fn, C.c_void_p).value, None, 4096, None, 0)
+    limit = 1 << 20
+    got = [L.coop_chunk_alloc(C.byref(c), n, t) for n, t in ((10, 1), (1024, 1), (1025, 1), (10, 0), (1000, 1), (1000, 1), (600, 1), (1024, 1))]
+    assert asked == [(4096, 1), (1025, 1), (10, 0), (4096, 1)]
+    assert got == [0x100000, 0x100100, 0x200000, 0x300000, 0x100500, 0x100900, 0x100D00, 0x400000]
+    limit = 2000
+    c = binding._CChunks(C.cast(fn, C.c_void_p).value, None, 4096, None, 0)
+    del asked[:]
+    assert [L.coop_chunk_alloc(C.byref(c), n, 1) for n in (10, 1024)] == [0x200000, 0x400000]
+    assert asked == [(4096, 1), (10, 1), (4096, 1), (1024, 1)]
+    assert L.coop_chunk_alloc(C.byref(c), (1 << 64) - 1, 1) is None and L.coop_chunk_alloc(None, 8, 1) is None
+
+
 def test_profile_table():
     L = P.lib()
     n = L.coop_profile_kernels()

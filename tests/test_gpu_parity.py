@@ -815,14 +815,47 @@ def test_frontier_dedup_of_short_lists(P, shape):
         assert "unique_filter" in ran or size > 100000, (size, ran.keys())
 
 
-@pytest.mark.parametrize("chunks", [True, False])
-def test_scratch_cut_from_chunks(P, tiny, chunks):
-    """Small scratch buffers are cut from chunks; an allocator that does not hand out buffers of a chunk's size is asked for
-    each of them instead, and every output has a buffer of its own either way."""
+@pytest.mark.parametrize("sampler,kappa", [(R.LABOR0, 1), (R.LABOR0, 4), (R.NS, 1), (R.NS, 4)])
+def test_a_callers_allocator_that_has_just_enough(P, tiny, sampler, kappa):
+    """A caller's own allocator is asked for what a call uses and no more: one that has exactly the bytes that the same call
+    takes from an arena serves it, whether that is a few kilobytes or a few megabytes."""
     import ctypes as C
     from paper_2310_12403_amd import binding
 
-    class Limited(binding._TorchAllocator):
+    class Bump:
+        view = P.Arena.view
+
+        def __init__(self, nbytes):
+            self.buf = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+            self.at = self.buf.data_ptr() + -self.buf.data_ptr() % 256
+            self.end, self.error = self.at + nbytes, None
+
+            def alloc(ctx, n, tag):
+                if self.at + n > self.end:
+                    return None
+                self.at += n
+                return self.at - n
+
+            self.fn_obj = binding.ALLOC_FN(alloc)
+            self.fn, self.ctx = C.cast(self.fn_obj, C.c_void_p), C.c_void_p()
+
+    for n_seeds in (1, 20, 60, 200, 700, 2000):
+        seeds = np.arange(5, 5 + n_seeds, dtype=np.int32)
+        arena = P.Arena(256 << 20)
+        compare(P, tiny, seeds, (10, 5), sampler, it=5, kappa=kappa, seed=n_seeds, arena=arena)
+        own = Bump(arena.c.used)
+        compare(P, tiny, seeds, (10, 5), sampler, it=5, kappa=kappa, seed=n_seeds, arena=own)
+        assert own.at == own.end
+
+
+@pytest.mark.parametrize("chunks", [True, False])
+def test_scratch_cut_from_chunks(P, tiny, chunks):
+    """coop_chunk_alloc cuts small scratch buffers from chunks; an allocator that does not hand out buffers of a chunk's size
+    is asked for each of them instead, and every output has a buffer of its own either way."""
+    import ctypes as C
+    from paper_2310_12403_amd import binding
+
+    class Limited(binding._SampleAllocator):
         def __init__(self):
             super().__init__(torch.device("cuda"))
             inner = self.fn_obj
@@ -833,7 +866,7 @@ def test_scratch_cut_from_chunks(P, tiny, chunks):
                 return inner(ctx, nbytes, tag) if chunks or nbytes != 1020 << 10 else None
 
             self.limited = binding.ALLOC_FN(alloc)
-            self.fn = C.cast(self.limited, C.c_void_p)
+            self.chunks.from_fn = C.cast(self.limited, C.c_void_p).value
 
     for sampler, kappa in ((R.LABOR0, 4), (R.NS, 1)):
         al = Limited()
