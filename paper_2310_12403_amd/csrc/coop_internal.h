@@ -191,9 +191,10 @@ struct UniqueWork {
   int64_t n_new = 0;
 };
 // launch: every kernel of the front half; one of them sends the sizes to the host; does not wait.  col_local (m entries)
-// holds intermediate results until `back` has run.
+// holds intermediate results until `back` has run, and so does `spare` (n_dst + m entries, e.g. the array that will be
+// src_ids) when it is not null.
 int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
-                        UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s);
+                        int32_t* spare, UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s);
 // finish: waits for the sizes (h_ctl then holds total_edges, total_new and the flags; w->n_new is set).  If the dedup
 // had to be run again (*redone), a relabelling launched in between has to be launched again.
 int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,

@@ -217,12 +217,12 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
       rc = sample_layer(edge_cap);
       if (rc != COOP_OK) break;
       const int64_t* m_dev = &cx.d_ctl->total_edges;
-      rc = unique_front_launch(dst, n_dst, blk.col_global, edge_cap, m_dev, blk.col_local, &uw, alloc, cx.d_ctl, h_ctl, s);
+      src = alloc.get<int32_t>(n_dst + edge_cap, COOP_TAG_OUTPUT);
+      if (alloc.failed) { rc = COOP_E_NOMEM; break; }
+      rc = unique_front_launch(dst, n_dst, blk.col_global, edge_cap, m_dev, blk.col_local, src, &uw, alloc, cx.d_ctl, h_ctl, s);
       if (rc != COOP_OK) break;
       // S^{l+1} and local ids (Eq. 2) are queued before the sizes are back, with room for the bound, so that the device
       // is at work while the host waits for the sizes and sets up the next layer
-      src = alloc.get<int32_t>(n_dst + edge_cap, COOP_TAG_OUTPUT);
-      if (alloc.failed) { rc = COOP_E_NOMEM; break; }
       rc = unique_back(dst, n_dst, blk.col_global, edge_cap, m_dev, uw, blk.col_local, src, s);
       if (rc != COOP_OK) break;
       rc = unique_front_finish(dst, n_dst, blk.col_global, edge_cap, m_dev, blk.col_local, &uw, alloc, cx.d_ctl, h_ctl, s, &redone);
@@ -245,7 +245,7 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
       rc = sample_layer(0);
       if (rc != COOP_OK) break;
       if (n_dst + blk.n_edges >= ((int64_t)1 << 32) - 1) { rc = COOP_E_CAPACITY; break; }
-      rc = unique_front_launch(dst, n_dst, blk.col_global, blk.n_edges, nullptr, blk.col_local, &uw, alloc, cx.d_ctl, h_ctl, s);
+      rc = unique_front_launch(dst, n_dst, blk.col_global, blk.n_edges, nullptr, blk.col_local, nullptr, &uw, alloc, cx.d_ctl, h_ctl, s);
       if (rc != COOP_OK) break;
       rc = unique_front_finish(dst, n_dst, blk.col_global, blk.n_edges, nullptr, blk.col_local, &uw, alloc, cx.d_ctl, h_ctl, s, &redone);
       if (rc != COOP_OK) break;

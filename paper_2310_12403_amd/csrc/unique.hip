@@ -253,7 +253,7 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
 // words in front of it in its block's stretch of positions (one record with the word: looking ranks up is bound by the number
 // of scattered requests), and those of the stretches in front (block_prefix).
 struct RankView {
-  const RankWord* word;
+  const RankWord* word;   // of the positions from the multiple of 64 at or below n_dst on
   const uint32_t* block_prefix;
   uint32_t n_blocks;  // when not 0: the stretches are those of the partition's blocks (part_stretch_len of the whole list)
 };
@@ -338,14 +338,22 @@ __global__ __launch_bounds__(kPartBlock) void k_part_count(const int32_t* __rest
 // The same stretch again: its pairs go to pairs[], bucket b's from place[b * gridDim.x + column] on (place = exclusive
 // scan of counts).  A tile of kTilePairs pairs is first ordered by bucket in LDS, so that the pairs of a tile that share a
 // bucket leave as one contiguous run written by neighbouring lanes, not as single 8-byte stores.  In the tile's new order,
-// went[] gets every pair's index in pairs[] and which[] its number in the tile, for k_uniq_collect.
+// every pair's index in pairs[] ("went") and its number in the tile ("which") are kept for k_uniq_collect.
 constexpr int kTilePairs = 8 * kPartBlock;
+// Where those two lie.  A tile without edges needs neither.  The indices of list position i go to the place in col_local
+// that k_uniq_collect fills from them, those of the one tile that begins below n_dst to `head` where they have none there.
+struct TileNotes {
+  uint32_t* first;  // [m] col_local
+  uint32_t* head;   // [kTilePairs]
+  uint16_t* which;  // [kTilePairs + m]
+  __device__ __forceinline__ uint32_t* went(int64_t i, int64_t n_dst) const { return i >= n_dst ? first + (i - n_dst) : head + (i + kTilePairs - n_dst); }
+  __device__ __forceinline__ uint16_t* which_of(int64_t i, int64_t n_dst) const { return which + (i + kTilePairs - n_dst); }
+};
 // PER: buckets that a thread looks after.  (64 registers, so that two blocks fit a CU.)
 template <int PER>
 __global__ __launch_bounds__(kPartBlock, PER <= 2 ? 8 : 4) void k_part_scatter(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
                                                              int64_t m, const int64_t* __restrict__ m_dev, uint32_t n_buckets,
-                                                             TiledScan<uint32_t> place, unsigned long long* __restrict__ pairs,
-                                                             uint32_t* __restrict__ went, uint16_t* __restrict__ which) {
+                                                             TiledScan<uint32_t> place, unsigned long long* __restrict__ pairs, TileNotes notes) {
   __shared__ unsigned long long staged[kTilePairs];  // the tile's pairs, by bucket
   extern __shared__ uint32_t off[];                  // [n_buckets] the tile's tallies, then run starts in the tile
   uint32_t* delta = off + n_buckets;                 // [n_buckets] run start in pairs[] minus run start in the tile
@@ -366,6 +374,7 @@ __global__ __launch_bounds__(kPartBlock, PER <= 2 ? 8 : 4) void k_part_scatter(c
   __syncthreads();
   for (int64_t tile = lo; tile < hi; tile += kTilePairs) {
     const uint32_t tile_n = (uint32_t)(hi - tile < kTilePairs ? hi - tile : kTilePairs);
+    const bool has_edges = tile + tile_n > n_dst;
     uint32_t key[U], place_in[U];  // place_in: bucket << 16 | rank in the tile's bucket
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -417,8 +426,10 @@ __global__ __launch_bounds__(kPartBlock, PER <= 2 ? 8 : 4) void k_part_scatter(c
         const unsigned long long pr = staged[j];
         const uint32_t to = delta[bucket_of_hash(hash_of_key((uint32_t)(pr >> 32)), n_buckets)] + j;
         pairs[to] = pr + (uint32_t)tile;  // (positions stay below 2^32)
-        went[tile + j] = to;
-        which[tile + j] = (uint16_t)pr;
+        if (has_edges) {
+          *notes.went(tile + j, n_dst) = to;
+          *notes.which_of(tile + j, n_dst) = (uint16_t)pr;
+        }
       }
     }
 #pragma unroll
@@ -430,10 +441,11 @@ __global__ __launch_bounds__(kPartBlock, PER <= 2 ? 8 : 4) void k_part_scatter(c
   }
 }
 
-// One bucket per block: first positions of the bucket's keys through a table in LDS; by_place[p] = that of pair p.
-// (64 registers and 64 KB of LDS: two blocks per CU.)
-__global__ __launch_bounds__(kFirstBlock, 8) void k_part_first(const unsigned long long* __restrict__ pairs, TiledScan<uint32_t> place,
-                                                               uint32_t G, int64_t n_dst, int64_t n_all, uint32_t* __restrict__ by_place,
+// One bucket per block: first positions of the bucket's keys through a table in LDS; by_place[p << shift] = that of pair p.
+// (With shift = 1 by_place is the pairs' own memory: pair p's result takes the place of its position, and nobody else reads
+// or writes pair p.  64 registers and 64 KB of LDS: two blocks per CU.)
+__global__ __launch_bounds__(kFirstBlock, 8) void k_part_first(const unsigned long long* pairs, TiledScan<uint32_t> place,
+                                                               uint32_t G, int64_t n_dst, int64_t n_all, uint32_t* by_place, int shift,
                                                                Ctl* ctl, Publish pub) {
   __shared__ unsigned long long table[kPartSlots];
   __shared__ BucketState st;
@@ -470,12 +482,12 @@ __global__ __launch_bounds__(kFirstBlock, 8) void k_part_first(const unsigned lo
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t i = lo + u * kFirstBlock + threadIdx.x;
-      if (i < hi) by_place[i] = (uint32_t)table[h[u]];
+      if (i < hi) by_place[(size_t)i << shift] = (uint32_t)table[h[u]];
     }
   } else if (st.full == 0) {
     for (uint32_t i = lo + threadIdx.x; i < hi; i += kFirstBlock) {
       const uint32_t key = (uint32_t)(pairs[i] >> 32);
-      by_place[i] = bucket_find(table, kPartSlots, table_slot_of_hash(hash_of_key(key)), key);
+      by_place[(size_t)i << shift] = bucket_find(table, kPartSlots, table_slot_of_hash(hash_of_key(key)), key);
     }
   }
   if (threadIdx.x == 0) bucket_done(ctl, st, n_dst, pub);
@@ -486,8 +498,8 @@ __global__ __launch_bounds__(kFirstBlock, 8) void k_part_first(const unsigned lo
 // list order.  Else first[e] is there already.  A block takes the stretch that the block of the same number scattered
 // (the same XCD, as blocks are dealt to the XCDs in order, and so the columns of by_place that its L2 has seen).
 template <bool GATHER>
-__global__ __launch_bounds__(kPartBlock, 8) void k_uniq_collect(uint32_t* __restrict__ first, const uint32_t* __restrict__ by_place,
-                                                             const uint32_t* __restrict__ went, const uint16_t* __restrict__ which, int64_t m,
+__global__ __launch_bounds__(kPartBlock, 8) void k_uniq_collect(uint32_t* first, const uint32_t* __restrict__ by_place, int shift,
+                                                             TileNotes notes, int64_t m,
                                                              const int64_t* __restrict__ m_dev, int64_t n_dst, RankWord* __restrict__ words,
                                                              uint32_t* __restrict__ block_total,
                                                              uint32_t* __restrict__ block_prefix, Ctl* ctl, Publish pub) {
@@ -507,21 +519,24 @@ __global__ __launch_bounds__(kPartBlock, 8) void k_uniq_collect(uint32_t* __rest
     hi = lo + kCollectStretch < n_all ? lo + kCollectStretch : n_all;
   }
   const int lane = lane_id(), wave = wave_in_block();
+  const int64_t w0 = n_dst >> 6;  // (the words in front have no bits and are not kept)
   uint32_t run = 0;  // (kept by the first wave)
   int flip = 0;
   for (int64_t tile = lo; tile < hi; tile += kTilePairs, flip ^= 1) {
     const uint32_t tile_n = (uint32_t)(hi - tile < kTilePairs ? hi - tile : kTilePairs);
     uint32_t f[U];
+    if (tile + tile_n <= n_dst) continue;  // (no edge in it; the same for the whole block)
     if constexpr (GATHER) {
       uint32_t at[U], to[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const uint32_t j = (uint32_t)(u * kPartBlock) + threadIdx.x;
-        at[u] = went[tile + (j < tile_n ? j : 0u)];
-        to[u] = which[tile + (j < tile_n ? j : 0u)];
+        const int64_t i = tile + (j < tile_n ? j : 0u);
+        at[u] = *notes.went(i, n_dst);
+        to[u] = *notes.which_of(i, n_dst);
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u) f[u] = by_place[at[u]];
+      for (int u = 0; u < U; ++u) f[u] = by_place[(size_t)at[u] << shift];
 #pragma unroll
       for (int u = 0; u < U; ++u) in_order[to[u]] = f[u];  // (a thread behind the tile's end repeats entry 0)
       __syncthreads();
@@ -545,7 +560,7 @@ __global__ __launch_bounds__(kPartBlock, 8) void k_uniq_collect(uint32_t* __rest
       const int64_t i = tile + j;
       const uint64_t b = ballot64(j < tile_n && i >= n_dst && (int64_t)f[u] == i);
       if (lane == 0) {
-        if (j < tile_n) words[i >> 6].bits = b;
+        if (j < tile_n && (i >> 6) >= w0) words[(i >> 6) - w0].bits = b;
         count[flip][u * kWaves + wave] = (uint32_t)__popcll(b);
       }
     }
@@ -554,8 +569,9 @@ __global__ __launch_bounds__(kPartBlock, 8) void k_uniq_collect(uint32_t* __rest
       const uint32_t a = count[flip][2 * lane], b = count[flip][2 * lane + 1];
       const uint32_t incl = wave_incl_scan(a + b);
       const uint32_t j = (uint32_t)lane * 128;
-      if (j < tile_n) words[(tile + j) >> 6].before = run + incl - a - b;
-      if (j + 64 < tile_n) words[((tile + j) >> 6) + 1].before = run + incl - b;
+      const int64_t w = ((tile + j) >> 6) - w0;
+      if (j < tile_n && w >= 0) words[w].before = run + incl - a - b;
+      if (j + 64 < tile_n && w + 1 >= 0) words[w + 1].before = run + incl - b;
       run += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
     }
   }
@@ -619,6 +635,7 @@ __global__ __launch_bounds__(kBlock) void k_uniq_relabel(const int32_t* __restri
     const int64_t e = e0 + u * kBlock;
     if (e < n_dst) src[e] = dst[e];
   }
+  const uint32_t w0 = (uint32_t)(n_dst >> 6);
   uint32_t f[kRelabelUnroll];
 #pragma unroll
   for (int u = 0; u < kRelabelUnroll; ++u) {
@@ -629,7 +646,7 @@ __global__ __launch_bounds__(kBlock) void k_uniq_relabel(const int32_t* __restri
 #pragma unroll
   for (int u = 0; u < kRelabelUnroll; ++u) {
     w[u] = RankWord{0, 0, 0};
-    if ((int64_t)f[u] >= n_dst && (int64_t)f[u] < n_dst + m) w[u] = rank.word[f[u] >> 6];
+    if ((int64_t)f[u] >= n_dst && (int64_t)f[u] < n_dst + m) w[u] = rank.word[(f[u] >> 6) - w0];
   }
 #pragma unroll
   for (int u = 0; u < kRelabelUnroll; ++u) {
@@ -656,14 +673,15 @@ int g_unique_mode = 0;  // COOP_TUNE_UNIQUE: 0 automatic, 1 table in HBM, 2 part
 // kernel that finds the first positions on.  col_local serves as the array of first positions (edge order).
 enum UniqPath { kByFilter, kByPartition, kByTable };
 static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
-                         UniqueWork* w, UniqPath path, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
+                         int32_t* spare, UniqueWork* w, UniqPath path, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
   const int64_t n_all = n_dst + m;
   uint32_t* first = (uint32_t*)col_local;
   w->pub = begin_publish(d_ctl, h_ctl);
   w->path = path;
   uint32_t collect_blocks = (uint32_t)((n_all + kCollectStretch - 1) / kCollectStretch);
-  const uint32_t *by_place = nullptr, *went_c = nullptr;
-  const uint16_t* which_c = nullptr;
+  const uint32_t* by_place = nullptr;
+  int shift = 0;
+  TileNotes notes{};
   w->part_blocks = 0;
   if (path == kByFilter) {
     int log2_buckets = 1;
@@ -678,26 +696,26 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     uint32_t* counts = alloc.get<uint32_t>(n_counts, COOP_TAG_SCRATCH);
     uint32_t* place = alloc.get<uint32_t>(n_counts + 1, COOP_TAG_SCRATCH);
     unsigned long long* pairs = alloc.get<unsigned long long>(n_all, COOP_TAG_SCRATCH);
-    uint32_t* firsts = alloc.get<uint32_t>(n_all, COOP_TAG_SCRATCH);
-    uint32_t* went = alloc.get<uint32_t>(n_all, COOP_TAG_SCRATCH);
-    uint16_t* which = alloc.get<uint16_t>(n_all, COOP_TAG_SCRATCH);
+    notes = TileNotes{first, alloc.get<uint32_t>(kTilePairs, COOP_TAG_SCRATCH), alloc.get<uint16_t>(kTilePairs + m, COOP_TAG_SCRATCH)};
     void* tmp = alloc.get<char>((int64_t)scan_tmp_bytes(n_counts), COOP_TAG_SCRATCH);
     if (alloc.failed) return COOP_E_NOMEM;
+    // the first positions, in the buckets' order: into the caller's spare array, else (8-byte steps instead of 4) over the pairs
+    uint32_t* firsts = spare ? (uint32_t*)spare : (uint32_t*)pairs;
+    shift = spare ? 0 : 1;
     const size_t lds = (size_t)n_buckets * sizeof(uint32_t);
     COOP_LAUNCH(K_PART_COUNT, k_part_count, dim3(G), dim3(kPartBlock), lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets, counts);
     const TiledScan<uint32_t> places = scan_u32_tiled(counts, n_counts, place, tmp, &d_ctl->scan_done, s);
     static_assert(kPartMaxBuckets <= 8 * kPartBlock, "a thread of the scatter looks after eight buckets at most");
     if (n_buckets <= 2 * kPartBlock)
       COOP_LAUNCH(K_PART_SCATTER, k_part_scatter<2>, dim3(G), dim3(kPartBlock), 2 * lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets,
-                  places, pairs, went, which);
+                  places, pairs, notes);
     else
       COOP_LAUNCH(K_PART_SCATTER, k_part_scatter<8>, dim3(G), dim3(kPartBlock), 2 * lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets,
-                  places, pairs, went, which);
-    COOP_LAUNCH(K_PART_FIRST, k_part_first, dim3((unsigned)n_buckets), dim3(kFirstBlock), 0, s, pairs, places, G, n_dst, n_all, firsts, d_ctl, w->pub);
+                  places, pairs, notes);
+    COOP_LAUNCH(K_PART_FIRST, k_part_first, dim3((unsigned)n_buckets), dim3(kFirstBlock), 0, s, pairs, places, G, n_dst, n_all, firsts, shift, d_ctl,
+                w->pub);
     if (hipGetLastError() != hipSuccess) return COOP_E_HIP;  // (a launch that did not happen would leave places or firsts unwritten)
     by_place = firsts;
-    went_c = went;
-    which_c = which;
     collect_blocks = w->part_blocks = G;
   } else {
     // at most half full; an even number of slots (the clear uses 16-byte stores)
@@ -719,10 +737,10 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     // (the table in HBM does not count its keys: there the ranks bring the number of new vertices, and the sizes leave with them)
     const Publish pub = path == kByTable ? w->pub : Publish{};
     if (by_place)
-      COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<true>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, went_c, which_c, m, m_dev, n_dst,
+      COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<true>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, shift, notes, m, m_dev, n_dst,
                   w->words, totals, w->block_prefix, d_ctl, pub);
     else
-      COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<false>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, went_c, which_c, m, m_dev, n_dst,
+      COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<false>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, shift, notes, m, m_dev, n_dst,
                   w->words, totals, w->block_prefix, d_ctl, pub);
   } else if (path == kByTable && launch_publish(w->pub, s) != COOP_OK) {
     return COOP_E_HIP;
@@ -731,9 +749,9 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
 }
 
 int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
-                        UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
+                        int32_t* spare, UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
   const int64_t n_all = n_dst + m;
-  const int64_t n_words = (n_all + 63) / 64;
+  const int64_t n_words = (n_all + 63) / 64 - (n_dst >> 6);
   w->words = alloc.get<RankWord>(n_words, COOP_TAG_SCRATCH);
   if (alloc.failed) return COOP_E_NOMEM;
   // by partition from kFilterMax entries on, as long as a block's counters fit LDS
@@ -744,7 +762,7 @@ int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_gl
   if (whole_rounds > 0 && n_all <= whole_rounds * (pairs_per_bucket + pairs_per_bucket / 8)) w->n_buckets = whole_rounds;
   const bool by_partition = m > 0 && w->n_buckets <= kPartMaxBuckets && g_unique_mode != 1 && (g_unique_mode >= 2 || n_all >= kFilterMax);
   const bool by_filter = !by_partition && g_unique_mode != 1 && n_all > 0 && n_all < kFilterMax;
-  return unique_launch(dst, n_dst, col_global, m, m_dev, col_local, w, by_partition ? kByPartition : by_filter ? kByFilter : kByTable, alloc,
+  return unique_launch(dst, n_dst, col_global, m, m_dev, col_local, spare, w, by_partition ? kByPartition : by_filter ? kByFilter : kByTable, alloc,
                        d_ctl, h_ctl, s);
 }
 
@@ -755,7 +773,7 @@ int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_gl
   if (rc != COOP_OK) return rc;
   if (w->path != kByTable && h_ctl->uniq_overflow != 0) {  // a bucket's table overflowed: once more through the table in HBM
     hipLaunchKernelGGL(k_clear_uniq_overflow, dim3(1), dim3(1), 0, s, d_ctl);
-    rc = unique_launch(dst, n_dst, col_global, m, m_dev, col_local, w, kByTable, alloc, d_ctl, h_ctl, s);
+    rc = unique_launch(dst, n_dst, col_global, m, m_dev, col_local, nullptr, w, kByTable, alloc, d_ctl, h_ctl, s);
     if (rc != COOP_OK) return rc;
     rc = wait_ctl(w->pub, h_ctl, s);
     if (rc != COOP_OK) return rc;

@@ -848,6 +848,51 @@ def test_a_callers_allocator_that_has_just_enough(P, tiny, sampler, kappa):
         assert own.at == own.end
 
 
+@pytest.fixture(scope="module")
+def uneven(P):
+    """400 thousand vertices with lists of 0 to 8 entries."""
+    deg = np.arange(400000) % 9
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]).astype(np.int64))
+    return G(P, indptr, torch.from_numpy(((np.arange(deg.sum()) * 7919) % 400000).astype(np.int32)))
+
+
+# (sampler, fanouts, kappa, COOP_TUNE_DEFER_SIZES, seeds): bytes of an arena that served the call before the dedup kept its
+# entries' places.  All of them go through the partition, with and without an array to spare for the first positions, and
+# with the last seed inside a tile, at the end of one, and in front of few edges.
+ARENAS = {
+    (R.NS, (3, 2), 1, 1, 150000): 61199872, (R.NS, (3, 2), 1, 0, 150000): 51733504, (R.NS, (70,), 1, 1, 200000): 35040000,
+    (R.LABOR0, (3, 2), 1, 1, 150000): 169931008, (R.LABOR0, (3, 2), 1, 0, 150000): 160077056,
+    (R.LABOR0, (3, 2), 16, 1, 150000): 190851840, (R.LABOR0, (3, 2), 16, 0, 150000): 180971008,
+    (R.LABOR0, (70,), 16, 1, 200000): 252900096, (R.NS, (10, 10), 1, 1, 20000): 45686016, (R.NS, (10, 10), 1, 0, 20000): 21292032,
+}
+
+
+@pytest.mark.parametrize("call", list(ARENAS))
+def test_a_program_sizes_its_arena_once(P, uneven, call):
+    sampler, fanouts, kappa, defer, n_seeds = call
+    P.coop_tune(P.COOP_TUNE_DEFER_SIZES, defer)
+    try:
+        compare(P, uneven, np.arange(1, n_seeds + 1), fanouts, sampler, it=5, kappa=kappa, seed=3, arena=P.Arena(ARENAS[call] + 256))
+    finally:
+        P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
+
+
+@pytest.mark.parametrize("n_seeds", [262143, 262144, 262145, 270336, 300000])
+@pytest.mark.parametrize("defer", [1, 0])
+def test_partition_with_few_edges_behind_many_seeds(P, n_seeds, defer):
+    """The tiles of the list that hold no edge, all but the last one or two here, leave nothing for the collecting kernel."""
+    n = 300000
+    deg = (np.arange(n) % 1000 == 7).astype(np.int64)
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]))
+    g = G(P, indptr, torch.from_numpy(((np.arange(deg.sum()) * 7919 + 1) % n).astype(np.int32)))
+    P.coop_tune(P.COOP_TUNE_DEFER_SIZES, defer)
+    try:
+        for fanouts in ((1, 1), (70,)):
+            compare(P, g, np.random.default_rng(n_seeds).permutation(n)[:n_seeds], fanouts, R.NS, seed=n_seeds)
+    finally:
+        P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
+
+
 @pytest.mark.parametrize("chunks", [True, False])
 def test_scratch_cut_from_chunks(P, tiny, chunks):
     """coop_chunk_alloc cuts small scratch buffers from chunks; an allocator that does not hand out buffers of a chunk's size
