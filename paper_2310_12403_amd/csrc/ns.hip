@@ -789,8 +789,9 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
       while (row_cap < 2 * target && row_cap < cap) row_cap <<= 1;
       NsCand* rows = alloc.get<NsCand>(n_dst * (int64_t)row_cap, COOP_TAG_SCRATCH);
       uint32_t* n_cand = alloc.get<uint32_t>(n_dst, COOP_TAG_SCRATCH);
-      // (the queue's counter: zero at the start of the call and whenever the layer is redone)
-      const NsRedo redo{alloc.get<uint32_t>(n_dst, COOP_TAG_SCRATCH), cx.d_piece_count + cx.L + l};
+      // (the queue takes the place of the counts, which have been scanned; its counter is zero at the start of the call and
+      // whenever the layer is redone)
+      const NsRedo redo{(uint32_t*)cnt, cx.d_piece_count + cx.L + l};
       if (alloc.failed) return COOP_E_NOMEM;
       const dim3 grid_redo((unsigned)(n_dst < kNsRedoWaves ? n_dst : kNsRedoWaves));
 #define COOP_NS_BLEND(VEC4)                                                                                                                    \

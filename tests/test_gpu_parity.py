@@ -857,10 +857,11 @@ def uneven(P):
 
 
 # (sampler, fanouts, kappa, COOP_TUNE_DEFER_SIZES, seeds): bytes of an arena that served the call before the dedup kept its
-# entries' places.  All of them go through the partition, with and without an array to spare for the first positions, and
-# with the last seed inside a tile, at the end of one, and in front of few edges.
+# entries' places and NS with c > 0 queued the lists left over.  All of them go through the partition, with and without an
+# array to spare for the first positions.
 ARENAS = {
     (R.NS, (3, 2), 1, 1, 150000): 61199872, (R.NS, (3, 2), 1, 0, 150000): 51733504, (R.NS, (70,), 1, 1, 200000): 35040000,
+    (R.NS, (3, 2), 16, 1, 150000): 313127168, (R.NS, (3, 2), 16, 0, 150000): 303671040, (R.NS, (10, 10), 16, 0, 20000): 83001088,
     (R.LABOR0, (3, 2), 1, 1, 150000): 169931008, (R.LABOR0, (3, 2), 1, 0, 150000): 160077056,
     (R.LABOR0, (3, 2), 16, 1, 150000): 190851840, (R.LABOR0, (3, 2), 16, 0, 150000): 180971008,
     (R.LABOR0, (70,), 16, 1, 200000): 252900096, (R.NS, (10, 10), 1, 1, 20000): 45686016, (R.NS, (10, 10), 1, 0, 20000): 21292032,
