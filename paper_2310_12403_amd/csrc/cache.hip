@@ -413,7 +413,7 @@ extern "C" int coop_cache_create(int64_t capacity_rows, int64_t n_vertices, int3
   c->free_list = alloc.get<int32_t>(capacity_rows, COOP_TAG_OUTPUT);
   c->slot_i = alloc.get<int32_t>(max_ids, COOP_TAG_OUTPUT);
   c->hit_bits = alloc.get<uint64_t>((max_ids + 63) / 64, COOP_TAG_OUTPUT);
-  c->rank_h = alloc.get<uint32_t>(max_ids, COOP_TAG_OUTPUT);
+  c->rank_h = alloc.get<uint32_t>((max_ids + 63) / 64, COOP_TAG_OUTPUT);  // (one per word of hit_bits)
   c->order = alloc.get<OrderEntry>(max_ids, COOP_TAG_OUTPUT);
   c->scan_tmp = alloc.get<char>((int64_t)scan_tmp_bytes(max_ids), COOP_TAG_OUTPUT);
   c->sel = alloc.get<SelShared>(1, COOP_TAG_OUTPUT);

@@ -307,6 +307,19 @@ def test_cache_selects_among_more_stamps_than_one_round_reads(P):
     cache.close()
 
 
+@pytest.mark.parametrize("max_ids", [4096, 100000])
+def test_cache_created_in_an_arena_of_a_stated_size(P, max_ids):
+    """What a cache takes from the allocator: its tables, 16 bytes and a bit per id of a call, and a few kilobytes."""
+    import ctypes as C
+    cap, n, dim = 1000, 5000, 16
+    sizes = [4 * n, 4 * cap, 8 * cap, 4 * cap * dim, 4 * cap, 4 * max_ids, max_ids // 8, 4 * max_ids, 8 * max_ids,
+             16 * (-(-max_ids // 2048) + 2), 1024, 256]
+    arena = P.Arena(sum(-(-s // 256) * 256 for s in sizes) + 256)
+    h = C.c_void_p()
+    assert P.lib().coop_cache_create(cap, n, dim, P.COOP_F32, max_ids, arena.fn, arena.ctx, None, C.byref(h)) == 0
+    assert P.lib().coop_cache_free(h) == 0
+
+
 def test_cache_on_sampled_batches_with_kappa(P, medium):
     """Input sets of consecutive dependent LABOR-0 batches through the cache: misses equal the oracle's on every
     iteration, and a larger kappa lowers the miss count (temporal locality of Sec. 4.2)."""
