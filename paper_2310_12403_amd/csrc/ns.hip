@@ -114,18 +114,13 @@ constexpr uint32_t kNsMaxSelect = 1024;  // largest fanout for which a longer li
 constexpr int64_t kNsQueueFrom = 32768;  // destinations from which the long lists are queued for the first waves
 constexpr int kNsLongDefault = 2048;
 int g_ns_long_min = kNsLongDefault;      // COOP_TUNE_NS_LONG_LIST: lists longer than this are queued (0 = none)
-constexpr uint32_t kNsRedo = 0xFFFFFFFFu;  // candidate count of a destination that the two-kernel path leaves to k_ns_fill
-// The two-kernel path's queue of such destinations (about one in 10^4; a kernel over all destinations that looked for them
-// took 14 us per layer).
-struct NsRedo {
-  uint32_t* list;
-  uint32_t* n;
-  __device__ __forceinline__ void add(int64_t w, uint32_t* __restrict__ n_cand) const {  // one lane
-    n_cand[w] = kNsRedo;
-    list[atomicAdd(n, 1u)] = (uint32_t)w;  // (a destination is queued once at most: by k_ns_collect, or else by k_ns_select)
-  }
-};
-constexpr int64_t kNsRedoWaves = 1024;
+constexpr uint32_t kNsRedo = 0xFFFFFFFFu;  // candidate count of a destination that the two-kernel path leaves to k_ns_redo
+// Such destinations, about one in 10^4, are found by their marks in n_cand.  A wave looks at as many marks as leave at least
+// kNsRedoWaves waves, up to one per lane: a wave for each mark costs 0.2 ns a mark (675 thousand destinations: 451 us for the
+// traversal and this, against 314).  Where one neighbour occurs many times over, every list can be among them, so there is no
+// queue (an atomic per list on its counter, one after the other) and no bound on the waves: 100 thousand such lists 1.86 ms,
+// as with a wave each, against 9.3 with a queue and 1,024 waves.
+constexpr int64_t kNsRedoWaves = 16384;
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 constexpr int kNsGroups = 4;  // 16-byte groups per lane and step of the fast traversal
@@ -148,6 +143,10 @@ struct NsQueue {
 // rule it out; the survivors of the integer bounds are evaluated 64 at a time.
 // STAGED (with c > 0): the exact evaluation is left to a later kernel; everything that the fp32 blend cannot rule out
 // is stored as a candidate (variate 0).
+// (not inlined: see k_ns_redo)
+__device__ __attribute__((noinline)) uint32_t ns_exact_variate(uint32_t u1, uint32_t u2, double cw, double sw) {
+  return kit_phi_to_u32(__builtin_fma(cw, kit_phi_inv_u32(u1), sw * kit_phi_inv_u32(u2)));
+}
 template <bool BLEND, bool VEC4, bool STAGED = false>
 __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_indices, int64_t beg, uint32_t d, uint32_t bound,
                                                const NsBlendThr& bt, const VariateParams& vp, uint32_t sigma_a, uint32_t sigma_b,
@@ -182,7 +181,7 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
         if constexpr (STAGED) {
           in = true;
         } else {
-          R = kit_phi_to_u32(__builtin_fma(vp.cw, kit_phi_inv_u32(u1), vp.sw * kit_phi_inv_u32(u2)));
+          R = ns_exact_variate(u1, u2, vp.cw, vp.sw);
           in = R <= bound;
         }
       }
@@ -389,9 +388,9 @@ __device__ __forceinline__ int64_t ns_list_of(int64_t n_dst, int waves_per_block
 //
 // The degree distribution is heavy-tailed and a wave takes a whole list, so the lists longer than long_min entries
 // are not left where the destination order puts them (a hub that starts late would keep the kernel waiting for one
-// wave): k_ns_count queues them, the first long_blocks blocks of the grid stride over the queue (its length is read from
-// device memory; every wave ends after a bounded number of steps), and the other blocks take the destinations in order
-// and skip the queued ones.
+// wave): k_ns_count queues them, the waves of the first long_blocks blocks of the grid take one queued list each (the
+// queue's length is read from device memory), and the other blocks take the destinations in order and skip the queued
+// ones.
 template <bool BLEND, bool VEC4>
 __device__ __forceinline__ void ns_fill_one(int64_t w, int wib, uint32_t* lds_words, NsQueue* queue, const int32_t* __restrict__ g_indices,
                                             const NsRecord* __restrict__ rec, const NsBlendThr* __restrict__ bthr, uint32_t k, uint32_t cap,
@@ -449,7 +448,7 @@ __device__ __forceinline__ void ns_fill_one(int64_t w, int wib, uint32_t* lds_wo
   ns_rank_write(n_c, k, cand_key, cand_k, cand_t, o, beg, col_global, eid);
 }
 
-template <bool BLEND, bool VEC4>
+template <bool VEC4>
 __global__ __launch_bounds__(kBlock) void k_ns_fill(const int32_t* __restrict__ g_indices,
                                                     const NsRecord* __restrict__ rec, const NsBlendThr* __restrict__ bthr,
                                                     int64_t n_dst, uint32_t k,
@@ -459,25 +458,38 @@ __global__ __launch_bounds__(kBlock) void k_ns_fill(const int32_t* __restrict__ 
                                                     uint32_t long_min, const uint32_t* __restrict__ long_list,
                                                     const uint32_t* __restrict__ n_long, int long_blocks) {
   extern __shared__ __align__(16) uint32_t lds_words[];  // per wave: cap 64-bit keys, cap keep flags, cap vertex ids
-  NsQueue* queues = reinterpret_cast<NsQueue*>(lds_words + (size_t)waves_per_block * cap * 4);  // (with c > 0; behind the candidates)
   const int wib = uniform_wave_in_block();
   if (wib >= waves_per_block) return;
-  NsQueue* queue = &queues[BLEND ? wib : 0];
-  if constexpr (BLEND) {  // the destinations queued in long_list, by all waves of the grid
-    int64_t n = (int64_t)*n_long;
-    if (n > n_dst) n = n_dst;
-    for (int64_t q = (int64_t)blockIdx.x * waves_per_block + wib; q < n; q += (int64_t)gridDim.x * waves_per_block) {
-      const int64_t w = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)long_list[q]);
-      if (w < n_dst)
-        ns_fill_one<BLEND, VEC4>(w, wib, lds_words, queue, g_indices, rec, bthr, k, cap, vp, eptr, col_global, eid, edge_limit, ctl, 0xFFFFFFFFu);
-      __builtin_amdgcn_wave_barrier();
-    }
-  } else {
-    bool queued;
-    const int64_t w = ns_list_of(n_dst, waves_per_block, wib, long_list, n_long, long_blocks, &queued);
-    if (w < 0) return;
-    ns_fill_one<BLEND, VEC4>(w, wib, lds_words, queue, g_indices, rec, bthr, k, cap, vp, eptr, col_global, eid, edge_limit, ctl,
-                             !queued && long_min != 0 ? long_min : 0xFFFFFFFFu);
+  bool queued;
+  const int64_t w = ns_list_of(n_dst, waves_per_block, wib, long_list, n_long, long_blocks, &queued);
+  if (w < 0) return;
+  ns_fill_one<false, VEC4>(w, wib, lds_words, nullptr, g_indices, rec, bthr, k, cap, vp, eptr, col_global, eid, edge_limit, ctl,
+                           !queued && long_min != 0 ? long_min : 0xFFFFFFFFu);
+}
+
+// c > 0: the destinations that the two kernels below leave over.  A wave looks at 2^lists_log2 marks at once.  (Six waves per
+// SIMD, 80 registers and some scratch memory, and the exact blend as a function in the place of 31 copies: with three
+// waves the lists took 3.0 ms in the place of 1.86.)
+template <bool VEC4>
+__global__ __launch_bounds__(kWave, 6) void k_ns_redo(const int32_t* __restrict__ g_indices,
+                                                    const NsRecord* __restrict__ rec, const NsBlendThr* __restrict__ bthr,
+                                                    int64_t n_dst, uint32_t k,
+                                                    uint32_t cap, int waves_per_block, VariateParams vp,
+                                                    const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
+                                                    int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl,
+                                                    const uint32_t* __restrict__ n_cand, int lists_log2) {
+  extern __shared__ __align__(16) uint32_t lds_words[];  // per wave as above, and a queue behind all of them
+  NsQueue* queues = reinterpret_cast<NsQueue*>(lds_words + (size_t)waves_per_block * cap * 4);
+  const int wib = uniform_wave_in_block();
+  if (wib >= waves_per_block) return;
+  const int64_t w0 = ((int64_t)blockIdx.x * waves_per_block + wib) << lists_log2;
+  const int lane = lane_id();
+  uint64_t left = ballot64(lane < (1 << lists_log2) && w0 + lane < n_dst && n_cand[w0 + lane] == kNsRedo);
+  while (left != 0) {
+    const int64_t w = w0 + __builtin_ctzll(left);
+    left &= left - 1;
+    ns_fill_one<true, VEC4>(w, wib, lds_words, &queues[wib], g_indices, rec, bthr, k, cap, vp, eptr, col_global, eid, edge_limit, ctl, 0xFFFFFFFFu);
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -486,7 +498,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_fill(const int32_t* __restrict__ 
 // the traversal and is wanted for a few dozen candidates per list only.  So the traversal kernel stops at the fp32
 // filter and leaves what passes, (list position, vertex) pairs, in a row of row_cap entries per destination; a second
 // kernel evaluates those exactly, drops the ones above the bound and selects.  A destination whose row overflows, or
-// that ends up with fewer than k candidates (about one in 10^4), is marked and done again by k_ns_fill, which adjusts
+// that ends up with fewer than k candidates (about one in 10^4), is marked and done again by k_ns_redo, which adjusts
 // the bound.
 struct NsCand { uint32_t j; int32_t t; };
 
@@ -495,7 +507,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_collect(const int32_t* __restrict
                                                        const NsBlendThr* __restrict__ bthr, int64_t n_dst, uint32_t k, uint32_t cap,
                                                        int waves_per_block, VariateParams vp, const int64_t* __restrict__ eptr,
                                                        int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit,
-                                                       NsCand* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand, NsRedo redo,
+                                                       NsCand* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand,
                                                        uint32_t long_min, const uint32_t* __restrict__ long_list,
                                                        const uint32_t* __restrict__ n_long, int long_blocks) {
   extern __shared__ __align__(16) uint32_t lds_words[];
@@ -528,7 +540,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_collect(const int32_t* __restrict
   __builtin_amdgcn_wave_barrier();
   __threadfence_block();
   if (n_c < k || n_c > row_cap || n_c > cap) {  // (too few even before the exact test, or no room)
-    if (lane == 0) redo.add(w, n_cand);
+    if (lane == 0) n_cand[w] = kNsRedo;
     return;
   }
   NsCand* row = rows + (size_t)w * row_cap;
@@ -540,7 +552,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
                                                       int waves_per_block, VariateParams vp, const int64_t* __restrict__ eptr,
                                                       int32_t* __restrict__ col_global, int64_t* __restrict__ eid,
                                                       const NsCand* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand,
-                                                      NsRedo redo, const NsBlendThr* __restrict__ bthr) {
+                                                      const NsBlendThr* __restrict__ bthr) {
   extern __shared__ __align__(16) uint32_t lds_words[];
   const int wib = uniform_wave_in_block();
   if (wib >= waves_per_block) return;
@@ -548,7 +560,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
   const int64_t w = (int64_t)blockIdx.x * waves_per_block + wib;
   if (w >= n_dst) return;
   const uint32_t n = n_cand[w];
-  if (n == 0 || n == kNsRedo) return;  // done by the collecting kernel, or left to k_ns_fill
+  if (n == 0 || n == kNsRedo) return;  // done by the collecting kernel, or left to k_ns_redo
   const NsRecord g = rec[w];
   uint64_t* cand_key = reinterpret_cast<uint64_t*>(lds_words + (size_t)wib * cap * 4);
   uint32_t* cand_k = lds_words + (size_t)wib * cap * 4 + 2 * cap;
@@ -583,7 +595,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
     // e_k must lie safely below what the traversal's filter let through, or a neighbour that it dropped could belong
     // to the k smallest
     if (!(e_k >= -5.0f && e_k <= 5.0f) || !(e_k + m <= bthr[w].lim2 - m)) {
-      if (lane == 0) redo.add(w, n_cand);
+      if (lane == 0) n_cand[w] = kNsRedo;
       return;
     }
     const bool in = has && est < e_k - m;
@@ -638,7 +650,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
     n_c += (uint32_t)__popcll(mask);
   }
   if (n_c < k) {
-    if (lane == 0) redo.add(w, n_cand);
+    if (lane == 0) n_cand[w] = kNsRedo;
     return;
   }
   ns_rank_write(n_c, k, cand_key, cand_k, cand_t, eptr[w], g.beg, col_global, eid);
@@ -789,24 +801,22 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
       while (row_cap < 2 * target && row_cap < cap) row_cap <<= 1;
       NsCand* rows = alloc.get<NsCand>(n_dst * (int64_t)row_cap, COOP_TAG_SCRATCH);
       uint32_t* n_cand = alloc.get<uint32_t>(n_dst, COOP_TAG_SCRATCH);
-      // (the queue takes the place of the counts, which have been scanned; its counter is zero at the start of the call and
-      // whenever the layer is redone)
-      const NsRedo redo{(uint32_t*)cnt, cx.d_piece_count + cx.L + l};
       if (alloc.failed) return COOP_E_NOMEM;
-      const dim3 grid_redo((unsigned)(n_dst < kNsRedoWaves ? n_dst : kNsRedoWaves));
+      int lists_log2 = 0;
+      while (lists_log2 < 6 && (n_dst >> (lists_log2 + 1)) >= kNsRedoWaves) ++lists_log2;
+      const dim3 grid_redo(blocks_for(n_dst, (int64_t)wpb << lists_log2));
 #define COOP_NS_BLEND(VEC4)                                                                                                                    \
-  COOP_LAUNCH(K_NS_FILL, k_ns_collect<VEC4>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, rows, row_cap, n_cand, redo, long_min,          \
+  COOP_LAUNCH(K_NS_FILL, k_ns_collect<VEC4>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, rows, row_cap, n_cand, long_min,                \
               (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);                                                               \
   COOP_LAUNCH(K_NS_SELECT, k_ns_select, grid, dim3(wpb * kWave), shmem, s, rec, n_dst, k, cap, wpb, vp, blk->indptr, blk->col_global, blk->eid, \
-              (const NsCand*)rows, row_cap, n_cand, redo, (const NsBlendThr*)bthr);                                                            \
-  COOP_LAUNCH(K_NS_FILL, (k_ns_fill<true, VEC4>), grid_redo, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, 0u,                           \
-              (const uint32_t*)redo.list, (const uint32_t*)redo.n, (int)grid_redo.x)
+              (const NsCand*)rows, row_cap, n_cand, (const NsBlendThr*)bthr);                                                                  \
+  COOP_LAUNCH(K_NS_FILL, k_ns_redo<VEC4>, grid_redo, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, (const uint32_t*)n_cand, lists_log2)
       if (cx.vec4) { COOP_NS_BLEND(true); } else { COOP_NS_BLEND(false); }
 #undef COOP_NS_BLEND
     } else {
-      if (cx.vec4) COOP_LAUNCH(K_NS_FILL, (k_ns_fill<false, true>), grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
+      if (cx.vec4) COOP_LAUNCH(K_NS_FILL, k_ns_fill<true>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
                                (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
-      else COOP_LAUNCH(K_NS_FILL, (k_ns_fill<false, false>), grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
+      else COOP_LAUNCH(K_NS_FILL, k_ns_fill<false>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
                        (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
     }
 #undef COOP_NS_ARGS

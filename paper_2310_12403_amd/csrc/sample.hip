@@ -20,7 +20,7 @@ __global__ __launch_bounds__(kBlock) void k_begin_call(const int32_t* __restrict
   if (i < (kTallyLines + 1) * 16) reinterpret_cast<DeviceCtl*>(ctl)->tally.word[i] = 0;
   if (i == 0) {
     *ctl = Ctl{};
-    for (int l = 0; l < 2 * L; ++l) piece_count[l] = 0;
+    for (int l = 0; l < L; ++l) piece_count[l] = 0;
   }
 }
 
@@ -79,10 +79,9 @@ int g_defer_sizes = 1;         // COOP_TUNE_DEFER_SIZES
 int g_enum_degree = 8192;      // COOP_TUNE_ENUM_DEGREE
 
 // puts back what a LABOR-0 pass at layer l changed in the control data, before the pass is run again
-__global__ void k_reset_layer(Ctl* ctl, uint32_t* piece_count, uint32_t* redo_count) {
+__global__ void k_reset_layer(Ctl* ctl, uint32_t* piece_count) {
   ctl->cand_overflow = 0;
   *piece_count = 0;
-  *redo_count = 0;
 }
 
 }  // namespace coop
@@ -172,7 +171,7 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
   Ctl* h_ctl = &h_pad->ctl;
   cx.h_ctl = h_ctl;
   cx.d_ctl = (Ctl*)alloc.get<DeviceCtl>(1, COOP_TAG_SCRATCH);
-  cx.d_piece_count = alloc.get<uint32_t>(2 * L, COOP_TAG_SCRATCH);
+  cx.d_piece_count = alloc.get<uint32_t>(L, COOP_TAG_SCRATCH);
   int32_t* seed_copy = alloc.get<int32_t>(n_seeds, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
   const int64_t n_begin = n_seeds > (kTallyLines + 1) * 16 ? n_seeds : (kTallyLines + 1) * 16;
@@ -235,7 +234,7 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
         done = true;
       } else {
         labor = labor_before;
-        hipLaunchKernelGGL(k_reset_layer, dim3(1), dim3(1), 0, s, cx.d_ctl, cx.d_piece_count + l, cx.d_piece_count + L + l);
+        hipLaunchKernelGGL(k_reset_layer, dim3(1), dim3(1), 0, s, cx.d_ctl, cx.d_piece_count + l);
         blk = coop_block{};
         blk.n_dst = n_dst;
         blk.dst_ids = const_cast<int32_t*>(dst);

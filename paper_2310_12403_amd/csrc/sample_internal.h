@@ -14,8 +14,7 @@ struct SampleCtx {
   Alloc* alloc;
   Ctl* d_ctl;
   Ctl* h_ctl;
-  uint32_t* d_piece_count;  // [2 L] zeroed at the start of the call: pieces queued by the LABOR-0 pass that ran at layer l (NS:
-                            // long lists queued), and from L on the destinations that NS with c > 0 leaves to the one-kernel path
+  uint32_t* d_piece_count;  // [L] zeroed at the start of the call: pieces queued by the LABOR-0 pass that ran at layer l (NS: long lists queued)
   const int32_t* fanouts;
   int L;
   int sampler;

@@ -937,7 +937,7 @@ def test_scratch_cut_from_chunks(P, tiny, chunks):
 
 def test_ns_lists_left_to_the_one_kernel_path(P):
     """c > 0: lists in which one neighbour occurs 200 times tie with themselves beyond what a row of candidates holds, so all
-    3,000 of them go through the queue of the one-kernel path, several per wave; next to lists that do not."""
+    3,000 of them are left to the one-kernel path; next to lists that are not."""
     n, big = 6000, 3000
     rng = np.random.default_rng(5)
     lists = [np.concatenate([np.full(200, (7 * v) % n), rng.integers(0, n, 20)]) if v < big else rng.integers(0, n, 30) for v in range(n)]
@@ -949,6 +949,28 @@ def test_ns_lists_left_to_the_one_kernel_path(P):
             compare(P, g, rng.permutation(n)[:5000], (10, 5), R.NS, it=5, kappa=16, seed=3)
         finally:
             P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
+
+
+@pytest.mark.parametrize("aligned", [True, False])
+def test_ns_lists_left_over_looked_for_several_at_a_time(P, aligned):
+    """As above with more destinations, where a wave looks at one, two or four marks: none, one or all of them set, and fewer
+    at the end."""
+    n = 65600
+    rng = np.random.default_rng(6)
+    v = np.arange(n)
+    big = (v % 64 < 5) | (v % 7 == 0)
+    deg = np.where(big, 90, 3)
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    indices = rng.integers(0, n, int(deg.sum())).astype(np.int32)
+    at = indptr[:-1][big][:, None] + np.arange(80)
+    indices[at] = ((7 * v[big]) % n)[:, None]
+    g = G(P, torch.from_numpy(indptr), torch.from_numpy(indices))
+    if not aligned:
+        base = torch.empty(len(indices) + 1, dtype=torch.int32, device="cuda")
+        base[1:] = g.indices_d
+        g.graph = P.coop_graph_load(g.indptr_d, base[1:], P.COOP_VALIDATE)
+    for size in (32767, 32768, 65535, 65537) if aligned else (32769,):
+        compare(P, g, v[:size], (10,), R.NS, it=5, kappa=16, seed=size)
 
 
 def test_ns_count_in_wide_blocks(P):
