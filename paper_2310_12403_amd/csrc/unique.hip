@@ -139,7 +139,10 @@ constexpr int kFilterBlock = 1024;
 constexpr uint32_t kFilterSlots = 4096;
 constexpr uint32_t kFilterFull = kFilterSlots / 4 * 3 - kFilterBlock;  // distinct keys at which a bucket gives up
 constexpr uint32_t kFilterList = 256;                   // positions that a wave can note
-constexpr int64_t kFilterPairs = 1024;                  // mean entries of a bucket (64 per wave)
+constexpr int64_t kFilterPairs = 1024;                  // most entries of a bucket in the mean (64 per wave) ...
+// ... and at least four buckets: the first wave looks at up to 512 entries of a list of two parts, and with two buckets noted
+// 256 to 270 of them on ordinary lists of 1,500 to 2,048 entries, one more than it can (15 us in the place of 12)
+constexpr int kFilterLeastLog2 = 2;
 constexpr int64_t kFilterMax = 262144;                  // 256 buckets at most: one per CU
 __device__ __forceinline__ uint32_t filter_hash(uint32_t key) { return key * 0x9E3779B9u; }
 
@@ -684,7 +687,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
   TileNotes notes{};
   w->part_blocks = 0;
   if (path == kByFilter) {
-    int log2_buckets = 1;
+    int log2_buckets = kFilterLeastLog2;
     while (((int64_t)kFilterPairs << log2_buckets) < n_all) ++log2_buckets;
     COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_filter, dim3(1u << log2_buckets), dim3(kFilterBlock), 0, s, dst, n_dst, col_global, m, m_dev, log2_buckets,
                 first, d_ctl, w->pub);
