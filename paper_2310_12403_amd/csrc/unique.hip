@@ -132,7 +132,8 @@ __device__ __forceinline__ void bucket_done(Ctl* ctl, const BucketState& st, int
 // ---- first positions of a short list -----------------------------------------------------------------------------
 // Block b reads the whole list and notes, wave by wave, the positions whose key hashes to bucket b; those keys go into the
 // block's table, and the edges among them get what the table then says.  One launch in the place of clearing a table,
-// inserting and looking up in HBM, and no atomic leaves the block.  Reading everything in every block is what it pays for
+// inserting and looking up in HBM, and no key's atomic leaves the block
+// (which counts itself once, in bucket_done).  Reading everything in every block is what it pays for
 // that, three vector instructions per key, which is why it ends at kFilterMax entries.  188 thousand entries 17 us (clear,
 // insert and look up in HBM: 25), 11 to 58 thousand 10 to 12 us (10 to 16).
 constexpr int kFilterBlock = 1024;
@@ -235,17 +236,43 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
 #pragma unroll
     for (int v = 0; v < V; ++v)
       if (pair[v] != kEmptySlot && (uint32_t)pair[v] >= nd) first[(uint32_t)pair[v] - nd] = (uint32_t)table[h[v]];
-  } else {  // (a vertex that very many lists keep): the whole list is read again, twice
-    for (uint32_t i = threadIdx.x; i < n; i += kFilterBlock) {
-      const uint32_t key = key_at(i), hash = filter_hash(key);
-      if (hash - low < width && lds_read(&st.full) == 0)
-        bucket_insert(table, kFilterSlots, kFilterFull, slot(hash), ((unsigned long long)key << 32) | i, nd, &st);
-    }
+  } else {
+    // a vertex that very many lists keep: the whole list is read again, twice, in the same steps.  (222 thousand entries, one
+    // in 72 the same: 76 us; with one key per thread and step 158, in a table in HBM 51 and two launches more.  All of 130
+    // thousand edges from one vertex: 165, 149 and 1,270.)
+    auto each = [&](const int32_t* __restrict__ p, uint32_t len, auto&& take) {
+      const uint32_t groups = (len + 3) / 4;
+      for (uint32_t g0 = 0; g0 < groups; g0 += U * kFilterBlock) {
+        u32x4 key[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+          const uint32_t g = g0 + u * kFilterBlock + threadIdx.x;
+          key[u] = reinterpret_cast<const u32x4*>(p)[g < groups ? g : groups - 1];
+        }
+        uint32_t flags = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u)
+#pragma unroll
+          for (uint32_t e = 0; e < 4; ++e) flags |= filter_hash(key[u][e]) - low < width ? 1u << (4 * u + e) : 0u;
+        for (; flags != 0; flags &= flags - 1) {
+          const uint32_t bit = (uint32_t)__builtin_ctz(flags);
+          uint32_t k = 0;
+#pragma unroll
+          for (uint32_t b = 0; b < 4 * U; ++b) k = bit == b ? key[b / 4][b % 4] : k;
+          const uint32_t i = (g0 + (bit >> 2) * kFilterBlock + threadIdx.x) * 4 + (bit & 3u);
+          if (i < len) take(i, k);
+        }
+      }
+    };
+    auto insert = [&](uint32_t i, uint32_t key) {
+      if (lds_read(&st.full) == 0)
+        bucket_insert(table, kFilterSlots, kFilterFull, slot(filter_hash(key)), ((unsigned long long)key << 32) | i, nd, &st);
+    };
+    each(dst, nd, insert);
+    each(col, n - nd, [&](uint32_t i, uint32_t key) { insert(nd + i, key); });
     __syncthreads();
-    for (uint32_t i = nd + threadIdx.x; i < n && st.full == 0; i += kFilterBlock) {
-      const uint32_t key = key_at(i), hash = filter_hash(key);
-      if (hash - low < width) first[i - nd] = bucket_find(table, kFilterSlots, slot(hash), key);
-    }
+    if (st.full == 0)
+      each(col, n - nd, [&](uint32_t i, uint32_t key) { first[i] = bucket_find(table, kFilterSlots, slot(filter_hash(key)), key); });
   }
   if (threadIdx.x == 0) bucket_done(ctl, st, n_dst, pub);
 }

@@ -828,6 +828,18 @@ def test_frontier_dedup_of_short_lists(P, shape):
         assert "unique_filter" in ran or size > 100000, (size, ran.keys())
 
 
+@pytest.mark.parametrize("size", [4096, 37000])
+def test_frontier_dedup_of_short_lists_with_a_hub(P, size):
+    """One source in 36 is the same vertex, among others that differ: in the longer list more of them than a wave can note (16
+    waves note 256 each), so that one block of many goes over the whole list again, of which the last groups are ragged."""
+    n = 300000
+    lists = np.random.default_rng(size).integers(0, n, (n, 6)).astype(np.int32)
+    lists[::6, 0] = 5
+    g = G(P, torch.arange(0, 6 * n + 1, 6, dtype=torch.int64), torch.from_numpy(lists.reshape(-1)))
+    for seeds in (np.random.default_rng(1).permutation(n)[:size], np.arange(0, 6 * 7001, 6)[:size - 1]):
+        compare(P, g, seeds, (6,), R.NS, seed=size)
+
+
 @pytest.mark.parametrize("sampler,kappa", [(R.LABOR0, 1), (R.LABOR0, 4), (R.NS, 1), (R.NS, 4)])
 def test_a_callers_allocator_that_has_just_enough(P, tiny, sampler, kappa):
     """A caller's own allocator is asked for what a call uses and no more: one that has exactly the bytes that the same call
