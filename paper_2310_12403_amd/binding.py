@@ -28,7 +28,7 @@ class _CArena(C.Structure):
 
 
 class _CChunks(C.Structure):
-    _fields_ = [("from_fn", C.c_void_p), ("ctx", C.c_void_p), ("chunk_bytes", C.c_size_t), ("at", C.c_void_p), ("left", C.c_size_t)]
+    _fields_ = [("from_fn", ALLOC_FN), ("ctx", C.c_void_p), ("chunk_bytes", C.c_size_t), ("at", C.c_void_p), ("left", C.c_size_t)]
 
 
 class _CCacheState(C.Structure):
@@ -218,8 +218,11 @@ class _TorchAllocator:
                 return None
 
         self.fn_obj = ALLOC_FN(_alloc)
+        self._address()
+
+    def _address(self):  # what the library is given
         self.fn = C.cast(self.fn_obj, C.c_void_p)
-        self.ctx = C.c_void_p()
+        self.ctx = None
 
     def view(self, ptr, count, dtype):
         if count == 0:
@@ -235,11 +238,10 @@ class _SampleAllocator(_TorchAllocator):
     tensor through this callback takes 3 to 4 us (few_seeds of perf/cases.py, 26 callbacks less: 174 -> 132 us)."""
     CHUNK = 1020 << 10  # with the callback's 256 bytes of room for alignment below torch's line for small blocks (1 MB)
 
-    def __init__(self, device):
-        super().__init__(device)
-        self.chunks = _CChunks(self.fn.value, None, self.CHUNK, None, 0)
+    def _address(self):
+        self.chunks = _CChunks(self.fn_obj, None, self.CHUNK, None, 0)
         self.fn = lib().coop_chunk_alloc_address
-        self.ctx = C.c_void_p(C.addressof(self.chunks))
+        self.ctx = C.addressof(self.chunks)
 
 
 class Block:

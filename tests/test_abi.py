@@ -86,13 +86,13 @@ def test_chunk_allocator():
         return 0x100000 * len(asked) if nbytes <= limit else None
 
     fn = binding.ALLOC_FN(alloc)
-    c = binding._CChunks(C.cast(fn, C.c_void_p).value, None, 4096, None, 0)
+    c = binding._CChunks(fn, None, 4096, None, 0)
     limit = 1 << 20
     got = [L.coop_chunk_alloc(C.byref(c), n, t) for n, t in ((10, 1), (1024, 1), (1025, 1), (10, 0), (1000, 1), (1000, 1), (600, 1), (1024, 1))]
     assert asked == [(4096, 1), (1025, 1), (10, 0), (4096, 1)]
     assert got == [0x100000, 0x100100, 0x200000, 0x300000, 0x100500, 0x100900, 0x100D00, 0x400000]
     limit = 2000
-    c = binding._CChunks(C.cast(fn, C.c_void_p).value, None, 4096, None, 0)
+    c = binding._CChunks(fn, None, 4096, None, 0)
     del asked[:]
     assert [L.coop_chunk_alloc(C.byref(c), n, 1) for n in (10, 1024)] == [0x200000, 0x400000]
     assert asked == [(4096, 1), (10, 1), (4096, 1), (1024, 1)]

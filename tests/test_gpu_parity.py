@@ -937,7 +937,7 @@ def test_scratch_cut_from_chunks(P, tiny, chunks):
                 return inner(ctx, nbytes, tag) if chunks or nbytes != 1020 << 10 else None
 
             self.limited = binding.ALLOC_FN(alloc)
-            self.chunks.from_fn = C.cast(self.limited, C.c_void_p).value
+            self.chunks.from_fn = self.limited
 
     for sampler, kappa in ((R.LABOR0, 4), (R.NS, 1)):
         al = Limited()
