@@ -468,12 +468,12 @@ __global__ __launch_bounds__(kBlock) void k_cache_export(const int32_t* __restri
 
 // entry i of the exported lists goes to slot i; its row is read again from the backing table
 template <int VB>
-__global__ __launch_bounds__(kBlock) void k_cache_import(const char* __restrict__ table, int64_t table_rows, RowShape sh,
+__global__ __launch_bounds__(kBlock) void k_cache_import(int64_t block0, const char* __restrict__ table, int64_t table_rows, RowShape sh,
                                                          const int32_t* __restrict__ vertices, const uint64_t* __restrict__ stamps,
                                                          int64_t n, int64_t n_vertices, char* __restrict__ rows,
                                                          int32_t* __restrict__ slot_of, int32_t* __restrict__ vertex_of,
                                                          uint64_t* __restrict__ stamp, CacheCtl* ctl) {
-  const BlockItems items((int64_t)blockIdx.x * kBlock, sh.vecs);
+  const BlockItems items((block0 + (int64_t)blockIdx.x) * kBlock, sh.vecs);
   uint32_t item;
   const int64_t i = items.row_of(threadIdx.x, sh, &item);
   if (i >= n) return;
@@ -541,10 +541,12 @@ extern "C" int coop_cache_import(coop_cache* c, const void* table, int64_t table
   reset(state->size);
   if (state->size > 0) {
     const RowShape sh = row_shape(c->row_bytes);
-    const unsigned grid = (unsigned)((state->size * (int64_t)sh.vecs + kBlock - 1) / kBlock);
-#define COOP_IMPORT(VB) COOP_LAUNCH(K_CACHE_UPDATE, k_cache_import<VB>, dim3(grid), dim3(kBlock), 0, s, (const char*)table, table_rows, sh,  \
-                                    vertices, stamps, state->size, c->n_vertices, (char*)c->rows, c->slot_of, c->vertex_of, c->stamp, \
-                                    c->d_ctl)
+    const int64_t blocks = (state->size * (int64_t)sh.vecs + kBlock - 1) / kBlock;
+#define COOP_IMPORT(VB)                                                                                                                 \
+  for (int64_t b = 0; b < blocks; b += kSliceBlocks)                                                                                    \
+    COOP_LAUNCH(K_CACHE_UPDATE, k_cache_import<VB>, dim3((unsigned)(blocks - b < kSliceBlocks ? blocks - b : kSliceBlocks)), dim3(kBlock), \
+                0, s, b, (const char*)table, table_rows, sh, vertices, stamps, state->size, c->n_vertices, (char*)c->rows, c->slot_of,  \
+                c->vertex_of, c->stamp, c->d_ctl)
     switch (sh.vec_bytes) {
       case 16: COOP_IMPORT(16); break;
       case 8: COOP_IMPORT(8); break;

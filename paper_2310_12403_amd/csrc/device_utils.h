@@ -102,6 +102,10 @@ inline RowShape row_shape(int64_t row_bytes) {
   return RowShape{row_bytes, vecs, (uint32_t)((((uint64_t)1 << 32) + vecs - 1) / vecs), vb};
 }
 
+// A launch has fewer than 2^32 threads (one that asks for more runs with what is left of the number modulo 2^32, without an
+// error), which is 64 GB of rows at an item per thread: kernels of that kind are launched in slices of blocks.
+constexpr int64_t kSliceBlocks = ((int64_t)1 << 32) / kBlock - 1;
+
 // The items [first, first + count) of a block, count <= 1024: thread items are given as offsets below count.
 struct BlockItems {
   int64_t row0;  // row of the block's first item

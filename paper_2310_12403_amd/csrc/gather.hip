@@ -89,11 +89,11 @@ struct MeanAcc {
 };
 
 template <int VB, bool F16>
-__global__ __launch_bounds__(kBlock) void k_gather_mean(const char* __restrict__ feat, int64_t n_rows, RowShape sh,
+__global__ __launch_bounds__(kBlock) void k_gather_mean(int64_t block0, const char* __restrict__ feat, int64_t n_rows, RowShape sh,
                                                         const int64_t* __restrict__ indptr, const int32_t* __restrict__ col,
                                                         int64_t n_dst, char* __restrict__ out, int32_t* __restrict__ bad) {
   typedef typename RowVec<VB>::T V;
-  const BlockItems items((int64_t)blockIdx.x * kBlock, sh.vecs);
+  const BlockItems items((block0 + (int64_t)blockIdx.x) * kBlock, sh.vecs);
   uint32_t item;
   const int64_t i = items.row_of(threadIdx.x, sh, &item);
   if (i >= n_dst) return;
@@ -190,9 +190,10 @@ namespace {
 template <int VB, bool F16>
 void launch_mean(const void* feat, int64_t n_rows, const RowShape& sh, const int64_t* indptr, const int32_t* col, int64_t n_dst,
                  void* out, int32_t* bad, hipStream_t s) {
-  const unsigned grid = (unsigned)((n_dst * (int64_t)sh.vecs + kBlock - 1) / kBlock);
-  COOP_LAUNCH(K_GATHER_MEAN, (k_gather_mean<VB, F16>), dim3(grid), dim3(kBlock), 0, s, (const char*)feat, n_rows, sh, indptr, col, n_dst,
-              (char*)out, bad);
+  const int64_t blocks = (n_dst * (int64_t)sh.vecs + kBlock - 1) / kBlock;
+  for (int64_t b = 0; b < blocks; b += kSliceBlocks)
+    COOP_LAUNCH(K_GATHER_MEAN, (k_gather_mean<VB, F16>), dim3((unsigned)(blocks - b < kSliceBlocks ? blocks - b : kSliceBlocks)), dim3(kBlock),
+                0, s, b, (const char*)feat, n_rows, sh, indptr, col, n_dst, (char*)out, bad);
 }
 }  // namespace
 

@@ -1,5 +1,7 @@
 """GPU parity: every array that libcoop produces must equal the CPU oracle's, byte for byte,
 on the same seeded synthetic inputs.  All calls go through the C ABI (ctypes binding)."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -195,6 +197,31 @@ def test_rows_of_any_size(P, dtype, dims, where):
             assert got.cpu().numpy().tobytes() == R.gather(feat.numpy(), batch.numpy()).tobytes(), dim
         cache.close()
     P.coop_gather_status()
+
+
+def test_more_items_than_a_launch_has_threads(P):
+    """Rows of 16 KB, 2^22 + 1 of them: one row more than 2^32 threads move at an item each.  (69 GB of output, or of cache.)"""
+    n, dim = (1 << 22) + 1, 4096
+    feat = synth.features(3, dim, torch.float32, seed=2)
+    indptr = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    indptr[n // 2:] = 1
+    indptr[-1] = 2
+    out = torch.full((n, dim), 7.0, device="cuda")
+    P.coop_gather_mean(feat.cuda(), indptr, torch.tensor([2, 1], dtype=torch.int32).cuda(), out=out)
+    P.coop_gather_status()
+    assert torch.equal(out[-1].cpu(), feat[1]) and torch.equal(out[n // 2 - 1].cpu(), feat[2])
+    out[-1] = out[n // 2 - 1] = 0.0
+    assert all(int(torch.count_nonzero(part)) == 0 for part in out.split(1 << 18))
+    del out
+    cache = P.Cache(n, n, dim, torch.float32, 1000)
+    cache.import_state(feat.cuda(), torch.arange(n, dtype=torch.int32).cuda(), torch.arange(1, n + 1, dtype=torch.int64).cuda(), (n, n + 1, 1))
+    ids = torch.cat([torch.arange(300), torch.arange(n // 2, n // 2 + 300), torch.arange(n - 300, n)]).to(torch.int32)
+    rows, n_miss = cache.gather(feat.cuda(), ids.cuda())
+    assert n_miss == 0 and torch.equal(rows.cpu(), feat[ids.long() % 3])
+    cache.close()
+    del cache
+    gc.collect()
+    torch.cuda.empty_cache()
 
 
 def test_sample_then_gather_end_to_end(P, tiny):
