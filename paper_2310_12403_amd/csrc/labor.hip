@@ -1020,12 +1020,12 @@ __global__ void k_labor_redo(Ctl* ctl, uint32_t* piece_count, uint32_t* cand_cou
 // staged rows -> the block's edge arrays: kFillLanes threads per destination, each taking every kFillLanes-th slot
 constexpr int kFillLanesLog2 = 3;
 // (edge_limit: entries of col_global / eid; nothing is written beyond them)
-__global__ __launch_bounds__(kBlock) void k_labor_fill_staged(LayerChunks ch, int64_t n_dst, uint32_t stage_cap,
+__global__ __launch_bounds__(kBlock) void k_labor_fill_staged(LayerChunks ch, int64_t first, int64_t n_dst, uint32_t stage_cap,
                                                               const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
                                                               int64_t* __restrict__ eid, int64_t edge_limit) {
   __shared__ uint32_t row_j[kBlock >> kFillLanesLog2][kWave];  // list positions of one staged row per lane group
   const int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t w = idx >> kFillLanesLog2;
+  const int64_t w = first + (idx >> kFillLanesLog2);
   if (w >= n_dst) return;
   const int64_t o = eptr[w];
   const int64_t c = eptr[w + 1] - o;
@@ -1066,11 +1066,11 @@ __global__ __launch_bounds__(kBlock) void k_labor_fill_staged(LayerChunks ch, in
 
 // second, ordered scan of the (rare) destinations whose staging row overflowed, writing straight to the edge arrays
 template <bool BLEND>
-__global__ __launch_bounds__(kBlock) void k_labor_fill_overflow(const int32_t* __restrict__ g_indices, LayerChunks ch, int64_t n_dst,
+__global__ __launch_bounds__(kBlock) void k_labor_fill_overflow(const int32_t* __restrict__ g_indices, LayerChunks ch, int64_t first, int64_t n_dst,
                                                                 LayerKeys K, double cw, double sw, uint32_t stage_cap,
                                                                 const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
                                                                 int64_t* __restrict__ eid) {
-  const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + uniform_wave_in_block();
+  const int64_t w = first + (int64_t)blockIdx.x * kWavesPerBlock + uniform_wave_in_block();
   if (w >= n_dst) return;
   const int64_t o = eptr[w];
   if (eptr[w + 1] - o <= (int64_t)stage_cap) return;
@@ -1294,6 +1294,7 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
       // lists per wave: a few amortise the record fetch once there are plenty of lists (the knob overrides)
       int lpw = g_lists_per_wave;
       if (lpw == 0) lpw = n_new >= 65536 ? (cx.blend && cx.vec4 ? 8 : 4) : 1;  // blended: fuller waves at the fp32 stage
+      while ((n_new + lpw - 1) / lpw > kSliceLists / 2) lpw *= 2;  // (and no more waves than a launch can have; 64 lists at most)
       const int64_t n_waves = (n_new + lpw - 1) / lpw;
       // the piece waves come first in the grid: one round of resident blocks, fewer if there cannot be that many pieces
       constexpr int64_t kPieceBlocks = 2048;
@@ -1349,19 +1350,23 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
   if (alloc.failed) return COOP_E_NOMEM;
 
   if (m > 0 && n_dst > 0) {
-    COOP_LAUNCH(K_LABOR_FILL, k_labor_fill_staged, dim3(blocks_for(n_dst << kFillLanesLog2, kBlock)), dim3(kBlock), 0, s, ch, n_dst, cap,
-                blk->indptr, blk->col_global, blk->eid, m);
+    constexpr int64_t kSliceRows = kSliceLists << (6 - kFillLanesLog2);
+    for (int64_t b = 0; b < n_dst; b += kSliceRows)
+      COOP_LAUNCH(K_LABOR_FILL, k_labor_fill_staged, dim3(blocks_for((n_dst - b < kSliceRows ? n_dst - b : kSliceRows) << kFillLanesLog2, kBlock)),
+                  dim3(kBlock), 0, s, ch, b, n_dst, cap, blk->indptr, blk->col_global, blk->eid, m);
     if (!defer && cx.h_ctl->n_overflow > 0) {
       LayerKeys K{};
       layer_keys(cx.seed, COOP_LABOR0, l, cx.group, K.Ka);
       layer_keys(cx.seed, COOP_LABOR0, l, cx.group + 1, K.Kb);
-      const dim3 grid(blocks_for(n_dst, kWavesPerBlock));
-      if (cx.blend)
-        COOP_LAUNCH(K_LABOR_OVERFLOW, k_labor_fill_overflow<true>, grid, dim3(kBlock), 0, s, cx.g->indices, ch, n_dst, K, cx.cw, cx.sw,
-                    cap, blk->indptr, blk->col_global, blk->eid);
-      else
-        COOP_LAUNCH(K_LABOR_OVERFLOW, k_labor_fill_overflow<false>, grid, dim3(kBlock), 0, s, cx.g->indices, ch, n_dst, K, cx.cw, cx.sw,
-                    cap, blk->indptr, blk->col_global, blk->eid);
+      for (int64_t b = 0; b < n_dst; b += kSliceLists) {
+        const dim3 grid(blocks_for(n_dst - b < kSliceLists ? n_dst - b : kSliceLists, kWavesPerBlock));
+        if (cx.blend)
+          COOP_LAUNCH(K_LABOR_OVERFLOW, k_labor_fill_overflow<true>, grid, dim3(kBlock), 0, s, cx.g->indices, ch, b, n_dst, K, cx.cw, cx.sw,
+                      cap, blk->indptr, blk->col_global, blk->eid);
+        else
+          COOP_LAUNCH(K_LABOR_OVERFLOW, k_labor_fill_overflow<false>, grid, dim3(kBlock), 0, s, cx.g->indices, ch, b, n_dst, K, cx.cw, cx.sw,
+                      cap, blk->indptr, blk->col_global, blk->eid);
+      }
     }
   }
   return COOP_OK;

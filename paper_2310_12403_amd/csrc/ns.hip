@@ -754,7 +754,8 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
   // lists above kLongListDegree up, a graph on which they hold less than an eighth of the edges is left alone: the queue
   // costs the count pass a reservation per block and buys nothing there)
   const bool hubs = !cx.g->symmetric || cx.g->long_mass >= cx.g->n_edges / 8;
-  const bool queue_long = g_ns_long_min != 0 && (g_ns_long_min != kNsLongDefault || (n_dst >= kNsQueueFrom && hubs));
+  const bool queue_long = g_ns_long_min != 0 && n_dst <= kSliceLists / 2 /* (the queue's waves are launched in front of the others) */ &&
+                          (g_ns_long_min != kNsLongDefault || (n_dst >= kNsQueueFrom && hubs));
   const uint32_t long_min = queue_long ? (uint32_t)g_ns_long_min : 0u;
   uint32_t* long_list = queue_long ? alloc.get<uint32_t>(n_dst, COOP_TAG_SCRATCH) : nullptr;
   uint32_t* n_long = cx.d_piece_count + l;  // (zero at the start of the call and whenever the layer is redone)
@@ -786,46 +787,56 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
     // layer; with dependent variates the traversal 3.0 -> 2.57 ms and the selection 0.99 -> 0.91)
     const int wpb = 1;
     const size_t shmem = (size_t)wpb * cap * 16 + (cx.blend ? (size_t)wpb * sizeof(NsQueue) : 0);
-    const dim3 grid(blocks_for(n_dst, wpb));
-#define COOP_NS_ARGS cx.g->indices, rec, bthr, n_dst, k, cap, wpb, vp, blk->indptr, blk->col_global, blk->eid, m
+    NsCand* rows = nullptr;
+    uint32_t* n_cand = nullptr;
+    uint32_t row_cap = 64;
+    if (cx.blend) {
+      // rows of the two-kernel path: room for twice the expected candidates (at least 64, at most the LDS capacity)
+      while (row_cap < 2 * target && row_cap < cap) row_cap <<= 1;
+      rows = alloc.get<NsCand>(n_dst * (int64_t)row_cap, COOP_TAG_SCRATCH);
+      n_cand = alloc.get<uint32_t>(n_dst, COOP_TAG_SCRATCH);
+      if (alloc.failed) return COOP_E_NOMEM;
+    }
     // the queue's waves, one per queued list: as many as there can be lists that long, by the degree census of the
     // registration and by the number of edges (the unused ones end at once)
     int64_t most_long = cx.g->n_edges / (int64_t)(long_min ? long_min : 1) + 1;
     if (most_long > n_dst) most_long = n_dst;
     if (long_min != 0 && most_long > cx.g->lists_longer_than(long_min)) most_long = cx.g->lists_longer_than(long_min);
     const int long_blocks = queue_long ? (int)blocks_for(most_long, wpb) : 0;
-    const dim3 grid_q(grid.x + (unsigned)long_blocks);
-    if (cx.blend) {
-      // rows of the two-kernel path: room for twice the expected candidates (at least 64, at most the LDS capacity)
-      uint32_t row_cap = 64;
-      while (row_cap < 2 * target && row_cap < cap) row_cap <<= 1;
-      NsCand* rows = alloc.get<NsCand>(n_dst * (int64_t)row_cap, COOP_TAG_SCRATCH);
-      uint32_t* n_cand = alloc.get<uint32_t>(n_dst, COOP_TAG_SCRATCH);
-      if (alloc.failed) return COOP_E_NOMEM;
-      int lists_log2 = 0;
-      while (lists_log2 < 6 && (n_dst >> (lists_log2 + 1)) >= kNsRedoWaves) ++lists_log2;
-      const dim3 grid_redo(blocks_for(n_dst, (int64_t)wpb << lists_log2));
-#define COOP_NS_BLEND(VEC4)                                                                                                                    \
-  COOP_LAUNCH(K_NS_FILL, k_ns_collect<VEC4>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, rows, row_cap, n_cand, long_min,                \
-              (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);                                                               \
-  COOP_LAUNCH(K_NS_SELECT, k_ns_select, grid, dim3(wpb * kWave), shmem, s, rec, n_dst, k, cap, wpb, vp, blk->indptr, blk->col_global, blk->eid, \
-              (const NsCand*)rows, row_cap, n_cand, (const NsBlendThr*)bthr);                                                                  \
-  COOP_LAUNCH(K_NS_FILL, k_ns_redo<VEC4>, grid_redo, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, (const uint32_t*)n_cand, lists_log2)
-      if (cx.vec4) { COOP_NS_BLEND(true); } else { COOP_NS_BLEND(false); }
+    for (int64_t b = 0; b < n_dst; b += kSliceLists) {  // (one slice, unless there are 67 million destinations)
+      const int64_t n = n_dst - b < kSliceLists ? n_dst - b : kSliceLists;
+      const dim3 grid(blocks_for(n, wpb)), grid_q(grid.x + (unsigned)long_blocks), grid_w(blocks_for(n, kWavesPerBlock));
+      const NsRecord* rec_b = rec + b;
+      const NsBlendThr* bthr_b = cx.blend ? bthr + b : nullptr;
+      const int64_t* eptr_b = blk->indptr + b;
+#define COOP_NS_ARGS cx.g->indices, rec_b, bthr_b, n, k, cap, wpb, vp, eptr_b, blk->col_global, blk->eid, m
+      if (cx.blend) {
+        NsCand* rows_b = rows + b * (int64_t)row_cap;
+        uint32_t* n_cand_b = n_cand + b;
+        int lists_log2 = 0;
+        while (lists_log2 < 6 && (n >> (lists_log2 + 1)) >= kNsRedoWaves) ++lists_log2;
+        const dim3 grid_redo(blocks_for(n, (int64_t)wpb << lists_log2));
+#define COOP_NS_BLEND(VEC4)                                                                                                                \
+  COOP_LAUNCH(K_NS_FILL, k_ns_collect<VEC4>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, rows_b, row_cap, n_cand_b, long_min,        \
+              (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);                                                           \
+  COOP_LAUNCH(K_NS_SELECT, k_ns_select, grid, dim3(wpb * kWave), shmem, s, rec_b, n, k, cap, wpb, vp, eptr_b, blk->col_global, blk->eid,    \
+              (const NsCand*)rows_b, row_cap, n_cand_b, bthr_b);                                                                           \
+  COOP_LAUNCH(K_NS_FILL, k_ns_redo<VEC4>, grid_redo, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, (const uint32_t*)n_cand_b, lists_log2)
+        if (cx.vec4) { COOP_NS_BLEND(true); } else { COOP_NS_BLEND(false); }
 #undef COOP_NS_BLEND
-    } else {
-      if (cx.vec4) COOP_LAUNCH(K_NS_FILL, k_ns_fill<true>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
-                               (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
-      else COOP_LAUNCH(K_NS_FILL, k_ns_fill<false>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
-                       (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
-    }
+      } else {
+        if (cx.vec4) COOP_LAUNCH(K_NS_FILL, k_ns_fill<true>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
+                                 (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
+        else COOP_LAUNCH(K_NS_FILL, k_ns_fill<false>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
+                         (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
+      }
 #undef COOP_NS_ARGS
-    if (k > kNsMaxSelect) {  // the lists longer than such a fanout (the kernels above skip them)
-      const dim3 grid_w(blocks_for(n_dst, kWavesPerBlock));
-      if (cx.blend) COOP_LAUNCH(K_NS_FILL, k_ns_fill_wide<true>, grid_w, dim3(kBlock), 0, s, cx.g->indices, rec, n_dst, k, vp, blk->indptr,
-                                blk->col_global, blk->eid, m);
-      else COOP_LAUNCH(K_NS_FILL, k_ns_fill_wide<false>, grid_w, dim3(kBlock), 0, s, cx.g->indices, rec, n_dst, k, vp, blk->indptr,
-                       blk->col_global, blk->eid, m);
+      if (k > kNsMaxSelect) {  // the lists longer than such a fanout (the kernels above skip them)
+        if (cx.blend) COOP_LAUNCH(K_NS_FILL, k_ns_fill_wide<true>, grid_w, dim3(kBlock), 0, s, cx.g->indices, rec_b, n, k, vp, eptr_b,
+                                  blk->col_global, blk->eid, m);
+        else COOP_LAUNCH(K_NS_FILL, k_ns_fill_wide<false>, grid_w, dim3(kBlock), 0, s, cx.g->indices, rec_b, n, k, vp, eptr_b,
+                         blk->col_global, blk->eid, m);
+      }
     }
   }
   return COOP_OK;

@@ -338,14 +338,16 @@ int rw_layer(const SampleCtx& cx, const RwConfig& rw, int l, const int32_t* dst,
                 cx.g->n_vertices, dst, n_dst, rp, T, tables, kept, rows, cnt, cx.d_ctl);
   } else if (n_dst > 0) {
     // table of 512 slots (up to 384 visits per destination, the paper's 3 x 100 included), else 2048
-    if (n_steps <= 384) {
-      const int wpb = kWavesPerBlock;
-      COOP_LAUNCH(K_RW_WALK, k_rw_walk<8>, dim3(blocks_for(n_dst, wpb)), dim3(kBlock), (size_t)wpb * 2 * 512 * 4, s, cx.g->indptr,
-                  cx.g->indices, cx.g->n_vertices, dst, n_dst, rp, wpb, rows, cnt, cx.d_ctl);
-    } else {
-      const int wpb = 2;
-      COOP_LAUNCH(K_RW_WALK, k_rw_walk<32>, dim3(blocks_for(n_dst, wpb)), dim3(kBlock), (size_t)wpb * 2 * 2048 * 4, s, cx.g->indptr,
-                  cx.g->indices, cx.g->n_vertices, dst, n_dst, rp, wpb, rows, cnt, cx.d_ctl);
+    const int wpb = n_steps <= 384 ? kWavesPerBlock : 2;  // (of the block's four waves)
+    const int64_t slice = kSliceLists * wpb / kWavesPerBlock;
+    for (int64_t b = 0; b < n_dst; b += slice) {
+      const int64_t n = n_dst - b < slice ? n_dst - b : slice;
+      if (n_steps <= 384)
+        COOP_LAUNCH(K_RW_WALK, k_rw_walk<8>, dim3(blocks_for(n, wpb)), dim3(kBlock), (size_t)wpb * 2 * 512 * 4, s, cx.g->indptr,
+                    cx.g->indices, cx.g->n_vertices, dst + b, n, rp, wpb, rows + b * (int64_t)rp.k_eff, cnt + b, cx.d_ctl);
+      else
+        COOP_LAUNCH(K_RW_WALK, k_rw_walk<32>, dim3(blocks_for(n, wpb)), dim3(kBlock), (size_t)wpb * 2 * 2048 * 4, s, cx.g->indptr,
+                    cx.g->indices, cx.g->n_vertices, dst + b, n, rp, wpb, rows + b * (int64_t)rp.k_eff, cnt + b, cx.d_ctl);
     }
   }
   if (defer) {
@@ -362,9 +364,12 @@ int rw_layer(const SampleCtx& cx, const RwConfig& rw, int l, const int32_t* dst,
   blk->eid = alloc.get<int64_t>(m, COOP_TAG_OUTPUT);
   blk->col_local = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
-  if (m > 0 && n_dst > 0)
-    COOP_LAUNCH(K_RW_FILL, k_rw_fill, dim3(blocks_for(n_dst * (int64_t)rp.k_eff, kBlock)), dim3(kBlock), 0, s, rows, rp.k_eff, n_dst,
-                blk->indptr, blk->col_global, blk->eid, m);
+  const int64_t most = (((int64_t)1 << 32) - kBlock) / rp.k_eff;  // (a thread per slot, in slices as above; k_eff is below 2^21)
+  for (int64_t b = 0; m > 0 && b < n_dst; b += most) {
+    const int64_t n = n_dst - b < most ? n_dst - b : most;
+    COOP_LAUNCH(K_RW_FILL, k_rw_fill, dim3(blocks_for(n * (int64_t)rp.k_eff, kBlock)), dim3(kBlock), 0, s, rows + b * (int64_t)rp.k_eff, rp.k_eff,
+                n, blk->indptr + b, blk->col_global, blk->eid, m);
+  }
   return COOP_OK;
 }
 

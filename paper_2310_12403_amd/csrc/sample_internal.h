@@ -86,6 +86,10 @@ extern int g_defer_sizes;
 extern int g_enum_degree;
 extern int g_ns_long_min;   // COOP_TUNE_NS_LONG_LIST (defined in ns.hip)
 
+// A launch has fewer than 2^32 threads (more are taken modulo that number, without an error): passes with a wave per
+// destination take the destinations in slices.
+constexpr int64_t kSliceLists = ((int64_t)1 << 26) - 64;
+
 static inline unsigned blocks_for(int64_t n, int64_t per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 
 }  // namespace coop

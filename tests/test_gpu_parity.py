@@ -224,6 +224,36 @@ def test_more_items_than_a_launch_has_threads(P):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("sampler,kappa", [(R.NS, 1), (R.NS, 16), (R.RW, 1), (R.LABOR0, 1)])
+def test_more_destinations_than_a_launch_has_waves(P, sampler, kappa):
+    """All vertices of a graph of 2^26 + 1,000 as destinations: lists of one entry, which is kept, and at the end of ten, whose
+    kept entries are the oracle's for those destinations alone (neither sampler looks at the others)."""
+    n, tail = (1 << 26) + 1000, 900
+    indptr = torch.cat([torch.arange(n - tail), torch.arange(tail + 1) * 10 + n - tail])
+    indices = ((torch.arange(n + 9 * tail) * 7919 + 13) % n).to(torch.int32)
+    g = P.coop_graph_load(indptr.cuda(), indices.cuda())
+    seeds = torch.arange(n, dtype=torch.int32)
+    if sampler == R.LABOR0:
+        P.coop_tune(P.COOP_TUNE_STAGE_CAP, 1)
+    try:
+        if sampler == R.RW:
+            blk, = P.coop_sample_rw(g, seeds.cuda(), (3,), 1, 8, 0.0, it=5, seed=3)
+        else:
+            blk, = P.coop_sample(g, seeds.cuda(), (3,), sampler, it=5, kappa=kappa, seed=3)
+    finally:
+        P.coop_tune(P.COOP_TUNE_STAGE_CAP, 0)
+    want, = R.sample(indptr.numpy(), indices.numpy(), seeds[-tail:].numpy(), (3,), sampler, it=5, kappa=kappa, seed=3,
+                     rw=(1, 8, 0.0) if sampler == R.RW else None)
+    head = n - tail
+    assert blk.n_edges == head + len(want["eid"]) and torch.equal(blk.indptr[:head].cpu(), torch.arange(head))
+    assert torch.equal(blk.col_global[:head].cpu(), indices[:head])
+    assert np.array_equal(blk.col_global[head:].cpu().numpy(), want["col_global"]) and np.array_equal(blk.eid[head:].cpu().numpy(), want["eid"])
+    assert torch.equal(blk.src_ids[:n].cpu(), seeds) and torch.equal(blk.src_ids[blk.col_local.long()], blk.col_global)
+    del blk
+    gc.collect()
+    torch.cuda.empty_cache()
+
+
 def test_sample_then_gather_end_to_end(P, tiny):
     feat = synth.features(tiny.n, 64, torch.float32, seed=0, device="cpu")
     seeds = synth.seed_batches(tiny.n, 1024, seed=0)(0).numpy()
