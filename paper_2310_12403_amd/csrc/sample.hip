@@ -8,8 +8,7 @@
 namespace coop {
 
 __global__ __launch_bounds__(kBlock) void k_copy_i32(const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) out[i] = in[i];
+  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) out[i] = in[i];
 }
 
 // start of a sampling call: the seed list is copied to the first block's dst_ids and the control data cleared
@@ -291,6 +290,7 @@ extern "C" int coop_copy_ids(const int32_t* in, int32_t* out, int64_t n, void* s
   if ((!in || !out) && n > 0) return COOP_E_NULL;
   if (n < 0 || n >= ((int64_t)1 << 39)) return COOP_E_ARG;
   hipStream_t s = (hipStream_t)stream;
-  if (n > 0) COOP_LAUNCH(K_COPY_IDS, k_copy_i32, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, s, in, out, n);
+  const int64_t blocks = (n + kBlock - 1) / kBlock;  // (a launch has fewer than 2^32 threads; longer lists: several entries each)
+  if (n > 0) COOP_LAUNCH(K_COPY_IDS, k_copy_i32, dim3((unsigned)(blocks < (1 << 20) ? blocks : (1 << 20))), dim3(kBlock), 0, s, in, out, n);
   return COOP_OK;
 }

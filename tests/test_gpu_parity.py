@@ -224,6 +224,15 @@ def test_more_items_than_a_launch_has_threads(P):
     torch.cuda.empty_cache()
 
 
+def test_copy_of_more_ids_than_a_launch_has_threads(P):
+    ids = torch.arange((1 << 20) + 1, dtype=torch.int32, device="cuda").repeat(1 << 12)
+    out = P.coop_copy_ids(ids)
+    assert torch.equal(out, ids)
+    del ids, out
+    gc.collect()
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("sampler,kappa", [(R.NS, 1), (R.NS, 16), (R.RW, 1), (R.LABOR0, 1)])
 def test_more_destinations_than_a_launch_has_waves(P, sampler, kappa):
     """All vertices of a graph of 2^26 + 1,000 as destinations: lists of one entry, which is kept, and at the end of ten, whose
