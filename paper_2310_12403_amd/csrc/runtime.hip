@@ -207,9 +207,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_offset(int64_t n, Out* __restri
 
 // The same per-tile scan, and the scan of the tile sums by whichever block finishes last: one launch.  The consumer adds
 // tile_prefix[tile] to an element when it reads it (TiledScan::at).
-template <typename Load, typename Out>
-__global__ __launch_bounds__(kBlock) void k_scan_tiled(Load load, int64_t n, Out* __restrict__ out, int64_t* __restrict__ tile_sum,
-                                                       Out* __restrict__ tile_prefix, uint32_t* done, int64_t* total_out, Publish pub) {
+__global__ __launch_bounds__(kBlock) void k_scan_tiled(LoadU32 load, int64_t n, uint32_t* __restrict__ out, int64_t* __restrict__ tile_sum,
+                                                       uint32_t* __restrict__ tile_prefix, uint32_t* done) {
   __shared__ int64_t lds[kWavesPerBlock];
   __shared__ uint32_t s_last;
   const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;  // a thread owns 8 in a row
@@ -227,7 +226,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiled(Load load, int64_t n, Out
 #pragma unroll
   for (int j = 0; j < kItems; ++j) {
     const int64_t i = base + j;
-    if (i < n) out[i] = (Out)run;
+    if (i < n) out[i] = (uint32_t)run;
     run += x[j];
   }
   if (threadIdx.x == 0) {
@@ -245,14 +244,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiled(Load load, int64_t n, Out
     const int64_t v = t < tiles ? __hip_atomic_load(&tile_sum[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     int64_t all;
     const int64_t upto = block_incl_scan(v, &all, lds);
-    if (t < tiles) tile_prefix[t] = (Out)(carry + upto - v);
+    if (t < tiles) tile_prefix[t] = (uint32_t)(carry + upto - v);
     carry += all;
   }
   if (threadIdx.x == 0) {
-    out[n] = (Out)carry;  // the entry one past the end holds the grand total
-    if (total_out) *total_out = carry;
-    *done = 0;            // ready for the next scan of this call (the stream keeps them apart)
-    publish_ctl(pub);
+    out[n] = (uint32_t)carry;  // the entry one past the end holds the grand total
+    *done = 0;                 // ready for the next scan of this call (the stream keeps them apart)
   }
 }
 
@@ -297,27 +294,6 @@ size_t scan_tmp_bytes(int64_t n) {  // tile sums, and the one-kernel scans' tile
 }
 
 constexpr int64_t kScanTiledMax = 64;  // tiles (131,072 elements) up to which the one-kernel scan is used
-template <typename Load>
-static TiledScan<uint32_t> scan_tiled_impl(Load load, int64_t n, uint32_t* out, int64_t* total_out, void* tmp, uint32_t* done, hipStream_t s,
-                                           const Publish* p) {
-  const Publish pub = p ? *p : Publish{};
-  if (n <= kScanSmall) {  // one block; `out` is the whole scan
-    COOP_LAUNCH(K_SCAN_LOCAL, (k_scan_small<Load, uint32_t>), dim3(1), dim3(kBlock), 0, s, load, n, out, out + n, total_out, pub);
-    return TiledScan<uint32_t>{out, nullptr, n};
-  }
-  const int64_t tiles = (n + kTile - 1) / kTile;
-  int64_t* tile_sum = (int64_t*)tmp;
-  if (tiles > kScanTiledMax) {  // long inputs: two kernels (measured: the fences of many tiles cost more than the second launch)
-    COOP_LAUNCH(K_SCAN_LOCAL, (k_scan_local<Load, uint32_t>), dim3((unsigned)tiles), dim3(kBlock), 0, s, load, n, out, tile_sum);
-    COOP_LAUNCH(K_SCAN_OFFSET, k_scan_offset<uint32_t>, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, out, (const int64_t*)tile_sum, out + n, total_out, pub);
-    return TiledScan<uint32_t>{out, nullptr, n};
-  }
-  uint32_t* tile_prefix = (uint32_t*)(tile_sum + tiles + 2);
-  COOP_LAUNCH(K_SCAN_LOCAL, (k_scan_tiled<Load, uint32_t>), dim3((unsigned)tiles), dim3(kBlock), 0, s, load, n, out, tile_sum, tile_prefix, done,
-              total_out, pub);
-  return TiledScan<uint32_t>{out, tile_prefix, n};
-}
-
 template <typename Load, typename Out>
 static void scan_impl(Load load, int64_t n, Out* out, Out* end_out, int64_t* total_out, void* tmp, hipStream_t s, const Publish* p) {
   const Publish pub = p ? *p : Publish{};
@@ -358,7 +334,15 @@ void scan_u32_to_u32(const uint32_t* in, int64_t n, uint32_t* out, void* tmp, hi
 }
 
 TiledScan<uint32_t> scan_u32_tiled(const uint32_t* in, int64_t n, uint32_t* out, void* tmp, uint32_t* done, hipStream_t s) {
-  return scan_tiled_impl<LoadU32>(LoadU32{in}, n, out, nullptr, tmp, done, s, nullptr);
+  const int64_t tiles = (n + kTile - 1) / kTile;
+  if (n <= kScanSmall || tiles > kScanTiledMax) {  // one block, or two kernels (measured: the fences of many tiles cost more than the second launch)
+    scan_u32_to_u32(in, n, out, tmp, s);
+    return TiledScan<uint32_t>{out, nullptr, n};
+  }
+  int64_t* tile_sum = (int64_t*)tmp;
+  uint32_t* tile_prefix = (uint32_t*)(tile_sum + tiles + 2);
+  COOP_LAUNCH(K_SCAN_LOCAL, k_scan_tiled, dim3((unsigned)tiles), dim3(kBlock), 0, s, LoadU32{in}, n, out, tile_sum, tile_prefix, done);
+  return TiledScan<uint32_t>{out, tile_prefix, n};
 }
 
 void scan_popc_to_u32(const uint64_t* bits, int64_t n_words, uint32_t* out, int64_t* total_out, void* tmp, hipStream_t s) {

@@ -787,7 +787,10 @@ int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_gl
   // by partition from kFilterMax entries on, as long as a block's counters fit LDS
   const int64_t pairs_per_bucket = g_unique_mode == 3 ? 16 * kPartPairs : kPartPairs;
   w->n_buckets = (n_all + pairs_per_bucket - 1) / pairs_per_bucket;
-  // two bucket blocks fit a CU: a last round of a few blocks is spread over the others, which grow by an eighth at most
+  // two bucket blocks fit a CU: a last round of a few blocks is spread over the others, which grow by an eighth at most.  (One
+  // round: lists of 2.2 and 2.3 M entries 20.5 us for the first positions, with the last round 23.4; two: 4.4 and 4.6 M 27.2
+  // and 28.1; from three rounds on half a us more there, a bucket of more than 4,096 pairs reading them twice, and one to
+  // three less in the scatter, which has fewer buckets: 7.0 M 40.5 and 43.4.)
   const int64_t whole_rounds = w->n_buckets / 512 * 512;
   if (whole_rounds > 0 && n_all <= whole_rounds * (pairs_per_bucket + pairs_per_bucket / 8)) w->n_buckets = whole_rounds;
   const bool by_partition = m > 0 && w->n_buckets <= kPartMaxBuckets && g_unique_mode != 1 && (g_unique_mode >= 2 || n_all >= kFilterMax);
