@@ -1294,7 +1294,7 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
       // lists per wave: a few amortise the record fetch once there are plenty of lists (the knob overrides)
       int lpw = g_lists_per_wave;
       if (lpw == 0) lpw = n_new >= 65536 ? (cx.blend && cx.vec4 ? 8 : 4) : 1;  // blended: fuller waves at the fp32 stage
-      while ((n_new + lpw - 1) / lpw > kSliceLists / 2) lpw *= 2;  // (and no more waves than a launch can have; 64 lists at most)
+      while (lpw < kWave && (n_new + lpw - 1) / lpw > kSliceLists / 2) lpw = 2 * lpw < kWave ? 2 * lpw : kWave;  // (no more waves than a launch can have)
       const int64_t n_waves = (n_new + lpw - 1) / lpw;
       // the piece waves come first in the grid: one round of resident blocks, fewer if there cannot be that many pieces
       constexpr int64_t kPieceBlocks = 2048;
