@@ -22,6 +22,17 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
 }
 
 __device__ __forceinline__ uint64_t ballot64(bool p) { return __ballot(p); }
+// the same of a plain comparison: the compare instruction's result as it is.  (Of a condition that combines several, the
+// compiler spends a select and a second comparison; combine the masks instead.)
+__device__ __forceinline__ uint64_t compare_mask(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+// is this lane's bit set in a wave-uniform mask?  (no instruction of its own: the mask becomes the execution mask)
+__device__ __forceinline__ bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+// the lowest n lanes (n <= 64)
+__device__ __forceinline__ uint64_t low_lanes(uint32_t n) { return n >= 64u ? ~0ull : (1ull << n) - 1ull; }
+// lanes_below plus `base`, the addition being part of the two counting instructions
+__device__ __forceinline__ uint32_t lanes_below_plus(uint64_t mask, uint32_t base) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, base));
+}
 
 // wave-wide inclusive sum of a uint32 (all lanes get their prefix)
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {

@@ -24,7 +24,7 @@ struct NsRecord {
   uint32_t d;
   int32_t s;
   uint32_t bound;  // first candidate bound: about `target` of the d variates are expected below it
-  uint32_t pad;
+  uint32_t mid;    // the destination's word of the variates of group g (ns_mid)
 };
 
 // (long_min > 0: the destinations whose list is longer than long_min entries, and than k, are also queued in long_list,
@@ -39,10 +39,11 @@ template <int kNsCountBlock, int kNsCountEach>
 __global__ __launch_bounds__(kNsCountBlock) void k_ns_count(const int64_t* __restrict__ g_indptr, int64_t n_vertices,
                                                             const int32_t* __restrict__ dst, int64_t n_dst, uint32_t k, uint32_t target,
                                                             int32_t* __restrict__ cnt, NsRecord* __restrict__ rec,
-                                                            NsBlendThr* __restrict__ bthr /* null when c = 0 */, double cw, double sw, Ctl* ctl,
+                                                            NsBlendThr* __restrict__ bthr /* null when c = 0 */, LayerKeys keys, double cw, double sw, Ctl* ctl,
                                                             uint32_t long_min, uint32_t* __restrict__ long_list, uint32_t* __restrict__ n_long) {
   __shared__ uint32_t wave_long[kNsCountBlock / kWave];
   __shared__ uint32_t block_base;
+  const uint32_t* K = keys.Ka;
   const int64_t i0 = (int64_t)blockIdx.x * (kNsCountBlock * kNsCountEach) + threadIdx.x;
   bool is_long[kNsCountEach];
   int32_t s[kNsCountEach];
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(kNsCountBlock) void k_ns_count(const int64_t* __res
     // list, here where every lane has a list of its own)
     uint64_t bound = d > 0 ? ((uint64_t)target << 32) / (uint64_t)d : 0xFFFFFFFFull;
     if (bound > 0xFFFFFFFFull) bound = 0xFFFFFFFFull;  // d <= target: every neighbour is a candidate
-    rec[i] = NsRecord{beg[u], (uint32_t)d, s[u], (uint32_t)bound, 0u};
+    rec[i] = NsRecord{beg[u], (uint32_t)d, s[u], (uint32_t)bound, ns_mid(K, ns_sigma(K, (uint32_t)s[u]))};
     if (bthr) bthr[i] = d > (int64_t)k ? ns_blend_thresholds((uint32_t)bound, cw, sw) : NsBlendThr{0u, 0u, 0u, 0.0f};
     is_long[u] = long_min != 0 && d > (int64_t)long_min && d > (int64_t)k;
   }
@@ -121,6 +122,7 @@ constexpr uint32_t kNsRedo = 0xFFFFFFFFu;  // candidate count of a destination t
 // queue (an atomic per list on its counter, one after the other) and no bound on the waves: 100 thousand such lists 1.86 ms,
 // as with a wave each, against 9.3 with a queue and 1,024 waves.
 constexpr int64_t kNsRedoWaves = 16384;
+constexpr int64_t kNsFillWaves = 16384;  // k_ns_fill's waves take up to eight destinations, where that leaves at least this many waves
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 constexpr int kNsGroups = 4;  // 16-byte groups per lane and step of the fast traversal
@@ -134,24 +136,125 @@ struct NsQueue {
   uint32_t u2[kNsQueueCap];
 };
 
-// One pass over the list [beg, beg + d): every neighbour whose variate is <= bound is appended to the candidate
-// arrays in LDS (key = variate in the upper, list position in the lower half of 64 bits: the order of the selection;
-// vertex), in no particular order; returns how many qualified (entries beyond
-// `cap` are counted but not stored).  Long lists in a 16-byte aligned array are read as aligned groups of four
-// entries, kNsGroups groups per lane and step, whole groups in the main loop and the ragged ends in one extra step.
-// With c > 0 the variate of an entry is evaluated exactly only if the integer bounds and then the fp32 blend cannot
-// rule it out; the survivors of the integer bounds are evaluated 64 at a time.
-// STAGED (with c > 0): the exact evaluation is left to a later kernel; everything that the fp32 blend cannot rule out
+// A list read through a buffer descriptor: an addition per load in the place of a lane's 64-bit address, and entries behind the
+// end come back as zeros without a test (the whole offset is in the vector register: the check leaves a scalar offset out).
+// 16 bytes per lane or 4, at the alignment of the entries.
+struct ListLoads {
+  static constexpr int kAux = 2;  // non-temporal
+  __amdgpu_buffer_rsrc_t rsrc;
+  int lane4, lane16;
+  __device__ __forceinline__ ListLoads(const int32_t* list, uint32_t n /* <= 2^28 */)
+      : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(list), 0, (int)(n * 4u), 0x00020000)), lane4(lane_id() * 4), lane16(lane_id() * 16) {}
+  __device__ __forceinline__ u32x4 group(uint32_t g) const {  // entries 256 g + 4 lane ..
+    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane16 + (int)(g * 1024u), 0, kAux);
+  }
+  __device__ __forceinline__ uint32_t entry(uint32_t at) const { return __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane4 + (int)(at * 4u), 0, kAux); }
+};
+
+// A candidate in LDS; slot_key orders by (variate, list position), the order of the selection.
+struct alignas(16) NsSlot {
+  uint32_t j, r;  // list position, variate
+  int32_t t;      // the vertex
+  uint32_t keep;  // among the k smallest
+};
+__device__ __forceinline__ uint64_t slot_key(const NsSlot* c) { return ((uint64_t)c->r << 32) | c->j; }
+
+// One pass over a list of d entries, c = 0: position and vertex of every neighbour whose variate is <= bound go to
+// the slots, in list order (those beyond `cap` are counted but not stored); returns how many qualified.
+//
+// Bound by the issue of instructions: the chip issues 560 G vector ones of this kind a second (two per ns and CU) and as many
+// scalar ones, and of the 225 M and 190 M that 717 thousand lists took, 13 of each 64 entries were the two mixers and the
+// test, the others what a list and a candidate cost besides.  So: whole groups of 256
+// entries (16 bytes per lane, at whatever alignment the list has: memory instructions take any) need no lane mask, and what
+// is left, fewer than 256, is read 64 at a time, so that neither ragged ends nor half a group of idle lanes are paid for;
+// the test leaves only masks in scalar registers; a group's masks give every lane the place of its first candidate, a
+// lane's next one is a slot further, and lanes without one write to a slot of their own that nobody reads, so that there is no
+// branch per entry.  The variate is not kept but evaluated again for the few dozen candidates.  Four groups are
+// in flight, each requested as soon as its registers are free.
+constexpr uint32_t kGroup = kWave * 4;
+constexpr uint32_t kStretch = 1u << 28;  // entries that a descriptor's offsets reach
+struct NsList {
+  ListLoads in;
+  uint32_t n, n_groups;
+  u32x4 ring[kNsGroups];
+  uint32_t rest[4];
+  __device__ __forceinline__ NsList(const int32_t* list, uint32_t entries) : in(list, entries), n(entries), n_groups(entries / kGroup) {
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) rest[q] = in.entry((n & ~(kGroup - 1)) + q * kWave);
+#pragma unroll
+    for (uint32_t q = 0; q < kNsGroups; ++q) ring[q] = in.group(q);  // (behind the end of the list: zeros, and no traffic)
+  }
+};
+__device__ __forceinline__ uint32_t ns_collect_plain(NsList& L, uint32_t j0, uint32_t bound, const NsKeys& K, NsSlot* __restrict__ slot, uint32_t cap,
+                                                     uint32_t n_c) {
+  const uint32_t lane = (uint32_t)lane_id();
+  const uint32_t idle = cap + lane;  // (the slots behind the candidates')
+  for (uint32_t g0 = 0; g0 < L.n_groups; g0 += kNsGroups) {
+#pragma unroll
+    for (uint32_t q = 0; q < kNsGroups; ++q) {
+      const uint32_t g = g0 + q;
+      if (g >= L.n_groups) break;
+      uint64_t m[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m[e] = compare_mask(ns_uniform(K, L.ring[q][e]) <= bound);
+      if ((m[0] | m[1] | m[2] | m[3]) != 0) {
+        uint32_t to = n_c;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) to = lanes_below_plus(m[e], to);
+        const uint32_t j = j0 + g * kGroup + lane * 4;
+        if (n_c + kGroup <= cap + (uint32_t)kWave) {  // (whatever the group holds fits: n_c < 64 and cap >= 256)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            NsSlot* s = slot + (lane_in(m[e]) ? to : idle);
+            s->j = j + e;
+            s->t = (int32_t)L.ring[q][e];
+            to += lane_in(m[e]) ? 1u : 0u;
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (lane_in(m[e])) {
+              if (to < cap) {
+                slot[to].j = j + e;
+                slot[to].t = (int32_t)L.ring[q][e];
+              }
+              ++to;
+            }
+          }
+        }
+        n_c = (uint32_t)__builtin_amdgcn_readlane((int)to, kWave - 1);
+      }
+      L.ring[q] = L.in.group(g + kNsGroups);
+    }
+  }
+  const uint32_t tail = L.n & ~(kGroup - 1);
+#pragma unroll
+  for (uint32_t q = 0; q < 4; ++q) {
+    const uint32_t at = tail + q * kWave;
+    if (at >= L.n) return n_c;
+    const uint64_t m = compare_mask(ns_uniform(K, L.rest[q]) <= bound) & low_lanes(L.n - at);
+    const uint32_t to = lanes_below_plus(m, n_c);
+    n_c += (uint32_t)__popcll(m);
+    if (lane_in(n_c <= cap ? m : 0ull)) {
+      slot[to].j = j0 + at + lane;
+      slot[to].t = (int32_t)L.rest[q];
+    }
+  }
+  return n_c;
+}
+
+// The same with c > 0.  The variate of an entry is evaluated exactly only if the integer bounds and then the fp32 blend cannot
+// rule it out; the survivors of the integer bounds are evaluated 64 at a time.  The candidates are in no particular order.
+// STAGED: the exact evaluation is left to a later kernel; everything that the fp32 blend cannot rule out
 // is stored as a candidate (variate 0).
 // (not inlined: see k_ns_redo)
 __device__ __attribute__((noinline)) uint32_t ns_exact_variate(uint32_t u1, uint32_t u2, double cw, double sw) {
   return kit_phi_to_u32(__builtin_fma(cw, kit_phi_inv_u32(u1), sw * kit_phi_inv_u32(u2)));
 }
-template <bool BLEND, bool VEC4, bool STAGED = false>
+template <bool VEC4, bool STAGED = false>
 __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_indices, int64_t beg, uint32_t d, uint32_t bound,
                                                const NsBlendThr& bt, const VariateParams& vp, uint32_t sigma_a, uint32_t sigma_b,
-                                               uint64_t* __restrict__ cand_key, int32_t* __restrict__ cand_t, uint32_t cap,
-                                               NsQueue* __restrict__ q) {
+                                               NsSlot* __restrict__ slot, uint32_t cap, NsQueue* __restrict__ q) {
   const uint32_t lane = (uint32_t)lane_id();
   uint32_t n_c = 0;
   auto append = [&](bool in, uint32_t r, uint32_t j, int32_t t) {
@@ -159,14 +262,13 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
     if (mask == 0) return;
     const uint32_t p = n_c + lanes_below(mask);
     if (in && p < cap) {
-      uint32_t* half = reinterpret_cast<uint32_t*>(cand_key + p);  // two 32-bit stores: no register pair needed in the hot loop
-      half[0] = j;
-      half[1] = r;
-      cand_t[p] = t;
+      slot[p].j = j;
+      slot[p].r = r;
+      slot[p].t = t;
     }
     n_c += (uint32_t)__popcll(mask);
   };
-  // ---- blended path: queue, and evaluation of its first n entries --------------------------------------------------
+  // ---- the queue, and evaluation of its first n entries
   uint32_t qn = 0;
   const float cwf = (float)vp.cw, swf = (float)vp.sw;
   auto evaluate = [&](uint32_t n) {
@@ -209,23 +311,14 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
       __builtin_amdgcn_wave_barrier();
     }
   };
-  // first look at one entry: its variate (c = 0) or the integer bounds on its two uniforms (c > 0; without their last fold,
-  // and the bounds rounded up to whole upper halves, so that nothing is lost: keyed_exact finishes the passers')
+  // first look at one entry: the integer bounds on its two uniforms (without their last fold, and the bounds rounded up to
+  // whole upper halves, so that nothing is lost: keyed_exact finishes the passers')
   auto first_look = [&](bool valid, int32_t t, uint32_t& r, uint32_t& u2) -> bool {
     const uint32_t folded = fold16((uint32_t)t);
-    if constexpr (!BLEND) {
-      r = keyed_from_head<true>(vp.K.Ka, folded, sigma_a);
-      return valid & (r <= bound);
-    } else {
-      r = keyed_rough<true>(vp.K.Ka, folded, sigma_a);
-      u2 = keyed_rough<true>(vp.K.Kb, folded, sigma_b);
-      const uint32_t lo = r < u2 ? r : u2, hi = r < u2 ? u2 : r;
-      return valid & ((lo <= (bt.a1 | 0xFFFFu)) | ((lo <= (bt.a2 | 0xFFFFu)) & (hi <= (bt.b2 | 0xFFFFu))));
-    }
-  };
-  auto take = [&](bool flag, int32_t t, uint32_t j, uint32_t r, uint32_t u2) {
-    if constexpr (!BLEND) append(flag, r, j, t);
-    else enqueue(flag, t, j, r, u2);
+    r = keyed_rough<true>(vp.K.Ka, folded, sigma_a);
+    u2 = keyed_rough<true>(vp.K.Kb, folded, sigma_b);
+    const uint32_t lo = r < u2 ? r : u2, hi = r < u2 ? u2 : r;
+    return valid & ((lo <= (bt.a1 | 0xFFFFu)) | ((lo <= (bt.a2 | 0xFFFFu)) & (hi <= (bt.b2 | 0xFFFFu))));
   };
 
   if (!VEC4 || d <= (uint32_t)kWave) {
@@ -235,7 +328,7 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
       if (j < d) t = g_indices[beg + j];
       uint32_t r = 0, u2 = 0;
       const bool flag = first_look(j < d, t, r, u2);
-      take(flag, t, j, r, u2);
+      enqueue(flag, t, j, r, u2);
     }
   } else {
     constexpr uint32_t kStep = kWave * 4 * kNsGroups;
@@ -245,18 +338,7 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
     const uint32_t vec_end = total & ~3u;          // whole groups end here
     const uint32_t vec_beg = head ? 4u : 0u;       // whole groups start here
     const int32_t* __restrict__ p = g_indices + abeg;
-    // the loads of the next step are issued before this step's entries are hashed
-    i32x4 nbuf[kNsGroups];
-    auto fetch = [&](uint32_t at) {
-#pragma unroll
-      for (int gq = 0; gq < kNsGroups; ++gq) {
-        const uint32_t r = at + (uint32_t)(gq * kWave * 4) + lane * 4;
-        nbuf[gq] = i32x4{0, 0, 0, 0};
-        if (r < vec_end) nbuf[gq] = __builtin_nontemporal_load(reinterpret_cast<const i32x4*>(p + r));
-      }
-    };
-    // (not with c > 0: the blended path needs the registers more than the overlap)
-    if (!BLEND && vec_beg < vec_end) fetch(vec_beg);
+    // (no loads of the next step before this step's entries are hashed, as with c = 0: the registers are needed more)
     // the ragged ends (lanes 0..2: the entries in front of the first whole group; lanes 3..5: those behind the last one) are
     // requested now, not when the whole groups are done, so that a short list waits for memory once
     const uint32_t end_pos = lane < 3 ? head + lane : vec_end + (lane - 3);
@@ -264,15 +346,15 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
     int32_t end_t = 0;
     if (end_valid) end_t = p[end_pos];
     for (uint32_t base = vec_beg; base < vec_end; base += kStep) {
-      if (BLEND) fetch(base);
       i32x4 buf[kNsGroups];
       bool ok[kNsGroups];
 #pragma unroll
       for (int gq = 0; gq < kNsGroups; ++gq) {
-        buf[gq] = nbuf[gq];
-        ok[gq] = base + (uint32_t)(gq * kWave * 4) + lane * 4 < vec_end;
+        const uint32_t r = base + (uint32_t)(gq * kWave * 4) + lane * 4;
+        ok[gq] = r < vec_end;
+        buf[gq] = i32x4{0, 0, 0, 0};
+        if (ok[gq]) buf[gq] = __builtin_nontemporal_load(reinterpret_cast<const i32x4*>(p + r));
       }
-      if (!BLEND && base + kStep < vec_end) fetch(base + kStep);
       auto group = [&](int gq, bool valid) {
         const uint32_t r = base + (uint32_t)(gq * kWave * 4) + lane * 4;
         uint32_t R[4], U2[4];
@@ -285,7 +367,7 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
         }
         if (ballot64(any) != 0) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) take(flag[e], buf[gq][e], r + e - head, R[e], U2[e]);
+          for (int e = 0; e < 4; ++e) enqueue(flag[e], buf[gq][e], r + e - head, R[e], U2[e]);
         }
       };
 #pragma unroll
@@ -297,84 +379,153 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
     {  // the ragged ends
       uint32_t r = 0, u2 = 0;
       const bool flag = first_look(end_valid, end_t, r, u2);
-      take(flag, end_t, end_pos - head, r, u2);
+      enqueue(flag, end_t, end_pos - head, r, u2);
     }
   }
-  if constexpr (BLEND) {
-    if (qn != 0) evaluate(qn);
-    __builtin_amdgcn_wave_barrier();
-  }
+  if (qn != 0) evaluate(qn);
+  __builtin_amdgcn_wave_barrier();
   return n_c;
 }
 
 // The k smallest by (variate, list position) among the n_c candidates in LDS (k <= n_c <= cap), written to the edge arrays
 // from o on in adjacency order: every candidate's rank among the candidates is counted, ranks below k are kept, and a
 // kept candidate's place is the number of kept candidates in front of it in the list.
-__device__ __forceinline__ void ns_rank_write(uint32_t n_c, uint32_t k, const uint64_t* cand_key, uint32_t* cand_k, const int32_t* cand_t,
-                                              int64_t o, int64_t beg, int32_t* __restrict__ col_global, int64_t* __restrict__ eid) {
+//
+// One candidate per lane, its key at hand; slots up to the next multiple of four behind the n candidates are there.  Every lane
+// reads the keys one after the other from LDS (the same address for all lanes: a broadcast), two vector instructions per
+// candidate where reading variate and position out of the other lanes' registers cost seven.
+__device__ __forceinline__ uint32_t ns_rank(uint32_t n, const NsSlot* slot, uint64_t my_key) {
+  uint32_t rank = 0;
+  const uint32_t n_u = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
+  for (uint32_t q = 0; q < n_u; q += 4)
+#pragma unroll
+    for (uint32_t e = 0; e < 4; ++e) rank += slot_key(slot + q + e) < my_key;
+  return rank;
+}
+// fills the slots behind the n candidates up to a multiple of four with keys above all others (n <= 64)
+__device__ __forceinline__ void ns_pad(uint32_t n, NsSlot* slot) {
+  const uint32_t lane = (uint32_t)lane_id();
+  if (lane < 4) slot[n + lane].j = slot[n + lane].r = 0xFFFFFFFFu;
+}
+__device__ __forceinline__ uint32_t ns_rank_of(uint32_t n_c, const NsSlot* slot, uint64_t my_key) {
+  uint32_t rank = 0;
+  for (uint32_t q = 0; q < n_c; ++q) rank += slot_key(slot + q) < my_key;
+  return rank;
+}
+__device__ __forceinline__ void ns_rank_write_many(uint32_t n_c, uint32_t k, NsSlot* slot, int64_t o, int64_t beg, int32_t* __restrict__ col_global,
+                                                   int64_t* __restrict__ eid) {
+  const uint32_t lane = (uint32_t)lane_id();
+  for (uint32_t i = lane; i < n_c; i += kWave) {
+    slot[i].keep = ns_rank_of(n_c, slot, slot_key(slot + i)) < k;
+  }
+  __builtin_amdgcn_wave_barrier();
+  __threadfence_block();
+  for (uint32_t i = lane; i < n_c; i += kWave) {
+    if (!slot[i].keep) continue;
+    const uint32_t my_j = slot[i].j;
+    uint32_t place = 0;
+    for (uint32_t q = 0; q < n_c; ++q) place += slot[q].keep && slot[q].j < my_j;
+    col_global[o + place] = slot[i].t;
+    eid[o + place] = beg + my_j;
+  }
+}
+// The lanes of the k smallest r among those of `has` (popcount > k >= 1), or 0 where equal variates stand across the border.  The
+// variates of a shrinking set of lanes are tried as the border, two vector instructions each, four tries for 18 lanes: ranking
+// all of them takes two per lane.
+__device__ __forceinline__ uint64_t ns_smallest(uint32_t r, uint64_t has, uint32_t k) {
+  uint64_t open = has, upto;  // the k-th smallest is one of `open`
+  for (;;) {
+    const uint32_t border = (uint32_t)__builtin_amdgcn_readlane((int)r, __builtin_ctzll(open));
+    const uint64_t below = compare_mask(r < border) & has;
+    upto = compare_mask(r <= border) & has;
+    if ((uint32_t)__popcll(below) >= k) open &= below;
+    else if ((uint32_t)__popcll(upto) < k) open &= ~upto;
+    else return (uint32_t)__popcll(upto) == k ? upto : 0ull;
+  }
+}
+// (after ns_collect_plain: the candidates stand in list order, and their variates are evaluated here)
+__device__ __forceinline__ void ns_rank_write_plain(uint32_t n_c, uint32_t k, const NsKeys& K, NsSlot* slot, int64_t o, int64_t beg, int32_t* __restrict__ col_global,
+                                                    int64_t* __restrict__ eid) {
   const uint32_t lane = (uint32_t)lane_id();
   __builtin_amdgcn_wave_barrier();
   __threadfence_block();
   if (n_c <= (uint32_t)kWave) {
-    // the usual case: one candidate per lane; every lane reads the keys one after the other from LDS (the same address
-    // for all lanes: a broadcast), two vector instructions per candidate where reading variate and position out of the
-    // other lanes' registers cost seven
-    const bool has = lane < n_c;
-    const uint64_t my_key = has ? cand_key[lane] : ~0ull;
-    const uint32_t my_j = (uint32_t)my_key;
-    const int32_t my_t = has ? cand_t[lane] : 0;
-    uint32_t rank = 0;
-    const uint32_t n_u = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_c);
-    for (uint32_t q = 0; q < n_u; ++q) rank += cand_key[q] < my_key;
-    const bool keep = has && rank < k;
-    const uint64_t kept = ballot64(keep);
-    uint32_t place = 0;  // kept candidates in front of this one in the list
-    uint64_t rest = kept;
-    while (rest != 0) {
-      const int q = __builtin_ctzll(rest);
-      rest &= rest - 1;
-      place += (uint32_t)__builtin_amdgcn_readlane((int)my_j, q) < my_j;
+    const uint32_t j = slot[lane].j;  // (cap >= 256: the slots behind the candidates are there)
+    const int32_t t = slot[lane].t;
+    uint64_t kept = low_lanes(n_c);
+    if (n_c != k) {
+      const uint32_t r = ns_uniform(K, (uint32_t)t);
+      kept = ns_smallest(r, kept, k);
+      if (kept == 0) {  // by variate and position
+        slot[lane].r = r;
+        __builtin_amdgcn_wave_barrier();
+        __threadfence_block();
+        kept = ballot64(lane < n_c && ns_rank_of(n_c, slot, ((uint64_t)r << 32) | j) < k);
+      }
     }
-    if (keep) {
-      col_global[o + place] = my_t;
-      eid[o + place] = beg + my_j;
+    if (lane_in(kept)) {
+      const uint32_t place = lanes_below(kept);
+      (col_global + o)[place] = t;
+      (eid + o)[place] = beg + j;
     }
     return;
   }
-  for (uint32_t i = lane; i < n_c; i += kWave) {
-    const uint64_t my_key = cand_key[i];
-    uint32_t rank = 0;
-    for (uint32_t q = 0; q < n_c; ++q) rank += cand_key[q] < my_key;
-    cand_k[i] = rank < k;
-  }
+  for (uint32_t i = lane; i < n_c; i += kWave) slot[i].r = ns_uniform(K, (uint32_t)slot[i].t);
   __builtin_amdgcn_wave_barrier();
   __threadfence_block();
-  for (uint32_t i = lane; i < n_c; i += kWave) {
-    if (!cand_k[i]) continue;
-    const uint32_t my_j = (uint32_t)cand_key[i];
-    uint32_t place = 0;
-    for (uint32_t q = 0; q < n_c; ++q) place += cand_k[q] && (uint32_t)cand_key[q] < my_j;
-    col_global[o + place] = cand_t[i];
+  ns_rank_write_many(n_c, k, slot, o, beg, col_global, eid);
+}
+__device__ __forceinline__ void ns_rank_write(uint32_t n_c, uint32_t k, NsSlot* slot, int64_t o, int64_t beg, int32_t* __restrict__ col_global,
+                                              int64_t* __restrict__ eid) {
+  const uint32_t lane = (uint32_t)lane_id();
+  if (n_c <= (uint32_t)kWave) ns_pad(n_c, slot);
+  __builtin_amdgcn_wave_barrier();
+  __threadfence_block();
+  if (n_c > (uint32_t)kWave) {
+    ns_rank_write_many(n_c, k, slot, o, beg, col_global, eid);
+    return;
+  }
+  const bool has = lane < n_c;
+  const uint64_t my_key = has ? slot_key(slot + lane) : ~0ull;
+  const uint32_t my_j = (uint32_t)my_key;
+  const int32_t my_t = has ? slot[lane].t : 0;
+  const bool keep = ns_rank(n_c, slot, my_key) < k && has;
+  const uint64_t kept = ballot64(keep);
+  uint32_t place = 0;  // kept candidates in front of this one in the list
+  uint64_t rest = kept;
+  while (rest != 0) {
+    const int q = __builtin_ctzll(rest);
+    rest &= rest - 1;
+    place += (uint32_t)__builtin_amdgcn_readlane((int)my_j, q) < my_j;
+  }
+  if (keep) {
+    col_global[o + place] = my_t;
     eid[o + place] = beg + my_j;
   }
 }
 
+// Block b of n, renumbered so that an XCD (blocks are dealt to the eight in turn) takes runs of 32 neighbouring numbers: what
+// neighbours read, records and offsets, then shares the cache lines of one L2.  (A bijection of 0 .. n - 1.)
+__device__ __forceinline__ uint32_t xcd_runs(uint32_t b, uint32_t n) {
+  const uint32_t whole = n & ~255u;
+  return b < whole ? (b & ~255u) | ((b & 7u) << 5) | ((b >> 3) & 31u) : b;
+}
+
 // The list of a traversal kernel's wave: the first long_blocks blocks take the queued long lists (the queue's length is read
-// from device memory), the others the destinations in order.  One list per wave and one wave per block: waves that stride
-// over many lists are not evened out by the dispatcher (fill 497 -> 531 us for 675 thousand lists).  -1: nothing to do.
-__device__ __forceinline__ int64_t ns_list_of(int64_t n_dst, int waves_per_block, int wib, const uint32_t* __restrict__ long_list,
+// from device memory), the others the destinations in order, `each` neighbouring ones.  -1: nothing to do.
+__device__ __forceinline__ int64_t ns_list_of(int64_t n_dst, int each, const uint32_t* __restrict__ long_list,
                                               const uint32_t* __restrict__ n_long, int long_blocks, bool* queued) {
   *queued = (int)blockIdx.x < long_blocks;
   int64_t w;
   if (*queued) {  // the q-th queued long list
-    const int64_t q = (int64_t)blockIdx.x * waves_per_block + wib;
+    const int64_t q = blockIdx.x;
     int64_t n_queued = (int64_t)*n_long;
     if (n_queued > n_dst) n_queued = n_dst;  // (holds by construction; keeps every access inside the queue regardless)
     if (q >= n_queued) return -1;
     // (the same in every lane; said so, or everything derived from it would be kept per lane)
     w = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)long_list[q]);
   } else {
-    w = (int64_t)((int)blockIdx.x - long_blocks) * waves_per_block + wib;
+    w = (int64_t)xcd_runs(blockIdx.x - (uint32_t)long_blocks, gridDim.x - (uint32_t)long_blocks) * each;
   }
   return w < n_dst ? w : -1;
 }
@@ -391,80 +542,132 @@ __device__ __forceinline__ int64_t ns_list_of(int64_t n_dst, int waves_per_block
 // wave): k_ns_count queues them, the waves of the first long_blocks blocks of the grid take one queued list each (the
 // queue's length is read from device memory), and the other blocks take the destinations in order and skip the queued
 // ones.
-template <bool BLEND, bool VEC4>
-__device__ __forceinline__ void ns_fill_one(int64_t w, int wib, uint32_t* lds_words, NsQueue* queue, const int32_t* __restrict__ g_indices,
+
+// The next bound to try for a list that turned up n_c candidates, fewer than k or more than cap (false: there is none)
+__device__ __forceinline__ bool ns_next_bound(uint32_t n_c, uint32_t k, uint32_t* lo, uint32_t* hi, uint32_t* bound) {
+  if (n_c < k) {
+    if (*bound == 0xFFFFFFFFu) return false;
+    *lo = *bound + 1;
+  } else {  // cannot be bracketed (more than cap - k equal variates): report instead of guessing
+    if (*bound == 0) return false;
+    *hi = *bound - 1;
+  }
+  if (*lo > *hi) return false;
+  // too few and no upper failure yet: double the bound (a midpoint of the whole range would flood the buffer)
+  if (*hi == 0xFFFFFFFFu && n_c < k) *bound = *bound < 0x7FFFFFFFu ? 2 * *bound + 1 : 0xFFFFFFFFu;
+  else *bound = *lo + (*hi - *lo) / 2;
+  return true;
+}
+
+// c = 0.  A wave takes `each` neighbouring destinations (at most 64; the dispatcher starts one-wave blocks at some 5 per ns, 150 us
+// for 745 thousand that do nothing).  Their records come in one load, a destination per lane; lists no longer than the fanout
+// are copied together, 64 / each lanes for each; the others go one after the other through the whole wave, the next one's entries
+// requested before this one's candidates are selected.  Last layer of a quarter of the papers100M shape, 717 thousand
+// destinations, 380 M entries: 494 us with a wave for each, 225 M vector and 191 M scalar instructions; 400 now, with 144 M
+// and 159 M (the entries alone, at the rate of a copy: 310).
+__global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict__ g_indices, const NsRecord* __restrict__ rec, uint32_t n_dst, uint32_t k,
+                                                    uint32_t cap, LayerKeys keys, const int64_t* __restrict__ eptr,
+                                                    int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl,
+                                                    uint32_t long_min, const uint32_t* __restrict__ long_list,
+                                                    const uint32_t* __restrict__ n_long, int long_blocks, int each_log2) {
+  extern __shared__ __align__(16) uint32_t lds_words[];  // cap slots, and one per lane
+  NsSlot* slot = reinterpret_cast<NsSlot*>(lds_words);
+  const uint32_t lane = (uint32_t)lane_id();
+  uint32_t w0, n_mine = 1, skip_above = 0xFFFFFFFFu;
+  if ((int)blockIdx.x < long_blocks) {  // the first blocks: a queued long list each (the queue's length is read from device memory)
+    uint32_t n_queued = *n_long;
+    if (n_queued > n_dst) n_queued = n_dst;  // (holds by construction; keeps every access inside the queue regardless)
+    if (blockIdx.x >= n_queued) return;
+    w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)long_list[blockIdx.x]);
+    each_log2 = 0;
+  } else {
+    w0 = xcd_runs(blockIdx.x - (uint32_t)long_blocks, gridDim.x - (uint32_t)long_blocks) << each_log2;
+    n_mine = 1u << each_log2;
+    if (long_min != 0) skip_above = long_min;
+  }
+  if (w0 >= n_dst) return;
+  if (n_mine > n_dst - w0) n_mine = n_dst - w0;
+  // a lane's destination: its number among the wave's in the copying below, and so, shifted, where the loop finds it
+  const uint32_t w = w0 + ((lane >> (6 - each_log2)) < n_mine ? lane >> (6 - each_log2) : n_mine - 1);
+  const NsRecord g = rec[w];
+  const int64_t o = eptr[w], o_end = eptr[w + 1];
+  const bool live = (lane >> (6 - each_log2)) < n_mine && g.d != 0 && o_end <= edge_limit;  // (no room: the caller redoes the layer)
+  if (live && g.d <= k) {
+    const uint32_t lanes = 64u >> each_log2;
+    for (uint32_t j = lane & (lanes - 1); j < g.d; j += lanes) {
+      (col_global + o)[j] = (g_indices + g.beg)[j];
+      (eid + o)[j] = g.beg + j;
+    }
+  }
+  if (k > kNsMaxSelect) return;  // degrees above a fanout that the candidate buffer cannot serve: left to k_ns_fill_wide
+  // (longer than skip_above: queued, one of the first waves takes it)
+  uint64_t todo = ballot64(live && g.d > k && g.d <= skip_above && (lane & ((64u >> each_log2) - 1)) == 0);
+  if (todo == 0) return;
+  auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
+  auto of64 = [&](int64_t x, int q) { return (int64_t)(((uint64_t)of((uint32_t)((uint64_t)x >> 32), q) << 32) | of((uint32_t)x, q)); };
+  int at = __builtin_ctzll(todo);
+  uint32_t d = of(g.d, at), bound = of(g.bound, at), mid = of(g.mid, at);
+  int64_t beg = of64(g.beg, at), o_this = of64(o, at);
+  uint32_t lo = 0, hi = 0xFFFFFFFFu, attempt = 0;  // bisection bracket on the bound, used only after a failed pass
+  uint32_t j0 = 0, n_c = 0;                        // entries looked at in earlier stretches of the list, candidates so far
+  const uint32_t head = vector_copy(keys.Ka[4]), tail = vector_copy(keys.Ka[3]);
+  for (NsList L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+    const NsKeys K{head, vector_copy(mid), tail};
+    n_c = ns_collect_plain(L, j0, bound, K, slot, cap, n_c);
+    const uint32_t found = n_c;
+    const int64_t o_done = o_this, beg_done = beg;
+    bool select = false;
+    if (d - j0 > kStretch) {  // the list's next stretch
+      j0 += kStretch;
+    } else if ((n_c < k || n_c > cap) && ++attempt < 40 && ns_next_bound(n_c, k, &lo, &hi, &bound)) {  // the list once more
+      j0 = n_c = 0;
+    } else {  // the next list
+      select = n_c >= k && n_c <= cap;
+      if (!select && lane == 0) atomicOr(&ctl->err_capacity, 1);
+      todo &= todo - 1;
+      at = todo != 0 ? __builtin_ctzll(todo) : 0;
+      d = todo != 0 ? of(g.d, at) : 0u;
+      bound = of(g.bound, at);
+      mid = of(g.mid, at);
+      beg = of64(g.beg, at);
+      o_this = of64(o, at);
+      lo = j0 = n_c = attempt = 0;
+      hi = 0xFFFFFFFFu;
+    }
+    L = NsList(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+    if (select) ns_rank_write_plain(found, k, K, slot, o_done, beg_done, col_global, eid);
+    if (todo == 0) break;
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// c > 0: one destination with exact variates
+template <bool VEC4>
+__device__ __forceinline__ void ns_redo_one(int64_t w, int wib, uint32_t* lds_words, NsQueue* queue, const int32_t* __restrict__ g_indices,
                                             const NsRecord* __restrict__ rec, const NsBlendThr* __restrict__ bthr, uint32_t k, uint32_t cap,
                                             const VariateParams& vp, const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
-                                            int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl, uint32_t skip_above) {
-  const uint32_t lane = (uint32_t)lane_id();
+                                            int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl) {
   const int64_t o = eptr[w];
-  if (eptr[w + 1] > edge_limit) return;  // the wave writes [o, eptr[w + 1]) only; no room: the caller redoes the layer
+  if (eptr[w + 1] > edge_limit) return;
   const NsRecord g = rec[w];
-  const int32_t s = g.s;
-  const int64_t beg = g.beg;
-  const uint32_t d = g.d;
-  if (d == 0) return;
-  if (d <= k) {
-    for (uint32_t j = lane; j < d; j += kWave) {
-      col_global[o + j] = g_indices[beg + j];
-      eid[o + j] = beg + j;
-    }
-    return;
-  }
-  if (d > skip_above) return;    // queued: one of the first waves takes it
-  if (k > kNsMaxSelect) return;  // a degree above a fanout that the candidate buffer cannot serve: left to k_ns_fill_wide
-  uint64_t* cand_key = reinterpret_cast<uint64_t*>(lds_words + (size_t)wib * cap * 4);  // [cap] (variate, position), d < 2^31
-  uint32_t* cand_k = lds_words + (size_t)wib * cap * 4 + 2 * cap;                       // [cap] 1 = among the k smallest
-  int32_t* cand_t = reinterpret_cast<int32_t*>(cand_k + cap);                           // [cap] the neighbours themselves
-  const uint32_t sigma_a = ns_sigma(vp.K.Ka, (uint32_t)s);
-  const uint32_t sigma_b = BLEND ? ns_sigma(vp.K.Kb, (uint32_t)s) : 0u;
-
-  uint64_t lo = 0, hi = 0xFFFFFFFFull;  // bisection bracket on the bound, used only after a failed pass
-  uint64_t bound = g.bound;
-  NsBlendThr bt{0u, 0u, 0u, 0.0f};
-  if constexpr (BLEND) bt = bthr[w];
+  if (g.d <= k || k > kNsMaxSelect) return;  // (never marked)
+  NsSlot* slot = reinterpret_cast<NsSlot*>(lds_words) + (size_t)wib * cap;  // [cap]
+  const uint32_t sigma_a = ns_sigma(vp.K.Ka, (uint32_t)g.s), sigma_b = ns_sigma(vp.K.Kb, (uint32_t)g.s);
+  uint32_t lo = 0, hi = 0xFFFFFFFFu, bound = g.bound;
+  NsBlendThr bt = bthr[w];
   uint32_t n_c = 0;
   for (int attempt = 0; attempt < 40; ++attempt) {
-    n_c = ns_collect<BLEND, VEC4>(g_indices, beg, d, (uint32_t)bound, bt, vp, sigma_a, sigma_b, cand_key, cand_t, cap, queue);
+    n_c = ns_collect<VEC4>(g_indices, g.beg, g.d, bound, bt, vp, sigma_a, sigma_b, slot, cap, queue);
     if (n_c >= k && n_c <= cap) break;
-    // cannot be bracketed (more than cap - k equal variates): report instead of guessing
-    if (n_c < k) {
-      if (bound >= 0xFFFFFFFFull) { n_c = 0; break; }
-      lo = bound + 1;
-    } else {
-      if (bound == 0) { n_c = 0; break; }
-      hi = bound - 1;
-    }
-    if (lo > hi) { n_c = 0; break; }
-    // too few and no upper failure yet: double the bound (a midpoint of the whole range would flood the buffer)
-    bound = (hi == 0xFFFFFFFFull && n_c < k) ? (2 * bound + 1 < hi ? 2 * bound + 1 : hi) : lo + (hi - lo) / 2;
-    if constexpr (BLEND) bt = ns_blend_thresholds((uint32_t)bound, vp.cw, vp.sw);  // (every lane computes the same)
+    if (!ns_next_bound(n_c, k, &lo, &hi, &bound)) { n_c = 0; break; }
+    bt = ns_blend_thresholds(bound, vp.cw, vp.sw);  // (every lane computes the same)
     __builtin_amdgcn_wave_barrier();
   }
   if (n_c < k || n_c > cap) {
-    if (lane == 0) atomicOr(&ctl->err_capacity, 1);
+    if (lane_id() == 0) atomicOr(&ctl->err_capacity, 1);
     return;
   }
-  ns_rank_write(n_c, k, cand_key, cand_k, cand_t, o, beg, col_global, eid);
-}
-
-template <bool VEC4>
-__global__ __launch_bounds__(kBlock) void k_ns_fill(const int32_t* __restrict__ g_indices,
-                                                    const NsRecord* __restrict__ rec, const NsBlendThr* __restrict__ bthr,
-                                                    int64_t n_dst, uint32_t k,
-                                                    uint32_t cap, int waves_per_block, VariateParams vp,
-                                                    const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
-                                                    int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl,
-                                                    uint32_t long_min, const uint32_t* __restrict__ long_list,
-                                                    const uint32_t* __restrict__ n_long, int long_blocks) {
-  extern __shared__ __align__(16) uint32_t lds_words[];  // per wave: cap 64-bit keys, cap keep flags, cap vertex ids
-  const int wib = uniform_wave_in_block();
-  if (wib >= waves_per_block) return;
-  bool queued;
-  const int64_t w = ns_list_of(n_dst, waves_per_block, wib, long_list, n_long, long_blocks, &queued);
-  if (w < 0) return;
-  ns_fill_one<false, VEC4>(w, wib, lds_words, nullptr, g_indices, rec, bthr, k, cap, vp, eptr, col_global, eid, edge_limit, ctl,
-                           !queued && long_min != 0 ? long_min : 0xFFFFFFFFu);
+  ns_rank_write(n_c, k, slot, o, g.beg, col_global, eid);
 }
 
 // c > 0: the destinations that the two kernels below leave over.  A wave looks at 2^lists_log2 marks at once.  (Six waves per
@@ -488,7 +691,7 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_redo(const int32_t* __restrict_
   while (left != 0) {
     const int64_t w = w0 + __builtin_ctzll(left);
     left &= left - 1;
-    ns_fill_one<true, VEC4>(w, wib, lds_words, &queues[wib], g_indices, rec, bthr, k, cap, vp, eptr, col_global, eid, edge_limit, ctl, 0xFFFFFFFFu);
+    ns_redo_one<VEC4>(w, wib, lds_words, &queues[wib], g_indices, rec, bthr, k, cap, vp, eptr, col_global, eid, edge_limit, ctl);
     __builtin_amdgcn_wave_barrier();
   }
 }
@@ -516,7 +719,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_collect(const int32_t* __restrict
   if (wib >= waves_per_block) return;
   const uint32_t lane = (uint32_t)lane_id();
   bool queued;
-  const int64_t w = ns_list_of(n_dst, waves_per_block, wib, long_list, n_long, long_blocks, &queued);
+  const int64_t w = ns_list_of(n_dst, 1, long_list, n_long, long_blocks, &queued);
   if (w < 0) return;
   const NsRecord g = rec[w];
   if (!queued && long_min != 0 && g.d > long_min && g.d > k) return;  // queued: one of the first waves takes it
@@ -532,11 +735,9 @@ __global__ __launch_bounds__(kBlock) void k_ns_collect(const int32_t* __restrict
     return;
   }
   if (k > kNsMaxSelect) return;  // (k_ns_fill_wide)
-  uint64_t* cand_key = reinterpret_cast<uint64_t*>(lds_words + (size_t)wib * cap * 4);
-  int32_t* cand_t = reinterpret_cast<int32_t*>(lds_words + (size_t)wib * cap * 4 + 3 * cap);
+  NsSlot* slot = reinterpret_cast<NsSlot*>(lds_words) + (size_t)wib * cap;
   const uint32_t sigma_a = ns_sigma(vp.K.Ka, (uint32_t)g.s), sigma_b = ns_sigma(vp.K.Kb, (uint32_t)g.s);
-  const uint32_t n_c = ns_collect<true, VEC4, true>(g_indices, g.beg, g.d, g.bound, bthr[w], vp, sigma_a, sigma_b, cand_key, cand_t, cap,
-                                                    &queues[wib]);
+  const uint32_t n_c = ns_collect<VEC4, true>(g_indices, g.beg, g.d, g.bound, bthr[w], vp, sigma_a, sigma_b, slot, cap, &queues[wib]);
   __builtin_amdgcn_wave_barrier();
   __threadfence_block();
   if (n_c < k || n_c > row_cap || n_c > cap) {  // (too few even before the exact test, or no room)
@@ -544,7 +745,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_collect(const int32_t* __restrict
     return;
   }
   NsCand* row = rows + (size_t)w * row_cap;
-  for (uint32_t i = lane; i < n_c; i += kWave) row[i] = NsCand{(uint32_t)cand_key[i], cand_t[i]};
+  for (uint32_t i = lane; i < n_c; i += kWave) row[i] = NsCand{slot[i].j, slot[i].t};
   if (lane == 0) n_cand[w] = n_c;
 }
 
@@ -562,9 +763,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
   const uint32_t n = n_cand[w];
   if (n == 0 || n == kNsRedo) return;  // done by the collecting kernel, or left to k_ns_redo
   const NsRecord g = rec[w];
-  uint64_t* cand_key = reinterpret_cast<uint64_t*>(lds_words + (size_t)wib * cap * 4);
-  uint32_t* cand_k = lds_words + (size_t)wib * cap * 4 + 2 * cap;
-  int32_t* cand_t = reinterpret_cast<int32_t*>(cand_k + cap);
+  NsSlot* slot = reinterpret_cast<NsSlot*>(lds_words) + (size_t)wib * cap;
   const uint32_t sigma_a = ns_sigma(vp.K.Ka, (uint32_t)g.s), sigma_b = ns_sigma(vp.K.Kb, (uint32_t)g.s);
   const NsCand* row = rows + (size_t)w * row_cap;
   if (n <= (uint32_t)kWave) {
@@ -581,12 +780,11 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
     // that unsigned order is numeric order, and every lane reads them back as broadcasts (as in ns_rank_write)
     const uint32_t eb = __float_as_uint(est);
     const uint64_t est_key = ((uint64_t)(eb ^ ((uint32_t)((int32_t)eb >> 31) | 0x80000000u)) << 32) | lane;
-    if (has) cand_key[lane] = est_key;
+    if (has) { slot[lane].j = lane; slot[lane].r = (uint32_t)(est_key >> 32); }
+    ns_pad(n, slot);
     __builtin_amdgcn_wave_barrier();
     __threadfence_block();
-    uint32_t rank_est = 0;
-    const uint32_t n_u = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
-    for (uint32_t q = 0; q < n_u; ++q) rank_est += cand_key[q] < est_key;
+    const uint32_t rank_est = ns_rank(n, slot, est_key);
     const uint64_t kth = ballot64(has && rank_est == k - 1);  // exactly one lane (n >= k)
     const float e_k = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(est), __builtin_ctzll(kth)));
     const float allow = (float)((vp.cw + vp.sw) * kPhiInvF32Allow + 2.0 * kBlendAbsWiden);
@@ -646,14 +844,14 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
     }
     const uint64_t mask = ballot64(in);
     const uint32_t at = n_c + lanes_below(mask);
-    if (in) { cand_key[at] = ((uint64_t)R << 32) | c.j; cand_t[at] = c.t; }  // (n <= cap)
+    if (in) { slot[at].j = c.j; slot[at].r = R; slot[at].t = c.t; }  // (n <= cap)
     n_c += (uint32_t)__popcll(mask);
   }
   if (n_c < k) {
     if (lane == 0) n_cand[w] = kNsRedo;
     return;
   }
-  ns_rank_write(n_c, k, cand_key, cand_k, cand_t, eptr[w], g.beg, col_global, eid);
+  ns_rank_write(n_c, k, slot, eptr[w], g.beg, col_global, eid);
 }
 
 // ---- fanouts above kNsMaxSelect ----------------------------------------------------------------------------------
@@ -762,7 +960,7 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
   if (alloc.failed) return COOP_E_NOMEM;
 #define COOP_NS_COUNT(BLOCK, EACH)                                                                                                             \
   COOP_LAUNCH(K_NS_COUNT, (k_ns_count<BLOCK, EACH>), dim3(blocks_for(n_dst, BLOCK * EACH)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices, \
-              dst, n_dst, k, target, cnt, rec, bthr, cx.cw, cx.sw, cx.d_ctl, long_min, long_list, n_long)
+              dst, n_dst, k, target, cnt, rec, bthr, vp.K, cx.cw, cx.sw, cx.d_ctl, long_min, long_list, n_long)
   if (n_dst >= kNsCountWideFrom && !cx.blend) COOP_NS_COUNT(1024, 2);
   else if (n_dst >= 16384 || (n_dst > 0 && !cx.blend)) COOP_NS_COUNT(kBlock, 1);
   else if (n_dst > 0) COOP_NS_COUNT(kWave, 1);
@@ -825,10 +1023,11 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
         if (cx.vec4) { COOP_NS_BLEND(true); } else { COOP_NS_BLEND(false); }
 #undef COOP_NS_BLEND
       } else {
-        if (cx.vec4) COOP_LAUNCH(K_NS_FILL, k_ns_fill<true>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
-                                 (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
-        else COOP_LAUNCH(K_NS_FILL, k_ns_fill<false>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, long_min,
-                         (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);
+        int each_log2 = 0;
+        while (each_log2 < 3 && (n >> (each_log2 + 1)) >= kNsFillWaves) ++each_log2;
+        COOP_LAUNCH(K_NS_FILL, k_ns_fill, dim3(blocks_for(n, (int64_t)1 << each_log2) + (unsigned)long_blocks), dim3(kWave),
+                    (cap + kWave) * sizeof(NsSlot), s, cx.g->indices, rec_b, (uint32_t)n, k, cap, vp.K, eptr_b, blk->col_global, blk->eid, m,
+                    cx.d_ctl, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2);
       }
 #undef COOP_NS_ARGS
       if (k > kNsMaxSelect) {  // the lists longer than such a fanout (the kernels above skip them)

@@ -75,6 +75,25 @@ inline void philox4x32_10(const uint32_t ctr[4], const uint32_t key[2], uint32_t
   out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
+// What the vector pipes of gfx950 charge (measured with 8 independent chains per wave, all SIMDs busy, 10^9 wave instructions a
+// second): xor, shift right, mul_f32, fma, bitop3 900 to 1,000; mul_lo, compare, min, max, anything SDWA or with a scalar
+// register as operand 510 to 580.  So the traversals keep their key words in vector registers (vector_copy), and write
+// x ^ (x >> 16) ^ key as a shift and a three-way xor: two full-rate instructions in the place of an SDWA xor with a scalar key
+// and another xor, three.
+__device__ __forceinline__ uint32_t vector_copy(uint32_t x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm("" : "+v"(x));
+#endif
+  return x;
+}
+__device__ __forceinline__ uint32_t fold16_xor(uint32_t x, uint32_t key) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_bitop3_b32(x >> 16, x, key, 0x96);
+#else
+  return fold16(x) ^ key;
+#endif
+}
+
 inline void layer_keys(uint64_t seed, int sampler, int layer, uint64_t g, uint32_t K[5]) {
   const uint32_t ctr[4] = {(uint32_t)g, (uint32_t)(g >> 32), (uint32_t)layer | ((uint32_t)sampler << 8), 0x434F4F50u};
   const uint32_t key[2] = {(uint32_t)seed, (uint32_t)(seed >> 32)};
@@ -295,6 +314,12 @@ __device__ __forceinline__ uint32_t keyed_rough(const uint32_t K[5], uint32_t he
 // U from keyed_rough's value
 template <bool NS>
 __device__ __forceinline__ uint32_t keyed_exact(const uint32_t K[5], uint32_t rough) { return rough ^ ((rough ^ (NS ? K[3] : K[1])) >> 16); }
+// the NS uniform, its three key words (K[4], fold16(K[1] ^ sigma), K[3]) at hand
+struct NsKeys { uint32_t head, mid, tail; };
+__device__ __forceinline__ uint32_t ns_mid(const uint32_t K[5], uint32_t sigma) { return fold16(K[1] ^ sigma); }
+__device__ __forceinline__ uint32_t ns_uniform(const NsKeys& K, uint32_t t) {
+  return fold16_xor(mix_body(mix_body(fold16_xor(t, K.head)) ^ K.mid), K.tail);
+}
 template <bool NS>
 __device__ __forceinline__ uint32_t keyed_from_head(const uint32_t K[5], uint32_t head, uint32_t sigma) {
   const uint32_t m = mix_body(head ^ K[4]);

@@ -1051,6 +1051,33 @@ def test_ns_lists_left_over_looked_for_several_at_a_time(P, aligned):
         compare(P, g, v[:size], (10,), R.NS, it=5, kappa=16, seed=size)
 
 
+@pytest.mark.parametrize("aligned", [True, False])
+def test_ns_lists_around_the_edges_of_groups(P, aligned):
+    """c = 0: lists of one entry less than, as many as and one more than 64 q entries, of whole groups of 256 with and without a
+    rest and of more groups than are in flight, starting at any alignment, among short ones; waves that take one, two and
+    eight destinations, the last of them fewer; and lists whose neighbours repeat, so that equal variates stand across the border
+    of the k smallest."""
+    n = 140000
+    rng = np.random.default_rng(11)
+    deg = rng.integers(0, 14, n)
+    edges = np.array([e for q in (1, 2, 3, 4, 5, 8, 12, 16, 20, 21, 32, 36, 64) for e in (64 * q - 1, 64 * q, 64 * q + 1)])
+    at = np.arange(97, n, 389)
+    deg[at] = edges[np.arange(len(at)) % len(edges)]
+    ties = np.arange(200, n, 1013)
+    deg[ties] = 40
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    indices = rng.integers(0, n, int(indptr[-1])).astype(np.int32)
+    for v in ties:
+        indices[indptr[v]:indptr[v + 1]] = v % 1000 + np.arange(40) % 3
+    g = G(P, torch.from_numpy(indptr), torch.from_numpy(indices))
+    if not aligned:
+        base = torch.empty(len(indices) + 1, dtype=torch.int32, device="cuda")
+        base[1:] = g.indices_d
+        g.graph = P.coop_graph_load(g.indptr_d, base[1:], P.COOP_VALIDATE)
+    for size, k in ((5000, 10), (32769, 25), (70001, 5), (131075, 10)) if aligned else ((131075, 10),):
+        compare(P, g, np.arange(size), (k,), R.NS, seed=size)
+
+
 def test_ns_count_in_wide_blocks(P):
     """From 262,144 destinations on the counting blocks take 2,048 each: a number of destinations that is no multiple of that,
     with long lists (queued from 64 entries on) at both ends of blocks and with lists without entries."""
