@@ -105,20 +105,21 @@ struct Publish {
   uint64_t ticket = 0;
 };
 
-// Device-wide exclusive scans; `tmp` needs scan_tmp_bytes(n) bytes.  out has n + 1 entries, out[n] = total;
-// the total also goes to *total_out (device) when that is not null.  With `pub`, the thread that stores the total then
-// publishes the control block (total_out normally points into it), which saves the read-back a kernel of its own.
-size_t scan_tmp_bytes(int64_t n);
-void scan_i32_to_i64(const int32_t* in, int64_t n, int64_t* out, int64_t* total_out, void* tmp, hipStream_t s,
-                     const Publish* pub = nullptr);
-// the same over an input that lies in up to four pieces: element i is ptr[p][i - start[p]] for the last p with start[p] <= i
+// int32 counts in up to four pieces: element i is ptr[p][i - start[p]] for the last p with start[p] <= i
 struct ChunkedI32 {
   const int32_t* ptr[4];
   int64_t start[4];
   int n_chunks;
 };
-void scan_chunks_to_i64(const ChunkedI32& in, int64_t n, int64_t* out, int64_t* total_out, void* tmp, hipStream_t s,
-                        const Publish* pub = nullptr);
+// Exclusive scan of n counts by the kernel that uses the offsets (device_utils.h, CountOffsets): up to kScanOwn counts nothing
+// comes before it; for more, this one launch leaves in out the offset of every tile's first element, inside its tile in the
+// place of the others', and the total in out[n] and *total_out; a consumer adds the two and writes the sum back.  With `pub` the
+// thread that stores the total then publishes the control block, which saves the read-back a kernel of its own.
+constexpr int64_t kScanOwn = 32768;
+constexpr int kOffsetTileLog2 = 12;
+void scan_tiles(const ChunkedI32& in, int64_t n, int64_t* out, int64_t* total_out, Ctl* ctl, hipStream_t s, const Publish* pub = nullptr);
+// Device-wide exclusive scans; `tmp` needs scan_tmp_bytes(n) bytes.
+size_t scan_tmp_bytes(int64_t n);
 // exclusive scan of n uint32 (sum below 2^32); out has n + 1 entries, the last one the total
 void scan_u32_to_u32(const uint32_t* in, int64_t n, uint32_t* out, void* tmp, hipStream_t s);
 void scan_popc_to_u32(const uint64_t* bits, int64_t n_words, uint32_t* out, int64_t* total_out, void* tmp, hipStream_t s);
@@ -189,7 +190,11 @@ struct UniqueWork {
   int path = 0;
   Publish pub{};
   int64_t n_new = 0;
+  uint64_t* clear = nullptr;         // words that must be zero before `launch`; whoever clears them on the way sets this to null
+  int64_t n_clear = 0;
 };
+// prepare: decides how the list is deduplicated and allocates the words of new-vertex bits.
+int unique_prepare(int64_t n_dst, int64_t m, UniqueWork* w, Alloc& alloc);
 // launch: every kernel of the front half; one of them sends the sizes to the host; does not wait.  col_local (m entries)
 // holds intermediate results until `back` has run, and so does `spare` (n_dst + m entries, e.g. the array that will be
 // src_ids) when it is not null.

@@ -76,6 +76,123 @@ __device__ __forceinline__ bool tally_last(Ctl* ctl, uint32_t add, uint32_t* tot
   return tally_last(&reinterpret_cast<DeviceCtl*>(ctl)->tally, add, total);
 }
 
+// inclusive scan over the block of one int64 per thread, WAVES waves; *total = the block's sum
+template <int WAVES>
+__device__ __forceinline__ int64_t block_incl_scan_i64(int64_t v, int64_t* total, int64_t* lds /* [WAVES] */) {
+  const int lane = lane_id(), w = wave_in_block();
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int64_t o = __shfl_up(v, off, kWave);
+    if (lane >= off) v += o;
+  }
+  if (lane == kWave - 1) lds[w] = v;
+  __syncthreads();
+  int64_t base = 0, tot = 0;
+#pragma unroll
+  for (int i = 0; i < WAVES; ++i) {
+    const int64_t x = lds[i];
+    if (i < w) base += x;
+    tot += x;
+  }
+  __syncthreads();
+  *total = tot;
+  return v + base;
+}
+
+// what a one-thread publishing kernel would do, done by a thread that has just stored what the host waits for
+__device__ __forceinline__ void publish_ctl(const Publish& pub) {
+  if (pub.h == nullptr) return;
+  pub.h->ctl = *pub.d_ctl;
+  __threadfence_system();
+  __hip_atomic_store(&pub.h->ticket, pub.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Tile by tile: out holds, for the first element of every tile of 2^log2 elements, the tile's sum (stored by tile_sum_done), and
+// the last block turns these sums into offsets.  The whole block calls it.
+template <int WAVES>
+__device__ __forceinline__ int64_t scan_tile_sums(int64_t n, int log2, int64_t* out, int64_t* lds) {
+  const int64_t tiles = (n + ((int64_t)1 << log2) - 1) >> log2;
+  int64_t carry = 0;
+  for (int64_t first = 0; first < tiles; first += WAVES * kWave) {
+    const int64_t t = first + threadIdx.x;
+    const int64_t v = t < tiles ? __hip_atomic_load(&out[t << log2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    int64_t all;
+    const int64_t upto = block_incl_scan_i64<WAVES>(v, &all, lds);
+    if (t < tiles) out[t << log2] = carry + upto - v;
+    carry += all;
+  }
+  return carry;
+}
+// one thread per block: leaves the tile's sum where its first element's offset belongs; true in the block that is last
+__device__ __forceinline__ bool tile_sum_done(int64_t sum, int64_t* first, Ctl* ctl) {
+  // the exchange has been performed when its result is here; the block counts itself behind it
+  const unsigned long long old = atomicExch(reinterpret_cast<unsigned long long*>(first), (unsigned long long)sum);
+  asm volatile("" : : "v"(old) : "memory");
+  uint32_t unused;
+  return tally_last(ctl, 0u, &unused);
+}
+
+// Where a destination's entries go, found by the kernel that puts them there: 1 << LOG2 neighbouring lanes for a destination,
+// blocks of BLOCK threads, destinations dealt to the blocks in order from `first` on.  OWN: from the counts alone, every block adding
+// up those in front of it (at most kScanOwn: 128 KB out of L2); 16 thousand 3 us more in this kernel in the place of two launches of
+// 5.  Else what scan_tiles left.  Either way the offsets leave in indptr.
+struct CountOffsets {
+  ChunkedI32 cnt;
+  int64_t* indptr;
+  int64_t* total_out;
+};
+template <bool OWN, int BLOCK, int LOG2>
+__device__ __forceinline__ int64_t offset_of(const CountOffsets& co, int64_t w, int64_t n_dst, int32_t* count) {
+  const bool live = w < n_dst, speaks = live && (threadIdx.x & ((1 << LOG2) - 1)) == 0;
+  int p = 0;
+#pragma unroll
+  for (int q = 1; q < 4; ++q)
+    if (q < co.cnt.n_chunks && w >= co.cnt.start[q]) p = q;
+  *count = live ? co.cnt.ptr[p][w - co.cnt.start[p]] : 0;
+  if constexpr (OWN) {
+    constexpr int kWaves = BLOCK / kWave;
+    __shared__ int64_t lds[2 * kWaves];
+    const int64_t w0 = (int64_t)blockIdx.x * (BLOCK >> LOG2);
+    int64_t part = 0;
+    for (int q = 0; q < co.cnt.n_chunks; ++q) {
+      const int64_t hi = q + 1 < co.cnt.n_chunks && co.cnt.start[q + 1] < w0 ? co.cnt.start[q + 1] : w0;
+#pragma unroll 4
+      for (int64_t i = co.cnt.start[q] + threadIdx.x; i < hi; i += BLOCK) part += co.cnt.ptr[q][i - co.cnt.start[q]];
+    }
+    part = wave_sum_i64(part);
+    const int64_t mine = speaks ? *count : 0;
+    int64_t upto = mine;
+#pragma unroll
+    for (int off = 1 << LOG2; off < kWave; off <<= 1) {
+      const int64_t o = __shfl_up(upto, off, kWave);
+      if (lane_id() >= off) upto += o;
+    }
+    if (lane_id() == 0) lds[wave_in_block()] = part;
+    if (lane_id() == kWave - (1 << LOG2)) lds[kWaves + wave_in_block()] = upto;
+    __syncthreads();
+    int64_t o = __shfl(upto - mine, lane_id() & ~((1 << LOG2) - 1), kWave);
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) o += lds[q] + (q < wave_in_block() ? lds[kWaves + q] : 0);
+    if (speaks) {
+      co.indptr[w] = o;
+      if (w == n_dst - 1) {
+        co.indptr[n_dst] = o + *count;
+        *co.total_out = o + *count;
+      }
+    }
+    return o;
+  } else {
+    if (!live) return 0;
+    const int64_t tile = w >> kOffsetTileLog2 << kOffsetTileLog2;
+    int64_t o = co.indptr[tile];
+    if (w != tile) {
+      o += co.indptr[w];  // (read by this group of lanes only, all of one wave, and overwritten behind that)
+      if (speaks) co.indptr[w] = o;
+    }
+    return o;
+  }
+}
+
 // ---- rows moved as items of up to 16 bytes --------------------------------------------------------------------------
 // Feature rows have any even number of bytes (an odd number of fp16 columns, 602 fp32 columns, ...), and the tables any
 // 2-byte aligned base.  A row is cut into vecs = ceil(row_bytes / VB) items of VB bytes, VB the largest power of two up to

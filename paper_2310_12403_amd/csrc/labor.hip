@@ -327,6 +327,9 @@ __global__ __launch_bounds__(kWalkBlock, 6) void k_enum_walk(const int32_t* __re
 // ones, which spread over more CUs what the thresholds of a blend cost in fp64 (1,024 destinations, three layers: 13 us in
 // one block, 10 in sixteen; 110 thousand with two layers 15 and 9).
 constexpr int64_t kSegWideFrom = 65536;
+// (c > 0) The buffer of candidates for the exact blend is split into kCandSub sub-buffers with a counter each (a block appends to sub-buffer blockIdx mod
+// kCandSub): appending costs an atomic with a returned value, and a single counter would serialise them.
+constexpr int kCandSub = 256;
 template <int kSegBlock>
 __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restrict__ g_indptr, int64_t n_vertices,
                                                      const int32_t* __restrict__ dst, int64_t n, int nf,
@@ -335,7 +338,11 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
                                                      double cw, double sw, int queued, Ctl* ctl,
                                                      uint32_t piece_len, uint32_t split_min, Piece* __restrict__ pieces, uint32_t piece_cap,
                                                      uint32_t* __restrict__ piece_count, ScanOut out, uint32_t enum_degree,
-                                                     uint32_t* __restrict__ long_bits, LongSlot* __restrict__ long_tab, uint32_t long_mask) {
+                                                     uint32_t* __restrict__ long_bits, LongSlot* __restrict__ long_tab, uint32_t long_mask,
+                                                     Clear clear, uint32_t* __restrict__ cand_count /* kCandSub, set to zero; null when c = 0 */) {
+  clear_words(clear);
+  if (cand_count != nullptr && blockIdx.x == 0)
+    for (int q = threadIdx.x; q < kCandSub; q += kSegBlock) cand_count[q] = 0;
   __shared__ uint32_t s_wave_at[kSegBlock / kWave];
   __shared__ uint32_t s_base, s_total;
   const int64_t i = (int64_t)blockIdx.x * kSegBlock + threadIdx.x;
@@ -615,9 +622,6 @@ struct Cand {
   uint32_t list;   // destination, index within the pass
   uint32_t layer;  // covered layer, 0 .. NF-1
 };
-// The buffer is split into kCandSub sub-buffers with a counter each (a block appends to sub-buffer blockIdx mod
-// kCandSub): appending costs an atomic with a returned value, and a single counter would serialise them.
-constexpr int kCandSub = 256;
 struct CandOut {
   Cand* buf;          // [kCandSub][cap_each]
   uint32_t* count;    // [kCandSub] entries appended so far (may run past cap_each: the excess is dropped, the pass redone)
@@ -1019,17 +1023,18 @@ __global__ void k_labor_redo(Ctl* ctl, uint32_t* piece_count, uint32_t* cand_cou
 
 // staged rows -> the block's edge arrays: kFillLanes threads per destination, each taking every kFillLanes-th slot
 constexpr int kFillLanesLog2 = 3;
+constexpr int kFillOwnBlock = 1024;  // where a block adds up the counts in front of it: fewer and larger ones
 // (edge_limit: entries of col_global / eid; nothing is written beyond them)
-__global__ __launch_bounds__(kBlock) void k_labor_fill_staged(LayerChunks ch, int64_t first, int64_t n_dst, uint32_t stage_cap,
-                                                              const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
-                                                              int64_t* __restrict__ eid, int64_t edge_limit) {
-  __shared__ uint32_t row_j[kBlock >> kFillLanesLog2][kWave];  // list positions of one staged row per lane group
-  const int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+template <bool OWN, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_labor_fill_staged(LayerChunks ch, CountOffsets co, int64_t first, int64_t n_dst, uint32_t stage_cap,
+                                                             int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit) {
+  __shared__ uint32_t row_j[BLOCK >> kFillLanesLog2][kWave];  // list positions of one staged row per lane group
+  const int64_t idx = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   const int64_t w = first + (idx >> kFillLanesLog2);
+  int32_t c;
+  const int64_t o = offset_of<OWN, BLOCK, kFillLanesLog2>(co, w, n_dst, &c);
   if (w >= n_dst) return;
-  const int64_t o = eptr[w];
-  const int64_t c = eptr[w + 1] - o;
-  if (c > (int64_t)stage_cap) return;  // overflowed row: the overflow pass writes these edges
+  if (c > (int32_t)stage_cap) return;  // overflowed row: the overflow pass writes these edges
   const int p = ch.find(w);
   const int64_t local = w - ch.start[p];
   const StageEntry* __restrict__ row = ch.stage[p] + (size_t)local * stage_cap;
@@ -1056,7 +1061,7 @@ __global__ __launch_bounds__(kBlock) void k_labor_fill_staged(LayerChunks ch, in
     const int slot = sub + (i << kFillLanesLog2);
     if (slot >= c) break;
     int64_t place = 0;
-    for (int q = 0; q < (int)c; ++q) place += js[q] < mine[i].j;
+    for (int q = 0; q < c; ++q) place += js[q] < mine[i].j;
     if (o + place < edge_limit) {
       col_global[o + place] = mine[i].t;
       eid[o + place] = g.beg + mine[i].j;
@@ -1135,7 +1140,6 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
     ps.cnt[f] = alloc.get<int32_t>(n_new, COOP_TAG_SCRATCH);
   }
   blk->indptr = alloc.get<int64_t>(n_dst + 1, COOP_TAG_OUTPUT);
-  void* scan_tmp = alloc.get<char>((int64_t)scan_tmp_bytes(n_dst), COOP_TAG_SCRATCH);
   if (alloc.failed) return COOP_E_NOMEM;
 
   FusedKeys keys{};
@@ -1177,7 +1181,6 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
     if (cand_cap > ((int64_t)1 << 30)) cand_cap = (int64_t)1 << 30;
     cand_count = alloc.get<uint32_t>(kCandSub, COOP_TAG_SCRATCH);
     if (alloc.failed) return COOP_E_NOMEM;
-    fill_u64((uint64_t*)cand_count, kCandSub / 2, 0, s);
   }
   // ---- this layer's destinations, piece by piece: a recorded pass covered it as its (l - first_layer)-th layer ------
   if (record) { st.n_pass += 1; st.covered = n_dst; }
@@ -1199,6 +1202,7 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
   if (nc == 0) { ch.seg[0] = ps.seg; ch.thr[0] = ps.thr; ch.stage[0] = ps.stage[0]; counts.ptr[0] = ps.cnt[0]; nc = 1; }  // n_dst == 0
   ch.n_chunks = counts.n_chunks = nc;
 
+  const bool own = defer && n_dst <= kScanOwn;  // the fill finds its offsets by itself
   bool no_enum = false, used_enum = false;
   for (;;) {
     used_enum = false;
@@ -1268,11 +1272,12 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
         if (alloc.failed) return COOP_E_NOMEM;
         fill_u64((uint64_t*)zeroed, (1 + kLongBits / 8 / sizeof(LongSlot) + (int64_t)slots) * (sizeof(LongSlot) / 8), 0, s);
       }
+      const Clear clear = take_clear(cx);
 #define COOP_SEGMENTS(BLOCK)                                                                                                          \
   COOP_LAUNCH(K_SEGMENTS, k_segments<BLOCK>, dim3(blocks_for(n_new, BLOCK)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices,          \
               dst + ps.start, n_new, ps.nf, ks[0], ks[1], ks[2], ks[3], ps.seg, ps.thr, pthr, lim2, cx.cw, cx.sw,                        \
               cx.blend && cx.vec4 ? 1 : 0, cx.d_ctl, piece_len, split_min, pieces, piece_cap, cx.d_piece_count + l, out, enum_degree,    \
-              long_bits, long_tab, long_mask)
+              long_bits, long_tab, long_mask, clear, cand_count)
       if (n_new >= kSegWideFrom) COOP_SEGMENTS(1024);
       else if (n_new >= 16384 || !cx.blend) COOP_SEGMENTS(256);
       else COOP_SEGMENTS(64);
@@ -1323,11 +1328,11 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
     }
 
     if (defer) {  // the count stays on the device; an overflow of the candidate buffer is the caller's to notice
-      scan_chunks_to_i64(counts, n_dst, blk->indptr, &cx.d_ctl->total_edges, scan_tmp, s, nullptr);
+      if (!own) scan_tiles(counts, n_dst, blk->indptr, &cx.d_ctl->total_edges, cx.d_ctl, s);
       break;
     }
     const Publish pub = begin_publish(cx.d_ctl, cx.h_ctl);  // the scan's last thread also sends the sizes to the host
-    scan_chunks_to_i64(counts, n_dst, blk->indptr, &cx.d_ctl->total_edges, scan_tmp, s, &pub);  // m_l = indptr[n_dst]
+    scan_tiles(counts, n_dst, blk->indptr, &cx.d_ctl->total_edges, cx.d_ctl, s, &pub);  // m_l = indptr[n_dst]
     const int rc = wait_ctl(pub, cx.h_ctl, s);
     if (rc != COOP_OK) return rc;
     if (used_enum && cx.h_ctl->cand_overflow != 0) {  // the lists of the listed vertices did not fit: once more, every list scanned
@@ -1351,9 +1356,15 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
 
   if (m > 0 && n_dst > 0) {
     constexpr int64_t kSliceRows = kSliceLists << (6 - kFillLanesLog2);
-    for (int64_t b = 0; b < n_dst; b += kSliceRows)
-      COOP_LAUNCH(K_LABOR_FILL, k_labor_fill_staged, dim3(blocks_for((n_dst - b < kSliceRows ? n_dst - b : kSliceRows) << kFillLanesLog2, kBlock)),
-                  dim3(kBlock), 0, s, ch, b, n_dst, cap, blk->indptr, blk->col_global, blk->eid, m);
+    const CountOffsets co{counts, blk->indptr, &cx.d_ctl->total_edges};
+    if (own)
+      COOP_LAUNCH(K_LABOR_FILL, (k_labor_fill_staged<true, kFillOwnBlock>), dim3(blocks_for(n_dst << kFillLanesLog2, kFillOwnBlock)), dim3(kFillOwnBlock),
+                  0, s, ch, co, (int64_t)0, n_dst, cap, blk->col_global, blk->eid, m);
+    else
+      for (int64_t b = 0; b < n_dst; b += kSliceRows)
+        COOP_LAUNCH(K_LABOR_FILL, (k_labor_fill_staged<false, kBlock>),
+                    dim3(blocks_for((n_dst - b < kSliceRows ? n_dst - b : kSliceRows) << kFillLanesLog2, kBlock)), dim3(kBlock), 0, s, ch, co, b, n_dst,
+                    cap, blk->col_global, blk->eid, m);
     if (!defer && cx.h_ctl->n_overflow > 0) {
       LayerKeys K{};
       layer_keys(cx.seed, COOP_LABOR0, l, cx.group, K.Ka);

@@ -35,17 +35,23 @@ struct NsRecord {
 // blocks are the quicker ones: 10 us against 12 for 110 thousand, 5 against 8 for 16 thousand, and half the time with c > 0;
 // with c > 0 below 16,384 blocks of one wave, which spread over more CUs.)
 constexpr int64_t kNsCountWideFrom = 262144;
+constexpr int ns_tile_log2(int n) { return n <= 1 ? 0 : 1 + ns_tile_log2(n / 2); }
 template <int kNsCountBlock, int kNsCountEach>
 __global__ __launch_bounds__(kNsCountBlock) void k_ns_count(const int64_t* __restrict__ g_indptr, int64_t n_vertices,
                                                             const int32_t* __restrict__ dst, int64_t n_dst, uint32_t k, uint32_t target,
-                                                            int32_t* __restrict__ cnt, NsRecord* __restrict__ rec,
+                                                            int64_t* __restrict__ indptr, NsRecord* __restrict__ rec,
                                                             NsBlendThr* __restrict__ bthr /* null when c = 0 */, LayerKeys keys, double cw, double sw, Ctl* ctl,
-                                                            uint32_t long_min, uint32_t* __restrict__ long_list, uint32_t* __restrict__ n_long) {
-  __shared__ uint32_t wave_long[kNsCountBlock / kWave];
-  __shared__ uint32_t block_base;
+                                                            uint32_t long_min, uint32_t* __restrict__ long_list, uint32_t* __restrict__ n_long,
+                                                            Clear clear, Publish pub) {
+  clear_words(clear);
+  constexpr int kWaves = kNsCountBlock / kWave;
+  __shared__ uint32_t wave_long[kWaves];
+  __shared__ uint32_t block_base, s_last;
+  __shared__ int64_t lds[kWaves];
   const uint32_t* K = keys.Ka;
   const int64_t i0 = (int64_t)blockIdx.x * (kNsCountBlock * kNsCountEach) + threadIdx.x;
   bool is_long[kNsCountEach];
+  int64_t cnt[kNsCountEach];
   int32_t s[kNsCountEach];
   int64_t beg[kNsCountEach], end[kNsCountEach];
 #pragma unroll
@@ -65,16 +71,17 @@ __global__ __launch_bounds__(kNsCountBlock) void k_ns_count(const int64_t* __res
   for (int u = 0; u < kNsCountEach; ++u) {
     const int64_t i = i0 + u * kNsCountBlock;
     is_long[u] = false;
+    cnt[u] = 0;
     if (i >= n_dst) continue;
     if ((uint64_t)(uint32_t)s[u] >= (uint64_t)n_vertices) {
       atomicOr(&ctl->err_range, 1);
-      cnt[i] = 0;
+      __threadfence();  // (before the block counts itself, below)
       rec[i] = NsRecord{0, 0u, 0, 0u, 0u};
       if (bthr) bthr[i] = NsBlendThr{0u, 0u, 0u, 0.0f};
       continue;
     }
     const int64_t d = end[u] - beg[u];
-    cnt[i] = (int32_t)(d < (int64_t)k ? d : (int64_t)k);
+    cnt[u] = d < (int64_t)k ? d : (int64_t)k;
     // bound such that E[#candidates] = target: R <= bound with probability (bound + 1) / 2^32 (one 64-bit division per
     // list, here where every lane has a list of its own)
     uint64_t bound = d > 0 ? ((uint64_t)target << 32) / (uint64_t)d : 0xFFFFFFFFull;
@@ -83,32 +90,69 @@ __global__ __launch_bounds__(kNsCountBlock) void k_ns_count(const int64_t* __res
     if (bthr) bthr[i] = d > (int64_t)k ? ns_blend_thresholds((uint32_t)bound, cw, sw) : NsBlendThr{0u, 0u, 0u, 0.0f};
     is_long[u] = long_min != 0 && d > (int64_t)long_min && d > (int64_t)k;
   }
-  if (long_min == 0) return;  // (the same for every thread)
-  uint64_t mask[kNsCountEach];
-  uint32_t mine = 0;
+  if (long_min != 0) {  // (the same for every thread)
+    uint64_t mask[kNsCountEach];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int u = 0; u < kNsCountEach; ++u) {
+      mask[u] = ballot64(is_long[u]);
+      mine += (uint32_t)__popcll(mask[u]);
+    }
+    const int wib = wave_in_block();
+    if (lane_id() == 0) wave_long[wib] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {  // one reservation per block
+      uint32_t total = 0;
+      for (int w = 0; w < kWaves; ++w) total += wave_long[w];
+      block_base = total ? atomicAdd(n_long, total) : 0u;
+    }
+    __syncthreads();
+    uint32_t at = block_base;
+    for (int w = 0; w < wib; ++w) at += wave_long[w];
+#pragma unroll
+    for (int u = 0; u < kNsCountEach; ++u) {
+      const uint32_t to = at + lanes_below(mask[u]);
+      if (is_long[u] && (int64_t)to < n_dst) long_list[to] = (uint32_t)(i0 + u * kNsCountBlock);  // (always: a destination is queued at most once)
+      at += (uint32_t)__popcll(mask[u]);
+    }
+  }
+  // The offsets, as scan_tiles leaves them, the block's destinations being a tile.  (Two launches of 5 us less than a scan of stored
+  // counts.)
+  int64_t in_front = 0;
 #pragma unroll
   for (int u = 0; u < kNsCountEach; ++u) {
-    mask[u] = ballot64(is_long[u]);
-    mine += (uint32_t)__popcll(mask[u]);
+    const int64_t i = i0 + u * kNsCountBlock;
+    int64_t sum;
+    const int64_t upto = in_front + block_incl_scan_i64<kWaves>(cnt[u], &sum, lds);
+    if (i < n_dst && (u != 0 || threadIdx.x != 0)) indptr[i] = upto - cnt[u];
+    in_front += sum;
   }
-  const int wib = wave_in_block();
-  if (lane_id() == 0) wave_long[wib] = mine;
+  if (threadIdx.x == 0) s_last = tile_sum_done(in_front, indptr + i0, ctl) ? 1u : 0u;
   __syncthreads();
-  if (threadIdx.x == 0) {  // one reservation per block
-    uint32_t total = 0;
-    for (int w = 0; w < kNsCountBlock / kWave; ++w) total += wave_long[w];
-    block_base = total ? atomicAdd(n_long, total) : 0u;
+  if (s_last == 0) return;
+  constexpr int kLog2 = ns_tile_log2(kNsCountBlock * kNsCountEach);
+  const int64_t total = scan_tile_sums<kWaves>(n_dst, kLog2, indptr, lds);
+  if (threadIdx.x == 0) {
+    indptr[n_dst] = total;
+    ctl->total_edges = total;
+    if (pub.h != nullptr) {
+      pub.h->ctl = *ctl;  // (the fields of earlier kernels; those of this one follow)
+      pub.h->ctl.total_edges = total;
+      pub.h->ctl.err_range = __hip_atomic_load(&ctl->err_range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __threadfence_system();
+      __hip_atomic_store(&pub.h->ticket, pub.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
-  __syncthreads();
-  if (mine == 0) return;  // (the same for the whole wave)
-  uint32_t at = block_base;
-  for (int w = 0; w < wib; ++w) at += wave_long[w];
-#pragma unroll
-  for (int u = 0; u < kNsCountEach; ++u) {
-    const uint32_t to = at + lanes_below(mask[u]);
-    if (is_long[u] && (int64_t)to < n_dst) long_list[to] = (uint32_t)(i0 + u * kNsCountBlock);  // (always: a destination is queued at most once)
-    at += (uint32_t)__popcll(mask[u]);
-  }
+}
+
+// The offset of destination w, its final value put in the place of what k_ns_count left there: by one wave per destination, in
+// the first kernel that uses the offsets.
+__device__ __forceinline__ int64_t ns_offset(const int64_t* indptr, int64_t w, int tile_log2) {
+  const int64_t tile = w >> tile_log2 << tile_log2;
+  return indptr[tile] + (w != tile ? indptr[w] : 0);
+}
+__device__ __forceinline__ void ns_settle_offset(int64_t* indptr, int64_t w, int tile_log2, int64_t o) {
+  if ((w & (((int64_t)1 << tile_log2) - 1)) != 0) indptr[w] = o;
 }
 
 constexpr uint32_t kNsMaxSelect = 1024;  // largest fanout for which a longer list is subsampled through the candidate arrays
@@ -566,7 +610,7 @@ __device__ __forceinline__ bool ns_next_bound(uint32_t n_c, uint32_t k, uint32_t
 // destinations, 380 M entries: 494 us with a wave for each, 225 M vector and 191 M scalar instructions; 400 now, with 144 M
 // and 159 M (the entries alone, at the rate of a copy: 310).
 __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict__ g_indices, const NsRecord* __restrict__ rec, uint32_t n_dst, uint32_t k,
-                                                    uint32_t cap, LayerKeys keys, const int64_t* __restrict__ eptr,
+                                                    uint32_t cap, LayerKeys keys, int64_t* indptr, int64_t first, int tile_log2,
                                                     int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl,
                                                     uint32_t long_min, const uint32_t* __restrict__ long_list,
                                                     const uint32_t* __restrict__ n_long, int long_blocks, int each_log2) {
@@ -590,8 +634,11 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
   // a lane's destination: its number among the wave's in the copying below, and so, shifted, where the loop finds it
   const uint32_t w = w0 + ((lane >> (6 - each_log2)) < n_mine ? lane >> (6 - each_log2) : n_mine - 1);
   const NsRecord g = rec[w];
-  const int64_t o = eptr[w], o_end = eptr[w + 1];
-  const bool live = (lane >> (6 - each_log2)) < n_mine && g.d != 0 && o_end <= edge_limit;  // (no room: the caller redoes the layer)
+  const int64_t o = ns_offset(indptr, first + w, tile_log2), o_end = o + (g.d < k ? g.d : k);
+  const bool mine = (lane >> (6 - each_log2)) < n_mine, speaks = mine && (lane & ((64u >> each_log2) - 1)) == 0;
+  // (longer than skip_above: queued, one of the first waves takes it)
+  if (speaks && (g.d <= k || g.d <= skip_above)) ns_settle_offset(indptr, first + w, tile_log2, o);
+  const bool live = mine && g.d != 0 && o_end <= edge_limit;  // (no room: the caller redoes the layer)
   if (live && g.d <= k) {
     const uint32_t lanes = 64u >> each_log2;
     for (uint32_t j = lane & (lanes - 1); j < g.d; j += lanes) {
@@ -600,8 +647,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
     }
   }
   if (k > kNsMaxSelect) return;  // degrees above a fanout that the candidate buffer cannot serve: left to k_ns_fill_wide
-  // (longer than skip_above: queued, one of the first waves takes it)
-  uint64_t todo = ballot64(live && g.d > k && g.d <= skip_above && (lane & ((64u >> each_log2) - 1)) == 0);
+  uint64_t todo = ballot64(live && speaks && g.d > k && g.d <= skip_above);
   if (todo == 0) return;
   auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
   auto of64 = [&](int64_t x, int q) { return (int64_t)(((uint64_t)of((uint32_t)((uint64_t)x >> 32), q) << 32) | of((uint32_t)x, q)); };
@@ -708,7 +754,7 @@ struct NsCand { uint32_t j; int32_t t; };
 template <bool VEC4>
 __global__ __launch_bounds__(kBlock) void k_ns_collect(const int32_t* __restrict__ g_indices, const NsRecord* __restrict__ rec,
                                                        const NsBlendThr* __restrict__ bthr, int64_t n_dst, uint32_t k, uint32_t cap,
-                                                       int waves_per_block, VariateParams vp, const int64_t* __restrict__ eptr,
+                                                       int waves_per_block, VariateParams vp, int64_t* indptr, int64_t first, int tile_log2,
                                                        int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit,
                                                        NsCand* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand,
                                                        uint32_t long_min, const uint32_t* __restrict__ long_list,
@@ -724,8 +770,9 @@ __global__ __launch_bounds__(kBlock) void k_ns_collect(const int32_t* __restrict
   const NsRecord g = rec[w];
   if (!queued && long_min != 0 && g.d > long_min && g.d > k) return;  // queued: one of the first waves takes it
   if (lane == 0) n_cand[w] = 0;  // nothing left to do for this destination, unless said otherwise below
-  const int64_t o = eptr[w];
-  if (eptr[w + 1] > edge_limit) return;
+  const int64_t o = ns_offset(indptr, first + w, tile_log2);
+  if (lane == 0) ns_settle_offset(indptr, first + w, tile_log2, o);
+  if (o + (g.d < k ? g.d : k) > edge_limit) return;
   if (g.d == 0) return;
   if (g.d <= k) {
     for (uint32_t j = lane; j < g.d; j += kWave) {
@@ -929,10 +976,8 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
   vp.cw = cx.cw;
   vp.sw = cx.sw;
   blk->indptr = alloc.get<int64_t>(n_dst + 1, COOP_TAG_OUTPUT);
-  int32_t* cnt = alloc.get<int32_t>(n_dst, COOP_TAG_SCRATCH);
   NsRecord* rec = alloc.get<NsRecord>(n_dst, COOP_TAG_SCRATCH);
   NsBlendThr* bthr = cx.blend ? alloc.get<NsBlendThr>(n_dst, COOP_TAG_SCRATCH) : nullptr;
-  void* scan_tmp = alloc.get<char>((int64_t)scan_tmp_bytes(n_dst), COOP_TAG_SCRATCH);
   if (alloc.failed) return COOP_E_NOMEM;
   // candidate buffer: cap >= 4k (power of two, at least 256).  With a fanout above kNsMaxSelect the lists longer than
   // the fanout are left to k_ns_fill_wide, which keeps no candidates.
@@ -958,18 +1003,22 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
   uint32_t* long_list = queue_long ? alloc.get<uint32_t>(n_dst, COOP_TAG_SCRATCH) : nullptr;
   uint32_t* n_long = cx.d_piece_count + l;  // (zero at the start of the call and whenever the layer is redone)
   if (alloc.failed) return COOP_E_NOMEM;
+  const Publish pub = defer ? Publish{} : begin_publish(cx.d_ctl, cx.h_ctl);  // (not deferred: the kernel also sends the sizes to the host)
+  const Clear clear = n_dst > 0 ? take_clear(cx) : Clear{nullptr, 0};
+  int tile_log2 = 0;
 #define COOP_NS_COUNT(BLOCK, EACH)                                                                                                             \
-  COOP_LAUNCH(K_NS_COUNT, (k_ns_count<BLOCK, EACH>), dim3(blocks_for(n_dst, BLOCK * EACH)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices, \
-              dst, n_dst, k, target, cnt, rec, bthr, vp.K, cx.cw, cx.sw, cx.d_ctl, long_min, long_list, n_long)
+  do {                                                                                                                                         \
+    tile_log2 = ns_tile_log2(BLOCK * EACH);                                                                                                    \
+    COOP_LAUNCH(K_NS_COUNT, (k_ns_count<BLOCK, EACH>), dim3(blocks_for(n_dst, BLOCK * EACH)), dim3(BLOCK), 0, s, cx.g->indptr,                 \
+                cx.g->n_vertices, dst, n_dst, k, target, blk->indptr, rec, bthr, vp.K, cx.cw, cx.sw, cx.d_ctl, long_min, long_list, n_long,    \
+                clear, pub);                                                                                                                   \
+  } while (0)
   if (n_dst >= kNsCountWideFrom && !cx.blend) COOP_NS_COUNT(1024, 2);
   else if (n_dst >= 16384 || (n_dst > 0 && !cx.blend)) COOP_NS_COUNT(kBlock, 1);
   else if (n_dst > 0) COOP_NS_COUNT(kWave, 1);
+  else scan_tiles(ChunkedI32{}, 0, blk->indptr, &cx.d_ctl->total_edges, cx.d_ctl, s, &pub);
 #undef COOP_NS_COUNT
-  if (defer) {
-    scan_i32_to_i64(cnt, n_dst, blk->indptr, &cx.d_ctl->total_edges, scan_tmp, s, nullptr);  // the count stays on the device
-  } else {
-    const Publish pub = begin_publish(cx.d_ctl, cx.h_ctl);  // the scan's last thread also sends the sizes to the host
-    scan_i32_to_i64(cnt, n_dst, blk->indptr, &cx.d_ctl->total_edges, scan_tmp, s, &pub);  // m_l = indptr[n_dst]
+  if (!defer) {
     const int rc = wait_ctl(pub, cx.h_ctl, s);
     if (rc != COOP_OK) return rc;
   }
@@ -1015,7 +1064,8 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
         while (lists_log2 < 6 && (n >> (lists_log2 + 1)) >= kNsRedoWaves) ++lists_log2;
         const dim3 grid_redo(blocks_for(n, (int64_t)wpb << lists_log2));
 #define COOP_NS_BLEND(VEC4)                                                                                                                \
-  COOP_LAUNCH(K_NS_FILL, k_ns_collect<VEC4>, grid_q, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, rows_b, row_cap, n_cand_b, long_min,        \
+  COOP_LAUNCH(K_NS_FILL, k_ns_collect<VEC4>, grid_q, dim3(wpb * kWave), shmem, s, cx.g->indices, rec_b, bthr_b, n, k, cap, wpb, vp,         \
+              blk->indptr, b, tile_log2, blk->col_global, blk->eid, m, rows_b, row_cap, n_cand_b, long_min,        \
               (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);                                                           \
   COOP_LAUNCH(K_NS_SELECT, k_ns_select, grid, dim3(wpb * kWave), shmem, s, rec_b, n, k, cap, wpb, vp, eptr_b, blk->col_global, blk->eid,    \
               (const NsCand*)rows_b, row_cap, n_cand_b, bthr_b);                                                                           \
@@ -1026,8 +1076,8 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
         int each_log2 = 0;
         while (each_log2 < 3 && (n >> (each_log2 + 1)) >= kNsFillWaves) ++each_log2;
         COOP_LAUNCH(K_NS_FILL, k_ns_fill, dim3(blocks_for(n, (int64_t)1 << each_log2) + (unsigned)long_blocks), dim3(kWave),
-                    (cap + kWave) * sizeof(NsSlot), s, cx.g->indices, rec_b, (uint32_t)n, k, cap, vp.K, eptr_b, blk->col_global, blk->eid, m,
-                    cx.d_ctl, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2);
+                    (cap + kWave) * sizeof(NsSlot), s, cx.g->indices, rec_b, (uint32_t)n, k, cap, vp.K, blk->indptr, b, tile_log2,
+                    blk->col_global, blk->eid, m, cx.d_ctl, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2);
       }
 #undef COOP_NS_ARGS
       if (k > kNsMaxSelect) {  // the lists longer than such a fanout (the kernels above skip them)

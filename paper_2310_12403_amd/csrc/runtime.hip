@@ -100,50 +100,10 @@ constexpr int kItems = 8;
 constexpr int kTile = kBlock * kItems;  // 2048
 static_assert(kTile == (1 << kScanTileLog2), "TiledScan::at() finds an element's tile by a shift");
 
-// inclusive block scan of one int64 per thread; returns the thread's inclusive prefix, *total = block sum
 __device__ __forceinline__ int64_t block_incl_scan(int64_t v, int64_t* total, int64_t* lds /* [kWavesPerBlock] */) {
-  const int lane = lane_id(), w = wave_in_block();
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    int64_t o = __shfl_up(v, off, kWave);
-    if (lane >= off) v += o;
-  }
-  if (lane == kWave - 1) lds[w] = v;
-  __syncthreads();
-  int64_t base = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < kWavesPerBlock; ++i) {
-    const int64_t x = lds[i];
-    if (i < w) base += x;
-    tot += x;
-  }
-  __syncthreads();
-  *total = tot;
-  return v + base;
+  return block_incl_scan_i64<kWavesPerBlock>(v, total, lds);
 }
 
-// what a one-thread publishing kernel would do, done by the thread that has just stored the scan's total
-__device__ __forceinline__ void publish_ctl(const Publish& pub) {
-  if (pub.h == nullptr) return;
-  pub.h->ctl = *pub.d_ctl;
-  __threadfence_system();
-  __hip_atomic_store(&pub.h->ticket, pub.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-struct LoadI32 {
-  const int32_t* in;
-  __device__ __forceinline__ int64_t operator()(int64_t i) const { return in[i]; }
-};
-struct LoadChunks {
-  ChunkedI32 c;
-  __device__ __forceinline__ int64_t operator()(int64_t i) const {
-    int p = 0;
-#pragma unroll
-    for (int q = 1; q < 4; ++q)
-      if (q < c.n_chunks && i >= c.start[q]) p = q;
-    return c.ptr[p][i - c.start[p]];
-  }
-};
 struct LoadU32 {
   const uint32_t* in;
   __device__ __forceinline__ int64_t operator()(int64_t i) const { return in[i]; }
@@ -179,7 +139,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_local(Load load, int64_t n, Out
 
 template <typename Out>
 __global__ __launch_bounds__(kBlock) void k_scan_offset(int64_t n, Out* __restrict__ out, const int64_t* __restrict__ tile_sum,
-                                                        Out* __restrict__ end_out, int64_t* total_out, Publish pub) {
+                                                        Out* __restrict__ end_out, int64_t* total_out) {
   __shared__ int64_t lds[kWavesPerBlock];
   int64_t part = 0;
   for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += kBlock) part += tile_sum[t];
@@ -201,7 +161,6 @@ __global__ __launch_bounds__(kBlock) void k_scan_offset(int64_t n, Out* __restri
     const int64_t total = off + tile_sum[blockIdx.x];
     if (end_out) *end_out = (Out)total;  // the entry one past the end holds the grand total
     if (total_out) *total_out = total;
-    publish_ctl(pub);
   }
 }
 
@@ -257,7 +216,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiled(LoadU32 load, int64_t n, 
 constexpr int64_t kScanSmall = 2 * kTile;  // 4096 elements (beyond that two parallel launches are quicker)
 template <typename Load, typename Out>
 __global__ __launch_bounds__(kBlock) void k_scan_small(Load load, int64_t n, Out* __restrict__ out, Out* __restrict__ end_out,
-                                                       int64_t* total_out, Publish pub) {
+                                                       int64_t* total_out) {
   __shared__ int64_t lds[kWavesPerBlock];
   int64_t carry = 0;
   for (int64_t tile = 0; tile < n; tile += kTile) {
@@ -284,7 +243,6 @@ __global__ __launch_bounds__(kBlock) void k_scan_small(Load load, int64_t n, Out
   if (threadIdx.x == 0) {
     if (end_out) *end_out = (Out)carry;
     if (total_out) *total_out = carry;
-    publish_ctl(pub);
   }
 }
 
@@ -295,42 +253,71 @@ size_t scan_tmp_bytes(int64_t n) {  // tile sums, and the one-kernel scans' tile
 
 constexpr int64_t kScanTiledMax = 64;  // tiles (131,072 elements) up to which the one-kernel scan is used
 template <typename Load, typename Out>
-static void scan_impl(Load load, int64_t n, Out* out, Out* end_out, int64_t* total_out, void* tmp, hipStream_t s, const Publish* p) {
-  const Publish pub = p ? *p : Publish{};
+static void scan_impl(Load load, int64_t n, Out* out, Out* end_out, int64_t* total_out, void* tmp, hipStream_t s) {
   if (n <= kScanSmall) {
-    COOP_LAUNCH(K_SCAN_LOCAL, (k_scan_small<Load, Out>), dim3(1), dim3(kBlock), 0, s, load, n, out, end_out, total_out, pub);
+    COOP_LAUNCH(K_SCAN_LOCAL, (k_scan_small<Load, Out>), dim3(1), dim3(kBlock), 0, s, load, n, out, end_out, total_out);
     return;
   }
   int64_t* tile_sum = (int64_t*)tmp;
   const int64_t tiles = (n + kTile - 1) / kTile;
   COOP_LAUNCH(K_SCAN_LOCAL, (k_scan_local<Load, Out>), dim3((unsigned)tiles), dim3(kBlock), 0, s, load, n, out, tile_sum);
-  COOP_LAUNCH(K_SCAN_OFFSET, k_scan_offset<Out>, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, out, tile_sum, end_out, total_out, pub);
+  COOP_LAUNCH(K_SCAN_OFFSET, k_scan_offset<Out>, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, out, tile_sum, end_out, total_out);
+}
+
+// counts to offsets, one launch (see CountOffsets)
+constexpr int kTilesBlock = 1024, kTilesItems = 4;
+static_assert(kTilesBlock * kTilesItems == 1 << kOffsetTileLog2, "a block takes a tile");
+__global__ __launch_bounds__(kTilesBlock) void k_scan_tiles(ChunkedI32 in, int64_t n, int64_t* __restrict__ out, int64_t* total_out, Ctl* ctl, Publish pub) {
+  __shared__ int64_t lds[kTilesBlock / kWave];
+  __shared__ uint32_t s_last;
+  const int64_t tile = (int64_t)blockIdx.x << kOffsetTileLog2, base = tile + (int64_t)threadIdx.x * kTilesItems;  // a thread owns 4 in a row
+  int64_t x[kTilesItems], sum = 0;
+#pragma unroll
+  for (int j = 0; j < kTilesItems; ++j) {
+    const int64_t i = base + j;
+    int p = 0;
+#pragma unroll
+    for (int q = 1; q < 4; ++q)
+      if (q < in.n_chunks && i >= in.start[q]) p = q;
+    x[j] = i < n ? in.ptr[p][i - in.start[p]] : 0;
+    sum += x[j];
+  }
+  int64_t tot;
+  int64_t run = block_incl_scan_i64<kTilesBlock / kWave>(sum, &tot, lds) - sum;
+#pragma unroll
+  for (int j = 0; j < kTilesItems; ++j) {
+    const int64_t i = base + j;
+    if (i < n && i != tile) out[i] = run;
+    run += x[j];
+  }
+  if (threadIdx.x == 0) s_last = tile_sum_done(tot, out + tile, ctl) ? 1u : 0u;
+  __syncthreads();
+  if (s_last == 0) return;
+  const int64_t total = scan_tile_sums<kTilesBlock / kWave>(n, kOffsetTileLog2, out, lds);
+  if (threadIdx.x == 0) {
+    out[n] = total;
+    *total_out = total;
+    publish_ctl(pub);
+  }
 }
 
 __global__ void k_store_total(int64_t* p, int64_t* total_out, Publish pub) {
   *p = 0;
-  if (total_out) *total_out = 0;
+  *total_out = 0;
   publish_ctl(pub);
 }
 
-void scan_i32_to_i64(const int32_t* in, int64_t n, int64_t* out, int64_t* total_out, void* tmp, hipStream_t s, const Publish* pub) {
-  if (n <= 0) {  // out[0] = 0
-    COOP_LAUNCH(K_FILL, k_store_total, dim3(1), dim3(1), 0, s, out, total_out, pub ? *pub : Publish{});
-    return;
-  }
-  scan_impl<LoadI32, int64_t>(LoadI32{in}, n, out, out + n, total_out, tmp, s, pub);
-}
-
-void scan_chunks_to_i64(const ChunkedI32& in, int64_t n, int64_t* out, int64_t* total_out, void* tmp, hipStream_t s, const Publish* pub) {
-  if (n <= 0) {
-    COOP_LAUNCH(K_FILL, k_store_total, dim3(1), dim3(1), 0, s, out, total_out, pub ? *pub : Publish{});
-    return;
-  }
-  scan_impl<LoadChunks, int64_t>(LoadChunks{in}, n, out, out + n, total_out, tmp, s, pub);
+void scan_tiles(const ChunkedI32& in, int64_t n, int64_t* out, int64_t* total_out, Ctl* ctl, hipStream_t s, const Publish* pub) {
+  const Publish p = pub ? *pub : Publish{};
+  if (n <= 0)  // out[0] = 0
+    COOP_LAUNCH(K_FILL, k_store_total, dim3(1), dim3(1), 0, s, out, total_out, p);
+  else
+    COOP_LAUNCH(K_SCAN_LOCAL, k_scan_tiles, dim3((unsigned)((n + (1 << kOffsetTileLog2) - 1) >> kOffsetTileLog2)), dim3(kTilesBlock), 0, s, in, n, out,
+                total_out, ctl, p);
 }
 
 void scan_u32_to_u32(const uint32_t* in, int64_t n, uint32_t* out, void* tmp, hipStream_t s) {
-  scan_impl<LoadU32, uint32_t>(LoadU32{in}, n, out, out + n, nullptr, tmp, s, nullptr);
+  scan_impl<LoadU32, uint32_t>(LoadU32{in}, n, out, out + n, nullptr, tmp, s);
 }
 
 TiledScan<uint32_t> scan_u32_tiled(const uint32_t* in, int64_t n, uint32_t* out, void* tmp, uint32_t* done, hipStream_t s) {
@@ -346,7 +333,7 @@ TiledScan<uint32_t> scan_u32_tiled(const uint32_t* in, int64_t n, uint32_t* out,
 }
 
 void scan_popc_to_u32(const uint64_t* bits, int64_t n_words, uint32_t* out, int64_t* total_out, void* tmp, hipStream_t s) {
-  scan_impl<LoadPopc, uint32_t>(LoadPopc{bits}, n_words, out, (uint32_t*)nullptr, total_out, tmp, s, nullptr);
+  scan_impl<LoadPopc, uint32_t>(LoadPopc{bits}, n_words, out, (uint32_t*)nullptr, total_out, tmp, s);
 }
 
 // ---- CSR validation -------------------------------------------------------------------------------------------

@@ -32,7 +32,8 @@ template <int E>
 __global__ __launch_bounds__(kBlock) void k_rw_walk(const int64_t* __restrict__ g_indptr, const int32_t* __restrict__ g_indices,
                                                     int64_t n_vertices, const int32_t* __restrict__ dst, int64_t n_dst, RwParams rp,
                                                     int waves_per_block, StageEntry* __restrict__ rows, int32_t* __restrict__ cnt,
-                                                    Ctl* ctl) {
+                                                    Ctl* ctl, Clear clear) {
+  clear_words(clear);
   extern __shared__ uint32_t rw_lds[];  // per wave: 64 E vertex keys, 64 E counts
   constexpr uint32_t T = (uint32_t)kWave * E;
   const int wib = uniform_wave_in_block();
@@ -290,18 +291,21 @@ __global__ __launch_bounds__(kBlock) void k_rw_walk_wide(const int64_t* __restri
 }
 
 // staged rows -> the block's edge arrays; eid carries the visit count (these are edges of sum_i A^i, not of the graph)
-__global__ __launch_bounds__(kBlock) void k_rw_fill(const StageEntry* __restrict__ rows, uint32_t k_eff, int64_t n_dst,
-                                                    const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
-                                                    int64_t* __restrict__ eid, int64_t edge_limit) {
-  const int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t w = idx / k_eff;
+// (eight lanes for a destination)
+constexpr int kRwFillLog2 = 3;
+template <bool OWN, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_rw_fill(const StageEntry* __restrict__ rows, CountOffsets co, uint32_t k_eff, int64_t first, int64_t n_dst,
+                                                   int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit) {
+  const int64_t w = first + (((int64_t)blockIdx.x * BLOCK + threadIdx.x) >> kRwFillLog2);
+  int32_t c;
+  const int64_t o = offset_of<OWN, BLOCK, kRwFillLog2>(co, w, n_dst, &c);
   if (w >= n_dst) return;
-  const int64_t slot = idx - w * k_eff;
-  const int64_t o = eptr[w];
-  if (slot >= eptr[w + 1] - o || o + slot >= edge_limit) return;
-  const StageEntry e = rows[idx];
-  col_global[o + slot] = e.t;
-  eid[o + slot] = (int64_t)e.j;
+  const StageEntry* row = rows + (size_t)w * k_eff;
+  for (int32_t slot = (int32_t)(threadIdx.x & ((1 << kRwFillLog2) - 1)); slot < c && o + slot < edge_limit; slot += 1 << kRwFillLog2) {
+    const StageEntry e = row[slot];
+    col_global[o + slot] = e.t;
+    eid[o + slot] = (int64_t)e.j;
+  }
 }
 
 int rw_layer(const SampleCtx& cx, const RwConfig& rw, int l, const int32_t* dst, int64_t n_dst, coop_block* blk, int64_t edge_cap) {
@@ -319,7 +323,6 @@ int rw_layer(const SampleCtx& cx, const RwConfig& rw, int l, const int32_t* dst,
   blk->indptr = alloc.get<int64_t>(n_dst + 1, COOP_TAG_OUTPUT);
   int32_t* cnt = alloc.get<int32_t>(n_dst, COOP_TAG_SCRATCH);
   StageEntry* rows = alloc.get<StageEntry>(n_dst * (int64_t)rp.k_eff, COOP_TAG_SCRATCH);
-  void* scan_tmp = alloc.get<char>((int64_t)scan_tmp_bytes(n_dst), COOP_TAG_SCRATCH);
   if (alloc.failed) return COOP_E_NOMEM;
   if (n_dst > 0 && n_steps > kRwMaxSteps) {
     // the tally in device memory: T slots per wave, and as many waves as half a gigabyte of tables allows
@@ -344,17 +347,21 @@ int rw_layer(const SampleCtx& cx, const RwConfig& rw, int l, const int32_t* dst,
       const int64_t n = n_dst - b < slice ? n_dst - b : slice;
       if (n_steps <= 384)
         COOP_LAUNCH(K_RW_WALK, k_rw_walk<8>, dim3(blocks_for(n, wpb)), dim3(kBlock), (size_t)wpb * 2 * 512 * 4, s, cx.g->indptr,
-                    cx.g->indices, cx.g->n_vertices, dst + b, n, rp, wpb, rows + b * (int64_t)rp.k_eff, cnt + b, cx.d_ctl);
+                    cx.g->indices, cx.g->n_vertices, dst + b, n, rp, wpb, rows + b * (int64_t)rp.k_eff, cnt + b, cx.d_ctl, take_clear(cx));
       else
         COOP_LAUNCH(K_RW_WALK, k_rw_walk<32>, dim3(blocks_for(n, wpb)), dim3(kBlock), (size_t)wpb * 2 * 2048 * 4, s, cx.g->indptr,
-                    cx.g->indices, cx.g->n_vertices, dst + b, n, rp, wpb, rows + b * (int64_t)rp.k_eff, cnt + b, cx.d_ctl);
+                    cx.g->indices, cx.g->n_vertices, dst + b, n, rp, wpb, rows + b * (int64_t)rp.k_eff, cnt + b, cx.d_ctl, take_clear(cx));
     }
   }
+  ChunkedI32 counts{};
+  counts.ptr[0] = cnt;
+  counts.n_chunks = 1;
+  const bool own = defer && n_dst <= kScanOwn;  // the fill finds its offsets by itself
   if (defer) {
-    scan_i32_to_i64(cnt, n_dst, blk->indptr, &cx.d_ctl->total_edges, scan_tmp, s, nullptr);  // the count stays on the device
+    if (!own) scan_tiles(counts, n_dst, blk->indptr, &cx.d_ctl->total_edges, cx.d_ctl, s);  // the count stays on the device
   } else {
     const Publish pub = begin_publish(cx.d_ctl, cx.h_ctl);  // the scan's last thread also sends the sizes to the host
-    scan_i32_to_i64(cnt, n_dst, blk->indptr, &cx.d_ctl->total_edges, scan_tmp, s, &pub);  // m_l = indptr[n_dst]
+    scan_tiles(counts, n_dst, blk->indptr, &cx.d_ctl->total_edges, cx.d_ctl, s, &pub);  // m_l = indptr[n_dst]
     const int rc = wait_ctl(pub, cx.h_ctl, s);
     if (rc != COOP_OK) return rc;
   }
@@ -364,11 +371,16 @@ int rw_layer(const SampleCtx& cx, const RwConfig& rw, int l, const int32_t* dst,
   blk->eid = alloc.get<int64_t>(m, COOP_TAG_OUTPUT);
   blk->col_local = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
-  const int64_t most = (((int64_t)1 << 32) - kBlock) / rp.k_eff;  // (a thread per slot, in slices as above; k_eff is below 2^21)
-  for (int64_t b = 0; m > 0 && b < n_dst; b += most) {
-    const int64_t n = n_dst - b < most ? n_dst - b : most;
-    COOP_LAUNCH(K_RW_FILL, k_rw_fill, dim3(blocks_for(n * (int64_t)rp.k_eff, kBlock)), dim3(kBlock), 0, s, rows + b * (int64_t)rp.k_eff, rp.k_eff,
-                n, blk->indptr + b, blk->col_global, blk->eid, m);
+  if (m > 0 && n_dst > 0) {
+    const CountOffsets co{counts, blk->indptr, &cx.d_ctl->total_edges};
+    constexpr int64_t kSliceRows = kSliceLists << (6 - kRwFillLog2);  // (a launch has fewer than 2^32 threads)
+    if (own)
+      COOP_LAUNCH(K_RW_FILL, (k_rw_fill<true, 1024>), dim3(blocks_for(n_dst << kRwFillLog2, 1024)), dim3(1024), 0, s, rows, co, rp.k_eff, (int64_t)0, n_dst,
+                  blk->col_global, blk->eid, m);
+    else
+      for (int64_t b = 0; b < n_dst; b += kSliceRows)
+        COOP_LAUNCH(K_RW_FILL, (k_rw_fill<false, kBlock>), dim3(blocks_for((n_dst - b < kSliceRows ? n_dst - b : kSliceRows) << kRwFillLog2, kBlock)),
+                    dim3(kBlock), 0, s, rows, co, rp.k_eff, b, n_dst, blk->col_global, blk->eid, m);
   }
   return COOP_OK;
 }

@@ -23,7 +23,21 @@ struct SampleCtx {
   bool blend;      // c > 0
   double cw, sw;   // cos(c pi/2), sin(c pi/2)
   bool vec4;       // the graph's indices array is 16-byte aligned
+  UniqueWork* clear = nullptr;  // words that the layer's first kernel is to set to zero, if any (take_clear)
 };
+// The words to clear go to a kernel that is launched anyway, before anything else uses them.
+struct Clear { uint64_t* p; int64_t n; };
+static inline Clear take_clear(const SampleCtx& cx) {
+  if (cx.clear == nullptr || cx.clear->clear == nullptr) return Clear{nullptr, 0};
+  const Clear c{cx.clear->clear, cx.clear->n_clear};
+  cx.clear->clear = nullptr;
+  return c;
+}
+#ifdef __HIPCC__
+__device__ __forceinline__ void clear_words(const Clear& c) {  // every thread of the grid
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < c.n; i += (int64_t)gridDim.x * blockDim.x) c.p[i] = 0;
+}
+#endif
 
 // One destination's neighbour list as the scan kernels see it.
 struct Segment { int64_t beg; uint32_t d; uint32_t split; };  // split != 0: scanned piecewise by several waves

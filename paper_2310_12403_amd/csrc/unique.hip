@@ -149,7 +149,8 @@ __device__ __forceinline__ uint32_t filter_hash(uint32_t key) { return key * 0x9
 
 __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
                                                               int64_t m, const int64_t* __restrict__ m_dev, int log2_buckets,
-                                                              uint32_t* __restrict__ first, Ctl* ctl, Publish pub) {
+                                                              uint32_t* __restrict__ first, unsigned long long* __restrict__ bits /* or null */,
+                                                              Ctl* ctl, Publish pub) {
   __shared__ unsigned long long table[kFilterSlots];
   __shared__ uint32_t noted[kFilterBlock / kWave][kFilterList];
   __shared__ BucketState st;
@@ -161,6 +162,11 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
   if (threadIdx.x == 0) { st = BucketState{0u, 0u, 0u}; s_overflow = 0; }
   __syncthreads();
   auto key_at = [&](uint32_t i) { return (uint32_t)(i < nd ? dst[i] : col[i - nd]); };
+  // the first position of edge position i; the edge whose position it is gets its bit (the words are clear when the kernel starts)
+  auto found = [&](uint32_t i, uint32_t at) {
+    first[i - nd] = at;
+    if (bits != nullptr && at == i) atomicOr(&bits[(i >> 6) - (nd >> 6)], 1ull << (i & 63u));
+  };
   const uint32_t width = 1u << (32 - log2_buckets), low = blockIdx.x * width;  // the bucket's hashes: low .. low + width - 1 (log2_buckets >= 1)
   auto slot = [&](uint32_t h) { return (h << log2_buckets) >> 20; };           // the hash bits behind those of the bucket
   static_assert(kFilterSlots == 1u << 12, "slot() takes 12 bits");
@@ -235,7 +241,7 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
     __syncthreads();
 #pragma unroll
     for (int v = 0; v < V; ++v)
-      if (pair[v] != kEmptySlot && (uint32_t)pair[v] >= nd) first[(uint32_t)pair[v] - nd] = (uint32_t)table[h[v]];
+      if (pair[v] != kEmptySlot && (uint32_t)pair[v] >= nd) found((uint32_t)pair[v], (uint32_t)table[h[v]]);
   } else {
     // a vertex that very many lists keep: the whole list is read again, twice, in the same steps.  (222 thousand entries, one
     // in 72 the same: 76 us; with one key per thread and step 158, in a table in HBM 51 and two launches more.  All of 130
@@ -272,7 +278,7 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
     each(col, n - nd, [&](uint32_t i, uint32_t key) { insert(nd + i, key); });
     __syncthreads();
     if (st.full == 0)
-      each(col, n - nd, [&](uint32_t i, uint32_t key) { first[i] = bucket_find(table, kFilterSlots, slot(filter_hash(key)), key); });
+      each(col, n - nd, [&](uint32_t i, uint32_t key) { found(nd + i, bucket_find(table, kFilterSlots, slot(filter_hash(key)), key)); });
   }
   if (threadIdx.x == 0) bucket_done(ctl, st, n_dst, pub);
 }
@@ -693,6 +699,64 @@ __global__ __launch_bounds__(kBlock) void k_uniq_relabel(const int32_t* __restri
   }
 }
 
+// The same for the shortest lists, straight from the bits that k_uniq_filter set: every block counts them all, 64 to a word, and keeps
+// words and ranks in LDS.  A launch of 5 to 6 us less than with k_uniq_collect in between; what the bits cost the filter, an atomic
+// per new vertex, grows with the list (6 to 8 us at 180 thousand entries).
+constexpr int kShortBlock = 1024, kShortEach = 4;
+constexpr int64_t kShortMax = 65536;  // entries of the whole list
+constexpr int kShortWords = (int)(kShortMax / 64) + 1;
+__global__ __launch_bounds__(kShortBlock) void k_uniq_relabel_short(const int32_t* __restrict__ dst, const int32_t* __restrict__ col, int64_t m,
+                                                                    const int64_t* __restrict__ m_dev, int64_t n_dst,
+                                                                    const unsigned long long* __restrict__ bits, int32_t* __restrict__ src,
+                                                                    int32_t* __restrict__ col_local) {
+  constexpr int kEach = (kShortWords + kShortBlock - 1) / kShortBlock;  // words per thread
+  __shared__ unsigned long long word[kEach * kShortBlock];
+  __shared__ uint32_t before[kEach * kShortBlock];
+  __shared__ uint32_t wave_total[kShortBlock / kWave];
+  const int64_t e0 = (int64_t)blockIdx.x * (kShortBlock * kShortEach) + threadIdx.x;
+  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  uint32_t f[kShortEach];
+#pragma unroll
+  for (int u = 0; u < kShortEach; ++u) {
+    const int64_t e = e0 + u * kShortBlock;
+    f[u] = e < m ? (uint32_t)col_local[e] : 0xFFFFFFFFu;
+    if (e < n_dst) src[e] = dst[e];
+  }
+  const uint32_t w0 = (uint32_t)(n_dst >> 6), n_words = (uint32_t)((n_dst + m + 63) >> 6) - w0;  // (at most kShortWords)
+  uint32_t c[kEach], sum = 0;
+#pragma unroll
+  for (int q = 0; q < kEach; ++q) {  // words in a row per thread
+    const uint32_t w = threadIdx.x * kEach + q;
+    const unsigned long long b = w < n_words ? bits[w] : 0ull;
+    word[w] = b;
+    c[q] = (uint32_t)__popcll(b);
+    sum += c[q];
+  }
+  const uint32_t incl = wave_incl_scan(sum);
+  if (lane_id() == kWave - 1) wave_total[wave_in_block()] = incl;
+  __syncthreads();
+  uint32_t run = incl - sum;
+  for (int q = 0; q < wave_in_block(); ++q) run += wave_total[q];
+#pragma unroll
+  for (int q = 0; q < kEach; ++q) {
+    before[threadIdx.x * kEach + q] = run;
+    run += c[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kShortEach; ++u) {
+    const int64_t e = e0 + u * kShortBlock;
+    if ((int64_t)f[u] >= n_dst + m) continue;  // (also: first positions that a failed dedup left unwritten)
+    int64_t local = f[u];
+    if (local >= n_dst) {
+      const uint32_t w = (f[u] >> 6) - w0;
+      local = n_dst + before[w] + __popcll(word[w] & ((1ull << (f[u] & 63)) - 1ull));
+      if ((int64_t)f[u] == n_dst + e && local < n_dst + m) src[local] = col[e];
+    }
+    col_local[e] = (int32_t)local;
+  }
+}
+
 __global__ void k_clear_uniq_overflow(Ctl* ctl) { ctl->uniq_overflow = 0; }
 
 static inline unsigned nblocks(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -717,7 +781,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     int log2_buckets = kFilterLeastLog2;
     while (((int64_t)kFilterPairs << log2_buckets) < n_all) ++log2_buckets;
     COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_filter, dim3(1u << log2_buckets), dim3(kFilterBlock), 0, s, dst, n_dst, col_global, m, m_dev, log2_buckets,
-                first, d_ctl, w->pub);
+                first, n_all <= kShortMax ? (unsigned long long*)w->words : (unsigned long long*)nullptr, d_ctl, w->pub);
   } else if (path == kByPartition) {
     const int64_t n_buckets = w->n_buckets;
     const int64_t by_size = (n_all + 4 * kPartBlock - 1) / (4 * kPartBlock);
@@ -760,7 +824,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     if (m > 0)
       COOP_LAUNCH(K_UNIQ_FLAG, k_uniq_lookup, dim3(nblocks(m)), dim3(kBlock), 0, s, col_global, m, m_dev, table, (uint64_t)cap, first);
   }
-  if (m > 0) {
+  if (m > 0 && !(path == kByFilter && n_all <= kShortMax)) {
     uint32_t* totals = alloc.get<uint32_t>(2 * (int64_t)collect_blocks, COOP_TAG_SCRATCH);
     if (alloc.failed) return COOP_E_NOMEM;
     w->block_prefix = totals + collect_blocks;
@@ -778,8 +842,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
   return COOP_OK;
 }
 
-int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
-                        int32_t* spare, UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
+int unique_prepare(int64_t n_dst, int64_t m, UniqueWork* w, Alloc& alloc) {
   const int64_t n_all = n_dst + m;
   const int64_t n_words = (n_all + 63) / 64 - (n_dst >> 6);
   w->words = alloc.get<RankWord>(n_words, COOP_TAG_SCRATCH);
@@ -795,8 +858,18 @@ int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_gl
   if (whole_rounds > 0 && n_all <= whole_rounds * (pairs_per_bucket + pairs_per_bucket / 8)) w->n_buckets = whole_rounds;
   const bool by_partition = m > 0 && w->n_buckets <= kPartMaxBuckets && g_unique_mode != 1 && (g_unique_mode >= 2 || n_all >= kFilterMax);
   const bool by_filter = !by_partition && g_unique_mode != 1 && n_all > 0 && n_all < kFilterMax;
-  return unique_launch(dst, n_dst, col_global, m, m_dev, col_local, spare, w, by_partition ? kByPartition : by_filter ? kByFilter : kByTable, alloc,
-                       d_ctl, h_ctl, s);
+  w->path = by_partition ? kByPartition : by_filter ? kByFilter : kByTable;
+  const bool bits = by_filter && n_all <= kShortMax;
+  w->clear = bits ? (uint64_t*)w->words : nullptr;
+  w->n_clear = bits ? n_words : 0;
+  return COOP_OK;
+}
+
+int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
+                        int32_t* spare, UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
+  if (w->clear != nullptr) fill_u64(w->clear, w->n_clear, 0, s);
+  w->clear = nullptr;
+  return unique_launch(dst, n_dst, col_global, m, m_dev, col_local, spare, w, (UniqPath)w->path, alloc, d_ctl, h_ctl, s);
 }
 
 int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
@@ -820,7 +893,10 @@ int unique_back(const int32_t* dst, int64_t n_dst, const int32_t* col_global, in
                 int32_t* col_local, int32_t* src, hipStream_t s) {
   const int64_t n_threads = m > n_dst ? m : n_dst;
   const RankView rank{w.words, w.block_prefix, w.part_blocks};
-  if (n_threads > 0)
+  if (n_threads > 0 && w.path == kByFilter && n_dst + m <= kShortMax)
+    COOP_LAUNCH(K_UNIQ_RELABEL, k_uniq_relabel_short, dim3((unsigned)((n_threads + kShortBlock * kShortEach - 1) / (kShortBlock * kShortEach))),
+                dim3(kShortBlock), 0, s, dst, col_global, m, m_dev, n_dst, (const unsigned long long*)w.words, src, col_local);
+  else if (n_threads > 0)
     COOP_LAUNCH(K_UNIQ_RELABEL, k_uniq_relabel, dim3(nblocks((n_threads + kRelabelUnroll - 1) / kRelabelUnroll)), dim3(kBlock), 0, s, dst, col_global, m, m_dev, n_dst, rank, src, col_local);
   return COOP_OK;
 }

@@ -894,6 +894,29 @@ def test_frontier_dedup_of_short_lists(P, shape):
         assert "unique_filter" in ran or size > 100000, (size, ran.keys())
 
 
+@pytest.mark.parametrize("mode", [1, 0])
+def test_offsets_around_the_edges_of_tiles(P, mode):
+    """Offsets that the filling kernel finds by itself (up to 32,768 destinations) and those that a scan leaves tile by tile
+    (4,096; NS: 64, 256 and 2,048), one destination to both sides, with the sizes read back late and at once; and lists of
+    destinations and edges to both sides of the 65,536 entries up to which the relabelling ranks the new vertices itself."""
+    n = 60000
+    rng = np.random.default_rng(21)
+    deg = rng.integers(0, 7, n)
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]).astype(np.int64))
+    g = G(P, indptr, torch.from_numpy(rng.integers(0, n, int(deg.sum())).astype(np.int32)))
+    perm = rng.permutation(n)
+    P.coop_tune(P.COOP_TUNE_DEFER_SIZES, mode)
+    try:
+        for size in (63, 65, 127, 129, 255, 257, 4095, 4096, 4097, 13107, 13108, 16385, 32767, 32768, 32769, 36864, 36865):
+            compare(P, g, perm[:size], (4,), R.NS, seed=size)
+            compare(P, g, perm[:size], (4, 2), R.LABOR0, seed=size)
+        for size in (127, 129, 4097, 32768, 32769):
+            compare(P, g, perm[:size], (4,), R.NS, it=3, kappa=4, seed=size)
+            compare_rw(P, g, perm[:size], (3,), 2, 5, 0.5, seed=size)
+    finally:
+        P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
+
+
 @pytest.mark.parametrize("size", [4096, 37000])
 def test_frontier_dedup_of_short_lists_with_a_hub(P, size):
     """One source in 36 is the same vertex, among others that differ: in the longer list more of them than a wave can note (16
