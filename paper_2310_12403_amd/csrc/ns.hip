@@ -223,10 +223,18 @@ struct NsList {
   u32x4 ring[kNsGroups];
   uint32_t rest[4];
   __device__ __forceinline__ NsList(const int32_t* list, uint32_t entries) : in(list, entries), n(entries), n_groups(entries / kGroup) {
+    // (no load for what is not there: 16 bytes per lane cost a CU 16 clocks, also where every lane is behind the end)
+    const uint32_t tail = n & ~(kGroup - 1);
 #pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) rest[q] = in.entry((n & ~(kGroup - 1)) + q * kWave);
+    for (uint32_t q = 0; q < 4; ++q) {
+      rest[q] = any_value();
+      if (tail + q * kWave < n) rest[q] = in.entry(tail + q * kWave);
+    }
 #pragma unroll
-    for (uint32_t q = 0; q < kNsGroups; ++q) ring[q] = in.group(q);  // (behind the end of the list: zeros, and no traffic)
+    for (uint32_t q = 0; q < kNsGroups; ++q) {
+      ring[q] = u32x4{any_value(), any_value(), any_value(), any_value()};
+      if (q < n_groups) ring[q] = in.group(q);
+    }
   }
 };
 __device__ __forceinline__ uint32_t ns_collect_plain(NsList& L, uint32_t j0, uint32_t bound, const NsKeys& K, NsSlot* __restrict__ slot, uint32_t cap,
@@ -268,7 +276,7 @@ __device__ __forceinline__ uint32_t ns_collect_plain(NsList& L, uint32_t j0, uin
         }
         n_c = (uint32_t)__builtin_amdgcn_readlane((int)to, kWave - 1);
       }
-      L.ring[q] = L.in.group(g + kNsGroups);
+      if (g + kNsGroups < L.n_groups) L.ring[q] = L.in.group(g + kNsGroups);
     }
   }
   const uint32_t tail = L.n & ~(kGroup - 1);

@@ -86,6 +86,16 @@ __device__ __forceinline__ uint32_t vector_copy(uint32_t x) {
 #endif
   return x;
 }
+// a register with whatever it holds (for values that are only used where they have been set)
+__device__ __forceinline__ uint32_t any_value() {
+#ifdef __HIP_DEVICE_COMPILE__
+  uint32_t x;
+  asm("" : "=v"(x));
+  return x;
+#else
+  return 0;
+#endif
+}
 __device__ __forceinline__ uint32_t fold16_xor(uint32_t x, uint32_t key) {
 #ifdef __HIP_DEVICE_COMPILE__
   return __builtin_amdgcn_bitop3_b32(x >> 16, x, key, 0x96);
