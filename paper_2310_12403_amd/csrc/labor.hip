@@ -10,6 +10,7 @@
 // second time, in order, straight into the edge arrays.
 #include "device_utils.h"
 #include "blend_filters.h"
+#include "list_reader.h"
 #include "sample_internal.h"
 
 namespace coop {
@@ -473,131 +474,210 @@ __device__ __forceinline__ uint32_t labor_scan_ordered(const int32_t* __restrict
   return count;
 }
 
-// Kept entries of one list and one layer, parked in registers: lane q holds the q-th kept entry.
-struct KeptRegs {
-  int32_t ent_t = 0, ent_j = 0;
-  uint32_t count = 0;  // wave-uniform
-  __device__ __forceinline__ void push(uint32_t lane, int32_t t, int32_t j) {
-    if (lane == (count & 63u)) { ent_t = t; ent_j = j; }
-    ++count;
-  }
-};
+// ---- independent variates (c = 0) ---------------------------------------------------------------------------------
+// A wave's kept entries of one list, layer by layer: in list order in LDS until the list is done, then one 8-byte store per
+// lane to the destination's staging row.
+constexpr uint32_t kKeptSlots = 64;  // (no staging row is longer; what a list keeps beyond it is counted, not stored)
+struct KeptSlots { StageEntry at[kKeptSlots + kWave]; };  // the last kWave: a slot per lane that nobody reads
 
-// Where the fast scan puts the kept entries of a list.  take(l, mm, f, t, j): in this wave step the lanes of mask mm
-// (f = this lane is one of them) keep entry t at list position j for layer l.
-//
-// RegSink parks them in registers, one entry per lane (for the pieces of a cut list: a piece learns its place in the
-// destination's staging row only when it knows how many entries it keeps).
 template <int NF>
-struct RegSink {
-  KeptRegs kept[NF];
-  __device__ __forceinline__ void take(int l, uint64_t mm, bool, int32_t t, int32_t j, uint32_t lane) {
-    while (mm != 0) {
-      const int src_lane = __builtin_ctzll(mm);
-      mm &= mm - 1;
-      kept[l].push(lane, __builtin_amdgcn_readlane(t, src_lane), __builtin_amdgcn_readlane(j, src_lane));
-    }
-  }
-};
-// RowSink writes them straight to the destination's staging row, each lane its own entry at the next free slots
-// (running count plus the lane's rank in the mask): no loop over the entries, and no particular order in the row
-// (the fill pass ranks such rows by list position).  Entries beyond the row's capacity are counted, not stored.
-template <int NF>
-struct RowSink {
-  StageEntry* row[NF];
-  uint32_t count[NF];  // wave-uniform
-  uint32_t cap;
-  __device__ __forceinline__ void take(int l, uint64_t mm, bool f, int32_t t, int32_t j, uint32_t) {
-    const uint32_t slot = count[l] + lanes_below(mm);
-    if (f && slot < cap) row[l][slot] = StageEntry{t, (uint32_t)j};
-    count[l] += (uint32_t)__popcll(mm);
-  }
-};
+struct PlainKeys { uint32_t head[NF], tail[NF]; };  // in vector registers (vector_copy)
+__device__ __forceinline__ uint32_t labor_uniform(uint32_t head, uint32_t tail, uint32_t t) { return fold16_xor(mix_body(fold16_xor(t, head)), tail); }
 
-// Fast scan of a long list (d > 64) for NF layers at once.  The list is read as 16-byte aligned groups of four
-// entries, kScanGroups groups per lane and step, all requested before the first is hashed.  Only groups that lie
-// wholly inside the list go through the main loop, so validity is one compare per group, not per entry; the up to
-// three entries in front of the first whole group and behind the last one are handled by one extra step.  Per entry
-// and layer the hot loop is the mixer and one compare; one ballot per group tells whether any lane kept anything for
-// any layer.  Only then are the (few) kept entries picked off per-entry ballot masks by a wave-uniform loop and
-// parked in registers, in no particular order (they are ranked when the list is done).
-template <bool BLEND, int NF, typename Sink>
-__device__ __forceinline__ void labor_scan_fast(const int32_t* __restrict__ g_indices, int64_t beg, uint32_t d, uint32_t j0,
-                                                const uint32_t (&thr)[NF], const FusedKeys& keys, Sink& sink) {
-  constexpr uint32_t kStep = kWave * 4 * kScanGroups;
-  const int64_t abeg = beg & ~(int64_t)3;        // first aligned group
-  const uint32_t head = (uint32_t)(beg - abeg);  // entries of that group that precede the list
-  const uint32_t total = head + d;               // list end, relative to abeg
-  const uint32_t vec_end = total & ~3u;          // whole groups end here
-  const uint32_t vec_beg = head ? 4u : 0u;       // whole groups start here
-  const int32_t* __restrict__ p = g_indices + abeg;
+// One pass over a list (or a stretch of it that starts at list position j0) for NF layers: neighbours with R_t <= thr[l] go to
+// layer l's slots behind the n[l] that are there; those behind kKeptSlots are counted, not stored.
+template <int NF>
+__device__ __forceinline__ void labor_collect(ListReader& L, uint32_t j0, const uint32_t (&thr)[NF], const PlainKeys<NF>& K, KeptSlots* slots,
+                                              uint32_t (&n)[NF]) {
   const uint32_t lane = (uint32_t)lane_id();
-  const int32_t j_lane = (int32_t)(lane * 4 + j0) - (int32_t)head;  // list position of this lane's first entry at r0 = 0
-
-  // The loads of the next step are issued before this step's entries are hashed.  A lane whose group lies behind the
-  // list loads the last whole group instead (in bounds, and cheaper than switching lanes off); `ok` discards it.
-  i32x4 nbuf[kScanGroups];
-  auto fetch = [&](uint32_t at) {
+  const uint32_t idle = kKeptSlots + lane;
+  for (uint32_t g0 = 0; g0 < L.n_groups; g0 += kReaderGroups) {
 #pragma unroll
-    for (int gq = 0; gq < kScanGroups; ++gq) {
-      if (at + (uint32_t)(gq * kWave * 4) >= vec_end) break;  // wave-uniform: the whole slot lies behind the list
-      uint32_t r = at + (uint32_t)(gq * kWave * 4) + lane * 4;
-      r = r < vec_end - 4 ? r : vec_end - 4;
-      nbuf[gq] = __builtin_nontemporal_load(reinterpret_cast<const i32x4*>(p + r));
-    }
-  };
+    for (uint32_t q = 0; q < kReaderGroups; ++q) {
+      const uint32_t g = g0 + q;
+      if (g >= L.n_groups) break;
+      uint64_t m[NF][4];
 #pragma unroll
-  for (int gq = 0; gq < kScanGroups; ++gq) nbuf[gq] = i32x4{0, 0, 0, 0};
-  if (vec_beg < vec_end) fetch(vec_beg);
-  // The ragged ends (lanes 0..2: the entries in front of the first whole group; lanes 3..5: those behind the last one)
-  // are requested right behind the first step, not when the whole groups are done: a list of one or two steps, and
-  // most lists are, then waits for memory once, not twice.
-  const uint32_t end_pos = lane < 3 ? head + lane : vec_end + (lane - 3);
-  const bool end_valid = lane < 3 ? (head != 0 && end_pos < 4 && end_pos < total) : (lane < 6 && end_pos < total && vec_end >= vec_beg);
-  int32_t end_t = 0;
-  if (end_valid) end_t = p[end_pos];
-  for (uint32_t base = vec_beg; base < vec_end; base += kStep) {
-    i32x4 buf[kScanGroups];
-    bool ok[kScanGroups];
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int gq = 0; gq < kScanGroups; ++gq) {
-      buf[gq] = nbuf[gq];
-      ok[gq] = base + (uint32_t)(gq * kWave * 4) + lane * 4 < vec_end;
-    }
-    if (base + kStep < vec_end) fetch(base + kStep);
+        for (int l = 0; l < NF; ++l) m[l][e] = compare_mask(labor_uniform(K.head[l], K.tail[l], L.ring[q][e]) <= thr[l]);
 #pragma unroll
-    for (int gq = 0; gq < kScanGroups; ++gq) {
-      const uint32_t r0 = base + (uint32_t)(gq * kWave * 4);  // wave-uniform
-      if (r0 >= vec_end) break;                                // the rest of this step lies behind the list
-      bool f[NF][4];
-      bool any = false;
+      for (int l = 0; l < NF; ++l) {
+        if ((m[l][0] | m[l][1] | m[l][2] | m[l][3]) == 0) continue;
+        uint32_t to = n[l];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t folded = fold16((uint32_t)buf[gq][e]);  // (shared by the layers)
+        for (int e = 0; e < 4; ++e) to = lanes_below_plus(m[l][e], to);
 #pragma unroll
-        for (int l = 0; l < NF; ++l) {
-          if constexpr (BLEND) f[l][e] = ok[gq] & (variate<false, true>(keys.K[l], keys.cw, keys.sw, (uint32_t)buf[gq][e], 0u, 0u) <= thr[l]);
-          else f[l][e] = ok[gq] & (keyed_from_head<false>(keys.K[l].Ka, folded, 0u) <= thr[l]);
-          any |= f[l][e];
-        }
-      }
-      if (ballot64(any) != 0) {
-#pragma unroll
-        for (int l = 0; l < NF; ++l) {
+        for (int e = 0; e < 4; ++e) n[l] += (uint32_t)__popcll(m[l][e]);
+        const uint32_t j = j0 + g * kGroup + lane * 4;
+        if (n[l] <= kKeptSlots) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const uint64_t mm = ballot64(f[l][e]);
-            if (mm != 0) sink.take(l, mm, f[l][e], buf[gq][e], j_lane + (int32_t)(r0 + e), lane);
+            slots[l].at[lane_in(m[l][e]) ? to : idle] = StageEntry{(int32_t)L.ring[q][e], j + e};
+            to += lane_in(m[l][e]) ? 1u : 0u;
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (lane_in(m[l][e])) {
+              if (to < kKeptSlots) slots[l].at[to] = StageEntry{(int32_t)L.ring[q][e], j + e};
+              ++to;
+            }
           }
         }
       }
+      if (g + kReaderGroups < L.n_groups) L.ring[q] = L.in.group(g + kReaderGroups);
     }
   }
+  const uint32_t tail = L.n & ~(kGroup - 1);
 #pragma unroll
-  for (int l = 0; l < NF; ++l) {  // the ragged ends
-    const bool fl = end_valid && variate<false, BLEND>(keys.K[l], keys.cw, keys.sw, (uint32_t)end_t, 0u, 0u) <= thr[l];
-    const uint64_t mm = ballot64(fl);
-    if (mm != 0) sink.take(l, mm, fl, end_t, (int32_t)(end_pos - head + j0), lane);
+  for (uint32_t q = 0; q < 4; ++q) {
+    const uint32_t at = tail + q * kWave;
+    if (at >= L.n) return;
+    const uint64_t there = low_lanes(L.n - at);
+#pragma unroll
+    for (int l = 0; l < NF; ++l) {
+      const uint64_t m = compare_mask(labor_uniform(K.head[l], K.tail[l], L.rest[q]) <= thr[l]) & there;
+      if (m == 0) continue;
+      const uint32_t to = lanes_below_plus(m, n[l]);
+      n[l] += (uint32_t)__popcll(m);
+      if (lane_in(m) && to < kKeptSlots) slots[l].at[to] = StageEntry{(int32_t)L.rest[q], j0 + at + lane};
+    }
+  }
+}
+
+// The scan pass with independent variates.  As k_ns_fill, which says what its parts are for: a wave takes `each` neighbouring
+// destinations (a power of two, at most 64), lists of up to twice the 64 / each lanes that a destination has are looked at
+// together, the others one after the other through the whole wave, the next one's entries requested before this one's kept
+// entries leave.  The first `piece_blocks` blocks take the pieces of the long lists (block b takes pieces b,
+// b + piece_blocks, ... of the queue, whose length is read from device memory); a piece adds its kept-edge counts to the list's
+// counters and puts its entries wherever that leaves them in the staging row: the fill pass sorts the rows by list position.
+template <int NF>
+__global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_scan_plain(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg,
+                                                               const uint32_t* __restrict__ thr_all, int64_t n, int each_log2, FusedKeys keys,
+                                                               uint32_t stage_cap, ScanOut out, Ctl* ctl, int piece_blocks,
+                                                               const Piece* __restrict__ pieces, const uint32_t* __restrict__ piece_count,
+                                                               uint32_t piece_cap, uint32_t piece_len) {
+  __shared__ KeptSlots slots[NF];
+  const uint32_t lane = (uint32_t)lane_id();
+  auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
+  auto of64 = [&](int64_t x, int q) { return (int64_t)(((uint64_t)of((uint32_t)((uint64_t)x >> 32), q) << 32) | of((uint32_t)x, q)); };
+  PlainKeys<NF> K;
+#pragma unroll
+  for (int l = 0; l < NF; ++l) { K.head[l] = vector_copy(keys.K[l].Ka[4]); K.tail[l] = vector_copy(keys.K[l].Ka[1]); }
+  auto settle = [] {
+    __builtin_amdgcn_wave_barrier();
+    __threadfence_block();
+  };
+  if ((int)blockIdx.x < piece_blocks) {
+    uint32_t n_pieces = *piece_count;
+    if (n_pieces > piece_cap) n_pieces = piece_cap;
+    for (uint32_t p = blockIdx.x; p < n_pieces; p += (uint32_t)piece_blocks) {
+      const Piece pc = pieces[p];
+      const uint32_t list = of(pc.list, 0), q = of(pc.q, 0);
+      if (list == kNoPiece) continue;
+      const Segment g = seg[list];
+      const int64_t beg = of64(g.beg, 0);
+      const uint32_t d = of(g.d, 0);
+      const uint32_t np = (d + piece_len - 1) / piece_len;  // as in k_segments
+      const uint32_t plen = ((d + np - 1) / np + 3u) & ~3u;
+      const uint64_t j0 = (uint64_t)q * plen;
+      if (j0 >= d) continue;  // rounding the piece length up can leave the last slots of a very long list empty
+      uint32_t thr[NF], kept[NF];
+#pragma unroll
+      for (int l = 0; l < NF; ++l) { thr[l] = of(thr_all[(int64_t)l * n + list], 0); kept[l] = 0; }
+      ListReader L(g_indices + beg + j0, d - (uint32_t)j0 < plen ? d - (uint32_t)j0 : plen);
+      labor_collect<NF>(L, (uint32_t)j0, thr, K, slots, kept);
+      settle();
+#pragma unroll
+      for (int l = 0; l < NF; ++l) {
+        const uint32_t c = kept[l];
+        if (c == 0) continue;
+        uint32_t at = 0;
+        if (lane == 0) at = (uint32_t)atomicAdd(&out.cnt[l][list], (int32_t)c);
+        at = of(at, 0);
+        if (at + c <= stage_cap) {  // c <= stage_cap <= kKeptSlots: every entry has its slot
+          if (lane < c) out.stage[l][(size_t)list * stage_cap + at + lane] = slots[l].at[lane];
+        } else if (at <= stage_cap && lane == 0) {
+          atomicAdd(&ctl->n_overflow, 1);  // the one piece that takes the row over its capacity reports the list
+        }
+      }
+      settle();
+    }
+    return;
+  }
+  const int64_t w0 = (int64_t)xcd_runs(blockIdx.x - (uint32_t)piece_blocks, gridDim.x - (uint32_t)piece_blocks) << each_log2;
+  if (w0 >= n) return;
+  const uint32_t n_mine = n - w0 < ((int64_t)1 << each_log2) ? (uint32_t)(n - w0) : 1u << each_log2;
+  const uint32_t lanes = 64u >> each_log2, sub = lane & (lanes - 1), number = lane >> (6 - each_log2);
+  const int64_t w = w0 + (number < n_mine ? number : n_mine - 1);
+  const Segment g = seg[w];
+  uint32_t my_thr[NF], my_kept[NF];
+#pragma unroll
+  for (int l = 0; l < NF; ++l) { my_thr[l] = thr_all[(int64_t)l * n + w]; my_kept[l] = 0; }
+  const bool live = number < n_mine && g.split == 0, speaks = live && sub == 0;  // (split: scanned by other waves, or not at all)
+  const uint32_t together = each_log2 != 0 ? 2 * lanes : 0;
+  if (ballot64(live && g.d <= together && g.d != 0) != 0) {
+    const uint64_t group = low_lanes(lanes) << (number * lanes);
+    bool in[2];
+    uint32_t t[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      in[r] = live && g.d <= together && sub + r * lanes < g.d;
+      t[r] = 0;
+      if (in[r]) t[r] = (uint32_t)(g_indices + g.beg)[sub + r * lanes];
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int l = 0; l < NF; ++l) {
+        const bool keep = in[r] && labor_uniform(K.head[l], K.tail[l], t[r]) <= my_thr[l];
+        const uint64_t m = ballot64(keep) & group;
+        const uint32_t place = my_kept[l] + lanes_below(m);
+        if (keep && place < stage_cap) out.stage[l][(size_t)w * stage_cap + place] = StageEntry{(int32_t)t[r], sub + r * lanes};
+        my_kept[l] += (uint32_t)__popcll(m);
+      }
+  }
+  uint64_t todo = ballot64(speaks && g.d > together);
+  if (todo != 0) {
+    int at = __builtin_ctzll(todo);
+    uint32_t d = of(g.d, at), j0 = 0, thr[NF], kept[NF];
+    int64_t beg = of64(g.beg, at);
+#pragma unroll
+    for (int l = 0; l < NF; ++l) { thr[l] = of(my_thr[l], at); kept[l] = 0; }
+    for (ListReader L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+      labor_collect<NF>(L, j0, thr, K, slots, kept);
+      if (d - j0 > kStretch) {  // the list's next stretch
+        j0 += kStretch;
+        L = ListReader(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+        continue;
+      }
+      const int done = at;
+      todo &= todo - 1;
+      at = todo != 0 ? __builtin_ctzll(todo) : 0;
+      d = todo != 0 ? of(g.d, at) : 0u;
+      beg = of64(g.beg, at);
+      j0 = 0;
+      L = ListReader(g_indices + beg, d < kStretch ? d : kStretch);
+      settle();
+#pragma unroll
+      for (int l = 0; l < NF; ++l) {
+        const uint32_t c = kept[l] < stage_cap ? kept[l] : stage_cap;
+        if (lane < c) out.stage[l][(size_t)(w0 + (done >> (6 - each_log2))) * stage_cap + lane] = slots[l].at[lane];
+        if ((int)lane == done) my_kept[l] = kept[l];
+        thr[l] = of(my_thr[l], at);
+        kept[l] = 0;
+      }
+      settle();
+      if (todo == 0) break;
+    }
+  }
+  if (speaks) {
+#pragma unroll
+    for (int l = 0; l < NF; ++l) {
+      out.cnt[l][w] = (int32_t)my_kept[l];
+      if (my_kept[l] > stage_cap) atomicAdd(&ctl->n_overflow, 1);
+    }
   }
 }
 
@@ -813,17 +893,16 @@ __device__ __forceinline__ void labor_scan_blend(const int32_t* __restrict__ g_i
 
 // The first `piece_blocks` blocks of the grid take the pieces of the long lists (wave w takes pieces w, w + W, ... of
 // the queue, W = their number of waves; the queue length is read from device memory, so every wave ends after a
-// bounded number of steps).  A piece adds its kept-edge counts to the list's counters and puts its entries wherever
-// that leaves them in the staging row; the fill pass sorts the rows of cut lists by list position.
-template <bool BLEND, int VEC, int NF>
-__global__ __launch_bounds__(kBlock) void k_labor_scan(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg,
+// bounded number of steps).  VEC = 4: the indices array is 16-byte aligned, and the variates go through the staged filters.
+template <int VEC, int NF>
+__global__ __launch_bounds__(kBlock) void k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg,
                                                        const uint32_t* __restrict__ thr_all, const PreThr* __restrict__ pthr_all,
                                                        const float* __restrict__ lim2_all, int64_t n, int lists_per_wave, FusedKeys keys,
                                                        uint32_t stage_cap, ScanOut out,
                                                        Ctl* ctl, int piece_blocks, const Piece* __restrict__ pieces,
                                                        const uint32_t* __restrict__ piece_count, uint32_t piece_cap, uint32_t piece_len,
                                                        CandOut cand) {
-  constexpr bool kQueued = BLEND && VEC == 4;  // blended variates through the staged filters
+  constexpr bool kQueued = VEC == 4;
   extern __shared__ __align__(16) uint32_t scan_lds[];  // with kQueued: a FirstQueue per wave of the block
   BlendState bst{};
   if constexpr (kQueued) {
@@ -852,43 +931,21 @@ __global__ __launch_bounds__(kBlock) void k_labor_scan(const int32_t* __restrict
         if (j0_64 >= d) continue;  // rounding the piece length up can leave the last slots of a very long list empty
         const uint32_t j0 = (uint32_t)j0_64;
         const uint32_t len = d - j0 < plen ? d - j0 : plen;
-        uint32_t thr[NF];
-#pragma unroll
-        for (int l = 0; l < NF; ++l) thr[l] = (uint32_t)__builtin_amdgcn_readfirstlane((int)thr_all[(int64_t)l * n + list]);
-        if constexpr (kQueued) {
-          PreThr pthr[NF];
-          ListBlend<NF> lb;
-          lb.first = list;  // every lane holds this list's thresholds: slot 0
-#pragma unroll
-          for (int l = 0; l < NF; ++l) {
-            const PreThr pt = pthr_all[(int64_t)l * n + list];
-            pthr[l].a2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pt.a2);
-            pthr[l].a1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pt.a1);
-            pthr[l].b2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pt.b2);
-            pthr[l].keep2 = pt.keep2;
-            lb.keep2[l] = pt.keep2;
-            lb.lim2[l] = lim2_all[(int64_t)l * n + list];
-          }
-          labor_scan_blend<NF>(g_indices, beg + j0, len, j0, 0u, pthr, lb, keys, bst, stage_cap, out, ctl);
-          blend_flush_first<NF>(bst, lb, keys, stage_cap, out, ctl);
-          continue;
-        }
-        RegSink<NF> sink;
-        KeptRegs (&kept)[NF] = sink.kept;
-        labor_scan_fast<BLEND, NF>(g_indices, beg + j0, len, j0, thr, keys, sink);
+        PreThr pthr[NF];
+        ListBlend<NF> lb;
+        lb.first = list;  // every lane holds this list's thresholds: slot 0
 #pragma unroll
         for (int l = 0; l < NF; ++l) {
-          const uint32_t c = kept[l].count;
-          if (c == 0) continue;
-          uint32_t at = 0;
-          if (lane == 0) at = (uint32_t)atomicAdd(&out.cnt[l][list], (int32_t)c);
-          at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-          if (at + c <= stage_cap) {  // c <= stage_cap <= 64: every entry is still in its register
-            if (lane < c) out.stage[l][(size_t)list * stage_cap + at + lane] = StageEntry{kept[l].ent_t, (uint32_t)kept[l].ent_j};
-          } else if (at <= stage_cap && lane == 0) {
-            atomicAdd(&ctl->n_overflow, 1);  // the one piece that takes the row over its capacity reports the list
-          }
+          const PreThr pt = pthr_all[(int64_t)l * n + list];
+          pthr[l].a2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pt.a2);
+          pthr[l].a1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pt.a1);
+          pthr[l].b2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pt.b2);
+          pthr[l].keep2 = pt.keep2;
+          lb.keep2[l] = pt.keep2;
+          lb.lim2[l] = lim2_all[(int64_t)l * n + list];
         }
+        labor_scan_blend<NF>(g_indices, beg + j0, len, j0, 0u, pthr, lb, keys, bst, stage_cap, out, ctl);
+        blend_flush_first<NF>(bst, lb, keys, stage_cap, out, ctl);
       }
       return;
     }
@@ -926,13 +983,6 @@ __global__ __launch_bounds__(kBlock) void k_labor_scan(const int32_t* __restrict
                                   (uint32_t)__builtin_amdgcn_readlane((int)beg_lo, i));
     const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)g.d, i);
     if (__builtin_amdgcn_readlane((int)g.split, i) != 0) continue;  // cut into pieces, scanned by other waves
-    uint32_t thr[NF];
-    bool any_all = false;
-#pragma unroll
-    for (int l = 0; l < NF; ++l) {
-      thr[l] = (uint32_t)__builtin_amdgcn_readlane((int)my_thr[l], i);
-      any_all |= thr[l] == kAllThr;
-    }
     if constexpr (kQueued) {  // every list, whatever its length: kept edges reach the rows through the queues
       PreThr pthr[NF];
 #pragma unroll
@@ -945,25 +995,15 @@ __global__ __launch_bounds__(kBlock) void k_labor_scan(const int32_t* __restrict
       if (d != 0) labor_scan_blend<NF>(g_indices, beg, d, 0u, (uint32_t)i, pthr, lbw, keys, bst, stage_cap, out, ctl);
       continue;
     }
-    if (VEC == 4 && !any_all && d > (uint32_t)kWave) {
-      RowSink<NF> sink;
-      sink.cap = stage_cap;
 #pragma unroll
-      for (int l = 0; l < NF; ++l) { sink.row[l] = out.stage[l] + (size_t)(first + i) * stage_cap; sink.count[l] = 0; }
-      labor_scan_fast<BLEND, NF>(g_indices, beg, d, 0u, thr, keys, sink);
-#pragma unroll
-      for (int l = 0; l < NF; ++l)
-        if ((int)lane == i) my_count[l] = sink.count[l];
-    } else {
-#pragma unroll
-      for (int l = 0; l < NF; ++l) {
-        StageEntry* row = out.stage[l] + (size_t)(first + i) * stage_cap;
-        const uint32_t c = labor_scan_ordered<BLEND>(g_indices, beg, d, thr[l], keys.K[l], keys.cw, keys.sw,
-                                                     [&](uint32_t rank, int32_t t, uint32_t j) {
-                                                       if (rank < stage_cap) row[rank] = StageEntry{t, j};
-                                                     });
-        if ((int)lane == i) my_count[l] = c;
-      }
+    for (int l = 0; l < NF; ++l) {
+      const uint32_t thr = (uint32_t)__builtin_amdgcn_readlane((int)my_thr[l], i);
+      StageEntry* row = out.stage[l] + (size_t)(first + i) * stage_cap;
+      const uint32_t c = labor_scan_ordered<true>(g_indices, beg, d, thr, keys.K[l], keys.cw, keys.sw,
+                                                  [&](uint32_t rank, int32_t t, uint32_t j) {
+                                                    if (rank < stage_cap) row[rank] = StageEntry{t, j};
+                                                  });
+      if ((int)lane == i) my_count[l] = c;
     }
   }
   if constexpr (kQueued) {
@@ -1089,17 +1129,40 @@ __global__ __launch_bounds__(kBlock) void k_labor_fill_overflow(const int32_t* _
   });
 }
 
-template <bool BLEND, int VEC>
-static void launch_scan(int nf, dim3 grid, dim3 block, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, const PreThr* pthr, const float* lim2, int64_t n,
-                        int lpw, const FusedKeys& keys, uint32_t cap, const ScanOut& out, Ctl* ctl, int piece_blocks, const Piece* pieces,
-                        const uint32_t* piece_count, uint32_t piece_cap, uint32_t piece_len, const CandOut& cand) {
+template <int VEC>
+static void launch_scan_blend(int nf, dim3 grid, dim3 block, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, const PreThr* pthr, const float* lim2, int64_t n,
+                              int lpw, const FusedKeys& keys, uint32_t cap, const ScanOut& out, Ctl* ctl, int piece_blocks, const Piece* pieces,
+                              const uint32_t* piece_count, uint32_t piece_cap, uint32_t piece_len, const CandOut& cand) {
+  const size_t lds = VEC == 4 ? (size_t)(block.x / kWave) * sizeof(FirstQueue) : 0;
+#define COOP_SCAN_BLEND(NF)                                                                                                              \
+  COOP_LAUNCH(K_LABOR_COUNT, (k_labor_scan_blend<VEC, NF>), grid, block, lds, s, indices, seg, thr, pthr, lim2, n, lpw, keys, cap, out, ctl, \
+              piece_blocks, pieces, piece_count, piece_cap, piece_len, cand)
   switch (nf) {
-    case 1: COOP_LAUNCH(K_LABOR_COUNT, (k_labor_scan<BLEND, VEC, 1>), grid, block, (BLEND && VEC == 4) ? (size_t)(block.x / kWave) * sizeof(FirstQueue) : 0, s, indices, seg, thr, pthr, lim2, n, lpw, keys, cap, out, ctl, piece_blocks, pieces, piece_count, piece_cap, piece_len, cand); break;
-    case 2: COOP_LAUNCH(K_LABOR_COUNT, (k_labor_scan<BLEND, VEC, 2>), grid, block, (BLEND && VEC == 4) ? (size_t)(block.x / kWave) * sizeof(FirstQueue) : 0, s, indices, seg, thr, pthr, lim2, n, lpw, keys, cap, out, ctl, piece_blocks, pieces, piece_count, piece_cap, piece_len, cand); break;
-    case 3: COOP_LAUNCH(K_LABOR_COUNT, (k_labor_scan<BLEND, VEC, 3>), grid, block, (BLEND && VEC == 4) ? (size_t)(block.x / kWave) * sizeof(FirstQueue) : 0, s, indices, seg, thr, pthr, lim2, n, lpw, keys, cap, out, ctl, piece_blocks, pieces, piece_count, piece_cap, piece_len, cand); break;
-    default: COOP_LAUNCH(K_LABOR_COUNT, (k_labor_scan<BLEND, VEC, 4>), grid, block, (BLEND && VEC == 4) ? (size_t)(block.x / kWave) * sizeof(FirstQueue) : 0, s, indices, seg, thr, pthr, lim2, n, lpw, keys, cap, out, ctl, piece_blocks, pieces, piece_count, piece_cap, piece_len, cand); break;
+    case 1: COOP_SCAN_BLEND(1); break;
+    case 2: COOP_SCAN_BLEND(2); break;
+    case 3: COOP_SCAN_BLEND(3); break;
+    default: COOP_SCAN_BLEND(4); break;
   }
+#undef COOP_SCAN_BLEND
 }
+static void launch_scan_plain(int nf, unsigned blocks, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, int64_t n, int each_log2,
+                              const FusedKeys& keys, uint32_t cap, const ScanOut& out, Ctl* ctl, int piece_blocks, const Piece* pieces,
+                              const uint32_t* piece_count, uint32_t piece_cap, uint32_t piece_len) {
+#define COOP_SCAN_PLAIN(NF)                                                                                                           \
+  COOP_LAUNCH(K_LABOR_COUNT, k_labor_scan_plain<NF>, dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, n, each_log2, keys, cap, out, ctl, \
+              piece_blocks, pieces, piece_count, piece_cap, piece_len)
+  switch (nf) {
+    case 1: COOP_SCAN_PLAIN(1); break;
+    case 2: COOP_SCAN_PLAIN(2); break;
+    case 3: COOP_SCAN_PLAIN(3); break;
+    default: COOP_SCAN_PLAIN(4); break;
+  }
+#undef COOP_SCAN_PLAIN
+}
+
+constexpr int64_t kPieceWaves = 8192;
+constexpr int64_t kScanWaves = 16384;
+constexpr int kScanEachLog2 = 3;
 
 int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop_block* blk, int64_t edge_cap) {
   const bool defer = edge_cap > 0;
@@ -1152,7 +1215,7 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
     ks[f] = (uint32_t)cx.fanouts[l + f];
   }
   // long lists are cut into pieces (k_segments queues them); room for every piece the graph's edges could make
-  const uint32_t piece_len = cx.vec4 ? (uint32_t)g_piece_len : 0u;
+  const uint32_t piece_len = cx.vec4 || !cx.blend ? (uint32_t)g_piece_len : 0u;
   // Lists longer than split_min go to the piece waves, which come first in the grid.  With independent variates that is
   // for the lists worth cutting (twice the piece length).  The blended scan costs three times as much per entry, and a
   // wave that meets a few lists of several thousand entries late in the kernel keeps it waiting: there every list above
@@ -1296,29 +1359,29 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
                     cx.g->indices, (const uint32_t*)cx.g->rev_pos, (const uint32_t*)long_bits, (const LongSlot*)long_tab, long_mask, cap, out,
                     eo, cx.d_ctl);
       }
-      // lists per wave: a few amortise the record fetch once there are plenty of lists (the knob overrides)
-      int lpw = g_lists_per_wave;
-      if (lpw == 0) lpw = n_new >= 65536 ? (cx.blend && cx.vec4 ? 8 : 4) : 1;  // blended: fuller waves at the fp32 stage
-      while (lpw < kWave && (n_new + lpw - 1) / lpw > kSliceLists / 2) lpw = 2 * lpw < kWave ? 2 * lpw : kWave;  // (no more waves than a launch can have)
-      const int64_t n_waves = (n_new + lpw - 1) / lpw;
       // the piece waves come first in the grid: one round of resident blocks, fewer if there cannot be that many pieces
-      constexpr int64_t kPieceBlocks = 2048;
-      // waves per block: a block leaves the CU when its slowest wave is done, and the lists differ in length by orders
-      // of magnitude, so with four waves a block's slots stand empty for much of its life; two waves per block take 3 to
-      // 8 % off the scan with independent variates (one: 2 to 5 %), one wave per block 2 % off the blended one, which
-      // is bound by its arithmetic (its first-stage queues are dynamic LDS, one per wave of the block)
-      const int wpb = cx.blend ? 1 : 2;
-      const dim3 block((unsigned)(wpb * kWave));
-      const int64_t piece_waves = (int64_t)piece_cap < kPieceBlocks * kWavesPerBlock ? (int64_t)piece_cap : kPieceBlocks * kWavesPerBlock;
-      const int piece_blocks = (int)blocks_for(piece_waves, wpb);
-      const dim3 grid(blocks_for(n_waves, wpb) + (unsigned)piece_blocks);
+      const int64_t piece_waves = (int64_t)piece_cap < kPieceWaves ? (int64_t)piece_cap : kPieceWaves;
       const uint32_t* pcount = cx.d_piece_count + l;
-      if (cx.blend) {
-        if (cx.vec4) launch_scan<true, 4>(ps.nf, grid, block, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, lpw, keys, cap, out, cx.d_ctl, piece_blocks, pieces, pcount, piece_cap, piece_len, cand);
-        else launch_scan<true, 1>(ps.nf, grid, block, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, lpw, keys, cap, out, cx.d_ctl, 0, pieces, pcount, 0u, 0u, cand);
+      if (!cx.blend) {
+        // destinations per wave: up to eight, where that leaves kScanWaves waves (the knob overrides, the next power of two)
+        int each_log2 = 0;
+        if (g_lists_per_wave != 0) while ((1 << each_log2) < g_lists_per_wave) ++each_log2;
+        else while (each_log2 < kScanEachLog2 && (n_new >> (each_log2 + 1)) >= kScanWaves) ++each_log2;
+        while (each_log2 < 6 && (n_new >> each_log2) > kSliceLists / 2) ++each_log2;  // (no more waves than a launch can have)
+        const int64_t waves = (n_new + ((int64_t)1 << each_log2) - 1) >> each_log2;
+        launch_scan_plain(ps.nf, (unsigned)(waves + piece_waves), s, cx.g->indices, ps.seg, ps.thr, n_new, each_log2, keys, cap, out, cx.d_ctl,
+                          (int)piece_waves, pieces, pcount, piece_cap, piece_len);
       } else {
-        if (cx.vec4) launch_scan<false, 4>(ps.nf, grid, block, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, lpw, keys, cap, out, cx.d_ctl, piece_blocks, pieces, pcount, piece_cap, piece_len, cand);
-        else launch_scan<false, 1>(ps.nf, grid, block, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, lpw, keys, cap, out, cx.d_ctl, 0, pieces, pcount, 0u, 0u, cand);
+        // lists per wave: with plenty of lists eight, for fuller waves at the fp32 stage (the knob overrides).  One wave per block:
+        // a block leaves the CU when its slowest wave is done (its first-stage queues are dynamic LDS)
+        int lpw = g_lists_per_wave;
+        if (lpw == 0) lpw = n_new >= 65536 ? (cx.vec4 ? 8 : 4) : 1;
+        while (lpw < kWave && (n_new + lpw - 1) / lpw > kSliceLists / 2) lpw = 2 * lpw < kWave ? 2 * lpw : kWave;
+        const dim3 block(kWave);
+        const int piece_blocks = cx.vec4 ? (int)piece_waves : 0;
+        const dim3 grid((unsigned)((n_new + lpw - 1) / lpw + piece_blocks));
+        if (cx.vec4) launch_scan_blend<4>(ps.nf, grid, block, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, lpw, keys, cap, out, cx.d_ctl, piece_blocks, pieces, pcount, piece_cap, piece_len, cand);
+        else launch_scan_blend<1>(ps.nf, grid, block, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, lpw, keys, cap, out, cx.d_ctl, 0, pieces, pcount, 0u, 0u, cand);
       }
       if (queued) {  // stage 3: the exact blend for the candidates that the scan appended
         const unsigned blocks = blocks_for(cand.cap_each, kBlock) < 16 ? blocks_for(cand.cap_each, kBlock) : 16;

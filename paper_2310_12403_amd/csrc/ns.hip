@@ -3,6 +3,7 @@
 // The count is known without looking at the list (min(k, d)), so every list is read once, by the fill pass.
 #include "blend_filters.h"
 #include "device_utils.h"
+#include "list_reader.h"
 #include "sample_internal.h"
 
 namespace coop {
@@ -180,21 +181,6 @@ struct NsQueue {
   uint32_t u2[kNsQueueCap];
 };
 
-// A list read through a buffer descriptor: an addition per load in the place of a lane's 64-bit address, and entries behind the
-// end come back as zeros without a test (the whole offset is in the vector register: the check leaves a scalar offset out).
-// 16 bytes per lane or 4, at the alignment of the entries.
-struct ListLoads {
-  static constexpr int kAux = 2;  // non-temporal
-  __amdgpu_buffer_rsrc_t rsrc;
-  int lane4, lane16;
-  __device__ __forceinline__ ListLoads(const int32_t* list, uint32_t n /* <= 2^28 */)
-      : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(list), 0, (int)(n * 4u), 0x00020000)), lane4(lane_id() * 4), lane16(lane_id() * 16) {}
-  __device__ __forceinline__ u32x4 group(uint32_t g) const {  // entries 256 g + 4 lane ..
-    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane16 + (int)(g * 1024u), 0, kAux);
-  }
-  __device__ __forceinline__ uint32_t entry(uint32_t at) const { return __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane4 + (int)(at * 4u), 0, kAux); }
-};
-
 // A candidate in LDS; slot_key orders by (variate, list position), the order of the selection.
 struct alignas(16) NsSlot {
   uint32_t j, r;  // list position, variate
@@ -215,35 +201,13 @@ __device__ __forceinline__ uint64_t slot_key(const NsSlot* c) { return ((uint64_
 // lane's next one is a slot further, and lanes without one write to a slot of their own that nobody reads, so that there is no
 // branch per entry.  The variate is not kept but evaluated again for the few dozen candidates.  Four groups are
 // in flight, each requested as soon as its registers are free.
-constexpr uint32_t kGroup = kWave * 4;
-constexpr uint32_t kStretch = 1u << 28;  // entries that a descriptor's offsets reach
-struct NsList {
-  ListLoads in;
-  uint32_t n, n_groups;
-  u32x4 ring[kNsGroups];
-  uint32_t rest[4];
-  __device__ __forceinline__ NsList(const int32_t* list, uint32_t entries) : in(list, entries), n(entries), n_groups(entries / kGroup) {
-    // (no load for what is not there: 16 bytes per lane cost a CU 16 clocks, also where every lane is behind the end)
-    const uint32_t tail = n & ~(kGroup - 1);
-#pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) {
-      rest[q] = any_value();
-      if (tail + q * kWave < n) rest[q] = in.entry(tail + q * kWave);
-    }
-#pragma unroll
-    for (uint32_t q = 0; q < kNsGroups; ++q) {
-      ring[q] = u32x4{any_value(), any_value(), any_value(), any_value()};
-      if (q < n_groups) ring[q] = in.group(q);
-    }
-  }
-};
-__device__ __forceinline__ uint32_t ns_collect_plain(NsList& L, uint32_t j0, uint32_t bound, const NsKeys& K, NsSlot* __restrict__ slot, uint32_t cap,
+__device__ __forceinline__ uint32_t ns_collect_plain(ListReader& L, uint32_t j0, uint32_t bound, const NsKeys& K, NsSlot* __restrict__ slot, uint32_t cap,
                                                      uint32_t n_c) {
   const uint32_t lane = (uint32_t)lane_id();
   const uint32_t idle = cap + lane;  // (the slots behind the candidates')
-  for (uint32_t g0 = 0; g0 < L.n_groups; g0 += kNsGroups) {
+  for (uint32_t g0 = 0; g0 < L.n_groups; g0 += kReaderGroups) {
 #pragma unroll
-    for (uint32_t q = 0; q < kNsGroups; ++q) {
+    for (uint32_t q = 0; q < kReaderGroups; ++q) {
       const uint32_t g = g0 + q;
       if (g >= L.n_groups) break;
       uint64_t m[4];
@@ -276,7 +240,7 @@ __device__ __forceinline__ uint32_t ns_collect_plain(NsList& L, uint32_t j0, uin
         }
         n_c = (uint32_t)__builtin_amdgcn_readlane((int)to, kWave - 1);
       }
-      if (g + kNsGroups < L.n_groups) L.ring[q] = L.in.group(g + kNsGroups);
+      if (g + kReaderGroups < L.n_groups) L.ring[q] = L.in.group(g + kReaderGroups);
     }
   }
   const uint32_t tail = L.n & ~(kGroup - 1);
@@ -556,13 +520,6 @@ __device__ __forceinline__ void ns_rank_write(uint32_t n_c, uint32_t k, NsSlot* 
   }
 }
 
-// Block b of n, renumbered so that an XCD (blocks are dealt to the eight in turn) takes runs of 32 neighbouring numbers: what
-// neighbours read, records and offsets, then shares the cache lines of one L2.  (A bijection of 0 .. n - 1.)
-__device__ __forceinline__ uint32_t xcd_runs(uint32_t b, uint32_t n) {
-  const uint32_t whole = n & ~255u;
-  return b < whole ? (b & ~255u) | ((b & 7u) << 5) | ((b >> 3) & 31u) : b;
-}
-
 // The list of a traversal kernel's wave: the first long_blocks blocks take the queued long lists (the queue's length is read
 // from device memory), the others the destinations in order, `each` neighbouring ones.  -1: nothing to do.
 __device__ __forceinline__ int64_t ns_list_of(int64_t n_dst, int each, const uint32_t* __restrict__ long_list,
@@ -665,7 +622,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
   uint32_t lo = 0, hi = 0xFFFFFFFFu, attempt = 0;  // bisection bracket on the bound, used only after a failed pass
   uint32_t j0 = 0, n_c = 0;                        // entries looked at in earlier stretches of the list, candidates so far
   const uint32_t head = vector_copy(keys.Ka[4]), tail = vector_copy(keys.Ka[3]);
-  for (NsList L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+  for (ListReader L(g_indices + beg, d < kStretch ? d : kStretch);;) {
     const NsKeys K{head, vector_copy(mid), tail};
     n_c = ns_collect_plain(L, j0, bound, K, slot, cap, n_c);
     const uint32_t found = n_c;
@@ -688,7 +645,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
       lo = j0 = n_c = attempt = 0;
       hi = 0xFFFFFFFFu;
     }
-    L = NsList(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+    L = ListReader(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
     if (select) ns_rank_write_plain(found, k, K, slot, o_done, beg_done, col_global, eid);
     if (todo == 0) break;
     __builtin_amdgcn_wave_barrier();

@@ -1075,6 +1075,39 @@ def test_ns_lists_left_over_looked_for_several_at_a_time(P, aligned):
 
 
 @pytest.mark.parametrize("aligned", [True, False])
+def test_labor_lists_around_the_edges_of_groups(P, aligned):
+    """c = 0: lists of one entry less than, as many as and one more than those that a wave looks at together (16, 32, 64, 128
+    lanes for two rounds), than 64 q entries, than whole groups of 256 and than the groups in flight, starting at any
+    alignment, among short ones; waves that take one to 64 destinations, the last of them fewer; lists no longer than one layer's
+    fanout but longer than another's; more kept entries than there are slots in LDS."""
+    n = 140000
+    rng = np.random.default_rng(12)
+    deg = rng.integers(0, 20, n)
+    edges = np.array([e for q in (16, 32, 64, 128, 192, 256, 320, 512, 1024, 1280, 2048, 4096) for e in (q - 1, q, q + 1)])
+    at = np.arange(3, n, 97)
+    deg[at] = edges[np.arange(len(at)) % len(edges)]
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    g = G(P, torch.from_numpy(indptr), torch.from_numpy(rng.integers(0, n, int(indptr[-1])).astype(np.int32)))
+    if not aligned:
+        base = torch.empty(len(g.indices_h) + 1, dtype=torch.int32, device="cuda")
+        base[1:] = g.indices_d
+        g.graph = P.coop_graph_load(g.indptr_d, base[1:], P.COOP_VALIDATE)
+    cases = ((5000, (10, 10)), (32769, (25,)), (70001, (5, 12)), (131075, (10,)), (40001, (3, 20, 2, 9)), (3000, (70, 20, 130)))
+    try:
+        for size, fanouts in cases if aligned else cases[3:]:
+            compare(P, g, np.arange(size), fanouts, R.LABOR0, seed=size)
+        for lists in (1, 2, 8, 64):
+            P.coop_tune(P.COOP_TUNE_LISTS_PER_WAVE, lists)
+            compare(P, g, np.arange(20003), (10, 4), R.LABOR0, seed=lists)
+            P.coop_tune(P.COOP_TUNE_STAGE_CAP, 8)  # most rows overflow
+            compare(P, g, np.arange(20003), (10,), R.LABOR0, seed=lists)
+            P.coop_tune(P.COOP_TUNE_STAGE_CAP, 0)
+    finally:
+        P.coop_tune(P.COOP_TUNE_LISTS_PER_WAVE, 0)
+        P.coop_tune(P.COOP_TUNE_STAGE_CAP, 0)
+
+
+@pytest.mark.parametrize("aligned", [True, False])
 def test_ns_lists_around_the_edges_of_groups(P, aligned):
     """c = 0: lists of one entry less than, as many as and one more than 64 q entries, of whole groups of 256 with and without a
     rest and of more groups than are in flight, starting at any alignment, among short ones; waves that take one, two and
