@@ -15,10 +15,7 @@
 
 namespace coop {
 
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-
 constexpr uint32_t kAllThr = 0xFFFFFFFFu;  // threshold of a list no longer than the fanout: everything is kept
-constexpr int kScanGroups = 4;             // 16-byte groups per lane and step of the fast scan (4 KiB per wave and step)
 
 struct ScanOut {
   StageEntry* stage[kMaxFuse];
@@ -336,7 +333,7 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
                                                      const int32_t* __restrict__ dst, int64_t n, int nf,
                                                      uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3, Segment* __restrict__ seg,
                                                      uint32_t* __restrict__ thr, PreThr* __restrict__ pthr, float* __restrict__ lim2,
-                                                     double cw, double sw, int queued, Ctl* ctl,
+                                                     double cw, double sw, Ctl* ctl,
                                                      uint32_t piece_len, uint32_t split_min, Piece* __restrict__ pieces, uint32_t piece_cap,
                                                      uint32_t* __restrict__ piece_count, ScanOut out, uint32_t enum_degree,
                                                      uint32_t* __restrict__ long_bits, LongSlot* __restrict__ long_tab, uint32_t long_mask,
@@ -373,7 +370,6 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
           pthr[(int64_t)f * n + i] = pt;
           lim2[(int64_t)f * n + i] = blend_second_threshold(t, cw + sw);
         }
-        if (queued) out.cnt[f][i] = 0;  // kept edges are counted by atomics
       }
   }
   // A list longer than enum_degree (when that is not 0) is not scanned at all: its kept neighbours are found from the
@@ -546,6 +542,17 @@ __device__ __forceinline__ void labor_collect(ListReader& L, uint32_t j0, const 
   }
 }
 
+// Where piece q of a list of d entries starts, and its length.  (Below 0: nowhere.  Rounding the piece length up can leave the last
+// slots of a very long list empty.)
+__device__ __forceinline__ int64_t piece_start(uint32_t d, uint32_t q, uint32_t piece_len, uint32_t* len) {
+  const uint32_t np = (d + piece_len - 1) / piece_len;  // as in k_segments
+  const uint32_t plen = ((d + np - 1) / np + 3u) & ~3u;
+  const uint64_t j0 = (uint64_t)q * plen;
+  if (j0 >= d) return -1;
+  *len = d - (uint32_t)j0 < plen ? d - (uint32_t)j0 : plen;
+  return (int64_t)j0;
+}
+
 // The scan pass with independent variates.  As k_ns_fill, which says what its parts are for: a wave takes `each` neighbouring
 // destinations (a power of two, at most 64), lists of up to twice the 64 / each lanes that a destination has are looked at
 // together, the others one after the other through the whole wave, the next one's entries requested before this one's kept
@@ -578,15 +585,13 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
       if (list == kNoPiece) continue;
       const Segment g = seg[list];
       const int64_t beg = of64(g.beg, 0);
-      const uint32_t d = of(g.d, 0);
-      const uint32_t np = (d + piece_len - 1) / piece_len;  // as in k_segments
-      const uint32_t plen = ((d + np - 1) / np + 3u) & ~3u;
-      const uint64_t j0 = (uint64_t)q * plen;
-      if (j0 >= d) continue;  // rounding the piece length up can leave the last slots of a very long list empty
+      uint32_t len;
+      const int64_t j0 = piece_start(of(g.d, 0), q, piece_len, &len);
+      if (j0 < 0) continue;
       uint32_t thr[NF], kept[NF];
 #pragma unroll
       for (int l = 0; l < NF; ++l) { thr[l] = of(thr_all[(int64_t)l * n + list], 0); kept[l] = 0; }
-      ListReader L(g_indices + beg + j0, d - (uint32_t)j0 < plen ? d - (uint32_t)j0 : plen);
+      ListReader L(g_indices + beg + j0, len);
       labor_collect<NF>(L, (uint32_t)j0, thr, K, slots, kept);
       settle();
 #pragma unroll
@@ -693,8 +698,6 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
 //      runs with every lane busy.
 // A kept edge takes the next free slot of its destination's staging row with an atomic on the row's counter; rows
 // filled this way are unordered and the fill pass ranks them by list position.
-constexpr int kQueueCap = 2 * kWave;
-
 // A candidate for the exact blend.
 struct Cand {
   int32_t t;       // neighbour
@@ -708,314 +711,292 @@ struct CandOut {
   uint32_t cap_each;
 };
 
-// Stage-1 queue: one per covered layer, three words per candidate: the neighbour, its list position, and which of
-// the wave's lists it belongs to (everything else is recomputed from t or looked up per list at stage 2).
-struct FirstQueue {
-  int32_t t[kMaxFuse][kQueueCap];
-  uint32_t j[kMaxFuse][kQueueCap];
-  uint32_t slot[kMaxFuse][kQueueCap];
+// Stage-1 passers of one covered layer wait here (per wave, in LDS): the neighbour, its list position, and the lane that has its
+// list's thresholds.  The last kWave places: one per lane that nobody reads.
+constexpr uint32_t kBlendQueue = 3 * kWave;
+struct BlendQueue {
+  StageEntry at[kBlendQueue + kWave];
+  uint8_t slot[kBlendQueue + kWave];
+  uint32_t own[kWave];  // kept edges so far of the list of each lane
+  float lim2[kWave], keep2[kWave];  // thresholds of stage 2 of the list of each lane
 };
 
-struct BlendState {
-  FirstQueue* q1;  // passed stage 1 (any list of this wave)
-  CandOut cand;    // where the stage-2 survivors go
-  uint32_t n1[kMaxFuse] = {0, 0, 0, 0};  // wave-uniform fill levels (each below 64 between calls)
-};
-
-// What stage 2 needs to know about the wave's lists: lane i holds the thresholds of list first + i.
+// What a wave of the blended scan has at hand.
 template <int NF>
-struct ListBlend {
-  uint32_t first;
-  float lim2[NF];
-  float keep2[NF];
-};
+struct BlendScan {
+  BlendQueue* queue;       // [NF]
+  bool owns;               // no other wave of this kernel keeps edges of these lists
+  uint32_t waiting[NF];    // entries in the queues (the same in every lane; below 64 between calls)
+  uint32_t head_a[NF], tail_a[NF], head_b[NF], tail_b[NF];  // key words, in vector registers
+  float cwf, swf;
+  uint32_t first, shift;      // the list of lane s is first + (s >> shift)
+  uint32_t stage_cap;
 
-// stage 2 on entries [first, first + n) of layer l's stage-1 queue (n <= 64): the two uniforms again, the blend in
-// fp32.  An estimate safely below the threshold is a kept edge (it takes the next free slot of its destination's
-// staging row); one safely above is dropped; the few in between are appended to the candidate buffer of the exact
-// stage (one atomic per call).
-template <int NF>
-__device__ __forceinline__ void blend_second(BlendState& st, int l, uint32_t first, uint32_t n, const ListBlend<NF>& lb, const FusedKeys& keys,
-                                             float cwf, float swf, uint32_t stage_cap, const ScanOut& out, Ctl* ctl) {
-  const uint32_t lane = (uint32_t)lane_id();
-  Cand e{};
-  uint32_t slot = 0;
-  if (lane < n) {
-    e.t = st.q1->t[l][first + lane];
-    e.j = st.q1->j[l][first + lane];
-    slot = st.q1->slot[l][first + lane];
-  }
-  // thresholds of the candidate's list: from the lane that holds them (every lane takes part in the exchange)
-  const float lim2 = __shfl(lb.lim2[l], (int)slot, kWave);
-  const float keep2 = __shfl(lb.keep2[l], (int)slot, kWave);
-  bool keep = false, maybe = false;
-  if (lane < n) {
-    const uint32_t folded = fold16((uint32_t)e.t);
-    const uint32_t u1 = keyed_from_head<false>(keys.K[l].Ka, folded, 0u), u2 = keyed_from_head<false>(keys.K[l].Kb, folded, 0u);
-    e.list = lb.first + slot;
-    e.layer = (uint32_t)l;
-    const float est = __builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2));
-    keep = est <= keep2;
-    maybe = !keep && est <= lim2;
-  }
-  if (keep) {
-    const uint32_t at = (uint32_t)atomicAdd(&out.cnt[l][e.list], 1);
-    if (at < stage_cap) out.stage[l][(size_t)e.list * stage_cap + at] = StageEntry{e.t, e.j};
-    else if (at == stage_cap) atomicAdd(&ctl->n_overflow, 1);  // exactly one entry sees the row fill up
-  }
-  const uint64_t mask = ballot64(maybe);
-  if (mask == 0) return;
-  const uint32_t sub = blockIdx.x & (kCandSub - 1);
-  uint32_t at = 0;
-  if (lane == 0) at = atomicAdd(&st.cand.count[sub], (uint32_t)__popcll(mask));
-  at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + lanes_below(mask);
-  if (maybe) {
-    if (at < st.cand.cap_each) st.cand.buf[(size_t)sub * st.cand.cap_each + at] = e;
-    else atomicOr(&ctl->cand_overflow, 1);
-  }
-}
-
-// stage-1 passers of layer l join its queue; a full wave of them goes through stage 2 at once
-template <int NF>
-__device__ __forceinline__ void blend_first(BlendState& st, int l, bool pre, int32_t t, uint32_t j, uint32_t slot, const ListBlend<NF>& lb,
-                                            const FusedKeys& keys, float cwf, float swf, uint32_t stage_cap, const ScanOut& out, Ctl* ctl) {
-  const uint64_t mask = ballot64(pre);
-  if (mask == 0) return;
-  if (pre) {
-    const uint32_t at = st.n1[l] + lanes_below(mask);  // below 128
-    st.q1->t[l][at] = t;
-    st.q1->j[l][at] = j;
-    st.q1->slot[l][at] = slot;
-  }
-  st.n1[l] += (uint32_t)__popcll(mask);
-  __builtin_amdgcn_wave_barrier();
-  if (st.n1[l] >= (uint32_t)kWave) {
-    blend_second<NF>(st, l, 0u, kWave, lb, keys, cwf, swf, stage_cap, out, ctl);
+  // Stage 2 on n <= 64 entries of layer l's queue from `from` on: the two uniforms again, the blend in fp32.  An estimate safely
+  // below the threshold is a kept edge (it takes the next free slot of its destination's staging row: by a counter in LDS, where
+  // no other wave of this kernel has that destination); one safely above is dropped; the few in between are
+  // appended to the candidate buffer of the exact stage (one atomic per call).
+  __device__ __forceinline__ void second(int l, uint32_t from, uint32_t n, const CandOut& cand, const ScanOut& out, Ctl* ctl) {
     const uint32_t lane = (uint32_t)lane_id();
-    const uint32_t rest = st.n1[l] - kWave;  // fewer than 64: to the front
-    int32_t mt = 0;
-    uint32_t mj = 0, ms = 0;
-    if (lane < rest) { mt = st.q1->t[l][kWave + lane]; mj = st.q1->j[l][kWave + lane]; ms = st.q1->slot[l][kWave + lane]; }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    if (lane < rest) { st.q1->t[l][lane] = mt; st.q1->j[l][lane] = mj; st.q1->slot[l][lane] = ms; }
-    st.n1[l] = rest;
+    StageEntry e{0, 0};
+    uint32_t slot = 0;
+    if (lane < n) {
+      e = queue[l].at[from + lane];
+      slot = queue[l].slot[from + lane];
+    }
+    const float lim = queue[l].lim2[slot], sure = queue[l].keep2[slot];
+    const uint32_t u1 = labor_uniform(head_a[l], tail_a[l], (uint32_t)e.t), u2 = labor_uniform(head_b[l], tail_b[l], (uint32_t)e.t);
+    const float est = __builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2));
+    const bool keep = lane < n && est <= sure, maybe = lane < n && !keep && est <= lim;
+    const uint32_t list = first + (slot >> shift);
+    if (keep) {
+      const uint32_t at = owns ? atomicAdd(&queue[l].own[slot], 1u) : (uint32_t)atomicAdd(&out.cnt[l][list], 1);
+      if (at < stage_cap) out.stage[l][(size_t)list * stage_cap + at] = e;
+      else if (at == stage_cap) atomicAdd(&ctl->n_overflow, 1);  // exactly one entry sees the row fill up
+    }
+    const uint64_t mask = ballot64(maybe);
+    if (mask != 0) {
+      const uint32_t sub = blockIdx.x & (kCandSub - 1);
+      uint32_t at = 0;
+      if (lane == 0) at = atomicAdd(&cand.count[sub], (uint32_t)__popcll(mask));
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + lanes_below(mask);
+      if (maybe) {
+        if (at < cand.cap_each) cand.buf[(size_t)sub * cand.cap_each + at] = Cand{e.t, e.j, list, (uint32_t)l};
+        else atomicOr(&ctl->cand_overflow, 1);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
-}
 
-// what still waits in the stage-1 queues goes through stage 2
-template <int NF>
-__device__ __forceinline__ void blend_flush_first(BlendState& st, const ListBlend<NF>& lb, const FusedKeys& keys, uint32_t stage_cap,
-                                                  const ScanOut& out, Ctl* ctl) {
-  const float cwf = (float)keys.cw, swf = (float)keys.sw;
+  // Four entries per lane, those of the masks m[0..3] being stage-1 passers of layer l, at list positions j + e step: they join the
+  // layer's queue, together where they fit (nearly always) or 64 at most at a time, and whole waves of them go through stage 2.
+  // (The last ones first: nothing has to move to the front.)
+  __device__ __forceinline__ void join(int l, const uint32_t (&t)[4], const uint64_t (&m)[4], uint32_t j, uint32_t step, uint32_t slot,
+                                       const CandOut& cand, const ScanOut& out, Ctl* ctl) {
+    if ((m[0] | m[1] | m[2] | m[3]) == 0) return;
+    const uint32_t idle = kBlendQueue + (uint32_t)lane_id();
+    const uint32_t all = waiting[l] + (uint32_t)(__popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]));
+    const uint64_t m0 = m[0], m1 = m[1], m2 = m[2], m3 = m[3];
+    const uint32_t t0 = t[0], t1 = t[1], t2 = t[2], t3 = t[3];
+    uint32_t done = 0;
+    if (all <= kBlendQueue) {
+      uint32_t to = waiting[l];
 #pragma unroll
-  for (int l = 0; l < NF; ++l)
-    if (st.n1[l] != 0) {
-      blend_second<NF>(st, l, 0u, st.n1[l], lb, keys, cwf, swf, stage_cap, out, ctl);
-      st.n1[l] = 0;
-      __builtin_amdgcn_wave_barrier();
-    }
-}
-
-// Blended scan of entries [beg, beg + d) of the wave's list number `slot` (a whole list, or the piece that starts at
-// list position j0): same traversal as labor_scan_fast; per entry and layer two mixer evaluations and the stage-1
-// compare against pthr.  Candidates may still wait in the stage-1 queues on return.
-template <int NF>
-__device__ __forceinline__ void labor_scan_blend(const int32_t* __restrict__ g_indices, int64_t beg, uint32_t d, uint32_t j0, uint32_t slot,
-                                                 const PreThr (&pthr)[NF], const ListBlend<NF>& lb, const FusedKeys& keys, BlendState& st,
-                                                 uint32_t stage_cap, const ScanOut& out, Ctl* ctl) {
-  constexpr uint32_t kStep = kWave * 4 * kScanGroups;
-  const int64_t abeg = beg & ~(int64_t)3;
-  const uint32_t head = (uint32_t)(beg - abeg);
-  const uint32_t total = head + d;
-  const uint32_t vec_end = total & ~3u;
-  const uint32_t vec_beg = head ? 4u : 0u;
-  const int32_t* __restrict__ p = g_indices + abeg;
-  const uint32_t lane = (uint32_t)lane_id();
-  const float cwf = (float)keys.cw, swf = (float)keys.sw;
-  // stage 1 looks at the uniforms without their last fold: the bounds are rounded up to whole upper halves, so that nothing is
-  // lost, and stage 2 evaluates the passers anew
-  uint32_t a1[NF], a2[NF], b2[NF];
-#pragma unroll
-  for (int l = 0; l < NF; ++l) { a1[l] = pthr[l].a1 | 0xFFFFu; a2[l] = pthr[l].a2 | 0xFFFFu; b2[l] = pthr[l].b2 | 0xFFFFu; }
-  // the ragged ends (lanes 0..2: the entries in front of the first whole group; lanes 3..5: those behind the last one) are
-  // requested now, so that a short list waits for memory once
-  const uint32_t end_pos = lane < 3 ? head + lane : vec_end + (lane - 3);
-  const bool end_valid = lane < 3 ? (head != 0 && end_pos < 4 && end_pos < total) : (lane < 6 && end_pos < total && vec_end >= vec_beg);
-  int32_t end_t = 0;
-  if (end_valid) end_t = p[end_pos];
-
-  for (uint32_t base = vec_beg; base < vec_end; base += kStep) {
-    i32x4 buf[kScanGroups];
-    bool ok[kScanGroups];
-#pragma unroll
-    for (int gq = 0; gq < kScanGroups; ++gq) {
-      const uint32_t r = base + (uint32_t)(gq * kWave * 4) + lane * 4;
-      ok[gq] = r < vec_end;
-      buf[gq] = i32x4{0, 0, 0, 0};
-      if (ok[gq]) buf[gq] = __builtin_nontemporal_load(reinterpret_cast<const i32x4*>(p + r));
-    }
-#pragma unroll
-    for (int gq = 0; gq < kScanGroups; ++gq) {
-      if (base + (uint32_t)(gq * kWave * 4) >= vec_end) break;  // wave-uniform: the rest of this step lies behind the list
-      const uint32_t r = base + (uint32_t)(gq * kWave * 4) + lane * 4;
-      bool pre[NF][4];
-      bool any = false;
+      for (int e = 0; e < 4; ++e) to = lanes_below_plus(m[e], to);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const uint32_t folded = fold16((uint32_t)buf[gq][e]);  // (shared by the layers and the two uniforms)
-#pragma unroll
-        for (int l = 0; l < NF; ++l) {
-          const uint32_t u1 = keyed_rough<false>(keys.K[l].Ka, folded, 0u), u2 = keyed_rough<false>(keys.K[l].Kb, folded, 0u);
-          const uint32_t lo = u1 < u2 ? u1 : u2, hi = u1 < u2 ? u2 : u1;
-          pre[l][e] = ok[gq] & ((lo <= a1[l]) | ((lo <= a2[l]) & (hi <= b2[l])));
-          any |= pre[l][e];
-        }
+        const uint32_t at = lane_in(m[e]) ? to : idle;
+        queue[l].at[at] = StageEntry{(int32_t)t[e], j + e * step};
+        queue[l].slot[at] = (uint8_t)slot;
+        to += lane_in(m[e]) ? 1u : 0u;
       }
-      if (ballot64(any) != 0) {
-#pragma unroll
-        for (int l = 0; l < NF; ++l) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) blend_first<NF>(st, l, pre[l][e], buf[gq][e], r + e - head + j0, slot, lb, keys, cwf, swf, stage_cap, out, ctl);
-        }
+      waiting[l] = all;
+      done = 4;
+    }
+#pragma nounroll
+    for (;;) {
+      if (waiting[l] >= (uint32_t)kWave) {
+        waiting[l] -= kWave;
+        second(l, waiting[l], kWave, cand, out, ctl);
+        continue;
       }
+      if (done == 4) break;
+      const uint64_t mm = done < 2 ? (done == 0 ? m0 : m1) : (done == 2 ? m2 : m3);
+      const uint32_t tt = done < 2 ? (done == 0 ? t0 : t1) : (done == 2 ? t2 : t3);
+      const uint32_t to = lanes_below_plus(mm, waiting[l]);  // (below 128)
+      if (lane_in(mm)) {
+        queue[l].at[to] = StageEntry{(int32_t)tt, j + done * step};
+        queue[l].slot[to] = (uint8_t)slot;
+      }
+      waiting[l] += (uint32_t)__popcll(mm);
+      ++done;
     }
   }
+  __device__ __forceinline__ void flush(const CandOut& cand, const ScanOut& out, Ctl* ctl) {
 #pragma unroll
-  for (int l = 0; l < NF; ++l) {  // the ragged ends
-    const uint32_t folded = fold16((uint32_t)end_t);
-    const uint32_t a = keyed_rough<false>(keys.K[l].Ka, folded, 0u), b = keyed_rough<false>(keys.K[l].Kb, folded, 0u);
-    const uint32_t lo = a < b ? a : b, hi = a < b ? b : a;
-    blend_first<NF>(st, l, end_valid && (lo <= a1[l] || (lo <= a2[l] && hi <= b2[l])), end_t, end_pos - head + j0, slot, lb, keys,
-                    cwf, swf, stage_cap, out, ctl);
+    for (int l = 0; l < NF; ++l)
+      if (waiting[l] != 0) {
+        second(l, 0u, waiting[l], cand, out, ctl);
+        waiting[l] = 0;
+      }
   }
-}
 
-// The first `piece_blocks` blocks of the grid take the pieces of the long lists (wave w takes pieces w, w + W, ... of
-// the queue, W = their number of waves; the queue length is read from device memory, so every wave ends after a
-// bounded number of steps).  VEC = 4: the indices array is 16-byte aligned, and the variates go through the staged filters.
-template <int VEC, int NF>
-__global__ __launch_bounds__(kBlock) void k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg,
-                                                       const uint32_t* __restrict__ thr_all, const PreThr* __restrict__ pthr_all,
-                                                       const float* __restrict__ lim2_all, int64_t n, int lists_per_wave, FusedKeys keys,
-                                                       uint32_t stage_cap, ScanOut out,
-                                                       Ctl* ctl, int piece_blocks, const Piece* __restrict__ pieces,
-                                                       const uint32_t* __restrict__ piece_count, uint32_t piece_cap, uint32_t piece_len,
-                                                       CandOut cand) {
-  constexpr bool kQueued = VEC == 4;
-  extern __shared__ __align__(16) uint32_t scan_lds[];  // with kQueued: a FirstQueue per wave of the block
-  BlendState bst{};
-  if constexpr (kQueued) {
-    bst.q1 = reinterpret_cast<FirstQueue*>(scan_lds) + uniform_wave_in_block();
-    bst.cand = cand;
+  // Stage 1 for one entry.  It looks at the uniforms without their last fold: the bounds come rounded up to whole upper halves, so that
+  // nothing is lost.  The test is (lo <= a1) | (lo <= a2 & hi <= b2), a1 <= a2.
+  __device__ __forceinline__ uint64_t passes(int l, uint32_t t, uint32_t a1, uint32_t a2, uint32_t b2) const {
+    const uint32_t u1 = mix_body(fold16_xor(t, head_a[l])) ^ tail_a[l], u2 = mix_body(fold16_xor(t, head_b[l])) ^ tail_b[l];
+    const uint32_t lo = u1 < u2 ? u1 : u2, hi = u1 < u2 ? u2 : u1;
+    return compare_mask(lo <= a1) | (compare_mask(lo <= a2) & compare_mask(hi <= b2));
   }
-  const uint32_t lane = (uint32_t)lane_id();
-  const uint32_t wpb = blockDim.x / kWave;  // waves per block (at most kWavesPerBlock)
-  if constexpr (VEC == 4) {
-    if ((int)blockIdx.x < piece_blocks) {
-      uint32_t n_pieces = *piece_count;
-      if (n_pieces > piece_cap) n_pieces = piece_cap;
-      const uint32_t n_waves = (uint32_t)piece_blocks * wpb;
-      for (uint32_t p = blockIdx.x * wpb + (uint32_t)uniform_wave_in_block(); p < n_pieces; p += n_waves) {
-        const Piece pc = pieces[p];
-        const uint32_t list = (uint32_t)__builtin_amdgcn_readfirstlane((int)pc.list);
-        if (list == kNoPiece) continue;
-        const uint32_t q = (uint32_t)__builtin_amdgcn_readfirstlane((int)pc.q);
-        const Segment g = seg[list];
-        const int64_t beg = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)g.beg >> 32)) << 32) |
-                                      (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)g.beg));
-        const uint32_t d = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.d);
-        const uint32_t np = (d + piece_len - 1) / piece_len;  // as in k_segments
-        const uint32_t plen = ((d + np - 1) / np + 3u) & ~3u;
-        const uint64_t j0_64 = (uint64_t)q * plen;
-        if (j0_64 >= d) continue;  // rounding the piece length up can leave the last slots of a very long list empty
-        const uint32_t j0 = (uint32_t)j0_64;
-        const uint32_t len = d - j0 < plen ? d - j0 : plen;
-        PreThr pthr[NF];
-        ListBlend<NF> lb;
-        lb.first = list;  // every lane holds this list's thresholds: slot 0
+
+  // Stage 1 on a list (or a stretch of it that starts at list position j0) whose thresholds lane `slot` has.
+  __device__ __forceinline__ void collect(ListReader& L, uint32_t j0, uint32_t slot, const uint32_t (&a1)[NF], const uint32_t (&a2)[NF],
+                                          const uint32_t (&b2)[NF], const CandOut& cand, const ScanOut& out, Ctl* ctl) {
+    const uint32_t lane = (uint32_t)lane_id();
+    for (uint32_t g0 = 0; g0 < L.n_groups; g0 += kReaderGroups) {
 #pragma unroll
-        for (int l = 0; l < NF; ++l) {
-          const PreThr pt = pthr_all[(int64_t)l * n + list];
-          pthr[l].a2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pt.a2);
-          pthr[l].a1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pt.a1);
-          pthr[l].b2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pt.b2);
-          pthr[l].keep2 = pt.keep2;
-          lb.keep2[l] = pt.keep2;
-          lb.lim2[l] = lim2_all[(int64_t)l * n + list];
+      for (uint32_t q = 0; q < kReaderGroups; ++q) {
+        const uint32_t g = g0 + q;
+        if (g >= L.n_groups) break;
+        const uint32_t t[4] = {L.ring[q][0], L.ring[q][1], L.ring[q][2], L.ring[q][3]};
+#pragma unroll
+        for (int l = 0; l < NF; ++l) {  // (layer by layer: the masks of all of them would not fit the scalar registers)
+          uint64_t m[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) m[e] = passes(l, t[e], a1[l], a2[l], b2[l]);
+          join(l, t, m, j0 + g * kGroup + lane * 4, 1u, slot, cand, out, ctl);
         }
-        labor_scan_blend<NF>(g_indices, beg + j0, len, j0, 0u, pthr, lb, keys, bst, stage_cap, out, ctl);
-        blend_flush_first<NF>(bst, lb, keys, stage_cap, out, ctl);
+        if (g + kReaderGroups < L.n_groups) L.ring[q] = L.in.group(g + kReaderGroups);
       }
-      return;
     }
-  }
-  const int64_t wave = ((int64_t)blockIdx.x - piece_blocks) * wpb + uniform_wave_in_block();
-  const int64_t first = wave * lists_per_wave;
-  if (first >= n) return;
-  const int64_t mine = first + lane;
-  const bool has = (int)lane < lists_per_wave && mine < n;
-  Segment g{0, 0, 0};
-  uint32_t my_thr[NF];
-  PreThr my_pthr[NF];
-  float my_lim2[NF];
-#pragma unroll
-  for (int l = 0; l < NF; ++l) { my_thr[l] = kAllThr; my_pthr[l] = PreThr{kAllThr, kAllThr, kAllThr, 0.0f}; my_lim2[l] = 0.0f; }
-  if (has) {
-    g = seg[mine];
+    const uint32_t tail = L.n & ~(kGroup - 1);
+    if (tail == L.n) return;
 #pragma unroll
     for (int l = 0; l < NF; ++l) {
-      my_thr[l] = thr_all[(int64_t)l * n + mine];
-      if constexpr (kQueued) { my_pthr[l] = pthr_all[(int64_t)l * n + mine]; my_lim2[l] = lim2_all[(int64_t)l * n + mine]; }
+      uint64_t m[4] = {0, 0, 0, 0};
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (tail + q * kWave < L.n) m[q] = passes(l, L.rest[q], a1[l], a2[l], b2[l]) & low_lanes(L.n - tail - q * kWave);
+      join(l, L.rest, m, j0 + tail + lane, (uint32_t)kWave, slot, cand, out, ctl);
     }
   }
-  const uint32_t beg_lo = (uint32_t)g.beg, beg_hi = (uint32_t)((uint64_t)g.beg >> 32);
-  uint32_t my_count[NF];
+};
+
+// The scan pass with blended variates: destinations, pieces and short lists as in k_labor_scan_plain.
+template <int NF>
+__global__ __launch_bounds__(kWave, NF == 1 ? 7 : NF == 2 ? 6 : NF == 3 ? 5 : 4) void
+k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg, const uint32_t* __restrict__ thr_all,
+                   const PreThr* __restrict__ pthr_all, const float* __restrict__ lim2_all, int64_t n, int each_log2, FusedKeys keys, uint32_t stage_cap,
+                   ScanOut out, Ctl* ctl, int piece_blocks, const Piece* __restrict__ pieces, const uint32_t* __restrict__ piece_count,
+                   uint32_t piece_cap, uint32_t piece_len, CandOut cand) {
+  __shared__ BlendQueue queue[NF];
+  const uint32_t lane = (uint32_t)lane_id();
+  auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
+  auto of64 = [&](int64_t x, int q) { return (int64_t)(((uint64_t)of((uint32_t)((uint64_t)x >> 32), q) << 32) | of((uint32_t)x, q)); };
+  BlendScan<NF> S;
+  S.queue = queue;
+  S.cwf = (float)keys.cw;
+  S.swf = (float)keys.sw;
+  S.stage_cap = stage_cap;
 #pragma unroll
-  for (int l = 0; l < NF; ++l) my_count[l] = 0;
-  ListBlend<NF> lbw;  // lane i: thresholds of list first + i
-  lbw.first = (uint32_t)first;
-#pragma unroll
-  for (int l = 0; l < NF; ++l) { lbw.lim2[l] = my_lim2[l]; lbw.keep2[l] = my_pthr[l].keep2; }
-  const int n_lists = (int)(n - first < lists_per_wave ? n - first : lists_per_wave);
-  for (int i = 0; i < n_lists; ++i) {
-    const int64_t beg = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)beg_hi, i) << 32) |
-                                  (uint32_t)__builtin_amdgcn_readlane((int)beg_lo, i));
-    const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)g.d, i);
-    if (__builtin_amdgcn_readlane((int)g.split, i) != 0) continue;  // cut into pieces, scanned by other waves
-    if constexpr (kQueued) {  // every list, whatever its length: kept edges reach the rows through the queues
-      PreThr pthr[NF];
+  for (int l = 0; l < NF; ++l) {
+    S.waiting[l] = 0;
+    S.head_a[l] = vector_copy(keys.K[l].Ka[4]);
+    S.tail_a[l] = vector_copy(keys.K[l].Ka[1]);
+    S.head_b[l] = vector_copy(keys.K[l].Kb[4]);
+    S.tail_b[l] = vector_copy(keys.K[l].Kb[1]);
+  }
+  if ((int)blockIdx.x < piece_blocks) {
+    S.owns = false;
+    S.shift = 0;
+    uint32_t n_pieces = *piece_count;
+    if (n_pieces > piece_cap) n_pieces = piece_cap;
+    for (uint32_t p = blockIdx.x; p < n_pieces; p += (uint32_t)piece_blocks) {
+      const Piece pc = pieces[p];
+      const uint32_t list = of(pc.list, 0), q = of(pc.q, 0);
+      if (list == kNoPiece) continue;
+      const Segment g = seg[list];
+      const int64_t beg = of64(g.beg, 0);
+      uint32_t len;
+      const int64_t j0 = piece_start(of(g.d, 0), q, piece_len, &len);
+      if (j0 < 0) continue;
+      S.first = list;  // (every lane has this list's thresholds: slot 0)
+      uint32_t a1[NF], a2[NF], b2[NF];
 #pragma unroll
       for (int l = 0; l < NF; ++l) {
-        pthr[l].a2 = (uint32_t)__builtin_amdgcn_readlane((int)my_pthr[l].a2, i);
-        pthr[l].a1 = (uint32_t)__builtin_amdgcn_readlane((int)my_pthr[l].a1, i);
-        pthr[l].b2 = (uint32_t)__builtin_amdgcn_readlane((int)my_pthr[l].b2, i);
-        pthr[l].keep2 = 0.0f;  // (stage 2 takes it from the lane that holds the list)
+        const PreThr pt = pthr_all[(int64_t)l * n + list];
+        a1[l] = of(pt.a1, 0) | 0xFFFFu;
+        a2[l] = of(pt.a2, 0) | 0xFFFFu;
+        b2[l] = of(pt.b2, 0) | 0xFFFFu;
+        queue[l].keep2[lane] = pt.keep2;
+        queue[l].lim2[lane] = lim2_all[(int64_t)l * n + list];
       }
-      if (d != 0) labor_scan_blend<NF>(g_indices, beg, d, 0u, (uint32_t)i, pthr, lbw, keys, bst, stage_cap, out, ctl);
-      continue;
+      ListReader L(g_indices + beg + j0, len);
+      S.collect(L, (uint32_t)j0, 0u, a1, a2, b2, cand, out, ctl);
+      S.flush(cand, out, ctl);
     }
+    return;
+  }
+  const int64_t w0 = (int64_t)xcd_runs(blockIdx.x - (uint32_t)piece_blocks, gridDim.x - (uint32_t)piece_blocks) << each_log2;
+  if (w0 >= n) return;
+  const uint32_t n_mine = n - w0 < ((int64_t)1 << each_log2) ? (uint32_t)(n - w0) : 1u << each_log2;
+  const uint32_t lanes = 64u >> each_log2, sub = lane & (lanes - 1), number = lane >> (6 - each_log2);
+  const int64_t w = w0 + (number < n_mine ? number : n_mine - 1);
+  S.owns = true;
+  S.first = (uint32_t)w0;
+  S.shift = (uint32_t)(6 - each_log2);
+  const Segment g = seg[w];
+  uint32_t my_a1[NF], my_a2[NF], my_b2[NF];
+#pragma unroll
+  for (int l = 0; l < NF; ++l) {
+    const PreThr pt = pthr_all[(int64_t)l * n + w];
+    my_a1[l] = pt.a1 | 0xFFFFu;
+    my_a2[l] = pt.a2 | 0xFFFFu;
+    my_b2[l] = pt.b2 | 0xFFFFu;
+    queue[l].keep2[lane] = pt.keep2;
+    queue[l].lim2[lane] = lim2_all[(int64_t)l * n + w];
+    queue[l].own[lane] = 0;
+  }
+  const bool live = number < n_mine && g.split == 0, speaks = live && sub == 0;
+  const uint32_t together = each_log2 != 0 ? 2 * lanes : 0;
+  if (ballot64(live && g.d <= together && g.d != 0) != 0) {
+    const bool mine = live && g.d <= together;
+    uint32_t t[2] = {0, 0};
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+      if (mine && sub + r * lanes < g.d) t[r] = (uint32_t)(g_indices + g.beg)[sub + r * lanes];
 #pragma unroll
     for (int l = 0; l < NF; ++l) {
-      const uint32_t thr = (uint32_t)__builtin_amdgcn_readlane((int)my_thr[l], i);
-      StageEntry* row = out.stage[l] + (size_t)(first + i) * stage_cap;
-      const uint32_t c = labor_scan_ordered<true>(g_indices, beg, d, thr, keys.K[l], keys.cw, keys.sw,
-                                                  [&](uint32_t rank, int32_t t, uint32_t j) {
-                                                    if (rank < stage_cap) row[rank] = StageEntry{t, j};
-                                                  });
-      if ((int)lane == i) my_count[l] = c;
-    }
-  }
-  if constexpr (kQueued) {
-    blend_flush_first<NF>(bst, lbw, keys, stage_cap, out, ctl);
-    return;  // (the counters were kept by atomics, here and in the exact stage)
-  }
-  if (has && g.split == 0) {  // (the pieces of a cut list add their counts themselves)
+      const bool all = queue[l].keep2[lane] == __builtin_inff();  // (nothing of such a list goes through the stages)
+      uint64_t m[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int l = 0; l < NF; ++l) {
-      out.cnt[l][mine] = (int32_t)my_count[l];
-      if (my_count[l] > stage_cap) atomicAdd(&ctl->n_overflow, 1);
+      for (uint32_t r = 0; r < 2; ++r) {
+        const uint32_t j = sub + r * lanes;
+        const bool in = mine && j < g.d;
+        if (in && all && j < stage_cap) out.stage[l][(size_t)w * stage_cap + j] = StageEntry{(int32_t)t[r], j};
+        m[r] = S.passes(l, t[r], my_a1[l], my_a2[l], my_b2[l]) & ballot64(in && !all);
+      }
+      if (all && mine && sub == 0) {
+        queue[l].own[lane] = g.d;
+        if (g.d > stage_cap) atomicAdd(&ctl->n_overflow, 1);
+      }
+      const uint32_t both[4] = {t[0], t[1], 0u, 0u};
+      S.join(l, both, m, sub, lanes, lane & ~(lanes - 1), cand, out, ctl);
     }
+  }
+  uint64_t todo = ballot64(speaks && g.d > together);
+  if (todo != 0) {
+    int at = __builtin_ctzll(todo);
+    uint32_t d = of(g.d, at), j0 = 0, a1[NF], a2[NF], b2[NF];
+    int64_t beg = of64(g.beg, at);
+    auto thresholds = [&]() {
+#pragma unroll
+      for (int l = 0; l < NF; ++l) { a1[l] = of(my_a1[l], at); a2[l] = of(my_a2[l], at); b2[l] = of(my_b2[l], at); }
+    };
+    thresholds();
+    for (ListReader L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+      S.collect(L, j0, (uint32_t)at, a1, a2, b2, cand, out, ctl);
+      if (d - j0 > kStretch) {  // the list's next stretch
+        j0 += kStretch;
+      } else {
+        todo &= todo - 1;
+        if (todo == 0) break;
+        at = __builtin_ctzll(todo);
+        d = of(g.d, at);
+        beg = of64(g.beg, at);
+        j0 = 0;
+        thresholds();
+      }
+      L = ListReader(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+    }
+  }
+  S.flush(cand, out, ctl);
+  if (speaks) {
+#pragma unroll
+    for (int l = 0; l < NF; ++l) out.cnt[l][w] = (int32_t)queue[l].own[lane];  // (the exact stage adds what it keeps)
   }
 }
 
@@ -1129,13 +1110,12 @@ __global__ __launch_bounds__(kBlock) void k_labor_fill_overflow(const int32_t* _
   });
 }
 
-template <int VEC>
-static void launch_scan_blend(int nf, dim3 grid, dim3 block, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, const PreThr* pthr, const float* lim2, int64_t n,
-                              int lpw, const FusedKeys& keys, uint32_t cap, const ScanOut& out, Ctl* ctl, int piece_blocks, const Piece* pieces,
-                              const uint32_t* piece_count, uint32_t piece_cap, uint32_t piece_len, const CandOut& cand) {
-  const size_t lds = VEC == 4 ? (size_t)(block.x / kWave) * sizeof(FirstQueue) : 0;
-#define COOP_SCAN_BLEND(NF)                                                                                                              \
-  COOP_LAUNCH(K_LABOR_COUNT, (k_labor_scan_blend<VEC, NF>), grid, block, lds, s, indices, seg, thr, pthr, lim2, n, lpw, keys, cap, out, ctl, \
+static void launch_scan_blend(int nf, unsigned blocks, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, const PreThr* pthr,
+                              const float* lim2, int64_t n, int each_log2, const FusedKeys& keys, uint32_t cap, const ScanOut& out, Ctl* ctl,
+                              int piece_blocks, const Piece* pieces, const uint32_t* piece_count, uint32_t piece_cap, uint32_t piece_len,
+                              const CandOut& cand) {
+#define COOP_SCAN_BLEND(NF)                                                                                                                  \
+  COOP_LAUNCH(K_LABOR_COUNT, k_labor_scan_blend<NF>, dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, pthr, lim2, n, each_log2, keys, cap, out, ctl, \
               piece_blocks, pieces, piece_count, piece_cap, piece_len, cand)
   switch (nf) {
     case 1: COOP_SCAN_BLEND(1); break;
@@ -1215,7 +1195,7 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
     ks[f] = (uint32_t)cx.fanouts[l + f];
   }
   // long lists are cut into pieces (k_segments queues them); room for every piece the graph's edges could make
-  const uint32_t piece_len = cx.vec4 || !cx.blend ? (uint32_t)g_piece_len : 0u;
+  const uint32_t piece_len = (uint32_t)g_piece_len;
   // Lists longer than split_min go to the piece waves, which come first in the grid.  With independent variates that is
   // for the lists worth cutting (twice the piece length).  The blended scan costs three times as much per entry, and a
   // wave that meets a few lists of several thousand entries late in the kernel keeps it waiting: there every list above
@@ -1234,7 +1214,7 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
   }
   // blended variates: stage 3 works from a buffer of the candidates that the fp32 blend left undecided, a few percent
   // of the k kept edges per destination and layer; k / 2 each is ample (a pass that overflows it is redone with more)
-  const bool queued = cx.blend && cx.vec4 && n_new > 0;
+  const bool queued = cx.blend && n_new > 0;
   int64_t cand_cap = 0;
   uint32_t* cand_count = nullptr;
   if (queued) {
@@ -1339,7 +1319,7 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
 #define COOP_SEGMENTS(BLOCK)                                                                                                          \
   COOP_LAUNCH(K_SEGMENTS, k_segments<BLOCK>, dim3(blocks_for(n_new, BLOCK)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices,          \
               dst + ps.start, n_new, ps.nf, ks[0], ks[1], ks[2], ks[3], ps.seg, ps.thr, pthr, lim2, cx.cw, cx.sw,                        \
-              cx.blend && cx.vec4 ? 1 : 0, cx.d_ctl, piece_len, split_min, pieces, piece_cap, cx.d_piece_count + l, out, enum_degree,    \
+              cx.d_ctl, piece_len, split_min, pieces, piece_cap, cx.d_piece_count + l, out, enum_degree,    \
               long_bits, long_tab, long_mask, clear, cand_count)
       if (n_new >= kSegWideFrom) COOP_SEGMENTS(1024);
       else if (n_new >= 16384 || !cx.blend) COOP_SEGMENTS(256);
@@ -1362,27 +1342,18 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
       // the piece waves come first in the grid: one round of resident blocks, fewer if there cannot be that many pieces
       const int64_t piece_waves = (int64_t)piece_cap < kPieceWaves ? (int64_t)piece_cap : kPieceWaves;
       const uint32_t* pcount = cx.d_piece_count + l;
-      if (!cx.blend) {
-        // destinations per wave: up to eight, where that leaves kScanWaves waves (the knob overrides, the next power of two)
-        int each_log2 = 0;
-        if (g_lists_per_wave != 0) while ((1 << each_log2) < g_lists_per_wave) ++each_log2;
-        else while (each_log2 < kScanEachLog2 && (n_new >> (each_log2 + 1)) >= kScanWaves) ++each_log2;
-        while (each_log2 < 6 && (n_new >> each_log2) > kSliceLists / 2) ++each_log2;  // (no more waves than a launch can have)
-        const int64_t waves = (n_new + ((int64_t)1 << each_log2) - 1) >> each_log2;
-        launch_scan_plain(ps.nf, (unsigned)(waves + piece_waves), s, cx.g->indices, ps.seg, ps.thr, n_new, each_log2, keys, cap, out, cx.d_ctl,
-                          (int)piece_waves, pieces, pcount, piece_cap, piece_len);
-      } else {
-        // lists per wave: with plenty of lists eight, for fuller waves at the fp32 stage (the knob overrides).  One wave per block:
-        // a block leaves the CU when its slowest wave is done (its first-stage queues are dynamic LDS)
-        int lpw = g_lists_per_wave;
-        if (lpw == 0) lpw = n_new >= 65536 ? (cx.vec4 ? 8 : 4) : 1;
-        while (lpw < kWave && (n_new + lpw - 1) / lpw > kSliceLists / 2) lpw = 2 * lpw < kWave ? 2 * lpw : kWave;
-        const dim3 block(kWave);
-        const int piece_blocks = cx.vec4 ? (int)piece_waves : 0;
-        const dim3 grid((unsigned)((n_new + lpw - 1) / lpw + piece_blocks));
-        if (cx.vec4) launch_scan_blend<4>(ps.nf, grid, block, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, lpw, keys, cap, out, cx.d_ctl, piece_blocks, pieces, pcount, piece_cap, piece_len, cand);
-        else launch_scan_blend<1>(ps.nf, grid, block, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, lpw, keys, cap, out, cx.d_ctl, 0, pieces, pcount, 0u, 0u, cand);
-      }
+      // destinations per wave: up to eight, where that leaves kScanWaves waves (the knob overrides, the next power of two)
+      int each_log2 = 0;
+      if (g_lists_per_wave != 0) while ((1 << each_log2) < g_lists_per_wave) ++each_log2;
+      else while (each_log2 < kScanEachLog2 && (n_new >> (each_log2 + 1)) >= kScanWaves) ++each_log2;
+      while (each_log2 < 6 && (n_new >> each_log2) > kSliceLists / 2) ++each_log2;  // (no more waves than a launch can have)
+      const unsigned blocks = (unsigned)(((n_new + ((int64_t)1 << each_log2) - 1) >> each_log2) + piece_waves);
+      if (cx.blend)
+        launch_scan_blend(ps.nf, blocks, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, each_log2, keys, cap, out, cx.d_ctl, (int)piece_waves,
+                          pieces, pcount, piece_cap, piece_len, cand);
+      else
+        launch_scan_plain(ps.nf, blocks, s, cx.g->indices, ps.seg, ps.thr, n_new, each_log2, keys, cap, out, cx.d_ctl, (int)piece_waves, pieces,
+                          pcount, piece_cap, piece_len);
       if (queued) {  // stage 3: the exact blend for the candidates that the scan appended
         const unsigned blocks = blocks_for(cand.cap_each, kBlock) < 16 ? blocks_for(cand.cap_each, kBlock) : 16;
         COOP_LAUNCH(K_LABOR_EXACT, k_labor_exact, dim3(blocks, kCandSub), dim3(kBlock), 0, s, cand, ps.thr, n_new, ps.nf, keys, cap, out,

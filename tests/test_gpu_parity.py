@@ -1074,12 +1074,13 @@ def test_ns_lists_left_over_looked_for_several_at_a_time(P, aligned):
         compare(P, g, v[:size], (10,), R.NS, it=5, kappa=16, seed=size)
 
 
+@pytest.mark.parametrize("kappa", [1, 4])
 @pytest.mark.parametrize("aligned", [True, False])
-def test_labor_lists_around_the_edges_of_groups(P, aligned):
-    """c = 0: lists of one entry less than, as many as and one more than those that a wave looks at together (16, 32, 64, 128
+def test_labor_lists_around_the_edges_of_groups(P, aligned, kappa):
+    """Lists of one entry less than, as many as and one more than those that a wave looks at together (16, 32, 64, 128
     lanes for two rounds), than 64 q entries, than whole groups of 256 and than the groups in flight, starting at any
     alignment, among short ones; waves that take one to 64 destinations, the last of them fewer; lists no longer than one layer's
-    fanout but longer than another's; more kept entries than there are slots in LDS."""
+    fanout but longer than another's; more kept entries than there are slots in LDS, more candidates of a blend than its queue holds."""
     n = 140000
     rng = np.random.default_rng(12)
     deg = rng.integers(0, 20, n)
@@ -1095,12 +1096,12 @@ def test_labor_lists_around_the_edges_of_groups(P, aligned):
     cases = ((5000, (10, 10)), (32769, (25,)), (70001, (5, 12)), (131075, (10,)), (40001, (3, 20, 2, 9)), (3000, (70, 20, 130)))
     try:
         for size, fanouts in cases if aligned else cases[3:]:
-            compare(P, g, np.arange(size), fanouts, R.LABOR0, seed=size)
+            compare(P, g, np.arange(size), fanouts, R.LABOR0, it=3 * (kappa > 1), kappa=kappa, seed=size)
         for lists in (1, 2, 8, 64):
             P.coop_tune(P.COOP_TUNE_LISTS_PER_WAVE, lists)
-            compare(P, g, np.arange(20003), (10, 4), R.LABOR0, seed=lists)
+            compare(P, g, np.arange(20003), (10, 4), R.LABOR0, it=kappa - 1, kappa=kappa, seed=lists)
             P.coop_tune(P.COOP_TUNE_STAGE_CAP, 8)  # most rows overflow
-            compare(P, g, np.arange(20003), (10,), R.LABOR0, seed=lists)
+            compare(P, g, np.arange(20003), (10,), R.LABOR0, it=kappa - 1, kappa=kappa, seed=lists)
             P.coop_tune(P.COOP_TUNE_STAGE_CAP, 0)
     finally:
         P.coop_tune(P.COOP_TUNE_LISTS_PER_WAVE, 0)
