@@ -9,7 +9,7 @@
 // a scan over the kept-edge counts and a copy of the rows.  A row that overflows is rare; those lists are scanned a
 // second time, in order, straight into the edge arrays.
 #include "device_utils.h"
-#include "blend_filters.h"
+#include "blend_scan.h"
 #include "list_reader.h"
 #include "sample_internal.h"
 
@@ -711,45 +711,19 @@ struct CandOut {
   uint32_t cap_each;
 };
 
-// Stage-1 passers of one covered layer wait here (per wave, in LDS): the neighbour, its list position, and the lane that has its
-// list's thresholds.  The last kWave places: one per lane that nobody reads.
-constexpr uint32_t kBlendQueue = 3 * kWave;
-struct BlendQueue {
-  StageEntry at[kBlendQueue + kWave];
-  uint8_t slot[kBlendQueue + kWave];
-  uint32_t own[kWave];  // kept edges so far of the list of each lane
-  float lim2[kWave], keep2[kWave];  // thresholds of stage 2 of the list of each lane
-};
-
-// What a wave of the blended scan has at hand.
-template <int NF>
-struct BlendScan {
-  BlendQueue* queue;       // [NF]
-  bool owns;               // no other wave of this kernel keeps edges of these lists
-  uint32_t waiting[NF];    // entries in the queues (the same in every lane; below 64 between calls)
-  uint32_t head_a[NF], tail_a[NF], head_b[NF], tail_b[NF];  // key words, in vector registers
-  float cwf, swf;
-  uint32_t first, shift;      // the list of lane s is first + (s >> shift)
+// What stage 2 leads to (blend_scan.h): an estimate safely below the threshold is a kept edge (it takes the next free slot of its
+// destination's staging row: by a counter in LDS, where no other wave of the kernel has that destination); one safely above is
+// dropped; the few in between are appended to the candidate buffer of the exact stage (one atomic per call).
+struct LaborSink {
+  ScanOut out;
+  CandOut cand;
+  Ctl* ctl;
   uint32_t stage_cap;
-
-  // Stage 2 on n <= 64 entries of layer l's queue from `from` on: the two uniforms again, the blend in fp32.  An estimate safely
-  // below the threshold is a kept edge (it takes the next free slot of its destination's staging row: by a counter in LDS, where
-  // no other wave of this kernel has that destination); one safely above is dropped; the few in between are
-  // appended to the candidate buffer of the exact stage (one atomic per call).
-  __device__ __forceinline__ void second(int l, uint32_t from, uint32_t n, const CandOut& cand, const ScanOut& out, Ctl* ctl) {
+  uint32_t first, shift;  // the list of lane s is first + (s >> shift)
+  bool owns;              // no other wave of this kernel keeps edges of these lists
+  __device__ __forceinline__ void take(BlendQueue<false>* queue, int l, bool there, const StageEntry& e, uint32_t slot, float est) {
     const uint32_t lane = (uint32_t)lane_id();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    StageEntry e{0, 0};
-    uint32_t slot = 0;
-    if (lane < n) {
-      e = queue[l].at[from + lane];
-      slot = queue[l].slot[from + lane];
-    }
-    const float lim = queue[l].lim2[slot], sure = queue[l].keep2[slot];
-    const uint32_t u1 = labor_uniform(head_a[l], tail_a[l], (uint32_t)e.t), u2 = labor_uniform(head_b[l], tail_b[l], (uint32_t)e.t);
-    const float est = __builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2));
-    const bool keep = lane < n && est <= sure, maybe = lane < n && !keep && est <= lim;
+    const bool keep = there && est <= queue[l].keep2[slot], maybe = there && !keep && est <= queue[l].lim2[slot];
     const uint32_t list = first + (slot >> shift);
     if (keep) {
       const uint32_t at = owns ? atomicAdd(&queue[l].own[slot], 1u) : (uint32_t)atomicAdd(&out.cnt[l][list], 1);
@@ -757,110 +731,14 @@ struct BlendScan {
       else if (at == stage_cap) atomicAdd(&ctl->n_overflow, 1);  // exactly one entry sees the row fill up
     }
     const uint64_t mask = ballot64(maybe);
-    if (mask != 0) {
-      const uint32_t sub = blockIdx.x & (kCandSub - 1);
-      uint32_t at = 0;
-      if (lane == 0) at = atomicAdd(&cand.count[sub], (uint32_t)__popcll(mask));
-      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + lanes_below(mask);
-      if (maybe) {
-        if (at < cand.cap_each) cand.buf[(size_t)sub * cand.cap_each + at] = Cand{e.t, e.j, list, (uint32_t)l};
-        else atomicOr(&ctl->cand_overflow, 1);
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  }
-
-  // Four entries per lane, those of the masks m[0..3] being stage-1 passers of layer l, at list positions j + e step: they join the
-  // layer's queue, together where they fit (nearly always) or 64 at most at a time, and whole waves of them go through stage 2.
-  // (The last ones first: nothing has to move to the front.)
-  __device__ __forceinline__ void join(int l, const uint32_t (&t)[4], const uint64_t (&m)[4], uint32_t j, uint32_t step, uint32_t slot,
-                                       const CandOut& cand, const ScanOut& out, Ctl* ctl) {
-    if ((m[0] | m[1] | m[2] | m[3]) == 0) return;
-    const uint32_t idle = kBlendQueue + (uint32_t)lane_id();
-    const uint32_t all = waiting[l] + (uint32_t)(__popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]));
-    const uint64_t m0 = m[0], m1 = m[1], m2 = m[2], m3 = m[3];
-    const uint32_t t0 = t[0], t1 = t[1], t2 = t[2], t3 = t[3];
-    uint32_t done = 0;
-    if (all <= kBlendQueue) {
-      uint32_t to = waiting[l];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) to = lanes_below_plus(m[e], to);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t at = lane_in(m[e]) ? to : idle;
-        queue[l].at[at] = StageEntry{(int32_t)t[e], j + e * step};
-        queue[l].slot[at] = (uint8_t)slot;
-        to += lane_in(m[e]) ? 1u : 0u;
-      }
-      waiting[l] = all;
-      done = 4;
-    }
-#pragma nounroll
-    for (;;) {
-      if (waiting[l] >= (uint32_t)kWave) {
-        waiting[l] -= kWave;
-        second(l, waiting[l], kWave, cand, out, ctl);
-        continue;
-      }
-      if (done == 4) break;
-      const uint64_t mm = done < 2 ? (done == 0 ? m0 : m1) : (done == 2 ? m2 : m3);
-      const uint32_t tt = done < 2 ? (done == 0 ? t0 : t1) : (done == 2 ? t2 : t3);
-      const uint32_t to = lanes_below_plus(mm, waiting[l]);  // (below 128)
-      if (lane_in(mm)) {
-        queue[l].at[to] = StageEntry{(int32_t)tt, j + done * step};
-        queue[l].slot[to] = (uint8_t)slot;
-      }
-      waiting[l] += (uint32_t)__popcll(mm);
-      ++done;
-    }
-  }
-  __device__ __forceinline__ void flush(const CandOut& cand, const ScanOut& out, Ctl* ctl) {
-#pragma unroll
-    for (int l = 0; l < NF; ++l)
-      if (waiting[l] != 0) {
-        second(l, 0u, waiting[l], cand, out, ctl);
-        waiting[l] = 0;
-      }
-  }
-
-  // Stage 1 for one entry.  It looks at the uniforms without their last fold: the bounds come rounded up to whole upper halves, so that
-  // nothing is lost.  The test is (lo <= a1) | (lo <= a2 & hi <= b2), a1 <= a2.
-  __device__ __forceinline__ uint64_t passes(int l, uint32_t t, uint32_t a1, uint32_t a2, uint32_t b2) const {
-    const uint32_t u1 = mix_body(fold16_xor(t, head_a[l])) ^ tail_a[l], u2 = mix_body(fold16_xor(t, head_b[l])) ^ tail_b[l];
-    const uint32_t lo = u1 < u2 ? u1 : u2, hi = u1 < u2 ? u2 : u1;
-    return compare_mask(lo <= a1) | (compare_mask(lo <= a2) & compare_mask(hi <= b2));
-  }
-
-  // Stage 1 on a list (or a stretch of it that starts at list position j0) whose thresholds lane `slot` has.
-  __device__ __forceinline__ void collect(ListReader& L, uint32_t j0, uint32_t slot, const uint32_t (&a1)[NF], const uint32_t (&a2)[NF],
-                                          const uint32_t (&b2)[NF], const CandOut& cand, const ScanOut& out, Ctl* ctl) {
-    const uint32_t lane = (uint32_t)lane_id();
-    for (uint32_t g0 = 0; g0 < L.n_groups; g0 += kReaderGroups) {
-#pragma unroll
-      for (uint32_t q = 0; q < kReaderGroups; ++q) {
-        const uint32_t g = g0 + q;
-        if (g >= L.n_groups) break;
-        const uint32_t t[4] = {L.ring[q][0], L.ring[q][1], L.ring[q][2], L.ring[q][3]};
-#pragma unroll
-        for (int l = 0; l < NF; ++l) {  // (layer by layer: the masks of all of them would not fit the scalar registers)
-          uint64_t m[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) m[e] = passes(l, t[e], a1[l], a2[l], b2[l]);
-          join(l, t, m, j0 + g * kGroup + lane * 4, 1u, slot, cand, out, ctl);
-        }
-        if (g + kReaderGroups < L.n_groups) L.ring[q] = L.in.group(g + kReaderGroups);
-      }
-    }
-    const uint32_t tail = L.n & ~(kGroup - 1);
-    if (tail == L.n) return;
-#pragma unroll
-    for (int l = 0; l < NF; ++l) {
-      uint64_t m[4] = {0, 0, 0, 0};
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (tail + q * kWave < L.n) m[q] = passes(l, L.rest[q], a1[l], a2[l], b2[l]) & low_lanes(L.n - tail - q * kWave);
-      join(l, L.rest, m, j0 + tail + lane, (uint32_t)kWave, slot, cand, out, ctl);
+    if (mask == 0) return;
+    const uint32_t sub = blockIdx.x & (kCandSub - 1);
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(&cand.count[sub], (uint32_t)__popcll(mask));
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + lanes_below(mask);
+    if (maybe) {
+      if (at < cand.cap_each) cand.buf[(size_t)sub * cand.cap_each + at] = Cand{e.t, e.j, list, (uint32_t)l};
+      else atomicOr(&ctl->cand_overflow, 1);
     }
   }
 };
@@ -872,26 +750,18 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
                    const PreThr* __restrict__ pthr_all, const float* __restrict__ lim2_all, int64_t n, int each_log2, FusedKeys keys, uint32_t stage_cap,
                    ScanOut out, Ctl* ctl, int piece_blocks, const Piece* __restrict__ pieces, const uint32_t* __restrict__ piece_count,
                    uint32_t piece_cap, uint32_t piece_len, CandOut cand) {
-  __shared__ BlendQueue queue[NF];
+  __shared__ BlendQueue<false> queue[NF];
   const uint32_t lane = (uint32_t)lane_id();
   auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
   auto of64 = [&](int64_t x, int q) { return (int64_t)(((uint64_t)of((uint32_t)((uint64_t)x >> 32), q) << 32) | of((uint32_t)x, q)); };
-  BlendScan<NF> S;
+  BlendScan<NF, false, LaborSink> S;
   S.queue = queue;
   S.cwf = (float)keys.cw;
   S.swf = (float)keys.sw;
-  S.stage_cap = stage_cap;
+  S.sink = LaborSink{out, cand, ctl, stage_cap, 0u, 0u, false};
 #pragma unroll
-  for (int l = 0; l < NF; ++l) {
-    S.waiting[l] = 0;
-    S.head_a[l] = vector_copy(keys.K[l].Ka[4]);
-    S.tail_a[l] = vector_copy(keys.K[l].Ka[1]);
-    S.head_b[l] = vector_copy(keys.K[l].Kb[4]);
-    S.tail_b[l] = vector_copy(keys.K[l].Kb[1]);
-  }
+  for (int l = 0; l < NF; ++l) S.set_keys(l, keys.K[l]);
   if ((int)blockIdx.x < piece_blocks) {
-    S.owns = false;
-    S.shift = 0;
     uint32_t n_pieces = *piece_count;
     if (n_pieces > piece_cap) n_pieces = piece_cap;
     for (uint32_t p = blockIdx.x; p < n_pieces; p += (uint32_t)piece_blocks) {
@@ -903,7 +773,7 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
       uint32_t len;
       const int64_t j0 = piece_start(of(g.d, 0), q, piece_len, &len);
       if (j0 < 0) continue;
-      S.first = list;  // (every lane has this list's thresholds: slot 0)
+      S.sink.first = list;  // (every lane has this list's thresholds: slot 0)
       uint32_t a1[NF], a2[NF], b2[NF];
 #pragma unroll
       for (int l = 0; l < NF; ++l) {
@@ -915,8 +785,8 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
         queue[l].lim2[lane] = lim2_all[(int64_t)l * n + list];
       }
       ListReader L(g_indices + beg + j0, len);
-      S.collect(L, (uint32_t)j0, 0u, a1, a2, b2, cand, out, ctl);
-      S.flush(cand, out, ctl);
+      S.collect(L, (uint32_t)j0, 0u, a1, a2, b2);
+      S.flush();
     }
     return;
   }
@@ -925,9 +795,9 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
   const uint32_t n_mine = n - w0 < ((int64_t)1 << each_log2) ? (uint32_t)(n - w0) : 1u << each_log2;
   const uint32_t lanes = 64u >> each_log2, sub = lane & (lanes - 1), number = lane >> (6 - each_log2);
   const int64_t w = w0 + (number < n_mine ? number : n_mine - 1);
-  S.owns = true;
-  S.first = (uint32_t)w0;
-  S.shift = (uint32_t)(6 - each_log2);
+  S.sink.owns = true;
+  S.sink.first = (uint32_t)w0;
+  S.sink.shift = (uint32_t)(6 - each_log2);
   const Segment g = seg[w];
   uint32_t my_a1[NF], my_a2[NF], my_b2[NF];
 #pragma unroll
@@ -964,7 +834,7 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
         if (g.d > stage_cap) atomicAdd(&ctl->n_overflow, 1);
       }
       const uint32_t both[4] = {t[0], t[1], 0u, 0u};
-      S.join(l, both, m, sub, lanes, lane & ~(lanes - 1), cand, out, ctl);
+      S.join(l, both, m, sub, lanes, lane & ~(lanes - 1));
     }
   }
   uint64_t todo = ballot64(speaks && g.d > together);
@@ -978,7 +848,7 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
     };
     thresholds();
     for (ListReader L(g_indices + beg, d < kStretch ? d : kStretch);;) {
-      S.collect(L, j0, (uint32_t)at, a1, a2, b2, cand, out, ctl);
+      S.collect(L, j0, (uint32_t)at, a1, a2, b2);
       if (d - j0 > kStretch) {  // the list's next stretch
         j0 += kStretch;
       } else {
@@ -993,7 +863,7 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
       L = ListReader(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
     }
   }
-  S.flush(cand, out, ctl);
+  S.flush();
   if (speaks) {
 #pragma unroll
     for (int l = 0; l < NF; ++l) out.cnt[l][w] = (int32_t)queue[l].own[lane];  // (the exact stage adds what it keeps)

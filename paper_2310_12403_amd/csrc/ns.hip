@@ -1,10 +1,7 @@
 // NS layers (App. A.1.1): a destination of degree d <= k keeps all of N(s); otherwise it keeps the k neighbours with
 // the smallest (R_ts, list position), a uniform k-subset.  Kept edges leave in (destination order, adjacency order).
 // The count is known without looking at the list (min(k, d)), so every list is read once, by the fill pass.
-#include "blend_filters.h"
-#include "device_utils.h"
-#include "list_reader.h"
-#include "sample_internal.h"
+#include "blend_scan.h"
 
 namespace coop {
 
@@ -261,13 +258,11 @@ __device__ __forceinline__ uint32_t ns_collect_plain(ListReader& L, uint32_t j0,
 
 // The same with c > 0.  The variate of an entry is evaluated exactly only if the integer bounds and then the fp32 blend cannot
 // rule it out; the survivors of the integer bounds are evaluated 64 at a time.  The candidates are in no particular order.
-// STAGED: the exact evaluation is left to a later kernel; everything that the fp32 blend cannot rule out
-// is stored as a candidate (variate 0).
 // (not inlined: see k_ns_redo)
 __device__ __attribute__((noinline)) uint32_t ns_exact_variate(uint32_t u1, uint32_t u2, double cw, double sw) {
   return kit_phi_to_u32(__builtin_fma(cw, kit_phi_inv_u32(u1), sw * kit_phi_inv_u32(u2)));
 }
-template <bool VEC4, bool STAGED = false>
+template <bool VEC4>
 __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_indices, int64_t beg, uint32_t d, uint32_t bound,
                                                const NsBlendThr& bt, const VariateParams& vp, uint32_t sigma_a, uint32_t sigma_b,
                                                NsSlot* __restrict__ slot, uint32_t cap, NsQueue* __restrict__ q) {
@@ -296,12 +291,8 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
       j = q->j[lane];
       const uint32_t u1 = keyed_exact<true>(vp.K.Ka, q->u1[lane]), u2 = keyed_exact<true>(vp.K.Kb, q->u2[lane]);
       if (__builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2)) <= bt.lim2) {
-        if constexpr (STAGED) {
-          in = true;
-        } else {
-          R = ns_exact_variate(u1, u2, vp.cw, vp.sw);
-          in = R <= bound;
-        }
+        R = ns_exact_variate(u1, u2, vp.cw, vp.sw);
+        in = R <= bound;
       }
     }
     append(in, R, j, t);
@@ -520,25 +511,6 @@ __device__ __forceinline__ void ns_rank_write(uint32_t n_c, uint32_t k, NsSlot* 
   }
 }
 
-// The list of a traversal kernel's wave: the first long_blocks blocks take the queued long lists (the queue's length is read
-// from device memory), the others the destinations in order, `each` neighbouring ones.  -1: nothing to do.
-__device__ __forceinline__ int64_t ns_list_of(int64_t n_dst, int each, const uint32_t* __restrict__ long_list,
-                                              const uint32_t* __restrict__ n_long, int long_blocks, bool* queued) {
-  *queued = (int)blockIdx.x < long_blocks;
-  int64_t w;
-  if (*queued) {  // the q-th queued long list
-    const int64_t q = blockIdx.x;
-    int64_t n_queued = (int64_t)*n_long;
-    if (n_queued > n_dst) n_queued = n_dst;  // (holds by construction; keeps every access inside the queue regardless)
-    if (q >= n_queued) return -1;
-    // (the same in every lane; said so, or everything derived from it would be kept per lane)
-    w = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)long_list[q]);
-  } else {
-    w = (int64_t)xcd_runs(blockIdx.x - (uint32_t)long_blocks, gridDim.x - (uint32_t)long_blocks) * each;
-  }
-  return w < n_dst ? w : -1;
-}
-
 // Selection of the k smallest (R, j) among d > k neighbours, one wave per destination:
 //   1. one pass over the list collects, in LDS, the candidates with R <= bound, where bound is chosen so that about
 //      `target` of them are expected (target > k, target < cap);
@@ -714,77 +686,140 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_redo(const int32_t* __restrict_
 // kernel evaluates those exactly, drops the ones above the bound and selects.  A destination whose row overflows, or
 // that ends up with fewer than k candidates (about one in 10^4), is marked and done again by k_ns_redo, which adjusts
 // the bound.
-struct NsCand { uint32_t j; int32_t t; };
-
-template <bool VEC4>
-__global__ __launch_bounds__(kBlock) void k_ns_collect(const int32_t* __restrict__ g_indices, const NsRecord* __restrict__ rec,
-                                                       const NsBlendThr* __restrict__ bthr, int64_t n_dst, uint32_t k, uint32_t cap,
-                                                       int waves_per_block, VariateParams vp, int64_t* indptr, int64_t first, int tile_log2,
-                                                       int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit,
-                                                       NsCand* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand,
-                                                       uint32_t long_min, const uint32_t* __restrict__ long_list,
-                                                       const uint32_t* __restrict__ n_long, int long_blocks) {
-  extern __shared__ __align__(16) uint32_t lds_words[];
-  NsQueue* queues = reinterpret_cast<NsQueue*>(lds_words + (size_t)waves_per_block * cap * 4);  // (behind the candidates)
-  const int wib = uniform_wave_in_block();
-  if (wib >= waves_per_block) return;
-  const uint32_t lane = (uint32_t)lane_id();
-  bool queued;
-  const int64_t w = ns_list_of(n_dst, 1, long_list, n_long, long_blocks, &queued);
-  if (w < 0) return;
-  const NsRecord g = rec[w];
-  if (!queued && long_min != 0 && g.d > long_min && g.d > k) return;  // queued: one of the first waves takes it
-  if (lane == 0) n_cand[w] = 0;  // nothing left to do for this destination, unless said otherwise below
-  const int64_t o = ns_offset(indptr, first + w, tile_log2);
-  if (lane == 0) ns_settle_offset(indptr, first + w, tile_log2, o);
-  if (o + (g.d < k ? g.d : k) > edge_limit) return;
-  if (g.d == 0) return;
-  if (g.d <= k) {
-    for (uint32_t j = lane; j < g.d; j += kWave) {
-      col_global[o + j] = g_indices[g.beg + j];
-      eid[o + j] = g.beg + j;
+//
+// The traversal's waves take destinations as k_ns_fill's do, which says what its parts are for; its candidates go through the
+// queue of a blended scan, which lives across the wave's lists (with a list to itself a wave of the fp32 stage had a quarter of its
+// lanes at work where 15 candidates are expected).
+struct NsSink {
+  StageEntry* rows;  // of the wave's first destination
+  uint32_t row_cap, shift;
+  __device__ __forceinline__ void take(BlendQueue<true>* queue, int, bool there, const StageEntry& e, uint32_t slot, float est) {
+    if (there && est <= queue->lim2[slot]) {
+      const uint32_t at = atomicAdd(&queue->own[slot], 1u);
+      if (at < row_cap) rows[(size_t)(slot >> shift) * row_cap + at] = e;
     }
-    return;
   }
-  if (k > kNsMaxSelect) return;  // (k_ns_fill_wide)
-  NsSlot* slot = reinterpret_cast<NsSlot*>(lds_words) + (size_t)wib * cap;
-  const uint32_t sigma_a = ns_sigma(vp.K.Ka, (uint32_t)g.s), sigma_b = ns_sigma(vp.K.Kb, (uint32_t)g.s);
-  const uint32_t n_c = ns_collect<VEC4, true>(g_indices, g.beg, g.d, g.bound, bthr[w], vp, sigma_a, sigma_b, slot, cap, &queues[wib]);
-  __builtin_amdgcn_wave_barrier();
-  __threadfence_block();
-  if (n_c < k || n_c > row_cap || n_c > cap) {  // (too few even before the exact test, or no room)
-    if (lane == 0) n_cand[w] = kNsRedo;
-    return;
+};
+
+__global__ __launch_bounds__(kWave, 7) void k_ns_collect(const int32_t* __restrict__ g_indices, const NsRecord* __restrict__ rec,
+                                                         const NsBlendThr* __restrict__ bthr, uint32_t n_dst, uint32_t k, LayerKeys keys, float cw,
+                                                         float sw, int64_t* indptr, int64_t first, int tile_log2, int32_t* __restrict__ col_global,
+                                                         int64_t* __restrict__ eid, int64_t edge_limit, StageEntry* __restrict__ rows, uint32_t row_cap,
+                                                         uint32_t* __restrict__ n_cand, uint32_t long_min, const uint32_t* __restrict__ long_list,
+                                                         const uint32_t* __restrict__ n_long, int long_blocks, int each_log2) {
+  __shared__ BlendQueue<true> queue;
+  const uint32_t lane = (uint32_t)lane_id();
+  uint32_t w0, n_mine = 1, skip_above = 0xFFFFFFFFu;
+  if ((int)blockIdx.x < long_blocks) {
+    uint32_t n_queued = *n_long;
+    if (n_queued > n_dst) n_queued = n_dst;  // (holds by construction; keeps every access inside the queue regardless)
+    if (blockIdx.x >= n_queued) return;
+    w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)long_list[blockIdx.x]);
+    each_log2 = 0;
+  } else {
+    w0 = xcd_runs(blockIdx.x - (uint32_t)long_blocks, gridDim.x - (uint32_t)long_blocks) << each_log2;
+    n_mine = 1u << each_log2;
+    if (long_min != 0) skip_above = long_min;
   }
-  NsCand* row = rows + (size_t)w * row_cap;
-  for (uint32_t i = lane; i < n_c; i += kWave) row[i] = NsCand{slot[i].j, slot[i].t};
-  if (lane == 0) n_cand[w] = n_c;
+  if (w0 >= n_dst) return;
+  if (n_mine > n_dst - w0) n_mine = n_dst - w0;
+  const uint32_t lanes = 64u >> each_log2, sub = lane & (lanes - 1), number = lane >> (6 - each_log2);
+  const uint32_t w = w0 + (number < n_mine ? number : n_mine - 1);
+  const NsRecord g = rec[w];
+  const NsBlendThr bt = bthr[w];
+  const int64_t o = ns_offset(indptr, first + w, tile_log2), o_end = o + (g.d < k ? g.d : k);
+  const bool mine = number < n_mine && (g.d <= k || g.d <= skip_above), speaks = mine && sub == 0;  // (the others: queued)
+  if (speaks) ns_settle_offset(indptr, first + w, tile_log2, o);
+  const bool live = mine && g.d != 0 && o_end <= edge_limit;  // (no room: the caller redoes the layer)
+  if (live && g.d <= k) {
+    for (uint32_t j = sub; j < g.d; j += lanes) {
+      (col_global + o)[j] = (g_indices + g.beg)[j];
+      (eid + o)[j] = g.beg + j;
+    }
+  }
+  const bool sampled = live && g.d > k && k <= kNsMaxSelect;  // (a larger fanout: k_ns_fill_wide)
+  BlendScan<1, true, NsSink> S;
+  S.queue = &queue;
+  S.set_keys(0, keys);
+  S.cwf = cw;
+  S.swf = sw;
+  S.sink = NsSink{rows + (size_t)w0 * row_cap, row_cap, (uint32_t)(6 - each_log2)};
+  const uint32_t mid_a = g.mid, mid_b = ns_mid(keys.Kb, ns_sigma(keys.Kb, (uint32_t)g.s));
+  const uint32_t my_a1 = bt.a1 | 0xFFFFu, my_a2 = bt.a2 | 0xFFFFu, my_b2 = bt.b2 | 0xFFFFu;
+  queue.mid_a[lane] = mid_a;
+  queue.mid_b[lane] = mid_b;
+  queue.lim2[lane] = bt.lim2;
+  queue.own[lane] = 0;
+  const uint32_t together = each_log2 != 0 ? 2 * lanes : 0;
+  if (ballot64(sampled && g.d <= together) != 0) {
+    uint32_t t[4] = {0, 0, 0, 0};
+    uint64_t m[4] = {0, 0, 0, 0};
+    S.mid_a = mid_a;
+    S.mid_b = mid_b;
+    bool in[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      in[r] = sampled && g.d <= together && sub + r * lanes < g.d;
+      if (in[r]) t[r] = (uint32_t)(g_indices + g.beg)[sub + r * lanes];
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) m[r] = S.passes(0, t[r], my_a1, my_a2, my_b2) & ballot64(in[r]);
+    S.join(0, t, m, sub, lanes, lane & ~(lanes - 1));
+  }
+  uint64_t todo = ballot64(sampled && sub == 0 && g.d > together);
+  if (todo != 0) {
+    auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
+    auto of64 = [&](int64_t x, int q) { return (int64_t)(((uint64_t)of((uint32_t)((uint64_t)x >> 32), q) << 32) | of((uint32_t)x, q)); };
+    int at = __builtin_ctzll(todo);
+    uint32_t d = of(g.d, at), j0 = 0, a1[1], a2[1], b2[1];
+    int64_t beg = of64(g.beg, at);
+    auto take = [&]() {
+      a1[0] = of(my_a1, at);
+      a2[0] = of(my_a2, at);
+      b2[0] = of(my_b2, at);
+      S.mid_a = vector_copy(of(mid_a, at));
+      S.mid_b = vector_copy(of(mid_b, at));
+    };
+    take();
+    for (ListReader L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+      S.collect(L, j0, (uint32_t)at, a1, a2, b2);
+      if (d - j0 > kStretch) {  // the list's next stretch
+        j0 += kStretch;
+      } else {
+        todo &= todo - 1;
+        if (todo == 0) break;
+        at = __builtin_ctzll(todo);
+        d = of(g.d, at);
+        beg = of64(g.beg, at);
+        j0 = 0;
+        take();
+      }
+      L = ListReader(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+    }
+  }
+  S.flush();
+  if (speaks) {  // (0: nothing left to do; too few even before the exact test, or no room in the row: k_ns_redo)
+    const uint32_t n = queue.own[lane];
+    n_cand[w] = !sampled ? 0u : n < k || n > row_cap ? kNsRedo : n;
+  }
 }
 
-__global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict__ rec, int64_t n_dst, uint32_t k, uint32_t cap,
-                                                      int waves_per_block, VariateParams vp, const int64_t* __restrict__ eptr,
-                                                      int32_t* __restrict__ col_global, int64_t* __restrict__ eid,
-                                                      const NsCand* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand,
-                                                      const NsBlendThr* __restrict__ bthr) {
-  extern __shared__ __align__(16) uint32_t lds_words[];
-  const int wib = uniform_wave_in_block();
-  if (wib >= waves_per_block) return;
+// One destination's candidates, by the whole wave (n = n_cand[w], not 0).
+__device__ __forceinline__ void ns_select_one(int64_t w, uint32_t n, NsSlot* slot, const NsRecord* __restrict__ rec, uint32_t k, const VariateParams& vp,
+                                              const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global, int64_t* __restrict__ eid,
+                                              const StageEntry* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand,
+                                              const NsBlendThr* __restrict__ bthr) {
   const uint32_t lane = (uint32_t)lane_id();
-  const int64_t w = (int64_t)blockIdx.x * waves_per_block + wib;
-  if (w >= n_dst) return;
-  const uint32_t n = n_cand[w];
-  if (n == 0 || n == kNsRedo) return;  // done by the collecting kernel, or left to k_ns_redo
   const NsRecord g = rec[w];
-  NsSlot* slot = reinterpret_cast<NsSlot*>(lds_words) + (size_t)wib * cap;
   const uint32_t sigma_a = ns_sigma(vp.K.Ka, (uint32_t)g.s), sigma_b = ns_sigma(vp.K.Kb, (uint32_t)g.s);
-  const NsCand* row = rows + (size_t)w * row_cap;
+  const StageEntry* row = rows + (size_t)w * row_cap;
   if (n <= (uint32_t)kWave) {
     // The usual case, one candidate per lane.  Only the set of the k smallest matters, so the fp32 blend (within
     // `allow` / 10 of the exact one in normal space) decides wherever it can: with e_k the k-th smallest estimate and
     // m = 2 allow, a candidate below e_k - m is among the k smallest, one above e_k + m is not, and the exact variates
     // are needed only to choose among those in between, and only if there are more of them than places left.
     const bool has = lane < n;
-    NsCand c{0xFFFFFFFFu, 0};
+    StageEntry c{0, 0xFFFFFFFFu};
     if (has) c = row[lane];
     const uint32_t u1 = keyed_uniform<true>(vp.K.Ka, (uint32_t)c.t, sigma_a), u2 = keyed_uniform<true>(vp.K.Kb, (uint32_t)c.t, sigma_b);
     const float est = has ? __builtin_fmaf((float)vp.cw, approx_phi_inv_f32(u1), (float)vp.sw * approx_phi_inv_f32(u2)) : __builtin_inff();
@@ -815,7 +850,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
     bool keep = in || und;
     if ((uint32_t)__popcll(und_mask) > need) {  // wave-uniform
       uint32_t R = 0;
-      if (und) R = kit_phi_to_u32(__builtin_fma(vp.cw, kit_phi_inv_u32(u1), vp.sw * kit_phi_inv_u32(u2)));
+      if (und) R = ns_exact_variate(u1, u2, vp.cw, vp.sw);
       const uint64_t my_key = ((uint64_t)R << 32) | c.j;
       uint32_t rank_u = 0;
       uint64_t rest = und_mask;
@@ -845,13 +880,13 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
   uint32_t n_c = 0;  // candidates with R <= bound, compacted into LDS
   for (uint32_t base = 0; base < n; base += kWave) {
     const uint32_t i = base + lane;
-    NsCand c{0u, 0};
+    StageEntry c{0, 0u};
     uint32_t R = 0;
     bool in = false;
     if (i < n) {
       c = row[i];
       const uint32_t u1 = keyed_uniform<true>(vp.K.Ka, (uint32_t)c.t, sigma_a), u2 = keyed_uniform<true>(vp.K.Kb, (uint32_t)c.t, sigma_b);
-      R = kit_phi_to_u32(__builtin_fma(vp.cw, kit_phi_inv_u32(u1), vp.sw * kit_phi_inv_u32(u2)));
+      R = ns_exact_variate(u1, u2, vp.cw, vp.sw);
       in = R <= g.bound;
     }
     const uint64_t mask = ballot64(in);
@@ -864,6 +899,105 @@ __global__ __launch_bounds__(kBlock) void k_ns_select(const NsRecord* __restrict
     return;
   }
   ns_rank_write(n_c, k, slot, eptr[w], g.beg, col_global, eid);
+}
+
+
+// A wave takes 2^each_log2 destinations, 2^(6 - group_log2) of them at a time with 2^group_log2 lanes each; those with more candidates
+// than that follow one by one.  (As ns_select_one, whose comments say why; a destination per wave had 15 to 35 of its lanes at
+// work, and starting a wave for each took a third of the time.)
+__global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restrict__ rec, int64_t n_dst, uint32_t k, VariateParams vp,
+                                                     const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global, int64_t* __restrict__ eid,
+                                                     const StageEntry* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand,
+                                                     const NsBlendThr* __restrict__ bthr, int each_log2, int group_log2) {
+  extern __shared__ __align__(16) uint32_t lds_words[];  // slots for ns_select_one, at least kWave
+  NsSlot* slot = reinterpret_cast<NsSlot*>(lds_words);
+  uint64_t* key_of = reinterpret_cast<uint64_t*>(lds_words);  // [kWave] the groups' keys, then positions
+  uint32_t* j_of = lds_words;
+  const uint32_t lane = (uint32_t)lane_id();
+  const uint32_t G = 1u << group_log2, at0 = lane & ~(G - 1), sub = lane & (G - 1);
+  const uint64_t group = low_lanes(G) << at0;
+  const int64_t w_end = ((int64_t)blockIdx.x + 1) << each_log2 < n_dst ? ((int64_t)blockIdx.x + 1) << each_log2 : n_dst;
+  const float cwf = (float)vp.cw, swf = (float)vp.sw;
+  const float allow = (float)((vp.cw + vp.sw) * kPhiInvF32Allow + 2.0 * kBlendAbsWiden);
+  const float m = 2.0f * allow;
+  auto settle = [] {
+    __builtin_amdgcn_wave_barrier();
+    __threadfence_block();
+  };
+  for (int64_t w0 = (int64_t)blockIdx.x << each_log2; w0 < w_end; w0 += 64 >> group_log2) {
+    const int64_t w = w0 + (lane >> group_log2);
+    uint32_t n = w < w_end ? n_cand[w] : 0u;
+    if (n == kNsRedo) n = 0;  // (0: done by the collecting kernel)
+    uint64_t many = ballot64(n > G && sub == 0);
+    if (n > G) n = 0;
+    if (ballot64(n != 0) != 0) {
+      const int64_t ww = n != 0 ? w : w0;
+      const NsRecord g = rec[ww];
+      const bool has = sub < n;
+      StageEntry c{0, 0xFFFFFFFFu};
+      if (has) c = rows[(size_t)w * row_cap + sub];
+      const uint32_t sigma_a = ns_sigma(vp.K.Ka, (uint32_t)g.s), sigma_b = ns_sigma(vp.K.Kb, (uint32_t)g.s);
+      const uint32_t u1 = keyed_uniform<true>(vp.K.Ka, (uint32_t)c.t, sigma_a), u2 = keyed_uniform<true>(vp.K.Kb, (uint32_t)c.t, sigma_b);
+      const float est = __builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2));
+      const uint32_t eb = __float_as_uint(est);
+      const uint64_t est_key = has ? ((uint64_t)(eb ^ ((uint32_t)((int32_t)eb >> 31) | 0x80000000u)) << 32) | lane : ~0ull;
+      uint32_t most = 0;  // candidates of the largest group
+      for (uint32_t q = 0; q < (uint32_t)kWave; q += G) {
+        const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)n, (int)q);
+        most = x > most ? x : most;
+      }
+      // a group's keys, one after the other: every lane counts those below its own (what stands behind the group's candidates is above all)
+      auto rank_of = [&](uint64_t key) {
+        settle();
+        key_of[lane] = key;
+        settle();
+        uint32_t rank = 0;
+        for (uint32_t q = 0; q < most; q += 4)
+#pragma unroll
+          for (uint32_t e = 0; e < 4; ++e) rank += key_of[at0 + q + e] < key;
+        return rank;
+      };
+      const uint32_t rank_est = rank_of(est_key);
+      // the k-th smallest estimate
+      settle();
+      if (has && rank_est == k - 1) reinterpret_cast<float*>(lds_words)[at0] = est;
+      settle();
+      const float e_k = n != 0 ? reinterpret_cast<float*>(lds_words)[at0] : 0.0f;
+      const bool sure = n != 0 && e_k >= -5.0f && e_k <= 5.0f && e_k + m <= bthr[ww].lim2 - m;
+      if (n != 0 && !sure && sub == 0) n_cand[w] = kNsRedo;
+      const bool in = has && sure && est < e_k - m;
+      const bool und = has && sure && !in && est <= e_k + m;
+      const uint32_t n_in = (uint32_t)__popcll(ballot64(in) & group), n_und = (uint32_t)__popcll(ballot64(und) & group);
+      const bool choose = und && n_und > k - n_in;
+      bool keep = in || und;
+      if (ballot64(choose) != 0) {
+        uint32_t R = 0;
+        if (choose) R = ns_exact_variate(u1, u2, vp.cw, vp.sw);
+        const uint32_t rank_u = rank_of(choose ? ((uint64_t)R << 32) | c.j : ~0ull);
+        if (choose) keep = rank_u < k - n_in;
+      }
+      // a kept candidate's place is the number of kept ones in front of it in the list
+      const uint32_t number = lanes_below(ballot64(keep) & group);
+      settle();
+      if (keep) j_of[at0 + number] = c.j;  // (k of them, where there are any)
+      settle();
+      if (keep) {
+        uint32_t place = 0;
+        for (uint32_t q = 0; q < k; ++q) place += j_of[at0 + q] < c.j;
+        const int64_t o = eptr[w];
+        col_global[o + place] = c.t;
+        eid[o + place] = g.beg + c.j;
+      }
+    }
+    while (many != 0) {
+      const int q = __builtin_ctzll(many);
+      many &= many - 1;
+      const int64_t w_q = w0 + (q >> group_log2);
+      settle();
+      ns_select_one(w_q, n_cand[w_q], slot, rec, k, vp, eptr, col_global, eid, rows, row_cap, n_cand, bthr);
+    }
+    settle();
+  }
 }
 
 // ---- fanouts above kNsMaxSelect ----------------------------------------------------------------------------------
@@ -999,13 +1133,13 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
     // layer; with dependent variates the traversal 3.0 -> 2.57 ms and the selection 0.99 -> 0.91)
     const int wpb = 1;
     const size_t shmem = (size_t)wpb * cap * 16 + (cx.blend ? (size_t)wpb * sizeof(NsQueue) : 0);
-    NsCand* rows = nullptr;
+    StageEntry* rows = nullptr;
     uint32_t* n_cand = nullptr;
     uint32_t row_cap = 64;
     if (cx.blend) {
       // rows of the two-kernel path: room for twice the expected candidates (at least 64, at most the LDS capacity)
       while (row_cap < 2 * target && row_cap < cap) row_cap <<= 1;
-      rows = alloc.get<NsCand>(n_dst * (int64_t)row_cap, COOP_TAG_SCRATCH);
+      rows = alloc.get<StageEntry>(n_dst * (int64_t)row_cap, COOP_TAG_SCRATCH);
       n_cand = alloc.get<uint32_t>(n_dst, COOP_TAG_SCRATCH);
       if (alloc.failed) return COOP_E_NOMEM;
     }
@@ -1017,29 +1151,32 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
     const int long_blocks = queue_long ? (int)blocks_for(most_long, wpb) : 0;
     for (int64_t b = 0; b < n_dst; b += kSliceLists) {  // (one slice, unless there are 67 million destinations)
       const int64_t n = n_dst - b < kSliceLists ? n_dst - b : kSliceLists;
-      const dim3 grid(blocks_for(n, wpb)), grid_q(grid.x + (unsigned)long_blocks), grid_w(blocks_for(n, kWavesPerBlock));
+      const dim3 grid_w(blocks_for(n, kWavesPerBlock));
+      int each_log2 = 0;
+      while (each_log2 < 3 && (n >> (each_log2 + 1)) >= kNsFillWaves) ++each_log2;
       const NsRecord* rec_b = rec + b;
       const NsBlendThr* bthr_b = cx.blend ? bthr + b : nullptr;
       const int64_t* eptr_b = blk->indptr + b;
 #define COOP_NS_ARGS cx.g->indices, rec_b, bthr_b, n, k, cap, wpb, vp, eptr_b, blk->col_global, blk->eid, m
       if (cx.blend) {
-        NsCand* rows_b = rows + b * (int64_t)row_cap;
+        StageEntry* rows_b = rows + b * (int64_t)row_cap;
+        // lanes per destination in the selection: as many as hold the candidates of most
+        const int group_log2 = target <= 10 ? 4 : target <= 24 ? 5 : 6;
+        const int select_log2 = each_log2 > 6 - group_log2 ? each_log2 : 6 - group_log2;
         uint32_t* n_cand_b = n_cand + b;
         int lists_log2 = 0;
         while (lists_log2 < 6 && (n >> (lists_log2 + 1)) >= kNsRedoWaves) ++lists_log2;
         const dim3 grid_redo(blocks_for(n, (int64_t)wpb << lists_log2));
-#define COOP_NS_BLEND(VEC4)                                                                                                                \
-  COOP_LAUNCH(K_NS_FILL, k_ns_collect<VEC4>, grid_q, dim3(wpb * kWave), shmem, s, cx.g->indices, rec_b, bthr_b, n, k, cap, wpb, vp,         \
-              blk->indptr, b, tile_log2, blk->col_global, blk->eid, m, rows_b, row_cap, n_cand_b, long_min,        \
-              (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks);                                                           \
-  COOP_LAUNCH(K_NS_SELECT, k_ns_select, grid, dim3(wpb * kWave), shmem, s, rec_b, n, k, cap, wpb, vp, eptr_b, blk->col_global, blk->eid,    \
-              (const NsCand*)rows_b, row_cap, n_cand_b, bthr_b);                                                                           \
+        COOP_LAUNCH(K_NS_FILL, k_ns_collect, dim3(blocks_for(n, (int64_t)1 << each_log2) + (unsigned)long_blocks), dim3(kWave), 0, s, cx.g->indices,
+                    rec_b, bthr_b, (uint32_t)n, k, vp.K, (float)vp.cw, (float)vp.sw, blk->indptr, b, tile_log2, blk->col_global, blk->eid, m, rows_b,
+                    row_cap, n_cand_b, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2);
+        COOP_LAUNCH(K_NS_SELECT, k_ns_select, dim3(blocks_for(n, (int64_t)1 << select_log2)), dim3(kWave), (size_t)cap * sizeof(NsSlot), s, rec_b, n, k, vp,
+                    eptr_b, blk->col_global, blk->eid, (const StageEntry*)rows_b, row_cap, n_cand_b, bthr_b, select_log2, group_log2);
+#define COOP_NS_BLEND(VEC4) \
   COOP_LAUNCH(K_NS_FILL, k_ns_redo<VEC4>, grid_redo, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, (const uint32_t*)n_cand_b, lists_log2)
         if (cx.vec4) { COOP_NS_BLEND(true); } else { COOP_NS_BLEND(false); }
 #undef COOP_NS_BLEND
       } else {
-        int each_log2 = 0;
-        while (each_log2 < 3 && (n >> (each_log2 + 1)) >= kNsFillWaves) ++each_log2;
         COOP_LAUNCH(K_NS_FILL, k_ns_fill, dim3(blocks_for(n, (int64_t)1 << each_log2) + (unsigned)long_blocks), dim3(kWave),
                     (cap + kWave) * sizeof(NsSlot), s, cx.g->indices, rec_b, (uint32_t)n, k, cap, vp.K, blk->indptr, b, tile_log2,
                     blk->col_global, blk->eid, m, cx.d_ctl, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2);

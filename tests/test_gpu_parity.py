@@ -1108,9 +1108,10 @@ def test_labor_lists_around_the_edges_of_groups(P, aligned, kappa):
         P.coop_tune(P.COOP_TUNE_STAGE_CAP, 0)
 
 
+@pytest.mark.parametrize("kappa", [1, 4])
 @pytest.mark.parametrize("aligned", [True, False])
-def test_ns_lists_around_the_edges_of_groups(P, aligned):
-    """c = 0: lists of one entry less than, as many as and one more than 64 q entries, of whole groups of 256 with and without a
+def test_ns_lists_around_the_edges_of_groups(P, aligned, kappa):
+    """Lists of one entry less than, as many as and one more than 64 q entries, of whole groups of 256 with and without a
     rest and of more groups than are in flight, starting at any alignment, among short ones; waves that take one, two and
     eight destinations, the last of them fewer; and lists whose neighbours repeat, so that equal variates stand across the border
     of the k smallest."""
@@ -1131,8 +1132,11 @@ def test_ns_lists_around_the_edges_of_groups(P, aligned):
         base = torch.empty(len(indices) + 1, dtype=torch.int32, device="cuda")
         base[1:] = g.indices_d
         g.graph = P.coop_graph_load(g.indptr_d, base[1:], P.COOP_VALIDATE)
-    for size, k in ((5000, 10), (32769, 25), (70001, 5), (131075, 10)) if aligned else ((131075, 10),):
-        compare(P, g, np.arange(size), (k,), R.NS, seed=size)
+    cases = ((5000, 10), (32769, 25), (70001, 5), (131075, 10)) if aligned else ((131075, 10),)
+    if kappa > 1:  # 16, 32 and 64 lanes per destination in the selection, and destinations with more candidates than that
+        cases += ((40001, 1), (40001, 7), (20001, 60))
+    for size, k in cases:
+        compare(P, g, np.arange(size), (k,), R.NS, it=kappa - 1, kappa=kappa, seed=size)
 
 
 def test_ns_count_in_wide_blocks(P):
