@@ -916,7 +916,8 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restri
   const uint32_t lane = (uint32_t)lane_id();
   const uint32_t G = 1u << group_log2, at0 = lane & ~(G - 1), sub = lane & (G - 1);
   const uint64_t group = low_lanes(G) << at0;
-  const int64_t w_end = ((int64_t)blockIdx.x + 1) << each_log2 < n_dst ? ((int64_t)blockIdx.x + 1) << each_log2 : n_dst;
+  const int64_t w_first = (int64_t)blockIdx.x << each_log2;
+  const uint32_t n_mine = n_dst - w_first < ((int64_t)1 << each_log2) ? (uint32_t)(n_dst - w_first) : 1u << each_log2;
   const float cwf = (float)vp.cw, swf = (float)vp.sw;
   const float allow = (float)((vp.cw + vp.sw) * kPhiInvF32Allow + 2.0 * kBlendAbsWiden);
   const float m = 2.0f * allow;
@@ -924,19 +925,38 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restri
     __builtin_amdgcn_wave_barrier();
     __threadfence_block();
   };
-  for (int64_t w0 = (int64_t)blockIdx.x << each_log2; w0 < w_end; w0 += 64 >> group_log2) {
-    const int64_t w = w0 + (lane >> group_log2);
-    uint32_t n = w < w_end ? n_cand[w] : 0u;
-    if (n == kNsRedo) n = 0;  // (0: done by the collecting kernel)
+  // What is known of the wave's destinations, one per lane, all of it requested together: with the requests of every step waiting
+  // for one another 250 thousand destinations with 15 candidates each took 49 us, now 44 (and before that, with a wave each, 112).
+  const int64_t w_lane = w_first + (lane < n_mine ? lane : n_mine - 1);
+  uint32_t all_n = n_cand[w_lane];
+  if (all_n == kNsRedo || lane >= n_mine) all_n = 0;  // (0: done by the collecting kernel)
+  const NsRecord all_rec = rec[w_lane];
+  const float all_lim2 = bthr[w_lane].lim2;
+  const int64_t all_o = eptr[w_lane];
+  const uint32_t all_sa = ns_sigma(vp.K.Ka, (uint32_t)all_rec.s), all_sb = ns_sigma(vp.K.Kb, (uint32_t)all_rec.s);
+  auto share = [](uint32_t x, uint32_t from) { return (uint32_t)__shfl((int)x, (int)from, kWave); };
+  auto share64 = [&](int64_t x, uint32_t from) { return (int64_t)(((uint64_t)share((uint32_t)((uint64_t)x >> 32), from) << 32) | share((uint32_t)x, from)); };
+  const uint32_t step = 64u >> group_log2;
+  auto fetch = [&](uint32_t i0) {  // the candidates of the step that begins with the wave's destination i0
+    const uint32_t i = i0 + (lane >> group_log2);
+    const uint32_t n = share(all_n, i < n_mine ? i : i0);  // (every lane takes part)
+    StageEntry c{0, 0xFFFFFFFFu};
+    if (i < n_mine && n <= G && sub < n) c = rows[(size_t)(w_first + i) * row_cap + sub];
+    return c;
+  };
+  StageEntry next = fetch(0);
+  for (uint32_t i0 = 0; i0 < n_mine; i0 += step) {
+    const uint32_t i = i0 + (lane >> group_log2), from = i < n_mine ? i : i0;
+    const int64_t w0 = w_first + i0, w = w_first + i;
+    uint32_t n = share(all_n, from);
+    if (i >= n_mine) n = 0;
     uint64_t many = ballot64(n > G && sub == 0);
     if (n > G) n = 0;
+    const StageEntry c = next;
+    if (i0 + step < n_mine) next = fetch(i0 + step);
     if (ballot64(n != 0) != 0) {
-      const int64_t ww = n != 0 ? w : w0;
-      const NsRecord g = rec[ww];
       const bool has = sub < n;
-      StageEntry c{0, 0xFFFFFFFFu};
-      if (has) c = rows[(size_t)w * row_cap + sub];
-      const uint32_t sigma_a = ns_sigma(vp.K.Ka, (uint32_t)g.s), sigma_b = ns_sigma(vp.K.Kb, (uint32_t)g.s);
+      const uint32_t sigma_a = share(all_sa, from), sigma_b = share(all_sb, from);
       const uint32_t u1 = keyed_uniform<true>(vp.K.Ka, (uint32_t)c.t, sigma_a), u2 = keyed_uniform<true>(vp.K.Kb, (uint32_t)c.t, sigma_b);
       const float est = __builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2));
       const uint32_t eb = __float_as_uint(est);
@@ -963,7 +983,8 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restri
       if (has && rank_est == k - 1) reinterpret_cast<float*>(lds_words)[at0] = est;
       settle();
       const float e_k = n != 0 ? reinterpret_cast<float*>(lds_words)[at0] : 0.0f;
-      const bool sure = n != 0 && e_k >= -5.0f && e_k <= 5.0f && e_k + m <= bthr[ww].lim2 - m;
+      const float lim2 = __shfl(all_lim2, (int)from, kWave);
+      const bool sure = n != 0 && e_k >= -5.0f && e_k <= 5.0f && e_k + m <= lim2 - m;
       if (n != 0 && !sure && sub == 0) n_cand[w] = kNsRedo;
       const bool in = has && sure && est < e_k - m;
       const bool und = has && sure && !in && est <= e_k + m;
@@ -981,12 +1002,12 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restri
       settle();
       if (keep) j_of[at0 + number] = c.j;  // (k of them, where there are any)
       settle();
+      const int64_t o = share64(all_o, from), beg = share64(all_rec.beg, from);
       if (keep) {
         uint32_t place = 0;
         for (uint32_t q = 0; q < k; ++q) place += j_of[at0 + q] < c.j;
-        const int64_t o = eptr[w];
         col_global[o + place] = c.t;
-        eid[o + place] = g.beg + c.j;
+        eid[o + place] = beg + c.j;
       }
     }
     while (many != 0) {
@@ -994,7 +1015,7 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restri
       many &= many - 1;
       const int64_t w_q = w0 + (q >> group_log2);
       settle();
-      ns_select_one(w_q, n_cand[w_q], slot, rec, k, vp, eptr, col_global, eid, rows, row_cap, n_cand, bthr);
+      ns_select_one(w_q, (uint32_t)__builtin_amdgcn_readlane((int)all_n, (int)(w_q - w_first)), slot, rec, k, vp, eptr, col_global, eid, rows, row_cap, n_cand, bthr);
     }
     settle();
   }
