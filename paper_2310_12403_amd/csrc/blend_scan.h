@@ -122,7 +122,8 @@ struct BlendScan {
   __device__ __forceinline__ uint64_t passes(int l, uint32_t t, uint32_t a1, uint32_t a2, uint32_t b2) const {
     const uint32_t u1 = rough(head_a[l], mid_a, tail_a[l], t), u2 = rough(head_b[l], mid_b, tail_b[l], t);
     const uint32_t lo = u1 < u2 ? u1 : u2, hi = u1 < u2 ? u2 : u1;
-    return compare_mask(lo <= a1) | (compare_mask(lo <= a2) & compare_mask(hi <= b2));
+    const uint32_t edge = hi <= b2 ? a2 : a1;
+    return compare_mask(lo <= edge);
   }
 
   // Stage 1 on a list (or a stretch of it that starts at list position j0) whose thresholds lane `slot` has.
