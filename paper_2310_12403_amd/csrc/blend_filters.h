@@ -63,18 +63,25 @@ __device__ __forceinline__ uint32_t blend_widen(uint32_t R) {
   return lim >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)lim;
 }
 
-__device__ __forceinline__ PreThr blend_first_thresholds(uint32_t thr, double cw, double sw) {
-  if (thr >= 0x7FFFFFF0u) return PreThr{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0.0f};  // k / d near or above 1/2: no useful bound
-  const double tau_s = kit_phi_inv_u32(thr + kThrWiden) * (1.0 - kBlendRelWiden);  // < 0
-  const double x2 = tau_s * kit_rcp(cw + sw);
-  PreThr p;
-  p.a2 = blend_widen(kit_phi_to_u32(x2));
-  p.a1 = kit_phi_to_u32(x2 - kStripShift);
-  const double x1 = kit_phi_inv_u32(p.a1);
+// (Its parts, for kernels that have several waves evaluate the thresholds of the same lists; thr < kThrAllPass.)
+constexpr uint32_t kThrAllPass = 0x7FFFFFF0u;  // k / d near or above 1/2: no useful bound
+__device__ __forceinline__ double blend_tau(uint32_t thr) { return kit_phi_inv_u32(thr + kThrWiden) * (1.0 - kBlendRelWiden); }  // < 0
+__device__ __forceinline__ uint32_t blend_a2(double x2) { return blend_widen(kit_phi_to_u32(x2)); }
+__device__ __forceinline__ void blend_strip(double tau_s, double x2, double cw, double sw, uint32_t* a1, uint32_t* b2) {
+  *a1 = kit_phi_to_u32(x2 - kStripShift);
+  const double x1 = kit_phi_inv_u32(*a1);
   const double cM = cw > sw ? cw : sw, cm = cw > sw ? sw : cw;
   double y2 = (tau_s - cM * x1) * kit_rcp(cm);
   y2 = y2 + kBlendRelWiden * (y2 < 0.0 ? -y2 : y2) + 1e-9;
-  p.b2 = y2 >= 6.0 ? 0xFFFFFFFFu : blend_widen(kit_phi_to_u32(y2));
+  *b2 = y2 >= 6.0 ? 0xFFFFFFFFu : blend_widen(kit_phi_to_u32(y2));
+}
+__device__ __forceinline__ PreThr blend_first_thresholds(uint32_t thr, double cw, double sw) {
+  if (thr >= kThrAllPass) return PreThr{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0.0f};
+  const double tau_s = blend_tau(thr);
+  const double x2 = tau_s * kit_rcp(cw + sw);
+  PreThr p;
+  p.a2 = blend_a2(x2);
+  blend_strip(tau_s, x2, cw, sw, &p.a1, &p.b2);
   p.keep2 = 0.0f;
   return p;
 }

@@ -325,10 +325,14 @@ __global__ __launch_bounds__(kWalkBlock, 6) void k_enum_walk(const int32_t* __re
 // ones, which spread over more CUs what the thresholds of a blend cost in fp64 (1,024 destinations, three layers: 13 us in
 // one block, 10 in sixteen; 110 thousand with two layers 15 and 9).
 constexpr int64_t kSegWideFrom = 65536;
+constexpr int64_t kSegSharedBelow = 16384;
 // (c > 0) The buffer of candidates for the exact blend is split into kCandSub sub-buffers with a counter each (a block appends to sub-buffer blockIdx mod
 // kCandSub): appending costs an atomic with a returned value, and a single counter would serialise them.
 constexpr int kCandSub = 256;
-template <int kSegBlock>
+// With SHARED (blocks of three waves and c > 0) the first wave has the block's 64 destinations, and the two others evaluate some of their
+// thresholds, each of them a chain of several hundred fp64 instructions: four behind one another in the place of seven (1,024 to 16
+// thousand destinations of the reddit-shaped step with a cache: 10.5 us a launch and 8.5).
+template <int kSegBlock, bool SHARED = false>
 __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restrict__ g_indptr, int64_t n_vertices,
                                                      const int32_t* __restrict__ dst, int64_t n, int nf,
                                                      uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3, Segment* __restrict__ seg,
@@ -343,8 +347,27 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
     for (int q = threadIdx.x; q < kCandSub; q += kSegBlock) cand_count[q] = 0;
   __shared__ uint32_t s_wave_at[kSegBlock / kWave];
   __shared__ uint32_t s_base, s_total;
-  const int64_t i = (int64_t)blockIdx.x * kSegBlock + threadIdx.x;
-  const bool live = i < n;
+  constexpr int kDestinations = SHARED ? kWave : kSegBlock;
+  const int64_t i = (int64_t)blockIdx.x * kDestinations + (SHARED ? (int)(threadIdx.x & (kWave - 1)) : (int)threadIdx.x);
+  const int share = SHARED ? uniform_wave_in_block() : 0;
+  if (SHARED && share != 0 && i < n) {
+    const int32_t s = dst[i];
+    uint32_t d = 0;
+    if ((uint64_t)(uint32_t)s < (uint64_t)n_vertices) d = (uint32_t)(g_indptr[s + 1] - g_indptr[s]);
+    const uint32_t ks[kMaxFuse] = {k0, k1, k2, k3};
+#pragma unroll
+    for (int f = 0; f < kMaxFuse; ++f)
+      if (f < nf) {
+        const uint32_t t = d > ks[f] ? (uint32_t)(((uint64_t)ks[f] << 32) / (uint64_t)d) : kAllThr;
+        if (share == 1) {
+          pthr[(int64_t)f * n + i].a2 = t < kThrAllPass ? blend_a2(blend_tau(t) * kit_rcp(cw + sw)) : 0xFFFFFFFFu;
+        } else {
+          pthr[(int64_t)f * n + i].keep2 = blend_keep_threshold(t, cw + sw);
+          lim2[(int64_t)f * n + i] = blend_second_threshold(t, cw + sw);
+        }
+      }
+  }
+  const bool live = share == 0 && i < n;
   Segment g{0, 0, 0};
   bool sampled = live;  // every covered layer keeps a proper subset (d > k)
   uint32_t thr_mine[kMaxFuse] = {0, 0, 0, 0};
@@ -364,7 +387,15 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
         sampled &= t != kAllThr;
         thr[(int64_t)f * n + i] = t;
         thr_mine[f] = t;
-        if (pthr) {
+        if constexpr (SHARED) {
+          uint32_t a1 = 0xFFFFFFFFu, b2 = 0xFFFFFFFFu;
+          if (t < kThrAllPass) {
+            const double tau_s = blend_tau(t);
+            blend_strip(tau_s, tau_s * kit_rcp(cw + sw), cw, sw, &a1, &b2);
+          }
+          pthr[(int64_t)f * n + i].a1 = a1;
+          pthr[(int64_t)f * n + i].b2 = b2;
+        } else if (pthr) {
           PreThr pt = blend_first_thresholds(t, cw, sw);
           pt.keep2 = blend_keep_threshold(t, cw + sw);
           pthr[(int64_t)f * n + i] = pt;
@@ -431,7 +462,7 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
       todo &= todo - 1;
       const uint32_t np_s = (uint32_t)__builtin_amdgcn_readlane((int)np, src);
       const uint32_t at = base + (uint32_t)__builtin_amdgcn_readlane((int)incl, src) - np_s;
-      const uint32_t list = (uint32_t)((int64_t)blockIdx.x * kSegBlock + (threadIdx.x & ~(kWave - 1)) + src);
+      const uint32_t list = (uint32_t)((int64_t)blockIdx.x * kDestinations + (threadIdx.x & ~(kWave - 1)) + src);
       for (uint32_t q = lane; q < np_s; q += kWave)
         if (at + q < piece_cap) pieces[at + q] = fits ? Piece{list, q} : Piece{kNoPiece, 0u};
     }
@@ -1186,14 +1217,14 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
         fill_u64((uint64_t*)zeroed, (1 + kLongBits / 8 / sizeof(LongSlot) + (int64_t)slots) * (sizeof(LongSlot) / 8), 0, s);
       }
       const Clear clear = take_clear(cx);
-#define COOP_SEGMENTS(BLOCK)                                                                                                          \
-  COOP_LAUNCH(K_SEGMENTS, k_segments<BLOCK>, dim3(blocks_for(n_new, BLOCK)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices,          \
+#define COOP_SEGMENTS(BLOCK, EACH, SHARED)                                                                                            \
+  COOP_LAUNCH(K_SEGMENTS, (k_segments<BLOCK, SHARED>), dim3(blocks_for(n_new, EACH)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices,  \
               dst + ps.start, n_new, ps.nf, ks[0], ks[1], ks[2], ks[3], ps.seg, ps.thr, pthr, lim2, cx.cw, cx.sw,                        \
               cx.d_ctl, piece_len, split_min, pieces, piece_cap, cx.d_piece_count + l, out, enum_degree,    \
               long_bits, long_tab, long_mask, clear, cand_count)
-      if (n_new >= kSegWideFrom) COOP_SEGMENTS(1024);
-      else if (n_new >= 16384 || !cx.blend) COOP_SEGMENTS(256);
-      else COOP_SEGMENTS(64);
+      if (n_new >= kSegWideFrom) COOP_SEGMENTS(1024, 1024, false);
+      else if (n_new >= kSegSharedBelow || !cx.blend) COOP_SEGMENTS(256, 256, false);
+      else COOP_SEGMENTS(3 * kWave, kWave, true);
 #undef COOP_SEGMENTS
       if (enum_degree != 0) {
         if (list_todo != 0) {
