@@ -478,8 +478,7 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
 
 // Ordered visit of the neighbour list [beg, beg + d) of one destination by the whole wave, one entry per lane and
 // step: calls emit(rank, t, j) for every kept neighbour t at list position j, rank counting kept neighbours in
-// adjacency order.  Returns the number kept (same value in every lane).  Used for short lists, for an indices array
-// that is not 16-byte aligned, and for the overflow pass.
+// adjacency order.  Returns the number kept (same value in every lane).  Used by the overflow pass.
 template <bool BLEND, typename Emit>
 __device__ __forceinline__ uint32_t labor_scan_ordered(const int32_t* __restrict__ g_indices, int64_t beg, uint32_t d, uint32_t thr,
                                                        const LayerKeys& K, double cw, double sw, Emit emit) {
@@ -590,6 +589,12 @@ __device__ __forceinline__ int64_t piece_start(uint32_t d, uint32_t q, uint32_t 
 // entries leave.  The first `piece_blocks` blocks take the pieces of the long lists (block b takes pieces b,
 // b + piece_blocks, ... of the queue, whose length is read from device memory); a piece adds its kept-edge counts to the list's
 // counters and puts its entries wherever that leaves them in the staging row: the fill pass sorts the rows by list position.
+//
+// Bound by instruction issue next to HBM: last layer of the products shape, 480 thousand lists, 95 us with a list at a time, an
+// ordered pass per layer over the short ones, lane masks in every group and a store to the row from every step with a kept entry,
+// 68 now; the papers100M shape without the lists above 8,192 entries, 290 M entries in three passes, 345 us and 320 (the entries
+// alone, at the rate of a copy: 237).  The next list's entries requested before this one's are looked at: 91 us and 330, for the
+// registers.
 template <int NF>
 __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_scan_plain(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg,
                                                                const uint32_t* __restrict__ thr_all, int64_t n, int each_log2, FusedKeys keys,
@@ -729,6 +734,7 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
 //      runs with every lane busy.
 // A kept edge takes the next free slot of its destination's staging row with an atomic on the row's counter; rows
 // filled this way are unordered and the fill pass ranks them by list position.
+
 // A candidate for the exact blend.
 struct Cand {
   int32_t t;       // neighbour
@@ -774,7 +780,9 @@ struct LaborSink {
   }
 };
 
-// The scan pass with blended variates: destinations, pieces and short lists as in k_labor_scan_plain.
+// The scan pass with blended variates: destinations, pieces and short lists as in k_labor_scan_plain; a list that a layer keeps whole
+// goes past the stages where it is short.  Bound by vector instructions (some 27 of 64 entries and layer in stage 1, as many for its
+// passers).  A quarter of the papers100M shape: one layer 305 us and 176 now, two layers 315 and 253 (blend_scan.h says what changed).
 template <int NF>
 __global__ __launch_bounds__(kWave, NF == 1 ? 7 : NF == 2 ? 6 : NF == 3 ? 5 : 4) void
 k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg, const uint32_t* __restrict__ thr_all,
@@ -962,7 +970,7 @@ __global__ __launch_bounds__(BLOCK) void k_labor_fill_staged(LayerChunks ch, Cou
   const StageEntry* __restrict__ row = ch.stage[p] + (size_t)local * stage_cap;
   const Segment g = ch.seg[p][local];
   const int sub = (int)(idx & ((1 << kFillLanesLog2) - 1));
-  // A row may hold its entries in any order (the fast scan writes them as they come, the pieces of a cut list and the
+  // A row may hold its entries in any order (the pieces of a cut list, the lists found from the other side and the
   // blended passes take slots by atomics): an entry's place is its rank by list position.  The lane group (all in one
   // wave) shares the positions through LDS.  Rows that happen to be in order go the same way: two paths side by side
   // in a wave cost more than ranking a dozen entries.
@@ -1041,7 +1049,10 @@ static void launch_scan_plain(int nf, unsigned blocks, hipStream_t s, const int3
 #undef COOP_SCAN_PLAIN
 }
 
-constexpr int64_t kPieceWaves = 8192;
+constexpr int64_t kPieceWaves = 8192;  // one round of resident waves
+// Destinations per wave, as a power of two: products-, papers100M-shaped and dependent steps 677, 1105 and 1043 us by this rule, 677,
+// 1103 and 1045 with four in every pass, 680, 1114 and 1046 with eight, 698, 1131 and 1072 with sixteen; the reddit-shaped step with a
+// cache, passes of a few thousand lists: 271 by this rule (one), 284 with four.
 constexpr int64_t kScanWaves = 16384;
 constexpr int kScanEachLog2 = 3;
 

@@ -1181,7 +1181,8 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
 #define COOP_NS_ARGS cx.g->indices, rec_b, bthr_b, n, k, cap, wpb, vp, eptr_b, blk->col_global, blk->eid, m
       if (cx.blend) {
         StageEntry* rows_b = rows + b * (int64_t)row_cap;
-        // lanes per destination in the selection: as many as hold the candidates of most
+        // Lanes per destination in the selection: as many as hold the candidates of most (a tenth more pass the filters than are
+        // expected; 250 thousand destinations with 15 expected: 112 us with 64 lanes and a wave for each, 49 with 32 and eight a wave).
         const int group_log2 = target <= 10 ? 4 : target <= 24 ? 5 : 6;
         const int select_log2 = each_log2 > 6 - group_log2 ? each_log2 : 6 - group_log2;
         uint32_t* n_cand_b = n_cand + b;
