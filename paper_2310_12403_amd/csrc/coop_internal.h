@@ -73,8 +73,7 @@ struct Ctl {
   int32_t n_overflow;    // LABOR-0 destinations whose staging row overflowed (this layer and earlier)
   int32_t cand_overflow; // blended LABOR-0: the candidate buffer of the exact stage was too small (the pass is redone)
   int32_t uniq_overflow; // dedup by partition: a bucket held more distinct vertices than its table (redone with the table in HBM)
-  uint32_t scan_done;    // one-kernel scans: tiles finished so far (the block that finishes last puts it back to zero)
-  int32_t pad[1];
+  int32_t pad[2];
 };
 
 // "Who is the last block?"  Returning atomics on one address are taken one after the other, some 20 ns each, so a kernel of
@@ -141,8 +140,7 @@ struct TiledScan {
   }
 #endif
 };
-// (`done` points at a zeroed uint32 that no other scan in flight uses; it is zero again when the scan has run.)
-TiledScan<uint32_t> scan_u32_tiled(const uint32_t* in, int64_t n, uint32_t* out, void* tmp, uint32_t* done, hipStream_t s);
+TiledScan<uint32_t> scan_u32_tiled(const uint32_t* in, int64_t n, uint32_t* out, void* tmp, Ctl* ctl, hipStream_t s);
 
 void fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
 

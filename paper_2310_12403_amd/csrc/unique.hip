@@ -798,7 +798,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     shift = spare ? 0 : 1;
     const size_t lds = (size_t)n_buckets * sizeof(uint32_t);
     COOP_LAUNCH(K_PART_COUNT, k_part_count, dim3(G), dim3(kPartBlock), lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets, counts);
-    const TiledScan<uint32_t> places = scan_u32_tiled(counts, n_counts, place, tmp, &d_ctl->scan_done, s);
+    const TiledScan<uint32_t> places = scan_u32_tiled(counts, n_counts, place, tmp, d_ctl, s);
     static_assert(kPartMaxBuckets <= 8 * kPartBlock, "a thread of the scatter looks after eight buckets at most");
     if (n_buckets <= 2 * kPartBlock)
       COOP_LAUNCH(K_PART_SCATTER, k_part_scatter<2>, dim3(G), dim3(kPartBlock), 2 * lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets,
