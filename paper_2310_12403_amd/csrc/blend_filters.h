@@ -22,9 +22,10 @@ constexpr uint32_t kThrWiden = 8u;        // thresholds are moved outwards by th
 // Second filter of the blended path: the blend itself in fp32.  A kept edge has n = cw n1 + sw n2 below
 // tau = Phi^-1 of slightly more than (thr + 1) / 2^32; the fp32 estimate of n (two approx_phi_inv_f32, each within
 // kPhiInvF32Gap of the kit's value; kPhiInvF32Allow is allowed for) must therefore lie below the value returned here, rounded up to a float.
-__device__ __forceinline__ float blend_second_threshold(uint32_t thr, double cs /* cw + sw */) {
-  if (thr >= 0x7FFFFFF0u) return __builtin_inff();
-  const double tau = kit_phi_inv_u32(thr + kThrWiden);
+constexpr uint32_t kThrAllPass = 0x7FFFFFF0u;  // k / d near or above 1/2: no useful bound
+__device__ __forceinline__ double blend_tau(uint32_t thr) { return kit_phi_inv_u32(thr + kThrWiden); }  // below 0 for thr < kThrAllPass
+__device__ __forceinline__ float blend_second_threshold(uint32_t thr, double tau /* blend_tau(thr) */, double cs /* cw + sw */) {
+  if (thr >= kThrAllPass) return __builtin_inff();
   const double lim = __builtin_fma(cs, kPhiInvF32Allow, tau * (1.0 - kBlendRelWiden)) + kBlendAbsWiden;
   float t = (float)lim;
   if ((double)t < lim) t = __uint_as_float(t >= 0.0f ? __float_as_uint(t) + 1u : __float_as_uint(t) - 1u);  // next float up
@@ -64,24 +65,23 @@ __device__ __forceinline__ uint32_t blend_widen(uint32_t R) {
 }
 
 // (Its parts, for kernels that have several waves evaluate the thresholds of the same lists; thr < kThrAllPass.)
-constexpr uint32_t kThrAllPass = 0x7FFFFFF0u;  // k / d near or above 1/2: no useful bound
-__device__ __forceinline__ double blend_tau(uint32_t thr) { return kit_phi_inv_u32(thr + kThrWiden) * (1.0 - kBlendRelWiden); }  // < 0
 __device__ __forceinline__ uint32_t blend_a2(double x2) { return blend_widen(kit_phi_to_u32(x2)); }
-__device__ __forceinline__ void blend_strip(double tau_s, double x2, double cw, double sw, uint32_t* a1, uint32_t* b2) {
+__device__ __forceinline__ double blend_x2(double tau, double cw, double sw) { return tau * (1.0 - kBlendRelWiden) * kit_rcp(cw + sw); }
+__device__ __forceinline__ void blend_strip(double tau, double x2, double cw, double sw, uint32_t* a1, uint32_t* b2) {
   *a1 = kit_phi_to_u32(x2 - kStripShift);
   const double x1 = kit_phi_inv_u32(*a1);
   const double cM = cw > sw ? cw : sw, cm = cw > sw ? sw : cw;
-  double y2 = (tau_s - cM * x1) * kit_rcp(cm);
+  double y2 = (tau * (1.0 - kBlendRelWiden) - cM * x1) * kit_rcp(cm);
   y2 = y2 + kBlendRelWiden * (y2 < 0.0 ? -y2 : y2) + 1e-9;
   *b2 = y2 >= 6.0 ? 0xFFFFFFFFu : blend_widen(kit_phi_to_u32(y2));
 }
-__device__ __forceinline__ PreThr blend_first_thresholds(uint32_t thr, double cw, double sw) {
+// (tau = blend_tau(thr), which the second filter's threshold needs as well)
+__device__ __forceinline__ PreThr blend_first_thresholds(uint32_t thr, double tau, double cw, double sw) {
   if (thr >= kThrAllPass) return PreThr{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0.0f};
-  const double tau_s = blend_tau(thr);
-  const double x2 = tau_s * kit_rcp(cw + sw);
+  const double x2 = blend_x2(tau, cw, sw);
   PreThr p;
   p.a2 = blend_a2(x2);
-  blend_strip(tau_s, x2, cw, sw, &p.a1, &p.b2);
+  blend_strip(tau, x2, cw, sw, &p.a1, &p.b2);
   p.keep2 = 0.0f;
   return p;
 }

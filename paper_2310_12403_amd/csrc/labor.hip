@@ -360,10 +360,10 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
       if (f < nf) {
         const uint32_t t = d > ks[f] ? (uint32_t)(((uint64_t)ks[f] << 32) / (uint64_t)d) : kAllThr;
         if (share == 1) {
-          pthr[(int64_t)f * n + i].a2 = t < kThrAllPass ? blend_a2(blend_tau(t) * kit_rcp(cw + sw)) : 0xFFFFFFFFu;
+          pthr[(int64_t)f * n + i].a2 = t < kThrAllPass ? blend_a2(blend_x2(blend_tau(t), cw, sw)) : 0xFFFFFFFFu;
         } else {
           pthr[(int64_t)f * n + i].keep2 = blend_keep_threshold(t, cw + sw);
-          lim2[(int64_t)f * n + i] = blend_second_threshold(t, cw + sw);
+          lim2[(int64_t)f * n + i] = blend_second_threshold(t, blend_tau(t), cw + sw);
         }
       }
   }
@@ -390,16 +390,17 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
         if constexpr (SHARED) {
           uint32_t a1 = 0xFFFFFFFFu, b2 = 0xFFFFFFFFu;
           if (t < kThrAllPass) {
-            const double tau_s = blend_tau(t);
-            blend_strip(tau_s, tau_s * kit_rcp(cw + sw), cw, sw, &a1, &b2);
+            const double tau = blend_tau(t);
+            blend_strip(tau, blend_x2(tau, cw, sw), cw, sw, &a1, &b2);
           }
           pthr[(int64_t)f * n + i].a1 = a1;
           pthr[(int64_t)f * n + i].b2 = b2;
         } else if (pthr) {
-          PreThr pt = blend_first_thresholds(t, cw, sw);
+          const double tau = blend_tau(t);
+          PreThr pt = blend_first_thresholds(t, tau, cw, sw);
           pt.keep2 = blend_keep_threshold(t, cw + sw);
           pthr[(int64_t)f * n + i] = pt;
-          lim2[(int64_t)f * n + i] = blend_second_threshold(t, cw + sw);
+          lim2[(int64_t)f * n + i] = blend_second_threshold(t, tau, cw + sw);
         }
       }
   }

@@ -11,8 +11,9 @@ struct NsBlendThr {
   float lim2;           // the blend in fp32 above this cannot be a candidate
 };
 __device__ __forceinline__ NsBlendThr ns_blend_thresholds(uint32_t bound, double cw, double sw) {
-  const PreThr p = blend_first_thresholds(bound, cw, sw);
-  return NsBlendThr{p.a2, p.a1, p.b2, blend_second_threshold(bound, cw + sw)};
+  const double tau = blend_tau(bound);
+  const PreThr p = blend_first_thresholds(bound, tau, cw, sw);
+  return NsBlendThr{p.a2, p.a1, p.b2, blend_second_threshold(bound, tau, cw + sw)};
 }
 
 // One destination's neighbour list as the fill pass sees it (written by the count pass, so that the fill pass
