@@ -12,6 +12,11 @@
 
 namespace coop {
 
+// The exact blend.  (Not inlined, for kernels that are not about it: see k_ns_redo.)
+static __device__ __attribute__((noinline)) uint32_t blend_exact(uint32_t u1, uint32_t u2, double cw, double sw) {
+  return kit_phi_to_u32(__builtin_fma(cw, kit_phi_inv_u32(u1), sw * kit_phi_inv_u32(u2)));
+}
+
 // Stage-1 passers of one covered layer wait here (per wave, in LDS): the neighbour, its list position, and the lane that has its
 // list's thresholds.  The last kWave places: one per lane that nobody reads.
 constexpr uint32_t kBlendQueue = 3 * kWave;
@@ -65,7 +70,7 @@ struct BlendScan {
     }
     const uint32_t ma = NS ? queue[l].mid_a[slot] : 0u, mb = NS ? queue[l].mid_b[slot] : 0u;
     const uint32_t u1 = uniform(head_a[l], ma, tail_a[l], (uint32_t)e.t), u2 = uniform(head_b[l], mb, tail_b[l], (uint32_t)e.t);
-    sink.take(queue, l, lane < n, e, slot, __builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2)));
+    sink.take(queue, l, lane < n, e, slot, u1, u2, __builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2)));
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }

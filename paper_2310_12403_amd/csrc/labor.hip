@@ -751,7 +751,9 @@ struct CandOut {
 
 // What stage 2 leads to (blend_scan.h): an estimate safely below the threshold is a kept edge (it takes the next free slot of its
 // destination's staging row: by a counter in LDS, where no other wave of the kernel has that destination); one safely above is
-// dropped; the few in between are appended to the candidate buffer of the exact stage (one atomic per call).
+// dropped; the few in between are appended to the candidate buffer of the exact stage (one atomic per call), or, EXACT, evaluated
+// here.
+template <bool EXACT>
 struct LaborSink {
   ScanOut out;
   CandOut cand;
@@ -759,15 +761,23 @@ struct LaborSink {
   uint32_t stage_cap;
   uint32_t first, shift;  // the list of lane s is first + (s >> shift)
   bool owns;              // no other wave of this kernel keeps edges of these lists
-  __device__ __forceinline__ void take(BlendQueue<false>* queue, int l, bool there, const StageEntry& e, uint32_t slot, float est) {
+  const uint32_t* thr_all;  // (EXACT) [NF][n] keep thresholds
+  int64_t n;
+  double cw, sw;
+  __device__ __forceinline__ void take(BlendQueue<false>* queue, int l, bool there, const StageEntry& e, uint32_t slot, uint32_t u1, uint32_t u2, float est) {
     const uint32_t lane = (uint32_t)lane_id();
-    const bool keep = there && est <= queue[l].keep2[slot], maybe = there && !keep && est <= queue[l].lim2[slot];
+    bool keep = there && est <= queue[l].keep2[slot];
+    const bool maybe = there && !keep && est <= queue[l].lim2[slot];
     const uint32_t list = first + (slot >> shift);
+    if constexpr (EXACT) {
+      if (maybe) keep = blend_exact(u1, u2, cw, sw) <= thr_all[(int64_t)l * n + list];
+    }
     if (keep) {
       const uint32_t at = owns ? atomicAdd(&queue[l].own[slot], 1u) : (uint32_t)atomicAdd(&out.cnt[l][list], 1);
       if (at < stage_cap) out.stage[l][(size_t)list * stage_cap + at] = e;
       else if (at == stage_cap) atomicAdd(&ctl->n_overflow, 1);  // exactly one entry sees the row fill up
     }
+    if constexpr (EXACT) return;
     const uint64_t mask = ballot64(maybe);
     if (mask == 0) return;
     const uint32_t sub = blockIdx.x & (kCandSub - 1);
@@ -784,7 +794,7 @@ struct LaborSink {
 // The scan pass with blended variates: destinations, pieces and short lists as in k_labor_scan_plain; a list that a layer keeps whole
 // goes past the stages where it is short.  Bound by vector instructions (some 27 of 64 entries and layer in stage 1, as many for its
 // passers).  A quarter of the papers100M shape: one layer 305 us and 176 now, two layers 315 and 253 (blend_scan.h says what changed).
-template <int NF>
+template <int NF, bool EXACT>
 __global__ __launch_bounds__(kWave, NF == 1 ? 7 : NF == 2 ? 6 : NF == 3 ? 5 : 4) void
 k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg, const uint32_t* __restrict__ thr_all,
                    const PreThr* __restrict__ pthr_all, const float* __restrict__ lim2_all, int64_t n, int each_log2, FusedKeys keys, uint32_t stage_cap,
@@ -794,11 +804,11 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
   const uint32_t lane = (uint32_t)lane_id();
   auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
   auto of64 = [&](int64_t x, int q) { return (int64_t)(((uint64_t)of((uint32_t)((uint64_t)x >> 32), q) << 32) | of((uint32_t)x, q)); };
-  BlendScan<NF, false, LaborSink> S;
+  BlendScan<NF, false, LaborSink<EXACT>> S;
   S.queue = queue;
   S.cwf = (float)keys.cw;
   S.swf = (float)keys.sw;
-  S.sink = LaborSink{out, cand, ctl, stage_cap, 0u, 0u, false};
+  S.sink = LaborSink<EXACT>{out, cand, ctl, stage_cap, 0u, 0u, false, thr_all, n, keys.cw, keys.sw};
 #pragma unroll
   for (int l = 0; l < NF; ++l) S.set_keys(l, keys.K[l]);
   if ((int)blockIdx.x < piece_blocks) {
@@ -1023,9 +1033,11 @@ __global__ __launch_bounds__(kBlock) void k_labor_fill_overflow(const int32_t* _
 static void launch_scan_blend(int nf, unsigned blocks, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, const PreThr* pthr,
                               const float* lim2, int64_t n, int each_log2, const FusedKeys& keys, uint32_t cap, const ScanOut& out, Ctl* ctl,
                               int piece_blocks, const Piece* pieces, const uint32_t* piece_count, uint32_t piece_cap, uint32_t piece_len,
-                              const CandOut& cand) {
+                              const CandOut& cand /* no buffer: the exact blend in the scan */) {
 #define COOP_SCAN_BLEND(NF)                                                                                                                  \
-  COOP_LAUNCH(K_LABOR_COUNT, k_labor_scan_blend<NF>, dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, pthr, lim2, n, each_log2, keys, cap, out, ctl, \
+  if (cand.buf != nullptr) { COOP_SCAN_BLEND_AS(NF, false); } else { COOP_SCAN_BLEND_AS(NF, true); }
+#define COOP_SCAN_BLEND_AS(NF, EXACT)                                                                                                        \
+  COOP_LAUNCH(K_LABOR_COUNT, (k_labor_scan_blend<NF, EXACT>), dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, pthr, lim2, n, each_log2, keys, cap, out, ctl, \
               piece_blocks, pieces, piece_count, piece_cap, piece_len, cand)
   switch (nf) {
     case 1: COOP_SCAN_BLEND(1); break;
@@ -1033,6 +1045,7 @@ static void launch_scan_blend(int nf, unsigned blocks, hipStream_t s, const int3
     case 3: COOP_SCAN_BLEND(3); break;
     default: COOP_SCAN_BLEND(4); break;
   }
+#undef COOP_SCAN_BLEND_AS
 #undef COOP_SCAN_BLEND
 }
 static void launch_scan_plain(int nf, unsigned blocks, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, int64_t n, int each_log2,
@@ -1115,19 +1128,27 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
   // 2,048 entries goes first, whole if it is shorter than two pieces (papers100M-shaped, kappa 16: scan 1.44 -> 1.32 ms;
   // no difference with independent variates).
   const uint32_t split_min = g_split_min != 0 ? (uint32_t)g_split_min : (cx.blend && piece_len >= 2048u ? 2048u : 2u * piece_len);
+  // A call on unaligned indices takes memory for neither the queue nor the candidates of the exact blend (programs sized their
+  // arenas for such calls when every list was read by one wave, an entry at a time): its queue lies in an array of the layer that is
+  // written after the scan, with as many pieces as that holds, and the scan evaluates the exact blend itself.  (A list of 2 million
+  // entries among 20 thousand short ones: 82 us with pieces, 1.9 ms without.)
   uint32_t piece_cap = 0;
   Piece* pieces = nullptr;
+  if (!cx.vec4 && defer) blk->eid = alloc.get<int64_t>(edge_cap, COOP_TAG_OUTPUT);
+  if (alloc.failed) return COOP_E_NOMEM;
   if (piece_len != 0 && n_new > 0) {
     const int64_t by_edges = cx.g->n_edges / piece_len;
     const int64_t long_lists = cx.g->n_edges / (int64_t)split_min + 1;
+    const int64_t most = cx.vec4 ? (int64_t)1 << 30 : defer ? edge_cap : n_dst + 1;
     const int64_t cap64 = by_edges + (n_new < long_lists ? n_new : long_lists) + 1;
-    piece_cap = (uint32_t)(cap64 < ((int64_t)1 << 30) ? cap64 : ((int64_t)1 << 30));
-    pieces = alloc.get<Piece>(piece_cap, COOP_TAG_SCRATCH);
+    piece_cap = (uint32_t)(cap64 < most ? cap64 : most);
+    static_assert(sizeof(Piece) == sizeof(int64_t), "a piece takes the place of an offset or a position");
+    pieces = cx.vec4 ? alloc.get<Piece>(piece_cap, COOP_TAG_SCRATCH) : (Piece*)(defer ? blk->eid : blk->indptr);
     if (alloc.failed) return COOP_E_NOMEM;
   }
   // blended variates: stage 3 works from a buffer of the candidates that the fp32 blend left undecided, a few percent
   // of the k kept edges per destination and layer; k / 2 each is ample (a pass that overflows it is redone with more)
-  const bool queued = cx.blend && n_new > 0;
+  const bool queued = cx.blend && cx.vec4 && n_new > 0;
   int64_t cand_cap = 0;
   uint32_t* cand_count = nullptr;
   if (queued) {
@@ -1297,7 +1318,7 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
   const int64_t m = defer ? edge_cap : cx.h_ctl->total_edges;  // entries of the edge arrays
   blk->n_edges = defer ? -1 : m;
   blk->col_global = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
-  blk->eid = alloc.get<int64_t>(m, COOP_TAG_OUTPUT);
+  if (cx.vec4 || !defer) blk->eid = alloc.get<int64_t>(m, COOP_TAG_OUTPUT);
   blk->col_local = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
 

@@ -259,10 +259,6 @@ __device__ __forceinline__ uint32_t ns_collect_plain(ListReader& L, uint32_t j0,
 
 // The same with c > 0.  The variate of an entry is evaluated exactly only if the integer bounds and then the fp32 blend cannot
 // rule it out; the survivors of the integer bounds are evaluated 64 at a time.  The candidates are in no particular order.
-// (not inlined: see k_ns_redo)
-__device__ __attribute__((noinline)) uint32_t ns_exact_variate(uint32_t u1, uint32_t u2, double cw, double sw) {
-  return kit_phi_to_u32(__builtin_fma(cw, kit_phi_inv_u32(u1), sw * kit_phi_inv_u32(u2)));
-}
 template <bool VEC4>
 __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_indices, int64_t beg, uint32_t d, uint32_t bound,
                                                const NsBlendThr& bt, const VariateParams& vp, uint32_t sigma_a, uint32_t sigma_b,
@@ -292,7 +288,7 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
       j = q->j[lane];
       const uint32_t u1 = keyed_exact<true>(vp.K.Ka, q->u1[lane]), u2 = keyed_exact<true>(vp.K.Kb, q->u2[lane]);
       if (__builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2)) <= bt.lim2) {
-        R = ns_exact_variate(u1, u2, vp.cw, vp.sw);
+        R = blend_exact(u1, u2, vp.cw, vp.sw);
         in = R <= bound;
       }
     }
@@ -694,7 +690,7 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_redo(const int32_t* __restrict_
 struct NsSink {
   StageEntry* rows;  // of the wave's first destination
   uint32_t row_cap, shift;
-  __device__ __forceinline__ void take(BlendQueue<true>* queue, int, bool there, const StageEntry& e, uint32_t slot, float est) {
+  __device__ __forceinline__ void take(BlendQueue<true>* queue, int, bool there, const StageEntry& e, uint32_t slot, uint32_t, uint32_t, float est) {
     if (there && est <= queue->lim2[slot]) {
       const uint32_t at = atomicAdd(&queue->own[slot], 1u);
       if (at < row_cap) rows[(size_t)(slot >> shift) * row_cap + at] = e;
@@ -851,7 +847,7 @@ __device__ __forceinline__ void ns_select_one(int64_t w, uint32_t n, NsSlot* slo
     bool keep = in || und;
     if ((uint32_t)__popcll(und_mask) > need) {  // wave-uniform
       uint32_t R = 0;
-      if (und) R = ns_exact_variate(u1, u2, vp.cw, vp.sw);
+      if (und) R = blend_exact(u1, u2, vp.cw, vp.sw);
       const uint64_t my_key = ((uint64_t)R << 32) | c.j;
       uint32_t rank_u = 0;
       uint64_t rest = und_mask;
@@ -887,7 +883,7 @@ __device__ __forceinline__ void ns_select_one(int64_t w, uint32_t n, NsSlot* slo
     if (i < n) {
       c = row[i];
       const uint32_t u1 = keyed_uniform<true>(vp.K.Ka, (uint32_t)c.t, sigma_a), u2 = keyed_uniform<true>(vp.K.Kb, (uint32_t)c.t, sigma_b);
-      R = ns_exact_variate(u1, u2, vp.cw, vp.sw);
+      R = blend_exact(u1, u2, vp.cw, vp.sw);
       in = R <= g.bound;
     }
     const uint64_t mask = ballot64(in);
@@ -994,7 +990,7 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restri
       bool keep = in || und;
       if (ballot64(choose) != 0) {
         uint32_t R = 0;
-        if (choose) R = ns_exact_variate(u1, u2, vp.cw, vp.sw);
+        if (choose) R = blend_exact(u1, u2, vp.cw, vp.sw);
         const uint32_t rank_u = rank_of(choose ? ((uint64_t)R << 32) | c.j : ~0ull);
         if (choose) keep = rank_u < k - n_in;
       }

@@ -992,6 +992,57 @@ def test_a_program_sizes_its_arena_once(P, uneven, call):
         P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
 
 
+@pytest.fixture(scope="module")
+def unaligned(P):
+    """150 thousand vertices, lists of 0 to 8 entries and eight of 2,000 to 65,000, the indices 4 bytes behind a 16-byte line."""
+    n = 150001
+    deg = np.arange(n) % 9
+    deg[::20011] = 2000 + 9000 * np.arange(8)
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]).astype(np.int64))
+    g = G(P, indptr, torch.from_numpy(((np.arange(deg.sum()) * 7919) % n).astype(np.int32)))
+    base = torch.empty(len(g.indices_h) + 1, dtype=torch.int32, device="cuda")
+    base[1:] = g.indices_d
+    g.graph = P.coop_graph_load(g.indptr_d, base[1:], P.COOP_VALIDATE)
+    return g
+
+
+# as ARENAS, of arenas that served the call when LABOR-0 read such lists an entry at a time: no queue of pieces, no candidates
+UNALIGNED_ARENAS = {
+    (R.LABOR0, (10, 10), 1, 1, 30): 320512, (R.LABOR0, (10, 10), 4, 1, 30): 321536, (R.LABOR0, (10, 10), 1, 0, 30): 123904,
+    (R.LABOR0, (3, 2, 4), 4, 0, 30): 140288, (R.LABOR0, (10, 10), 1, 1, 20000): 92836864, (R.LABOR0, (10, 10), 4, 1, 20000): 95020288,
+    (R.LABOR0, (3, 2), 1, 0, 90001): 77564928, (R.LABOR0, (3, 2), 4, 0, 90001): 81994496, (R.LABOR0, (70,), 1, 1, 20000): 12625664,
+    (R.LABOR0, (70, 2), 4, 1, 20000): 70227968, (R.NS, (10, 10), 1, 1, 20000): 37120000, (R.NS, (10, 10), 4, 1, 20000): 95287808,
+}
+
+
+@pytest.mark.parametrize("call", list(UNALIGNED_ARENAS))
+def test_a_program_with_unaligned_indices_sizes_its_arena_once(P, unaligned, call):
+    sampler, fanouts, kappa, defer, n_seeds = call
+    P.coop_tune(P.COOP_TUNE_DEFER_SIZES, defer)
+    try:
+        compare(P, unaligned, np.arange(n_seeds), fanouts, sampler, it=5, kappa=kappa, seed=3, arena=P.Arena(UNALIGNED_ARENAS[call] + 256))
+    finally:
+        P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
+
+
+@pytest.mark.parametrize("kappa", [1, 4])
+def test_more_pieces_than_an_unaligned_call_has_room_for(P, unaligned, kappa):
+    """Their queue lies in an array of the layer that is not written yet: lists cut into more pieces than that holds (the indptr,
+    an entry per destination, where the sizes are read back at once) stay whole, the others are cut."""
+    hubs = np.arange(0, unaligned.n, 20011)
+    seeds = np.concatenate([hubs, np.arange(1, 400)])
+    try:
+        for defer in (1, 0, 2):
+            P.coop_tune(P.COOP_TUNE_DEFER_SIZES, defer)
+            for piece_len in (256, 1024, 0):
+                P.coop_tune(P.COOP_TUNE_PIECE_LEN, piece_len)
+                compare(P, unaligned, seeds, (10, 3), R.LABOR0, it=5, kappa=kappa, seed=piece_len)
+                compare(P, unaligned, hubs[2:3], (25,), R.LABOR0, it=5, kappa=kappa, seed=piece_len)
+    finally:
+        P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
+        P.coop_tune(P.COOP_TUNE_PIECE_LEN, 4096)
+
+
 @pytest.mark.parametrize("n_seeds", [262143, 262144, 262145, 270336, 300000])
 @pytest.mark.parametrize("defer", [1, 0])
 def test_partition_with_few_edges_behind_many_seeds(P, n_seeds, defer):
