@@ -416,21 +416,89 @@ __device__ __forceinline__ uint32_t ns_rank_of(uint32_t n_c, const NsSlot* slot,
   for (uint32_t q = 0; q < n_c; ++q) rank += slot_key(slot + q) < my_key;
   return rank;
 }
-__device__ __forceinline__ void ns_rank_write_many(uint32_t n_c, uint32_t k, NsSlot* slot, int64_t o, int64_t beg, int32_t* __restrict__ col_global,
-                                                   int64_t* __restrict__ eid) {
+// More candidates than lanes (all with a variate <= bound).  The border of the k smallest is bisected, between 0 and `bound` and
+// until exactly k lie on its side: some log2(n_c) + 1 counts, an LDS read and a comparison per 64 candidates, in the place of a rank
+// for every candidate.  Of equal variates at the border the first in the list are kept.  ORDERED: the candidates stand in list order
+// (c = 0), so a kept one's place is the number of kept ones in front of it; otherwise the k kept ones move to the front and are
+// ranked by position.
+// (Steps over 90 thousand lists of 30 to 1,500 entries, fanouts 60 and 200: 447 and 3,512 us with ranks, 217 and 515; c > 0 684 and
+// 4,431, 412 and 1,196.  30 such lists with fanout 1,000: 2,461 and 73, c > 0 2,792 and 410.)
+template <bool ORDERED>
+__device__ __forceinline__ void ns_rank_write_many(uint32_t n_c, uint32_t k, uint32_t bound, NsSlot* slot, int64_t o, int64_t beg,
+                                                   int32_t* __restrict__ col_global, int64_t* __restrict__ eid) {
   const uint32_t lane = (uint32_t)lane_id();
-  for (uint32_t i = lane; i < n_c; i += kWave) {
-    slot[i].keep = ns_rank_of(n_c, slot, slot_key(slot + i)) < k;
+  auto settle = [] {
+    __builtin_amdgcn_wave_barrier();
+    __threadfence_block();
+  };
+  auto upto = [&](uint32_t border) {  // (slots up to the next multiple of 64 are there)
+    uint32_t n = 0;
+#pragma unroll 4
+    for (uint32_t base = 0; base < n_c; base += kWave) n += (uint32_t)__popcll(compare_mask(slot[base + lane].r <= border) & low_lanes(n_c - base));
+    return n;
+  };
+  constexpr uint32_t kAll = 0xFFFFFFFFu;
+  uint32_t lo = 0, hi = bound, border = bound, need = kAll;  // of the candidates at the border `need` are kept
+  while (n_c != k) {  // #{r <= hi} >= k
+    border = lo + (hi - lo) / 2;
+    const uint32_t n = upto(border);
+    if (n == k) break;
+    if (lo == hi) {
+      need = k - (border == 0 ? 0u : upto(border - 1));
+      break;
+    }
+    if (n < k) lo = border + 1;
+    else hi = border;
   }
-  __builtin_amdgcn_wave_barrier();
-  __threadfence_block();
-  for (uint32_t i = lane; i < n_c; i += kWave) {
-    if (!slot[i].keep) continue;
+  if (!ORDERED && need != kAll) {
+    for (uint32_t i = lane; i < n_c; i += kWave) {
+      uint32_t rank = 0;
+      if (slot[i].r == border)
+        for (uint32_t q = 0; q < n_c; ++q) rank += slot[q].r == border && slot[q].j < slot[i].j;
+      slot[i].keep = rank < need;
+    }
+    settle();
+  }
+  uint32_t placed = 0, ties = 0;
+  for (uint32_t base = 0; base < n_c; base += kWave) {
+    const uint32_t i = base + lane;
+    const NsSlot c = slot[i];
+    bool keep = i < n_c && c.r <= border;
+    if (need != kAll && ORDERED) {
+      const uint64_t m = ballot64(keep && c.r == border);
+      if (c.r == border) keep = keep && ties + lanes_below(m) < need;
+      ties += (uint32_t)__popcll(m);
+    } else if (need != kAll && c.r == border) {
+      keep = keep && c.keep != 0;
+    }
+    const uint64_t m = ballot64(keep);
+    const uint32_t place = placed + lanes_below(m);
+    placed += (uint32_t)__popcll(m);
+    if (ORDERED) {
+      if (keep) {
+        (col_global + o)[place] = c.t;
+        (eid + o)[place] = beg + c.j;
+      }
+    } else {
+      settle();
+      if (keep) {  // (place <= i: that slot was read in this round or before)
+        slot[place].j = c.j;
+        slot[place].t = c.t;
+      }
+      settle();
+    }
+  }
+  if (ORDERED) return;
+  for (uint32_t base = 0; base < k; base += kWave) {
+    const uint32_t i = base + lane;
     const uint32_t my_j = slot[i].j;
     uint32_t place = 0;
-    for (uint32_t q = 0; q < n_c; ++q) place += slot[q].keep && slot[q].j < my_j;
-    col_global[o + place] = slot[i].t;
-    eid[o + place] = beg + my_j;
+#pragma unroll 4
+    for (uint32_t q = 0; q < k; ++q) place += slot[q].j < my_j;
+    if (i < k) {
+      (col_global + o)[place] = slot[i].t;
+      (eid + o)[place] = beg + my_j;
+    }
   }
 }
 // The lanes of the k smallest r among those of `has` (popcount > k >= 1), or 0 where equal variates stand across the border.  The
@@ -448,7 +516,7 @@ __device__ __forceinline__ uint64_t ns_smallest(uint32_t r, uint64_t has, uint32
   }
 }
 // (after ns_collect_plain: the candidates stand in list order, and their variates are evaluated here)
-__device__ __forceinline__ void ns_rank_write_plain(uint32_t n_c, uint32_t k, const NsKeys& K, NsSlot* slot, int64_t o, int64_t beg, int32_t* __restrict__ col_global,
+__device__ __forceinline__ void ns_rank_write_plain(uint32_t n_c, uint32_t k, uint32_t bound, const NsKeys& K, NsSlot* slot, int64_t o, int64_t beg, int32_t* __restrict__ col_global,
                                                     int64_t* __restrict__ eid) {
   const uint32_t lane = (uint32_t)lane_id();
   __builtin_amdgcn_wave_barrier();
@@ -477,16 +545,16 @@ __device__ __forceinline__ void ns_rank_write_plain(uint32_t n_c, uint32_t k, co
   for (uint32_t i = lane; i < n_c; i += kWave) slot[i].r = ns_uniform(K, (uint32_t)slot[i].t);
   __builtin_amdgcn_wave_barrier();
   __threadfence_block();
-  ns_rank_write_many(n_c, k, slot, o, beg, col_global, eid);
+  ns_rank_write_many<true>(n_c, k, bound, slot, o, beg, col_global, eid);
 }
-__device__ __forceinline__ void ns_rank_write(uint32_t n_c, uint32_t k, NsSlot* slot, int64_t o, int64_t beg, int32_t* __restrict__ col_global,
+__device__ __forceinline__ void ns_rank_write(uint32_t n_c, uint32_t k, uint32_t bound, NsSlot* slot, int64_t o, int64_t beg, int32_t* __restrict__ col_global,
                                               int64_t* __restrict__ eid) {
   const uint32_t lane = (uint32_t)lane_id();
   if (n_c <= (uint32_t)kWave) ns_pad(n_c, slot);
   __builtin_amdgcn_wave_barrier();
   __threadfence_block();
   if (n_c > (uint32_t)kWave) {
-    ns_rank_write_many(n_c, k, slot, o, beg, col_global, eid);
+    ns_rank_write_many<false>(n_c, k, bound, slot, o, beg, col_global, eid);
     return;
   }
   const bool has = lane < n_c;
@@ -596,6 +664,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
     n_c = ns_collect_plain(L, j0, bound, K, slot, cap, n_c);
     const uint32_t found = n_c;
     const int64_t o_done = o_this, beg_done = beg;
+    const uint32_t bound_done = bound;
     bool select = false;
     if (d - j0 > kStretch) {  // the list's next stretch
       j0 += kStretch;
@@ -615,7 +684,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
       hi = 0xFFFFFFFFu;
     }
     L = ListReader(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
-    if (select) ns_rank_write_plain(found, k, K, slot, o_done, beg_done, col_global, eid);
+    if (select) ns_rank_write_plain(found, k, bound_done, K, slot, o_done, beg_done, col_global, eid);
     if (todo == 0) break;
     __builtin_amdgcn_wave_barrier();
   }
@@ -647,7 +716,7 @@ __device__ __forceinline__ void ns_redo_one(int64_t w, int wib, uint32_t* lds_wo
     if (lane_id() == 0) atomicOr(&ctl->err_capacity, 1);
     return;
   }
-  ns_rank_write(n_c, k, slot, o, g.beg, col_global, eid);
+  ns_rank_write(n_c, k, bound, slot, o, g.beg, col_global, eid);
 }
 
 // c > 0: the destinations that the two kernels below leave over.  A wave looks at 2^lists_log2 marks at once.  (Six waves per
@@ -895,7 +964,7 @@ __device__ __forceinline__ void ns_select_one(int64_t w, uint32_t n, NsSlot* slo
     if (lane == 0) n_cand[w] = kNsRedo;
     return;
   }
-  ns_rank_write(n_c, k, slot, eptr[w], g.beg, col_global, eid);
+  ns_rank_write(n_c, k, g.bound, slot, eptr[w], g.beg, col_global, eid);
 }
 
 
@@ -1181,7 +1250,9 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
         // Lanes per destination in the selection: as many as hold the candidates of most (a tenth more pass the filters than are
         // expected; 250 thousand destinations with 15 expected: 112 us with 64 lanes and a wave for each, 49 with 32 and eight a wave).
         const int group_log2 = target <= 10 ? 4 : target <= 24 ? 5 : 6;
-        const int select_log2 = each_log2 > 6 - group_log2 ? each_log2 : 6 - group_log2;
+        // (A destination to itself where more candidates than lanes are expected: some 10 us each, one after the other.  Fanout 200, 90
+        // thousand lists, twelve of them long: 3.51 ms with eight a wave, 3.41.)
+        const int select_log2 = target > (uint32_t)kWave ? 0 : each_log2 > 6 - group_log2 ? each_log2 : 6 - group_log2;
         uint32_t* n_cand_b = n_cand + b;
         int lists_log2 = 0;
         while (lists_log2 < 6 && (n >> (lists_log2 + 1)) >= kNsRedoWaves) ++lists_log2;

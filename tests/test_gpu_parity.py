@@ -1190,6 +1190,27 @@ def test_ns_lists_around_the_edges_of_groups(P, aligned, kappa):
         compare(P, g, np.arange(size), (k,), R.NS, it=kappa - 1, kappa=kappa, seed=size)
 
 
+@pytest.mark.parametrize("kappa", [1, 4])
+def test_ns_selection_of_more_candidates_than_lanes(P, kappa):
+    """Fanouts that leave one, two, four or many rounds of 64 candidates to select from: lists just longer than the fanout and
+    much longer ones, with distinct neighbours and with neighbours that repeat, so that equal variates stand across the border of
+    the k smallest (of which the first in the list are kept), one destination at a time and tens of thousands."""
+    n = 40000
+    rng = np.random.default_rng(31)
+    deg = rng.integers(0, 30, n)
+    special = np.arange(5, n, 40)
+    deg[special] = np.array([61, 65, 127, 129, 257, 400, 700, 1030, 1300, 3000])[np.arange(len(special)) % 10]
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    indices = rng.integers(0, n, int(indptr[-1])).astype(np.int32)
+    for v in special[(np.arange(len(special)) // 10) % 2 == 1]:  # a third as many neighbours as entries
+        indices[indptr[v]:indptr[v + 1]] = 7 * v % 30000 + rng.integers(0, max(deg[v] // 3, 1), deg[v])
+    g = G(P, torch.from_numpy(indptr), torch.from_numpy(indices))
+    for k in (40, 60, 64, 100, 126, 250, 511, 700, 1024):
+        compare(P, g, special, (k,), R.NS, it=kappa - 1, kappa=kappa, seed=k)
+    compare(P, g, special[6:8], (300, 2), R.NS, it=kappa - 1, kappa=kappa, seed=1)
+    compare(P, g, np.arange(35000), (60,), R.NS, it=kappa - 1, kappa=kappa, seed=2)
+
+
 def test_ns_count_in_wide_blocks(P):
     """From 262,144 destinations on the counting blocks take 2,048 each: a number of destinations that is no multiple of that,
     with long lists (queued from 64 entries on) at both ends of blocks and with lists without entries."""
