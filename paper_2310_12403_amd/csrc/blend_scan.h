@@ -137,7 +137,7 @@ struct BlendScan {
   }
 
   // Stage 1 on a list (or a stretch of it that starts at list position j0) whose thresholds lane `slot` has.
-  __device__ __forceinline__ void collect(ListReader& L, uint32_t j0, uint32_t slot, const uint32_t (&a1)[NF], const uint32_t (&a2)[NF],
+  __device__ __forceinline__ void collect(ListReader<>& L, uint32_t j0, uint32_t slot, const uint32_t (&a1)[NF], const uint32_t (&a2)[NF],
                                           const uint32_t (&b2)[NF]) {
     const uint32_t lane = (uint32_t)lane_id();
     for (uint32_t g0 = 0; g0 < L.n_groups; g0 += kReaderGroups) {

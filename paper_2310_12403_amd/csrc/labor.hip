@@ -514,7 +514,7 @@ __device__ __forceinline__ uint32_t labor_uniform(uint32_t head, uint32_t tail, 
 // One pass over a list (or a stretch of it that starts at list position j0) for NF layers: neighbours with R_t <= thr[l] go to
 // layer l's slots behind the n[l] that are there; those behind kKeptSlots are counted, not stored.
 template <int NF>
-__device__ __forceinline__ void labor_collect(ListReader& L, uint32_t j0, const uint32_t (&thr)[NF], const PlainKeys<NF>& K, KeptSlots* slots,
+__device__ __forceinline__ void labor_collect(ListReader<>& L, uint32_t j0, const uint32_t (&thr)[NF], const PlainKeys<NF>& K, KeptSlots* slots,
                                               uint32_t (&n)[NF]) {
   const uint32_t lane = (uint32_t)lane_id();
   const uint32_t idle = kKeptSlots + lane;
@@ -628,7 +628,7 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
       uint32_t thr[NF], kept[NF];
 #pragma unroll
       for (int l = 0; l < NF; ++l) { thr[l] = of(thr_all[(int64_t)l * n + list], 0); kept[l] = 0; }
-      ListReader L(g_indices + beg + j0, len);
+      ListReader<> L(g_indices + beg + j0, len);
       labor_collect<NF>(L, (uint32_t)j0, thr, K, slots, kept);
       settle();
 #pragma unroll
@@ -687,11 +687,11 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
     int64_t beg = of64(g.beg, at);
 #pragma unroll
     for (int l = 0; l < NF; ++l) { thr[l] = of(my_thr[l], at); kept[l] = 0; }
-    for (ListReader L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+    for (ListReader<> L(g_indices + beg, d < kStretch ? d : kStretch);;) {
       labor_collect<NF>(L, j0, thr, K, slots, kept);
       if (d - j0 > kStretch) {  // the list's next stretch
         j0 += kStretch;
-        L = ListReader(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+        L = ListReader<>(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
         continue;
       }
       const int done = at;
@@ -700,7 +700,7 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
       d = todo != 0 ? of(g.d, at) : 0u;
       beg = of64(g.beg, at);
       j0 = 0;
-      L = ListReader(g_indices + beg, d < kStretch ? d : kStretch);
+      L = ListReader<>(g_indices + beg, d < kStretch ? d : kStretch);
       settle();
 #pragma unroll
       for (int l = 0; l < NF; ++l) {
@@ -834,7 +834,7 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
         queue[l].keep2[lane] = pt.keep2;
         queue[l].lim2[lane] = lim2_all[(int64_t)l * n + list];
       }
-      ListReader L(g_indices + beg + j0, len);
+      ListReader<> L(g_indices + beg + j0, len);
       S.collect(L, (uint32_t)j0, 0u, a1, a2, b2);
       S.flush();
     }
@@ -897,7 +897,7 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
       for (int l = 0; l < NF; ++l) { a1[l] = of(my_a1[l], at); a2[l] = of(my_a2[l], at); b2[l] = of(my_b2[l], at); }
     };
     thresholds();
-    for (ListReader L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+    for (ListReader<> L(g_indices + beg, d < kStretch ? d : kStretch);;) {
       S.collect(L, j0, (uint32_t)at, a1, a2, b2);
       if (d - j0 > kStretch) {  // the list's next stretch
         j0 += kStretch;
@@ -910,7 +910,7 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
         j0 = 0;
         thresholds();
       }
-      L = ListReader(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+      L = ListReader<>(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
     }
   }
   S.flush();

@@ -21,14 +21,15 @@ struct ListLoads {
 };
 
 // The entries of a list (or of a stretch of it): whole groups of 256, and the rest 64 at a time.  Everything that fits is requested
-// at once; a loop over the groups asks for group g + kReaderGroups when it is through with group g.
+// at once; a loop over the groups asks for group g + GROUPS when it is through with group g.
 constexpr uint32_t kGroup = kWave * 4;  // entries of a 16-byte load by every lane
-constexpr uint32_t kReaderGroups = 4;     // ... of which so many are in flight
+constexpr uint32_t kReaderGroups = 4;   // ... of which so many are in flight
 constexpr uint32_t kStretch = 1u << 28;  // entries that a descriptor's offsets reach
+template <uint32_t GROUPS = kReaderGroups>
 struct ListReader {
   ListLoads in;
   uint32_t n, n_groups;
-  u32x4 ring[kReaderGroups];
+  u32x4 ring[GROUPS];
   uint32_t rest[4];
   __device__ __forceinline__ ListReader(const int32_t* list, uint32_t entries) : in(list, entries), n(entries), n_groups(entries / kGroup) {
     // (no load for what is not there: 16 bytes per lane cost a CU 16 clocks, also where every lane is behind the end)
@@ -39,7 +40,7 @@ struct ListReader {
       if (tail + q * kWave < n) rest[q] = in.entry(tail + q * kWave);
     }
 #pragma unroll
-    for (uint32_t q = 0; q < kReaderGroups; ++q) {
+    for (uint32_t q = 0; q < GROUPS; ++q) {
       ring[q] = u32x4{any_value(), any_value(), any_value(), any_value()};
       if (q < n_groups) ring[q] = in.group(q);
     }

@@ -169,6 +169,10 @@ constexpr int64_t kNsFillWaves = 16384;  // k_ns_fill's waves take up to eight d
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 constexpr int kNsGroups = 4;  // 16-byte groups per lane and step of the fast traversal
+// Groups of a list in flight in k_ns_fill: as many as 64 registers hold.  A list of 2 million entries is one wave's, waiting for
+// memory, and a group is requested when the one in its place has been looked at: 1.81 ms with four in flight, 1.72 with five, 1.64
+// with six, 1.58 with seven; short lists the same with any of them.
+constexpr uint32_t kFillGroups = 7;
 
 // Stage-1 passers of the blended path wait here (per wave, in LDS) until 64 of them can be evaluated together.
 constexpr int kNsQueueCap = 2 * kWave;
@@ -197,15 +201,15 @@ __device__ __forceinline__ uint64_t slot_key(const NsSlot* c) { return ((uint64_
 // is left, fewer than 256, is read 64 at a time, so that neither ragged ends nor half a group of idle lanes are paid for;
 // the test leaves only masks in scalar registers; a group's masks give every lane the place of its first candidate, a
 // lane's next one is a slot further, and lanes without one write to a slot of their own that nobody reads, so that there is no
-// branch per entry.  The variate is not kept but evaluated again for the few dozen candidates.  Four groups are
-// in flight, each requested as soon as its registers are free.
-__device__ __forceinline__ uint32_t ns_collect_plain(ListReader& L, uint32_t j0, uint32_t bound, const NsKeys& K, NsSlot* __restrict__ slot, uint32_t cap,
+// branch per entry.  The variate is not kept but evaluated again for the few dozen candidates.  kFillGroups
+// groups are in flight, each requested as soon as its registers are free.
+__device__ __forceinline__ uint32_t ns_collect_plain(ListReader<kFillGroups>& L, uint32_t j0, uint32_t bound, const NsKeys& K, NsSlot* __restrict__ slot, uint32_t cap,
                                                      uint32_t n_c) {
   const uint32_t lane = (uint32_t)lane_id();
   const uint32_t idle = cap + lane;  // (the slots behind the candidates')
-  for (uint32_t g0 = 0; g0 < L.n_groups; g0 += kReaderGroups) {
+  for (uint32_t g0 = 0; g0 < L.n_groups; g0 += kFillGroups) {
 #pragma unroll
-    for (uint32_t q = 0; q < kReaderGroups; ++q) {
+    for (uint32_t q = 0; q < kFillGroups; ++q) {
       const uint32_t g = g0 + q;
       if (g >= L.n_groups) break;
       uint64_t m[4];
@@ -238,7 +242,7 @@ __device__ __forceinline__ uint32_t ns_collect_plain(ListReader& L, uint32_t j0,
         }
         n_c = (uint32_t)__builtin_amdgcn_readlane((int)to, kWave - 1);
       }
-      if (g + kReaderGroups < L.n_groups) L.ring[q] = L.in.group(g + kReaderGroups);
+      if (g + kFillGroups < L.n_groups) L.ring[q] = L.in.group(g + kFillGroups);
     }
   }
   const uint32_t tail = L.n & ~(kGroup - 1);
@@ -659,7 +663,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
   uint32_t lo = 0, hi = 0xFFFFFFFFu, attempt = 0;  // bisection bracket on the bound, used only after a failed pass
   uint32_t j0 = 0, n_c = 0;                        // entries looked at in earlier stretches of the list, candidates so far
   const uint32_t head = vector_copy(keys.Ka[4]), tail = vector_copy(keys.Ka[3]);
-  for (ListReader L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+  for (ListReader<kFillGroups> L(g_indices + beg, d < kStretch ? d : kStretch);;) {
     const NsKeys K{head, vector_copy(mid), tail};
     n_c = ns_collect_plain(L, j0, bound, K, slot, cap, n_c);
     const uint32_t found = n_c;
@@ -683,7 +687,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
       lo = j0 = n_c = attempt = 0;
       hi = 0xFFFFFFFFu;
     }
-    L = ListReader(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+    L = ListReader<kFillGroups>(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
     if (select) ns_rank_write_plain(found, k, bound_done, K, slot, o_done, beg_done, col_global, eid);
     if (todo == 0) break;
     __builtin_amdgcn_wave_barrier();
@@ -847,7 +851,7 @@ __global__ __launch_bounds__(kWave, 7) void k_ns_collect(const int32_t* __restri
       S.mid_b = vector_copy(of(mid_b, at));
     };
     take();
-    for (ListReader L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+    for (ListReader<> L(g_indices + beg, d < kStretch ? d : kStretch);;) {
       S.collect(L, j0, (uint32_t)at, a1, a2, b2);
       if (d - j0 > kStretch) {  // the list's next stretch
         j0 += kStretch;
@@ -860,7 +864,7 @@ __global__ __launch_bounds__(kWave, 7) void k_ns_collect(const int32_t* __restri
         j0 = 0;
         take();
       }
-      L = ListReader(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+      L = ListReader<>(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
     }
   }
   S.flush();

@@ -1190,6 +1190,22 @@ def test_ns_lists_around_the_edges_of_groups(P, aligned, kappa):
         compare(P, g, np.arange(size), (k,), R.NS, it=kappa - 1, kappa=kappa, seed=size)
 
 
+@pytest.mark.parametrize("size", [300, 40000])
+def test_ns_lists_around_the_groups_in_flight(P, size):
+    """Lists of one to three times as many groups of 256 entries as are in flight, one entry less and one more, with and without a
+    rest, a destination a wave and several."""
+    n = 40000
+    rng = np.random.default_rng(17)
+    deg = rng.integers(0, 12, n)
+    at = np.arange(1, n, 131)
+    deg[at] = np.array([256 * q + r for q in (5, 6, 7, 8, 13, 14, 15, 21) for r in (-1, 0, 1, 100, 255)])[np.arange(len(at)) % 40]
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    g = G(P, torch.from_numpy(indptr), torch.from_numpy(rng.integers(0, n, int(indptr[-1])).astype(np.int32)))
+    seeds = at[:size] if size < 1000 else np.arange(size)
+    for k in (3, 10, 70):
+        compare(P, g, seeds, (k,), R.NS, seed=k)
+
+
 @pytest.mark.parametrize("kappa", [1, 4])
 def test_ns_selection_of_more_candidates_than_lanes(P, kappa):
     """Fanouts that leave one, two, four or many rounds of 64 candidates to select from: lists just longer than the fanout and
