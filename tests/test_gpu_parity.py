@@ -683,6 +683,17 @@ def test_random_walk_sampler_medium_and_degenerate(P, tiny, medium):
     assert all(torch.equal(x, y.col_global) for x, y in zip(first, b))
 
 
+@pytest.mark.parametrize("size", [1, 4095, 4096, 4097, 8200])
+def test_random_walks_with_fanouts_around_sixty_four(P, medium, size):
+    """Up to 64 entries a destination are moved by eight lanes, more by a block: one destination, tiles of 4,096 offsets with one
+    less and one more, and rows of any length up to the fanout."""
+    seeds = np.random.default_rng(size).permutation(medium.n)[:size]
+    for fanout in (64, 65, 110):
+        compare_rw(P, medium, seeds, (fanout,), 2, 60, 0.3, it=fanout, seed=size)
+    if size < 4096:
+        compare_rw(P, medium, seeds[:40], (300,), 3, 120, 0.1, seed=size)
+
+
 @pytest.mark.parametrize("o,a,p", [(33, 32, 0.5), (3, 600, 0.3), (1500, 1, 0.0), (40, 40, 0.9)])
 def test_random_walks_with_more_than_1024_steps(P, tiny, medium, o, a, p):
     """App. A.1.3 puts no bound on the number of walks or their length.  Above 1,024 steps per destination the visit
