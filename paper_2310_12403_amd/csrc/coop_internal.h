@@ -188,8 +188,9 @@ struct UniqueWork {
   int path = 0;
   Publish pub{};
   int64_t n_new = 0;
-  uint64_t* clear = nullptr;         // words that must be zero before `launch`; whoever clears them on the way sets this to null
+  uint64_t* clear = nullptr;         // words that a kernel in front of `launch` may set to zero; whoever does sets this to null, ...
   int64_t n_clear = 0;
+  bool bits = false;                 // ... and then the first positions are marked in them as they are found
 };
 // prepare: decides how the list is deduplicated and allocates the words of new-vertex bits.
 int unique_prepare(int64_t n_dst, int64_t m, UniqueWork* w, Alloc& alloc);

@@ -145,6 +145,8 @@ constexpr int64_t kFilterPairs = 1024;                  // most entries of a buc
 // 256 to 270 of them on ordinary lists of 1,500 to 2,048 entries, one more than it can (15 us in the place of 12)
 constexpr int kFilterLeastLog2 = 2;
 constexpr int64_t kFilterMax = 262144;                  // 256 buckets at most: one per CU
+constexpr int64_t kShortMax = 65536;                    // entries up to which the kernel also marks the new vertices (k_uniq_relabel_short)
+constexpr int kShortWords = (int)(kShortMax / 64) + 1;
 __device__ __forceinline__ uint32_t filter_hash(uint32_t key) { return key * 0x9E3779B9u; }
 
 __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
@@ -155,17 +157,22 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
   __shared__ uint32_t noted[kFilterBlock / kWave][kFilterList];
   __shared__ BucketState st;
   __shared__ uint32_t s_overflow;
+  __shared__ unsigned long long word[kShortWords];  // the block's bits
   if (m_dev != nullptr && *m_dev < m) m = *m_dev;
   const uint32_t n = (uint32_t)(n_dst + m);  // (below kFilterMax)
   const uint32_t nd = (uint32_t)n_dst;
+  const uint32_t n_words = bits != nullptr ? ((n + 63u) >> 6) - (nd >> 6) : 0u;  // (at most kShortWords)
+  for (uint32_t i = threadIdx.x; i < n_words; i += kFilterBlock) word[i] = 0;
   for (uint32_t i = threadIdx.x; i < kFilterSlots; i += kFilterBlock) table[i] = kEmptySlot;
   if (threadIdx.x == 0) { st = BucketState{0u, 0u, 0u}; s_overflow = 0; }
   __syncthreads();
   auto key_at = [&](uint32_t i) { return (uint32_t)(i < nd ? dst[i] : col[i - nd]); };
-  // the first position of edge position i; the edge whose position it is gets its bit (the words are clear when the kernel starts)
+  // The first position of edge position i; the edge whose position it is gets its bit.  (The words are clear when the kernel starts.
+  // A block's bits are gathered in LDS: an atomic in L2 for each of them, on a few cache lines, made the kernel 4 to 8 us longer
+  // where a pass that collects the words takes 5.)
   auto found = [&](uint32_t i, uint32_t at) {
     first[i - nd] = at;
-    if (bits != nullptr && at == i) atomicOr(&bits[(i >> 6) - (nd >> 6)], 1ull << (i & 63u));
+    if (bits != nullptr && at == i) atomicOr(&word[(i >> 6) - (nd >> 6)], 1ull << (i & 63u));
   };
   const uint32_t width = 1u << (32 - log2_buckets), low = blockIdx.x * width;  // the bucket's hashes: low .. low + width - 1 (log2_buckets >= 1)
   auto slot = [&](uint32_t h) { return (h << log2_buckets) >> 20; };           // the hash bits behind those of the bucket
@@ -279,6 +286,11 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
     __syncthreads();
     if (st.full == 0)
       each(col, n - nd, [&](uint32_t i, uint32_t key) { found(nd + i, bucket_find(table, kFilterSlots, slot(filter_hash(key)), key)); });
+  }
+  if (n_words != 0) {
+    __syncthreads();
+    for (uint32_t i = threadIdx.x - kWave; threadIdx.x >= kWave && i < n_words; i += kFilterBlock - kWave)
+      if (word[i] != 0) atomicOr(&bits[i], word[i]);
   }
   if (threadIdx.x == 0) bucket_done(ctl, st, n_dst, pub);
 }
@@ -700,11 +712,9 @@ __global__ __launch_bounds__(kBlock) void k_uniq_relabel(const int32_t* __restri
 }
 
 // The same for the shortest lists, straight from the bits that k_uniq_filter set: every block counts them all, 64 to a word, and keeps
-// words and ranks in LDS.  A launch of 5 to 6 us less than with k_uniq_collect in between; what the bits cost the filter, an atomic
-// per new vertex, grows with the list (6 to 8 us at 180 thousand entries).
+// words and ranks in LDS.  A launch less than with k_uniq_collect in between: calls over 300 to 60 thousand entries 1 to 4 us
+// shorter (44.9 and 45.7 us, 51.8 and 55.2), below 300 none.
 constexpr int kShortBlock = 1024, kShortEach = 4;
-constexpr int64_t kShortMax = 65536;  // entries of the whole list
-constexpr int kShortWords = (int)(kShortMax / 64) + 1;
 __global__ __launch_bounds__(kShortBlock) void k_uniq_relabel_short(const int32_t* __restrict__ dst, const int32_t* __restrict__ col, int64_t m,
                                                                     const int64_t* __restrict__ m_dev, int64_t n_dst,
                                                                     const unsigned long long* __restrict__ bits, int32_t* __restrict__ src,
@@ -781,7 +791,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     int log2_buckets = kFilterLeastLog2;
     while (((int64_t)kFilterPairs << log2_buckets) < n_all) ++log2_buckets;
     COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_filter, dim3(1u << log2_buckets), dim3(kFilterBlock), 0, s, dst, n_dst, col_global, m, m_dev, log2_buckets,
-                first, n_all <= kShortMax ? (unsigned long long*)w->words : (unsigned long long*)nullptr, d_ctl, w->pub);
+                first, w->bits ? (unsigned long long*)w->words : (unsigned long long*)nullptr, d_ctl, w->pub);
   } else if (path == kByPartition) {
     const int64_t n_buckets = w->n_buckets;
     const int64_t by_size = (n_all + 4 * kPartBlock - 1) / (4 * kPartBlock);
@@ -824,7 +834,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     if (m > 0)
       COOP_LAUNCH(K_UNIQ_FLAG, k_uniq_lookup, dim3(nblocks(m)), dim3(kBlock), 0, s, col_global, m, m_dev, table, (uint64_t)cap, first);
   }
-  if (m > 0 && !(path == kByFilter && n_all <= kShortMax)) {
+  if (m > 0 && !(path == kByFilter && w->bits)) {
     uint32_t* totals = alloc.get<uint32_t>(2 * (int64_t)collect_blocks, COOP_TAG_SCRATCH);
     if (alloc.failed) return COOP_E_NOMEM;
     w->block_prefix = totals + collect_blocks;
@@ -867,8 +877,9 @@ int unique_prepare(int64_t n_dst, int64_t m, UniqueWork* w, Alloc& alloc) {
 
 int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
                         int32_t* spare, UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
-  if (w->clear != nullptr) fill_u64(w->clear, w->n_clear, 0, s);
-  w->clear = nullptr;
+  // (Words that nobody has cleared on the way, the list's length having been unknown, are left to k_uniq_collect: a launch as well,
+  // and 2 us less than clearing them here.)
+  w->bits = w->n_clear != 0 && w->clear == nullptr;
   return unique_launch(dst, n_dst, col_global, m, m_dev, col_local, spare, w, (UniqPath)w->path, alloc, d_ctl, h_ctl, s);
 }
 
@@ -893,7 +904,7 @@ int unique_back(const int32_t* dst, int64_t n_dst, const int32_t* col_global, in
                 int32_t* col_local, int32_t* src, hipStream_t s) {
   const int64_t n_threads = m > n_dst ? m : n_dst;
   const RankView rank{w.words, w.block_prefix, w.part_blocks};
-  if (n_threads > 0 && w.path == kByFilter && n_dst + m <= kShortMax)
+  if (n_threads > 0 && w.path == kByFilter && w.bits)
     COOP_LAUNCH(K_UNIQ_RELABEL, k_uniq_relabel_short, dim3((unsigned)((n_threads + kShortBlock * kShortEach - 1) / (kShortBlock * kShortEach))),
                 dim3(kShortBlock), 0, s, dst, col_global, m, m_dev, n_dst, (const unsigned long long*)w.words, src, col_local);
   else if (n_threads > 0)
