@@ -928,6 +928,20 @@ def test_offsets_around_the_edges_of_tiles(P, mode):
         P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
 
 
+@pytest.mark.parametrize("size", [1, 1023, 1024, 1025, 4096, 4097])
+def test_offsets_of_one_tile(P, medium, size):
+    """Offsets scanned by a block of 256 threads (up to 1,024 counts), by one of 1,024 that is alone (4,096) and by several, with
+    the sizes read back at once."""
+    seeds = np.random.default_rng(size).permutation(medium.n)[:size]
+    P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 0)
+    try:
+        for kappa in (1, 4):
+            compare(P, medium, seeds, (5,), R.LABOR0, it=kappa - 1, kappa=kappa, seed=size)
+        compare_rw(P, medium, seeds, (5,), 2, 10, 0.3, seed=size)
+    finally:
+        P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
+
+
 @pytest.mark.parametrize("size", [4096, 37000])
 def test_frontier_dedup_of_short_lists_with_a_hub(P, size):
     """One source in 36 is the same vertex, among others that differ: in the longer list more of them than a wave can note (16
