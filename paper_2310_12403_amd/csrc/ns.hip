@@ -609,6 +609,34 @@ __device__ __forceinline__ bool ns_next_bound(uint32_t n_c, uint32_t k, uint32_t
   return true;
 }
 
+// The lists that are kept whole, of a wave's destinations, 64 >> each_log2 lanes and g of each: short ones together, those longer than
+// 4 entries for each of the lanes one after the other by the whole wave.  (Steps over 90 thousand lists of 30 to
+// 1,500 entries 1.99 ms with eight lanes for each, 1.51 so; a thousand lists of a papers100M shape 74 us with a load at a time, 61 with
+// eight in flight.)
+__device__ __forceinline__ void ns_copy_whole(const int32_t* __restrict__ g_indices, const NsRecord& g, int64_t o, bool whole, uint32_t k, int each_log2,
+                                              int32_t* __restrict__ col_global, int64_t* __restrict__ eid) {
+  const uint32_t lane = (uint32_t)lane_id(), lanes = 64u >> each_log2, sub = lane & (lanes - 1);
+  if (whole && g.d <= 4 * lanes) {
+    for (uint32_t j = sub; j < g.d; j += lanes) {
+      (col_global + o)[j] = (g_indices + g.beg)[j];
+      (eid + o)[j] = g.beg + j;
+    }
+  }
+  if (k <= 4 * lanes) return;
+  auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
+  auto of64 = [&](int64_t x, int q) { return (int64_t)(((uint64_t)of((uint32_t)((uint64_t)x >> 32), q) << 32) | of((uint32_t)x, q)); };
+  for (uint64_t todo = ballot64(whole && sub == 0 && g.d > 4 * lanes); todo != 0; todo &= todo - 1) {
+    const int at = __builtin_ctzll(todo);
+    const uint32_t d = of(g.d, at);
+    const int64_t beg = of64(g.beg, at), to = of64(o, at);
+#pragma unroll 8
+    for (uint32_t j = lane; j < d; j += kWave) {
+      (col_global + to)[j] = (g_indices + beg)[j];
+      (eid + to)[j] = beg + j;
+    }
+  }
+}
+
 // c = 0.  A wave takes `each` neighbouring destinations (at most 64; the dispatcher starts one-wave blocks at some 5 per ns, 150 us
 // for 745 thousand that do nothing).  Their records come in one load, a destination per lane; lists no longer than the fanout
 // are copied together, 64 / each lanes for each; the others go one after the other through the whole wave, the next one's entries
@@ -645,13 +673,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
   // (longer than skip_above: queued, one of the first waves takes it)
   if (speaks && (g.d <= k || g.d <= skip_above)) ns_settle_offset(indptr, first + w, tile_log2, o);
   const bool live = mine && g.d != 0 && o_end <= edge_limit;  // (no room: the caller redoes the layer)
-  if (live && g.d <= k) {
-    const uint32_t lanes = 64u >> each_log2;
-    for (uint32_t j = lane & (lanes - 1); j < g.d; j += lanes) {
-      (col_global + o)[j] = (g_indices + g.beg)[j];
-      (eid + o)[j] = g.beg + j;
-    }
-  }
+  ns_copy_whole(g_indices, g, o, live && g.d <= k, k, each_log2, col_global, eid);
   if (k > kNsMaxSelect) return;  // degrees above a fanout that the candidate buffer cannot serve: left to k_ns_fill_wide
   uint64_t todo = ballot64(live && speaks && g.d > k && g.d <= skip_above);
   if (todo == 0) return;
@@ -801,12 +823,7 @@ __global__ __launch_bounds__(kWave, 7) void k_ns_collect(const int32_t* __restri
   const bool mine = number < n_mine && (g.d <= k || g.d <= skip_above), speaks = mine && sub == 0;  // (the others: queued)
   if (speaks) ns_settle_offset(indptr, first + w, tile_log2, o);
   const bool live = mine && g.d != 0 && o_end <= edge_limit;  // (no room: the caller redoes the layer)
-  if (live && g.d <= k) {
-    for (uint32_t j = sub; j < g.d; j += lanes) {
-      (col_global + o)[j] = (g_indices + g.beg)[j];
-      (eid + o)[j] = g.beg + j;
-    }
-  }
+  ns_copy_whole(g_indices, g, o, live && g.d <= k, k, each_log2, col_global, eid);
   const bool sampled = live && g.d > k && k <= kNsMaxSelect;  // (a larger fanout: k_ns_fill_wide)
   BlendScan<1, true, NsSink> S;
   S.queue = &queue;

@@ -1215,6 +1215,23 @@ def test_ns_lists_around_the_edges_of_groups(P, aligned, kappa):
         compare(P, g, np.arange(size), (k,), R.NS, it=kappa - 1, kappa=kappa, seed=size)
 
 
+@pytest.mark.parametrize("kappa", [1, 4])
+@pytest.mark.parametrize("size", [700, 40000, 70001])
+def test_ns_lists_kept_whole(P, size, kappa):
+    """Lists no longer than the fanout, to both sides of four entries per lane (32, 64 and 128 lanes' worth, by the destinations a
+    wave takes) and of eight rounds of a wave, next to empty and to longer ones."""
+    n = 70001
+    rng = np.random.default_rng(23)
+    deg = rng.integers(0, 10, n)
+    at = np.arange(0, n, 53)
+    deg[at] = np.array([31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1025])[np.arange(len(at)) % 16]
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    g = G(P, torch.from_numpy(indptr), torch.from_numpy(rng.integers(0, n, int(indptr[-1])).astype(np.int32)))
+    seeds = at[:size] if size < 1000 else np.arange(size)
+    for k in (32, 64, 128, 256, 512, 4000):
+        compare(P, g, seeds, (k,), R.NS, it=kappa - 1, kappa=kappa, seed=k)
+
+
 @pytest.mark.parametrize("size", [300, 40000])
 def test_ns_lists_around_the_groups_in_flight(P, size):
     """Lists of one to three times as many groups of 256 entries as are in flight, one entry less and one more, with and without a
