@@ -723,9 +723,9 @@ __device__ __forceinline__ void ns_redo_one(int64_t w, int wib, uint32_t* lds_wo
                                             const VariateParams& vp, const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
                                             int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl) {
   const int64_t o = eptr[w];
-  if (eptr[w + 1] > edge_limit) return;
   const NsRecord g = rec[w];
   if (g.d <= k || k > kNsMaxSelect) return;  // (never marked)
+  if (o + k > edge_limit) return;  // (by its own record: eptr[w + 1] may be the next slice's, whose offsets are not settled yet)
   NsSlot* slot = reinterpret_cast<NsSlot*>(lds_words) + (size_t)wib * cap;  // [cap]
   const uint32_t sigma_a = ns_sigma(vp.K.Ka, (uint32_t)g.s), sigma_b = ns_sigma(vp.K.Kb, (uint32_t)g.s);
   uint32_t lo = 0, hi = 0xFFFFFFFFu, bound = g.bound;
@@ -1123,7 +1123,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_fill_wide(const int32_t* __restri
   if (w >= n_dst) return;
   const NsRecord g = rec[w];
   if (g.d <= k) return;  // (copied whole by the fill kernel)
-  if (eptr[w + 1] > edge_limit) return;
+  if (eptr[w] + k > edge_limit) return;
   const uint32_t lane = (uint32_t)lane_id();
   const int32_t* __restrict__ list = g_indices + g.beg;
   const uint32_t d = g.d;
