@@ -353,6 +353,9 @@ const char* coop_strerror(int code);
                                       about COOP_TUNE_PIECE_LEN entries, a single piece if they are shorter than that);
                                       0 (default): twice the piece length with independent variates, 2048 with dependent
                                       ones; otherwise 64..2^30 */
+#define COOP_TUNE_STRETCH 11       /* lists (or what is left of them) longer than this many entries are read in stretches of so
+                                      many: a multiple of 256 in 256..2^28; 0 (default): 2^28, as far as a 32-bit byte
+                                      offset reaches.  Other values are meant for tests. */
 int coop_tune(int knob, int64_t value);
 
 /* out[i] = in[i] for a device id list (a plain streaming copy on `stream`: 4n bytes read, 4n written).  Besides its

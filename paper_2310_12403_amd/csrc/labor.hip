@@ -601,7 +601,7 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
                                                                const uint32_t* __restrict__ thr_all, int64_t n, int each_log2, FusedKeys keys,
                                                                uint32_t stage_cap, ScanOut out, Ctl* ctl, int piece_blocks,
                                                                const Piece* __restrict__ pieces, const uint32_t* __restrict__ piece_count,
-                                                               uint32_t piece_cap, uint32_t piece_len) {
+                                                               uint32_t piece_cap, uint32_t piece_len, uint32_t stretch) {
   __shared__ KeptSlots slots[NF];
   const uint32_t lane = (uint32_t)lane_id();
   auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
@@ -687,11 +687,11 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
     int64_t beg = of64(g.beg, at);
 #pragma unroll
     for (int l = 0; l < NF; ++l) { thr[l] = of(my_thr[l], at); kept[l] = 0; }
-    for (ListReader<> L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+    for (ListReader<> L(g_indices + beg, d < stretch ? d : stretch);;) {
       labor_collect<NF>(L, j0, thr, K, slots, kept);
-      if (d - j0 > kStretch) {  // the list's next stretch
-        j0 += kStretch;
-        L = ListReader<>(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+      if (d - j0 > stretch) {  // the list's next stretch
+        j0 += stretch;
+        L = ListReader<>(g_indices + beg + j0, d - j0 < stretch ? d - j0 : stretch);
         continue;
       }
       const int done = at;
@@ -700,7 +700,7 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
       d = todo != 0 ? of(g.d, at) : 0u;
       beg = of64(g.beg, at);
       j0 = 0;
-      L = ListReader<>(g_indices + beg, d < kStretch ? d : kStretch);
+      L = ListReader<>(g_indices + beg, d < stretch ? d : stretch);
       settle();
 #pragma unroll
       for (int l = 0; l < NF; ++l) {
@@ -799,7 +799,7 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 7 : NF == 2 ? 6 : NF == 3 ? 5 : 4)
 k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg, const uint32_t* __restrict__ thr_all,
                    const PreThr* __restrict__ pthr_all, const float* __restrict__ lim2_all, int64_t n, int each_log2, FusedKeys keys, uint32_t stage_cap,
                    ScanOut out, Ctl* ctl, int piece_blocks, const Piece* __restrict__ pieces, const uint32_t* __restrict__ piece_count,
-                   uint32_t piece_cap, uint32_t piece_len, CandOut cand) {
+                   uint32_t piece_cap, uint32_t piece_len, CandOut cand, uint32_t stretch) {
   __shared__ BlendQueue<false> queue[NF];
   const uint32_t lane = (uint32_t)lane_id();
   auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
@@ -897,10 +897,10 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
       for (int l = 0; l < NF; ++l) { a1[l] = of(my_a1[l], at); a2[l] = of(my_a2[l], at); b2[l] = of(my_b2[l], at); }
     };
     thresholds();
-    for (ListReader<> L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+    for (ListReader<> L(g_indices + beg, d < stretch ? d : stretch);;) {
       S.collect(L, j0, (uint32_t)at, a1, a2, b2);
-      if (d - j0 > kStretch) {  // the list's next stretch
-        j0 += kStretch;
+      if (d - j0 > stretch) {  // the list's next stretch
+        j0 += stretch;
       } else {
         todo &= todo - 1;
         if (todo == 0) break;
@@ -910,7 +910,7 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
         j0 = 0;
         thresholds();
       }
-      L = ListReader<>(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+      L = ListReader<>(g_indices + beg + j0, d - j0 < stretch ? d - j0 : stretch);
     }
   }
   S.flush();
@@ -1038,7 +1038,7 @@ static void launch_scan_blend(int nf, unsigned blocks, hipStream_t s, const int3
   if (cand.buf != nullptr) { COOP_SCAN_BLEND_AS(NF, false); } else { COOP_SCAN_BLEND_AS(NF, true); }
 #define COOP_SCAN_BLEND_AS(NF, EXACT)                                                                                                        \
   COOP_LAUNCH(K_LABOR_COUNT, (k_labor_scan_blend<NF, EXACT>), dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, pthr, lim2, n, each_log2, keys, cap, out, ctl, \
-              piece_blocks, pieces, piece_count, piece_cap, piece_len, cand)
+              piece_blocks, pieces, piece_count, piece_cap, piece_len, cand, (uint32_t)g_stretch)
   switch (nf) {
     case 1: COOP_SCAN_BLEND(1); break;
     case 2: COOP_SCAN_BLEND(2); break;
@@ -1053,7 +1053,7 @@ static void launch_scan_plain(int nf, unsigned blocks, hipStream_t s, const int3
                               const uint32_t* piece_count, uint32_t piece_cap, uint32_t piece_len) {
 #define COOP_SCAN_PLAIN(NF)                                                                                                           \
   COOP_LAUNCH(K_LABOR_COUNT, k_labor_scan_plain<NF>, dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, n, each_log2, keys, cap, out, ctl, \
-              piece_blocks, pieces, piece_count, piece_cap, piece_len)
+              piece_blocks, pieces, piece_count, piece_cap, piece_len, (uint32_t)g_stretch)
   switch (nf) {
     case 1: COOP_SCAN_PLAIN(1); break;
     case 2: COOP_SCAN_PLAIN(2); break;

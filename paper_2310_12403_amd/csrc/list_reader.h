@@ -24,7 +24,7 @@ struct ListLoads {
 // at once; a loop over the groups asks for group g + GROUPS when it is through with group g.
 constexpr uint32_t kGroup = kWave * 4;  // entries of a 16-byte load by every lane
 constexpr uint32_t kReaderGroups = 4;   // ... of which so many are in flight
-constexpr uint32_t kStretch = 1u << 28;  // entries that a descriptor's offsets reach
+constexpr uint32_t kStretchMost = 1u << 28;  // entries that a descriptor's offsets reach: longer lists are read in stretches (g_stretch)
 template <uint32_t GROUPS = kReaderGroups>
 struct ListReader {
   ListLoads in;

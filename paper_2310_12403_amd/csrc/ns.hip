@@ -647,7 +647,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
                                                     uint32_t cap, LayerKeys keys, int64_t* indptr, int64_t first, int tile_log2,
                                                     int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl,
                                                     uint32_t long_min, const uint32_t* __restrict__ long_list,
-                                                    const uint32_t* __restrict__ n_long, int long_blocks, int each_log2) {
+                                                    const uint32_t* __restrict__ n_long, int long_blocks, int each_log2, uint32_t stretch) {
   extern __shared__ __align__(16) uint32_t lds_words[];  // cap slots, and one per lane
   NsSlot* slot = reinterpret_cast<NsSlot*>(lds_words);
   const uint32_t lane = (uint32_t)lane_id();
@@ -685,15 +685,15 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
   uint32_t lo = 0, hi = 0xFFFFFFFFu, attempt = 0;  // bisection bracket on the bound, used only after a failed pass
   uint32_t j0 = 0, n_c = 0;                        // entries looked at in earlier stretches of the list, candidates so far
   const uint32_t head = vector_copy(keys.Ka[4]), tail = vector_copy(keys.Ka[3]);
-  for (ListReader<kFillGroups> L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+  for (ListReader<kFillGroups> L(g_indices + beg, d < stretch ? d : stretch);;) {
     const NsKeys K{head, vector_copy(mid), tail};
     n_c = ns_collect_plain(L, j0, bound, K, slot, cap, n_c);
     const uint32_t found = n_c;
     const int64_t o_done = o_this, beg_done = beg;
     const uint32_t bound_done = bound;
     bool select = false;
-    if (d - j0 > kStretch) {  // the list's next stretch
-      j0 += kStretch;
+    if (d - j0 > stretch) {  // the list's next stretch
+      j0 += stretch;
     } else if ((n_c < k || n_c > cap) && ++attempt < 40 && ns_next_bound(n_c, k, &lo, &hi, &bound)) {  // the list once more
       j0 = n_c = 0;
     } else {  // the next list
@@ -709,7 +709,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
       lo = j0 = n_c = attempt = 0;
       hi = 0xFFFFFFFFu;
     }
-    L = ListReader<kFillGroups>(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+    L = ListReader<kFillGroups>(g_indices + beg + j0, d - j0 < stretch ? d - j0 : stretch);
     if (select) ns_rank_write_plain(found, k, bound_done, K, slot, o_done, beg_done, col_global, eid);
     if (todo == 0) break;
     __builtin_amdgcn_wave_barrier();
@@ -798,7 +798,7 @@ __global__ __launch_bounds__(kWave, 7) void k_ns_collect(const int32_t* __restri
                                                          float sw, int64_t* indptr, int64_t first, int tile_log2, int32_t* __restrict__ col_global,
                                                          int64_t* __restrict__ eid, int64_t edge_limit, StageEntry* __restrict__ rows, uint32_t row_cap,
                                                          uint32_t* __restrict__ n_cand, uint32_t long_min, const uint32_t* __restrict__ long_list,
-                                                         const uint32_t* __restrict__ n_long, int long_blocks, int each_log2) {
+                                                         const uint32_t* __restrict__ n_long, int long_blocks, int each_log2, uint32_t stretch) {
   __shared__ BlendQueue<true> queue;
   const uint32_t lane = (uint32_t)lane_id();
   uint32_t w0, n_mine = 1, skip_above = 0xFFFFFFFFu;
@@ -868,10 +868,10 @@ __global__ __launch_bounds__(kWave, 7) void k_ns_collect(const int32_t* __restri
       S.mid_b = vector_copy(of(mid_b, at));
     };
     take();
-    for (ListReader<> L(g_indices + beg, d < kStretch ? d : kStretch);;) {
+    for (ListReader<> L(g_indices + beg, d < stretch ? d : stretch);;) {
       S.collect(L, j0, (uint32_t)at, a1, a2, b2);
-      if (d - j0 > kStretch) {  // the list's next stretch
-        j0 += kStretch;
+      if (d - j0 > stretch) {  // the list's next stretch
+        j0 += stretch;
       } else {
         todo &= todo - 1;
         if (todo == 0) break;
@@ -881,7 +881,7 @@ __global__ __launch_bounds__(kWave, 7) void k_ns_collect(const int32_t* __restri
         j0 = 0;
         take();
       }
-      L = ListReader<>(g_indices + beg + j0, d - j0 < kStretch ? d - j0 : kStretch);
+      L = ListReader<>(g_indices + beg + j0, d - j0 < stretch ? d - j0 : stretch);
     }
   }
   S.flush();
@@ -1280,7 +1280,7 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
         const dim3 grid_redo(blocks_for(n, (int64_t)wpb << lists_log2));
         COOP_LAUNCH(K_NS_FILL, k_ns_collect, dim3(blocks_for(n, (int64_t)1 << each_log2) + (unsigned)long_blocks), dim3(kWave), 0, s, cx.g->indices,
                     rec_b, bthr_b, (uint32_t)n, k, vp.K, (float)vp.cw, (float)vp.sw, blk->indptr, b, tile_log2, blk->col_global, blk->eid, m, rows_b,
-                    row_cap, n_cand_b, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2);
+                    row_cap, n_cand_b, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2, (uint32_t)g_stretch);
         COOP_LAUNCH(K_NS_SELECT, k_ns_select, dim3(blocks_for(n, (int64_t)1 << select_log2)), dim3(kWave), (size_t)cap * sizeof(NsSlot), s, rec_b, n, k, vp,
                     eptr_b, blk->col_global, blk->eid, (const StageEntry*)rows_b, row_cap, n_cand_b, bthr_b, select_log2, group_log2);
 #define COOP_NS_BLEND(VEC4) \
@@ -1290,7 +1290,8 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
       } else {
         COOP_LAUNCH(K_NS_FILL, k_ns_fill, dim3(blocks_for(n, (int64_t)1 << each_log2) + (unsigned)long_blocks), dim3(kWave),
                     (cap + kWave) * sizeof(NsSlot), s, cx.g->indices, rec_b, (uint32_t)n, k, cap, vp.K, blk->indptr, b, tile_log2,
-                    blk->col_global, blk->eid, m, cx.d_ctl, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2);
+                    blk->col_global, blk->eid, m, cx.d_ctl, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2,
+                    (uint32_t)g_stretch);
       }
 #undef COOP_NS_ARGS
       if (k > kNsMaxSelect) {  // the lists longer than such a fanout (the kernels above skip them)

@@ -2,7 +2,7 @@
 // kept edges of S^l in (destination order, adjacency order); unique.hip forms S^{l+1} (Eq. 2) and the local ids.
 #include <math.h>
 
-#include "device_utils.h"
+#include "list_reader.h"
 #include "sample_internal.h"
 
 namespace coop {
@@ -76,6 +76,7 @@ int g_split_min = 0;           // COOP_TUNE_SPLIT_MIN (0 = twice the piece lengt
 int64_t g_blend_candidates = 0;  // COOP_TUNE_BLEND_CANDIDATES (0 = automatic)
 int g_defer_sizes = 1;         // COOP_TUNE_DEFER_SIZES
 int g_enum_degree = 8192;      // COOP_TUNE_ENUM_DEGREE
+int64_t g_stretch = kStretchMost;  // COOP_TUNE_STRETCH
 
 // puts back what a LABOR-0 pass at layer l changed in the control data, before the pass is run again
 __global__ void k_reset_layer(Ctl* ctl, uint32_t* piece_count) {
@@ -128,6 +129,10 @@ extern "C" int coop_tune(int knob, int64_t value) {
     case COOP_TUNE_NS_LONG_LIST:
       if (value != 0 && (value < 64 || value > ((int64_t)1 << 30))) return COOP_E_ARG;
       g_ns_long_min = (int)value;
+      return COOP_OK;
+    case COOP_TUNE_STRETCH:
+      if (value != 0 && (value < 256 || value > (int64_t)kStretchMost || (value & 255))) return COOP_E_ARG;
+      g_stretch = value != 0 ? value : (int64_t)kStretchMost;
       return COOP_OK;
     default:
       return COOP_E_ARG;

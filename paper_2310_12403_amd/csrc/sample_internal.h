@@ -98,6 +98,7 @@ extern int g_split_min;
 extern int64_t g_blend_candidates;
 extern int g_defer_sizes;
 extern int g_enum_degree;
+extern int64_t g_stretch;
 extern int g_ns_long_min;   // COOP_TUNE_NS_LONG_LIST (defined in ns.hip)
 
 // A launch has fewer than 2^32 threads (more are taken modulo that number, without an error): passes with a wave per

@@ -1185,6 +1185,35 @@ def test_labor_lists_around_the_edges_of_groups(P, aligned, kappa):
 
 
 @pytest.mark.parametrize("kappa", [1, 4])
+@pytest.mark.parametrize("stretch", [256, 512, 1792])
+def test_lists_read_in_stretches(P, stretch, kappa):
+    """Lists of more than 2^28 entries are read a stretch at a time, here far shorter ones: lists that end with a stretch, one entry
+    before and behind, of one stretch and of many, of both samplers, whole (never cut into pieces), one a wave and several; and lists
+    that NS has to collect again from the beginning, with a bound that lets too few or too many neighbours through."""
+    n = 40000
+    rng = np.random.default_rng(41)
+    deg = rng.integers(0, 12, n)
+    at = np.arange(2, n, 61)
+    deg[at] = np.array([q * stretch + r for q in (1, 2, 3, 7) for r in (-1, 0, 1, 100, 255)])[np.arange(len(at)) % 20]
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    indices = rng.integers(0, n, int(indptr[-1])).astype(np.int32)
+    for v in at[::7]:  # neighbours that occur some hundred times each: a bound lets that many more through or none
+        indices[indptr[v]:indptr[v + 1]] = v % 1000 + rng.integers(0, deg[v] // 100 + 2, deg[v])
+    g = G(P, torch.from_numpy(indptr), torch.from_numpy(indices))
+    try:
+        P.coop_tune(P.COOP_TUNE_STRETCH, stretch)
+        P.coop_tune(P.COOP_TUNE_PIECE_LEN, 0)
+        for seeds in (at[:500], np.arange(n)):
+            for k in (1, 10, 70):
+                compare(P, g, seeds, (k,), R.NS, it=kappa - 1, kappa=kappa, seed=k)
+            compare(P, g, seeds, (10, 4), R.LABOR0, it=kappa - 1, kappa=kappa, seed=3)
+            compare(P, g, seeds, (60,), R.LABOR0, it=kappa - 1, kappa=kappa, seed=3)
+    finally:
+        P.coop_tune(P.COOP_TUNE_STRETCH, 0)
+        P.coop_tune(P.COOP_TUNE_PIECE_LEN, 4096)
+
+
+@pytest.mark.parametrize("kappa", [1, 4])
 @pytest.mark.parametrize("aligned", [True, False])
 def test_ns_lists_around_the_edges_of_groups(P, aligned, kappa):
     """Lists of one entry less than, as many as and one more than 64 q entries, of whole groups of 256 with and without a
