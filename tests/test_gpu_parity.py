@@ -1184,6 +1184,18 @@ def test_labor_lists_around_the_edges_of_groups(P, aligned, kappa):
         P.coop_tune(P.COOP_TUNE_STAGE_CAP, 0)
 
 
+@pytest.mark.parametrize("lists", [3, 33, 63])
+def test_lists_per_wave_that_are_no_power_of_two(P, medium, lists):
+    """The scan takes the next power of two."""
+    seeds = np.random.default_rng(lists).permutation(medium.n)[:10007]
+    P.coop_tune(P.COOP_TUNE_LISTS_PER_WAVE, lists)
+    try:
+        for kappa in (1, 4):
+            compare(P, medium, seeds, (10, 4), R.LABOR0, it=kappa - 1, kappa=kappa, seed=lists)
+    finally:
+        P.coop_tune(P.COOP_TUNE_LISTS_PER_WAVE, 0)
+
+
 @pytest.mark.parametrize("kappa", [1, 4])
 @pytest.mark.parametrize("stretch", [256, 512, 1792])
 def test_lists_read_in_stretches(P, stretch, kappa):
