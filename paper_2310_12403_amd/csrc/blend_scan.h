@@ -47,15 +47,6 @@ struct BlendScan {
     tail_b[l] = vector_copy(K.Kb[NS ? 3 : 1]);
     waiting[l] = 0;
   }
-  // a uniform without its last fold
-  static __device__ __forceinline__ uint32_t rough(uint32_t head, uint32_t mid, uint32_t tail, uint32_t t) {
-    const uint32_t m = mix_body(fold16_xor(t, head));
-    return (NS ? mix_body(m ^ mid) : m) ^ tail;
-  }
-  static __device__ __forceinline__ uint32_t uniform(uint32_t head, uint32_t mid, uint32_t tail, uint32_t t) {
-    const uint32_t m = mix_body(fold16_xor(t, head));
-    return fold16_xor(NS ? mix_body(m ^ mid) : m, tail);
-  }
 
   // Stage 2 on n <= 64 entries of layer l's queue from `from` on: the two uniforms again, the blend in fp32.
   __device__ __forceinline__ void second(int l, uint32_t from, uint32_t n) {
@@ -69,7 +60,7 @@ struct BlendScan {
       slot = queue[l].slot[from + lane];
     }
     const uint32_t ma = NS ? queue[l].mid_a[slot] : 0u, mb = NS ? queue[l].mid_b[slot] : 0u;
-    const uint32_t u1 = uniform(head_a[l], ma, tail_a[l], (uint32_t)e.t), u2 = uniform(head_b[l], mb, tail_b[l], (uint32_t)e.t);
+    const uint32_t u1 = words_uniform<NS>(head_a[l], ma, tail_a[l], (uint32_t)e.t), u2 = words_uniform<NS>(head_b[l], mb, tail_b[l], (uint32_t)e.t);
     sink.take(queue, l, lane < n, e, slot, u1, u2, __builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2)));
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -130,7 +121,7 @@ struct BlendScan {
   // Stage 1 for one entry.  It looks at the uniforms without their last fold: the bounds come rounded up to whole upper halves, so that
   // nothing is lost.  The test is (lo <= a1) | (lo <= a2 & hi <= b2), a1 <= a2.
   __device__ __forceinline__ uint64_t passes(int l, uint32_t t, uint32_t a1, uint32_t a2, uint32_t b2) const {
-    const uint32_t u1 = rough(head_a[l], mid_a, tail_a[l], t), u2 = rough(head_b[l], mid_b, tail_b[l], t);
+    const uint32_t u1 = words_rough<NS>(head_a[l], mid_a, tail_a[l], t), u2 = words_rough<NS>(head_b[l], mid_b, tail_b[l], t);
     const uint32_t lo = u1 < u2 ? u1 : u2, hi = u1 < u2 ? u2 : u1;
     const uint32_t edge = hi <= b2 ? a2 : a1;
     return compare_mask(lo <= edge);

@@ -509,7 +509,7 @@ struct KeptSlots { StageEntry at[kKeptSlots + kWave]; };  // the last kWave: a s
 
 template <int NF>
 struct PlainKeys { uint32_t head[NF], tail[NF]; };  // in vector registers (vector_copy)
-__device__ __forceinline__ uint32_t labor_uniform(uint32_t head, uint32_t tail, uint32_t t) { return fold16_xor(mix_body(fold16_xor(t, head)), tail); }
+__device__ __forceinline__ uint32_t labor_uniform(uint32_t head, uint32_t tail, uint32_t t) { return words_uniform<false>(head, 0u, tail, t); }
 
 // One pass over a list (or a stretch of it that starts at list position j0) for NF layers: neighbours with R_t <= thr[l] go to
 // layer l's slots behind the n[l] that are there; those behind kKeptSlots are counted, not stored.

@@ -179,7 +179,7 @@ constexpr int kNsQueueCap = 2 * kWave;
 struct NsQueue {
   int32_t t[kNsQueueCap];
   uint32_t j[kNsQueueCap];
-  uint32_t u1[kNsQueueCap];  // (keyed_rough)
+  uint32_t u1[kNsQueueCap];  // (ns_rough)
   uint32_t u2[kNsQueueCap];
 };
 
@@ -290,7 +290,7 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
     if (lane < n) {
       t = q->t[lane];
       j = q->j[lane];
-      const uint32_t u1 = keyed_exact<true>(vp.K.Ka, q->u1[lane]), u2 = keyed_exact<true>(vp.K.Kb, q->u2[lane]);
+      const uint32_t u1 = ns_exact(vp.K.Ka, q->u1[lane]), u2 = ns_exact(vp.K.Kb, q->u2[lane]);
       if (__builtin_fmaf(cwf, approx_phi_inv_f32(u1), swf * approx_phi_inv_f32(u2)) <= bt.lim2) {
         R = blend_exact(u1, u2, vp.cw, vp.sw);
         in = R <= bound;
@@ -320,11 +320,11 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
     }
   };
   // first look at one entry: the integer bounds on its two uniforms (without their last fold, and the bounds rounded up to
-  // whole upper halves, so that nothing is lost: keyed_exact finishes the passers')
+  // whole upper halves, so that nothing is lost: ns_exact finishes the passers')
   auto first_look = [&](bool valid, int32_t t, uint32_t& r, uint32_t& u2) -> bool {
     const uint32_t folded = fold16((uint32_t)t);
-    r = keyed_rough<true>(vp.K.Ka, folded, sigma_a);
-    u2 = keyed_rough<true>(vp.K.Kb, folded, sigma_b);
+    r = ns_rough(vp.K.Ka, folded, sigma_a);
+    u2 = ns_rough(vp.K.Kb, folded, sigma_b);
     const uint32_t lo = r < u2 ? r : u2, hi = r < u2 ? u2 : r;
     return valid & ((lo <= (bt.a1 | 0xFFFFu)) | ((lo <= (bt.a2 | 0xFFFFu)) & (hi <= (bt.b2 | 0xFFFFu))));
   };

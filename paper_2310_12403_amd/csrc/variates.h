@@ -310,32 +310,28 @@ __device__ __forceinline__ uint32_t kit_phi_to_u32(double x) {
 // sigma = mix(s ^ K2) of the destination, wave-uniform; NS only
 __device__ __forceinline__ uint32_t ns_sigma(const uint32_t K[5], uint32_t s) { return mix32(s ^ K[2]); }
 
-// U = mix32(t ^ K0) ^ K1, for NS mix32(that ^ sigma) ^ K3.  Evaluated from head = fold16(t), which the layers and the two
-// uniforms of a blend share; the folds between the two mixers of NS cancel.
-// keyed_rough leaves the last fold out: its upper 16 bits are those of U.
-// (The folded key K[4] comes from the host: if the compiler sees it made, it turns fold16(t) ^ fold16(K0) back into three
-// instructions per entry.)
-template <bool NS>
-__device__ __forceinline__ uint32_t keyed_rough(const uint32_t K[5], uint32_t head, uint32_t sigma) {
-  const uint32_t m = mix_body(head ^ K[4]);
-  if constexpr (!NS) return m ^ K[1];
-  else return mix_body(m ^ fold16(K[1] ^ sigma)) ^ K[3];
-}
-// U from keyed_rough's value
-template <bool NS>
-__device__ __forceinline__ uint32_t keyed_exact(const uint32_t K[5], uint32_t rough) { return rough ^ ((rough ^ (NS ? K[3] : K[1])) >> 16); }
-// the NS uniform, its three key words (K[4], fold16(K[1] ^ sigma), K[3]) at hand
-struct NsKeys { uint32_t head, mid, tail; };
+// U = mix32(t ^ K0) ^ K1, for NS mix32(that ^ sigma) ^ K3; the folds between the two mixers of NS cancel.  From its key words:
+// head = K[4] (folded by the host: if the compiler sees it made, it turns fold16(t) ^ fold16(K0) back into three instructions per
+// entry), tail = K[1] or, NS, K[3], and, NS, mid = ns_mid.  The rough one leaves the last fold out: its upper 16 bits are those of U.
 __device__ __forceinline__ uint32_t ns_mid(const uint32_t K[5], uint32_t sigma) { return fold16(K[1] ^ sigma); }
-__device__ __forceinline__ uint32_t ns_uniform(const NsKeys& K, uint32_t t) {
-  return fold16_xor(mix_body(mix_body(fold16_xor(t, K.head)) ^ K.mid), K.tail);
+template <bool NS>
+__device__ __forceinline__ uint32_t words_body(uint32_t head, uint32_t mid, uint32_t t) {
+  const uint32_t m = mix_body(fold16_xor(t, head));
+  return NS ? mix_body(m ^ mid) : m;
 }
 template <bool NS>
-__device__ __forceinline__ uint32_t keyed_from_head(const uint32_t K[5], uint32_t head, uint32_t sigma) {
-  const uint32_t m = mix_body(head ^ K[4]);
-  if constexpr (!NS) return fold16(m) ^ K[1];
-  else return fold16(mix_body(m ^ fold16(K[1] ^ sigma))) ^ K[3];
+__device__ __forceinline__ uint32_t words_rough(uint32_t head, uint32_t mid, uint32_t tail, uint32_t t) { return words_body<NS>(head, mid, t) ^ tail; }
+template <bool NS>
+__device__ __forceinline__ uint32_t words_uniform(uint32_t head, uint32_t mid, uint32_t tail, uint32_t t) {
+  return fold16_xor(words_body<NS>(head, mid, t), tail);
 }
+struct NsKeys { uint32_t head, mid, tail; };
+__device__ __forceinline__ uint32_t ns_uniform(const NsKeys& K, uint32_t t) { return words_uniform<true>(K.head, K.mid, K.tail, t); }
+// (NS) the rough uniform from fold16(t), which the two of a blend share, and U from it
+__device__ __forceinline__ uint32_t ns_rough(const uint32_t K[5], uint32_t folded, uint32_t sigma) {
+  return mix_body(mix_body(folded ^ K[4]) ^ ns_mid(K, sigma)) ^ K[3];
+}
+__device__ __forceinline__ uint32_t ns_exact(const uint32_t K[5], uint32_t rough) { return rough ^ ((rough ^ K[3]) >> 16); }
 template <bool NS>
 __device__ __forceinline__ uint32_t keyed_uniform(const uint32_t K[5], uint32_t t, uint32_t sigma) {
   const uint32_t m = mix_body(fold16(t ^ K[0]));
