@@ -123,7 +123,11 @@ __device__ __forceinline__ int64_t scan_tile_sums(int64_t n, int log2, int64_t* 
   }
   return carry;
 }
-// one thread per block: leaves the tile's sum where its first element's offset belongs; true in the block that is last
+// One thread per block: leaves the tile's sum where its first element's offset belongs; true in the block that is last.
+// No fence stands between the sum and the count: an atomic that returns a value has been performed in memory when the value is
+// here (the asm waits for it), and the count is sent behind that; the reader of the sums (scan_tile_sums, k_scan_tiled) uses
+// agent-scope loads, which pass the caches that are not shared.  That is how gfx950 carries these instructions out, not a promise
+// of the language's memory model for relaxed accesses.
 __device__ __forceinline__ bool tile_sum_done(int64_t sum, int64_t* first, Ctl* ctl) {
   // the exchange has been performed when its result is here; the block counts itself behind it
   const unsigned long long old = atomicExch(reinterpret_cast<unsigned long long*>(first), (unsigned long long)sum);

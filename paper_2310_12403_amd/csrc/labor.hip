@@ -983,8 +983,8 @@ __global__ __launch_bounds__(BLOCK) void k_labor_fill_staged(LayerChunks ch, Cou
   const int sub = (int)(idx & ((1 << kFillLanesLog2) - 1));
   // A row may hold its entries in any order (the pieces of a cut list, the lists found from the other side and the
   // blended passes take slots by atomics): an entry's place is its rank by list position.  The lane group (all in one
-  // wave) shares the positions through LDS.  Rows that happen to be in order go the same way: two paths side by side
-  // in a wave cost more than ranking a dozen entries.
+  // wave) shares the positions through LDS.  The rows that k_labor_scan_plain leaves in list order, those of uncut lists, go the
+  // same way: two paths side by side in a wave cost more than ranking a dozen entries.
   uint32_t* js = row_j[threadIdx.x >> kFillLanesLog2];
   constexpr int kPerLane = kWave >> kFillLanesLog2;
   StageEntry mine[kPerLane];

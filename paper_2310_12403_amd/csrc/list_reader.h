@@ -1,4 +1,4 @@
-// A neighbour list on its way to a wave: what the traversals with c = 0 read (k_ns_fill, k_labor_scan_plain).
+// A neighbour list on its way to a wave: what the traversals read (k_ns_fill, k_labor_scan_plain, and blend_scan.h with c > 0).
 #pragma once
 #include "device_utils.h"
 #include "variates.h"

@@ -220,7 +220,9 @@ __device__ __forceinline__ uint32_t ns_collect_plain(ListReader<kFillGroups>& L,
 #pragma unroll
         for (int e = 0; e < 4; ++e) to = lanes_below_plus(m[e], to);
         const uint32_t j = j0 + g * kGroup + lane * 4;
-        if (n_c + kGroup <= cap + (uint32_t)kWave) {  // (whatever the group holds fits: n_c < 64 and cap >= 256)
+        // (Whatever the group holds then fits the cap + kWave slots.  Those from cap on are the idle lanes' as well, who may write over
+        // a candidate there: nobody looks at it, since with more than cap candidates the list is collected again.)
+        if (n_c + kGroup <= cap + (uint32_t)kWave) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             NsSlot* s = slot + (lane_in(m[e]) ? to : idle);
@@ -346,7 +348,7 @@ __device__ __forceinline__ uint32_t ns_collect(const int32_t* __restrict__ g_ind
     const uint32_t vec_end = total & ~3u;          // whole groups end here
     const uint32_t vec_beg = head ? 4u : 0u;       // whole groups start here
     const int32_t* __restrict__ p = g_indices + abeg;
-    // (no loads of the next step before this step's entries are hashed, as with c = 0: the registers are needed more)
+    // (no loads of the next step before this step's entries are hashed: the registers are needed more)
     // the ragged ends (lanes 0..2: the entries in front of the first whole group; lanes 3..5: those behind the last one) are
     // requested now, not when the whole groups are done, so that a short list waits for memory once
     const uint32_t end_pos = lane < 3 ? head + lane : vec_end + (lane - 3);
