@@ -1273,6 +1273,34 @@ def test_ns_lists_kept_whole(P, size, kappa):
         compare(P, g, seeds, (k,), R.NS, it=kappa - 1, kappa=kappa, seed=k)
 
 
+@pytest.mark.parametrize("aligned", [True, False])
+@pytest.mark.parametrize("size", [700, 70001])
+def test_blended_labor_lists_kept_whole(P, size, aligned):
+    """LABOR-0 with dependent variates over lists that no layer, one layer or every layer of a scan keeps whole: shorter and longer than
+    the lanes a destination has, and than a staging row, whose overflow is counted once per wave."""
+    n = 70001
+    rng = np.random.default_rng(29)
+    deg = rng.integers(0, 10, n)
+    at = np.arange(0, n, 53)
+    deg[at] = np.array([15, 16, 17, 31, 33, 63, 64, 65, 127, 128, 129, 257, 400, 513])[np.arange(len(at)) % 14]
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    g = G(P, torch.from_numpy(indptr), torch.from_numpy(rng.integers(0, n, int(indptr[-1])).astype(np.int32)))
+    if not aligned:
+        base = torch.empty(len(g.indices_h) + 1, dtype=torch.int32, device="cuda")
+        base[1:] = g.indices_d
+        g.graph = P.coop_graph_load(g.indptr_d, base[1:], P.COOP_VALIDATE)
+    seeds = at[:size] if size < 1000 else np.arange(size)
+    P.coop_tune(P.COOP_TUNE_FUSE_LAYERS, 2)
+    try:
+        for fanouts in ((30,), (64,), (128,), (600,), (16, 128), (128, 16), (600, 600)):
+            compare(P, g, seeds, fanouts, R.LABOR0, it=2, kappa=4, seed=fanouts[0])
+        P.coop_tune(P.COOP_TUNE_STAGE_CAP, 16)
+        compare(P, g, seeds, (30, 128), R.LABOR0, it=2, kappa=4, seed=5)
+    finally:
+        P.coop_tune(P.COOP_TUNE_STAGE_CAP, 0)
+        P.coop_tune(P.COOP_TUNE_FUSE_LAYERS, 1)
+
+
 @pytest.mark.parametrize("size", [300, 40000])
 def test_ns_lists_around_the_groups_in_flight(P, size):
     """Lists of one to three times as many groups of 256 entries as are in flight, one entry less and one more, with and without a
