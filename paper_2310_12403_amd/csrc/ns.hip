@@ -1273,9 +1273,9 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
         // Lanes per destination in the selection: as many as hold the candidates of most (a tenth more pass the filters than are
         // expected; 250 thousand destinations with 15 expected: 112 us with 64 lanes and a wave for each, 49 with 32 and eight a wave).
         const int group_log2 = target <= 10 ? 4 : target <= 24 ? 5 : 6;
-        // (A destination to itself where more candidates than lanes are expected: some 10 us each, one after the other.  Fanout 200, 90
-        // thousand lists, twelve of them long: 3.51 ms with eight a wave, 3.41.)
-        const int select_log2 = target > (uint32_t)kWave ? 0 : each_log2 > 6 - group_log2 ? each_log2 : 6 - group_log2;
+        // (Also where more candidates than lanes are expected: a wave for each of 400 thousand destinations whose lists are shorter than
+        // a fanout of 60 cost 91 us, eight a wave 32; over longer lists, 65,536 to 262,144 of them, fanout 200, no difference but noise.)
+        const int select_log2 = each_log2 > 6 - group_log2 ? each_log2 : 6 - group_log2;
         uint32_t* n_cand_b = n_cand + b;
         int lists_log2 = 0;
         while (lists_log2 < 6 && (n >> (lists_log2 + 1)) >= kNsRedoWaves) ++lists_log2;
