@@ -186,14 +186,16 @@ struct UniqueWork {
   int64_t n_buckets = 0;
   uint32_t part_blocks = 0;          // blocks of the partition whose stretches those are (0: stretches of fixed length)
   int path = 0;
+  bool tagged = false;
   Publish pub{};
   int64_t n_new = 0;
   uint64_t* clear = nullptr;         // words that a kernel in front of `launch` may set to zero; whoever does sets this to null, ...
   int64_t n_clear = 0;
   bool bits = false;                 // ... and then the first positions are marked in them as they are found
 };
-// prepare: decides how the list is deduplicated and allocates the words of new-vertex bits.
-int unique_prepare(int64_t n_dst, int64_t m, UniqueWork* w, Alloc& alloc);
+// prepare: decides how the list is deduplicated and allocates the words of new-vertex bits.  `tagged`: the kernels that write the
+// edges can leave every source's tag in `spare`, and do so if w->tagged says that the dedup reads them.
+int unique_prepare(int64_t n_dst, int64_t m, bool tagged, UniqueWork* w, Alloc& alloc);
 // launch: every kernel of the front half; one of them sends the sizes to the host; does not wait.  col_local (m entries)
 // holds intermediate results until `back` has run, and so does `spare` (n_dst + m entries, e.g. the array that will be
 // src_ids) when it is not null.

@@ -34,6 +34,10 @@ __device__ __forceinline__ uint32_t lanes_below_plus(uint64_t mask, uint32_t bas
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, base));
 }
 
+// A source's tag: the highest byte of the hash by which the dedup of a short list deals the vertices to buckets (unique.hip).
+constexpr uint32_t kSourceHash = 0x9E3779B9u;
+__device__ __forceinline__ uint32_t source_tag(uint32_t key) { return key * kSourceHash >> 24; }
+
 // wave-wide inclusive sum of a uint32 (all lanes get their prefix)
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
 #pragma unroll
@@ -41,6 +45,12 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
     uint32_t o = __shfl_up(v, off, kWave);
     if (lane_id() >= off) v += o;
   }
+  return v;
+}
+
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
   return v;
 }
 

@@ -985,7 +985,7 @@ constexpr int kFillOwnBlock = 1024;  // where a block adds up the counts in fron
 // (edge_limit: entries of col_global / eid; nothing is written beyond them)
 template <bool OWN, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_labor_fill_staged(LayerChunks ch, CountOffsets co, int64_t first, int64_t n_dst, uint32_t stage_cap,
-                                                             int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit) {
+                                                             EdgeOut edges, int64_t edge_limit) {
   __shared__ uint32_t row_j[BLOCK >> kFillLanesLog2][kWave];  // list positions of one staged row per lane group
   const int64_t idx = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   const int64_t w = first + (idx >> kFillLanesLog2);
@@ -1018,11 +1018,10 @@ __global__ __launch_bounds__(BLOCK) void k_labor_fill_staged(LayerChunks ch, Cou
   for (int i = 0; i < kPerLane; ++i) {
     const int slot = sub + (i << kFillLanesLog2);
     if (slot >= c) break;
-    int64_t place = 0;
+    uint32_t place = 0;
     for (int q = 0; q < c; ++q) place += js[q] < mine[i].j;
-    if (o + place < edge_limit) {
-      col_global[o + place] = mine[i].t;
-      eid[o + place] = g.beg + mine[i].j;
+    if (o + (int64_t)place < edge_limit) {
+      put_edge(edges, o, place, mine[i].t, g.beg + mine[i].j);
     }
   }
 }
@@ -1031,8 +1030,7 @@ __global__ __launch_bounds__(BLOCK) void k_labor_fill_staged(LayerChunks ch, Cou
 template <bool BLEND>
 __global__ __launch_bounds__(kBlock) void k_labor_fill_overflow(const int32_t* __restrict__ g_indices, LayerChunks ch, int64_t first, int64_t n_dst,
                                                                 LayerKeys K, double cw, double sw, uint32_t stage_cap,
-                                                                const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
-                                                                int64_t* __restrict__ eid) {
+                                                                const int64_t* __restrict__ eptr, EdgeOut edges) {
   const int64_t w = first + (int64_t)blockIdx.x * kWavesPerBlock + uniform_wave_in_block();
   if (w >= n_dst) return;
   const int64_t o = eptr[w];
@@ -1042,8 +1040,7 @@ __global__ __launch_bounds__(kBlock) void k_labor_fill_overflow(const int32_t* _
   const Segment g = ch.seg[p][local];
   const uint32_t thr = ch.thr[p][local];
   labor_scan_ordered<BLEND>(g_indices, g.beg, g.d, thr, K, cw, sw, [&](uint32_t rank, int32_t t, uint32_t j) {
-    col_global[o + rank] = t;
-    eid[o + rank] = g.beg + j;
+    put_edge(edges, o, rank, t, g.beg + j);
   });
 }
 
@@ -1339,17 +1336,18 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
   blk->col_local = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
 
+  const EdgeOut edges{blk->col_global, blk->eid, cx.tags};
   if (m > 0 && n_dst > 0) {
     constexpr int64_t kSliceRows = kSliceLists << (6 - kFillLanesLog2);
     const CountOffsets co{counts, blk->indptr, &cx.d_ctl->total_edges};
     if (own)
       COOP_LAUNCH(K_LABOR_FILL, (k_labor_fill_staged<true, kFillOwnBlock>), dim3(blocks_for(n_dst << kFillLanesLog2, kFillOwnBlock)), dim3(kFillOwnBlock),
-                  0, s, ch, co, (int64_t)0, n_dst, cap, blk->col_global, blk->eid, m);
+                  0, s, ch, co, (int64_t)0, n_dst, cap, edges, m);
     else
       for (int64_t b = 0; b < n_dst; b += kSliceRows)
         COOP_LAUNCH(K_LABOR_FILL, (k_labor_fill_staged<false, kBlock>),
                     dim3(blocks_for((n_dst - b < kSliceRows ? n_dst - b : kSliceRows) << kFillLanesLog2, kBlock)), dim3(kBlock), 0, s, ch, co, b, n_dst,
-                    cap, blk->col_global, blk->eid, m);
+                    cap, edges, m);
     if (!defer && cx.h_ctl->n_overflow > 0) {
       LayerKeys K{};
       layer_keys(cx.seed, COOP_LABOR0, l, cx.group, K.Ka);
@@ -1358,10 +1356,10 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
         const dim3 grid(blocks_for(n_dst - b < kSliceLists ? n_dst - b : kSliceLists, kWavesPerBlock));
         if (cx.blend)
           COOP_LAUNCH(K_LABOR_OVERFLOW, k_labor_fill_overflow<true>, grid, dim3(kBlock), 0, s, cx.g->indices, ch, b, n_dst, K, cx.cw, cx.sw,
-                      cap, blk->indptr, blk->col_global, blk->eid);
+                      cap, blk->indptr, edges);
         else
           COOP_LAUNCH(K_LABOR_OVERFLOW, k_labor_fill_overflow<false>, grid, dim3(kBlock), 0, s, cx.g->indices, ch, b, n_dst, K, cx.cw, cx.sw,
-                      cap, blk->indptr, blk->col_global, blk->eid);
+                      cap, blk->indptr, edges);
       }
     }
   }

@@ -431,7 +431,7 @@ __device__ __forceinline__ uint32_t ns_rank_of(uint32_t n_c, const NsSlot* slot,
 // 4,431, 412 and 1,196.  30 such lists with fanout 1,000: 2,461 and 73, c > 0 2,792 and 410.)
 template <bool ORDERED>
 __device__ __forceinline__ void ns_rank_write_many(uint32_t n_c, uint32_t k, uint32_t bound, NsSlot* slot, int64_t o, int64_t beg,
-                                                   int32_t* __restrict__ col_global, int64_t* __restrict__ eid) {
+                                                   EdgeOut edges) {
   const uint32_t lane = (uint32_t)lane_id();
   auto settle = [] {
     __builtin_amdgcn_wave_barrier();
@@ -482,8 +482,7 @@ __device__ __forceinline__ void ns_rank_write_many(uint32_t n_c, uint32_t k, uin
     placed += (uint32_t)__popcll(m);
     if (ORDERED) {
       if (keep) {
-        (col_global + o)[place] = c.t;
-        (eid + o)[place] = beg + c.j;
+        put_edge(edges, o, place, c.t, beg + c.j);
       }
     } else {
       settle();
@@ -502,8 +501,7 @@ __device__ __forceinline__ void ns_rank_write_many(uint32_t n_c, uint32_t k, uin
 #pragma unroll 4
     for (uint32_t q = 0; q < k; ++q) place += slot[q].j < my_j;
     if (i < k) {
-      (col_global + o)[place] = slot[i].t;
-      (eid + o)[place] = beg + my_j;
+      put_edge(edges, o, place, slot[i].t, beg + my_j);
     }
   }
 }
@@ -522,8 +520,7 @@ __device__ __forceinline__ uint64_t ns_smallest(uint32_t r, uint64_t has, uint32
   }
 }
 // (after ns_collect_plain: the candidates stand in list order, and their variates are evaluated here)
-__device__ __forceinline__ void ns_rank_write_plain(uint32_t n_c, uint32_t k, uint32_t bound, const NsKeys& K, NsSlot* slot, int64_t o, int64_t beg, int32_t* __restrict__ col_global,
-                                                    int64_t* __restrict__ eid) {
+__device__ __forceinline__ void ns_rank_write_plain(uint32_t n_c, uint32_t k, uint32_t bound, const NsKeys& K, NsSlot* slot, int64_t o, int64_t beg, EdgeOut edges) {
   const uint32_t lane = (uint32_t)lane_id();
   __builtin_amdgcn_wave_barrier();
   __threadfence_block();
@@ -543,24 +540,22 @@ __device__ __forceinline__ void ns_rank_write_plain(uint32_t n_c, uint32_t k, ui
     }
     if (lane_in(kept)) {
       const uint32_t place = lanes_below(kept);
-      (col_global + o)[place] = t;
-      (eid + o)[place] = beg + j;
+      put_edge(edges, o, place, t, beg + j);
     }
     return;
   }
   for (uint32_t i = lane; i < n_c; i += kWave) slot[i].r = ns_uniform(K, (uint32_t)slot[i].t);
   __builtin_amdgcn_wave_barrier();
   __threadfence_block();
-  ns_rank_write_many<true>(n_c, k, bound, slot, o, beg, col_global, eid);
+  ns_rank_write_many<true>(n_c, k, bound, slot, o, beg, edges);
 }
-__device__ __forceinline__ void ns_rank_write(uint32_t n_c, uint32_t k, uint32_t bound, NsSlot* slot, int64_t o, int64_t beg, int32_t* __restrict__ col_global,
-                                              int64_t* __restrict__ eid) {
+__device__ __forceinline__ void ns_rank_write(uint32_t n_c, uint32_t k, uint32_t bound, NsSlot* slot, int64_t o, int64_t beg, EdgeOut edges) {
   const uint32_t lane = (uint32_t)lane_id();
   if (n_c <= (uint32_t)kWave) ns_pad(n_c, slot);
   __builtin_amdgcn_wave_barrier();
   __threadfence_block();
   if (n_c > (uint32_t)kWave) {
-    ns_rank_write_many<false>(n_c, k, bound, slot, o, beg, col_global, eid);
+    ns_rank_write_many<false>(n_c, k, bound, slot, o, beg, edges);
     return;
   }
   const bool has = lane < n_c;
@@ -577,8 +572,7 @@ __device__ __forceinline__ void ns_rank_write(uint32_t n_c, uint32_t k, uint32_t
     place += (uint32_t)__builtin_amdgcn_readlane((int)my_j, q) < my_j;
   }
   if (keep) {
-    col_global[o + place] = my_t;
-    eid[o + place] = beg + my_j;
+    put_edge(edges, o, place, my_t, beg + my_j);
   }
 }
 
@@ -616,12 +610,11 @@ __device__ __forceinline__ bool ns_next_bound(uint32_t n_c, uint32_t k, uint32_t
 // 1,500 entries 1.99 ms with eight lanes for each, 1.51 so; a thousand lists of a papers100M shape 74 us with a load at a time, 61 with
 // eight in flight.)
 __device__ __forceinline__ void ns_copy_whole(const int32_t* __restrict__ g_indices, const NsRecord& g, int64_t o, bool whole, uint32_t k, int each_log2,
-                                              int32_t* __restrict__ col_global, int64_t* __restrict__ eid) {
+                                              EdgeOut edges) {
   const uint32_t lane = (uint32_t)lane_id(), lanes = 64u >> each_log2, sub = lane & (lanes - 1);
   if (whole && g.d <= 4 * lanes) {
     for (uint32_t j = sub; j < g.d; j += lanes) {
-      (col_global + o)[j] = (g_indices + g.beg)[j];
-      (eid + o)[j] = g.beg + j;
+      put_edge(edges, o, j, (g_indices + g.beg)[j], g.beg + j);
     }
   }
   if (k <= 4 * lanes) return;
@@ -633,8 +626,7 @@ __device__ __forceinline__ void ns_copy_whole(const int32_t* __restrict__ g_indi
     const int64_t beg = of64(g.beg, at), to = of64(o, at);
 #pragma unroll 8
     for (uint32_t j = lane; j < d; j += kWave) {
-      (col_global + to)[j] = (g_indices + beg)[j];
-      (eid + to)[j] = beg + j;
+      put_edge(edges, to, j, (g_indices + beg)[j], beg + j);
     }
   }
 }
@@ -647,7 +639,7 @@ __device__ __forceinline__ void ns_copy_whole(const int32_t* __restrict__ g_indi
 // and 159 M (the entries alone, at the rate of a copy: 310).
 __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict__ g_indices, const NsRecord* __restrict__ rec, uint32_t n_dst, uint32_t k,
                                                     uint32_t cap, LayerKeys keys, int64_t* indptr, int64_t first, int tile_log2,
-                                                    int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl,
+                                                    EdgeOut edges, int64_t edge_limit, Ctl* ctl,
                                                     uint32_t long_min, const uint32_t* __restrict__ long_list,
                                                     const uint32_t* __restrict__ n_long, int long_blocks, int each_log2, uint32_t stretch) {
   extern __shared__ __align__(16) uint32_t lds_words[];  // cap slots, and one per lane
@@ -675,7 +667,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
   // (longer than skip_above: queued, one of the first waves takes it)
   if (speaks && (g.d <= k || g.d <= skip_above)) ns_settle_offset(indptr, first + w, tile_log2, o);
   const bool live = mine && g.d != 0 && o_end <= edge_limit;  // (no room: the caller redoes the layer)
-  ns_copy_whole(g_indices, g, o, live && g.d <= k, k, each_log2, col_global, eid);
+  ns_copy_whole(g_indices, g, o, live && g.d <= k, k, each_log2, edges);
   if (k > kNsMaxSelect) return;  // degrees above a fanout that the candidate buffer cannot serve: left to k_ns_fill_wide
   uint64_t todo = ballot64(live && speaks && g.d > k && g.d <= skip_above);
   if (todo == 0) return;
@@ -712,7 +704,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
       hi = 0xFFFFFFFFu;
     }
     L = ListReader<kFillGroups>(g_indices + beg + j0, d - j0 < stretch ? d - j0 : stretch);
-    if (select) ns_rank_write_plain(found, k, bound_done, K, slot, o_done, beg_done, col_global, eid);
+    if (select) ns_rank_write_plain(found, k, bound_done, K, slot, o_done, beg_done, edges);
     if (todo == 0) break;
     __builtin_amdgcn_wave_barrier();
   }
@@ -722,8 +714,7 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
 template <bool VEC4>
 __device__ __forceinline__ void ns_redo_one(int64_t w, int wib, uint32_t* lds_words, NsQueue* queue, const int32_t* __restrict__ g_indices,
                                             const NsRecord* __restrict__ rec, const NsBlendThr* __restrict__ bthr, uint32_t k, uint32_t cap,
-                                            const VariateParams& vp, const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
-                                            int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl) {
+                                            const VariateParams& vp, const int64_t* __restrict__ eptr, EdgeOut edges, int64_t edge_limit, Ctl* ctl) {
   const int64_t o = eptr[w];
   const NsRecord g = rec[w];
   if (g.d <= k || k > kNsMaxSelect) return;  // (never marked)
@@ -744,7 +735,7 @@ __device__ __forceinline__ void ns_redo_one(int64_t w, int wib, uint32_t* lds_wo
     if (lane_id() == 0) atomicOr(&ctl->err_capacity, 1);
     return;
   }
-  ns_rank_write(n_c, k, bound, slot, o, g.beg, col_global, eid);
+  ns_rank_write(n_c, k, bound, slot, o, g.beg, edges);
 }
 
 // c > 0: the destinations that the two kernels below leave over.  A wave looks at 2^lists_log2 marks at once.  (Six waves per
@@ -755,8 +746,7 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_redo(const int32_t* __restrict_
                                                     const NsRecord* __restrict__ rec, const NsBlendThr* __restrict__ bthr,
                                                     int64_t n_dst, uint32_t k,
                                                     uint32_t cap, int waves_per_block, VariateParams vp,
-                                                    const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
-                                                    int64_t* __restrict__ eid, int64_t edge_limit, Ctl* ctl,
+                                                    const int64_t* __restrict__ eptr, EdgeOut edges, int64_t edge_limit, Ctl* ctl,
                                                     const uint32_t* __restrict__ n_cand, int lists_log2) {
   extern __shared__ __align__(16) uint32_t lds_words[];  // per wave as above, and a queue behind all of them
   NsQueue* queues = reinterpret_cast<NsQueue*>(lds_words + (size_t)waves_per_block * cap * 4);
@@ -768,7 +758,7 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_redo(const int32_t* __restrict_
   while (left != 0) {
     const int64_t w = w0 + __builtin_ctzll(left);
     left &= left - 1;
-    ns_redo_one<VEC4>(w, wib, lds_words, &queues[wib], g_indices, rec, bthr, k, cap, vp, eptr, col_global, eid, edge_limit, ctl);
+    ns_redo_one<VEC4>(w, wib, lds_words, &queues[wib], g_indices, rec, bthr, k, cap, vp, eptr, edges, edge_limit, ctl);
     __builtin_amdgcn_wave_barrier();
   }
 }
@@ -797,8 +787,7 @@ struct NsSink {
 
 __global__ __launch_bounds__(kWave, 7) void k_ns_collect(const int32_t* __restrict__ g_indices, const NsRecord* __restrict__ rec,
                                                          const NsBlendThr* __restrict__ bthr, uint32_t n_dst, uint32_t k, LayerKeys keys, float cw,
-                                                         float sw, int64_t* indptr, int64_t first, int tile_log2, int32_t* __restrict__ col_global,
-                                                         int64_t* __restrict__ eid, int64_t edge_limit, StageEntry* __restrict__ rows, uint32_t row_cap,
+                                                         float sw, int64_t* indptr, int64_t first, int tile_log2, EdgeOut edges, int64_t edge_limit, StageEntry* __restrict__ rows, uint32_t row_cap,
                                                          uint32_t* __restrict__ n_cand, uint32_t long_min, const uint32_t* __restrict__ long_list,
                                                          const uint32_t* __restrict__ n_long, int long_blocks, int each_log2, uint32_t stretch) {
   __shared__ BlendQueue<true> queue;
@@ -825,7 +814,7 @@ __global__ __launch_bounds__(kWave, 7) void k_ns_collect(const int32_t* __restri
   const bool mine = number < n_mine && (g.d <= k || g.d <= skip_above), speaks = mine && sub == 0;  // (the others: queued)
   if (speaks) ns_settle_offset(indptr, first + w, tile_log2, o);
   const bool live = mine && g.d != 0 && o_end <= edge_limit;  // (no room: the caller redoes the layer)
-  ns_copy_whole(g_indices, g, o, live && g.d <= k, k, each_log2, col_global, eid);
+  ns_copy_whole(g_indices, g, o, live && g.d <= k, k, each_log2, edges);
   const bool sampled = live && g.d > k && k <= kNsMaxSelect;  // (a larger fanout: k_ns_fill_wide)
   BlendScan<1, true, NsSink> S;
   S.queue = &queue;
@@ -895,7 +884,7 @@ __global__ __launch_bounds__(kWave, 7) void k_ns_collect(const int32_t* __restri
 
 // One destination's candidates, by the whole wave (n = n_cand[w], not 0).
 __device__ __forceinline__ void ns_select_one(int64_t w, uint32_t n, NsSlot* slot, const NsRecord* __restrict__ rec, uint32_t k, const VariateParams& vp,
-                                              const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global, int64_t* __restrict__ eid,
+                                              const int64_t* __restrict__ eptr, EdgeOut edges,
                                               const StageEntry* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand,
                                               const NsBlendThr* __restrict__ bthr) {
   const uint32_t lane = (uint32_t)lane_id();
@@ -961,8 +950,7 @@ __device__ __forceinline__ void ns_select_one(int64_t w, uint32_t n, NsSlot* slo
     }
     if (keep) {
       const int64_t o = eptr[w];
-      col_global[o + place] = c.t;
-      eid[o + place] = g.beg + c.j;
+      put_edge(edges, o, place, c.t, g.beg + c.j);
     }
     return;
   }
@@ -987,7 +975,7 @@ __device__ __forceinline__ void ns_select_one(int64_t w, uint32_t n, NsSlot* slo
     if (lane == 0) n_cand[w] = kNsRedo;
     return;
   }
-  ns_rank_write(n_c, k, g.bound, slot, eptr[w], g.beg, col_global, eid);
+  ns_rank_write(n_c, k, g.bound, slot, eptr[w], g.beg, edges);
 }
 
 
@@ -995,7 +983,7 @@ __device__ __forceinline__ void ns_select_one(int64_t w, uint32_t n, NsSlot* slo
 // than that follow one by one.  (As ns_select_one, whose comments say why; a destination per wave had 15 to 35 of its lanes at
 // work, and starting a wave for each took a third of the time.)
 __global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restrict__ rec, int64_t n_dst, uint32_t k, VariateParams vp,
-                                                     const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global, int64_t* __restrict__ eid,
+                                                     const int64_t* __restrict__ eptr, EdgeOut edges,
                                                      const StageEntry* __restrict__ rows, uint32_t row_cap, uint32_t* __restrict__ n_cand,
                                                      const NsBlendThr* __restrict__ bthr, int each_log2, int group_log2) {
   extern __shared__ __align__(16) uint32_t lds_words[];  // slots for ns_select_one, at least kWave
@@ -1095,8 +1083,7 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restri
       if (keep) {
         uint32_t place = 0;
         for (uint32_t q = 0; q < k; ++q) place += j_of[at0 + q] < c.j;
-        col_global[o + place] = c.t;
-        eid[o + place] = beg + c.j;
+        put_edge(edges, o, place, c.t, beg + c.j);
       }
     }
     while (many != 0) {
@@ -1104,7 +1091,7 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restri
       many &= many - 1;
       const int64_t w_q = w0 + (q >> group_log2);
       settle();
-      ns_select_one(w_q, (uint32_t)__builtin_amdgcn_readlane((int)all_n, (int)(w_q - w_first)), slot, rec, k, vp, eptr, col_global, eid, rows, row_cap, n_cand, bthr);
+      ns_select_one(w_q, (uint32_t)__builtin_amdgcn_readlane((int)all_n, (int)(w_q - w_first)), slot, rec, k, vp, eptr, edges, rows, row_cap, n_cand, bthr);
     }
     settle();
   }
@@ -1120,7 +1107,7 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restri
 template <bool BLEND>
 __global__ __launch_bounds__(kBlock) void k_ns_fill_wide(const int32_t* __restrict__ g_indices, const NsRecord* __restrict__ rec,
                                                          int64_t n_dst, uint32_t k, VariateParams vp, const int64_t* __restrict__ eptr,
-                                                         int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit) {
+                                                         EdgeOut edges, int64_t edge_limit) {
   const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + uniform_wave_in_block();
   if (w >= n_dst) return;
   const NsRecord g = rec[w];
@@ -1166,8 +1153,7 @@ __global__ __launch_bounds__(kBlock) void k_ns_fill_wide(const int32_t* __restri
     const uint64_t keep_mask = ballot64(keep);
     if (keep) {
       const uint32_t at = placed + lanes_below(keep_mask);  // below k: exactly k entries are kept
-      col_global[o + at] = t;
-      eid[o + at] = g.beg + j;
+      put_edge(edges, o, at, t, g.beg + j);
     }
     placed += (uint32_t)__popcll(keep_mask);
     ties += (uint32_t)__popcll(eq_mask);
@@ -1237,6 +1223,7 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
   blk->eid = alloc.get<int64_t>(m, COOP_TAG_OUTPUT);
   blk->col_local = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
+  const EdgeOut edges{blk->col_global, blk->eid, cx.tags};
   if (m > 0 && n_dst > 0) {
     // one wave per block: a block leaves the CU when its slowest wave is done, and a wave takes one list, short or long;
     // with four waves a block's slots stood empty for much of its life (fill 1.61 -> 1.52 ms on the papers100M-shaped
@@ -1267,7 +1254,7 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
       const NsRecord* rec_b = rec + b;
       const NsBlendThr* bthr_b = cx.blend ? bthr + b : nullptr;
       const int64_t* eptr_b = blk->indptr + b;
-#define COOP_NS_ARGS cx.g->indices, rec_b, bthr_b, n, k, cap, wpb, vp, eptr_b, blk->col_global, blk->eid, m
+#define COOP_NS_ARGS cx.g->indices, rec_b, bthr_b, n, k, cap, wpb, vp, eptr_b, edges, m
       if (cx.blend) {
         StageEntry* rows_b = rows + b * (int64_t)row_cap;
         // Lanes per destination in the selection: as many as hold the candidates of most (a tenth more pass the filters than are
@@ -1281,10 +1268,10 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
         while (lists_log2 < 6 && (n >> (lists_log2 + 1)) >= kNsRedoWaves) ++lists_log2;
         const dim3 grid_redo(blocks_for(n, (int64_t)wpb << lists_log2));
         COOP_LAUNCH(K_NS_FILL, k_ns_collect, dim3(blocks_for(n, (int64_t)1 << each_log2) + (unsigned)long_blocks), dim3(kWave), 0, s, cx.g->indices,
-                    rec_b, bthr_b, (uint32_t)n, k, vp.K, (float)vp.cw, (float)vp.sw, blk->indptr, b, tile_log2, blk->col_global, blk->eid, m, rows_b,
+                    rec_b, bthr_b, (uint32_t)n, k, vp.K, (float)vp.cw, (float)vp.sw, blk->indptr, b, tile_log2, edges, m, rows_b,
                     row_cap, n_cand_b, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2, (uint32_t)g_stretch);
         COOP_LAUNCH(K_NS_SELECT, k_ns_select, dim3(blocks_for(n, (int64_t)1 << select_log2)), dim3(kWave), (size_t)cap * sizeof(NsSlot), s, rec_b, n, k, vp,
-                    eptr_b, blk->col_global, blk->eid, (const StageEntry*)rows_b, row_cap, n_cand_b, bthr_b, select_log2, group_log2);
+                    eptr_b, edges, (const StageEntry*)rows_b, row_cap, n_cand_b, bthr_b, select_log2, group_log2);
 #define COOP_NS_BLEND(VEC4) \
   COOP_LAUNCH(K_NS_FILL, k_ns_redo<VEC4>, grid_redo, dim3(wpb * kWave), shmem, s, COOP_NS_ARGS, cx.d_ctl, (const uint32_t*)n_cand_b, lists_log2)
         if (cx.vec4) { COOP_NS_BLEND(true); } else { COOP_NS_BLEND(false); }
@@ -1292,15 +1279,15 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
       } else {
         COOP_LAUNCH(K_NS_FILL, k_ns_fill, dim3(blocks_for(n, (int64_t)1 << each_log2) + (unsigned)long_blocks), dim3(kWave),
                     (cap + kWave) * sizeof(NsSlot), s, cx.g->indices, rec_b, (uint32_t)n, k, cap, vp.K, blk->indptr, b, tile_log2,
-                    blk->col_global, blk->eid, m, cx.d_ctl, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2,
+                    edges, m, cx.d_ctl, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2,
                     (uint32_t)g_stretch);
       }
 #undef COOP_NS_ARGS
       if (k > kNsMaxSelect) {  // the lists longer than such a fanout (the kernels above skip them)
         if (cx.blend) COOP_LAUNCH(K_NS_FILL, k_ns_fill_wide<true>, grid_w, dim3(kBlock), 0, s, cx.g->indices, rec_b, n, k, vp, eptr_b,
-                                  blk->col_global, blk->eid, m);
+                                  edges, m);
         else COOP_LAUNCH(K_NS_FILL, k_ns_fill_wide<false>, grid_w, dim3(kBlock), 0, s, cx.g->indices, rec_b, n, k, vp, eptr_b,
-                         blk->col_global, blk->eid, m);
+                         edges, m);
       }
     }
   }

@@ -295,7 +295,7 @@ __global__ __launch_bounds__(kBlock) void k_rw_walk_wide(const int64_t* __restri
 constexpr int kRwFillLog2 = 3;
 template <bool OWN, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_rw_fill(const StageEntry* __restrict__ rows, CountOffsets co, uint32_t k_eff, int64_t first, int64_t n_dst,
-                                                   int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit) {
+                                                   EdgeOut edges, int64_t edge_limit) {
   const int64_t w = first + (((int64_t)blockIdx.x * BLOCK + threadIdx.x) >> kRwFillLog2);
   int32_t c;
   const int64_t o = offset_of<OWN, BLOCK, kRwFillLog2>(co, w, n_dst, &c);
@@ -303,8 +303,7 @@ __global__ __launch_bounds__(BLOCK) void k_rw_fill(const StageEntry* __restrict_
   const StageEntry* row = rows + (size_t)w * k_eff;
   for (int32_t slot = (int32_t)(threadIdx.x & ((1 << kRwFillLog2) - 1)); slot < c && o + slot < edge_limit; slot += 1 << kRwFillLog2) {
     const StageEntry e = row[slot];
-    col_global[o + slot] = e.t;
-    eid[o + slot] = (int64_t)e.j;
+    put_edge(edges, o, (uint32_t)slot, e.t, (int64_t)e.j);
   }
 }
 
@@ -312,7 +311,7 @@ __global__ __launch_bounds__(BLOCK) void k_rw_fill(const StageEntry* __restrict_
 // eight lanes; a thousand 8.8 and 11.5)
 constexpr uint32_t kRwFillNarrow = 64;
 __global__ __launch_bounds__(kBlock) void k_rw_fill_wide(const StageEntry* __restrict__ rows, CountOffsets co, uint32_t k_eff, int64_t first,
-                                                         int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit) {
+                                                         EdgeOut edges, int64_t edge_limit) {
   const int64_t w = first + blockIdx.x;
   const int32_t c = co.cnt.ptr[0][w];
   const int64_t tile = w >> kOffsetTileLog2 << kOffsetTileLog2, o = co.indptr[tile] + (w != tile ? co.indptr[w] : 0);
@@ -323,8 +322,7 @@ __global__ __launch_bounds__(kBlock) void k_rw_fill_wide(const StageEntry* __res
   for (int32_t slot = (int32_t)threadIdx.x; slot < c; slot += kBlock) {
     const StageEntry e = row[slot];
     if (o + slot < edge_limit) {
-      col_global[o + slot] = e.t;
-      eid[o + slot] = (int64_t)e.j;
+      put_edge(edges, o, (uint32_t)slot, e.t, (int64_t)e.j);
     }
   }
 }
@@ -393,19 +391,20 @@ int rw_layer(const SampleCtx& cx, const RwConfig& rw, int l, const int32_t* dst,
   blk->col_local = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
   if (m > 0 && n_dst > 0) {
+    const EdgeOut edges{blk->col_global, blk->eid, cx.tags};
     const CountOffsets co{counts, blk->indptr, &cx.d_ctl->total_edges};
     constexpr int64_t kSliceRows = kSliceLists << (6 - kRwFillLog2);  // (a launch has fewer than 2^32 threads)
     if (own)
       COOP_LAUNCH(K_RW_FILL, (k_rw_fill<true, 1024>), dim3(blocks_for(n_dst << kRwFillLog2, 1024)), dim3(1024), 0, s, rows, co, rp.k_eff, (int64_t)0, n_dst,
-                  blk->col_global, blk->eid, m);
+                  edges, m);
     else if (rp.k_eff > kRwFillNarrow)
       for (int64_t b = 0; b < n_dst; b += kSliceLists / kWavesPerBlock)
         COOP_LAUNCH(K_RW_FILL, k_rw_fill_wide, dim3((unsigned)(n_dst - b < kSliceLists / kWavesPerBlock ? n_dst - b : kSliceLists / kWavesPerBlock)), dim3(kBlock),
-                    0, s, rows, co, rp.k_eff, b, blk->col_global, blk->eid, m);
+                    0, s, rows, co, rp.k_eff, b, edges, m);
     else
       for (int64_t b = 0; b < n_dst; b += kSliceRows)
         COOP_LAUNCH(K_RW_FILL, (k_rw_fill<false, kBlock>), dim3(blocks_for((n_dst - b < kSliceRows ? n_dst - b : kSliceRows) << kRwFillLog2, kBlock)),
-                    dim3(kBlock), 0, s, rows, co, rp.k_eff, b, n_dst, blk->col_global, blk->eid, m);
+                    dim3(kBlock), 0, s, rows, co, rp.k_eff, b, n_dst, edges, m);
   }
   return COOP_OK;
 }

@@ -217,15 +217,17 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
     int64_t n_src = 0;
     bool done = false, redone = false;
     if (edge_cap > 0) {
-      rc = unique_prepare(n_dst, edge_cap, &uw, alloc);
+      rc = unique_prepare(n_dst, edge_cap, true, &uw, alloc);
       if (rc != COOP_OK) break;
-      cx.clear = &uw;
-      rc = sample_layer(edge_cap);
-      cx.clear = nullptr;
-      if (rc != COOP_OK) break;
-      const int64_t* m_dev = &cx.d_ctl->total_edges;
       src = alloc.get<int32_t>(n_dst + edge_cap, COOP_TAG_OUTPUT);
       if (alloc.failed) { rc = COOP_E_NOMEM; break; }
+      cx.clear = &uw;
+      cx.tags = uw.tagged ? (uint8_t*)src : nullptr;  // (until S^{l+1} goes there)
+      rc = sample_layer(edge_cap);
+      cx.clear = nullptr;
+      cx.tags = nullptr;
+      if (rc != COOP_OK) break;
+      const int64_t* m_dev = &cx.d_ctl->total_edges;
       rc = unique_front_launch(dst, n_dst, blk.col_global, edge_cap, m_dev, blk.col_local, src, &uw, alloc, cx.d_ctl, h_ctl, s);
       if (rc != COOP_OK) break;
       // S^{l+1} and local ids (Eq. 2) are queued before the sizes are back, with room for the bound, so that the device
@@ -252,7 +254,7 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
       rc = sample_layer(0);
       if (rc != COOP_OK) break;
       if (n_dst + blk.n_edges >= ((int64_t)1 << 32) - 1) { rc = COOP_E_CAPACITY; break; }
-      rc = unique_prepare(n_dst, blk.n_edges, &uw, alloc);
+      rc = unique_prepare(n_dst, blk.n_edges, false, &uw, alloc);
       if (rc != COOP_OK) break;
       rc = unique_front_launch(dst, n_dst, blk.col_global, blk.n_edges, nullptr, blk.col_local, nullptr, &uw, alloc, cx.d_ctl, h_ctl, s);
       if (rc != COOP_OK) break;

@@ -1,6 +1,9 @@
 // Pieces shared by the sampling driver (sample.hip) and the two samplers (labor.hip, ns.hip).
 #pragma once
 #include "coop_internal.h"
+#ifdef __HIPCC__
+#include "device_utils.h"
+#endif
 #include "variates.h"
 
 namespace coop {
@@ -23,6 +26,7 @@ struct SampleCtx {
   bool blend;      // c > 0
   double cw, sw;   // cos(c pi/2), sin(c pi/2)
   bool vec4;       // the graph's indices array is 16-byte aligned
+  uint8_t* tags = nullptr;      // EdgeOut::tag
   UniqueWork* clear = nullptr;  // words that the layer's first kernel is to set to zero, if any (take_clear)
 };
 // The words to clear go to a kernel that is launched anyway, before anything else uses them.
@@ -36,6 +40,17 @@ static inline Clear take_clear(const SampleCtx& cx) {
 #ifdef __HIPCC__
 __device__ __forceinline__ void clear_words(const Clear& c) {  // every thread of the grid
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < c.n; i += (int64_t)gridDim.x * blockDim.x) c.p[i] = 0;
+}
+#endif
+
+// Where the kernels that write a layer's edges put them.  `tag` (or null): the tag of every edge's source, by which the dedup of a
+// short list tells the buckets apart (unique.hip).
+struct EdgeOut { int32_t* col; int64_t* eid; uint8_t* tag; };
+#ifdef __HIPCC__
+__device__ __forceinline__ void put_edge(const EdgeOut& out, int64_t o, uint32_t place, int32_t t, int64_t eid) {
+  (out.col + o)[place] = t;
+  (out.eid + o)[place] = eid;
+  if (out.tag != nullptr) (out.tag + o)[place] = (uint8_t)source_tag((uint32_t)t);
 }
 #endif
 

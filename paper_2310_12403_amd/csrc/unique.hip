@@ -100,6 +100,41 @@ __device__ __forceinline__ uint32_t bucket_insert(unsigned long long* table, uin
     h = (h + 1) & (slots - 1);
   }
 }
+// N insertions of a thread into a table that cannot fill up (all of the block's together are at most three quarters of its slots), one
+// step of all of them before the next step of any: what they wait for is LDS, one operation after the other, so the claim is tried
+// without a look at the slot first, and the claimed slots are counted in a register.  mine: kEmptySlot for nothing to insert.
+// Afterwards h[u] is the slot of mine[u]'s key; returns the number of slots claimed.
+template <int N>
+__device__ __forceinline__ uint32_t bucket_insert_many(unsigned long long* table, uint32_t slots, uint32_t (&h)[N], const unsigned long long (&mine)[N],
+                                                       uint32_t nd, BucketState* st) {
+  uint32_t claimed = 0, pending = 0;
+#pragma unroll
+  for (int u = 0; u < N; ++u) pending |= mine[u] != kEmptySlot ? 1u << u : 0u;
+  while (pending != 0) {
+    unsigned long long cur[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (pending >> u & 1u) cur[u] = atomicCAS(&table[h[u]], (unsigned long long)kEmptySlot, mine[u]);
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      if (!(pending >> u & 1u)) continue;
+      if (cur[u] == kEmptySlot) {
+        ++claimed;
+        pending &= ~(1u << u);
+      } else if ((uint32_t)(cur[u] >> 32) == (uint32_t)(mine[u] >> 32)) {
+        pending &= ~(1u << u);
+        if ((uint32_t)mine[u] < nd) {
+          if ((uint32_t)atomicMin(&table[h[u]], mine[u]) < nd) st->dup = 1;  // S^l holds a vertex twice
+        } else if (mine[u] < cur[u]) {
+          atomicMin(&table[h[u]], mine[u]);
+        }
+      } else {
+        h[u] = (h[u] + 1) & (slots - 1);
+      }
+    }
+  }
+  return claimed;
+}
 __device__ __forceinline__ uint32_t bucket_find(const unsigned long long* table, uint32_t slots, uint32_t h, uint32_t key) {
   for (;;) {  // (every key looked up was inserted; an empty slot ends the search regardless)
     const unsigned long long cur = table[h];
@@ -132,39 +167,51 @@ __device__ __forceinline__ void bucket_done(Ctl* ctl, const BucketState& st, int
 // ---- first positions of a short list -----------------------------------------------------------------------------
 // Block b reads the whole list and notes, wave by wave, the positions whose key hashes to bucket b; those keys go into the
 // block's table, and the edges among them get what the table then says.  One launch in the place of clearing a table,
-// inserting and looking up in HBM, and no key's atomic leaves the block
-// (which counts itself once, in bucket_done).  Reading everything in every block is what it pays for
-// that, three vector instructions per key, which is why it ends at kFilterMax entries.  188 thousand entries 17 us (clear,
-// insert and look up in HBM: 25), 11 to 58 thousand 10 to 12 us (10 to 16).
+// inserting and looking up in HBM, and no key's atomic leaves the block (which counts itself once, in bucket_done).
+// Reading everything in every block is what it pays for that: ten instructions per key in every block were 12 of the 20 us that a
+// list of 180 thousand entries took.  So it is not the edges' sources that are read but their tags, a byte each (EdgeOut::tag, left by
+// the kernel that wrote the edges): 16 to a load, and fewer than three instructions for each.  180 thousand entries 20.5 -> 14.5 us,
+// 213 thousand 22.5 -> 15.3, 75 thousand 12.4 -> 10.5; calls over 300 to 500 thousand, which went to the partition, 7 to 0 us less.
 constexpr int kFilterBlock = 1024;
-constexpr uint32_t kFilterSlots = 4096;
-constexpr uint32_t kFilterFull = kFilterSlots / 4 * 3 - kFilterBlock;  // distinct keys at which a bucket gives up
-constexpr uint32_t kFilterList = 256;                   // positions that a wave can note
+constexpr uint32_t kFilterList = 256;                   // positions that a wave can note (twice that with the larger table)
 constexpr int64_t kFilterPairs = 1024;                  // most entries of a bucket in the mean (64 per wave) ...
 // ... and at least four buckets: the first wave looks at up to 512 entries of a list of two parts, and with two buckets noted
 // 256 to 270 of them on ordinary lists of 1,500 to 2,048 entries, one more than it can (15 us in the place of 12)
 constexpr int kFilterLeastLog2 = 2;
-constexpr int64_t kFilterMax = 262144;                  // 256 buckets at most: one per CU
+constexpr int kFilterMostLog2 = 8;                      // one block per CU, and a tag tells no more buckets apart
+constexpr int64_t kFilterMax = 262144;                  // entries up to which it is used, with tables of 4,096 slots ...
+// ... and with tags, there with 8,192: 495 and 520 thousand entries 84 and 80 us a call, 85 and 80 by partition; 340 thousand 73 and
+// 80; 660 thousand 93 and 89.  (Its 4-byte stores of first positions are scattered over the list, and so are its looks at the keys.)
+constexpr int64_t kFilterTaggedMax = 524288;
+// Shorter lists are read by their keys: a lane's 16 tags are of entries in a row, so that few lanes have all there is to note
+// (1.3 thousand entries 50 us a call, 40 by keys; 11 thousand 41 and 40; 21 thousand 42 either way, 52 thousand 45 and 47).
+constexpr int64_t kFilterTaggedFrom = 16384;
 constexpr int64_t kShortMax = 65536;                    // entries up to which the kernel also marks the new vertices (k_uniq_relabel_short)
 constexpr int kShortWords = (int)(kShortMax / 64) + 1;
 __device__ __forceinline__ uint32_t filter_hash(uint32_t key) { return key * 0x9E3779B9u; }
+static_assert(kSourceHash == 0x9E3779B9u, "a source's tag is the highest byte of this hash");
 
+template <bool TAGS, int SLOTS_LOG2>
 __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
-                                                              int64_t m, const int64_t* __restrict__ m_dev, int log2_buckets,
+                                                              const uint8_t* __restrict__ tags, int64_t m, const int64_t* __restrict__ m_dev, int log2_buckets,
                                                               uint32_t* __restrict__ first, unsigned long long* __restrict__ bits /* or null */,
                                                               Ctl* ctl, Publish pub) {
-  __shared__ unsigned long long table[kFilterSlots];
-  __shared__ uint32_t noted[kFilterBlock / kWave][kFilterList];
+  constexpr uint32_t kSlots = 1u << SLOTS_LOG2;
+  constexpr uint32_t kFull = kSlots / 4 * 3 - kFilterBlock;  // distinct keys at which a bucket gives up
+  constexpr uint32_t kList = kFilterList << (SLOTS_LOG2 - 12);  // positions that a wave can note
+  constexpr bool kBits = SLOTS_LOG2 == 12;                   // (lists with larger tables are longer than kShortMax)
+  __shared__ unsigned long long table[kSlots];
+  __shared__ uint32_t noted[kFilterBlock / kWave][kList];
   __shared__ BucketState st;
-  __shared__ uint32_t s_overflow;
-  __shared__ unsigned long long word[kShortWords];  // the block's bits
+  __shared__ uint32_t s_noted, s_overflow;
+  __shared__ unsigned long long word[kBits ? kShortWords : 1];  // the block's bits
   if (m_dev != nullptr && *m_dev < m) m = *m_dev;
-  const uint32_t n = (uint32_t)(n_dst + m);  // (below kFilterMax)
+  const uint32_t n = (uint32_t)(n_dst + m);
   const uint32_t nd = (uint32_t)n_dst;
-  const uint32_t n_words = bits != nullptr ? ((n + 63u) >> 6) - (nd >> 6) : 0u;  // (at most kShortWords)
+  const uint32_t n_words = kBits && bits != nullptr ? ((n + 63u) >> 6) - (nd >> 6) : 0u;  // (at most kShortWords)
   for (uint32_t i = threadIdx.x; i < n_words; i += kFilterBlock) word[i] = 0;
-  for (uint32_t i = threadIdx.x; i < kFilterSlots; i += kFilterBlock) table[i] = kEmptySlot;
-  if (threadIdx.x == 0) { st = BucketState{0u, 0u, 0u}; s_overflow = 0; }
+  for (uint32_t i = threadIdx.x; i < kSlots; i += kFilterBlock) table[i] = kEmptySlot;
+  if (threadIdx.x == 0) { st = BucketState{0u, 0u, 0u}; s_noted = 0; s_overflow = 0; }
   __syncthreads();
   auto key_at = [&](uint32_t i) { return (uint32_t)(i < nd ? dst[i] : col[i - nd]); };
   // The first position of edge position i; the edge whose position it is gets its bit.  (The words are clear when the kernel starts.
@@ -172,65 +219,81 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
   // where a pass that collects the words takes 5.)
   auto found = [&](uint32_t i, uint32_t at) {
     first[i - nd] = at;
-    if (bits != nullptr && at == i) atomicOr(&word[(i >> 6) - (nd >> 6)], 1ull << (i & 63u));
+    if (kBits && bits != nullptr && at == i) atomicOr(&word[(i >> 6) - (nd >> 6)], 1ull << (i & 63u));
   };
   const uint32_t width = 1u << (32 - log2_buckets), low = blockIdx.x * width;  // the bucket's hashes: low .. low + width - 1 (log2_buckets >= 1)
-  auto slot = [&](uint32_t h) { return (h << log2_buckets) >> 20; };           // the hash bits behind those of the bucket
-  static_assert(kFilterSlots == 1u << 12, "slot() takes 12 bits");
-  uint32_t* list = noted[uniform_wave_in_block()];
-  uint32_t count = 0;  // (the same in every lane)
-  // Each part of the list ([S^l], [col]; 256-byte aligned and padded to that) is read as groups of four keys, U groups per
-  // thread and step, the next step's groups requested before this step's keys are looked at.
-  constexpr uint32_t U = 4;
-  auto part = [&](const int32_t* __restrict__ p, uint32_t len, uint32_t at0) {
+  auto slot = [&](uint32_t h) { return (h << log2_buckets) >> (32 - SLOTS_LOG2); };  // the hash bits behind those of the bucket
+  // Each part of the list ([S^l], [col]; 256-byte aligned and padded to that) is read in groups of 16 bytes, a few groups per thread
+  // and step, the next step's groups requested before this step's are looked at.  take(flags, entry): those of this lane's keys
+  // that are in the bucket, and which entry of the part a flag stands for.
+  auto fetch = [&](const void* __restrict__ p, uint32_t groups, uint32_t g0, auto& to) {
+#pragma unroll
+    for (uint32_t u = 0; u < sizeof(to) / sizeof(to[0]); ++u) {
+      const uint32_t g = g0 + u * kFilterBlock + threadIdx.x;
+      to[u] = reinterpret_cast<const u32x4*>(p)[g < groups ? g : groups - 1];
+    }
+  };
+  auto by_key = [&](const int32_t* __restrict__ p, uint32_t len, auto&& take) {
+    constexpr uint32_t U = 4;
     const uint32_t groups = (len + 3) / 4;
     u32x4 next[U];
-    auto fetch = [&](uint32_t g0) {
-#pragma unroll
-      for (uint32_t u = 0; u < U; ++u) {
-        const uint32_t g = g0 + u * kFilterBlock + threadIdx.x;
-        next[u] = reinterpret_cast<const u32x4*>(p)[g < groups ? g : groups - 1];
-      }
-    };
-    if (groups > 0) fetch(0);
+    if (groups > 0) fetch(p, groups, 0, next);
     for (uint32_t g0 = 0; g0 < groups; g0 += U * kFilterBlock) {
-      uint32_t off[U][4];  // hash minus the bucket's lowest: one of the bucket's if below width
-      uint32_t least = 0xFFFFFFFFu;
-#pragma unroll
-      for (uint32_t u = 0; u < U; ++u)
-#pragma unroll
-        for (uint32_t e = 0; e < 4; ++e) {
-          off[u][e] = filter_hash(next[u][e]) - low;
-          least = off[u][e] < least ? off[u][e] : least;
-        }
-      if (g0 + U * kFilterBlock < groups) fetch(g0 + U * kFilterBlock);
-      if (ballot64(least < width) == 0) continue;
       uint32_t flags = 0;  // bit 4 u + e
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u)
 #pragma unroll
-        for (uint32_t e = 0; e < 4; ++e) flags |= off[u][e] < width ? 1u << (4 * u + e) : 0u;
-      const uint32_t i0 = (g0 + threadIdx.x) * 4;  // entry of this thread's first key in this part
-      for (;;) {  // a few of the wave's 1024 keys: every round notes one of each lane's
-        const uint64_t some = ballot64(flags != 0);
-        if (some == 0) break;
-        const uint32_t bit = flags != 0 ? (uint32_t)__builtin_ctz(flags) : 0u;
-        const uint32_t i = i0 + (bit >> 2) * (4 * kFilterBlock) + (bit & 3u);
+        for (uint32_t e = 0; e < 4; ++e) flags |= filter_hash(next[u][e]) - low < width ? 1u << (4 * u + e) : 0u;
+      if (g0 + U * kFilterBlock < groups) fetch(p, groups, g0 + U * kFilterBlock, next);
+      take(flags, [&](uint32_t bit) { return (g0 + (bit >> 2) * kFilterBlock + threadIdx.x) * 4 + (bit & 3u); });
+    }
+  };
+  auto by_tag = [&](uint32_t len, auto&& take) {
+    constexpr uint32_t U = 2;
+    const uint32_t groups = (len + 15) / 16;
+    const uint32_t mask = ((0xFF00u >> log2_buckets) & 0xFFu) * 0x01010101u, mine = (blockIdx.x << (8 - log2_buckets)) * 0x01010101u;
+    u32x4 next[U];
+    if (groups > 0) fetch(tags, groups, 0, next);
+    for (uint32_t g0 = 0; g0 < groups; g0 += U * kFilterBlock) {
+      uint32_t flags = 0;  // bit 8 b + 7 - q: byte b of word q
+#pragma unroll
+      for (uint32_t q = 0; q < 4 * U; ++q) {
+        const uint32_t x = (next[q / 4][q % 4] ^ mine) & mask;  // a zero byte: one of the bucket's
+        flags |= ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu) >> q;
+      }
+      if (g0 + U * kFilterBlock < groups) fetch(tags, groups, g0 + U * kFilterBlock, next);
+      take(flags, [&](uint32_t bit) {
+        const uint32_t q = 7u - (bit & 7u);
+        return (g0 + (q >> 2) * kFilterBlock + threadIdx.x) * 16 + (q & 3u) * 4 + (bit >> 3);
+      });
+    }
+  };
+  uint32_t* list = noted[uniform_wave_in_block()];
+  uint32_t count = 0;  // (the same in every lane)
+  auto note = [&](uint32_t len, uint32_t at0) {
+    return [&, len, at0](uint32_t flags, auto&& entry) {
+      for (;;) {  // a few of the wave's keys: every round notes one of each lane's
+        if (ballot64(flags != 0) == 0) break;
+        const uint32_t i = entry(flags != 0 ? (uint32_t)__builtin_ctz(flags) : 0u);
         const bool in = flags != 0 && i < len;
         const uint64_t mask = ballot64(in);
         const uint32_t to = count + lanes_below(mask);
-        if (in && to < kFilterList) list[to] = at0 + i;
+        if (in && to < kList) list[to] = at0 + i;
         count += (uint32_t)__popcll(mask);
         flags &= flags - 1;
       }
-    }
+    };
   };
-  part(dst, nd, 0u);
-  part(col, n - nd, nd);
-  if (count > kFilterList && lane_id() == 0) s_overflow = 1;
+  by_key(dst, nd, note(nd, 0u));
+  if constexpr (TAGS) by_tag(n - nd, note(n - nd, nd));
+  else by_key(col, n - nd, note(n - nd, nd));
+  if (lane_id() == 0) {
+    if (count > kList) s_overflow = 1;
+    else atomicAdd(&s_noted, count);
+  }
   __syncthreads();
   if (s_overflow == 0) {  // every wave goes on with its own list
-    constexpr int V = kFilterList / kWave;
+    constexpr int V = kList / kWave;
     unsigned long long pair[V];
     uint32_t h[V];
 #pragma unroll
@@ -242,50 +305,40 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
       h[v] = slot(filter_hash(key));
       pair[v] = in ? ((unsigned long long)key << 32) | i : kEmptySlot;
     }
+    if (s_noted <= kSlots / 4 * 3) {  // (no room for more)
+      const uint32_t claimed = wave_sum_u32(bucket_insert_many<V>(table, kSlots, h, pair, nd, &st));
+      if (lane_id() == 0) atomicAdd(&st.claimed, claimed);
+    } else {
 #pragma unroll
-    for (int v = 0; v < V; ++v)
-      if (pair[v] != kEmptySlot && lds_read(&st.full) == 0) h[v] = bucket_insert(table, kFilterSlots, kFilterFull, h[v], pair[v], nd, &st);
+      for (int v = 0; v < V; ++v)
+        if (pair[v] != kEmptySlot && lds_read(&st.full) == 0) h[v] = bucket_insert(table, kSlots, kFull, h[v], pair[v], nd, &st);
+    }
     __syncthreads();
 #pragma unroll
     for (int v = 0; v < V; ++v)
       if (pair[v] != kEmptySlot && (uint32_t)pair[v] >= nd) found((uint32_t)pair[v], (uint32_t)table[h[v]]);
   } else {
-    // a vertex that very many lists keep: the whole list is read again, twice, in the same steps.  (222 thousand entries, one
-    // in 72 the same: 76 us; with one key per thread and step 158, in a table in HBM 51 and two launches more.  All of 130
-    // thousand edges from one vertex: 165, 149 and 1,270.)
-    auto each = [&](const int32_t* __restrict__ p, uint32_t len, auto&& take) {
-      const uint32_t groups = (len + 3) / 4;
-      for (uint32_t g0 = 0; g0 < groups; g0 += U * kFilterBlock) {
-        u32x4 key[U];
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {
-          const uint32_t g = g0 + u * kFilterBlock + threadIdx.x;
-          key[u] = reinterpret_cast<const u32x4*>(p)[g < groups ? g : groups - 1];
-        }
-        uint32_t flags = 0;
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u)
-#pragma unroll
-          for (uint32_t e = 0; e < 4; ++e) flags |= filter_hash(key[u][e]) - low < width ? 1u << (4 * u + e) : 0u;
+    // a vertex that very many lists keep: the whole list is read again, twice, and every key goes straight to the table.
+    auto each = [&](uint32_t len, uint32_t at0, auto&& what) {
+      return [&, len, at0](uint32_t flags, auto&& entry) {
         for (; flags != 0; flags &= flags - 1) {
-          const uint32_t bit = (uint32_t)__builtin_ctz(flags);
-          uint32_t k = 0;
-#pragma unroll
-          for (uint32_t b = 0; b < 4 * U; ++b) k = bit == b ? key[b / 4][b % 4] : k;
-          const uint32_t i = (g0 + (bit >> 2) * kFilterBlock + threadIdx.x) * 4 + (bit & 3u);
-          if (i < len) take(i, k);
+          const uint32_t i = entry((uint32_t)__builtin_ctz(flags));
+          if (i < len) what(at0 + i, key_at(at0 + i));
         }
-      }
+      };
     };
     auto insert = [&](uint32_t i, uint32_t key) {
-      if (lds_read(&st.full) == 0)
-        bucket_insert(table, kFilterSlots, kFilterFull, slot(filter_hash(key)), ((unsigned long long)key << 32) | i, nd, &st);
+      if (lds_read(&st.full) == 0) bucket_insert(table, kSlots, kFull, slot(filter_hash(key)), ((unsigned long long)key << 32) | i, nd, &st);
     };
-    each(dst, nd, insert);
-    each(col, n - nd, [&](uint32_t i, uint32_t key) { insert(nd + i, key); });
+    auto look_up = [&](uint32_t i, uint32_t key) { found(i, bucket_find(table, kSlots, slot(filter_hash(key)), key)); };
+    by_key(dst, nd, each(nd, 0u, insert));
+    if constexpr (TAGS) by_tag(n - nd, each(n - nd, nd, insert));
+    else by_key(col, n - nd, each(n - nd, nd, insert));
     __syncthreads();
-    if (st.full == 0)
-      each(col, n - nd, [&](uint32_t i, uint32_t key) { found(nd + i, bucket_find(table, kFilterSlots, slot(filter_hash(key)), key)); });
+    if (st.full == 0) {
+      if constexpr (TAGS) by_tag(n - nd, each(n - nd, nd, look_up));
+      else by_key(col, n - nd, each(n - nd, nd, look_up));
+    }
   }
   if (n_words != 0) {
     __syncthreads();
@@ -501,7 +554,8 @@ __global__ __launch_bounds__(kFirstBlock, 8) void k_part_first(const unsigned lo
   if ((int64_t)hi > n_all) hi = (uint32_t)n_all;  // (holds by construction; keeps every access inside the arrays regardless)
   if (lo > hi) lo = hi;
   const uint32_t nd = (uint32_t)n_dst;
-  constexpr int U = 4;  // pairs per thread and round, loaded together
+  constexpr int U = 5;  // pairs per thread and round, loaded together (a bucket of the mean size and a quarter more in one round)
+  static_assert((uint32_t)(U * kFirstBlock) <= kPartFull, "one round cannot fill the table");
   unsigned long long mine[U];
   auto fetch = [&](uint32_t base) {
 #pragma unroll
@@ -515,27 +569,33 @@ __global__ __launch_bounds__(kFirstBlock, 8) void k_part_first(const unsigned lo
   if (threadIdx.x == 0) st = BucketState{0u, 0u, 0u};
   __syncthreads();
   uint32_t h[U];
-  for (uint32_t base = lo; base < hi; base += U * kFirstBlock) {
-    if (base != lo) fetch(base);
-    if (lds_read(&st.full) != 0) break;
+  if (hi - lo <= (uint32_t)(U * kFirstBlock)) {  // the usual bucket
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      h[u] = 0;
-      if (mine[u] == kEmptySlot || lds_read(&st.full) != 0) continue;
-      h[u] = bucket_insert(table, kPartSlots, kPartFull, table_slot_of_hash(hash_of_key((uint32_t)(mine[u] >> 32))), mine[u], nd, &st);
-    }
-  }
-  __syncthreads();
-  if (hi - lo <= (uint32_t)(U * kFirstBlock)) {  // the usual bucket: one round, whose slots are at hand
+    for (int u = 0; u < U; ++u) h[u] = table_slot_of_hash(hash_of_key((uint32_t)(mine[u] >> 32)));
+    const uint32_t claimed = wave_sum_u32(bucket_insert_many<U>(table, kPartSlots, h, mine, nd, &st));
+    if (lane_id() == 0) atomicAdd(&st.claimed, claimed);
+    __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t i = lo + u * kFirstBlock + threadIdx.x;
       if (i < hi) by_place[(size_t)i << shift] = (uint32_t)table[h[u]];
     }
-  } else if (st.full == 0) {
-    for (uint32_t i = lo + threadIdx.x; i < hi; i += kFirstBlock) {
-      const uint32_t key = (uint32_t)(pairs[i] >> 32);
-      by_place[(size_t)i << shift] = bucket_find(table, kPartSlots, table_slot_of_hash(hash_of_key(key)), key);
+  } else {
+    for (uint32_t base = lo; base < hi; base += U * kFirstBlock) {
+      if (base != lo) fetch(base);
+      if (lds_read(&st.full) != 0) break;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (mine[u] == kEmptySlot || lds_read(&st.full) != 0) continue;
+        bucket_insert(table, kPartSlots, kPartFull, table_slot_of_hash(hash_of_key((uint32_t)(mine[u] >> 32))), mine[u], nd, &st);
+      }
+    }
+    __syncthreads();
+    if (st.full == 0) {
+      for (uint32_t i = lo + threadIdx.x; i < hi; i += kFirstBlock) {
+        const uint32_t key = (uint32_t)(pairs[i] >> 32);
+        by_place[(size_t)i << shift] = bucket_find(table, kPartSlots, table_slot_of_hash(hash_of_key(key)), key);
+      }
     }
   }
   if (threadIdx.x == 0) bucket_done(ctl, st, n_dst, pub);
@@ -789,9 +849,16 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
   w->part_blocks = 0;
   if (path == kByFilter) {
     int log2_buckets = kFilterLeastLog2;
-    while (((int64_t)kFilterPairs << log2_buckets) < n_all) ++log2_buckets;
-    COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_filter, dim3(1u << log2_buckets), dim3(kFilterBlock), 0, s, dst, n_dst, col_global, m, m_dev, log2_buckets,
-                first, w->bits ? (unsigned long long*)w->words : (unsigned long long*)nullptr, d_ctl, w->pub);
+    while (log2_buckets < kFilterMostLog2 && (kFilterPairs << log2_buckets) < n_all) ++log2_buckets;
+    unsigned long long* bits = w->bits ? (unsigned long long*)w->words : (unsigned long long*)nullptr;
+    const uint8_t* tags = w->tagged ? (const uint8_t*)spare : nullptr;
+#define COOP_UNIQ_FILTER(TAGS, SLOTS_LOG2)                                                                                                  \
+  COOP_LAUNCH(K_UNIQ_FILTER, (k_uniq_filter<TAGS, SLOTS_LOG2>), dim3(1u << log2_buckets), dim3(kFilterBlock), 0, s, dst, n_dst, col_global, tags, m, \
+              m_dev, log2_buckets, first, bits, d_ctl, w->pub)
+    if (tags == nullptr) COOP_UNIQ_FILTER(false, 12);
+    else if (n_all < kFilterMax) COOP_UNIQ_FILTER(true, 12);
+    else COOP_UNIQ_FILTER(true, 13);
+#undef COOP_UNIQ_FILTER
   } else if (path == kByPartition) {
     const int64_t n_buckets = w->n_buckets;
     const int64_t by_size = (n_all + 4 * kPartBlock - 1) / (4 * kPartBlock);
@@ -852,7 +919,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
   return COOP_OK;
 }
 
-int unique_prepare(int64_t n_dst, int64_t m, UniqueWork* w, Alloc& alloc) {
+int unique_prepare(int64_t n_dst, int64_t m, bool tagged, UniqueWork* w, Alloc& alloc) {
   const int64_t n_all = n_dst + m;
   const int64_t n_words = (n_all + 63) / 64 - (n_dst >> 6);
   w->words = alloc.get<RankWord>(n_words, COOP_TAG_SCRATCH);
@@ -866,8 +933,10 @@ int unique_prepare(int64_t n_dst, int64_t m, UniqueWork* w, Alloc& alloc) {
   // three less in the scatter, which has fewer buckets: 7.0 M 40.5 and 43.4.)
   const int64_t whole_rounds = w->n_buckets / 512 * 512;
   if (whole_rounds > 0 && n_all <= whole_rounds * (pairs_per_bucket + pairs_per_bucket / 8)) w->n_buckets = whole_rounds;
-  const bool by_partition = m > 0 && w->n_buckets <= kPartMaxBuckets && g_unique_mode != 1 && (g_unique_mode >= 2 || n_all >= kFilterMax);
-  const bool by_filter = !by_partition && g_unique_mode != 1 && n_all > 0 && n_all < kFilterMax;
+  const int64_t filter_max = tagged ? kFilterTaggedMax : kFilterMax;
+  const bool by_partition = m > 0 && w->n_buckets <= kPartMaxBuckets && g_unique_mode != 1 && (g_unique_mode >= 2 || n_all >= filter_max);
+  const bool by_filter = !by_partition && g_unique_mode != 1 && n_all > 0 && n_all < filter_max;
+  w->tagged = tagged && by_filter && n_all >= kFilterTaggedFrom;
   w->path = by_partition ? kByPartition : by_filter ? kByFilter : kByTable;
   const bool bits = by_filter && n_all <= kShortMax;
   w->clear = bits ? (uint64_t*)w->words : nullptr;

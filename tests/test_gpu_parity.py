@@ -905,6 +905,40 @@ def test_frontier_dedup_of_short_lists(P, shape):
         assert "unique_filter" in ran or size > 100000, (size, ran.keys())
 
 
+@pytest.mark.parametrize("shape", ["ring", "star", "few", "one_bucket"])
+def test_frontier_dedup_by_tags(P, shape):
+    """The same where the blocks read the sources' tags: lists of one entry to both sides of the lengths from which tags are
+    read (16,384), the new vertices are collected (65,536), the tables are larger (262,144) and the partition takes over (524,288);
+    a vertex that every list keeps, a thousand that all lists share, and seeds that share a bucket."""
+    n = 300000
+    rng = np.random.default_rng(12)
+    if shape == "star":
+        indices = torch.full((n,), 7, dtype=torch.int32)
+    elif shape == "few":
+        indices = torch.from_numpy(rng.integers(0, 1000, n).astype(np.int32))
+    else:
+        indices = ((torch.arange(n) + 7) % n).to(torch.int32)
+    g = G(P, torch.arange(n + 1, dtype=torch.int64), indices)
+    perm = rng.permutation(n).astype(np.int32)
+    sizes = (8191, 8192, 8193, 32767, 32768, 32769, 131071, 131072, 262143, 262144)
+    if shape == "one_bucket":
+        hashes = (perm.astype(np.uint64) * np.uint64(0x9E3779B9)) & np.uint64(0xFFFFFFFF)
+        perm = perm[(hashes >> np.uint64(27)) == 9]
+        sizes = (9000,)               # n_all = 18,000: 32 buckets, and one of them gets all the seeds
+    for size in sizes:
+        P.profile_reset()
+        P.profile_enable(True)
+        compare(P, g, perm[:size], (1,), R.NS, seed=size)
+        P.profile_enable(False)
+        ran = P.profile_read_all()
+        assert ("unique_insert" in ran) == (shape == "one_bucket"), (size, ran.keys())
+        assert ("unique_filter" in ran) == (size < 262144), (size, ran.keys())
+    if shape != "one_bucket":
+        compare(P, g, perm[:40000], (2,), R.LABOR0, it=1, seed=5)
+        compare(P, g, perm[:40000], (2,), R.NS, it=1, kappa=3, seed=6)
+        compare_rw(P, g, perm[:20000], (2,), 2, 4, 0.5, seed=7)
+
+
 @pytest.mark.parametrize("mode", [1, 0])
 def test_offsets_around_the_edges_of_tiles(P, mode):
     """Offsets that the filling kernel finds by itself (up to 32,768 destinations) and those that a scan leaves tile by tile
