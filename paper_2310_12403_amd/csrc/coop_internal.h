@@ -90,14 +90,30 @@ struct DeviceCtl {
   Tally tally;
 };
 
-// Landing pad of the control block in mapped pinned host memory (see read_ctl).
+// Landing pad of the control block in mapped pinned host memory (see read_ctl).  The device stores the block as three words, each
+// with the ticket in its highest bits: a word is whole when its ticket is there, so no store waits for another to arrive (with the
+// block first, a fence and then a ticket the last thread of a kernel waited a microsecond for the host's memory).
+constexpr int kMailValueBits = 44;
 struct HostCtl {
-  Ctl ctl;               // must stay the first member
-  uint64_t ticket;       // written by the device after ctl
-  uint64_t next_ticket;  // host side only
+  Ctl ctl;                          // must stay the first member; host side only: what the words said (open_mail)
+  alignas(64) uint64_t mail[3];     // total_edges, total_new, n_overflow and the flags
+  alignas(64) uint64_t next_ticket; // host side only
+  static bool arrived(uint64_t word, uint64_t ticket) { return word >> kMailValueBits == (ticket & (((uint64_t)1 << (64 - kMailValueBits)) - 1)); }
 };
+#ifdef __HIPCC__
+__device__ __forceinline__ void send_ctl(HostCtl* h, uint64_t ticket, const Ctl& c) {
+  const uint64_t flags = (uint64_t)(uint32_t)c.n_overflow | (uint64_t)(c.err_range != 0) << 32 | (uint64_t)(c.err_dup != 0) << 33 |
+                         (uint64_t)(c.err_capacity != 0) << 34 | (uint64_t)(c.cand_overflow != 0) << 35 | (uint64_t)(c.uniq_overflow != 0) << 36;
+  constexpr int64_t kMost = ((int64_t)1 << (kMailValueBits - 1)) - 1;  // (far beyond what a layer may have)
+  const uint64_t value[3] = {(uint64_t)(c.total_edges < kMost ? c.total_edges : kMost), (uint64_t)c.total_new, flags};
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    __hip_atomic_store(&h->mail[i], ticket << kMailValueBits | (value[i] & (((uint64_t)1 << kMailValueBits) - 1)), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+#endif
 
-// A size read-back in flight: the device stores the control block and then `ticket` into the landing pad.
+// A size read-back in flight: the device stores the control block with `ticket` into the landing pad.
 struct Publish {
   const Ctl* d_ctl = nullptr;
   HostCtl* h = nullptr;

@@ -112,9 +112,7 @@ __device__ __forceinline__ int64_t block_incl_scan_i64(int64_t v, int64_t* total
 // what a one-thread publishing kernel would do, done by a thread that has just stored what the host waits for
 __device__ __forceinline__ void publish_ctl(const Publish& pub) {
   if (pub.h == nullptr) return;
-  pub.h->ctl = *pub.d_ctl;
-  __threadfence_system();
-  __hip_atomic_store(&pub.h->ticket, pub.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  send_ctl(pub.h, pub.ticket, *pub.d_ctl);
 }
 
 // Tile by tile: out holds, for the first element of every tile of 2^log2 elements, the tile's sum (stored by tile_sum_done), and

@@ -135,11 +135,10 @@ __global__ __launch_bounds__(kNsCountBlock) void k_ns_count(const int64_t* __res
     indptr[n_dst] = total;
     ctl->total_edges = total;
     if (pub.h != nullptr) {
-      pub.h->ctl = *ctl;  // (the fields of earlier kernels; those of this one follow)
-      pub.h->ctl.total_edges = total;
-      pub.h->ctl.err_range = __hip_atomic_load(&ctl->err_range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __threadfence_system();
-      __hip_atomic_store(&pub.h->ticket, pub.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      Ctl c = *ctl;  // (the fields of earlier kernels; those of this one follow)
+      c.total_edges = total;
+      c.err_range = __hip_atomic_load(&ctl->err_range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      send_ctl(pub.h, pub.ticket, c);
     }
   }
 }

@@ -23,14 +23,12 @@ __global__ __launch_bounds__(kBlock) void k_begin_call(const int32_t* __restrict
   }
 }
 
-// The control block travels to the host by a one-thread kernel that stores it into mapped pinned memory and then a
+// The control block travels to the host by a one-thread kernel that stores it into mapped pinned memory with a
 // ticket; the host polls the ticket.  That is a few microseconds quicker per read-back than an asynchronous copy
 // followed by a stream synchronisation, and a sampling call has one read-back per layer (two for a layer that is redone or has a large fanout).  The wait is bounded: after
 // a while the host falls back to synchronising the stream.
 __global__ void k_publish_ctl(const Ctl* __restrict__ d_ctl, HostCtl* h, uint64_t ticket) {
-  h->ctl = *d_ctl;
-  __threadfence_system();
-  __hip_atomic_store(&h->ticket, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  send_ctl(h, ticket, *d_ctl);
 }
 
 Publish begin_publish(Ctl* d_ctl, Ctl* h_ctl) {
@@ -43,18 +41,37 @@ int launch_publish(const Publish& pub, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? COOP_OK : COOP_E_HIP;
 }
 
+// Has the block with this ticket arrived?  Then what it says stands in h->ctl.
+static bool open_mail(HostCtl* h, uint64_t ticket) {
+  uint64_t w[3];
+  for (int i = 0; i < 3; ++i) {
+    w[i] = __atomic_load_n(&h->mail[i], __ATOMIC_ACQUIRE);
+    if (!HostCtl::arrived(w[i], ticket)) return false;
+  }
+  auto value = [](uint64_t x) { return (int64_t)(x << (64 - kMailValueBits)) >> (64 - kMailValueBits); };
+  h->ctl.total_edges = value(w[0]);
+  h->ctl.total_new = value(w[1]);
+  h->ctl.n_overflow = (int32_t)(uint32_t)w[2];
+  h->ctl.err_range = (int32_t)(w[2] >> 32 & 1);
+  h->ctl.err_dup = (int32_t)(w[2] >> 33 & 1);
+  h->ctl.err_capacity = (int32_t)(w[2] >> 34 & 1);
+  h->ctl.cand_overflow = (int32_t)(w[2] >> 35 & 1);
+  h->ctl.uniq_overflow = (int32_t)(w[2] >> 36 & 1);
+  return true;
+}
+
 int wait_ctl(const Publish& pub, Ctl* h_ctl, hipStream_t s) {
   HostCtl* h = pub.h;
   const uint64_t ticket = pub.ticket;
   bool seen = false;
   for (int64_t spin = 0; spin < ((int64_t)1 << 26); ++spin) {
-    if (__atomic_load_n(&h->ticket, __ATOMIC_ACQUIRE) == ticket) { seen = true; break; }
+    if (open_mail(h, ticket)) { seen = true; break; }
     if ((spin & 0xFFFF) == 0xFFFF && hipStreamQuery(s) == hipSuccess) break;  // the stream ran dry: look once more below
     __builtin_ia32_pause();
   }
   if (!seen) {
     if (hipStreamSynchronize(s) != hipSuccess) return COOP_E_HIP;
-    if (__atomic_load_n(&h->ticket, __ATOMIC_ACQUIRE) != ticket) return COOP_E_HIP;
+    if (!open_mail(h, ticket)) return COOP_E_HIP;
   }
   if (h_ctl->err_range) return COOP_E_RANGE;
   if (h_ctl->err_dup) return COOP_E_DUPSEED;

@@ -156,12 +156,11 @@ __device__ __forceinline__ void bucket_done(Ctl* ctl, const BucketState& st, int
   const int64_t n_new = (int64_t)distinct - n_dst;
   ctl->total_new = n_new;
   if (pub.h == nullptr) return;
-  pub.h->ctl = *ctl;  // (the fields of earlier kernels; those of this one follow)
-  pub.h->ctl.total_new = n_new;
-  pub.h->ctl.err_dup = __hip_atomic_load(&ctl->err_dup, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  pub.h->ctl.uniq_overflow = __hip_atomic_load(&ctl->uniq_overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __threadfence_system();
-  __hip_atomic_store(&pub.h->ticket, pub.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  Ctl c = *ctl;  // (the fields of earlier kernels; those of this one follow)
+  c.total_new = n_new;
+  c.err_dup = __hip_atomic_load(&ctl->err_dup, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  c.uniq_overflow = __hip_atomic_load(&ctl->uniq_overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  send_ctl(pub.h, pub.ticket, c);
 }
 
 // ---- first positions of a short list -----------------------------------------------------------------------------
@@ -711,10 +710,9 @@ __global__ __launch_bounds__(kPartBlock, 8) void k_uniq_collect(uint32_t* first,
   }
   if (threadIdx.x == 0 && pub.h != nullptr) {
     ctl->total_new = carry;
-    pub.h->ctl = *ctl;
-    pub.h->ctl.total_new = carry;
-    __threadfence_system();
-    __hip_atomic_store(&pub.h->ticket, pub.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    Ctl c = *ctl;
+    c.total_new = carry;
+    send_ctl(pub.h, pub.ticket, c);
   }
 }
 
