@@ -1,6 +1,8 @@
 """ctypes binding of libcoop.so (see include/coop.h for the contract of every call)."""
 import ctypes as C
+import itertools
 import os
+import weakref
 
 import torch
 
@@ -123,7 +125,13 @@ def coop_version():
     return lib().coop_version()
 
 
+# (torch.cuda.current_stream() builds a Stream object, 2.9 us a call; this is 0.3)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream=None):
+    if stream is None and _raw_stream is not None:
+        return C.c_void_p(_raw_stream(torch.cuda.current_device()))
     s = torch.cuda.current_stream() if stream is None else stream
     return C.c_void_p(s.cuda_stream)
 
@@ -193,44 +201,61 @@ class Arena:
         if count == 0:
             return torch.empty(0, dtype=dtype, device=self.buf.device)
         off = ptr - self.buf.data_ptr()
-        nbytes = count * torch.empty(0, dtype=dtype).element_size()
-        return self.buf[off:off + nbytes].view(dtype)
+        return self.buf[off:off + count * dtype.itemsize].view(dtype)
+
+
+# One callback serves every _TorchAllocator, which it finds by the key that it is given as context: a callback of its own for each
+# (a ctypes thunk, and a cycle through its closure that only the garbage collector freed, and with it the call's buffers) made
+# 19 us of a call of a handful of seeds.
+_live = {}
+_keys = itertools.count(1)
+
+
+def _take(ctx, nbytes, tag):
+    al = None
+    try:
+        al = _live[ctx]()
+        t = torch.empty(nbytes + 256, dtype=torch.uint8, device=al.device)
+        p = t.data_ptr()
+        p += (-p) % 256
+        al.tensors[p] = t
+        al.error = None
+        return p
+    except Exception as e:  # never let an exception cross the C boundary
+        if al is not None:
+            al.error = e
+        return None
+
+
+_TAKE = ALLOC_FN(_take)
+_TAKE_ADDRESS = C.cast(_TAKE, C.c_void_p)
 
 
 class _TorchAllocator:
     """coop_alloc_fn backed by torch.empty: every buffer is an ordinary torch tensor."""
+    fn_obj = _TAKE
 
     def __init__(self, device):
         self.device = device
         self.tensors = {}
         self.error = None
-
-        def _alloc(ctx, nbytes, tag):
-            try:
-                t = torch.empty(int(nbytes) + 256, dtype=torch.uint8, device=self.device)
-                p = t.data_ptr()
-                p += (-p) % 256
-                self.tensors[p] = t
-                self.error = None
-                return p
-            except Exception as e:  # never let an exception cross the C boundary
-                self.error = e
-                return None
-
-        self.fn_obj = ALLOC_FN(_alloc)
+        self.key = next(_keys)
+        _live[self.key] = weakref.ref(self)
         self._address()
 
+    def __del__(self, live=_live):  # (at interpreter exit the module's names may be gone)
+        live.pop(self.key, None)
+
     def _address(self):  # what the library is given
-        self.fn = C.cast(self.fn_obj, C.c_void_p)
-        self.ctx = None
+        self.fn = _TAKE_ADDRESS
+        self.ctx = self.key
 
     def view(self, ptr, count, dtype):
         if count == 0:
             return torch.empty(0, dtype=dtype, device=self.device)
         t = self.tensors[ptr]
         off = ptr - t.data_ptr()
-        nbytes = count * torch.empty(0, dtype=dtype).element_size()
-        return t[off:off + nbytes].view(dtype)
+        return t[off:off + count * dtype.itemsize].view(dtype)
 
 
 class _SampleAllocator(_TorchAllocator):
@@ -239,7 +264,7 @@ class _SampleAllocator(_TorchAllocator):
     CHUNK = 1020 << 10  # with the callback's 256 bytes of room for alignment below torch's line for small blocks (1 MB)
 
     def _address(self):
-        self.chunks = _CChunks(self.fn_obj, None, self.CHUNK, None, 0)
+        self.chunks = _CChunks(_TAKE, self.key, self.CHUNK, None, 0)
         self.fn = lib().coop_chunk_alloc_address
         self.ctx = C.addressof(self.chunks)
 
