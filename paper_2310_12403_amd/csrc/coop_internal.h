@@ -209,9 +209,10 @@ struct UniqueWork {
   int64_t n_clear = 0;
   bool bits = false;                 // ... and then the first positions are marked in them as they are found
 };
-// prepare: decides how the list is deduplicated and allocates the words of new-vertex bits.  `tagged`: the kernels that write the
-// edges can leave every source's tag in `spare`, and do so if w->tagged says that the dedup reads them.
-int unique_prepare(int64_t n_dst, int64_t m, bool tagged, UniqueWork* w, Alloc& alloc);
+// prepare: decides how the list is deduplicated and allocates the words of new-vertex bits.  `deferred`: `spare` will be given, as
+// the array that becomes src_ids, before the edges are written; the kernels that write them leave every source's tag in it if
+// w->tagged says that the dedup reads them, and a dedup in one block puts src_ids there.
+int unique_prepare(int64_t n_dst, int64_t m, bool deferred, UniqueWork* w, Alloc& alloc);
 // launch: every kernel of the front half; one of them sends the sizes to the host; does not wait.  col_local (m entries)
 // holds intermediate results until `back` has run, and so does `spare` (n_dst + m entries, e.g. the array that will be
 // src_ids) when it is not null.

@@ -5,8 +5,8 @@
 // n_dst + rank in S^{l+1}: the order is "S^l, then first appearance in col_global", independent of scheduling.
 //
 // First positions come from hash tables in LDS: a block owns the keys of one bucket of hash values, and all occurrences of
-// a key share a bucket, so the minimum position found there is the global one.  Short lists: every block reads the whole
-// list and picks its keys (k_uniq_filter).  Long lists: a partition brings each bucket's pairs together first.  A bucket
+// a key share a bucket, so the minimum position found there is the global one.  The shortest lists: one block
+// does everything (k_uniq_small).  Short lists: every block reads the whole list and picks its keys (k_uniq_filter).  Long lists: a partition brings each bucket's pairs together first.  A bucket
 // with more distinct keys than its table serves sends the call to one open-addressing table in HBM (k_uniq_insert).
 // The distinct keys are known once the first positions are, so the block that finishes last there sends the sizes to the
 // host, and the host's wait and the setup of the next layer run beside the collecting and relabelling kernels.
@@ -100,41 +100,39 @@ __device__ __forceinline__ uint32_t bucket_insert(unsigned long long* table, uin
     h = (h + 1) & (slots - 1);
   }
 }
-// N insertions of a thread into a table that cannot fill up (all of the block's together are at most three quarters of its slots), one
-// step of all of them before the next step of any: what they wait for is LDS, one operation after the other, so the claim is tried
-// without a look at the slot first, and the claimed slots are counted in a register.  mine: kEmptySlot for nothing to insert.
-// Afterwards h[u] is the slot of mine[u]'s key; returns the number of slots claimed.
+// N insertions of a thread into a table that cannot fill up (all of the block's together are at most three quarters of its slots).  The
+// first tries go side by side and without a look at the slot; what did not find its slot goes on alone, by a step of its key's own (in
+// steps of one a wave waits for the longest run of slots that any of its lanes meets).  A try is to be a dozen instructions: nothing is
+// asked about a seed's position here (seed_twice tells afterwards), the claimed slots are counted in a register.  (10 thousand entries by
+// one block: 49 us in steps of one, 42 with the seeds' question in every try, 10 so.  Buckets of 4,096 pairs: 28.2 us for 1,250 of them
+// with a look at every slot first, 25.9 so, 13.7 and 10.3 for 290.)  mine: kEmptySlot for nothing to insert.  Afterwards h[u] is the slot
+// of mine[u]'s key; returns the number of slots claimed.
 template <int N>
-__device__ __forceinline__ uint32_t bucket_insert_many(unsigned long long* table, uint32_t slots, uint32_t (&h)[N], const unsigned long long (&mine)[N],
-                                                       uint32_t nd, BucketState* st) {
-  uint32_t claimed = 0, pending = 0;
+__device__ __forceinline__ uint32_t bucket_insert_many(unsigned long long* table, uint32_t slots, uint32_t (&h)[N], const unsigned long long (&mine)[N]) {
+  uint32_t claimed = 0;
+  unsigned long long cur[N];
 #pragma unroll
-  for (int u = 0; u < N; ++u) pending |= mine[u] != kEmptySlot ? 1u << u : 0u;
-  while (pending != 0) {
-    unsigned long long cur[N];
-#pragma unroll
-    for (int u = 0; u < N; ++u)
-      if (pending >> u & 1u) cur[u] = atomicCAS(&table[h[u]], (unsigned long long)kEmptySlot, mine[u]);
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      if (!(pending >> u & 1u)) continue;
-      if (cur[u] == kEmptySlot) {
-        ++claimed;
-        pending &= ~(1u << u);
-      } else if ((uint32_t)(cur[u] >> 32) == (uint32_t)(mine[u] >> 32)) {
-        pending &= ~(1u << u);
-        if ((uint32_t)mine[u] < nd) {
-          if ((uint32_t)atomicMin(&table[h[u]], mine[u]) < nd) st->dup = 1;  // S^l holds a vertex twice
-        } else if (mine[u] < cur[u]) {
-          atomicMin(&table[h[u]], mine[u]);
-        }
-      } else {
-        h[u] = (h[u] + 1) & (slots - 1);
-      }
-    }
+  for (int u = 0; u < N; ++u) {
+    cur[u] = mine[u];
+    if (mine[u] != kEmptySlot) cur[u] = atomicCAS(&table[h[u]], (unsigned long long)kEmptySlot, mine[u]);
   }
-  return claimed;
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const uint32_t key = (uint32_t)(mine[u] >> 32);
+    while (cur[u] != kEmptySlot && (uint32_t)(cur[u] >> 32) != key) {
+      h[u] = (h[u] + (key * 0x85EBCA6Bu >> 16 | 1u)) & (slots - 1);
+      cur[u] = atomicCAS(&table[h[u]], (unsigned long long)kEmptySlot, mine[u]);
+    }
+    claimed += cur[u] == kEmptySlot ? 1u : 0u;
+    if (mine[u] < cur[u] && cur[u] != kEmptySlot) atomicMin(&table[h[u]], mine[u]);
+  }
+  uint32_t none = 0;
+#pragma unroll
+  for (int u = 0; u < N; ++u) none += mine[u] == kEmptySlot ? 1u : 0u;
+  return claimed - none;
 }
+// Is the vertex of list position i a seed that stands in S^l twice?  (`at`: its first position, known by now.)
+__device__ __forceinline__ bool seed_twice(uint32_t i, uint32_t at, uint32_t nd) { return i < nd && at != i; }
 __device__ __forceinline__ uint32_t bucket_find(const unsigned long long* table, uint32_t slots, uint32_t h, uint32_t key) {
   for (;;) {  // (every key looked up was inserted; an empty slot ends the search regardless)
     const unsigned long long cur = table[h];
@@ -304,8 +302,9 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
       h[v] = slot(filter_hash(key));
       pair[v] = in ? ((unsigned long long)key << 32) | i : kEmptySlot;
     }
-    if (s_noted <= kSlots / 4 * 3) {  // (no room for more)
-      const uint32_t claimed = wave_sum_u32(bucket_insert_many<V>(table, kSlots, h, pair, nd, &st));
+    const bool fits = s_noted <= kSlots / 4 * 3;  // (the others have their room counted, and seeds that stand there twice reported)
+    if (fits) {
+      const uint32_t claimed = wave_sum_u32(bucket_insert_many<V>(table, kSlots, h, pair));
       if (lane_id() == 0) atomicAdd(&st.claimed, claimed);
     } else {
 #pragma unroll
@@ -314,8 +313,12 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
     }
     __syncthreads();
 #pragma unroll
-    for (int v = 0; v < V; ++v)
-      if (pair[v] != kEmptySlot && (uint32_t)pair[v] >= nd) found((uint32_t)pair[v], (uint32_t)table[h[v]]);
+    for (int v = 0; v < V; ++v) {
+      if (pair[v] == kEmptySlot) continue;
+      const uint32_t i = (uint32_t)pair[v], at = (uint32_t)table[h[v]];
+      if (i >= nd) found(i, at);
+      else if (fits && seed_twice(i, at, nd)) st.dup = 1;
+    }
   } else {
     // a vertex that very many lists keep: the whole list is read again, twice, and every key goes straight to the table.
     auto each = [&](uint32_t len, uint32_t at0, auto&& what) {
@@ -339,8 +342,8 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
       else by_key(col, n - nd, each(n - nd, nd, look_up));
     }
   }
+  __syncthreads();
   if (n_words != 0) {
-    __syncthreads();
     for (uint32_t i = threadIdx.x - kWave; threadIdx.x >= kWave && i < n_words; i += kFilterBlock - kWave)
       if (word[i] != 0) atomicOr(&bits[i], word[i]);
   }
@@ -571,14 +574,18 @@ __global__ __launch_bounds__(kFirstBlock, 8) void k_part_first(const unsigned lo
   if (hi - lo <= (uint32_t)(U * kFirstBlock)) {  // the usual bucket
 #pragma unroll
     for (int u = 0; u < U; ++u) h[u] = table_slot_of_hash(hash_of_key((uint32_t)(mine[u] >> 32)));
-    const uint32_t claimed = wave_sum_u32(bucket_insert_many<U>(table, kPartSlots, h, mine, nd, &st));
+    const uint32_t claimed = wave_sum_u32(bucket_insert_many<U>(table, kPartSlots, h, mine));
     if (lane_id() == 0) atomicAdd(&st.claimed, claimed);
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t i = lo + u * kFirstBlock + threadIdx.x;
-      if (i < hi) by_place[(size_t)i << shift] = (uint32_t)table[h[u]];
+      if (i >= hi) continue;
+      const uint32_t at = (uint32_t)table[h[u]];
+      by_place[(size_t)i << shift] = at;
+      if (seed_twice((uint32_t)mine[u], at, nd)) st.dup = 1;
     }
+    __syncthreads();
   } else {
     for (uint32_t base = lo; base < hi; base += U * kFirstBlock) {
       if (base != lo) fetch(base);
@@ -825,6 +832,106 @@ __global__ __launch_bounds__(kShortBlock) void k_uniq_relabel_short(const int32_
   }
 }
 
+// ---- the shortest lists in one block ------------------------------------------------------------------------------------
+// Everything from the first positions to the local ids, U entries of the list per thread, in one launch in the place of k_uniq_filter
+// and k_uniq_relabel_short: nothing goes through memory in between, no other block is counted, and the table has room for all
+// entries.  Short of that it waits, for memory twice and for LDS a dozen times; from 4,096 entries on the insertions, all on one CU, are
+// what counts (1.3 thousand entries 0.9 us of 4.5, 3.9 thousand 2.2 of 6.0, 10 thousand 9.7 of 16).  Calls over 1.3 and 3.9 thousand
+// entries 5 us shorter than with the two kernels (35.0 -> 30.2, 35.9 -> 30.7), over 6.5 thousand 1, over 7.8 thousand none.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallEach = 8;
+constexpr int64_t kSmallMax = 7936;
+static_assert(kSmallMax <= (int64_t)kSmallBlock * kSmallEach, "a thread has room for its entries");
+template <int U>
+__global__ __launch_bounds__(kSmallBlock) void k_uniq_small(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col, int64_t m,
+                                                            const int64_t* __restrict__ m_dev, int32_t* __restrict__ src, int32_t* __restrict__ col_local,
+                                                            Ctl* ctl, Publish pub) {
+  constexpr uint32_t kSlots = 16384;  // (128 KB of LDS; nobody else wants them)
+  static_assert((uint32_t)(U * kSmallBlock) <= kSlots / 4 * 3, "a probe must always reach an empty slot");
+  constexpr int kWaves = kSmallBlock / kWave, kWords = U * kWaves;
+  __shared__ unsigned long long table[kSlots];
+  __shared__ unsigned long long bits[kWords];  // new vertices among 64 entries
+  __shared__ uint32_t before[kWords];          // ... and in the words in front
+  __shared__ BucketState st;
+  const uint32_t nd = (uint32_t)n_dst;
+  uint32_t key[U];
+  auto fetch = [&](uint32_t n) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t i = (uint32_t)(u * kSmallBlock) + threadIdx.x;
+      key[u] = i < n ? (uint32_t)(i < nd ? dst[i] : col[i - nd]) : 0u;
+    }
+  };
+  fetch((uint32_t)(n_dst + m));  // (as many as there is room for: how many there are is on its way)
+  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  for (uint32_t i = threadIdx.x; i < kSlots; i += kSmallBlock) table[i] = kEmptySlot;
+  if (threadIdx.x == 0) st = BucketState{0u, 0u, 0u};
+  __syncthreads();
+  const uint32_t n = (uint32_t)(n_dst + m);
+  unsigned long long mine[U];
+  uint32_t h[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t i = (uint32_t)(u * kSmallBlock) + threadIdx.x;
+    h[u] = filter_hash(key[u]) >> (32 - 14);
+    mine[u] = i < n ? ((unsigned long long)key[u] << 32) | i : kEmptySlot;
+  }
+  bucket_insert_many<U>(table, kSlots, h, mine);
+  __syncthreads();
+  uint32_t f[U];
+  const int wave = wave_in_block(), lane = lane_id();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t i = (uint32_t)(u * kSmallBlock) + threadIdx.x;
+    f[u] = i < n ? (uint32_t)table[h[u]] : 0xFFFFFFFFu;
+    if (i < n && seed_twice(i, f[u], nd)) st.dup = 1;
+    const uint64_t b = ballot64(i >= nd && f[u] == i);
+    if (lane == 0) bits[u * kWaves + wave] = b;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    constexpr int kEach = (kWords + kWave - 1) / kWave;  // words in a row per lane
+    uint32_t c[kEach], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) {
+      const int w = lane * kEach + q;
+      c[q] = w < kWords ? (uint32_t)__popcll(bits[w]) : 0u;
+      sum += c[q];
+    }
+    const uint32_t incl = wave_incl_scan(sum);
+    uint32_t run = incl - sum;
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) {
+      const int w = lane * kEach + q;
+      if (w < kWords) before[w] = run;
+      run += c[q];
+    }
+    if (lane == kWave - 1) {  // the sizes
+      Ctl sizes = *ctl;
+      sizes.total_new = ctl->total_new = incl;
+      if (st.dup) sizes.err_dup = ctl->err_dup = 1;
+      if (pub.h != nullptr) send_ctl(pub.h, pub.ticket, sizes);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t i = (uint32_t)(u * kSmallBlock) + threadIdx.x;
+    if (i >= n) break;
+    if (i < nd) {
+      src[i] = (int32_t)key[u];
+      continue;
+    }
+    uint32_t local = f[u];
+    if (local >= nd) {
+      const uint32_t w = f[u] >> 6;
+      local = nd + before[w] + (uint32_t)__popcll(bits[w] & ((1ull << (f[u] & 63u)) - 1ull));
+      if (f[u] == i) src[local] = (int32_t)key[u];
+    }
+    col_local[i - nd] = (int32_t)local;
+  }
+}
+
 __global__ void k_clear_uniq_overflow(Ctl* ctl) { ctl->uniq_overflow = 0; }
 
 static inline unsigned nblocks(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -833,7 +940,7 @@ int g_unique_mode = 0;  // COOP_TUNE_UNIQUE: 0 automatic, 1 table in HBM, 2 part
 
 // launches the dedup's kernels up to the one that ranks the new vertices; the sizes are on their way to the host from the
 // kernel that finds the first positions on.  col_local serves as the array of first positions (edge order).
-enum UniqPath { kByFilter, kByPartition, kByTable };
+enum UniqPath { kByFilter, kByPartition, kByTable, kInOneBlock };
 static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
                          int32_t* spare, UniqueWork* w, UniqPath path, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
   const int64_t n_all = n_dst + m;
@@ -845,6 +952,14 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
   int shift = 0;
   TileNotes notes{};
   w->part_blocks = 0;
+  if (path == kInOneBlock) {  // (the relabelling too; spare becomes src_ids)
+    if (n_all <= 4 * kSmallBlock)
+      COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_small<4>, dim3(1), dim3(kSmallBlock), 0, s, dst, n_dst, col_global, m, m_dev, spare, col_local, d_ctl, w->pub);
+    else
+      COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_small<kSmallEach>, dim3(1), dim3(kSmallBlock), 0, s, dst, n_dst, col_global, m, m_dev, spare, col_local, d_ctl,
+                  w->pub);
+    return COOP_OK;
+  }
   if (path == kByFilter) {
     int log2_buckets = kFilterLeastLog2;
     while (log2_buckets < kFilterMostLog2 && (kFilterPairs << log2_buckets) < n_all) ++log2_buckets;
@@ -917,7 +1032,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
   return COOP_OK;
 }
 
-int unique_prepare(int64_t n_dst, int64_t m, bool tagged, UniqueWork* w, Alloc& alloc) {
+int unique_prepare(int64_t n_dst, int64_t m, bool deferred, UniqueWork* w, Alloc& alloc) {
   const int64_t n_all = n_dst + m;
   const int64_t n_words = (n_all + 63) / 64 - (n_dst >> 6);
   w->words = alloc.get<RankWord>(n_words, COOP_TAG_SCRATCH);
@@ -931,12 +1046,13 @@ int unique_prepare(int64_t n_dst, int64_t m, bool tagged, UniqueWork* w, Alloc& 
   // three less in the scatter, which has fewer buckets: 7.0 M 40.5 and 43.4.)
   const int64_t whole_rounds = w->n_buckets / 512 * 512;
   if (whole_rounds > 0 && n_all <= whole_rounds * (pairs_per_bucket + pairs_per_bucket / 8)) w->n_buckets = whole_rounds;
-  const int64_t filter_max = tagged ? kFilterTaggedMax : kFilterMax;
+  const int64_t filter_max = deferred ? kFilterTaggedMax : kFilterMax;
   const bool by_partition = m > 0 && w->n_buckets <= kPartMaxBuckets && g_unique_mode != 1 && (g_unique_mode >= 2 || n_all >= filter_max);
   const bool by_filter = !by_partition && g_unique_mode != 1 && n_all > 0 && n_all < filter_max;
-  w->tagged = tagged && by_filter && n_all >= kFilterTaggedFrom;
-  w->path = by_partition ? kByPartition : by_filter ? kByFilter : kByTable;
-  const bool bits = by_filter && n_all <= kShortMax;
+  w->tagged = deferred && by_filter && n_all >= kFilterTaggedFrom;
+  const bool small = deferred && by_filter && n_all <= kSmallMax;
+  w->path = by_partition ? kByPartition : small ? kInOneBlock : by_filter ? kByFilter : kByTable;
+  const bool bits = by_filter && !small && n_all <= kShortMax;
   w->clear = bits ? (uint64_t*)w->words : nullptr;
   w->n_clear = bits ? n_words : 0;
   return COOP_OK;
@@ -971,6 +1087,7 @@ int unique_back(const int32_t* dst, int64_t n_dst, const int32_t* col_global, in
                 int32_t* col_local, int32_t* src, hipStream_t s) {
   const int64_t n_threads = m > n_dst ? m : n_dst;
   const RankView rank{w.words, w.block_prefix, w.part_blocks};
+  if (w.path == kInOneBlock) return COOP_OK;
   if (n_threads > 0 && w.path == kByFilter && w.bits)
     COOP_LAUNCH(K_UNIQ_RELABEL, k_uniq_relabel_short, dim3((unsigned)((n_threads + kShortBlock * kShortEach - 1) / (kShortBlock * kShortEach))),
                 dim3(kShortBlock), 0, s, dst, col_global, m, m_dev, n_dst, (const unsigned long long*)w.words, src, col_local);

@@ -939,6 +939,35 @@ def test_frontier_dedup_by_tags(P, shape):
         compare_rw(P, g, perm[:20000], (2,), 2, 4, 0.5, seed=7)
 
 
+@pytest.mark.parametrize("shape", ["ring", "star", "few"])
+def test_frontier_dedup_in_one_block(P, shape):
+    """Lists that one block dedups and relabels (up to 7,936 entries, to both sides of that and of the 4,096 up to which a thread has
+    four entries), and seeds that stand in the list twice, for every way in which a list can be deduplicated."""
+    n = 300000
+    rng = np.random.default_rng(13)
+    if shape == "star":
+        indices = torch.full((n,), 7, dtype=torch.int32)
+    elif shape == "few":
+        indices = torch.from_numpy(rng.integers(0, 50, n).astype(np.int32))
+    else:
+        indices = ((torch.arange(n) + 7) % n).to(torch.int32)
+    g = G(P, torch.arange(n + 1, dtype=torch.int64), indices)
+    perm = rng.permutation(n).astype(np.int32)
+    for size in (1, 2, 31, 32, 33, 511, 512, 513, 2047, 2048, 2049, 3967, 3968, 3969):
+        compare(P, g, perm[:size], (1, 1), R.NS, seed=size)
+        compare(P, g, perm[:size], (2,), R.LABOR0, it=1, seed=size)
+    compare_rw(P, g, perm[:700], (2, 2), 2, 4, 0.5, seed=7)
+    for size in (2, 2000, 3900, 8000, 20000, 200000, 280000):
+        for first, second in ((0, size - 1), (size // 2, size // 2 + 1)):
+            seeds = perm[:size].copy()
+            if first != second and second < size:
+                seeds[second] = seeds[first]
+                for sampler in (R.NS, R.LABOR0):
+                    with pytest.raises(P.CoopError) as e:
+                        P.coop_sample(g.graph, torch.from_numpy(seeds).cuda(), (1,), sampler)
+                    assert e.value.code == -3, (size, first, second)
+
+
 @pytest.mark.parametrize("mode", [1, 0])
 def test_offsets_around_the_edges_of_tiles(P, mode):
     """Offsets that the filling kernel finds by itself (up to 32,768 destinations) and those that a scan leaves tile by tile
