@@ -598,7 +598,7 @@ __device__ __forceinline__ int64_t piece_start(uint32_t d, uint32_t q, uint32_t 
 // registers.
 template <int NF>
 __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_scan_plain(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg,
-                                                               const uint32_t* __restrict__ thr_all, int64_t n, int each_log2, FusedKeys keys,
+                                                               const uint32_t* __restrict__ thr_all, int64_t n, Dealing deal, FusedKeys keys,
                                                                uint32_t stage_cap, ScanOut out, Ctl* ctl, int piece_blocks,
                                                                const Piece* __restrict__ pieces, const uint32_t* __restrict__ piece_count,
                                                                uint32_t piece_cap, uint32_t piece_len, uint32_t stretch) {
@@ -648,7 +648,8 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
     }
     return;
   }
-  const int64_t w0 = (int64_t)xcd_runs(blockIdx.x - (uint32_t)piece_blocks, gridDim.x - (uint32_t)piece_blocks) << each_log2;
+  int each_log2;
+  const int64_t w0 = deal.first_list(blockIdx.x - (uint32_t)piece_blocks, &each_log2);
   if (w0 >= n) return;
   const uint32_t n_mine = n - w0 < ((int64_t)1 << each_log2) ? (uint32_t)(n - w0) : 1u << each_log2;
   const uint32_t lanes = 64u >> each_log2, sub = lane & (lanes - 1), number = lane >> (6 - each_log2);
@@ -797,7 +798,7 @@ struct LaborSink {
 template <int NF, bool EXACT>
 __global__ __launch_bounds__(kWave, NF == 1 ? 7 : NF == 2 ? 6 : NF == 3 ? 5 : 4) void
 k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg, const uint32_t* __restrict__ thr_all,
-                   const PreThr* __restrict__ pthr_all, const float* __restrict__ lim2_all, int64_t n, int each_log2, FusedKeys keys, uint32_t stage_cap,
+                   const PreThr* __restrict__ pthr_all, const float* __restrict__ lim2_all, int64_t n, Dealing deal, FusedKeys keys, uint32_t stage_cap,
                    ScanOut out, Ctl* ctl, int piece_blocks, const Piece* __restrict__ pieces, const uint32_t* __restrict__ piece_count,
                    uint32_t piece_cap, uint32_t piece_len, CandOut cand, uint32_t stretch) {
   __shared__ BlendQueue<false> queue[NF];
@@ -840,7 +841,8 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
     }
     return;
   }
-  const int64_t w0 = (int64_t)xcd_runs(blockIdx.x - (uint32_t)piece_blocks, gridDim.x - (uint32_t)piece_blocks) << each_log2;
+  int each_log2;
+  const int64_t w0 = deal.first_list(blockIdx.x - (uint32_t)piece_blocks, &each_log2);
   if (w0 >= n) return;
   const uint32_t n_mine = n - w0 < ((int64_t)1 << each_log2) ? (uint32_t)(n - w0) : 1u << each_log2;
   const uint32_t lanes = 64u >> each_log2, sub = lane & (lanes - 1), number = lane >> (6 - each_log2);
@@ -1045,13 +1047,13 @@ __global__ __launch_bounds__(kBlock) void k_labor_fill_overflow(const int32_t* _
 }
 
 static void launch_scan_blend(int nf, unsigned blocks, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, const PreThr* pthr,
-                              const float* lim2, int64_t n, int each_log2, const FusedKeys& keys, uint32_t cap, const ScanOut& out, Ctl* ctl,
+                              const float* lim2, int64_t n, const Dealing& deal, const FusedKeys& keys, uint32_t cap, const ScanOut& out, Ctl* ctl,
                               int piece_blocks, const Piece* pieces, const uint32_t* piece_count, uint32_t piece_cap, uint32_t piece_len,
                               const CandOut& cand /* no buffer: the exact blend in the scan */) {
 #define COOP_SCAN_BLEND(NF)                                                                                                                  \
   if (cand.buf != nullptr) { COOP_SCAN_BLEND_AS(NF, false); } else { COOP_SCAN_BLEND_AS(NF, true); }
 #define COOP_SCAN_BLEND_AS(NF, EXACT)                                                                                                        \
-  COOP_LAUNCH(K_LABOR_COUNT, (k_labor_scan_blend<NF, EXACT>), dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, pthr, lim2, n, each_log2, keys, cap, out, ctl, \
+  COOP_LAUNCH(K_LABOR_COUNT, (k_labor_scan_blend<NF, EXACT>), dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, pthr, lim2, n, deal, keys, cap, out, ctl, \
               piece_blocks, pieces, piece_count, piece_cap, piece_len, cand, (uint32_t)g_stretch)
   switch (nf) {
     case 1: COOP_SCAN_BLEND(1); break;
@@ -1062,11 +1064,11 @@ static void launch_scan_blend(int nf, unsigned blocks, hipStream_t s, const int3
 #undef COOP_SCAN_BLEND_AS
 #undef COOP_SCAN_BLEND
 }
-static void launch_scan_plain(int nf, unsigned blocks, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, int64_t n, int each_log2,
+static void launch_scan_plain(int nf, unsigned blocks, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, int64_t n, const Dealing& deal,
                               const FusedKeys& keys, uint32_t cap, const ScanOut& out, Ctl* ctl, int piece_blocks, const Piece* pieces,
                               const uint32_t* piece_count, uint32_t piece_cap, uint32_t piece_len) {
 #define COOP_SCAN_PLAIN(NF)                                                                                                           \
-  COOP_LAUNCH(K_LABOR_COUNT, k_labor_scan_plain<NF>, dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, n, each_log2, keys, cap, out, ctl, \
+  COOP_LAUNCH(K_LABOR_COUNT, k_labor_scan_plain<NF>, dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, n, deal, keys, cap, out, ctl, \
               piece_blocks, pieces, piece_count, piece_cap, piece_len, (uint32_t)g_stretch)
   switch (nf) {
     case 1: COOP_SCAN_PLAIN(1); break;
@@ -1295,12 +1297,13 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
       if (g_lists_per_wave != 0) while ((1 << each_log2) < g_lists_per_wave) ++each_log2;
       else while (each_log2 < kScanEachLog2 && (n_new >> (each_log2 + 1)) >= kScanWaves) ++each_log2;
       while (each_log2 < 6 && (n_new >> each_log2) > kSliceLists / 2) ++each_log2;  // (no more waves than a launch can have)
-      const unsigned blocks = (unsigned)(((n_new + ((int64_t)1 << each_log2) - 1) >> each_log2) + piece_waves);
+      const Dealing deal = deal_lists(n_new, each_log2);
+      const unsigned blocks = deal.blocks + (unsigned)piece_waves;
       if (cx.blend)
-        launch_scan_blend(ps.nf, blocks, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, each_log2, keys, cap, out, cx.d_ctl, (int)piece_waves,
+        launch_scan_blend(ps.nf, blocks, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, deal, keys, cap, out, cx.d_ctl, (int)piece_waves,
                           pieces, pcount, piece_cap, piece_len, cand);
       else
-        launch_scan_plain(ps.nf, blocks, s, cx.g->indices, ps.seg, ps.thr, n_new, each_log2, keys, cap, out, cx.d_ctl, (int)piece_waves, pieces,
+        launch_scan_plain(ps.nf, blocks, s, cx.g->indices, ps.seg, ps.thr, n_new, deal, keys, cap, out, cx.d_ctl, (int)piece_waves, pieces,
                           pcount, piece_cap, piece_len);
       if (queued) {  // stage 3: the exact blend for the candidates that the scan appended
         const unsigned blocks = blocks_for(cand.cap_each, kBlock) < 16 ? blocks_for(cand.cap_each, kBlock) : 16;

@@ -640,19 +640,19 @@ __global__ __launch_bounds__(kWave, 8) void k_ns_fill(const int32_t* __restrict_
                                                     uint32_t cap, LayerKeys keys, int64_t* indptr, int64_t first, int tile_log2,
                                                     EdgeOut edges, int64_t edge_limit, Ctl* ctl,
                                                     uint32_t long_min, const uint32_t* __restrict__ long_list,
-                                                    const uint32_t* __restrict__ n_long, int long_blocks, int each_log2, uint32_t stretch) {
+                                                    const uint32_t* __restrict__ n_long, int long_blocks, Dealing deal, uint32_t stretch) {
   extern __shared__ __align__(16) uint32_t lds_words[];  // cap slots, and one per lane
   NsSlot* slot = reinterpret_cast<NsSlot*>(lds_words);
   const uint32_t lane = (uint32_t)lane_id();
   uint32_t w0, n_mine = 1, skip_above = 0xFFFFFFFFu;
+  int each_log2 = 0;
   if ((int)blockIdx.x < long_blocks) {  // the first blocks: a queued long list each (the queue's length is read from device memory)
     uint32_t n_queued = *n_long;
     if (n_queued > n_dst) n_queued = n_dst;  // (holds by construction; keeps every access inside the queue regardless)
     if (blockIdx.x >= n_queued) return;
     w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)long_list[blockIdx.x]);
-    each_log2 = 0;
   } else {
-    w0 = xcd_runs(blockIdx.x - (uint32_t)long_blocks, gridDim.x - (uint32_t)long_blocks) << each_log2;
+    w0 = (uint32_t)deal.first_list(blockIdx.x - (uint32_t)long_blocks, &each_log2);
     n_mine = 1u << each_log2;
     if (long_min != 0) skip_above = long_min;
   }
@@ -788,18 +788,18 @@ __global__ __launch_bounds__(kWave, 7) void k_ns_collect(const int32_t* __restri
                                                          const NsBlendThr* __restrict__ bthr, uint32_t n_dst, uint32_t k, LayerKeys keys, float cw,
                                                          float sw, int64_t* indptr, int64_t first, int tile_log2, EdgeOut edges, int64_t edge_limit, StageEntry* __restrict__ rows, uint32_t row_cap,
                                                          uint32_t* __restrict__ n_cand, uint32_t long_min, const uint32_t* __restrict__ long_list,
-                                                         const uint32_t* __restrict__ n_long, int long_blocks, int each_log2, uint32_t stretch) {
+                                                         const uint32_t* __restrict__ n_long, int long_blocks, Dealing deal, uint32_t stretch) {
   __shared__ BlendQueue<true> queue;
   const uint32_t lane = (uint32_t)lane_id();
   uint32_t w0, n_mine = 1, skip_above = 0xFFFFFFFFu;
+  int each_log2 = 0;
   if ((int)blockIdx.x < long_blocks) {
     uint32_t n_queued = *n_long;
     if (n_queued > n_dst) n_queued = n_dst;  // (holds by construction; keeps every access inside the queue regardless)
     if (blockIdx.x >= n_queued) return;
     w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)long_list[blockIdx.x]);
-    each_log2 = 0;
   } else {
-    w0 = xcd_runs(blockIdx.x - (uint32_t)long_blocks, gridDim.x - (uint32_t)long_blocks) << each_log2;
+    w0 = (uint32_t)deal.first_list(blockIdx.x - (uint32_t)long_blocks, &each_log2);
     n_mine = 1u << each_log2;
     if (long_min != 0) skip_above = long_min;
   }
@@ -1250,6 +1250,7 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
       const dim3 grid_w(blocks_for(n, kWavesPerBlock));
       int each_log2 = 0;
       while (each_log2 < 3 && (n >> (each_log2 + 1)) >= kNsFillWaves) ++each_log2;
+      const Dealing deal = deal_lists(n, each_log2);
       const NsRecord* rec_b = rec + b;
       const NsBlendThr* bthr_b = cx.blend ? bthr + b : nullptr;
       const int64_t* eptr_b = blk->indptr + b;
@@ -1266,9 +1267,9 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
         int lists_log2 = 0;
         while (lists_log2 < 6 && (n >> (lists_log2 + 1)) >= kNsRedoWaves) ++lists_log2;
         const dim3 grid_redo(blocks_for(n, (int64_t)wpb << lists_log2));
-        COOP_LAUNCH(K_NS_FILL, k_ns_collect, dim3(blocks_for(n, (int64_t)1 << each_log2) + (unsigned)long_blocks), dim3(kWave), 0, s, cx.g->indices,
+        COOP_LAUNCH(K_NS_FILL, k_ns_collect, dim3(deal.blocks + (unsigned)long_blocks), dim3(kWave), 0, s, cx.g->indices,
                     rec_b, bthr_b, (uint32_t)n, k, vp.K, (float)vp.cw, (float)vp.sw, blk->indptr, b, tile_log2, edges, m, rows_b,
-                    row_cap, n_cand_b, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2, (uint32_t)g_stretch);
+                    row_cap, n_cand_b, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, deal, (uint32_t)g_stretch);
         COOP_LAUNCH(K_NS_SELECT, k_ns_select, dim3(blocks_for(n, (int64_t)1 << select_log2)), dim3(kWave), (size_t)cap * sizeof(NsSlot), s, rec_b, n, k, vp,
                     eptr_b, edges, (const StageEntry*)rows_b, row_cap, n_cand_b, bthr_b, select_log2, group_log2);
 #define COOP_NS_BLEND(VEC4) \
@@ -1276,9 +1277,9 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
         if (cx.vec4) { COOP_NS_BLEND(true); } else { COOP_NS_BLEND(false); }
 #undef COOP_NS_BLEND
       } else {
-        COOP_LAUNCH(K_NS_FILL, k_ns_fill, dim3(blocks_for(n, (int64_t)1 << each_log2) + (unsigned)long_blocks), dim3(kWave),
+        COOP_LAUNCH(K_NS_FILL, k_ns_fill, dim3(deal.blocks + (unsigned)long_blocks), dim3(kWave),
                     (cap + kWave) * sizeof(NsSlot), s, cx.g->indices, rec_b, (uint32_t)n, k, cap, vp.K, blk->indptr, b, tile_log2,
-                    edges, m, cx.d_ctl, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, each_log2,
+                    edges, m, cx.d_ctl, long_min, (const uint32_t*)long_list, (const uint32_t*)n_long, long_blocks, deal,
                     (uint32_t)g_stretch);
       }
 #undef COOP_NS_ARGS

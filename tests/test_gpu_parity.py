@@ -968,6 +968,29 @@ def test_frontier_dedup_in_one_block(P, shape):
                     assert e.value.code == -3, (size, first, second)
 
 
+@pytest.mark.parametrize("size", [1, 2, 3, 5, 17, 32767, 32769, 65535, 65537, 131071, 131072, 131073, 140001])
+def test_lists_dealt_to_the_last_waves(P, size):
+    """The last lists of a pass go to waves that take fewer of them: numbers of destinations to both sides of those from which a wave
+    takes two, four and eight, and some that divide into nothing; lists of 0 to 90 entries."""
+    n = 150000
+    rng = np.random.default_rng(22)
+    deg = rng.integers(0, 7, n) + 85 * (rng.random(n) < 0.02)
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]).astype(np.int64))
+    g = G(P, indptr, torch.from_numpy(rng.integers(0, n, int(deg.sum())).astype(np.int32)))
+    seeds = rng.permutation(n)[:size]
+    compare(P, g, seeds, (3,), R.NS, seed=size)
+    compare(P, g, seeds, (3,), R.LABOR0, seed=size)
+    if size < 40000:
+        compare(P, g, seeds, (3,), R.NS, it=1, kappa=3, seed=size)
+        compare(P, g, seeds, (3,), R.LABOR0, it=1, kappa=3, seed=size)
+        for each in (4, 8, 64):
+            P.coop_tune(P.COOP_TUNE_LISTS_PER_WAVE, each)
+            try:
+                compare(P, g, seeds, (3, 2), R.LABOR0, seed=size + each)
+            finally:
+                P.coop_tune(P.COOP_TUNE_LISTS_PER_WAVE, 0)
+
+
 @pytest.mark.parametrize("mode", [1, 0])
 def test_offsets_around_the_edges_of_tiles(P, mode):
     """Offsets that the filling kernel finds by itself (up to 32,768 destinations) and those that a scan leaves tile by tile
