@@ -981,50 +981,71 @@ __global__ void k_labor_redo(Ctl* ctl, uint32_t* piece_count, uint32_t* cand_cou
   cand_count[threadIdx.x] = 0;
 }
 
-// staged rows -> the block's edge arrays: kFillLanes threads per destination, each taking every kFillLanes-th slot
-constexpr int kFillLanesLog2 = 3;
+// staged rows -> the block's edge arrays: 2^LOG2 neighbouring threads per destination, each taking every 2^LOG2-th slot
 constexpr int kFillOwnBlock = 1024;  // where a block adds up the counts in front of it: fewer and larger ones
+// Four threads per destination where there are many: the rows of 464 thousand destinations 43.6 us with eight, 56 with sixteen, 50 with
+// two, 35.9 with four (41.8 and 37.3 before a lane ranked its four slots in one go over the positions).  Sixteen where a block adds up
+// the counts in front of it: there it is the wait for memory that counts, and more blocks share the work (264 destinations 7.4 us with
+// eight, 6.1; 16,384 of them 9.1 and 7.9), up to the number from which adding up costs more (30 thousand 9.9 and 11.0).
+constexpr int kFillLog2 = 2, kFillOwnLog2 = 3, kFillFewLog2 = 4;
+constexpr int64_t kFillFew = 20480;
 // (edge_limit: entries of col_global / eid; nothing is written beyond them)
-template <bool OWN, int BLOCK>
+template <bool OWN, int BLOCK, int LOG2>
 __global__ __launch_bounds__(BLOCK) void k_labor_fill_staged(LayerChunks ch, CountOffsets co, int64_t first, int64_t n_dst, uint32_t stage_cap,
                                                              EdgeOut edges, int64_t edge_limit) {
-  __shared__ uint32_t row_j[BLOCK >> kFillLanesLog2][kWave];  // list positions of one staged row per lane group
+  __shared__ uint32_t row_j[BLOCK >> LOG2][kWave];  // list positions of one staged row per lane group
   const int64_t idx = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  const int64_t w = first + (idx >> kFillLanesLog2);
+  const int64_t w = first + (idx >> LOG2);
+  // What is known of the destination is requested ahead of its offset and count, and so is as much of its row as nearly all hold.
+  const int64_t w_in = w < n_dst ? w : n_dst - 1;
+  const int p = ch.find(w_in);
+  const int64_t local = w_in - ch.start[p];
+  const StageEntry* __restrict__ row = ch.stage[p] + (size_t)local * stage_cap;
+  const int64_t beg = ch.seg[p][local].beg;
+  const int sub = (int)(idx & ((1 << LOG2) - 1));
+  constexpr int kPerLane = kWave >> LOG2, kAhead = 16 >> LOG2;
+  StageEntry mine[kPerLane];
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) {
+    const int slot = sub + (i << LOG2);
+    mine[i] = row[slot < (int)stage_cap ? slot : 0];
+  }
   int32_t c;
-  const int64_t o = offset_of<OWN, BLOCK, kFillLanesLog2>(co, w, n_dst, &c);
+  const int64_t o = offset_of<OWN, BLOCK, LOG2>(co, w, n_dst, &c);
   if (w >= n_dst) return;
   if (c > (int32_t)stage_cap) return;  // overflowed row: the overflow pass writes these edges
-  const int p = ch.find(w);
-  const int64_t local = w - ch.start[p];
-  const StageEntry* __restrict__ row = ch.stage[p] + (size_t)local * stage_cap;
-  const Segment g = ch.seg[p][local];
-  const int sub = (int)(idx & ((1 << kFillLanesLog2) - 1));
   // A row may hold its entries in any order (the pieces of a cut list, the lists found from the other side and the
   // blended passes take slots by atomics): an entry's place is its rank by list position.  The lane group (all in one
   // wave) shares the positions through LDS.  The rows that k_labor_scan_plain leaves in list order, those of uncut lists, go the
   // same way: two paths side by side in a wave cost more than ranking a dozen entries.
-  uint32_t* js = row_j[threadIdx.x >> kFillLanesLog2];
-  constexpr int kPerLane = kWave >> kFillLanesLog2;
-  StageEntry mine[kPerLane];
+  uint32_t* js = row_j[threadIdx.x >> LOG2];
 #pragma unroll
   for (int i = 0; i < kPerLane; ++i) {
-    const int slot = sub + (i << kFillLanesLog2);
-    mine[i] = StageEntry{0, 0xFFFFFFFFu};
-    if (slot < c) { mine[i] = row[slot]; js[slot] = mine[i].j; }  // (only js[0..c) is read below)
+    const int slot = sub + (i << LOG2);
+    if (i >= kAhead) mine[i] = StageEntry{0, 0u};
+    if (slot < c) {  // (only js[0..c) is read below)
+      if (i >= kAhead) mine[i] = row[slot];
+      js[slot] = mine[i].j;
+    }
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  constexpr int kTogether = kAhead;  // slots of a lane whose ranks are counted together
 #pragma unroll
-  for (int i = 0; i < kPerLane; ++i) {
-    const int slot = sub + (i << kFillLanesLog2);
-    if (slot >= c) break;
-    uint32_t place = 0;
-    for (int q = 0; q < c; ++q) place += js[q] < mine[i].j;
-    if (o + (int64_t)place < edge_limit) {
-      put_edge(edges, o, place, mine[i].t, g.beg + mine[i].j);
+  for (int i0 = 0; i0 < kPerLane; i0 += kTogether) {
+    if (sub + (i0 << LOG2) >= c) break;
+    uint32_t place[kTogether];
+#pragma unroll
+    for (int i = 0; i < kTogether; ++i) place[i] = 0;
+    for (int q = 0; q < c; ++q) {
+      const uint32_t j = js[q];
+#pragma unroll
+      for (int i = 0; i < kTogether; ++i) place[i] += j < mine[i0 + i].j;
     }
+#pragma unroll
+    for (int i = 0; i < kTogether; ++i)
+      if (sub + ((i0 + i) << LOG2) < c && o + (int64_t)place[i] < edge_limit) put_edge(edges, o, place[i], mine[i0 + i].t, beg + mine[i0 + i].j);
   }
 }
 
@@ -1341,15 +1362,18 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
 
   const EdgeOut edges{blk->col_global, blk->eid, cx.tags};
   if (m > 0 && n_dst > 0) {
-    constexpr int64_t kSliceRows = kSliceLists << (6 - kFillLanesLog2);
+    constexpr int64_t kSliceRows = kSliceLists << (6 - kFillLog2);
     const CountOffsets co{counts, blk->indptr, &cx.d_ctl->total_edges};
-    if (own)
-      COOP_LAUNCH(K_LABOR_FILL, (k_labor_fill_staged<true, kFillOwnBlock>), dim3(blocks_for(n_dst << kFillLanesLog2, kFillOwnBlock)), dim3(kFillOwnBlock),
-                  0, s, ch, co, (int64_t)0, n_dst, cap, edges, m);
+    if (own && n_dst <= kFillFew)
+      COOP_LAUNCH(K_LABOR_FILL, (k_labor_fill_staged<true, kFillOwnBlock, kFillFewLog2>), dim3(blocks_for(n_dst << kFillFewLog2, kFillOwnBlock)),
+                  dim3(kFillOwnBlock), 0, s, ch, co, (int64_t)0, n_dst, cap, edges, m);
+    else if (own)
+      COOP_LAUNCH(K_LABOR_FILL, (k_labor_fill_staged<true, kFillOwnBlock, kFillOwnLog2>), dim3(blocks_for(n_dst << kFillOwnLog2, kFillOwnBlock)),
+                  dim3(kFillOwnBlock), 0, s, ch, co, (int64_t)0, n_dst, cap, edges, m);
     else
       for (int64_t b = 0; b < n_dst; b += kSliceRows)
-        COOP_LAUNCH(K_LABOR_FILL, (k_labor_fill_staged<false, kBlock>),
-                    dim3(blocks_for((n_dst - b < kSliceRows ? n_dst - b : kSliceRows) << kFillLanesLog2, kBlock)), dim3(kBlock), 0, s, ch, co, b, n_dst,
+        COOP_LAUNCH(K_LABOR_FILL, (k_labor_fill_staged<false, kBlock, kFillLog2>),
+                    dim3(blocks_for((n_dst - b < kSliceRows ? n_dst - b : kSliceRows) << kFillLog2, kBlock)), dim3(kBlock), 0, s, ch, co, b, n_dst,
                     cap, edges, m);
     if (!defer && cx.h_ctl->n_overflow > 0) {
       LayerKeys K{};
