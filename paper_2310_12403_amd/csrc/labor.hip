@@ -1327,7 +1327,12 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
         launch_scan_plain(ps.nf, blocks, s, cx.g->indices, ps.seg, ps.thr, n_new, deal, keys, cap, out, cx.d_ctl, (int)piece_waves, pieces,
                           pcount, piece_cap, piece_len);
       if (queued) {  // stage 3: the exact blend for the candidates that the scan appended
-        const unsigned blocks = blocks_for(cand.cap_each, kBlock) < 16 ? blocks_for(cand.cap_each, kBlock) : 16;
+        // (Blocks for an eighth of the kept edges, where a few percent are undecided, at most 16 a sub-buffer; the threads stride, so more
+        // candidates only take longer.  With as many blocks as the buffers have room for, 4,096, a launch over 113 thousand destinations
+        // and two layers took 19.9 us and one over 463 thousand 19.6, most of it for blocks with nothing to do; now 7.5 and 10.1.)
+        const int64_t expected = ((int64_t)ks[0] * n_new * ps.nf) / 8;
+        const int64_t each = (expected / kCandSub + kBlock - 1) / kBlock + 1;
+        const unsigned blocks = (unsigned)(each < 16 ? each : 16);
         COOP_LAUNCH(K_LABOR_EXACT, k_labor_exact, dim3(blocks, kCandSub), dim3(kBlock), 0, s, cand, ps.thr, n_new, ps.nf, keys, cap, out,
                     cx.d_ctl);
       }
