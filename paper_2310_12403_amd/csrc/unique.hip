@@ -457,7 +457,7 @@ template <int PER>
 __global__ __launch_bounds__(kPartBlock, PER <= 2 ? 8 : 4) void k_part_scatter(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
                                                              int64_t m, const int64_t* __restrict__ m_dev, uint32_t n_buckets,
                                                              TiledScan<uint32_t> place, unsigned long long* __restrict__ pairs, TileNotes notes) {
-  __shared__ unsigned long long staged[kTilePairs];  // the tile's pairs, by bucket
+  __shared__ unsigned long long staged[kTilePairs];  // the tile's pairs, by bucket: key, bucket (16 bits), number in the tile (16 bits)
   extern __shared__ uint32_t off[];                  // [n_buckets] the tile's tallies, then run starts in the tile
   uint32_t* delta = off + n_buckets;                 // [n_buckets] run start in pairs[] minus run start in the tile
   __shared__ uint32_t wave_total[kPartBlock / kWave];
@@ -467,6 +467,16 @@ __global__ __launch_bounds__(kPartBlock, PER <= 2 ? 8 : 4) void k_part_scatter(c
   const uint32_t column = part_column();
   const int lane = lane_id(), wave = wave_in_block();
   constexpr int U = kTilePairs / kPartBlock;
+  // A tile's keys are requested before anything else, the next tile's when this one's stand in LDS.
+  uint32_t key[U];
+  auto fetch = [&](int64_t tile) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = tile + u * kPartBlock + threadIdx.x;
+      key[u] = i < hi ? (uint32_t)(i < n_dst ? dst[i] : col[i - n_dst]) : 0u;
+    }
+  };
+  fetch(lo);
   uint32_t cursor[PER];  // next free place of this thread's buckets in this column
 #pragma unroll
   for (uint32_t q = 0; q < PER; ++q) {
@@ -478,12 +488,7 @@ __global__ __launch_bounds__(kPartBlock, PER <= 2 ? 8 : 4) void k_part_scatter(c
   for (int64_t tile = lo; tile < hi; tile += kTilePairs) {
     const uint32_t tile_n = (uint32_t)(hi - tile < kTilePairs ? hi - tile : kTilePairs);
     const bool has_edges = tile + tile_n > n_dst;
-    uint32_t key[U], place_in[U];  // place_in: bucket << 16 | rank in the tile's bucket
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = tile + u * kPartBlock + threadIdx.x;
-      key[u] = i < hi ? (uint32_t)(i < n_dst ? dst[i] : col[i - n_dst]) : 0u;
-    }
+    uint32_t place_in[U];  // bucket << 16 | rank in the tile's bucket
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t bucket = bucket_of_hash(hash_of_key(key[u]), n_buckets);
@@ -519,16 +524,18 @@ __global__ __launch_bounds__(kPartBlock, PER <= 2 ? 8 : 4) void k_part_scatter(c
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t j = (uint32_t)(u * kPartBlock) + threadIdx.x;
-      if (j < tile_n) staged[off[place_in[u] >> 16] + (place_in[u] & 0xFFFFu)] = ((unsigned long long)key[u] << 32) | j;
+      if (j < tile_n) 
+        staged[off[place_in[u] >> 16] + (place_in[u] & 0xFFFFu)] = ((unsigned long long)key[u] << 32) | (place_in[u] & 0xFFFF0000u) | j;
     }
+    if (tile + kTilePairs < hi) fetch(tile + kTilePairs);
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t j = (uint32_t)(u * kPartBlock) + threadIdx.x;
       if (j < tile_n) {
         const unsigned long long pr = staged[j];
-        const uint32_t to = delta[bucket_of_hash(hash_of_key((uint32_t)(pr >> 32)), n_buckets)] + j;
-        pairs[to] = pr + (uint32_t)tile;  // (positions stay below 2^32)
+        const uint32_t to = delta[(uint32_t)pr >> 16] + j;
+        pairs[to] = (pr >> 32 << 32) | ((uint32_t)tile + ((uint32_t)pr & 0xFFFFu));  // (positions stay below 2^32)
         if (has_edges) {
           *notes.went(tile + j, n_dst) = to;
           *notes.which_of(tile + j, n_dst) = (uint16_t)pr;
@@ -989,6 +996,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     const size_t lds = (size_t)n_buckets * sizeof(uint32_t);
     COOP_LAUNCH(K_PART_COUNT, k_part_count, dim3(G), dim3(kPartBlock), lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets, counts);
     const TiledScan<uint32_t> places = scan_u32_tiled(counts, n_counts, place, tmp, d_ctl, s);
+    static_assert(kPartMaxBuckets <= 65536 && kTilePairs <= 65536, "a staged pair has 16 bits for either");
     static_assert(kPartMaxBuckets <= 8 * kPartBlock, "a thread of the scatter looks after eight buckets at most");
     if (n_buckets <= 2 * kPartBlock)
       COOP_LAUNCH(K_PART_SCATTER, k_part_scatter<2>, dim3(G), dim3(kPartBlock), 2 * lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets,
