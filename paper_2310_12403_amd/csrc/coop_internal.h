@@ -248,5 +248,11 @@ struct coop_graph {
     for (; k < 32; ++k) n += census[k];
     return n;
   }
+  // every list has fewer entries than this (when the graph was looked at)
+  int64_t longest_list_below() const {
+    int k = 31;
+    while (k > 0 && census[k] == 0) --k;
+    return (int64_t)2 << k;
+  }
 };
 constexpr int64_t kLongListDegree = 8192;  // default of COOP_TUNE_ENUM_DEGREE

@@ -1100,7 +1100,9 @@ static void launch_scan_plain(int nf, unsigned blocks, hipStream_t s, const int3
 #undef COOP_SCAN_PLAIN
 }
 
-constexpr int64_t kPieceWaves = 8192;  // one round of resident waves
+// One round of resident waves; fewer where there cannot be as many pieces.  (Starting 8,192 that find nothing costs a pass over a few
+// hundred lists 2 us.)
+constexpr int64_t kPieceWaves = 8192;
 // Destinations per wave, as a power of two: products-, papers100M-shaped and dependent steps 677, 1105 and 1043 us by this rule, 677,
 // 1103 and 1045 with four in every pass, 680, 1114 and 1046 with eight, 698, 1131 and 1072 with sixteen; the reddit-shaped step with a
 // cache, passes of a few thousand lists: 271 by this rule (one), 284 with four.
@@ -1158,13 +1160,16 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
     ks[f] = (uint32_t)cx.fanouts[l + f];
   }
   // long lists are cut into pieces (k_segments queues them); room for every piece the graph's edges could make
-  const uint32_t piece_len = (uint32_t)g_piece_len;
+  uint32_t piece_len = (uint32_t)g_piece_len;
   // Lists longer than split_min go to the piece waves, which come first in the grid.  With independent variates that is
   // for the lists worth cutting (twice the piece length).  The blended scan costs three times as much per entry, and a
   // wave that meets a few lists of several thousand entries late in the kernel keeps it waiting: there every list above
   // 2,048 entries goes first, whole if it is shorter than two pieces (papers100M-shaped, kappa 16: scan 1.44 -> 1.32 ms;
   // no difference with independent variates).
   const uint32_t split_min = g_split_min != 0 ? (uint32_t)g_split_min : (cx.blend && piece_len >= 2048u ? 2048u : 2u * piece_len);
+  // (a graph whose degrees were looked at when it was registered and that has no such list: nothing is queued)
+  const int64_t most_long = cx.g->lists_longer_than(split_min);
+  if (most_long == 0) piece_len = 0;
   // A call on unaligned indices takes memory for neither the queue nor the candidates of the exact blend (programs sized their
   // arenas for such calls when every list was read by one wave, an entry at a time): its queue lies in an array of the layer that is
   // written after the scan, with as many pieces as that holds, and the scan evaluates the exact blend itself.  (A list of 2 million
@@ -1311,7 +1316,11 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
                     eo, cx.d_ctl);
       }
       // the piece waves come first in the grid: one round of resident blocks, fewer if there cannot be that many pieces
-      const int64_t piece_waves = (int64_t)piece_cap < kPieceWaves ? (int64_t)piece_cap : kPieceWaves;
+      int64_t piece_waves = (int64_t)piece_cap < kPieceWaves ? (int64_t)piece_cap : kPieceWaves;
+      if (piece_len != 0 && cx.g->have_census) {  // (the longest list in pieces, for every list that can be long)
+        const int64_t most = (n_new < most_long ? n_new : most_long) * (int64_t)((cx.g->longest_list_below() - 1) / piece_len + 1);
+        if (most < piece_waves) piece_waves = most;
+      }
       const uint32_t* pcount = cx.d_piece_count + l;
       // destinations per wave: up to eight, where that leaves kScanWaves waves (the knob overrides, the next power of two)
       int each_log2 = 0;
