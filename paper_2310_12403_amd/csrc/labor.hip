@@ -1100,6 +1100,8 @@ static void launch_scan_plain(int nf, unsigned blocks, hipStream_t s, const int3
 #undef COOP_SCAN_PLAIN
 }
 
+constexpr int64_t kFewLists = 16384;
+constexpr uint32_t kFewPieceLen = 1024;
 // One round of resident waves; fewer where there cannot be as many pieces.  (Starting 8,192 that find nothing costs a pass over a few
 // hundred lists 2 us.)
 constexpr int64_t kPieceWaves = 8192;
@@ -1166,7 +1168,15 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
   // wave that meets a few lists of several thousand entries late in the kernel keeps it waiting: there every list above
   // 2,048 entries goes first, whole if it is shorter than two pieces (papers100M-shaped, kappa 16: scan 1.44 -> 1.32 ms;
   // no difference with independent variates).
-  const uint32_t split_min = g_split_min != 0 ? (uint32_t)g_split_min : (cx.blend && piece_len >= 2048u ? 2048u : 2u * piece_len);
+  uint32_t split_min = g_split_min != 0 ? (uint32_t)g_split_min : (cx.blend && piece_len >= 2048u ? 2048u : 2u * piece_len);
+  const int64_t room_pieces = piece_len != 0 ? cx.g->n_edges / piece_len : 0, room_lists = piece_len != 0 ? cx.g->n_edges / (int64_t)split_min + 1 : 0;
+  // A pass that does not fill the chip with its lists ends when its longest list does: those are cut into pieces that one step of a
+  // wave's requests covers.  (64 seeds, three layers 147 -> 142 us, 1,024 seeds 117 -> 114, both with pieces of 1,024; of 512 144 and
+  // 115.  A queue with no room for that many pieces leaves lists whole.)
+  if (n_new < kFewLists && piece_len == kPieceLen && g_split_min == 0) {
+    piece_len = kFewPieceLen;
+    split_min = 2 * kFewPieceLen;
+  }
   // (a graph whose degrees were looked at when it was registered and that has no such list: nothing is queued)
   const int64_t most_long = cx.g->lists_longer_than(split_min);
   if (most_long == 0) piece_len = 0;
@@ -1179,10 +1189,8 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
   if (!cx.vec4 && defer) blk->eid = alloc.get<int64_t>(edge_cap, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
   if (piece_len != 0 && n_new > 0) {
-    const int64_t by_edges = cx.g->n_edges / piece_len;
-    const int64_t long_lists = cx.g->n_edges / (int64_t)split_min + 1;
     const int64_t most = cx.vec4 ? (int64_t)1 << 30 : defer ? edge_cap : n_dst + 1;
-    const int64_t cap64 = by_edges + (n_new < long_lists ? n_new : long_lists) + 1;
+    const int64_t cap64 = room_pieces + (n_new < room_lists ? n_new : room_lists) + 1;
     piece_cap = (uint32_t)(cap64 < most ? cap64 : most);
     static_assert(sizeof(Piece) == sizeof(int64_t), "a piece takes the place of an offset or a position");
     pieces = cx.vec4 ? alloc.get<Piece>(piece_cap, COOP_TAG_SCRATCH) : (Piece*)(defer ? blk->eid : blk->indptr);

@@ -88,7 +88,7 @@ int read_ctl(Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
 int g_stage_cap_override = 0;  // COOP_TUNE_STAGE_CAP
 int g_lists_per_wave = 0;      // COOP_TUNE_LISTS_PER_WAVE (0 = automatic)
 int g_fuse_layers = 1;         // COOP_TUNE_FUSE_LAYERS
-int g_piece_len = 4096;        // COOP_TUNE_PIECE_LEN
+int g_piece_len = kPieceLen;   // COOP_TUNE_PIECE_LEN
 int g_split_min = 0;           // COOP_TUNE_SPLIT_MIN (0 = twice the piece length)
 int64_t g_blend_candidates = 0;  // COOP_TUNE_BLEND_CANDIDATES (0 = automatic)
 int g_defer_sizes = 1;         // COOP_TUNE_DEFER_SIZES
