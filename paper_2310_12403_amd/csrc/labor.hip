@@ -334,14 +334,15 @@ constexpr int kCandSub = 256;
 // thousand destinations of the reddit-shaped step with a cache: 10.5 us a launch and 8.5).
 template <int kSegBlock, bool SHARED = false>
 __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restrict__ g_indptr, int64_t n_vertices,
-                                                     const int32_t* __restrict__ dst, int64_t n, int nf,
+                                                     const int32_t* dst, int64_t n, int nf,
                                                      uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3, Segment* __restrict__ seg,
                                                      uint32_t* __restrict__ thr, PreThr* __restrict__ pthr, float* __restrict__ lim2,
                                                      double cw, double sw, Ctl* ctl,
                                                      uint32_t piece_len, uint32_t split_min, Piece* __restrict__ pieces, uint32_t piece_cap,
                                                      uint32_t* __restrict__ piece_count, ScanOut out, uint32_t enum_degree,
                                                      uint32_t* __restrict__ long_bits, LongSlot* __restrict__ long_tab, uint32_t long_mask,
-                                                     Clear clear, uint32_t* __restrict__ cand_count /* kCandSub, set to zero; null when c = 0 */) {
+                                                     Clear clear, Begin begin, uint32_t* __restrict__ cand_count /* kCandSub, set to zero; null when c = 0 */) {
+  dst = begin_in_block(begin, dst);
   clear_words(clear);
   if (cand_count != nullptr && blockIdx.x == 0)
     for (int q = threadIdx.x; q < kCandSub; q += kSegBlock) cand_count[q] = 0;
@@ -1304,7 +1305,7 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
   COOP_LAUNCH(K_SEGMENTS, (k_segments<BLOCK, SHARED>), dim3(blocks_for(n_new, EACH)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices,  \
               dst + ps.start, n_new, ps.nf, ks[0], ks[1], ks[2], ks[3], ps.seg, ps.thr, pthr, lim2, cx.cw, cx.sw,                        \
               cx.d_ctl, piece_len, split_min, pieces, piece_cap, cx.d_piece_count + l, out, enum_degree,    \
-              long_bits, long_tab, long_mask, clear, cand_count)
+              long_bits, long_tab, long_mask, clear, take_begin(cx, blocks_for(n_new, EACH)), cand_count)
       if (n_new >= kSegWideFrom) COOP_SEGMENTS(1024, 1024, false);
       else if (n_new >= kSegSharedBelow || !cx.blend) COOP_SEGMENTS(256, 256, false);
       else COOP_SEGMENTS(3 * kWave, kWave, true);

@@ -37,11 +37,12 @@ constexpr int64_t kNsCountWideFrom = 262144;
 constexpr int ns_tile_log2(int n) { return n <= 1 ? 0 : 1 + ns_tile_log2(n / 2); }
 template <int kNsCountBlock, int kNsCountEach>
 __global__ __launch_bounds__(kNsCountBlock) void k_ns_count(const int64_t* __restrict__ g_indptr, int64_t n_vertices,
-                                                            const int32_t* __restrict__ dst, int64_t n_dst, uint32_t k, uint32_t target,
+                                                            const int32_t* dst, int64_t n_dst, uint32_t k, uint32_t target,
                                                             int64_t* __restrict__ indptr, NsRecord* __restrict__ rec,
                                                             NsBlendThr* __restrict__ bthr /* null when c = 0 */, LayerKeys keys, double cw, double sw, Ctl* ctl,
                                                             uint32_t long_min, uint32_t* __restrict__ long_list, uint32_t* __restrict__ n_long,
-                                                            Clear clear, Publish pub) {
+                                                            Clear clear, Begin begin, Publish pub) {
+  dst = begin_in_block(begin, dst);
   clear_words(clear);
   constexpr int kWaves = kNsCountBlock / kWave;
   __shared__ uint32_t wave_long[kWaves];
@@ -1210,7 +1211,7 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
     tile_log2 = ns_tile_log2(BLOCK * EACH);                                                                                                    \
     COOP_LAUNCH(K_NS_COUNT, (k_ns_count<BLOCK, EACH>), dim3(blocks_for(n_dst, BLOCK * EACH)), dim3(BLOCK), 0, s, cx.g->indptr,                 \
                 cx.g->n_vertices, dst, n_dst, k, target, blk->indptr, rec, bthr, vp.K, cx.cw, cx.sw, cx.d_ctl, long_min, long_list, n_long,    \
-                clear, pub);                                                                                                                   \
+                clear, take_begin(cx, blocks_for(n_dst, BLOCK * EACH)), pub);                                                                  \
   } while (0)
   if (n_dst >= kNsCountWideFrom && !cx.blend) COOP_NS_COUNT(1024, 2);
   else if (n_dst >= 16384 || (n_dst > 0 && !cx.blend)) COOP_NS_COUNT(kBlock, 1);

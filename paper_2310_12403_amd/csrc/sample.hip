@@ -12,16 +12,7 @@ __global__ __launch_bounds__(kBlock) void k_copy_i32(const int32_t* __restrict__
 }
 
 // start of a sampling call: the seed list is copied to the first block's dst_ids and the control data cleared
-__global__ __launch_bounds__(kBlock) void k_begin_call(const int32_t* __restrict__ seeds, int32_t* __restrict__ seed_copy, int64_t n_seeds,
-                                                       Ctl* ctl, uint32_t* piece_count, int L) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < n_seeds) seed_copy[i] = seeds[i];
-  if (i < (kTallyLines + 1) * 16) reinterpret_cast<DeviceCtl*>(ctl)->tally.word[i] = 0;
-  if (i == 0) {
-    *ctl = Ctl{};
-    for (int l = 0; l < L; ++l) piece_count[l] = 0;
-  }
-}
+__global__ __launch_bounds__(kBlock) void k_begin_call(Begin b) { begin_call(b, (int64_t)blockIdx.x * kBlock + threadIdx.x); }
 
 // The control block travels to the host by a one-thread kernel that stores it into mapped pinned memory with a
 // ticket; the host polls the ticket.  That is a few microseconds quicker per read-back than an asynchronous copy
@@ -156,6 +147,9 @@ extern "C" int coop_tune(int knob, int64_t value) {
   }
 }
 
+// Up to how many seeds the first kernel of the call (k_segments, k_ns_count) is one block.
+static int64_t first_block_lists(const SampleCtx& cx) { return cx.sampler == COOP_RW ? 0 : cx.blend ? kWave : kBlock; }
+
 static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_seeds, const int32_t* fanouts, int L,
                          int sampler, const RwConfig* rw, uint64_t iter, uint32_t kappa, uint64_t seed, coop_alloc_fn alloc_fn,
                          void* alloc_ctx, void* stream, coop_block* blocks_out) {
@@ -195,9 +189,15 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
   cx.d_piece_count = alloc.get<uint32_t>(L, COOP_TAG_SCRATCH);
   int32_t* seed_copy = alloc.get<int32_t>(n_seeds, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
-  const int64_t n_begin = n_seeds > (kTallyLines + 1) * 16 ? n_seeds : (kTallyLines + 1) * 16;
-  COOP_LAUNCH(K_COPY_IDS, k_begin_call, dim3(blocks_for(n_begin, kBlock)), dim3(kBlock), 0, s, seeds, seed_copy, n_seeds,
-              cx.d_ctl, cx.d_piece_count, L);
+  Begin begin{seeds, seed_copy, n_seeds, cx.d_ctl, cx.d_piece_count, L};
+  static_assert(kBeginThreads >= 255, "as many threads as there can be layers");
+  const int64_t first_block = first_block_lists(cx);
+  if (n_seeds > 0 && n_seeds <= first_block) {
+    cx.begin = &begin;
+  } else {
+    const int64_t n_begin = n_seeds > kBeginThreads ? n_seeds : kBeginThreads;
+    COOP_LAUNCH(K_COPY_IDS, k_begin_call, dim3(blocks_for(n_begin, kBlock)), dim3(kBlock), 0, s, begin);
+  }
 
   LaborState labor;
   bool defer_ok = true;

@@ -10,6 +10,34 @@ namespace coop {
 
 constexpr int kMaxFuse = 4;  // LABOR-0: most layers whose keep tests are evaluated in one scan of a list
 
+// What comes before everything else: the seed list goes to the first block's dst_ids and the control data is cleared.  By a kernel of its
+// own (k_begin_call), or, where the first kernel of the call has a single block, by that one: a launch of 2 to 3 us less.
+struct Begin {
+  const int32_t* seeds;
+  int32_t* seed_copy;
+  int64_t n_seeds;
+  Ctl* ctl;
+  uint32_t* piece_count;
+  int L;
+};
+#ifdef __HIPCC__
+__device__ __forceinline__ void begin_call(const Begin& b, int64_t i) {  // thread i of n_seeds or more, at least kBeginThreads
+  if (i < b.n_seeds) b.seed_copy[i] = b.seeds[i];
+  if (i < (kTallyLines + 1) * 16) reinterpret_cast<DeviceCtl*>(b.ctl)->tally.word[i] = 0;
+  if (i < b.L) b.piece_count[i] = 0;
+  if (i == 0) *b.ctl = Ctl{};
+}
+// the whole block; returns where the destinations are to be read (the copy may not have arrived)
+__device__ __forceinline__ const int32_t* begin_in_block(const Begin& b, const int32_t* dst) {
+  if (b.ctl == nullptr) return dst;
+  for (int64_t i = threadIdx.x; i < (kTallyLines + 1) * 16; i += blockDim.x) begin_call(b, i);
+  __threadfence_block();
+  __syncthreads();
+  return b.seeds;
+}
+#endif
+constexpr int kBeginThreads = (kTallyLines + 1) * 16;  // covers the tally and, with that, L
+
 // Everything a sampler needs to know about the call.
 struct SampleCtx {
   const coop_graph* g;
@@ -27,6 +55,7 @@ struct SampleCtx {
   double cw, sw;   // cos(c pi/2), sin(c pi/2)
   bool vec4;       // the graph's indices array is 16-byte aligned
   uint8_t* tags = nullptr;      // EdgeOut::tag
+  Begin* begin = nullptr;       // still to be done, by a first kernel of one block (take_begin); null when it has been
   UniqueWork* clear = nullptr;  // words that the layer's first kernel is to set to zero, if any (take_clear)
 };
 // The words to clear go to a kernel that is launched anyway, before anything else uses them.
@@ -36,6 +65,13 @@ static inline Clear take_clear(const SampleCtx& cx) {
   const Clear c{cx.clear->clear, cx.clear->n_clear};
   cx.clear->clear = nullptr;
   return c;
+}
+// (blocks: those of the kernel about to be launched)
+static inline Begin take_begin(const SampleCtx& cx, int64_t blocks) {
+  if (cx.begin == nullptr || cx.begin->ctl == nullptr || blocks != 1) return Begin{};
+  const Begin b = *cx.begin;
+  cx.begin->ctl = nullptr;
+  return b;
 }
 #ifdef __HIPCC__
 __device__ __forceinline__ void clear_words(const Clear& c) {  // every thread of the grid

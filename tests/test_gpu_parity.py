@@ -968,6 +968,25 @@ def test_frontier_dedup_in_one_block(P, shape):
                     assert e.value.code == -3, (size, first, second)
 
 
+@pytest.mark.parametrize("defer", [1, 0, 2])
+def test_calls_that_begin_in_their_first_kernel(P, tiny, defer):
+    """Up to 256 seeds (64 with dependent variates) the first kernel of a call clears the control data and copies the seeds: numbers to
+    both sides, three layers, with the sizes read back late, at once and twice, and calls that fail in between."""
+    P.coop_tune(P.COOP_TUNE_DEFER_SIZES, defer)
+    try:
+        for size in (1, 63, 64, 65, 255, 256, 257):
+            for sampler in (R.NS, R.LABOR0):
+                compare(P, tiny, np.arange(3, 3 + size), (4, 3, 2), sampler, it=5, seed=size)
+                compare(P, tiny, np.arange(3, 3 + size), (4, 3, 2), sampler, it=5, kappa=4, seed=size)
+                for bad, code in ((list(range(size)) + [1 << 20], -2), (list(range(size)) + [0], -3)):
+                    with pytest.raises(P.CoopError) as e:
+                        P.coop_sample(tiny.graph, torch.tensor(bad, dtype=torch.int32).cuda(), (3, 3), sampler)
+                    assert e.value.code == code
+            compare_rw(P, tiny, np.arange(3, 3 + size), (4, 3), 2, 8, 0.5, seed=size)
+    finally:
+        P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
+
+
 @pytest.mark.parametrize("size", [1, 2, 3, 5, 17, 32767, 32769, 65535, 65537, 131071, 131072, 131073, 140001])
 def test_lists_dealt_to_the_last_waves(P, size):
     """The last lists of a pass go to waves that take fewer of them: numbers of destinations to both sides of those from which a wave
