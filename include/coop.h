@@ -327,7 +327,8 @@ const char* coop_strerror(int code);
                                       pass over fewer than 32768 lists covers its own layer only; 2: always fused; 0: never */
 #define COOP_TUNE_PIECE_LEN 4      /* a LABOR-0 list longer than twice this many entries is cut into pieces of about this
                                       many entries, each scanned by a wave of its own: multiple of 4 in 256..2^24
-                                      (default 4096); 0: lists are never cut */
+                                      (default 4096, and 1024 in passes over fewer than 16,384 lists); 0: lists are
+                                      never cut */
 #define COOP_TUNE_BLEND_CANDIDATES 5 /* first size (entries) of the buffer that holds the candidates of the exact blend of a
                                       LABOR-0 pass with c > 0; a pass that overflows it is redone with 8 times the size;
                                       0 (default): k / 2 entries per destination and layer plus 65536 */
@@ -335,9 +336,11 @@ const char* coop_strerror(int code);
                                       is read back together with |S^{l+1}|; 0: |E^l| is read back first and the arrays have
                                       exactly that size; 2: as 1 with a bound that falls short, so that every layer is redone
                                       (exercises the fallback) */
-#define COOP_TUNE_UNIQUE 7         /* how the frontier is deduplicated.  0 (default): lists of 262,144 entries or more (S^l and
-                                      the sampled edges together) by partition into buckets that are deduplicated in LDS,
-                                      shorter ones in LDS as well, every block picking its bucket's keys from the whole list;
+#define COOP_TUNE_UNIQUE 7         /* how the frontier is deduplicated.  0 (default): lists of 524,288 entries or more (S^l and
+                                      the sampled edges together; 262,144 where the number of edges is read back first) by
+                                      partition into buckets that are deduplicated in LDS, shorter ones in LDS as well, every
+                                      block picking its bucket's keys from the whole list, or one block taking all of up to
+                                      7,936;
                                       1: always a hash table in HBM; 2: by partition
                                       whatever the length; 3: as 2 with buckets 16 times too large, so that buckets overflow
                                       and the call falls back to the table (exercises the fallback) */
@@ -354,7 +357,7 @@ const char* coop_strerror(int code);
 #define COOP_TUNE_SPLIT_MIN 10     /* LABOR-0: lists longer than this many entries are handed to the piece waves (in pieces of
                                       about COOP_TUNE_PIECE_LEN entries, a single piece if they are shorter than that);
                                       0 (default): twice the piece length with independent variates, 2048 with dependent
-                                      ones; otherwise 64..2^30 */
+                                      ones and in passes over fewer than 16,384 lists; otherwise 64..2^30 */
 #define COOP_TUNE_STRETCH 11       /* lists (or what is left of them) longer than this many entries are read in stretches of so
                                       many: a multiple of 256 in 256..2^28; 0 (default): 2^28, as far as a 32-bit byte
                                       offset reaches.  Other values are meant for tests. */

@@ -594,8 +594,8 @@ __device__ __forceinline__ int64_t piece_start(uint32_t d, uint32_t q, uint32_t 
 //
 // Bound by instruction issue next to HBM: last layer of the products shape, 480 thousand lists, 95 us with a list at a time, an
 // ordered pass per layer over the short ones, lane masks in every group and a store to the row from every step with a kept entry,
-// 68 now; the papers100M shape without the lists above 8,192 entries, 290 M entries in three passes, 345 us and 320 (the entries
-// alone, at the rate of a copy: 237).  The next list's entries requested before this one's are looked at: 91 us and 330, for the
+// 68 now; the papers100M shape without the lists above 8,192 entries, 290 M entries in three passes, 345 us and 320, 310 with
+// the last lists dealt two to a wave (the entries alone, at the rate of a copy: 237).  The next list's entries requested before this one's are looked at: 91 us and 330, for the
 // registers.
 template <int NF>
 __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_scan_plain(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg,

@@ -74,8 +74,8 @@ __global__ __launch_bounds__(kBlock) void k_uniq_lookup(const int32_t* __restric
 // ---- a bucket's table in LDS -------------------------------------------------------------------------------------
 // Slots of 8 bytes (key << 32 | position), as in the table in HBM.  The table gives up at `most` distinct keys, with room
 // left for one claim per thread under way, so that a probe always reaches an empty slot.  (The reads are relaxed atomics:
-// volatile ones would become flat loads.  Keys and positions in separate 32-bit arrays, and two or four insertions side
-// by side per thread, were slower: 45 us for the 1,536 buckets of 5.8 M entries in the place of 36.)
+// volatile ones would become flat loads.  Keys and positions in separate 32-bit arrays, and every try of two or four insertions
+// side by side per thread, were slower: 45 us for the 1,536 buckets of 5.8 M entries in the place of 36.)
 struct BucketState { uint32_t claimed, full, dup; };
 __device__ __forceinline__ uint32_t lds_read(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 __device__ __forceinline__ uint32_t bucket_insert(unsigned long long* table, uint32_t slots, uint32_t most, uint32_t h, unsigned long long mine,
@@ -372,9 +372,8 @@ constexpr int64_t kCollectStretch = 8192;
 // tile it is; the first positions are left in the buckets' order, written in streams, and the collecting kernel reads
 // them back run by run and puts the tile into list order in LDS.  4-byte stores from the buckets to the places in the list
 // cost a partial line each (5.8 M of them 72 us, however they are spread over the XCDs).  For the 5.8 M entries of a last
-// papers100M-shaped layer: scatter 37 us (2.8 TB/s; as before, with 6 bytes per entry more to write), first positions 36
-// (84 with the stores to random places), collecting with the ranks 26 (20 for two kernels that only made flags and ranks),
-// relabelling 21 (24; 75 MB, 3.6 TB/s).
+// papers100M-shaped layer: scatter 38 us (2.8 TB/s), first positions 39 to 41 (84 with the stores to random places), collecting
+// with the ranks 26 (20 for two kernels that only made flags and ranks), relabelling 22 (75 MB, 3.4 TB/s).
 constexpr int kPartBlock = 1024;        // threads of a counting / scattering block
 constexpr int kPartMaxBlocks = 512;     // blocks of those two kernels (two per compute unit)
 constexpr int kPartPairs = 4096;        // mean pairs of a bucket
@@ -1045,7 +1044,7 @@ int unique_prepare(int64_t n_dst, int64_t m, bool deferred, UniqueWork* w, Alloc
   const int64_t n_words = (n_all + 63) / 64 - (n_dst >> 6);
   w->words = alloc.get<RankWord>(n_words, COOP_TAG_SCRATCH);
   if (alloc.failed) return COOP_E_NOMEM;
-  // by partition from kFilterMax entries on, as long as a block's counters fit LDS
+  // by partition from filter_max entries on, as long as a block's counters fit LDS
   const int64_t pairs_per_bucket = g_unique_mode == 3 ? 16 * kPartPairs : kPartPairs;
   w->n_buckets = (n_all + pairs_per_bucket - 1) / pairs_per_bucket;
   // two bucket blocks fit a CU: a last round of a few blocks is spread over the others, which grow by an eighth at most.  (One
