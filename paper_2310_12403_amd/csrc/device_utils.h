@@ -147,20 +147,27 @@ __device__ __forceinline__ bool tile_sum_done(int64_t sum, int64_t* first, Ctl* 
 // Where a destination's entries go, found by the kernel that puts them there: 1 << LOG2 neighbouring lanes for a destination,
 // blocks of BLOCK threads, destinations dealt to the blocks in order from `first` on.  OWN: from the counts alone, every block adding
 // up those in front of it (at most kScanOwn: 128 KB out of L2); 16 thousand 3 us more in this kernel in the place of two launches of
-// 5.  Else what scan_tiles left.  Either way the offsets leave in indptr.
+// 5.  Else what scan_in_tiles left, every wave adding up the tiles in front of its own, or, where those are many, what scan_tiles
+// left.  Either way the offsets leave in indptr.
+// Where element i of counts in pieces lies.  The pieces' addresses are chosen among, not looked up by the piece's number: an argument
+// indexed by a lane's number is read from memory by the lane, a wait ahead of the load that needs it.
+__device__ __forceinline__ const int32_t* chunk_at(const ChunkedI32& c, int64_t i) {
+  const int32_t* from = c.ptr[0] - c.start[0];
+#pragma unroll
+  for (int q = 1; q < 4; ++q)
+    if (q < c.n_chunks && i >= c.start[q]) from = c.ptr[q] - c.start[q];
+  return from + i;
+}
 struct CountOffsets {
   ChunkedI32 cnt;
   int64_t* indptr;
   int64_t* total_out;
+  const int64_t* sums;  // the tiles' sums, when they have not been turned into offsets (scan_in_tiles)
 };
 template <bool OWN, int BLOCK, int LOG2>
 __device__ __forceinline__ int64_t offset_of(const CountOffsets& co, int64_t w, int64_t n_dst, int32_t* count) {
   const bool live = w < n_dst, speaks = live && (threadIdx.x & ((1 << LOG2) - 1)) == 0;
-  int p = 0;
-#pragma unroll
-  for (int q = 1; q < 4; ++q)
-    if (q < co.cnt.n_chunks && w >= co.cnt.start[q]) p = q;
-  *count = live ? co.cnt.ptr[p][w - co.cnt.start[p]] : 0;
+  *count = live ? *chunk_at(co.cnt, w) : 0;
   if constexpr (OWN) {
     constexpr int kWaves = BLOCK / kWave;
     __shared__ int64_t lds[2 * kWaves];
@@ -194,8 +201,28 @@ __device__ __forceinline__ int64_t offset_of(const CountOffsets& co, int64_t w, 
     }
     return o;
   } else {
-    if (!live) return 0;
     const int64_t tile = w >> kOffsetTileLog2 << kOffsetTileLog2;
+    if (co.sums != nullptr) {
+      const int64_t in_tile = live && w != tile ? co.indptr[w] : 0;
+      // (a wave's destinations are neighbours of one tile)
+      const int in_front = __builtin_amdgcn_readfirstlane((int)(w >> kOffsetTileLog2));
+      int64_t part = 0;
+#pragma unroll
+      for (int q = 0; q < (int)kTilesAhead / kWave; ++q) {
+        const int t = q * kWave + lane_id();
+        if (t < in_front) part += co.sums[t];
+      }
+      const int64_t o = wave_sum_i64(part) + in_tile;
+      if (speaks) {
+        co.indptr[w] = o;
+        if (w == n_dst - 1) {
+          co.indptr[n_dst] = o + *count;
+          *co.total_out = o + *count;
+        }
+      }
+      return o;
+    }
+    if (!live) return 0;
     int64_t o = co.indptr[tile];
     if (w != tile) {
       o += co.indptr[w];  // (read by this group of lanes only, all of one wave, and overwritten behind that)

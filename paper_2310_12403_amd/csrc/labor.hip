@@ -999,10 +999,19 @@ __global__ __launch_bounds__(BLOCK) void k_labor_fill_staged(LayerChunks ch, Cou
   const int64_t w = first + (idx >> LOG2);
   // What is known of the destination is requested ahead of its offset and count, and so is as much of its row as nearly all hold.
   const int64_t w_in = w < n_dst ? w : n_dst - 1;
-  const int p = ch.find(w_in);
-  const int64_t local = w_in - ch.start[p];
-  const StageEntry* __restrict__ row = ch.stage[p] + (size_t)local * stage_cap;
-  const int64_t beg = ch.seg[p][local].beg;
+  const Segment* seg = ch.seg[0];
+  const StageEntry* stage = ch.stage[0];
+  int64_t start = ch.start[0];
+#pragma unroll
+  for (int q = 1; q < kMaxFuse; ++q)  // (see chunk_at)
+    if (q < ch.n_chunks && w_in >= ch.start[q]) {
+      seg = ch.seg[q];
+      stage = ch.stage[q];
+      start = ch.start[q];
+    }
+  const int64_t local = w_in - start;
+  const StageEntry* __restrict__ row = stage + (size_t)local * stage_cap;
+  const int64_t beg = seg[local].beg;
   const int sub = (int)(idx & ((1 << LOG2) - 1));
   constexpr int kPerLane = kWave >> LOG2, kAhead = 16 >> LOG2;
   StageEntry mine[kPerLane];
@@ -1231,6 +1240,10 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
   ch.n_chunks = counts.n_chunks = nc;
 
   const bool own = defer && n_dst <= kScanOwn;  // the fill finds its offsets by itself
+  // the tiles' sums lie in col_local, which nothing is written to before the dedup
+  if (defer) blk->col_local = alloc.get<int32_t>(edge_cap, COOP_TAG_OUTPUT);
+  if (alloc.failed) return COOP_E_NOMEM;
+  int64_t* sums = defer && sums_ahead(n_dst) && edge_cap >= 2 * kTilesAhead ? (int64_t*)blk->col_local : nullptr;
   bool no_enum = false, used_enum = false;
   for (;;) {
     used_enum = false;
@@ -1357,7 +1370,8 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
     }
 
     if (defer) {  // the count stays on the device; an overflow of the candidate buffer is the caller's to notice
-      if (!own) scan_tiles(counts, n_dst, blk->indptr, &cx.d_ctl->total_edges, cx.d_ctl, s);
+      if (sums != nullptr) scan_in_tiles(counts, n_dst, blk->indptr, sums, s);
+      else if (!own) scan_tiles(counts, n_dst, blk->indptr, &cx.d_ctl->total_edges, cx.d_ctl, s);
       break;
     }
     const Publish pub = begin_publish(cx.d_ctl, cx.h_ctl);  // the scan's last thread also sends the sizes to the host
@@ -1380,13 +1394,13 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
   blk->n_edges = defer ? -1 : m;
   blk->col_global = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
   if (cx.vec4 || !defer) blk->eid = alloc.get<int64_t>(m, COOP_TAG_OUTPUT);
-  blk->col_local = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
+  if (!defer) blk->col_local = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
 
   const EdgeOut edges{blk->col_global, blk->eid, cx.tags};
   if (m > 0 && n_dst > 0) {
     constexpr int64_t kSliceRows = kSliceLists << (6 - kFillLog2);
-    const CountOffsets co{counts, blk->indptr, &cx.d_ctl->total_edges};
+    const CountOffsets co{counts, blk->indptr, &cx.d_ctl->total_edges, sums};
     if (own && n_dst <= kFillFew)
       COOP_LAUNCH(K_LABOR_FILL, (k_labor_fill_staged<true, kFillOwnBlock, kFillFewLog2>), dim3(blocks_for(n_dst << kFillFewLog2, kFillOwnBlock)),
                   dim3(kFillOwnBlock), 0, s, ch, co, (int64_t)0, n_dst, cap, edges, m);

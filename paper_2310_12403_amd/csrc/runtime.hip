@@ -264,28 +264,42 @@ static void scan_impl(Load load, int64_t n, Out* out, Out* end_out, int64_t* tot
 constexpr int kTilesBlock = 1024, kTilesItems = 4;
 static_assert(kTilesBlock * kTilesItems == 1 << kOffsetTileLog2, "a block takes a tile");
 template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_scan_tiles(ChunkedI32 in, int64_t n, int64_t* __restrict__ out, int64_t* total_out, Ctl* ctl, Publish pub) {
+__global__ __launch_bounds__(BLOCK) void k_scan_tiles(ChunkedI32 in, int64_t n, int64_t* __restrict__ out, int64_t* total_out, Ctl* ctl, Publish pub,
+                                                      int64_t* __restrict__ sums /* or null: scan_in_tiles */) {
   __shared__ int64_t lds[BLOCK / kWave];
   __shared__ uint32_t s_last;
   const int64_t tile = (int64_t)blockIdx.x << kOffsetTileLog2, base = tile + (int64_t)threadIdx.x * kTilesItems;  // a thread owns 4 in a row
+  static_assert(kTilesItems == 4, "one load");
+  typedef int i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+  typedef long long i64x2 __attribute__((ext_vector_type(2)));
   int64_t x[kTilesItems], sum = 0;
+  const int32_t* from = chunk_at(in, base);
+  const bool whole = base + kTilesItems <= n;
+  if (whole && chunk_at(in, base + kTilesItems - 1) == from + kTilesItems - 1) {  // (nearly every thread)
+    const i32x4 v = *reinterpret_cast<const i32x4*>(from);
 #pragma unroll
-  for (int j = 0; j < kTilesItems; ++j) {
-    const int64_t i = base + j;
-    int p = 0;
+    for (int j = 0; j < kTilesItems; ++j) sum += x[j] = v[j];
+  } else {
 #pragma unroll
-    for (int q = 1; q < 4; ++q)
-      if (q < in.n_chunks && i >= in.start[q]) p = q;
-    x[j] = i < n ? in.ptr[p][i - in.start[p]] : 0;
-    sum += x[j];
+    for (int j = 0; j < kTilesItems; ++j) sum += x[j] = base + j < n ? *chunk_at(in, base + j) : 0;
   }
   int64_t tot;
   int64_t run = block_incl_scan_i64<BLOCK / kWave>(sum, &tot, lds) - sum;
+  if (whole && (base != tile || gridDim.x == 1)) {
+    i64x2* to = reinterpret_cast<i64x2*>(out + base);
+    to[0] = i64x2{run, run + x[0]};
+    to[1] = i64x2{run + x[0] + x[1], run + x[0] + x[1] + x[2]};
+  } else {
 #pragma unroll
-  for (int j = 0; j < kTilesItems; ++j) {
-    const int64_t i = base + j;
-    if (i < n && (i != tile || gridDim.x == 1)) out[i] = run;
-    run += x[j];
+    for (int j = 0; j < kTilesItems; ++j) {
+      const int64_t i = base + j;
+      if (i < n && (i != tile || gridDim.x == 1)) out[i] = run;
+      run += x[j];
+    }
+  }
+  if (sums != nullptr) {
+    if (threadIdx.x == 0) sums[blockIdx.x] = tot;
+    return;
   }
   if (gridDim.x == 1) {
     if (threadIdx.x == 0) {
@@ -317,10 +331,15 @@ void scan_tiles(const ChunkedI32& in, int64_t n, int64_t* out, int64_t* total_ou
   if (n <= 0)  // out[0] = 0
     COOP_LAUNCH(K_FILL, k_store_total, dim3(1), dim3(1), 0, s, out, total_out, p);
   else if (n <= kBlock * kTilesItems)
-    COOP_LAUNCH(K_SCAN_LOCAL, k_scan_tiles<kBlock>, dim3(1), dim3(kBlock), 0, s, in, n, out, total_out, ctl, p);
+    COOP_LAUNCH(K_SCAN_LOCAL, k_scan_tiles<kBlock>, dim3(1), dim3(kBlock), 0, s, in, n, out, total_out, ctl, p, (int64_t*)nullptr);
   else
     COOP_LAUNCH(K_SCAN_LOCAL, k_scan_tiles<kTilesBlock>, dim3((unsigned)((n + (1 << kOffsetTileLog2) - 1) >> kOffsetTileLog2)), dim3(kTilesBlock), 0, s, in, n, out,
-                total_out, ctl, p);
+                total_out, ctl, p, (int64_t*)nullptr);
+}
+
+void scan_in_tiles(const ChunkedI32& in, int64_t n, int64_t* out, int64_t* sums, hipStream_t s) {
+  COOP_LAUNCH(K_SCAN_LOCAL, k_scan_tiles<kTilesBlock>, dim3((unsigned)((n + (1 << kOffsetTileLog2) - 1) >> kOffsetTileLog2)), dim3(kTilesBlock), 0, s, in, n, out,
+              (int64_t*)nullptr, (Ctl*)nullptr, Publish{}, sums);
 }
 
 void scan_u32_to_u32(const uint32_t* in, int64_t n, uint32_t* out, void* tmp, hipStream_t s) {

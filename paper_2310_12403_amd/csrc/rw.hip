@@ -376,8 +376,13 @@ int rw_layer(const SampleCtx& cx, const RwConfig& rw, int l, const int32_t* dst,
   counts.ptr[0] = cnt;
   counts.n_chunks = 1;
   const bool own = defer && n_dst <= kScanOwn;  // the fill finds its offsets by itself
+  // the tiles' sums lie in col_local, which nothing is written to before the dedup
+  if (defer) blk->col_local = alloc.get<int32_t>(edge_cap, COOP_TAG_OUTPUT);
+  if (alloc.failed) return COOP_E_NOMEM;
+  int64_t* sums = defer && rp.k_eff <= kRwFillNarrow && sums_ahead(n_dst) && edge_cap >= 2 * kTilesAhead ? (int64_t*)blk->col_local : nullptr;
   if (defer) {
-    if (!own) scan_tiles(counts, n_dst, blk->indptr, &cx.d_ctl->total_edges, cx.d_ctl, s);  // the count stays on the device
+    if (sums != nullptr) scan_in_tiles(counts, n_dst, blk->indptr, sums, s);
+    else if (!own) scan_tiles(counts, n_dst, blk->indptr, &cx.d_ctl->total_edges, cx.d_ctl, s);  // the count stays on the device
   } else {
     const Publish pub = begin_publish(cx.d_ctl, cx.h_ctl);  // the scan's last thread also sends the sizes to the host
     scan_tiles(counts, n_dst, blk->indptr, &cx.d_ctl->total_edges, cx.d_ctl, s, &pub);  // m_l = indptr[n_dst]
@@ -388,11 +393,11 @@ int rw_layer(const SampleCtx& cx, const RwConfig& rw, int l, const int32_t* dst,
   blk->n_edges = defer ? -1 : m;
   blk->col_global = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
   blk->eid = alloc.get<int64_t>(m, COOP_TAG_OUTPUT);
-  blk->col_local = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
+  if (!defer) blk->col_local = alloc.get<int32_t>(m, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
   if (m > 0 && n_dst > 0) {
     const EdgeOut edges{blk->col_global, blk->eid, cx.tags};
-    const CountOffsets co{counts, blk->indptr, &cx.d_ctl->total_edges};
+    const CountOffsets co{counts, blk->indptr, &cx.d_ctl->total_edges, sums};
     constexpr int64_t kSliceRows = kSliceLists << (6 - kRwFillLog2);  // (a launch has fewer than 2^32 threads)
     if (own)
       COOP_LAUNCH(K_RW_FILL, (k_rw_fill<true, 1024>), dim3(blocks_for(n_dst << kRwFillLog2, 1024)), dim3(1024), 0, s, rows, co, rp.k_eff, (int64_t)0, n_dst,

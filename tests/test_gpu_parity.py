@@ -1010,6 +1010,20 @@ def test_lists_dealt_to_the_last_waves(P, size):
                 P.coop_tune(P.COOP_TUNE_LISTS_PER_WAVE, 0)
 
 
+@pytest.mark.parametrize("size", [36864, 36865, 1048575, 1048576, 1048577])
+def test_offsets_from_sums_of_tiles(P, size):
+    """Offsets that the filling kernel's waves find by adding up the sums of the tiles in front of theirs, up to 256 tiles of 4,096
+    destinations, and those that the scan's last block leaves for more; the second layer's counts lie in two pieces that meet anywhere."""
+    n = 1060000
+    rng = np.random.default_rng(24)
+    deg = rng.integers(0, 4, n)
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]).astype(np.int64))
+    g = G(P, indptr, torch.from_numpy(rng.integers(0, n, int(deg.sum())).astype(np.int32)))
+    seeds = rng.permutation(n)[:size]
+    compare(P, g, seeds, (2,) if size > 40000 else (2, 2), R.LABOR0, seed=size)
+    compare_rw(P, g, seeds, (2,), 1, 3, 0.5, seed=size)
+
+
 @pytest.mark.parametrize("mode", [1, 0])
 def test_offsets_around_the_edges_of_tiles(P, mode):
     """Offsets that the filling kernel finds by itself (up to 32,768 destinations) and those that a scan leaves tile by tile
