@@ -209,6 +209,7 @@ struct UniqueWork {
   RankWord* words = nullptr;
   uint32_t* block_prefix = nullptr;  // ... and in the stretches in front
   int64_t n_buckets = 0;
+  uint32_t n_totals = 0;             // ... of so many stretches the totals are there in its place, for the relabelling to scan
   uint32_t part_blocks = 0;          // blocks of the partition whose stretches those are (0: stretches of fixed length)
   int path = 0;
   bool tagged = false;

@@ -357,8 +357,9 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
 // of scattered requests), and those of the stretches in front (block_prefix).
 struct RankView {
   const RankWord* word;   // of the positions from the multiple of 64 at or below n_dst on
-  const uint32_t* block_prefix;
+  const uint32_t* block_prefix;  // ... or, when n_totals is not 0, the stretches' own totals, which the reader scans
   uint32_t n_blocks;  // when not 0: the stretches are those of the partition's blocks (part_stretch_len of the whole list)
+  uint32_t n_totals;
 };
 constexpr int64_t kCollectStretch = 8192;
 
@@ -373,7 +374,7 @@ constexpr int64_t kCollectStretch = 8192;
 // them back run by run and puts the tile into list order in LDS.  4-byte stores from the buckets to the places in the list
 // cost a partial line each (5.8 M of them 72 us, however they are spread over the XCDs).  For the 5.8 M entries of a last
 // papers100M-shaped layer: scatter 38 us (2.8 TB/s), first positions 39 to 41 (84 with the stores to random places), collecting
-// with the ranks 26 (20 for two kernels that only made flags and ranks), relabelling 22 (75 MB, 3.4 TB/s).
+// with the ranks 24 (20 for two kernels that only made flags and ranks), relabelling 23 (75 MB, 3.3 TB/s).
 constexpr int kPartBlock = 1024;        // threads of a counting / scattering block
 constexpr int kPartMaxBlocks = 512;     // blocks of those two kernels (two per compute unit)
 constexpr int kPartPairs = 4096;        // mean pairs of a bucket
@@ -695,6 +696,10 @@ __global__ __launch_bounds__(kPartBlock, 8) void k_uniq_collect(uint32_t* first,
       run += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
     }
   }
+  if (block_prefix == nullptr) {  // the relabelling scans the totals
+    if (threadIdx.x == 0) block_total[blockIdx.x] = run;
+    return;
+  }
   if (threadIdx.x == 0) {
     // the exchange has been performed when its result is here; the block counts itself behind it
     const uint32_t old = atomicExch(&block_total[blockIdx.x], run);
@@ -744,8 +749,18 @@ __global__ __launch_bounds__(kBlock) void k_uniq_relabel(const int32_t* __restri
   const int64_t stretch = rank.n_blocks ? part_stretch_len(n_dst + m, rank.n_blocks) : kCollectStretch;
   const uint32_t d = (uint32_t)(stretch >> 10), magic = d <= 1 ? 0u : 0xFFFFFFFFu / d + 1u;
   __shared__ uint32_t prefix[kPartMaxBlocks];
-  if (rank.n_blocks) {
-    for (uint32_t b = threadIdx.x; b < rank.n_blocks; b += kBlock) prefix[b] = rank.block_prefix[b];
+  if (rank.n_totals) {
+    __shared__ uint32_t wave_total[kWavesPerBlock];
+    static_assert(kPartMaxBlocks == 2 * kBlock, "two totals per thread");
+    const uint32_t b = 2 * threadIdx.x;
+    const uint32_t t0 = b < rank.n_totals ? rank.block_prefix[b] : 0u, t1 = b + 1 < rank.n_totals ? rank.block_prefix[b + 1] : 0u;
+    uint32_t upto = wave_incl_scan(t0 + t1);
+    if (lane_id() == kWave - 1) wave_total[wave_in_block()] = upto;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kWavesPerBlock - 1; ++q) upto += q < wave_in_block() ? wave_total[q] : 0u;
+    prefix[b] = upto - t0 - t1;
+    prefix[b + 1] = upto - t1;
     __syncthreads();
   }
   const int64_t e0 = (int64_t)blockIdx.x * (kBlock * kRelabelUnroll) + threadIdx.x;
@@ -774,7 +789,7 @@ __global__ __launch_bounds__(kBlock) void k_uniq_relabel(const int32_t* __restri
     int64_t local = f[u];
     if (local >= n_dst) {
       const uint32_t q = f[u] >> 10, block = d <= 1 ? q : __umulhi(q, magic);
-      const uint32_t in_front = rank.n_blocks ? prefix[block] : rank.block_prefix[block];
+      const uint32_t in_front = rank.n_totals ? prefix[block] : rank.block_prefix[block];
       local = n_dst + in_front + w[u].before + __popcll(w[u].bits & ((1ull << (f[u] & 63)) - 1ull));
       if ((int64_t)f[u] == n_dst + e) src[local] = col[e];
     }
@@ -958,6 +973,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
   int shift = 0;
   TileNotes notes{};
   w->part_blocks = 0;
+  w->n_totals = 0;
   if (path == kInOneBlock) {  // (the relabelling too; spare becomes src_ids)
     if (n_all <= 4 * kSmallBlock)
       COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_small<4>, dim3(1), dim3(kSmallBlock), 0, s, dst, n_dst, col_global, m, m_dev, spare, col_local, d_ctl, w->pub);
@@ -1024,15 +1040,21 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
   if (m > 0 && !(path == kByFilter && w->bits)) {
     uint32_t* totals = alloc.get<uint32_t>(2 * (int64_t)collect_blocks, COOP_TAG_SCRATCH);
     if (alloc.failed) return COOP_E_NOMEM;
-    w->block_prefix = totals + collect_blocks;
+    // Up to kPartMaxBlocks stretches every block of the relabelling scans their totals for itself, in the place of the block that finishes
+    // last here, behind two atomics per block (120 thousand, 1 and 2.4 M entries: this kernel 6.1, 11.3 and 23.0 us -> 4.5, 9.3 and 20.6,
+    // the relabelling 18.1 -> 19.3 for the longest).  Only the fallback can have more.
+    static_assert(kFilterTaggedMax <= kCollectStretch * kPartMaxBlocks, "a short list has no more stretches than that");
+    w->n_totals = path != kByTable ? (uint32_t)collect_blocks : 0u;
+    uint32_t* const prefix = path != kByTable ? nullptr : totals + collect_blocks;
+    w->block_prefix = prefix ? prefix : totals;
     // (the table in HBM does not count its keys: there the ranks bring the number of new vertices, and the sizes leave with them)
     const Publish pub = path == kByTable ? w->pub : Publish{};
     if (by_place)
       COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<true>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, shift, notes, m, m_dev, n_dst,
-                  w->words, totals, w->block_prefix, d_ctl, pub);
+                  w->words, totals, prefix, d_ctl, pub);
     else
       COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<false>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, shift, notes, m, m_dev, n_dst,
-                  w->words, totals, w->block_prefix, d_ctl, pub);
+                  w->words, totals, prefix, d_ctl, pub);
   } else if (path == kByTable && launch_publish(w->pub, s) != COOP_OK) {
     return COOP_E_HIP;
   }
@@ -1093,7 +1115,7 @@ int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_gl
 int unique_back(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, const UniqueWork& w,
                 int32_t* col_local, int32_t* src, hipStream_t s) {
   const int64_t n_threads = m > n_dst ? m : n_dst;
-  const RankView rank{w.words, w.block_prefix, w.part_blocks};
+  const RankView rank{w.words, w.block_prefix, w.part_blocks, w.n_totals};
   if (w.path == kInOneBlock) return COOP_OK;
   if (n_threads > 0 && w.path == kByFilter && w.bits)
     COOP_LAUNCH(K_UNIQ_RELABEL, k_uniq_relabel_short, dim3((unsigned)((n_threads + kShortBlock * kShortEach - 1) / (kShortBlock * kShortEach))),
