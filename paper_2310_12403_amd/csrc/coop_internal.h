@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "coop.h"
+#include "pieces.h"
 
 namespace coop {
 
@@ -258,11 +259,6 @@ struct coop_graph {
     for (; k < 32; ++k) n += census[k];
     return n;
   }
-  // every list has fewer entries than this (when the graph was looked at)
-  int64_t longest_list_below() const {
-    int k = 31;
-    while (k > 0 && census[k] == 0) --k;
-    return (int64_t)2 << k;
-  }
+  coop::Degrees degrees() const { return coop::Degrees{n_edges, have_census ? census : nullptr}; }
 };
 constexpr int64_t kLongListDegree = 8192;  // default of COOP_TUNE_ENUM_DEGREE

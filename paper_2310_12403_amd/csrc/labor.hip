@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
                                                      uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3, Segment* __restrict__ seg,
                                                      uint32_t* __restrict__ thr, PreThr* __restrict__ pthr, float* __restrict__ lim2,
                                                      double cw, double sw, Ctl* ctl,
-                                                     uint32_t piece_len, uint32_t split_min, Piece* __restrict__ pieces, uint32_t piece_cap,
+                                                     PieceCut cut, Piece* __restrict__ pieces, uint32_t piece_cap,
                                                      uint32_t* __restrict__ piece_count, ScanOut out, uint32_t enum_degree,
                                                      uint32_t* __restrict__ long_bits, LongSlot* __restrict__ long_tab, uint32_t long_mask,
                                                      Clear clear, Begin begin, uint32_t* __restrict__ cand_count /* kCandSub, set to zero; null when c = 0 */) {
@@ -430,15 +430,14 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
     atomicOr(&long_bits[b >> 5], 1u << (b & 31u));
     sampled = false;  // no pieces
   }
-  if (piece_len == 0) {  // wave-uniform
+  if (cut.len == 0) {  // wave-uniform
     if (live) seg[i] = g;
     return;
   }
-  // A long list is cut into pieces of about piece_len entries (equal lengths, multiples of 4), each scanned by a wave
+  // A long list is cut into pieces (PieceCut: equal lengths, multiples of 4), each scanned by a wave
   // of its own: the waves of the scan then all have about the same amount of work whatever the degree distribution.
   // The block reserves queue slots for all its long lists with one atomic; each wave then writes its pieces together.
-  uint32_t np = sampled && g.d > split_min ? (g.d + piece_len - 1) / piece_len : 0u;
-  if (np > (1u << 20)) np = 0;  // keeps the block's sum below 2^30 (only lists of 2^28 entries and more, at the smallest piece length)
+  const uint32_t np = sampled && g.d > cut.split_min ? cut.pieces(g.d) : 0u;
   const uint32_t incl = wave_incl_scan(np);
   const uint32_t lane = (uint32_t)lane_id();
   const int wv = uniform_wave_in_block();
@@ -454,8 +453,8 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
   const uint32_t total = s_total;
   if (total != 0) {  // block-uniform
     const uint32_t block_base = s_base;
-    // room always suffices for distinct destinations (the queue holds a piece for every piece_len edges of the graph);
-    // a seed list with duplicates may run out: its lists then stay whole and what was reserved becomes empty slots
+    // room suffices for distinct destinations (cut_pieces; short of that only on unaligned indices, whose queue lies in an array of the
+    // layer); a seed list with duplicates may run out: its lists then stay whole and what was reserved becomes empty slots
     const bool fits = block_base <= piece_cap && total <= piece_cap - block_base;
     const uint32_t base = block_base + s_wave_at[wv];
     uint64_t todo = ballot64(np != 0);
@@ -469,7 +468,7 @@ __global__ __launch_bounds__(kSegBlock) void k_segments(const int64_t* __restric
         if (at + q < piece_cap) pieces[at + q] = fits ? Piece{list, q} : Piece{kNoPiece, 0u};
     }
     if (fits && np != 0) {
-      g.split = 1;
+      g.split = cut.each(g.d);
 #pragma unroll
       for (int f = 0; f < kMaxFuse; ++f)
         if (f < nf) out.cnt[f][i] = 0;  // the pieces add their counts
@@ -574,17 +573,6 @@ __device__ __forceinline__ void labor_collect(ListReader<>& L, uint32_t j0, cons
   }
 }
 
-// Where piece q of a list of d entries starts, and its length.  (Below 0: nowhere.  Rounding the piece length up can leave the last
-// slots of a very long list empty.)
-__device__ __forceinline__ int64_t piece_start(uint32_t d, uint32_t q, uint32_t piece_len, uint32_t* len) {
-  const uint32_t np = (d + piece_len - 1) / piece_len;  // as in k_segments
-  const uint32_t plen = ((d + np - 1) / np + 3u) & ~3u;
-  const uint64_t j0 = (uint64_t)q * plen;
-  if (j0 >= d) return -1;
-  *len = d - (uint32_t)j0 < plen ? d - (uint32_t)j0 : plen;
-  return (int64_t)j0;
-}
-
 // The scan pass with independent variates.  As k_ns_fill, which says what its parts are for: a wave takes `each` neighbouring
 // destinations (a power of two, at most 64), lists of up to twice the 64 / each lanes that a destination has are looked at
 // together, the others one after the other through the whole wave, the next one's entries requested before this one's kept
@@ -602,7 +590,7 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
                                                                const uint32_t* __restrict__ thr_all, int64_t n, Dealing deal, FusedKeys keys,
                                                                uint32_t stage_cap, ScanOut out, Ctl* ctl, int piece_blocks,
                                                                const Piece* __restrict__ pieces, const uint32_t* __restrict__ piece_count,
-                                                               uint32_t piece_cap, uint32_t piece_len, uint32_t stretch) {
+                                                               uint32_t piece_cap, uint32_t stretch) {
   __shared__ KeptSlots slots[NF];
   const uint32_t lane = (uint32_t)lane_id();
   auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
@@ -624,7 +612,7 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 8 : NF == 2 ? 7 : 6) void k_labor_
       const Segment g = seg[list];
       const int64_t beg = of64(g.beg, 0);
       uint32_t len;
-      const int64_t j0 = piece_start(of(g.d, 0), q, piece_len, &len);
+      const int64_t j0 = piece_start(of(g.d, 0), of(g.split, 0), q, &len);
       if (j0 < 0) continue;
       uint32_t thr[NF], kept[NF];
 #pragma unroll
@@ -801,7 +789,7 @@ __global__ __launch_bounds__(kWave, NF == 1 ? 7 : NF == 2 ? 6 : NF == 3 ? 5 : 4)
 k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restrict__ seg, const uint32_t* __restrict__ thr_all,
                    const PreThr* __restrict__ pthr_all, const float* __restrict__ lim2_all, int64_t n, Dealing deal, FusedKeys keys, uint32_t stage_cap,
                    ScanOut out, Ctl* ctl, int piece_blocks, const Piece* __restrict__ pieces, const uint32_t* __restrict__ piece_count,
-                   uint32_t piece_cap, uint32_t piece_len, CandOut cand, uint32_t stretch) {
+                   uint32_t piece_cap, CandOut cand, uint32_t stretch) {
   __shared__ BlendQueue<false> queue[NF];
   const uint32_t lane = (uint32_t)lane_id();
   auto of = [](uint32_t x, int q) { return (uint32_t)__builtin_amdgcn_readlane((int)x, q); };
@@ -823,7 +811,7 @@ k_labor_scan_blend(const int32_t* __restrict__ g_indices, const Segment* __restr
       const Segment g = seg[list];
       const int64_t beg = of64(g.beg, 0);
       uint32_t len;
-      const int64_t j0 = piece_start(of(g.d, 0), q, piece_len, &len);
+      const int64_t j0 = piece_start(of(g.d, 0), of(g.split, 0), q, &len);
       if (j0 < 0) continue;
       S.sink.first = list;  // (every lane has this list's thresholds: slot 0)
       uint32_t a1[NF], a2[NF], b2[NF];
@@ -1079,13 +1067,13 @@ __global__ __launch_bounds__(kBlock) void k_labor_fill_overflow(const int32_t* _
 
 static void launch_scan_blend(int nf, unsigned blocks, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, const PreThr* pthr,
                               const float* lim2, int64_t n, const Dealing& deal, const FusedKeys& keys, uint32_t cap, const ScanOut& out, Ctl* ctl,
-                              int piece_blocks, const Piece* pieces, const uint32_t* piece_count, uint32_t piece_cap, uint32_t piece_len,
+                              int piece_blocks, const Piece* pieces, const uint32_t* piece_count, uint32_t piece_cap,
                               const CandOut& cand /* no buffer: the exact blend in the scan */) {
 #define COOP_SCAN_BLEND(NF)                                                                                                                  \
   if (cand.buf != nullptr) { COOP_SCAN_BLEND_AS(NF, false); } else { COOP_SCAN_BLEND_AS(NF, true); }
 #define COOP_SCAN_BLEND_AS(NF, EXACT)                                                                                                        \
   COOP_LAUNCH(K_LABOR_COUNT, (k_labor_scan_blend<NF, EXACT>), dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, pthr, lim2, n, deal, keys, cap, out, ctl, \
-              piece_blocks, pieces, piece_count, piece_cap, piece_len, cand, (uint32_t)g_stretch)
+              piece_blocks, pieces, piece_count, piece_cap, cand, (uint32_t)g_stretch)
   switch (nf) {
     case 1: COOP_SCAN_BLEND(1); break;
     case 2: COOP_SCAN_BLEND(2); break;
@@ -1097,10 +1085,10 @@ static void launch_scan_blend(int nf, unsigned blocks, hipStream_t s, const int3
 }
 static void launch_scan_plain(int nf, unsigned blocks, hipStream_t s, const int32_t* indices, const Segment* seg, const uint32_t* thr, int64_t n, const Dealing& deal,
                               const FusedKeys& keys, uint32_t cap, const ScanOut& out, Ctl* ctl, int piece_blocks, const Piece* pieces,
-                              const uint32_t* piece_count, uint32_t piece_cap, uint32_t piece_len) {
+                              const uint32_t* piece_count, uint32_t piece_cap) {
 #define COOP_SCAN_PLAIN(NF)                                                                                                           \
   COOP_LAUNCH(K_LABOR_COUNT, k_labor_scan_plain<NF>, dim3(blocks), dim3(kWave), 0, s, indices, seg, thr, n, deal, keys, cap, out, ctl, \
-              piece_blocks, pieces, piece_count, piece_cap, piece_len, (uint32_t)g_stretch)
+              piece_blocks, pieces, piece_count, piece_cap, (uint32_t)g_stretch)
   switch (nf) {
     case 1: COOP_SCAN_PLAIN(1); break;
     case 2: COOP_SCAN_PLAIN(2); break;
@@ -1110,8 +1098,6 @@ static void launch_scan_plain(int nf, unsigned blocks, hipStream_t s, const int3
 #undef COOP_SCAN_PLAIN
 }
 
-constexpr int64_t kFewLists = 16384;
-constexpr uint32_t kFewPieceLen = 1024;
 // One round of resident waves; fewer where there cannot be as many pieces.  (Starting 8,192 that find nothing costs a pass over a few
 // hundred lists 2 us.)
 constexpr int64_t kPieceWaves = 8192;
@@ -1171,37 +1157,19 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
     layer_keys(cx.seed, COOP_LABOR0, l + f, cx.group + 1, keys.K[f].Kb);
     ks[f] = (uint32_t)cx.fanouts[l + f];
   }
-  // long lists are cut into pieces (k_segments queues them); room for every piece the graph's edges could make
-  uint32_t piece_len = (uint32_t)g_piece_len;
-  // Lists longer than split_min go to the piece waves, which come first in the grid.  With independent variates that is
-  // for the lists worth cutting (twice the piece length).  The blended scan costs three times as much per entry, and a
-  // wave that meets a few lists of several thousand entries late in the kernel keeps it waiting: there every list above
-  // 2,048 entries goes first, whole if it is shorter than two pieces (papers100M-shaped, kappa 16: scan 1.44 -> 1.32 ms;
-  // no difference with independent variates).
-  uint32_t split_min = g_split_min != 0 ? (uint32_t)g_split_min : (cx.blend && piece_len >= 2048u ? 2048u : 2u * piece_len);
-  const int64_t room_pieces = piece_len != 0 ? cx.g->n_edges / piece_len : 0, room_lists = piece_len != 0 ? cx.g->n_edges / (int64_t)split_min + 1 : 0;
-  // A pass that does not fill the chip with its lists ends when its longest list does: those are cut into pieces that one step of a
-  // wave's requests covers.  (64 seeds, three layers 147 -> 142 us, 1,024 seeds 117 -> 114, both with pieces of 1,024; of 512 144 and
-  // 115.  A queue with no room for that many pieces leaves lists whole.)
-  if (n_new < kFewLists && piece_len == kPieceLen && g_split_min == 0) {
-    piece_len = kFewPieceLen;
-    split_min = 2 * kFewPieceLen;
-  }
-  // (a graph whose degrees were looked at when it was registered and that has no such list: nothing is queued)
-  const int64_t most_long = cx.g->lists_longer_than(split_min);
-  if (most_long == 0) piece_len = 0;
   // A call on unaligned indices takes memory for neither the queue nor the candidates of the exact blend (programs sized their
   // arenas for such calls when every list was read by one wave, an entry at a time): its queue lies in an array of the layer that is
   // written after the scan, with as many pieces as that holds, and the scan evaluates the exact blend itself.  (A list of 2 million
   // entries among 20 thousand short ones: 82 us with pieces, 1.9 ms without.)
-  uint32_t piece_cap = 0;
   Piece* pieces = nullptr;
   if (!cx.vec4 && defer) blk->eid = alloc.get<int64_t>(edge_cap, COOP_TAG_OUTPUT);
   if (alloc.failed) return COOP_E_NOMEM;
-  if (piece_len != 0 && n_new > 0) {
-    const int64_t most = cx.vec4 ? (int64_t)1 << 30 : defer ? edge_cap : n_dst + 1;
-    const int64_t cap64 = room_pieces + (n_new < room_lists ? n_new : room_lists) + 1;
-    piece_cap = (uint32_t)(cap64 < most ? cap64 : most);
+  // long lists are cut into pieces, which k_segments queues
+  int64_t piece_room = 0;
+  const Degrees degrees = cx.g->degrees();
+  const PieceCut cut = cut_pieces(n_new, degrees, cx.blend, g_piece_len, g_split_min, cx.vec4 ? (int64_t)1 << 30 : defer ? edge_cap : n_dst + 1, &piece_room);
+  const uint32_t piece_cap = (uint32_t)piece_room;
+  if (cut.len != 0) {
     static_assert(sizeof(Piece) == sizeof(int64_t), "a piece takes the place of an offset or a position");
     pieces = cx.vec4 ? alloc.get<Piece>(piece_cap, COOP_TAG_SCRATCH) : (Piece*)(defer ? blk->eid : blk->indptr);
     if (alloc.failed) return COOP_E_NOMEM;
@@ -1317,7 +1285,7 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
 #define COOP_SEGMENTS(BLOCK, EACH, SHARED)                                                                                            \
   COOP_LAUNCH(K_SEGMENTS, (k_segments<BLOCK, SHARED>), dim3(blocks_for(n_new, EACH)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices,  \
               dst + ps.start, n_new, ps.nf, ks[0], ks[1], ks[2], ks[3], ps.seg, ps.thr, pthr, lim2, cx.cw, cx.sw,                        \
-              cx.d_ctl, piece_len, split_min, pieces, piece_cap, cx.d_piece_count + l, out, enum_degree,    \
+              cx.d_ctl, cut, pieces, piece_cap, cx.d_piece_count + l, out, enum_degree,    \
               long_bits, long_tab, long_mask, clear, take_begin(cx, blocks_for(n_new, EACH)), cand_count)
       if (n_new >= kSegWideFrom) COOP_SEGMENTS(1024, 1024, false);
       else if (n_new >= kSegSharedBelow || !cx.blend) COOP_SEGMENTS(256, 256, false);
@@ -1339,8 +1307,8 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
       }
       // the piece waves come first in the grid: one round of resident blocks, fewer if there cannot be that many pieces
       int64_t piece_waves = (int64_t)piece_cap < kPieceWaves ? (int64_t)piece_cap : kPieceWaves;
-      if (piece_len != 0 && cx.g->have_census) {  // (the longest list in pieces, for every list that can be long)
-        const int64_t most = (n_new < most_long ? n_new : most_long) * (int64_t)((cx.g->longest_list_below() - 1) / piece_len + 1);
+      if (cut.len != 0) {
+        const int64_t most = degrees.pieces(n_new, cut.split_min, cut.len);
         if (most < piece_waves) piece_waves = most;
       }
       const uint32_t* pcount = cx.d_piece_count + l;
@@ -1353,10 +1321,10 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
       const unsigned blocks = deal.blocks + (unsigned)piece_waves;
       if (cx.blend)
         launch_scan_blend(ps.nf, blocks, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, deal, keys, cap, out, cx.d_ctl, (int)piece_waves,
-                          pieces, pcount, piece_cap, piece_len, cand);
+                          pieces, pcount, piece_cap, cand);
       else
         launch_scan_plain(ps.nf, blocks, s, cx.g->indices, ps.seg, ps.thr, n_new, deal, keys, cap, out, cx.d_ctl, (int)piece_waves, pieces,
-                          pcount, piece_cap, piece_len);
+                          pcount, piece_cap);
       if (queued) {  // stage 3: the exact blend for the candidates that the scan appended
         // (Blocks for an eighth of the kept edges, where a few percent are undecided, at most 16 a sub-buffer; the threads stride, so more
         // candidates only take longer.  With as many blocks as the buffers have room for, 4,096, a launch over 113 thousand destinations

@@ -91,7 +91,7 @@ __device__ __forceinline__ void put_edge(const EdgeOut& out, int64_t o, uint32_t
 #endif
 
 // One destination's neighbour list as the scan kernels see it.
-struct Segment { int64_t beg; uint32_t d; uint32_t split; };  // split != 0: scanned piecewise by several waves
+struct Segment { int64_t beg; uint32_t d; uint32_t split; };  // split != 0: scanned by several waves, in pieces of that length
 
 // The q-th stretch of a long list, scanned by one wave (LABOR-0).  list == kNoPiece: an empty queue slot.
 struct Piece { uint32_t list, q; };
@@ -145,7 +145,6 @@ extern int g_stage_cap_override;
 extern int g_lists_per_wave;
 extern int g_fuse_layers;
 extern int g_piece_len;
-constexpr int kPieceLen = 4096;  // its default
 extern int g_split_min;
 extern int64_t g_blend_candidates;
 extern int g_defer_sizes;

@@ -557,6 +557,28 @@ def test_labor_long_lists_cut_into_pieces(P, tiny, medium, piece_len):
         P.coop_tune(P.COOP_TUNE_STAGE_CAP, 0)
 
 
+@pytest.mark.parametrize("hubs,each,size", [(1, 300000, 20), (20, 30000, 700), (300, 2500, 2000), (2, 100000, 16384)])
+@pytest.mark.parametrize("census", [True, False])
+def test_long_lists_that_are_most_of_a_graph(P, hubs, each, size, census):
+    """Small passes over graphs whose long lists are nearly all there is, with the default knobs: what the queue of pieces has room for
+    decides how finely they are cut.  Degrees known and unknown, aligned and unaligned, independent and dependent variates."""
+    n = 20000
+    rng = np.random.default_rng(hubs)
+    deg = rng.integers(0, 5, n)
+    deg[:hubs] = each
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]).astype(np.int64))
+    indices = torch.from_numpy(rng.integers(0, n, int(deg.sum()) + 1).astype(np.int32))
+    seeds = np.concatenate([np.arange(hubs), hubs + rng.permutation(n - hubs)[:size - hubs]])
+    for at in (0, 1):
+        g = G(P, indptr, indices[:-1], flags=P.COOP_VALIDATE if census else 0)
+        if at == 1:
+            g.keep = indices.cuda()
+            g.indices_h = indices[1:].numpy()
+            g.graph = P.coop_graph_load(g.indptr_d, g.keep[1:], P.COOP_VALIDATE if census else 0)
+        compare(P, g, seeds, (10,), R.LABOR0, it=1, seed=31)
+        compare(P, g, seeds, (10, 5), R.LABOR0, it=3, kappa=4, seed=31)
+
+
 @pytest.mark.parametrize("split_min,piece_len", [(64, 4096), (200, 512), (1000, 256)])
 def test_labor_lists_handed_to_the_piece_waves_whole(P, tiny, medium, split_min, piece_len):
     """Lists longer than COOP_TUNE_SPLIT_MIN go to the waves that come first in the scan's grid: as a single piece when they
