@@ -76,6 +76,16 @@ struct Ctl {
   int32_t uniq_overflow; // dedup by partition: a bucket held more distinct vertices than its table (redone with the table in HBM)
   int32_t pad[2];
 };
+#ifdef __HIPCC__
+// The edges that a layer's dedup is about (see unique_front_launch).  None in a layer of which a staging row overflowed: it is
+// sampled again whatever comes out, and some of its edges, and the tags beside them, were never written.  (What stood there before
+// could send a bucket over the whole list, or the call to the table in HBM: fanout 64, 3,000 lists of up to 5,000 entries 375 -> 824 us.)
+__device__ __forceinline__ int64_t edges_there(const Ctl* sizes, int64_t m) {
+  if (sizes == nullptr) return m;
+  const int64_t there = sizes->n_overflow != 0 ? 0 : sizes->total_edges;
+  return there < m ? there : m;
+}
+#endif
 
 // "Who is the last block?"  Returning atomics on one address are taken one after the other, some 20 ns each, so a kernel of
 // a thousand blocks that all count themselves in one word takes 20 us for that alone.  Blocks therefore count themselves
@@ -198,9 +208,9 @@ int read_ctl(Ctl* d_ctl, Ctl* h_ctl, hipStream_t s);
 
 // Dedup + relabel of one layer (Eq. 2), in two halves around the size read-back.
 //   front: finds every edge's first occurrence in [dst ; col_global] and counts the new vertices.  `m` is the number of
-//          edges, or, when m_dev is given, an upper bound of it known to the host (the exact number is then *m_dev, on
-//          the device, and comes back in the control block's total_edges together with everything else: one read-back
-//          serves the sampler and the dedup).
+//          edges, or, when `sizes` (the control block on the device) is given, an upper bound of it known to the host (the
+//          exact number is then its total_edges, which comes back together with everything else: one read-back serves the
+//          sampler and the dedup).
 //   back:  writes src_ids and col_local.
 extern int g_unique_mode;  // COOP_TUNE_UNIQUE
 // 64 positions of [dst ; col_global]: which are the first occurrence of a new vertex, and how many of those the words in
@@ -227,15 +237,15 @@ int unique_prepare(int64_t n_dst, int64_t m, bool deferred, UniqueWork* w, Alloc
 // launch: every kernel of the front half; one of them sends the sizes to the host; does not wait.  col_local (m entries)
 // holds intermediate results until `back` has run, and so does `spare` (n_dst + m entries, e.g. the array that will be
 // src_ids) when it is not null.
-int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
+int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const Ctl* sizes, int32_t* col_local,
                         int32_t* spare, UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s);
 // finish: waits for the sizes (h_ctl then holds total_edges, total_new and the flags; w->n_new is set).  If the dedup
 // had to be run again (*redone), a relabelling launched in between has to be launched again.
-int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
+int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const Ctl* sizes, int32_t* col_local,
                         UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s, bool* redone);
 // back: writes src_ids (S^l, then the new vertices) and col_local[m]; src must have room for n_dst + (number of new
 // vertices) entries.  May be launched between launch and finish with room for n_dst + m entries.
-int unique_back(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, const UniqueWork& w,
+int unique_back(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const Ctl* sizes, const UniqueWork& w,
                 int32_t* col_local, int32_t* src, hipStream_t s);
 
 }  // namespace coop

@@ -244,19 +244,18 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
       cx.clear = nullptr;
       cx.tags = nullptr;
       if (rc != COOP_OK) break;
-      const int64_t* m_dev = &cx.d_ctl->total_edges;
-      rc = unique_front_launch(dst, n_dst, blk.col_global, edge_cap, m_dev, blk.col_local, src, &uw, alloc, cx.d_ctl, h_ctl, s);
+      rc = unique_front_launch(dst, n_dst, blk.col_global, edge_cap, cx.d_ctl, blk.col_local, src, &uw, alloc, cx.d_ctl, h_ctl, s);
       if (rc != COOP_OK) break;
       // S^{l+1} and local ids (Eq. 2) are queued before the sizes are back, with room for the bound, so that the device
       // is at work while the host waits for the sizes and sets up the next layer
-      rc = unique_back(dst, n_dst, blk.col_global, edge_cap, m_dev, uw, blk.col_local, src, s);
+      rc = unique_back(dst, n_dst, blk.col_global, edge_cap, cx.d_ctl, uw, blk.col_local, src, s);
       if (rc != COOP_OK) break;
-      rc = unique_front_finish(dst, n_dst, blk.col_global, edge_cap, m_dev, blk.col_local, &uw, alloc, cx.d_ctl, h_ctl, s, &redone);
+      rc = unique_front_finish(dst, n_dst, blk.col_global, edge_cap, cx.d_ctl, blk.col_local, &uw, alloc, cx.d_ctl, h_ctl, s, &redone);
       if (rc != COOP_OK) break;
       if (h_ctl->n_overflow > 0) defer_ok = false;  // the counter is never reset: the overflow pass runs from here on
       if (h_ctl->total_edges <= edge_cap && h_ctl->n_overflow == 0 && h_ctl->cand_overflow == 0) {
         blk.n_edges = h_ctl->total_edges;
-        if (redone) rc = unique_back(dst, n_dst, blk.col_global, edge_cap, m_dev, uw, blk.col_local, src, s);
+        if (redone) rc = unique_back(dst, n_dst, blk.col_global, edge_cap, cx.d_ctl, uw, blk.col_local, src, s);
         if (rc != COOP_OK) break;
         done = true;
       } else {

@@ -23,12 +23,12 @@ __device__ __forceinline__ uint64_t slot_of_key(uint32_t key, uint64_t cap) {
   return ((uint64_t)h * cap) >> 32;
 }
 
-// (m_dev, optional: the exact number of edges, on the device; m is then the capacity of col)
+// (sizes, optional: says the exact number of edges, on the device; m is then the capacity of col)
 __global__ __launch_bounds__(kBlock) void k_uniq_insert(const int32_t* __restrict__ dst, int64_t n_dst,
-                                                        const int32_t* __restrict__ col, int64_t m, const int64_t* __restrict__ m_dev,
+                                                        const int32_t* __restrict__ col, int64_t m, const Ctl* __restrict__ sizes,
                                                         unsigned long long* __restrict__ table, uint64_t cap, Ctl* ctl) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  m = edges_there(sizes, m);
   if (i >= n_dst + m) return;
   const uint32_t key = (uint32_t)(i < n_dst ? dst[i] : col[i - n_dst]);
   const unsigned long long mine = ((unsigned long long)key << 32) | (uint32_t)i;
@@ -63,11 +63,11 @@ __device__ __forceinline__ uint32_t first_position(const unsigned long long* __r
 }
 
 // first[e] = first position of col[e] in [S^l ; col]
-__global__ __launch_bounds__(kBlock) void k_uniq_lookup(const int32_t* __restrict__ col, int64_t m, const int64_t* __restrict__ m_dev,
+__global__ __launch_bounds__(kBlock) void k_uniq_lookup(const int32_t* __restrict__ col, int64_t m, const Ctl* __restrict__ sizes,
                                                         const unsigned long long* __restrict__ table, uint64_t cap,
                                                         uint32_t* __restrict__ first) {
   const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  m = edges_there(sizes, m);
   if (e < m) first[e] = first_position(table, cap, (uint32_t)col[e]);
 }
 
@@ -190,7 +190,7 @@ static_assert(kSourceHash == 0x9E3779B9u, "a source's tag is the highest byte of
 
 template <bool TAGS, int SLOTS_LOG2>
 __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
-                                                              const uint8_t* __restrict__ tags, int64_t m, const int64_t* __restrict__ m_dev, int log2_buckets,
+                                                              const uint8_t* __restrict__ tags, int64_t m, const Ctl* __restrict__ sizes, int log2_buckets,
                                                               uint32_t* __restrict__ first, unsigned long long* __restrict__ bits /* or null */,
                                                               Ctl* ctl, Publish pub) {
   constexpr uint32_t kSlots = 1u << SLOTS_LOG2;
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
   __shared__ BucketState st;
   __shared__ uint32_t s_noted, s_overflow;
   __shared__ unsigned long long word[kBits ? kShortWords : 1];  // the block's bits
-  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  m = edges_there(sizes, m);
   const uint32_t n = (uint32_t)(n_dst + m);
   const uint32_t nd = (uint32_t)n_dst;
   const uint32_t n_words = kBits && bits != nullptr ? ((n + 63u) >> 6) - (nd >> 6) : 0u;  // (at most kShortWords)
@@ -413,10 +413,10 @@ __device__ __forceinline__ uint32_t part_column() { return (blockIdx.x & 7u) * (
 
 // counts[b * gridDim.x + column] = pairs of this block's stretch that fall into bucket b
 __global__ __launch_bounds__(kPartBlock) void k_part_count(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
-                                                           int64_t m, const int64_t* __restrict__ m_dev, uint32_t n_buckets,
+                                                           int64_t m, const Ctl* __restrict__ sizes, uint32_t n_buckets,
                                                            uint32_t* __restrict__ counts) {
   extern __shared__ uint32_t tally[];  // [n_buckets]
-  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  m = edges_there(sizes, m);
   int64_t lo, hi;
   part_stretch(n_dst + m, gridDim.x, blockIdx.x, &lo, &hi);
   for (uint32_t b = threadIdx.x; b < n_buckets; b += kPartBlock) tally[b] = 0u;
@@ -455,13 +455,13 @@ struct TileNotes {
 // PER: buckets that a thread looks after.  (64 registers, so that two blocks fit a CU.)
 template <int PER>
 __global__ __launch_bounds__(kPartBlock, PER <= 2 ? 8 : 4) void k_part_scatter(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
-                                                             int64_t m, const int64_t* __restrict__ m_dev, uint32_t n_buckets,
+                                                             int64_t m, const Ctl* __restrict__ sizes, uint32_t n_buckets,
                                                              TiledScan<uint32_t> place, unsigned long long* __restrict__ pairs, TileNotes notes) {
   __shared__ unsigned long long staged[kTilePairs];  // the tile's pairs, by bucket: key, bucket (16 bits), number in the tile (16 bits)
   extern __shared__ uint32_t off[];                  // [n_buckets] the tile's tallies, then run starts in the tile
   uint32_t* delta = off + n_buckets;                 // [n_buckets] run start in pairs[] minus run start in the tile
   __shared__ uint32_t wave_total[kPartBlock / kWave];
-  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  m = edges_there(sizes, m);
   int64_t lo, hi;
   part_stretch(n_dst + m, gridDim.x, blockIdx.x, &lo, &hi);
   const uint32_t column = part_column();
@@ -621,7 +621,7 @@ __global__ __launch_bounds__(kFirstBlock, 8) void k_part_first(const unsigned lo
 template <bool GATHER>
 __global__ __launch_bounds__(kPartBlock, 8) void k_uniq_collect(uint32_t* first, const uint32_t* __restrict__ by_place, int shift,
                                                              TileNotes notes, int64_t m,
-                                                             const int64_t* __restrict__ m_dev, int64_t n_dst, RankWord* __restrict__ words,
+                                                             const Ctl* __restrict__ sizes, int64_t n_dst, RankWord* __restrict__ words,
                                                              uint32_t* __restrict__ block_total,
                                                              uint32_t* __restrict__ block_prefix, Ctl* ctl, Publish pub) {
   constexpr int U = kTilePairs / kPartBlock, kWaves = kPartBlock / kWave, kWords = kTilePairs / 64;
@@ -630,7 +630,7 @@ __global__ __launch_bounds__(kPartBlock, 8) void k_uniq_collect(uint32_t* first,
   __shared__ uint32_t in_order[GATHER ? kTilePairs : 1];
   __shared__ uint32_t count[2][kWords];
   __shared__ uint32_t s_last;
-  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  m = edges_there(sizes, m);
   const int64_t n_all = n_dst + m;
   int64_t lo, hi;
   if constexpr (GATHER) {
@@ -736,15 +736,15 @@ __global__ __launch_bounds__(kPartBlock, 8) void k_uniq_collect(uint32_t* first,
 
 // col_local and the tail of src_ids; the threads of the first n_dst positions also copy S^l to the front of src_ids.
 // col_local holds the first positions and gets the local ids in their place.
-// (m_dev, optional: the exact number of edges, on the device; m is then the capacity of col.  The kernel may be
+// (sizes, optional: says the exact number of edges, on the device; m is then the capacity of col.  The kernel may be
 // launched before the host has seen the dedup's error and overflow flags, on first positions that a failed dedup left
 // partly unwritten: positions outside [0, n_dst + m) are skipped, so that every access stays inside the arrays whatever
 // they are; the caller discards the result in that case.)
 constexpr int kRelabelUnroll = 4;  // edges per thread in flight
 __global__ __launch_bounds__(kBlock) void k_uniq_relabel(const int32_t* __restrict__ dst, const int32_t* __restrict__ col, int64_t m,
-                                                         const int64_t* __restrict__ m_dev, int64_t n_dst, RankView rank,
+                                                         const Ctl* __restrict__ sizes, int64_t n_dst, RankView rank,
                                                          int32_t* __restrict__ src, int32_t* __restrict__ col_local) {
-  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  m = edges_there(sizes, m);
   // the stretch of a word by multiplication: exact while (positions / 1024) * (stretch / 1024) stays below 2^32
   const int64_t stretch = rank.n_blocks ? part_stretch_len(n_dst + m, rank.n_blocks) : kCollectStretch;
   const uint32_t d = (uint32_t)(stretch >> 10), magic = d <= 1 ? 0u : 0xFFFFFFFFu / d + 1u;
@@ -802,7 +802,7 @@ __global__ __launch_bounds__(kBlock) void k_uniq_relabel(const int32_t* __restri
 // shorter (44.9 and 45.7 us, 51.8 and 55.2), below 300 none.
 constexpr int kShortBlock = 1024, kShortEach = 4;
 __global__ __launch_bounds__(kShortBlock) void k_uniq_relabel_short(const int32_t* __restrict__ dst, const int32_t* __restrict__ col, int64_t m,
-                                                                    const int64_t* __restrict__ m_dev, int64_t n_dst,
+                                                                    const Ctl* __restrict__ sizes, int64_t n_dst,
                                                                     const unsigned long long* __restrict__ bits, int32_t* __restrict__ src,
                                                                     int32_t* __restrict__ col_local) {
   constexpr int kEach = (kShortWords + kShortBlock - 1) / kShortBlock;  // words per thread
@@ -810,7 +810,7 @@ __global__ __launch_bounds__(kShortBlock) void k_uniq_relabel_short(const int32_
   __shared__ uint32_t before[kEach * kShortBlock];
   __shared__ uint32_t wave_total[kShortBlock / kWave];
   const int64_t e0 = (int64_t)blockIdx.x * (kShortBlock * kShortEach) + threadIdx.x;
-  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  m = edges_there(sizes, m);
   uint32_t f[kShortEach];
 #pragma unroll
   for (int u = 0; u < kShortEach; ++u) {
@@ -865,7 +865,7 @@ constexpr int64_t kSmallMax = 7936;
 static_assert(kSmallMax <= (int64_t)kSmallBlock * kSmallEach, "a thread has room for its entries");
 template <int U>
 __global__ __launch_bounds__(kSmallBlock) void k_uniq_small(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col, int64_t m,
-                                                            const int64_t* __restrict__ m_dev, int32_t* __restrict__ src, int32_t* __restrict__ col_local,
+                                                            const Ctl* __restrict__ sizes, int32_t* __restrict__ src, int32_t* __restrict__ col_local,
                                                             Ctl* ctl, Publish pub) {
   constexpr uint32_t kSlots = 16384;  // (128 KB of LDS; nobody else wants them)
   static_assert((uint32_t)(U * kSmallBlock) <= kSlots / 4 * 3, "a probe must always reach an empty slot");
@@ -884,7 +884,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_uniq_small(const int32_t* __res
     }
   };
   fetch((uint32_t)(n_dst + m));  // (as many as there is room for: how many there are is on its way)
-  if (m_dev != nullptr && *m_dev < m) m = *m_dev;
+  m = edges_there(sizes, m);
   for (uint32_t i = threadIdx.x; i < kSlots; i += kSmallBlock) table[i] = kEmptySlot;
   if (threadIdx.x == 0) st = BucketState{0u, 0u, 0u};
   __syncthreads();
@@ -928,10 +928,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_uniq_small(const int32_t* __res
       run += c[q];
     }
     if (lane == kWave - 1) {  // the sizes
-      Ctl sizes = *ctl;
-      sizes.total_new = ctl->total_new = incl;
-      if (st.dup) sizes.err_dup = ctl->err_dup = 1;
-      if (pub.h != nullptr) send_ctl(pub.h, pub.ticket, sizes);
+      Ctl c = *ctl;
+      c.total_new = ctl->total_new = incl;
+      if (st.dup) c.err_dup = ctl->err_dup = 1;
+      if (pub.h != nullptr) send_ctl(pub.h, pub.ticket, c);
     }
   }
   __syncthreads();
@@ -962,7 +962,7 @@ int g_unique_mode = 0;  // COOP_TUNE_UNIQUE: 0 automatic, 1 table in HBM, 2 part
 // launches the dedup's kernels up to the one that ranks the new vertices; the sizes are on their way to the host from the
 // kernel that finds the first positions on.  col_local serves as the array of first positions (edge order).
 enum UniqPath { kByFilter, kByPartition, kByTable, kInOneBlock };
-static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
+static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const Ctl* sizes, int32_t* col_local,
                          int32_t* spare, UniqueWork* w, UniqPath path, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
   const int64_t n_all = n_dst + m;
   uint32_t* first = (uint32_t*)col_local;
@@ -976,9 +976,9 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
   w->n_totals = 0;
   if (path == kInOneBlock) {  // (the relabelling too; spare becomes src_ids)
     if (n_all <= 4 * kSmallBlock)
-      COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_small<4>, dim3(1), dim3(kSmallBlock), 0, s, dst, n_dst, col_global, m, m_dev, spare, col_local, d_ctl, w->pub);
+      COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_small<4>, dim3(1), dim3(kSmallBlock), 0, s, dst, n_dst, col_global, m, sizes, spare, col_local, d_ctl, w->pub);
     else
-      COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_small<kSmallEach>, dim3(1), dim3(kSmallBlock), 0, s, dst, n_dst, col_global, m, m_dev, spare, col_local, d_ctl,
+      COOP_LAUNCH(K_UNIQ_FILTER, k_uniq_small<kSmallEach>, dim3(1), dim3(kSmallBlock), 0, s, dst, n_dst, col_global, m, sizes, spare, col_local, d_ctl,
                   w->pub);
     return COOP_OK;
   }
@@ -989,7 +989,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     const uint8_t* tags = w->tagged ? (const uint8_t*)spare : nullptr;
 #define COOP_UNIQ_FILTER(TAGS, SLOTS_LOG2)                                                                                                  \
   COOP_LAUNCH(K_UNIQ_FILTER, (k_uniq_filter<TAGS, SLOTS_LOG2>), dim3(1u << log2_buckets), dim3(kFilterBlock), 0, s, dst, n_dst, col_global, tags, m, \
-              m_dev, log2_buckets, first, bits, d_ctl, w->pub)
+              sizes, log2_buckets, first, bits, d_ctl, w->pub)
     if (tags == nullptr) COOP_UNIQ_FILTER(false, 12);
     else if (n_all < kFilterMax) COOP_UNIQ_FILTER(true, 12);
     else COOP_UNIQ_FILTER(true, 13);
@@ -1009,15 +1009,15 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     uint32_t* firsts = spare ? (uint32_t*)spare : (uint32_t*)pairs;
     shift = spare ? 0 : 1;
     const size_t lds = (size_t)n_buckets * sizeof(uint32_t);
-    COOP_LAUNCH(K_PART_COUNT, k_part_count, dim3(G), dim3(kPartBlock), lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets, counts);
+    COOP_LAUNCH(K_PART_COUNT, k_part_count, dim3(G), dim3(kPartBlock), lds, s, dst, n_dst, col_global, m, sizes, (uint32_t)n_buckets, counts);
     const TiledScan<uint32_t> places = scan_u32_tiled(counts, n_counts, place, tmp, d_ctl, s);
     static_assert(kPartMaxBuckets <= 65536 && kTilePairs <= 65536, "a staged pair has 16 bits for either");
     static_assert(kPartMaxBuckets <= 8 * kPartBlock, "a thread of the scatter looks after eight buckets at most");
     if (n_buckets <= 2 * kPartBlock)
-      COOP_LAUNCH(K_PART_SCATTER, k_part_scatter<2>, dim3(G), dim3(kPartBlock), 2 * lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets,
+      COOP_LAUNCH(K_PART_SCATTER, k_part_scatter<2>, dim3(G), dim3(kPartBlock), 2 * lds, s, dst, n_dst, col_global, m, sizes, (uint32_t)n_buckets,
                   places, pairs, notes);
     else
-      COOP_LAUNCH(K_PART_SCATTER, k_part_scatter<8>, dim3(G), dim3(kPartBlock), 2 * lds, s, dst, n_dst, col_global, m, m_dev, (uint32_t)n_buckets,
+      COOP_LAUNCH(K_PART_SCATTER, k_part_scatter<8>, dim3(G), dim3(kPartBlock), 2 * lds, s, dst, n_dst, col_global, m, sizes, (uint32_t)n_buckets,
                   places, pairs, notes);
     COOP_LAUNCH(K_PART_FIRST, k_part_first, dim3((unsigned)n_buckets), dim3(kFirstBlock), 0, s, pairs, places, G, n_dst, n_all, firsts, shift, d_ctl,
                 w->pub);
@@ -1031,11 +1031,11 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     if (alloc.failed) return COOP_E_NOMEM;
     if (n_all > 0) {
       fill_u64((uint64_t*)table, cap, kEmptySlot, s);
-      COOP_LAUNCH(K_UNIQ_INSERT, k_uniq_insert, dim3(nblocks(n_all)), dim3(kBlock), 0, s, dst, n_dst, col_global, m, m_dev, table, (uint64_t)cap,
+      COOP_LAUNCH(K_UNIQ_INSERT, k_uniq_insert, dim3(nblocks(n_all)), dim3(kBlock), 0, s, dst, n_dst, col_global, m, sizes, table, (uint64_t)cap,
                   d_ctl);
     }
     if (m > 0)
-      COOP_LAUNCH(K_UNIQ_FLAG, k_uniq_lookup, dim3(nblocks(m)), dim3(kBlock), 0, s, col_global, m, m_dev, table, (uint64_t)cap, first);
+      COOP_LAUNCH(K_UNIQ_FLAG, k_uniq_lookup, dim3(nblocks(m)), dim3(kBlock), 0, s, col_global, m, sizes, table, (uint64_t)cap, first);
   }
   if (m > 0 && !(path == kByFilter && w->bits)) {
     uint32_t* totals = alloc.get<uint32_t>(2 * (int64_t)collect_blocks, COOP_TAG_SCRATCH);
@@ -1050,10 +1050,10 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     // (the table in HBM does not count its keys: there the ranks bring the number of new vertices, and the sizes leave with them)
     const Publish pub = path == kByTable ? w->pub : Publish{};
     if (by_place)
-      COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<true>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, shift, notes, m, m_dev, n_dst,
+      COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<true>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, shift, notes, m, sizes, n_dst,
                   w->words, totals, prefix, d_ctl, pub);
     else
-      COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<false>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, shift, notes, m, m_dev, n_dst,
+      COOP_LAUNCH(K_UNIQ_COLLECT, k_uniq_collect<false>, dim3(collect_blocks), dim3(kPartBlock), 0, s, first, by_place, shift, notes, m, sizes, n_dst,
                   w->words, totals, prefix, d_ctl, pub);
   } else if (path == kByTable && launch_publish(w->pub, s) != COOP_OK) {
     return COOP_E_HIP;
@@ -1087,22 +1087,22 @@ int unique_prepare(int64_t n_dst, int64_t m, bool deferred, UniqueWork* w, Alloc
   return COOP_OK;
 }
 
-int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
+int unique_front_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const Ctl* sizes, int32_t* col_local,
                         int32_t* spare, UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
   // (Words that nobody has cleared on the way, the list's length having been unknown, are left to k_uniq_collect: a launch as well,
   // and 2 us less than clearing them here.)
   w->bits = w->n_clear != 0 && w->clear == nullptr;
-  return unique_launch(dst, n_dst, col_global, m, m_dev, col_local, spare, w, (UniqPath)w->path, alloc, d_ctl, h_ctl, s);
+  return unique_launch(dst, n_dst, col_global, m, sizes, col_local, spare, w, (UniqPath)w->path, alloc, d_ctl, h_ctl, s);
 }
 
-int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, int32_t* col_local,
+int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const Ctl* sizes, int32_t* col_local,
                         UniqueWork* w, Alloc& alloc, Ctl* d_ctl, Ctl* h_ctl, hipStream_t s, bool* redone) {
   *redone = false;
   int rc = wait_ctl(w->pub, h_ctl, s);
   if (rc != COOP_OK) return rc;
   if (w->path != kByTable && h_ctl->uniq_overflow != 0) {  // a bucket's table overflowed: once more through the table in HBM
     hipLaunchKernelGGL(k_clear_uniq_overflow, dim3(1), dim3(1), 0, s, d_ctl);
-    rc = unique_launch(dst, n_dst, col_global, m, m_dev, col_local, nullptr, w, kByTable, alloc, d_ctl, h_ctl, s);
+    rc = unique_launch(dst, n_dst, col_global, m, sizes, col_local, nullptr, w, kByTable, alloc, d_ctl, h_ctl, s);
     if (rc != COOP_OK) return rc;
     rc = wait_ctl(w->pub, h_ctl, s);
     if (rc != COOP_OK) return rc;
@@ -1112,16 +1112,16 @@ int unique_front_finish(const int32_t* dst, int64_t n_dst, const int32_t* col_gl
   return COOP_OK;
 }
 
-int unique_back(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const int64_t* m_dev, const UniqueWork& w,
+int unique_back(const int32_t* dst, int64_t n_dst, const int32_t* col_global, int64_t m, const Ctl* sizes, const UniqueWork& w,
                 int32_t* col_local, int32_t* src, hipStream_t s) {
   const int64_t n_threads = m > n_dst ? m : n_dst;
   const RankView rank{w.words, w.block_prefix, w.part_blocks, w.n_totals};
   if (w.path == kInOneBlock) return COOP_OK;
   if (n_threads > 0 && w.path == kByFilter && w.bits)
     COOP_LAUNCH(K_UNIQ_RELABEL, k_uniq_relabel_short, dim3((unsigned)((n_threads + kShortBlock * kShortEach - 1) / (kShortBlock * kShortEach))),
-                dim3(kShortBlock), 0, s, dst, col_global, m, m_dev, n_dst, (const unsigned long long*)w.words, src, col_local);
+                dim3(kShortBlock), 0, s, dst, col_global, m, sizes, n_dst, (const unsigned long long*)w.words, src, col_local);
   else if (n_threads > 0)
-    COOP_LAUNCH(K_UNIQ_RELABEL, k_uniq_relabel, dim3(nblocks((n_threads + kRelabelUnroll - 1) / kRelabelUnroll)), dim3(kBlock), 0, s, dst, col_global, m, m_dev, n_dst, rank, src, col_local);
+    COOP_LAUNCH(K_UNIQ_RELABEL, k_uniq_relabel, dim3(nblocks((n_threads + kRelabelUnroll - 1) / kRelabelUnroll)), dim3(kBlock), 0, s, dst, col_global, m, sizes, n_dst, rank, src, col_local);
   return COOP_OK;
 }
 

@@ -961,6 +961,34 @@ def test_frontier_dedup_by_tags(P, shape):
         compare_rw(P, g, perm[:20000], (2,), 2, 4, 0.5, seed=7)
 
 
+@pytest.mark.parametrize("size", [300, 3000, 20000])
+@pytest.mark.parametrize("kappa", [1, 4])
+def test_dedup_of_a_layer_that_is_sampled_again(P, size, kappa):
+    """A layer whose staging rows overflow (LABOR-0, fanout 64) is sampled again, and some of its edges are never written the first
+    time: what the memory held before must not send their dedup to the table in HBM, or decide anything else."""
+    n = 150000
+    rng = np.random.default_rng(17)
+    deg = rng.integers(60, 120, n)
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]).astype(np.int64))
+    g = G(P, indptr, torch.from_numpy(rng.integers(0, n, int(deg.sum())).astype(np.int32)))
+    arena = P.Arena(1 << 30)
+    seeds = rng.permutation(n)[:size]
+    for pattern in ("numbers", "zeros", "ones"):
+        words = arena.buf.view(torch.int32)
+        if pattern == "numbers":
+            torch.arange(words.numel(), out=words)
+        else:
+            words.fill_(0 if pattern == "zeros" else -1)
+        arena.reset()
+        P.profile_reset()
+        P.profile_enable(True)
+        compare(P, g, seeds, (64,), R.LABOR0, it=1, kappa=kappa, seed=5, arena=arena)
+        P.profile_enable(False)
+        ran = P.profile_read_all()
+        assert ran["segments"][1] == 2, ran["segments"]     # (the layer was sampled again)
+        assert "unique_insert" not in ran, pattern
+
+
 @pytest.mark.parametrize("shape", ["ring", "star", "few"])
 def test_frontier_dedup_in_one_block(P, shape):
     """Lists that one block dedups and relabels (up to 7,936 entries, to both sides of that and of the 4,096 up to which a thread has
