@@ -336,11 +336,10 @@ const char* coop_strerror(int code);
                                       is read back together with |S^{l+1}|; 0: |E^l| is read back first and the arrays have
                                       exactly that size; 2: as 1 with a bound that falls short, so that every layer is redone
                                       (exercises the fallback) */
-#define COOP_TUNE_UNIQUE 7         /* how the frontier is deduplicated.  0 (default): lists of 524,288 entries or more (S^l and
-                                      the sampled edges together; 262,144 where the number of edges is read back first) by
-                                      partition into buckets that are deduplicated in LDS, shorter ones in LDS as well, every
-                                      block picking its bucket's keys from the whole list, or one block taking all of up to
-                                      7,936;
+#define COOP_TUNE_UNIQUE 7         /* how the frontier is deduplicated.  0 (default): lists of 262,144 entries or more (S^l and
+                                      the sampled edges together) by partition into buckets that are deduplicated in LDS,
+                                      shorter ones in LDS as well, every block picking its bucket's keys from the whole list,
+                                      or one block taking all of up to 7,936;
                                       1: always a hash table in HBM; 2: by partition
                                       whatever the length; 3: as 2 with buckets 16 times too large, so that buckets overflow
                                       and the call falls back to the table (exercises the fallback) */

@@ -168,18 +168,19 @@ __device__ __forceinline__ void bucket_done(Ctl* ctl, const BucketState& st, int
 // Reading everything in every block is what it pays for that: ten instructions per key in every block were 12 of the 20 us that a
 // list of 180 thousand entries took.  So it is not the edges' sources that are read but their tags, a byte each (EdgeOut::tag, left by
 // the kernel that wrote the edges): 16 to a load, and fewer than three instructions for each.  180 thousand entries 20.5 -> 14.5 us,
-// 213 thousand 22.5 -> 15.3, 75 thousand 12.4 -> 10.5; calls over 300 to 500 thousand, which went to the partition, 7 to 0 us less.
+// 213 thousand 22.5 -> 15.3, 75 thousand 12.4 -> 10.5.
 constexpr int kFilterBlock = 1024;
-constexpr uint32_t kFilterList = 256;                   // positions that a wave can note (twice that with the larger table)
+constexpr uint32_t kFilterSlots = 4096;
+constexpr uint32_t kFilterFull = kFilterSlots / 4 * 3 - kFilterBlock;  // distinct keys at which a bucket gives up
+constexpr uint32_t kFilterList = 256;                   // positions that a wave can note
 constexpr int64_t kFilterPairs = 1024;                  // most entries of a bucket in the mean (64 per wave) ...
 // ... and at least four buckets: the first wave looks at up to 512 entries of a list of two parts, and with two buckets noted
 // 256 to 270 of them on ordinary lists of 1,500 to 2,048 entries, one more than it can (15 us in the place of 12)
 constexpr int kFilterLeastLog2 = 2;
-constexpr int kFilterMostLog2 = 8;                      // one block per CU, and a tag tells no more buckets apart
-constexpr int64_t kFilterMax = 262144;                  // entries up to which it is used, with tables of 4,096 slots ...
-// ... and with tags, there with 8,192: 495 and 520 thousand entries 84 and 80 us a call, 85 and 80 by partition; 340 thousand 73 and
-// 80; 660 thousand 93 and 89.  (Its 4-byte stores of first positions are scattered over the list, and so are its looks at the keys.)
-constexpr int64_t kFilterTaggedMax = 524288;
+// 256 buckets at most: one per CU, and a tag tells no more apart.  (With tables of 8,192 slots and tags 340 thousand entries took 73 us a
+// call in the place of 80 by partition, 495 thousand 84 and 85; but where every list keeps one vertex 300 thousand took 162 and 132,
+// 520 thousand 247 and 153, all of them from one vertex 458 and 233: the block that has that vertex goes over the whole list.)
+constexpr int64_t kFilterMax = 262144;
 // Shorter lists are read by their keys: a lane's 16 tags are of entries in a row, so that few lanes have all there is to note
 // (1.3 thousand entries 50 us a call, 40 by keys; 11 thousand 41 and 40; 21 thousand 42 either way, 52 thousand 45 and 47).
 constexpr int64_t kFilterTaggedFrom = 16384;
@@ -188,26 +189,22 @@ constexpr int kShortWords = (int)(kShortMax / 64) + 1;
 __device__ __forceinline__ uint32_t filter_hash(uint32_t key) { return key * 0x9E3779B9u; }
 static_assert(kSourceHash == 0x9E3779B9u, "a source's tag is the highest byte of this hash");
 
-template <bool TAGS, int SLOTS_LOG2>
+template <bool TAGS>
 __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __restrict__ dst, int64_t n_dst, const int32_t* __restrict__ col,
                                                               const uint8_t* __restrict__ tags, int64_t m, const Ctl* __restrict__ sizes, int log2_buckets,
                                                               uint32_t* __restrict__ first, unsigned long long* __restrict__ bits /* or null */,
                                                               Ctl* ctl, Publish pub) {
-  constexpr uint32_t kSlots = 1u << SLOTS_LOG2;
-  constexpr uint32_t kFull = kSlots / 4 * 3 - kFilterBlock;  // distinct keys at which a bucket gives up
-  constexpr uint32_t kList = kFilterList << (SLOTS_LOG2 - 12);  // positions that a wave can note
-  constexpr bool kBits = SLOTS_LOG2 == 12;                   // (lists with larger tables are longer than kShortMax)
-  __shared__ unsigned long long table[kSlots];
-  __shared__ uint32_t noted[kFilterBlock / kWave][kList];
+  __shared__ unsigned long long table[kFilterSlots];
+  __shared__ uint32_t noted[kFilterBlock / kWave][kFilterList];
   __shared__ BucketState st;
   __shared__ uint32_t s_noted, s_overflow;
-  __shared__ unsigned long long word[kBits ? kShortWords : 1];  // the block's bits
+  __shared__ unsigned long long word[kShortWords];  // the block's bits
   m = edges_there(sizes, m);
-  const uint32_t n = (uint32_t)(n_dst + m);
+  const uint32_t n = (uint32_t)(n_dst + m);  // (below kFilterMax)
   const uint32_t nd = (uint32_t)n_dst;
-  const uint32_t n_words = kBits && bits != nullptr ? ((n + 63u) >> 6) - (nd >> 6) : 0u;  // (at most kShortWords)
+  const uint32_t n_words = bits != nullptr ? ((n + 63u) >> 6) - (nd >> 6) : 0u;  // (at most kShortWords)
   for (uint32_t i = threadIdx.x; i < n_words; i += kFilterBlock) word[i] = 0;
-  for (uint32_t i = threadIdx.x; i < kSlots; i += kFilterBlock) table[i] = kEmptySlot;
+  for (uint32_t i = threadIdx.x; i < kFilterSlots; i += kFilterBlock) table[i] = kEmptySlot;
   if (threadIdx.x == 0) { st = BucketState{0u, 0u, 0u}; s_noted = 0; s_overflow = 0; }
   __syncthreads();
   auto key_at = [&](uint32_t i) { return (uint32_t)(i < nd ? dst[i] : col[i - nd]); };
@@ -216,10 +213,11 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
   // where a pass that collects the words takes 5.)
   auto found = [&](uint32_t i, uint32_t at) {
     first[i - nd] = at;
-    if (kBits && bits != nullptr && at == i) atomicOr(&word[(i >> 6) - (nd >> 6)], 1ull << (i & 63u));
+    if (bits != nullptr && at == i) atomicOr(&word[(i >> 6) - (nd >> 6)], 1ull << (i & 63u));
   };
   const uint32_t width = 1u << (32 - log2_buckets), low = blockIdx.x * width;  // the bucket's hashes: low .. low + width - 1 (log2_buckets >= 1)
-  auto slot = [&](uint32_t h) { return (h << log2_buckets) >> (32 - SLOTS_LOG2); };  // the hash bits behind those of the bucket
+  auto slot = [&](uint32_t h) { return (h << log2_buckets) >> 20; };           // the hash bits behind those of the bucket
+  static_assert(kFilterSlots == 1u << 12, "slot() takes 12 bits");
   // Each part of the list ([S^l], [col]; 256-byte aligned and padded to that) is read in groups of 16 bytes, a few groups per thread
   // and step, the next step's groups requested before this step's are looked at.  take(flags, entry): those of this lane's keys
   // that are in the bucket, and which entry of the part a flag stands for.
@@ -275,7 +273,7 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
         const bool in = flags != 0 && i < len;
         const uint64_t mask = ballot64(in);
         const uint32_t to = count + lanes_below(mask);
-        if (in && to < kList) list[to] = at0 + i;
+        if (in && to < kFilterList) list[to] = at0 + i;
         count += (uint32_t)__popcll(mask);
         flags &= flags - 1;
       }
@@ -285,12 +283,12 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
   if constexpr (TAGS) by_tag(n - nd, note(n - nd, nd));
   else by_key(col, n - nd, note(n - nd, nd));
   if (lane_id() == 0) {
-    if (count > kList) s_overflow = 1;
+    if (count > kFilterList) s_overflow = 1;
     else atomicAdd(&s_noted, count);
   }
   __syncthreads();
   if (s_overflow == 0) {  // every wave goes on with its own list
-    constexpr int V = kList / kWave;
+    constexpr int V = kFilterList / kWave;
     unsigned long long pair[V];
     uint32_t h[V];
 #pragma unroll
@@ -302,14 +300,14 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
       h[v] = slot(filter_hash(key));
       pair[v] = in ? ((unsigned long long)key << 32) | i : kEmptySlot;
     }
-    const bool fits = s_noted <= kSlots / 4 * 3;  // (the others have their room counted, and seeds that stand there twice reported)
+    const bool fits = s_noted <= kFilterSlots / 4 * 3;  // (the others have their room counted, and seeds that stand there twice reported)
     if (fits) {
-      const uint32_t claimed = wave_sum_u32(bucket_insert_many<V>(table, kSlots, h, pair));
+      const uint32_t claimed = wave_sum_u32(bucket_insert_many<V>(table, kFilterSlots, h, pair));
       if (lane_id() == 0) atomicAdd(&st.claimed, claimed);
     } else {
 #pragma unroll
       for (int v = 0; v < V; ++v)
-        if (pair[v] != kEmptySlot && lds_read(&st.full) == 0) h[v] = bucket_insert(table, kSlots, kFull, h[v], pair[v], nd, &st);
+        if (pair[v] != kEmptySlot && lds_read(&st.full) == 0) h[v] = bucket_insert(table, kFilterSlots, kFilterFull, h[v], pair[v], nd, &st);
     }
     __syncthreads();
 #pragma unroll
@@ -320,27 +318,39 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
       else if (fits && seed_twice(i, at, nd)) st.dup = 1;
     }
   } else {
-    // a vertex that very many lists keep: the whole list is read again, twice, and every key goes straight to the table.
-    auto each = [&](uint32_t len, uint32_t at0, auto&& what) {
-      return [&, len, at0](uint32_t flags, auto&& entry) {
+    // a vertex that very many lists keep: the whole list is read again, twice, by its keys, which go from the registers straight to
+    // the table.  (All of 108 thousand edges from one vertex 135 us; with the edges found by their tags, and a key requested for each,
+    // 188.)
+    constexpr uint32_t U = 4;
+    auto each = [&](const int32_t* __restrict__ p, uint32_t len, auto&& take) {
+      const uint32_t groups = (len + 3) / 4;
+      for (uint32_t g0 = 0; g0 < groups; g0 += U * kFilterBlock) {
+        u32x4 key[U];
+        fetch(p, groups, g0, key);
+        uint32_t flags = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u)
+#pragma unroll
+          for (uint32_t e = 0; e < 4; ++e) flags |= filter_hash(key[u][e]) - low < width ? 1u << (4 * u + e) : 0u;
         for (; flags != 0; flags &= flags - 1) {
-          const uint32_t i = entry((uint32_t)__builtin_ctz(flags));
-          if (i < len) what(at0 + i, key_at(at0 + i));
+          const uint32_t bit = (uint32_t)__builtin_ctz(flags);
+          uint32_t k = 0;
+#pragma unroll
+          for (uint32_t b = 0; b < 4 * U; ++b) k = bit == b ? key[b / 4][b % 4] : k;
+          const uint32_t i = (g0 + (bit >> 2) * kFilterBlock + threadIdx.x) * 4 + (bit & 3u);
+          if (i < len) take(i, k);
         }
-      };
+      }
     };
     auto insert = [&](uint32_t i, uint32_t key) {
-      if (lds_read(&st.full) == 0) bucket_insert(table, kSlots, kFull, slot(filter_hash(key)), ((unsigned long long)key << 32) | i, nd, &st);
+      if (lds_read(&st.full) == 0)
+        bucket_insert(table, kFilterSlots, kFilterFull, slot(filter_hash(key)), ((unsigned long long)key << 32) | i, nd, &st);
     };
-    auto look_up = [&](uint32_t i, uint32_t key) { found(i, bucket_find(table, kSlots, slot(filter_hash(key)), key)); };
-    by_key(dst, nd, each(nd, 0u, insert));
-    if constexpr (TAGS) by_tag(n - nd, each(n - nd, nd, insert));
-    else by_key(col, n - nd, each(n - nd, nd, insert));
+    each(dst, nd, insert);
+    each(col, n - nd, [&](uint32_t i, uint32_t key) { insert(nd + i, key); });
     __syncthreads();
-    if (st.full == 0) {
-      if constexpr (TAGS) by_tag(n - nd, each(n - nd, nd, look_up));
-      else by_key(col, n - nd, each(n - nd, nd, look_up));
-    }
+    if (st.full == 0)
+      each(col, n - nd, [&](uint32_t i, uint32_t key) { found(nd + i, bucket_find(table, kFilterSlots, slot(filter_hash(key)), key)); });
   }
   __syncthreads();
   if (n_words != 0) {
@@ -984,16 +994,11 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
   }
   if (path == kByFilter) {
     int log2_buckets = kFilterLeastLog2;
-    while (log2_buckets < kFilterMostLog2 && (kFilterPairs << log2_buckets) < n_all) ++log2_buckets;
+    while ((kFilterPairs << log2_buckets) < n_all) ++log2_buckets;
     unsigned long long* bits = w->bits ? (unsigned long long*)w->words : (unsigned long long*)nullptr;
     const uint8_t* tags = w->tagged ? (const uint8_t*)spare : nullptr;
-#define COOP_UNIQ_FILTER(TAGS, SLOTS_LOG2)                                                                                                  \
-  COOP_LAUNCH(K_UNIQ_FILTER, (k_uniq_filter<TAGS, SLOTS_LOG2>), dim3(1u << log2_buckets), dim3(kFilterBlock), 0, s, dst, n_dst, col_global, tags, m, \
-              sizes, log2_buckets, first, bits, d_ctl, w->pub)
-    if (tags == nullptr) COOP_UNIQ_FILTER(false, 12);
-    else if (n_all < kFilterMax) COOP_UNIQ_FILTER(true, 12);
-    else COOP_UNIQ_FILTER(true, 13);
-#undef COOP_UNIQ_FILTER
+    COOP_LAUNCH(K_UNIQ_FILTER, (tags != nullptr ? k_uniq_filter<true> : k_uniq_filter<false>), dim3(1u << log2_buckets), dim3(kFilterBlock), 0, s, dst,
+                n_dst, col_global, tags, m, sizes, log2_buckets, first, bits, d_ctl, w->pub);
   } else if (path == kByPartition) {
     const int64_t n_buckets = w->n_buckets;
     const int64_t by_size = (n_all + 4 * kPartBlock - 1) / (4 * kPartBlock);
@@ -1043,7 +1048,7 @@ static int unique_launch(const int32_t* dst, int64_t n_dst, const int32_t* col_g
     // Up to kPartMaxBlocks stretches every block of the relabelling scans their totals for itself, in the place of the block that finishes
     // last here, behind two atomics per block (120 thousand, 1 and 2.4 M entries: this kernel 6.1, 11.3 and 23.0 us -> 4.5, 9.3 and 20.6,
     // the relabelling 18.1 -> 19.3 for the longest).  Only the fallback can have more.
-    static_assert(kFilterTaggedMax <= kCollectStretch * kPartMaxBlocks, "a short list has no more stretches than that");
+    static_assert(kFilterMax <= kCollectStretch * kPartMaxBlocks, "a short list has no more stretches than that");
     w->n_totals = path != kByTable ? (uint32_t)collect_blocks : 0u;
     uint32_t* const prefix = path != kByTable ? nullptr : totals + collect_blocks;
     w->block_prefix = prefix ? prefix : totals;
@@ -1066,7 +1071,7 @@ int unique_prepare(int64_t n_dst, int64_t m, bool deferred, UniqueWork* w, Alloc
   const int64_t n_words = (n_all + 63) / 64 - (n_dst >> 6);
   w->words = alloc.get<RankWord>(n_words, COOP_TAG_SCRATCH);
   if (alloc.failed) return COOP_E_NOMEM;
-  // by partition from filter_max entries on, as long as a block's counters fit LDS
+  // by partition from kFilterMax entries on, as long as a block's counters fit LDS
   const int64_t pairs_per_bucket = g_unique_mode == 3 ? 16 * kPartPairs : kPartPairs;
   w->n_buckets = (n_all + pairs_per_bucket - 1) / pairs_per_bucket;
   // two bucket blocks fit a CU: a last round of a few blocks is spread over the others, which grow by an eighth at most.  (One
@@ -1075,9 +1080,8 @@ int unique_prepare(int64_t n_dst, int64_t m, bool deferred, UniqueWork* w, Alloc
   // three less in the scatter, which has fewer buckets: 7.0 M 40.5 and 43.4.)
   const int64_t whole_rounds = w->n_buckets / 512 * 512;
   if (whole_rounds > 0 && n_all <= whole_rounds * (pairs_per_bucket + pairs_per_bucket / 8)) w->n_buckets = whole_rounds;
-  const int64_t filter_max = deferred ? kFilterTaggedMax : kFilterMax;
-  const bool by_partition = m > 0 && w->n_buckets <= kPartMaxBuckets && g_unique_mode != 1 && (g_unique_mode >= 2 || n_all >= filter_max);
-  const bool by_filter = !by_partition && g_unique_mode != 1 && n_all > 0 && n_all < filter_max;
+  const bool by_partition = m > 0 && w->n_buckets <= kPartMaxBuckets && g_unique_mode != 1 && (g_unique_mode >= 2 || n_all >= kFilterMax);
+  const bool by_filter = !by_partition && g_unique_mode != 1 && n_all > 0 && n_all < kFilterMax;
   w->tagged = deferred && by_filter && n_all >= kFilterTaggedFrom;
   const bool small = deferred && by_filter && n_all <= kSmallMax;
   w->path = by_partition ? kByPartition : small ? kInOneBlock : by_filter ? kByFilter : kByTable;

@@ -930,7 +930,7 @@ def test_frontier_dedup_of_short_lists(P, shape):
 @pytest.mark.parametrize("shape", ["ring", "star", "few", "one_bucket"])
 def test_frontier_dedup_by_tags(P, shape):
     """The same where the blocks read the sources' tags: lists of one entry to both sides of the lengths from which tags are
-    read (16,384), the new vertices are collected (65,536), the tables are larger (262,144) and the partition takes over (524,288);
+    read (16,384), the new vertices are collected (65,536) and the partition takes over (262,144), and longer ones;
     a vertex that every list keeps, a thousand that all lists share, and seeds that share a bucket."""
     n = 300000
     rng = np.random.default_rng(12)
@@ -954,11 +954,51 @@ def test_frontier_dedup_by_tags(P, shape):
         P.profile_enable(False)
         ran = P.profile_read_all()
         assert ("unique_insert" in ran) == (shape == "one_bucket"), (size, ran.keys())
-        assert ("unique_filter" in ran) == (size < 262144), (size, ran.keys())
+        assert ("unique_filter" in ran) == (size < 131072), (size, ran.keys())
     if shape != "one_bucket":
         compare(P, g, perm[:40000], (2,), R.LABOR0, it=1, seed=5)
         compare(P, g, perm[:40000], (2,), R.NS, it=1, kappa=3, seed=6)
         compare_rw(P, g, perm[:20000], (2,), 2, 4, 0.5, seed=7)
+
+
+def dedup_time(P, call, reps=7):
+    """Median over `reps` of the time (ms) that the dedup's kernels take in a call."""
+    call()
+    times = []
+    for _ in range(reps):
+        P.profile_reset()
+        P.profile_enable(True)
+        call()
+        torch.cuda.synchronize()
+        P.profile_enable(False)
+        times.append(sum(ms for name, (ms, _) in P.profile_read_all().items() if name.startswith("unique")))
+    return sorted(times)[reps // 2]
+
+
+@pytest.mark.parametrize("share", [1.0, 0.2])
+@pytest.mark.parametrize("n_all", [270000, 400000, 520000])
+def test_a_vertex_that_every_list_keeps_goes_by_partition(P, n_all, share):
+    """The block that has such a vertex goes over the whole of a short list: from where the partition is used that must not cost more
+    than the partition itself does (at 520 thousand entries it had taken twice as long)."""
+    n = n_all // 6
+    rng = np.random.default_rng(19)
+    lists = rng.integers(0, n, (n, 5)).astype(np.int32)
+    lists[:, :max(1, round(5 * share))] = 7
+    g = G(P, torch.arange(0, 5 * n + 1, 5, dtype=torch.int64), torch.from_numpy(lists.reshape(-1)))
+    arena = P.Arena(256 << 20)
+    seeds = torch.from_numpy(rng.permutation(n).astype(np.int32)).cuda()
+
+    def call():
+        arena.reset()
+        P.coop_sample(g.graph, seeds, (5,), R.NS, seed=1, arena=arena)
+    usual = dedup_time(P, call)
+    P.coop_tune(P.COOP_TUNE_UNIQUE, 2)
+    try:
+        partition = dedup_time(P, call)
+    finally:
+        P.coop_tune(P.COOP_TUNE_UNIQUE, 0)
+    assert usual <= 1.25 * partition, (usual, partition)
+    compare(P, g, seeds.cpu().numpy(), (5,), R.LABOR0, seed=2)
 
 
 @pytest.mark.parametrize("size", [300, 3000, 20000])
