@@ -615,9 +615,15 @@ __global__ __launch_bounds__(kFirstBlock, 8) void k_part_first(const unsigned lo
     }
     __syncthreads();
     if (st.full == 0) {
-      for (uint32_t i = lo + threadIdx.x; i < hi; i += kFirstBlock) {
-        const uint32_t key = (uint32_t)(pairs[i] >> 32);
-        by_place[(size_t)i << shift] = bucket_find(table, kPartSlots, table_slot_of_hash(hash_of_key(key)), key);
+      // (U pairs at a time: with one at a time every load waited for the store before it.  1.7 M pairs of one key 1.61 ms, 1.03 so.)
+      for (uint32_t base = lo; base < hi; base += U * kFirstBlock) {
+        fetch(base);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (mine[u] == kEmptySlot) continue;
+          const uint32_t key = (uint32_t)(mine[u] >> 32);
+          by_place[(size_t)(base + u * kFirstBlock + threadIdx.x) << shift] = bucket_find(table, kPartSlots, table_slot_of_hash(hash_of_key(key)), key);
+        }
       }
     }
   }

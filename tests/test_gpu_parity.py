@@ -998,7 +998,13 @@ def test_a_vertex_that_every_list_keeps_goes_by_partition(P, n_all, share):
     finally:
         P.coop_tune(P.COOP_TUNE_UNIQUE, 0)
     assert usual <= 1.25 * partition, (usual, partition)
-    compare(P, g, seeds.cpu().numpy(), (5,), R.LABOR0, seed=2)
+    for mode in (0, 1):  # (0: the first positions take the place of the pairs)
+        P.coop_tune(P.COOP_TUNE_DEFER_SIZES, mode)
+        try:
+            compare(P, g, seeds.cpu().numpy(), (5,), R.LABOR0, seed=2)
+            compare(P, g, seeds.cpu().numpy()[:n // 3], (5, 5), R.NS, seed=2)
+        finally:
+            P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
 
 
 @pytest.mark.parametrize("size", [300, 3000, 20000])
