@@ -1051,7 +1051,8 @@ __global__ __launch_bounds__(BLOCK) void k_labor_fill_staged(LayerChunks ch, Cou
 template <bool BLEND>
 __global__ __launch_bounds__(kBlock) void k_labor_fill_overflow(const int32_t* __restrict__ g_indices, LayerChunks ch, int64_t first, int64_t n_dst,
                                                                 LayerKeys K, double cw, double sw, uint32_t stage_cap,
-                                                                const int64_t* __restrict__ eptr, EdgeOut edges) {
+                                                                const int64_t* __restrict__ eptr, int32_t* __restrict__ col_global,
+                                                                 int64_t* __restrict__ eid) {
   const int64_t w = first + (int64_t)blockIdx.x * kWavesPerBlock + uniform_wave_in_block();
   if (w >= n_dst) return;
   const int64_t o = eptr[w];
@@ -1061,7 +1062,9 @@ __global__ __launch_bounds__(kBlock) void k_labor_fill_overflow(const int32_t* _
   const Segment g = ch.seg[p][local];
   const uint32_t thr = ch.thr[p][local];
   labor_scan_ordered<BLEND>(g_indices, g.beg, g.d, thr, K, cw, sw, [&](uint32_t rank, int32_t t, uint32_t j) {
-    put_edge(edges, o, rank, t, g.beg + j);
+    // (no tag: this pass comes behind a read-back, and the dedup of such a layer reads keys)
+    col_global[o + rank] = t;
+    eid[o + rank] = g.beg + j;
   });
 }
 
@@ -1388,10 +1391,10 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
         const dim3 grid(blocks_for(n_dst - b < kSliceLists ? n_dst - b : kSliceLists, kWavesPerBlock));
         if (cx.blend)
           COOP_LAUNCH(K_LABOR_OVERFLOW, k_labor_fill_overflow<true>, grid, dim3(kBlock), 0, s, cx.g->indices, ch, b, n_dst, K, cx.cw, cx.sw,
-                      cap, blk->indptr, edges);
+                      cap, blk->indptr, blk->col_global, blk->eid);
         else
           COOP_LAUNCH(K_LABOR_OVERFLOW, k_labor_fill_overflow<false>, grid, dim3(kBlock), 0, s, cx.g->indices, ch, b, n_dst, K, cx.cw, cx.sw,
-                      cap, blk->indptr, edges);
+                      cap, blk->indptr, blk->col_global, blk->eid);
       }
     }
   }
