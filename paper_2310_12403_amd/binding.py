@@ -136,6 +136,20 @@ def _stream_ptr(stream=None):
     return C.c_void_p(s.cuda_stream)
 
 
+# What the binding takes from torch belongs to torch's current stream: for work on another one, torch is told of it, so that the memory is
+# not handed out again before that stream is through with it, however early the last tensor over it goes.
+def _torch_stream(stream):
+    return stream if isinstance(stream, torch.Stream) else torch.cuda.ExternalStream(stream.cuda_stream)
+
+
+def _used_on(stream, *tensors):
+    if stream is not None:
+        s = _torch_stream(stream)
+        for t in tensors:
+            if t is not None:
+                t.record_stream(s)
+
+
 def _dev_ptr(t, dtype):
     assert t.is_cuda and t.dtype == dtype and t.is_contiguous(), (t.device, t.dtype)
     return C.c_void_p(t.data_ptr())
@@ -148,6 +162,11 @@ class Graph:
         self.handle, self.indptr, self.indices = handle, indptr, indices
         self.n_vertices = indptr.numel() - 1
         self.n_edges = indices.numel()
+        self._memory = None     # the allocator with what the library has built on the graph, if it came from torch
+
+    def used_on(self, stream):
+        if self._memory is not None:
+            self._memory.used_on(stream)
 
     def close(self):
         if self.handle:
@@ -167,14 +186,14 @@ def coop_graph_load(indptr, indices, flags=0, stream=None, torch_memory=False):
     allocator through coop_graph_load_with and lives as long as the Graph object."""
     h = C.c_void_p()
     if torch_memory:
-        al = _TorchAllocator(indptr.device)
+        al = _TorchAllocator(indptr.device, stream)
         rc = lib().coop_graph_load_with(_dev_ptr(indptr, torch.int64), _dev_ptr(indices, torch.int32), indptr.numel() - 1,
                                         indices.numel(), flags, al.fn, al.ctx, _stream_ptr(stream), C.byref(h))
         if rc != 0 and al.error is not None:
             raise al.error
         _check(rc)
         g = Graph(h, indptr, indices)
-        g._memory = al          # the tensors behind the handle
+        g._memory = al
         return g
     rc = lib().coop_graph_load(_dev_ptr(indptr, torch.int64), _dev_ptr(indices, torch.int32), indptr.numel() - 1,
                                indices.numel(), flags, _stream_ptr(stream), C.byref(h))
@@ -216,6 +235,8 @@ def _take(ctx, nbytes, tag):
     try:
         al = _live[ctx]()
         t = torch.empty(nbytes + 256, dtype=torch.uint8, device=al.device)
+        if al.stream is not None:
+            _used_on(al.stream, t)
         p = t.data_ptr()
         p += (-p) % 256
         al.tensors[p] = t
@@ -232,11 +253,13 @@ _TAKE_ADDRESS = C.cast(_TAKE, C.c_void_p)
 
 
 class _TorchAllocator:
-    """coop_alloc_fn backed by torch.empty: every buffer is an ordinary torch tensor."""
+    """coop_alloc_fn backed by torch.empty: every buffer is an ordinary torch tensor.  stream: where the work on them goes, if not to
+    torch's current stream."""
     fn_obj = _TAKE
 
-    def __init__(self, device):
+    def __init__(self, device, stream=None):
         self.device = device
+        self.stream = stream
         self.tensors = {}
         self.error = None
         self.key = next(_keys)
@@ -245,6 +268,10 @@ class _TorchAllocator:
 
     def __del__(self, live=_live):  # (at interpreter exit the module's names may be gone)
         live.pop(self.key, None)
+
+    def used_on(self, stream):
+        """Work on what has been taken so far goes to this stream too."""
+        _used_on(stream, *self.tensors.values())
 
     def _address(self):  # what the library is given
         self.fn = _TAKE_ADDRESS
@@ -297,7 +324,9 @@ def coop_sample(graph, seeds, fanouts, sampler, it=0, kappa=1, seed=0, arena=Non
     L = len(fanouts)
     fan = (C.c_int32 * max(L, 1))(*[int(k) for k in fanouts])
     blocks = (_CBlock * max(L, 1))()
-    al = arena if arena is not None else _SampleAllocator(seeds.device)
+    al = arena if arena is not None else _SampleAllocator(seeds.device, stream)
+    if stream is not None:
+        graph.used_on(stream)
     rc = lib().coop_sample(graph.handle, _dev_ptr(seeds, torch.int32), seeds.numel(), fan, L, sampler, it, kappa, seed,
                            al.fn, al.ctx, _stream_ptr(stream), blocks)
     if rc != 0 and getattr(al, "error", None) is not None:
@@ -312,7 +341,9 @@ def coop_sample_rw(graph, seeds, fanouts, walk_length, n_walks, restart_p, it=0,
     L = len(fanouts)
     fan = (C.c_int32 * max(L, 1))(*[int(k) for k in fanouts])
     blocks = (_CBlock * max(L, 1))()
-    al = arena if arena is not None else _SampleAllocator(seeds.device)
+    al = arena if arena is not None else _SampleAllocator(seeds.device, stream)
+    if stream is not None:
+        graph.used_on(stream)
     rc = lib().coop_sample_rw(graph.handle, _dev_ptr(seeds, torch.int32), seeds.numel(), fan, L, int(walk_length), int(n_walks),
                               float(restart_p), it, seed, al.fn, al.ctx, _stream_ptr(stream), blocks)
     if rc != 0 and getattr(al, "error", None) is not None:
@@ -338,10 +369,12 @@ def coop_bucket_by_owner(ids, n_vertices, n_parts, scheme=COOP_OWNER_RANGE, seed
         raise CoopError(-4)
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=ids.device)
+        _used_on(stream, workspace)
     assert workspace.numel() * workspace.element_size() >= need
     out = torch.empty_like(ids)
     origin = torch.empty_like(ids) if want_origin else None
     offsets = torch.empty(n_parts + 1, dtype=torch.int64, device=ids.device)
+    _used_on(stream, out, origin, offsets)
     rc = L.coop_bucket_by_owner(_dev_ptr(ids, torch.int32) if n else None, n, n_vertices, n_parts, scheme, seed,
                                 C.c_void_p(out.data_ptr()) if n else None, C.c_void_p(origin.data_ptr()) if want_origin and n else None,
                                 C.c_void_p(offsets.data_ptr()), C.c_void_p(workspace.data_ptr()),
@@ -362,10 +395,13 @@ def coop_bucket_by_owner_static(ids, n_vertices, n_parts, scheme=COOP_OWNER_RANG
     n = ids.numel()
     if out is None:
         out = torch.empty_like(ids)
+        _used_on(stream, out)
     if origin is None:
         origin = torch.empty_like(ids)
+        _used_on(stream, origin)
     if offsets is None:
         offsets = torch.empty(n_parts + 1, dtype=torch.int64, device=ids.device)
+        _used_on(stream, offsets)
     assert out.numel() >= n and origin.numel() >= n and offsets.numel() >= n_parts + 1
     rc = L.coop_bucket_by_owner_static(_dev_ptr(ids, torch.int32) if n else None, n, n_vertices, n_parts, scheme, seed,
                                        C.c_void_p(out.data_ptr()) if n else None, C.c_void_p(origin.data_ptr()) if n else None,
@@ -378,6 +414,7 @@ def coop_copy_ids(ids, out=None, stream=None):
     """A plain copy of a device int32 list on the stream."""
     if out is None:
         out = torch.empty_like(ids)
+        _used_on(stream, out)
     assert out.numel() == ids.numel()
     _check(lib().coop_copy_ids(_dev_ptr(ids, torch.int32), _dev_ptr(out, torch.int32), ids.numel(), _stream_ptr(stream)))
     return out
@@ -392,6 +429,7 @@ def coop_gather(feat, ids, out=None, stream=None):
     n, dim = feat.shape
     if out is None:
         out = torch.empty((ids.numel(), dim), dtype=feat.dtype, device=ids.device)
+        _used_on(stream, out)
     # `out` may have more rows than there are ids (a buffer sized once and reused): the first ids.numel() rows are written
     assert out.is_contiguous() and out.dtype == feat.dtype and out.dim() == 2 and out.shape[1] == dim and out.shape[0] >= ids.numel()
     rc = lib().coop_gather(C.c_void_p(feat.data_ptr()), n, dim, _DTYPES[feat.dtype], _dev_ptr(ids, torch.int32), ids.numel(),
@@ -407,6 +445,7 @@ def coop_gather_mean(feat, indptr, col_global, out=None, stream=None):
     n_dst = indptr.numel() - 1
     if out is None:
         out = torch.empty((n_dst, dim), dtype=feat.dtype, device=indptr.device)
+        _used_on(stream, out)
     assert out.is_contiguous() and out.dtype == feat.dtype and tuple(out.shape) == (n_dst, dim)
     rc = lib().coop_gather_mean(C.c_void_p(feat.data_ptr()), n, dim, _DTYPES[feat.dtype], _dev_ptr(indptr, torch.int64),
                                 _dev_ptr(col_global, torch.int32), n_dst, C.c_void_p(out.data_ptr()), _stream_ptr(stream))
@@ -429,7 +468,7 @@ class Cache:
     """LRU vertex cache (coop_cache_*).  The backing table may be a cuda tensor or a pinned host tensor."""
 
     def __init__(self, capacity_rows, n_vertices, dim, dtype, max_ids, device="cuda", stream=None):
-        self._alloc = _TorchAllocator(torch.device(device))
+        self._alloc = _TorchAllocator(torch.device(device), stream)
         self.capacity, self.n_vertices, self.dim, self.dtype, self.max_ids = capacity_rows, n_vertices, dim, dtype, max_ids
         h = C.c_void_p()
         rc = lib().coop_cache_create(capacity_rows, n_vertices, dim, _DTYPES[dtype], max_ids, self._alloc.fn, self._alloc.ctx,
@@ -454,6 +493,8 @@ class Cache:
         """Returns (out, n_miss)."""
         if out is None:
             out = torch.empty((ids.numel(), self.dim), dtype=self.dtype, device=ids.device)
+            _used_on(stream, out)
+        self._alloc.used_on(stream)
         n_miss = C.c_int64()
         rc = lib().coop_cache_gather(self.handle, C.c_void_p(self._table_ptr(table)), table.shape[0], _dev_ptr(ids, torch.int32), ids.numel(),
                                      C.c_void_p(out.data_ptr()), C.byref(n_miss), _stream_ptr(stream))
@@ -474,12 +515,15 @@ class Cache:
         v = torch.empty(max(self.capacity, 1), dtype=torch.int32, device=self._alloc.device)
         st = torch.empty(max(self.capacity, 1), dtype=torch.int64, device=self._alloc.device)
         state = _CCacheState()
+        _used_on(stream, v, st)
+        self._alloc.used_on(stream)
         _check(lib().coop_cache_export(self.handle, C.c_void_p(v.data_ptr()), C.c_void_p(st.data_ptr()), C.byref(state),
                                        _stream_ptr(stream)))
         return v[:state.size].clone(), st[:state.size].clone(), (state.size, state.clock, state.base)
 
     def import_state(self, table, vertices, stamps, state, stream=None):
         cs = _CCacheState(*state)
+        self._alloc.used_on(stream)
         _check(lib().coop_cache_import(self.handle, C.c_void_p(self._table_ptr(table)), table.shape[0],
                                        _dev_ptr(vertices, torch.int32), _dev_ptr(stamps, torch.int64), C.byref(cs), _stream_ptr(stream)))
 
