@@ -1286,10 +1286,13 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
       }
       const Clear clear = take_clear(cx);
 #define COOP_SEGMENTS(BLOCK, EACH, SHARED)                                                                                            \
-  COOP_LAUNCH(K_SEGMENTS, (k_segments<BLOCK, SHARED>), dim3(blocks_for(n_new, EACH)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices,  \
-              dst + ps.start, n_new, ps.nf, ks[0], ks[1], ks[2], ks[3], ps.seg, ps.thr, pthr, lim2, cx.cw, cx.sw,                        \
-              cx.d_ctl, cut, pieces, piece_cap, cx.d_piece_count + l, out, enum_degree,    \
-              long_bits, long_tab, long_mask, clear, take_begin(cx, blocks_for(n_new, EACH)), cand_count)
+  do {                                                                                                                                \
+    const Begin begin = take_begin(cx, blocks_for(n_new, EACH));                                                                      \
+    COOP_LAUNCH(K_SEGMENTS, (k_segments<BLOCK, SHARED>), dim3(blocks_for(n_new, EACH)), dim3(BLOCK), 0, s, cx.g->indptr, cx.g->n_vertices,  \
+                dst + ps.start, n_new, ps.nf, ks[0], ks[1], ks[2], ks[3], ps.seg, ps.thr, pthr, lim2, cx.cw, cx.sw,                      \
+                cx.d_ctl, cut, pieces, piece_cap, cx.d_piece_count + l, out, enum_degree,    \
+                long_bits, long_tab, long_mask, clear, begin, cand_count);                                                             \
+  } while (0)
       if (n_new >= kSegWideFrom) COOP_SEGMENTS(1024, 1024, false);
       else if (n_new >= kSegSharedBelow || !cx.blend) COOP_SEGMENTS(256, 256, false);
       else COOP_SEGMENTS(3 * kWave, kWave, true);

@@ -1209,9 +1209,10 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
 #define COOP_NS_COUNT(BLOCK, EACH)                                                                                                             \
   do {                                                                                                                                         \
     tile_log2 = ns_tile_log2(BLOCK * EACH);                                                                                                    \
+    const Begin begin = take_begin(cx, blocks_for(n_dst, BLOCK * EACH));                                                                       \
     COOP_LAUNCH(K_NS_COUNT, (k_ns_count<BLOCK, EACH>), dim3(blocks_for(n_dst, BLOCK * EACH)), dim3(BLOCK), 0, s, cx.g->indptr,                 \
                 cx.g->n_vertices, dst, n_dst, k, target, blk->indptr, rec, bthr, vp.K, cx.cw, cx.sw, cx.d_ctl, long_min, long_list, n_long,    \
-                clear, take_begin(cx, blocks_for(n_dst, BLOCK * EACH)), pub);                                                                  \
+                clear, begin, pub);                                                                                                            \
   } while (0)
   if (n_dst >= kNsCountWideFrom && !cx.blend) COOP_NS_COUNT(1024, 2);
   else if (n_dst >= 16384 || (n_dst > 0 && !cx.blend)) COOP_NS_COUNT(kBlock, 1);

@@ -147,7 +147,21 @@ extern "C" int coop_tune(int knob, int64_t value) {
   }
 }
 
-// Up to how many seeds the first kernel of the call (k_segments, k_ns_count) is one block.
+static void launch_begin(const Begin& b, hipStream_t s) {
+  COOP_LAUNCH(K_COPY_IDS, k_begin_call, dim3(blocks_for(b.n_seeds > kBeginThreads ? b.n_seeds : kBeginThreads, kBlock)), dim3(kBlock), 0, s, b);
+}
+
+Begin coop::take_begin(const SampleCtx& cx, int64_t blocks) {
+  if (cx.begin == nullptr || cx.begin->ctl == nullptr) return Begin{};
+  const Begin b = *cx.begin;
+  cx.begin->ctl = nullptr;
+  if (blocks == 1 && b.n_seeds <= kBeginThreads) return b;
+  launch_begin(b, cx.s);
+  return Begin{};
+}
+
+// Up to how many seeds the first kernel of the call (k_segments, k_ns_count) is one block and begins it.  For more the kernel that does
+// nothing else starts while the host still sets the layer up.  (What this says costs or saves time only: take_begin looks at the kernel.)
 static int64_t first_block_lists(const SampleCtx& cx) { return cx.sampler == COOP_RW ? 0 : cx.blend ? kWave : kBlock; }
 
 static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_seeds, const int32_t* fanouts, int L,
@@ -191,12 +205,10 @@ static int sample_layers(const coop_graph* g, const int32_t* seeds, int64_t n_se
   if (alloc.failed) return COOP_E_NOMEM;
   Begin begin{seeds, seed_copy, n_seeds, cx.d_ctl, cx.d_piece_count, L};
   static_assert(kBeginThreads >= 255, "as many threads as there can be layers");
-  const int64_t first_block = first_block_lists(cx);
-  if (n_seeds > 0 && n_seeds <= first_block) {
-    cx.begin = &begin;
-  } else {
-    const int64_t n_begin = n_seeds > kBeginThreads ? n_seeds : kBeginThreads;
-    COOP_LAUNCH(K_COPY_IDS, k_begin_call, dim3(blocks_for(n_begin, kBlock)), dim3(kBlock), 0, s, begin);
+  cx.begin = &begin;
+  if (n_seeds == 0 || n_seeds > first_block_lists(cx)) {
+    launch_begin(begin, s);
+    begin.ctl = nullptr;
   }
 
   LaborState labor;

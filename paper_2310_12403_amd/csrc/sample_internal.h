@@ -55,7 +55,7 @@ struct SampleCtx {
   double cw, sw;   // cos(c pi/2), sin(c pi/2)
   bool vec4;       // the graph's indices array is 16-byte aligned
   uint8_t* tags = nullptr;      // EdgeOut::tag
-  Begin* begin = nullptr;       // still to be done, by a first kernel of one block (take_begin); null when it has been
+  Begin* begin = nullptr;       // still to be done if its ctl is not null (take_begin)
   UniqueWork* clear = nullptr;  // words that the layer's first kernel is to set to zero, if any (take_clear)
 };
 // The words to clear go to a kernel that is launched anyway, before anything else uses them.
@@ -66,13 +66,9 @@ static inline Clear take_clear(const SampleCtx& cx) {
   cx.clear->clear = nullptr;
   return c;
 }
-// (blocks: those of the kernel about to be launched)
-static inline Begin take_begin(const SampleCtx& cx, int64_t blocks) {
-  if (cx.begin == nullptr || cx.begin->ctl == nullptr || blocks != 1) return Begin{};
-  const Begin b = *cx.begin;
-  cx.begin->ctl = nullptr;
-  return b;
-}
+// For the kernel about to be launched, of so many blocks, which is the first to use what `begin` prepares: it is left to that kernel if it
+// is a single block, and done in front of it otherwise.
+Begin take_begin(const SampleCtx& cx, int64_t blocks);
 #ifdef __HIPCC__
 __device__ __forceinline__ void clear_words(const Clear& c) {  // every thread of the grid
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < c.n; i += (int64_t)gridDim.x * blockDim.x) c.p[i] = 0;
