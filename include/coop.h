@@ -326,9 +326,10 @@ const char* coop_strerror(int code);
 #define COOP_TUNE_FUSE_LAYERS 3    /* 1 (default): a LABOR-0 list is scanned once for all remaining layers, except that a
                                       pass over fewer than 32768 lists covers its own layer only; 2: always fused; 0: never */
 #define COOP_TUNE_PIECE_LEN 4      /* a LABOR-0 list longer than twice this many entries is cut into pieces of about this
-                                      many entries, each scanned by a wave of its own: multiple of 4 in 256..2^24
-                                      (default 4096, and 1024 in passes over fewer than 16,384 lists); 0: lists are
-                                      never cut */
+                                      many entries, each scanned by a wave of its own: multiple of 4 in 256..2^24;
+                                      0: lists are never cut; -1 (default): 4096, and 1024 in passes over fewer than
+                                      16,384 lists as far as the queue of pieces, which is as long as 4096 makes it, has
+                                      room for that */
 #define COOP_TUNE_BLEND_CANDIDATES 5 /* first size (entries) of the buffer that holds the candidates of the exact blend of a
                                       LABOR-0 pass with c > 0; a pass that overflows it is redone with 8 times the size;
                                       0 (default): k / 2 entries per destination and layer plus 65536 */

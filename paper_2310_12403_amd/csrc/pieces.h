@@ -11,8 +11,9 @@
 
 namespace coop {
 
-constexpr int kPieceLen = 4096;  // entries of a piece, unless COOP_TUNE_PIECE_LEN says otherwise ...
-constexpr int kFewPieceLen = 1024;  // ... and in passes over fewer than kFewLists lists
+constexpr int kPieceLenAuto = -1;   // COOP_TUNE_PIECE_LEN: as long as is best, that is ...
+constexpr int kPieceLen = 4096;     // ... so many entries ...
+constexpr int kFewPieceLen = 1024;  // ... and so many in passes over fewer than kFewLists lists
 constexpr int64_t kFewLists = 16384;
 constexpr uint32_t kNoBound = 0xFFFFFFFFu;
 constexpr uint32_t kMostPiecesOfAList = 1u << 20;  // keeps the sum over the 1,024 lists of a block at 2^30
@@ -71,7 +72,7 @@ struct Degrees {
   }
 };
 
-// piece_len, split_set: the knobs (0: never cut, 0: automatic).  room_most: what the caller has room for at most.  *room: entries of
+// piece_len, split_set: the knobs (0: never cut, kPieceLenAuto: automatic; 0: automatic).  room_most: what the caller has room for at most.  *room: entries of
 // the queue, enough for all pieces of distinct destinations (a queue that room_most keeps shorter may leave lists whole).
 //
 // Lists longer than split_min go to the piece waves, which come first in the grid.  With independent variates that is for the
@@ -89,12 +90,13 @@ inline PieceCut cut_pieces(int64_t n_new, const Degrees& g, bool blend, int piec
   PieceCut cut;
   *room = 0;
   if (piece_len == 0 || n_new <= 0) return cut;
-  cut.len = cut.whole_len = (uint32_t)piece_len;
+  const bool automatic = piece_len == kPieceLenAuto;
+  cut.len = cut.whole_len = (uint32_t)(automatic ? kPieceLen : piece_len);
   cut.split_min = split_set != 0 ? (uint32_t)split_set : (blend && cut.len >= 2048u ? 2048u : 2u * cut.len);
   const int64_t room_lists = g.n_edges / (int64_t)cut.split_min + 1;
   const int64_t enough = g.n_edges / (int64_t)cut.len + (n_new < room_lists ? n_new : room_lists) + 1;
   *room = enough < room_most ? enough : room_most;
-  if (n_new < kFewLists && piece_len == kPieceLen && split_set == 0) {
+  if (n_new < kFewLists && automatic && split_set == 0) {
     const PieceCut fine{2 * kFewPieceLen, kFewPieceLen, kPieceLen, kNoBound};
     const int64_t lists = g.longer(n_new, fine.split_min), spare = *room - g.pieces(n_new, fine.split_min, kPieceLen);
     if (g.pieces(n_new, fine.split_min, kFewPieceLen) <= *room) {

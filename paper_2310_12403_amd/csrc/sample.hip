@@ -79,7 +79,7 @@ int read_ctl(Ctl* d_ctl, Ctl* h_ctl, hipStream_t s) {
 int g_stage_cap_override = 0;  // COOP_TUNE_STAGE_CAP
 int g_lists_per_wave = 0;      // COOP_TUNE_LISTS_PER_WAVE (0 = automatic)
 int g_fuse_layers = 1;         // COOP_TUNE_FUSE_LAYERS
-int g_piece_len = kPieceLen;   // COOP_TUNE_PIECE_LEN
+int g_piece_len = kPieceLenAuto;  // COOP_TUNE_PIECE_LEN
 int g_split_min = 0;           // COOP_TUNE_SPLIT_MIN (0 = twice the piece length)
 int64_t g_blend_candidates = 0;  // COOP_TUNE_BLEND_CANDIDATES (0 = automatic)
 int g_defer_sizes = 1;         // COOP_TUNE_DEFER_SIZES
@@ -111,7 +111,7 @@ extern "C" int coop_tune(int knob, int64_t value) {
       g_fuse_layers = (int)value;
       return COOP_OK;
     case COOP_TUNE_PIECE_LEN:
-      if (value != 0 && (value < 256 || value > ((int64_t)1 << 24) || (value & 3))) return COOP_E_ARG;
+      if (value != 0 && value != kPieceLenAuto && (value < 256 || value > ((int64_t)1 << 24) || (value & 3))) return COOP_E_ARG;
       g_piece_len = (int)value;
       return COOP_OK;
     case COOP_TUNE_BLEND_CANDIDATES:

@@ -105,3 +105,11 @@ def test_profile_table():
     names = [L.coop_profile_name(i).decode() for i in range(n)]
     assert len(set(names)) == n and "gather" in names and "labor_scan" in names
     assert L.coop_profile_name(n) is None
+
+
+def test_piece_lengths_that_are_taken():
+    L = P.lib()
+    for value in (0, 256, 260, 4096, 1 << 24, -1):       # (-1, the default: left as it is found)
+        assert L.coop_tune(P.COOP_TUNE_PIECE_LEN, value) == 0, value
+    for value in (-2, -4096, 1, 252, 258, (1 << 24) + 4):
+        assert L.coop_tune(P.COOP_TUNE_PIECE_LEN, value) == -4, value

@@ -20,6 +20,14 @@ def P():
     return P
 
 
+@pytest.fixture(autouse=True)
+def pieces_of_the_default_length(P):
+    """Tests that set COOP_TUNE_PIECE_LEN put 4,096 back, which is not the default: that is what the library finds best for a pass."""
+    P.coop_tune(P.COOP_TUNE_PIECE_LEN, -1)
+    yield
+    P.coop_tune(P.COOP_TUNE_PIECE_LEN, -1)
+
+
 class G:
     def __init__(self, P, indptr, indices, flags=None):
         self.indptr_h = indptr.cpu().numpy()

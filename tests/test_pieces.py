@@ -54,7 +54,7 @@ def rule(tmp_path_factory):
     so = C.CDLL(lib)
     so.queue_of.restype = so.most_pieces.restype = C.c_int64
 
-    def queue_of(graph, taken, census=True, blend=False, piece_len=4096, split_set=0, room_most=1 << 30):
+    def queue_of(graph, taken, census=True, blend=False, piece_len=-1, split_set=0, room_most=1 << 30):
         """graph: all degrees; taken: those of the destinations.  (room, pieces, mean length of the finest cut, longest stretch)"""
         graph, taken = np.ascontiguousarray(graph, dtype=np.int64), np.ascontiguousarray(taken, dtype=np.uint32)
         counts = np.bincount(np.log2(np.maximum(graph[graph > 0], 1)).astype(np.int64), minlength=32).astype(np.int64)
@@ -104,7 +104,7 @@ def test_random_graphs(rule):
         n = int(rng.integers(1, min(size, 16383) + 1))
         taken = rng.permutation(graph)[:n] if case % 2 else np.sort(graph)[::-1][:n]
         blend, census = bool(rng.integers(2)), bool(rng.integers(2))
-        for piece_len, split_set in ((4096, 0), (256, 0), (512, 1000), (4096, 64)):
+        for piece_len, split_set in ((-1, 0), (-1, 500), (4096, 0), (256, 0), (512, 1000), (4096, 64)):
             room, total, _, _ = rule(graph, taken, census, blend, piece_len, split_set)
             assert total <= room, (case, piece_len, split_set)
         counts = np.bincount(np.log2(np.maximum(graph, 1)).astype(np.int64), minlength=32).astype(np.int64)
@@ -131,3 +131,14 @@ def test_what_the_caller_has_room_for(rule):
         room, total, _, _ = rule(graph, np.sort(graph)[::-1][:300], room_most=room_most)
         assert room <= room_most
         assert total <= room or room_most < 1221 + 10   # (fewer entries than pieces of 4,096: lists may stay whole)
+
+
+@pytest.mark.parametrize("blend", [False, True])
+def test_a_length_that_was_asked_for(rule, blend):
+    """4,096 asked for is 4,096 in small passes too, with the queue that belongs to it."""
+    for name, (graph, n) in GRAPHS.items():
+        taken = np.sort(graph)[::-1][:n].astype(np.int64)
+        room, total, _, longest = rule(graph, taken, blend=blend, piece_len=4096)
+        long = taken[taken > (2048 if blend else 8192)]
+        assert total == int((-(-long // 4096)).sum()), name
+        assert total <= room
