@@ -1332,8 +1332,9 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
         launch_scan_plain(ps.nf, blocks, s, cx.g->indices, ps.seg, ps.thr, n_new, deal, keys, cap, out, cx.d_ctl, (int)piece_waves, pieces,
                           pcount, piece_cap);
       if (queued) {  // stage 3: the exact blend for the candidates that the scan appended
-        // (Blocks for an eighth of the kept edges, where a few percent are undecided, at most 16 a sub-buffer; the threads stride, so more
-        // candidates only take longer.  With as many blocks as the buffers have room for, 4,096, a launch over 113 thousand destinations
+        // (Blocks for an eighth of what the first covered layer's fanout keeps in every layer, where a few percent are undecided, at most
+        // 16 a sub-buffer; the threads stride, so more candidates only take longer.  By the sum of the fanouts it is no better: 300 thousand
+        // destinations, fanouts 1 and 25, 25.4 us so and 30.8 with seven times the blocks, 100 thousand and 1, 1, 25 28.8 and 26.6.  With as many blocks as the buffers have room for, 4,096, a launch over 113 thousand destinations
         // and two layers took 19.9 us and one over 463 thousand 19.6, most of it for blocks with nothing to do; now 7.5 and 10.1.)
         const int64_t expected = ((int64_t)ks[0] * n_new * ps.nf) / 8;
         const int64_t each = (expected / kCandSub + kBlock - 1) / kBlock + 1;
