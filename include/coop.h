@@ -321,8 +321,8 @@ const char* coop_strerror(int code);
  */
 #define COOP_TUNE_STAGE_CAP 1
 #define COOP_TUNE_LISTS_PER_WAVE 2 /* neighbour lists handled by one wave of the LABOR-0 scan: 1..64, the next power of two
-                                      being taken (and more in passes over so many lists that a launch had not the threads);
-                                      0 = automatic */
+                                      being taken (a quarter as many of the last lists of a pass, and more in passes over so
+                                      many lists that a launch had not the threads); 0 = automatic */
 #define COOP_TUNE_FUSE_LAYERS 3    /* 1 (default): a LABOR-0 list is scanned once for all remaining layers, except that a
                                       pass over fewer than 32768 lists covers its own layer only; 2: always fused; 0: never */
 #define COOP_TUNE_PIECE_LEN 4      /* a LABOR-0 list longer than twice this many entries is cut into pieces of about this

@@ -269,6 +269,6 @@ struct coop_graph {
     for (; k < 32; ++k) n += census[k];
     return n;
   }
-  coop::Degrees degrees() const { return coop::Degrees{n_edges, have_census ? census : nullptr}; }
+  coop::Degrees degrees() const { return coop::Degrees{n_edges, have_census ? census : nullptr, n_vertices}; }
 };
 constexpr int64_t kLongListDegree = 8192;  // default of COOP_TUNE_ENUM_DEGREE

@@ -1323,7 +1323,7 @@ int labor_layer(LaborState& st, const SampleCtx& cx, int l, const int32_t* dst, 
       if (g_lists_per_wave != 0) while ((1 << each_log2) < g_lists_per_wave) ++each_log2;
       else while (each_log2 < kScanEachLog2 && (n_new >> (each_log2 + 1)) >= kScanWaves) ++each_log2;
       while (each_log2 < 6 && (n_new >> each_log2) > kSliceLists / 2) ++each_log2;  // (no more waves than a launch can have)
-      const Dealing deal = deal_lists(n_new, each_log2);
+      const Dealing deal = deal_lists(n_new, each_log2, g_lists_per_wave != 0 || finer_last(degrees, each_log2, l > 0));
       const unsigned blocks = deal.blocks + (unsigned)piece_waves;
       if (cx.blend)
         launch_scan_blend(ps.nf, blocks, s, cx.g->indices, ps.seg, ps.thr, pthr, lim2, n_new, deal, keys, cap, out, cx.d_ctl, (int)piece_waves,

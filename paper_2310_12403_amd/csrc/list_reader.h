@@ -1,6 +1,7 @@
 // A neighbour list on its way to a wave: what the traversals read (k_ns_fill, k_labor_scan_plain, and blend_scan.h with c > 0).
 #pragma once
 #include "device_utils.h"
+#include "dealing.h"
 #include "variates.h"
 
 namespace coop {
@@ -46,38 +47,5 @@ struct ListReader {
     }
   }
 };
-
-// Block b of n, renumbered so that an XCD (blocks are dealt to the eight in turn) takes runs of 32 neighbouring numbers: what
-// neighbours read, records and offsets, then shares the cache lines of one L2.  (A bijection of 0 .. n - 1.)
-__device__ __forceinline__ uint32_t xcd_runs(uint32_t b, uint32_t n) {
-  const uint32_t whole = n & ~255u;
-  return b < whole ? (b & ~255u) | ((b & 7u) << 5) | ((b >> 3) & 31u) : b;
-}
-
-// How the lists of a pass are dealt to one-wave blocks: neighbouring lists for each, a quarter as many for the last blocks, so that
-// the waves end more nearly together (eight lists are some 35 us of a wave's time on the reddit shape, and without this the number of
-// waves in flight fell for the last 25 us of 132).  The last 16,384 lists, two for each of the 8,192 waves that the chip holds: steps
-// of the reddit shape 647 -> 641 us, papers100M 1,098 -> 1,085, dependent batches 1,034 -> 1,025; with 8,192 lists 643, 1,090 and 1,027,
-// with 32,768 642, 1,083 and 1,026, with 65,536 650 and more, for starting a wave costs as well.
-constexpr int64_t kTailLists = 16384;
-constexpr int kTailShift = 2;
-struct Dealing {
-  uint32_t head, blocks;     // of `blocks` blocks the first `head` take 2^head_log2 lists each, the others 2^tail_log2
-  int head_log2, tail_log2;
-  __device__ __forceinline__ int64_t first_list(uint32_t b, int* each_log2) const {
-    const bool in_head = b < head;
-    *each_log2 = in_head ? head_log2 : tail_log2;
-    const uint32_t at = in_head ? xcd_runs(b, head) : xcd_runs(b - head, blocks - head);
-    return ((int64_t)(in_head ? 0u : head) << head_log2) + ((int64_t)at << *each_log2);
-  }
-};
-inline Dealing deal_lists(int64_t n, int each_log2) {
-  Dealing d{0, 0, each_log2, each_log2 > kTailShift ? each_log2 - kTailShift : 0};
-  const int64_t tail = n / 2 < kTailLists ? n / 2 : kTailLists;
-  d.head = (uint32_t)((n - tail) >> each_log2);
-  const int64_t rest = n - ((int64_t)d.head << each_log2);
-  d.blocks = d.head + (uint32_t)((rest + ((int64_t)1 << d.tail_log2) - 1) >> d.tail_log2);
-  return d;
-}
 
 }  // namespace coop

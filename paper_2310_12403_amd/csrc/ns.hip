@@ -1257,7 +1257,7 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
       const dim3 grid_w(blocks_for(n, kWavesPerBlock));
       int each_log2 = 0;
       while (each_log2 < 3 && (n >> (each_log2 + 1)) >= kNsFillWaves) ++each_log2;
-      const Dealing deal = deal_lists(n, each_log2);
+      const Dealing deal = deal_lists(n, each_log2, finer_last(cx.g->degrees(), each_log2, l > 0));
       const NsRecord* rec_b = rec + b;
       const NsBlendThr* bthr_b = cx.blend ? bthr + b : nullptr;
       const int64_t* eptr_b = blk->indptr + b;

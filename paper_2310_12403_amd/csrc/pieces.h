@@ -46,6 +46,18 @@ COOP_HOST_DEVICE int64_t piece_start(uint32_t d, uint32_t each, uint32_t q, uint
 struct Degrees {
   int64_t n_edges;
   const int64_t* census;
+  int64_t n_vertices = 0;
+  // do most vertices, or, of_edges, most of those that an edge leads to in a graph with every edge both ways, have at least `len` entries
+  // (a power of two)?  Of a graph that nobody looked at: does the mean list?
+  bool most_have(int64_t len, bool of_edges) const {
+    if (census == nullptr) return n_edges >= len * n_vertices;
+    int64_t lists = 0, shorter = 0;
+    for (int k = 0; k < 32; ++k) {
+      if ((int64_t)1 << k >= len) lists += census[k];
+      else shorter += census[k] * ((int64_t)3 << k) / 2;
+    }
+    return of_edges ? 2 * shorter <= n_edges : 2 * lists >= n_vertices;
+  }
   // at most so many of n distinct lists have more than split_min entries ...
   int64_t longer(int64_t n, uint32_t split_min) const {
     int64_t most = n_edges / ((int64_t)split_min + 1);

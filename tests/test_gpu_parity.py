@@ -1114,6 +1114,20 @@ def test_lists_dealt_to_the_last_waves(P, size):
                 P.coop_tune(P.COOP_TUNE_LISTS_PER_WAVE, 0)
 
 
+@pytest.mark.parametrize("size", [65537, 131071, 131073, 140001])
+def test_longer_lists_dealt_to_the_last_waves(P, size):
+    """The same with lists long enough for the last waves to get fewer of them by default (most of at least 64 entries)."""
+    n = 150000
+    rng = np.random.default_rng(23)
+    deg = rng.integers(0, 200, n)
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]).astype(np.int64))
+    g = G(P, indptr, torch.from_numpy(rng.integers(0, n, int(deg.sum())).astype(np.int32)))
+    seeds = rng.permutation(n)[:size]
+    compare(P, g, seeds, (3,), R.NS, seed=size)
+    compare(P, g, seeds, (3,), R.LABOR0, seed=size)
+    compare(P, g, seeds, (3,), R.LABOR0, it=1, kappa=3, seed=size)
+
+
 @pytest.mark.parametrize("size", [36864, 36865, 1048575, 1048576, 1048577])
 def test_offsets_from_sums_of_tiles(P, size):
     """Offsets that the filling kernel's waves find by adding up the sums of the tiles in front of theirs, up to 256 tiles of 4,096
