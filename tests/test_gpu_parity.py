@@ -587,6 +587,39 @@ def test_long_lists_that_are_most_of_a_graph(P, hubs, each, size, census):
         compare(P, g, seeds, (10, 5), R.LABOR0, it=3, kappa=4, seed=31)
 
 
+@pytest.mark.parametrize("lo,hi", [(2500, 5000), (8000, 12000), (2049, 30000)])
+def test_queueing_long_lists_is_cheap(P, lo, hi):
+    """Where nearly all lists of a pass are cut into a few pieces each, queueing them had taken longer than all else that their kernel
+    does.  (Pieces by their lane and by the wave: up to 8, and more.)"""
+    n, size = 8000, 4000
+    rng = np.random.default_rng(hi)
+    deg = rng.integers(lo, hi, n)
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]).astype(np.int64))
+    g = G(P, indptr, torch.from_numpy(rng.integers(0, n, int(deg.sum())).astype(np.int32)))
+    seeds = rng.permutation(n)[:size]
+    arena = P.Arena(256 << 20)
+    seeds_d = torch.from_numpy(seeds.astype(np.int32)).cuda()
+
+    def segments():
+        times = []
+        for i in range(9):
+            arena.reset()
+            P.profile_reset()
+            P.profile_enable(True)
+            P.coop_sample(g.graph, seeds_d, (10,), R.LABOR0, it=i, seed=3, arena=arena)
+            P.profile_enable(False)
+            ms, calls = P.profile_read_all()["segments"]
+            times.append(ms / calls)
+        return sorted(times)[4]
+    cut = segments()
+    P.coop_tune(P.COOP_TUNE_PIECE_LEN, 0)
+    whole = segments()
+    P.coop_tune(P.COOP_TUNE_PIECE_LEN, -1)
+    assert cut <= 1.5 * whole, (cut, whole)
+    for kappa in (1, 4):
+        compare(P, g, seeds[:1000], (10, 3), R.LABOR0, it=kappa - 1, kappa=kappa, seed=3)
+
+
 @pytest.mark.parametrize("split_min,piece_len", [(64, 4096), (200, 512), (1000, 256)])
 def test_labor_lists_handed_to_the_piece_waves_whole(P, tiny, medium, split_min, piece_len):
     """Lists longer than COOP_TUNE_SPLIT_MIN go to the waves that come first in the scan's grid: as a single piece when they
