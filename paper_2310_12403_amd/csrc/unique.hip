@@ -283,8 +283,8 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
   if constexpr (TAGS) by_tag(n - nd, note(n - nd, nd));
   else by_key(col, n - nd, note(n - nd, nd));
   if (lane_id() == 0) {
+    atomicAdd(&s_noted, count);
     if (count > kFilterList) s_overflow = 1;
-    else atomicAdd(&s_noted, count);
   }
   __syncthreads();
   if (s_overflow == 0) {  // every wave goes on with its own list
@@ -318,9 +318,10 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
       else if (fits && seed_twice(i, at, nd)) st.dup = 1;
     }
   } else {
-    // a vertex that very many lists keep: the whole list is read again, twice, by its keys, which go from the registers straight to
-    // the table.  (All of 108 thousand edges from one vertex 135 us; with the edges found by their tags, and a key requested for each,
-    // 188.)
+    // vertices that very many lists keep: the whole list is read again, twice.  Where most of it is the block's, by its keys, which go
+    // from the registers straight to the table; else by its tags, and a key is requested for each that is found.  (235 thousand entries,
+    // a fifth of the edges from one vertex: 150 us by keys, 133 by tags, three tenths 179 and 173, four tenths 205 and 213, all 278 and 386;
+    // 17 thousand and three tenths 24 and 28.  Where edges lead to vertices by a power law, 80 and 130 thousand entries: 39 and 32, 51 and 40.)
     constexpr uint32_t U = 4;
     auto each = [&](const int32_t* __restrict__ p, uint32_t len, auto&& take) {
       const uint32_t groups = (len + 3) / 4;
@@ -346,11 +347,24 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
       if (lds_read(&st.full) == 0)
         bucket_insert(table, kFilterSlots, kFilterFull, slot(filter_hash(key)), ((unsigned long long)key << 32) | i, nd, &st);
     };
+    auto look_up = [&](uint32_t i, uint32_t key) { found(i, bucket_find(table, kFilterSlots, slot(filter_hash(key)), key)); };
+    auto tagged = [&](auto&& what) {
+      return [&](uint32_t flags, auto&& entry) {
+        for (; flags != 0; flags &= flags - 1) {
+          const uint32_t i = entry((uint32_t)__builtin_ctz(flags));
+          if (i < n - nd) what(nd + i, (uint32_t)col[i]);
+        }
+      };
+    };
+    const bool use_tags = TAGS && s_noted <= n / 4;
     each(dst, nd, insert);
-    each(col, n - nd, [&](uint32_t i, uint32_t key) { insert(nd + i, key); });
+    if (use_tags) by_tag(n - nd, tagged(insert));
+    else each(col, n - nd, [&](uint32_t i, uint32_t key) { insert(nd + i, key); });
     __syncthreads();
-    if (st.full == 0)
-      each(col, n - nd, [&](uint32_t i, uint32_t key) { found(nd + i, bucket_find(table, kFilterSlots, slot(filter_hash(key)), key)); });
+    if (st.full == 0) {
+      if (use_tags) by_tag(n - nd, tagged(look_up));
+      else each(col, n - nd, [&](uint32_t i, uint32_t key) { look_up(nd + i, key); });
+    }
   }
   __syncthreads();
   if (n_words != 0) {

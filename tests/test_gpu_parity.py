@@ -1048,6 +1048,37 @@ def test_a_vertex_that_every_list_keeps_goes_by_partition(P, n_all, share):
             P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
 
 
+def times_by_tags_and_by_keys(P, size, share):
+    """Of the dedup of size seeds and 10 * size edges, a share of them from one vertex."""
+    n = 300000
+    rng = np.random.default_rng(29)
+    lists = rng.integers(0, n, (n, 10)).astype(np.int32)
+    lists[rng.random((n, 10)) < share] = 7
+    g = G(P, torch.arange(0, 10 * n + 1, 10, dtype=torch.int64), torch.from_numpy(lists.reshape(-1)))
+    arena = P.Arena(256 << 20)
+    seeds = rng.permutation(n)[:size].astype(np.int32)
+    seeds_d = torch.from_numpy(seeds).cuda()
+
+    def call():
+        arena.reset()
+        P.coop_sample(g.graph, seeds_d, (10,), R.NS, seed=1, arena=arena)
+    tags = dedup_time(P, call)
+    P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 0)
+    keys = dedup_time(P, call)
+    P.coop_tune(P.COOP_TUNE_DEFER_SIZES, 1)
+    compare(P, g, seeds, (10,), R.NS, seed=1)
+    return tags, keys
+
+
+@pytest.mark.parametrize("size", [12000, 23000])
+@pytest.mark.parametrize("share,most", [(0.1, 0.93), (0.2, 0.96), (0.5, 1.1), (1.0, 1.1)])
+def test_second_reading_of_a_short_list(P, size, share, most):
+    """A short list with a vertex that very many lists keep is read again, by whichever is the quicker: its tags while the vertex has
+    less than a quarter of the entries, else its keys (by keys throughout a fifth of the edges had taken a seventh longer)."""
+    tags, keys = times_by_tags_and_by_keys(P, size, share)
+    assert tags <= most * keys, (tags, keys)
+
+
 @pytest.mark.parametrize("size", [300, 3000, 20000])
 @pytest.mark.parametrize("kappa", [1, 4])
 def test_dedup_of_a_layer_that_is_sampled_again(P, size, kappa):
