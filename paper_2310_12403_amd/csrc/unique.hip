@@ -243,23 +243,34 @@ __global__ __launch_bounds__(kFilterBlock) void k_uniq_filter(const int32_t* __r
       take(flags, [&](uint32_t bit) { return (g0 + (bit >> 2) * kFilterBlock + threadIdx.x) * 4 + (bit & 3u); });
     }
   };
+  // (Tags: 16 of them to a load, and a stretch of the part for each wave.  Dealt out load by load, 24 thousand entries left seven waves
+  // with twice as many as the others, and their lists ran out of room that much earlier.)
   auto by_tag = [&](uint32_t len, auto&& take) {
-    constexpr uint32_t U = 2;
-    const uint32_t groups = (len + 15) / 16;
+    constexpr uint32_t U = 2, kWaves = kFilterBlock / kWave;
+    const uint32_t groups = (len + 15) / 16, each = (groups + kWaves - 1) / kWaves;
+    const uint32_t lo = each * (uint32_t)uniform_wave_in_block(), hi = lo + each < groups ? lo + each : groups;
     const uint32_t mask = ((0xFF00u >> log2_buckets) & 0xFFu) * 0x01010101u, mine = (blockIdx.x << (8 - log2_buckets)) * 0x01010101u;
     u32x4 next[U];
-    if (groups > 0) fetch(tags, groups, 0, next);
-    for (uint32_t g0 = 0; g0 < groups; g0 += U * kFilterBlock) {
+    auto request = [&](uint32_t g0) {
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t g = g0 + u * kWave + lane_id();
+        next[u] = reinterpret_cast<const u32x4*>(tags)[g < hi ? g : hi - 1];
+      }
+    };
+    if (lo < hi) request(lo);
+    for (uint32_t g0 = lo; g0 < hi; g0 += U * kWave) {
       uint32_t flags = 0;  // bit 8 b + 7 - q: byte b of word q
 #pragma unroll
       for (uint32_t q = 0; q < 4 * U; ++q) {
         const uint32_t x = (next[q / 4][q % 4] ^ mine) & mask;  // a zero byte: one of the bucket's
-        flags |= ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu) >> q;
+        const uint32_t f = ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu) >> q;
+        flags |= g0 + (q / 4) * kWave + lane_id() < hi ? f : 0u;
       }
-      if (g0 + U * kFilterBlock < groups) fetch(tags, groups, g0 + U * kFilterBlock, next);
+      if (g0 + U * kWave < hi) request(g0 + U * kWave);
       take(flags, [&](uint32_t bit) {
         const uint32_t q = 7u - (bit & 7u);
-        return (g0 + (q >> 2) * kFilterBlock + threadIdx.x) * 16 + (q & 3u) * 4 + (bit >> 3);
+        return (g0 + (q >> 2) * kWave + lane_id()) * 16 + (q & 3u) * 4 + (bit >> 3);
       });
     }
   };

@@ -1079,6 +1079,13 @@ def test_second_reading_of_a_short_list(P, size, share, most):
     assert tags <= most * keys, (tags, keys)
 
 
+@pytest.mark.parametrize("size,share", [(2182, 0.1), (1700, 0.13)])
+def test_tags_are_dealt_evenly(P, size, share):
+    """Lists of little more than 16,384 entries with a vertex that the waves' lists have room for if all of them note as much of it."""
+    tags, keys = times_by_tags_and_by_keys(P, size, share)
+    assert tags <= 0.95 * keys, (tags, keys)
+
+
 @pytest.mark.parametrize("size", [300, 3000, 20000])
 @pytest.mark.parametrize("kappa", [1, 4])
 def test_dedup_of_a_layer_that_is_sampled_again(P, size, kappa):
