@@ -186,9 +186,10 @@ def coop_graph_load(indptr, indices, flags=0, stream=None, torch_memory=False):
     allocator through coop_graph_load_with and lives as long as the Graph object."""
     h = C.c_void_p()
     if torch_memory:
-        al = _TorchAllocator(indptr.device, stream)
+        al = _TorchAllocator(indptr.device)
         rc = lib().coop_graph_load_with(_dev_ptr(indptr, torch.int64), _dev_ptr(indices, torch.int32), indptr.numel() - 1,
                                         indices.numel(), flags, al.fn, al.ctx, _stream_ptr(stream), C.byref(h))
+        al.used_on(stream)
         if rc != 0 and al.error is not None:
             raise al.error
         _check(rc)
@@ -235,8 +236,6 @@ def _take(ctx, nbytes, tag):
     try:
         al = _live[ctx]()
         t = torch.empty(nbytes + 256, dtype=torch.uint8, device=al.device)
-        if al.stream is not None:
-            _used_on(al.stream, t)
         p = t.data_ptr()
         p += (-p) % 256
         al.tensors[p] = t
@@ -253,15 +252,14 @@ _TAKE_ADDRESS = C.cast(_TAKE, C.c_void_p)
 
 
 class _TorchAllocator:
-    """coop_alloc_fn backed by torch.empty: every buffer is an ordinary torch tensor.  stream: where the work on them goes, if not to
-    torch's current stream."""
+    """coop_alloc_fn backed by torch.empty: every buffer is an ordinary torch tensor."""
     fn_obj = _TAKE
 
-    def __init__(self, device, stream=None):
+    def __init__(self, device):
         self.device = device
-        self.stream = stream
         self.tensors = {}
         self.error = None
+        self.streams = {}       # used_on: how many tensors each stream has been told of
         self.key = next(_keys)
         _live[self.key] = weakref.ref(self)
         self._address()
@@ -270,8 +268,10 @@ class _TorchAllocator:
         live.pop(self.key, None)
 
     def used_on(self, stream):
-        """Work on what has been taken so far goes to this stream too."""
-        _used_on(stream, *self.tensors.values())
+        """Work on what has been taken so far goes to this stream too.  (Said once for a stream: torch keeps it with the memory.)"""
+        if stream is not None and self.streams.get(stream.cuda_stream) != len(self.tensors):
+            _used_on(stream, *self.tensors.values())
+            self.streams[stream.cuda_stream] = len(self.tensors)
 
     def _address(self):  # what the library is given
         self.fn = _TAKE_ADDRESS
@@ -287,8 +287,28 @@ class _TorchAllocator:
 
 class _SampleAllocator(_TorchAllocator):
     """The torch allocator for one sampling call: small scratch buffers are cut from chunks by coop_chunk_alloc, since a
-    tensor through this callback takes 3 to 4 us (few_seeds of perf/cases.py, 26 callbacks less: 174 -> 132 us)."""
+    tensor through this callback takes 3 to 4 us (few_seeds of perf/cases.py, 26 callbacks less: 174 -> 132 us).
+    stream: where the call's work goes, if not to torch's current stream.  That work is nearly always done when the last block is
+    dropped, and only if it is not (an event behind the call tells) torch is told of the stream: 3 us a call, where telling torch of
+    every tensor took 60 (24 seeds, two layers: 61 us on torch's current stream)."""
     CHUNK = 1020 << 10  # with the callback's 256 bytes of room for alignment below torch's line for small blocks (1 MB)
+
+    def __init__(self, device, stream=None):
+        self.stream, self.done = stream, None
+        super().__init__(device)
+
+    def called(self):
+        """All of the call's work has been queued."""
+        if self.stream is not None:
+            self.done = _torch_stream(self.stream).record_event()
+
+    def __del__(self):
+        super().__del__()
+        try:
+            if self.stream is not None and not (self.done is not None and self.done.query()):
+                _used_on(self.stream, *self.tensors.values())
+        except Exception:       # (interpreter exit)
+            pass
 
     def _address(self):
         self.chunks = _CChunks(_TAKE, self.key, self.CHUNK, None, 0)
@@ -329,6 +349,8 @@ def coop_sample(graph, seeds, fanouts, sampler, it=0, kappa=1, seed=0, arena=Non
         graph.used_on(stream)
     rc = lib().coop_sample(graph.handle, _dev_ptr(seeds, torch.int32), seeds.numel(), fan, L, sampler, it, kappa, seed,
                            al.fn, al.ctx, _stream_ptr(stream), blocks)
+    if arena is None:
+        al.called()
     if rc != 0 and getattr(al, "error", None) is not None:
         raise al.error
     _check(rc)
@@ -346,6 +368,8 @@ def coop_sample_rw(graph, seeds, fanouts, walk_length, n_walks, restart_p, it=0,
         graph.used_on(stream)
     rc = lib().coop_sample_rw(graph.handle, _dev_ptr(seeds, torch.int32), seeds.numel(), fan, L, int(walk_length), int(n_walks),
                               float(restart_p), it, seed, al.fn, al.ctx, _stream_ptr(stream), blocks)
+    if arena is None:
+        al.called()
     if rc != 0 and getattr(al, "error", None) is not None:
         raise al.error
     _check(rc)
@@ -468,11 +492,12 @@ class Cache:
     """LRU vertex cache (coop_cache_*).  The backing table may be a cuda tensor or a pinned host tensor."""
 
     def __init__(self, capacity_rows, n_vertices, dim, dtype, max_ids, device="cuda", stream=None):
-        self._alloc = _TorchAllocator(torch.device(device), stream)
+        self._alloc = _TorchAllocator(torch.device(device))
         self.capacity, self.n_vertices, self.dim, self.dtype, self.max_ids = capacity_rows, n_vertices, dim, dtype, max_ids
         h = C.c_void_p()
         rc = lib().coop_cache_create(capacity_rows, n_vertices, dim, _DTYPES[dtype], max_ids, self._alloc.fn, self._alloc.ctx,
                                      _stream_ptr(stream), C.byref(h))
+        self._alloc.used_on(stream)
         if rc != 0 and self._alloc.error is not None:
             raise self._alloc.error
         _check(rc)

@@ -26,6 +26,17 @@ class Buffer:
         self.streams.append(stream)
 
 
+class Stream:
+    def __init__(self, idle=True):
+        self.cuda_stream, self.idle = id(self), idle
+
+    def record_event(self):
+        return self
+
+    def query(self):
+        return self.idle
+
+
 @pytest.fixture
 def buffers(monkeypatch):
     Buffer.made = []
@@ -34,21 +45,36 @@ def buffers(monkeypatch):
     return Buffer.made
 
 
-def test_a_callback_tells_torch_of_the_stream(buffers):
-    side = object()
-    for kind in (binding._TorchAllocator, binding._SampleAllocator):
-        del buffers[:]
-        al = kind(torch.device("cpu"), side)
-        assert all(binding._take(al.key, n, 0) for n in (1, 256, 5000))
-        assert [b.streams for b in buffers] == [[side]] * 3
-        other = object()
-        al.used_on(other)       # a later call on memory that outlives the first one (a cache's, a graph's)
-        assert [b.streams[1:] for b in buffers] == [[other]] * 3
-        al.used_on(None)        # (torch's current stream: the memory is that one's)
-        assert all(len(b.streams) == 2 for b in buffers)
-        del buffers[:]
-        al = kind(torch.device("cpu"))
-        assert binding._take(al.key, 256, 0) and buffers[0].streams == []
+@pytest.mark.parametrize("queued,idle", [(True, True), (True, False), (False, True)])
+def test_torch_is_told_of_a_stream_that_is_still_at_work(buffers, queued, idle):
+    """... when the last block of a call goes, or of a call that has failed; not of one that is through with the call."""
+    side = Stream(idle)
+    al = binding._SampleAllocator(torch.device("cpu"), side)
+    assert all(binding._take(al.key, n, 0) for n in (1, 256, 5000))
+    if queued:
+        al.called()
+    assert [b.streams for b in buffers] == [[]] * 3
+    del al
+    assert [b.streams for b in buffers] == [[] if queued and idle else [side]] * 3
+    del buffers[:]
+    al = binding._SampleAllocator(torch.device("cpu"))     # (torch's current stream: the memory is that one's)
+    assert binding._take(al.key, 256, 0)
+    al.called()
+    del al
+    assert [b.streams for b in buffers] == [[]]
+
+
+def test_memory_that_outlives_a_call(buffers):
+    """A cache's, a graph's: every stream is recorded, once for what it has been told of."""
+    al = binding._TorchAllocator(torch.device("cpu"))
+    one, two = Stream(), Stream()
+    assert all(binding._take(al.key, n, 0) for n in (1, 256))
+    for stream in (one, None, one, two, one, two):
+        al.used_on(stream)
+    assert [b.streams for b in buffers] == [[one, two]] * 2
+    assert binding._take(al.key, 4096, 0)
+    al.used_on(two)
+    assert buffers[2].streams == [two]
 
 
 @pytest.mark.gpu
@@ -72,6 +98,8 @@ def test_blocks_dropped_while_the_stream_is_at_work(sampler):
         torch.cuda._sleep(200_000_000)        # (a tenth of a second, or two seconds by a slow clock)
         done = torch.cuda.Event()
         done.record()
+        if blocks[0]._alloc.done is not None:
+            blocks[0]._alloc.done.record()    # (as if the call's own work took that long)
     held = {t.untyped_storage().data_ptr(): t.untyped_storage().nbytes() for t in blocks[0]._alloc.tensors.values()}
     del blocks
     again = [torch.empty(nbytes, dtype=torch.uint8, device="cuda") for nbytes in held.values() for _ in range(2)]
