@@ -31,7 +31,7 @@ struct Dealing {
 inline Dealing deal_lists(int64_t n, int each_log2, bool finer) {
   Dealing d{0, 0, each_log2, each_log2};
   if (finer) d.tail_log2 = each_log2 > kTailShift ? each_log2 - kTailShift : 0;
-  const int64_t tail = n / 2 < kTailLists ? n / 2 : kTailLists;
+  const int64_t tail = d.tail_log2 == each_log2 ? 0 : n / 2 < kTailLists ? n / 2 : kTailLists;
   d.head = (uint32_t)((n - tail) >> each_log2);
   const int64_t rest = n - ((int64_t)d.head << each_log2);
   d.blocks = d.head + (uint32_t)((rest + ((int64_t)1 << d.tail_log2) - 1) >> d.tail_log2);

@@ -21,6 +21,15 @@ extern "C" int64_t blocks_of(int64_t n, int each_log2, int finer, uint8_t* taken
   }
   return d.blocks;
 }
+extern "C" int64_t out_of_place(int64_t n, int each_log2) {
+  const Dealing d = deal_lists(n, each_log2, false);
+  int64_t bad = 0;
+  for (uint32_t b = 0; b < (uint32_t)(n >> each_log2); ++b) {
+    int log2 = 0;
+    bad += d.first_list(b, &log2) != (int64_t)xcd_runs(b, (uint32_t)(n >> each_log2)) << each_log2;
+  }
+  return bad;
+}
 extern "C" int finer(int64_t n_edges, const int64_t* census, int64_t n_vertices, int each_log2, int of_edges) {
   return finer_last(Degrees{n_edges, census, n_vertices}, each_log2, of_edges != 0);
 }
@@ -34,7 +43,7 @@ def lib(tmp_path_factory):
     open(src, "w").write(SHIM)
     subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, src, "-o", out])
     so = C.CDLL(out)
-    so.blocks_of.restype = C.c_int64
+    so.blocks_of.restype = so.out_of_place.restype = C.c_int64
     return so
 
 
@@ -55,6 +64,13 @@ def test_every_list_once(lib, each_log2, finer):
             assert blocks == least, n
         else:
             assert least <= blocks <= least + min(n, 16384 + (1 << each_log2)), n
+
+
+def test_an_even_dealing_is_one_run(lib):
+    """Where no list is dealt finer the neighbours that an XCD takes are those of the whole pass, not of two halves."""
+    for n in sizes():
+        for each_log2 in range(4):
+            assert lib.out_of_place(C.c_int64(n), each_log2) == 0, (n, each_log2)
 
 
 def asked(lib, degrees, each_log2, of_edges, census=True):
