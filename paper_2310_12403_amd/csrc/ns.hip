@@ -610,6 +610,16 @@ __device__ __forceinline__ bool ns_next_bound(uint32_t n_c, uint32_t k, uint32_t
   return true;
 }
 
+// (Pointers that say they do not overlap and no test for a tag: without either, every load waits for the store before it.  10 thousand
+// lists of 900 entries, fanout 1,000: the fill 142 us, 94 so.)
+__device__ __forceinline__ void ns_copy_list(const int32_t* __restrict__ from, uint32_t d, int64_t beg, int32_t* __restrict__ col, int64_t* __restrict__ eid) {
+#pragma unroll 8
+  for (uint32_t j = (uint32_t)lane_id(); j < d; j += kWave) {
+    col[j] = from[j];
+    eid[j] = beg + j;
+  }
+}
+
 // The lists that are kept whole, of a wave's destinations, 64 >> each_log2 lanes and g of each: short ones together, those longer than
 // 4 entries for each of the lanes one after the other by the whole wave.  (Steps over 90 thousand lists of 30 to
 // 1,500 entries 1.99 ms with eight lanes for each, 1.51 so; a thousand lists of a papers100M shape 74 us with a load at a time, 61 with
@@ -629,10 +639,8 @@ __device__ __forceinline__ void ns_copy_whole(const int32_t* __restrict__ g_indi
     const int at = __builtin_ctzll(todo);
     const uint32_t d = of(g.d, at);
     const int64_t beg = of64(g.beg, at), to = of64(o, at);
-#pragma unroll 8
-    for (uint32_t j = lane; j < d; j += kWave) {
-      put_edge(edges, to, j, (g_indices + beg)[j], beg + j);
-    }
+    if (edges.tag == nullptr) ns_copy_list(g_indices + beg, d, beg, edges.col + to, edges.eid + to);
+    else for (uint32_t j = lane; j < d; j += kWave) put_edge(edges, to, j, (g_indices + beg)[j], beg + j);
   }
 }
 

@@ -1185,6 +1185,32 @@ def test_lists_dealt_to_the_last_waves(P, size):
                 P.coop_tune(P.COOP_TUNE_LISTS_PER_WAVE, 0)
 
 
+def test_long_lists_that_ns_keeps_whole(P):
+    """Lists that are copied, eight loads in flight: with a wait between each and the next the copying had taken half as long again.
+    (Beside the same lists inside a group of dependent batches, which a kernel with less LDS copies.)"""
+    n, size, d = 20000, 10000, 900
+    rng = np.random.default_rng(31)
+    g = G(P, torch.arange(0, d * n + 1, d, dtype=torch.int64), torch.from_numpy(rng.integers(0, n, d * n).astype(np.int32)))
+    seeds = rng.permutation(n)[:size]
+    seeds_d = torch.from_numpy(seeds.astype(np.int32)).cuda()
+    arena = P.Arena(1 << 30)
+
+    def fill(kappa):
+        times = []
+        for r in range(9):
+            arena.reset()
+            P.profile_reset()
+            P.profile_enable(True)
+            P.coop_sample(g.graph, seeds_d, (1000,), R.NS, it=r, kappa=kappa, seed=1, arena=arena)
+            P.profile_enable(False)
+            times.append(P.profile_read_all()["ns_fill"][0])
+        return sorted(times)[4]
+    plain, blended = fill(1), fill(4)
+    assert plain <= 2.35 * blended, (plain, blended)
+    for kappa in (1, 4):
+        compare(P, g, seeds[:500], (1000,), R.NS, it=1, kappa=kappa, seed=2)
+
+
 @pytest.mark.parametrize("size", [65537, 131071, 131073, 140001])
 def test_longer_lists_dealt_to_the_last_waves(P, size):
     """The same with lists long enough for the last waves to get fewer of them by default (most of at least 64 entries)."""
