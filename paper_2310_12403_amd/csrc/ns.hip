@@ -1120,7 +1120,7 @@ __global__ __launch_bounds__(kWave, 6) void k_ns_select(const NsRecord* __restri
 template <bool BLEND>
 __global__ __launch_bounds__(kBlock) void k_ns_fill_wide(const int32_t* __restrict__ g_indices, const NsRecord* __restrict__ rec,
                                                          int64_t n_dst, uint32_t k, VariateParams vp, const int64_t* __restrict__ eptr,
-                                                         EdgeOut edges, int64_t edge_limit) {
+                                                         int32_t* __restrict__ col_global, int64_t* __restrict__ eid, int64_t edge_limit) {
   const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + uniform_wave_in_block();
   if (w >= n_dst) return;
   const NsRecord g = rec[w];
@@ -1166,7 +1166,8 @@ __global__ __launch_bounds__(kBlock) void k_ns_fill_wide(const int32_t* __restri
     const uint64_t keep_mask = ballot64(keep);
     if (keep) {
       const uint32_t at = placed + lanes_below(keep_mask);  // below k: exactly k entries are kept
-      put_edge(edges, o, at, t, g.beg + j);
+      col_global[o + at] = t;  // (no tag: the dedup of layers with such fanouts reads keys)
+      eid[o + at] = g.beg + j;
     }
     placed += (uint32_t)__popcll(keep_mask);
     ties += (uint32_t)__popcll(eq_mask);
@@ -1300,9 +1301,9 @@ int ns_layer(const SampleCtx& cx, int l, const int32_t* dst, int64_t n_dst, coop
 #undef COOP_NS_ARGS
       if (k > kNsMaxSelect) {  // the lists longer than such a fanout (the kernels above skip them)
         if (cx.blend) COOP_LAUNCH(K_NS_FILL, k_ns_fill_wide<true>, grid_w, dim3(kBlock), 0, s, cx.g->indices, rec_b, n, k, vp, eptr_b,
-                                  edges, m);
+                                  blk->col_global, blk->eid, m);
         else COOP_LAUNCH(K_NS_FILL, k_ns_fill_wide<false>, grid_w, dim3(kBlock), 0, s, cx.g->indices, rec_b, n, k, vp, eptr_b,
-                         edges, m);
+                         blk->col_global, blk->eid, m);
       }
     }
   }
