@@ -74,8 +74,9 @@ __global__ __launch_bounds__(kBlock) void k_uniq_lookup(const int32_t* __restric
 // ---- a bucket's table in LDS -------------------------------------------------------------------------------------
 // Slots of 8 bytes (key << 32 | position), as in the table in HBM.  The table gives up at `most` distinct keys, with room
 // left for one claim per thread under way, so that a probe always reaches an empty slot.  (The reads are relaxed atomics:
-// volatile ones would become flat loads.  Keys and positions in separate 32-bit arrays, and every try of two or four insertions
-// side by side per thread, were slower: 45 us for the 1,536 buckets of 5.8 M entries in the place of 36.)
+// volatile ones would become flat loads.  Keys and positions in separate 32-bit arrays were slower, and so were two or four insertions
+// per thread that stay side by side until the last of them has its slot: 45 us for the 1,536 buckets of 5.8 M entries in the place of
+// 36.  bucket_insert_many makes only the first tries side by side.)
 struct BucketState { uint32_t claimed, full, dup; };
 __device__ __forceinline__ uint32_t lds_read(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 __device__ __forceinline__ uint32_t bucket_insert(unsigned long long* table, uint32_t slots, uint32_t most, uint32_t h, unsigned long long mine,
@@ -898,8 +899,9 @@ __global__ __launch_bounds__(kShortBlock) void k_uniq_relabel_short(const int32_
 // Everything from the first positions to the local ids, U entries of the list per thread, in one launch in the place of k_uniq_filter
 // and k_uniq_relabel_short: nothing goes through memory in between, no other block is counted, and the table has room for all
 // entries.  Short of that it waits, for memory twice and for LDS a dozen times; from 4,096 entries on the insertions, all on one CU, are
-// what counts (1.3 thousand entries 0.9 us of 4.5, 3.9 thousand 2.2 of 6.0, 10 thousand 9.7 of 16).  Calls over 1.3 and 3.9 thousand
-// entries 5 us shorter than with the two kernels (35.0 -> 30.2, 35.9 -> 30.7), over 6.5 thousand 1, over 7.8 thousand none.
+// what counts (1.3 thousand entries 0.9 us of 4.5, 3.9 thousand 2.2 of 6.0; with room for ten entries per thread, 10 thousand 9.7 of 16).
+// Calls over 1.3 and 3.9 thousand entries 5 us shorter than with the two kernels (35.0 -> 30.2, 35.9 -> 30.7), over 6.5 thousand 1,
+// over 7.8 thousand none: there it ends.
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallEach = 8;
 constexpr int64_t kSmallMax = 7936;
